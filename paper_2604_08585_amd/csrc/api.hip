@@ -91,6 +91,9 @@ static qcf_status need_ws(const void* ws, size_t have, size_t need) {
   return QCF_OK;
 }
 
+// bytes of an optional workspace (one that is missing or misaligned is not used)
+static size_t usable_ws(const void* ws, size_t have) { return ws && aligned16(ws) ? have : 0; }
+
 constexpr int64_t kMaxRows = (int64_t)1 << 30;   // indices are int32
 
 qcf_status check_score_args(const qcf_layer_desc* desc, int32_t B, const void* q_probe,
@@ -252,9 +255,9 @@ qcf_status qcf_recompute_qkv(const qcf_layer_desc* desc, const void* x, int64_t 
   QCF_TRY(opt_ptr(q_out, "q_out"));
   QCF_TRY(opt_ptr(k_out, "k_out"));
   QCF_TRY(opt_ptr(v_out, "v_out"));
-  QCF_TRY(need_ws(workspace, workspace_bytes, qkv_workspace(*desc, M)));
+  QCF_TRY(need_ws(workspace, workspace_bytes, qkv_workspace_needed(*desc, M)));
   return launch_qkv(*desc, x, x_rows, x_gather_dev, M, w_qkv, pos_dev, q_out, k_out, v_out, nullptr, nullptr,
-                    nullptr, 0, workspace, (hipStream_t)stream);
+                    nullptr, 0, workspace, usable_ws(workspace, workspace_bytes), (hipStream_t)stream);
 }
 
 qcf_status qcf_recompute_qkv_scatter(const qcf_layer_desc* desc, const void* x, int64_t x_rows,
@@ -279,9 +282,9 @@ qcf_status qcf_recompute_qkv_scatter(const qcf_layer_desc* desc, const void* x, 
   QCF_TRY(need_idx_ptr(dst_rows_dev, "dst_rows_dev"));
   QCF_TRY(need_ptr(k_fused, "k_fused"));
   QCF_TRY(need_ptr(v_fused, "v_fused"));
-  QCF_TRY(need_ws(workspace, workspace_bytes, qkv_workspace(*desc, M)));
+  QCF_TRY(need_ws(workspace, workspace_bytes, qkv_workspace_needed(*desc, M)));
   return launch_qkv(*desc, x, x_rows, x_gather_dev, M, w_qkv, pos_dev, q_out, k_out, v_out, dst_rows_dev, k_fused,
-                    v_fused, total_rows, workspace, (hipStream_t)stream);
+                    v_fused, total_rows, workspace, usable_ws(workspace, workspace_bytes), (hipStream_t)stream);
 }
 
 // ---- scatter --------------------------------------------------------------------
@@ -362,8 +365,9 @@ qcf_status qcf_linear(const qcf_layer_desc* desc, const void* x, int64_t M, int3
   QCF_TRY(need_ptr(w, "w"));
   QCF_TRY(opt_ptr(residual, "residual"));
   QCF_TRY(need_ptr(out, "out"));
-  QCF_TRY(need_ws(workspace, workspace_bytes, linear_workspace(*desc, M, K, N)));
-  return launch_linear(*desc, x, M, K, w, N, residual, out, workspace, (hipStream_t)stream);
+  QCF_TRY(need_ws(workspace, workspace_bytes, linear_workspace_needed(*desc, M, K, N)));
+  return launch_linear(*desc, x, M, K, w, N, residual, out, workspace, usable_ws(workspace, workspace_bytes),
+                       (hipStream_t)stream);
 }
 
 qcf_status qcf_rmsnorm(const qcf_layer_desc* desc, const void* x, const void* weight, double eps, int64_t M,

@@ -151,31 +151,17 @@ __device__ __forceinline__ void load_to_lds_addr(const void* gptr, void* lds) {
                : "memory");
 }
 
-// The same two forms without the compiler-level memory fence: ordinary LDS accesses may be scheduled
-// across them (for loops that interleave these loads with fragment reads of another stage and order
-// everything with their own waits and barriers).
-// Form 1.
-__device__ __forceinline__ void load_to_lds_nf(const void* base, uint32_t lane_off, void* lds) {
-  const uint32_t lds_addr = __builtin_amdgcn_readfirstlane((int)lds_offset_of(lds));
+// Form 1 without the compiler-level memory fence (ordinary LDS accesses may be scheduled across it: for loops that
+// interleave these loads with fragment reads of another stage and order everything with their own waits and
+// barriers), with the LDS destination as wave-uniform base + constant and M0 left as it is.
+// (M0 is reserved: the compiler sets it right before each use of its own, so it is not restored here.)
+template <int OFF>
+__device__ __forceinline__ void load_to_lds_const(const void* base, uint32_t lane_off, uint32_t lds_base) {
   const uint64_t b = (uint64_t)(uintptr_t)base;
-  // the builtin returns a signed int: widen through uint32_t, or a low half >= 2^31 would smear ones
-  // over the high half of the address
   const uint64_t sb = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32) |
                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-  uint32_t saved_m0;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b32 m0, %0"
-               : "=&s"(saved_m0)
-               : "v"(lane_off), "s"(sb), "s"(lds_addr)
-               :);
-}
-// Form 2.
-__device__ __forceinline__ void load_to_lds_addr_nf(const void* gptr, void* lds) {
-  const uint32_t lds_addr = __builtin_amdgcn_readfirstlane((int)lds_offset_of(lds));
-  uint32_t saved_m0;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
-               : "=&s"(saved_m0)
-               : "v"(gptr), "s"(lds_addr)
-               :);
+  asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :: "v"(lane_off), "s"(sb), "s"(lds_base), "n"(OFF) : "scc");
 }
 
 // ---- launchers (one per translation unit) --------------------------------------
@@ -207,7 +193,7 @@ size_t qkv_workspace(const qcf_layer_desc& L, int64_t M);
 qcf_status launch_qkv(const qcf_layer_desc& L, const void* x, int64_t x_rows, const int32_t* gather,
                       int64_t M, const void* w, const int32_t* pos, void* q, void* k, void* v,
                       const int32_t* dst_rows, void* k_fused, void* v_fused, int64_t fused_rows,
-                      void* ws, hipStream_t st);
+                      void* ws, size_t ws_bytes, hipStream_t st);
 
 qcf_status launch_scatter(const qcf_layer_desc& L, const void* k_new, const void* v_new,
                           const int32_t* rows, int64_t M, void* kf, void* vf, int64_t total_rows,
@@ -225,7 +211,10 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
 
 size_t linear_workspace(const qcf_layer_desc& L, int64_t M, int32_t K, int32_t N);
 qcf_status launch_linear(const qcf_layer_desc& L, const void* x, int64_t M, int32_t K, const void* w, int32_t N,
-                         const void* residual, void* out, void* ws, hipStream_t st);
+                         const void* residual, void* out, void* ws, size_t ws_bytes, hipStream_t st);
+// bytes a call cannot do without (the rest of the workspace only makes it faster)
+size_t qkv_workspace_needed(const qcf_layer_desc& L, int64_t M);
+size_t linear_workspace_needed(const qcf_layer_desc& L, int64_t M, int32_t K, int32_t N);
 qcf_status launch_rmsnorm(const qcf_layer_desc& L, const void* x, const void* weight, double eps, int64_t M,
                           int32_t cols, void* out, hipStream_t st);
 qcf_status launch_swiglu(const qcf_layer_desc& L, const void* gate_up, int64_t M, int32_t F, void* out,

@@ -2,13 +2,12 @@
 // [Q|K|V] = X_sel W_qkv^T, rotary embedding on Q and K at the tokens' absolute positions.
 //
 // The bf16 path is a 32x32x16-MFMA GEMM (both operands are contiguous along the contraction
-// dimension) with a ring of LDS stages; an output tile is 128 columns wide, i.e. whole heads, so
-// the rotary partner of every element is inside the tile and the embedding is applied in the
-// epilogue, which forms the rotation itself: the angle pos * theta_i is taken in turns, with the
-// frequency split in two floats and the product's rounding error recovered by a fused
-// multiply-add (a plain float32 product would be off by 1e-3 rad at 8K positions), reduced to its
-// fraction and handed to the hardware sine and cosine (inputs in turns, errors far below a bf16
-// ulp).  Positions of 2^24 and more take the same steps in float64.
+// dimension) with a ring of LDS stages; a wave's outputs are whole heads, so the rotary partner of
+// every element is in the same lane and the embedding is applied in the epilogue, which forms the
+// rotation itself: the angle pos * theta_i is taken in turns, with the frequency split in two floats
+// and the product's rounding error recovered by a fused multiply-add (a plain float32 product would be
+// off by 1e-3 rad at 8K positions), reduced to its fraction and handed to the hardware sine and cosine
+// (inputs in turns, errors far below a bf16 ulp).
 // The generic path (f32, or shapes the MFMA tiling does not cover) writes the raw product to
 // the workspace and rotates it in a second kernel with a (cos, sin) table built from float64
 // angles by a small table kernel.
@@ -215,9 +214,7 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const T* __restrict__ gate_
 // ------------------------------------------------------------------ MFMA path (bf16)
 
 constexpr int kBK = 64;                  // contraction elements per LDS stage (rows of 128 bytes)
-constexpr int kBN = 128;                 // output columns per workgroup (whole heads)
-constexpr int kCStride = kBN + 8;        // floats per row of the epilogue tile (rows 4 apart: 32 banks apart)
-constexpr int kStages = 3;               // ring of LDS stages filled by asynchronous loads
+constexpr int kBN = 128;                 // columns of an output block: whole heads, or 64 gate + 64 up columns
 constexpr size_t kRhoBytes = 64 * sizeof(float2);   // theta_i / (2 pi) of up to 64 rotary pairs, as (high, low) floats
 
 struct QkvArgs {
@@ -228,77 +225,70 @@ struct QkvArgs {
   double neg2_over_d_log2base;   // theta_i = 2^(i * this)
   int64_t x_rows, M;
   int d_model, H, Hkv, D;
-  int m_tiles, n_tiles;
+  int m_tiles, n_tiles;          // row tiles and 128-column blocks of this launch
+  int n_tile0;                   // first block of this launch
+  int m_group;                   // row tiles walked together (workgroup order of the 256 x 256 kernel)
+  int rows_over_xcds;            // workgroup order of the load/compute-split kernel (see there)
+  int splits, split_len;         // the contraction is cut into `splits` ranges of split_len k-tiles
+  float4* part;                  // their partial sums (splits > 1)
   bf16_t* q;
   bf16_t* k;
   bf16_t* v;
-  // plain linear map (qcf_linear): all H*D columns go to q without rotation; residual (may be NULL) is added
-  int plain;
+  // plain linear map (qcf_linear): all H*D columns go to q without rotation, or with the residual added (kAdd)
   const bf16_t* residual;
+  // gated SiLU: block b holds weight rows 64 b .. +63 (gate) and glu + 64 b .. +63 (up) and gives
+  // 64 output columns
+  int glu;
   // projection fused with the write-back: row m of the K and V tiles also goes to row dst_rows[m] of the fused
   // cache (rows outside [0, fused_rows) are skipped); all null / 0 otherwise
-  int rows_over_xcds;            // workgroup order of the specialised kernel (see there)
   const int32_t* dst_rows;
   bf16_t* k_fused;
   bf16_t* v_fused;
   int64_t fused_rows;
 };
 
-template <int TM, int TN, int WGM, int WGN>
-struct Tile {
-  static constexpr int BM = 32 * TM * WGM;
-  static constexpr int NTHR = 64 * WGM * WGN;
-  static constexpr int NWAVE = WGM * WGN;
-  static constexpr int A_LD = BM / 8 / NWAVE;             // 1 KB load instructions per wave and stage
-  static constexpr int B_LD = kBN / 8 / NWAVE;
-  static constexpr int STAGE = (BM + kBN) * kBK * 2;      // bytes per stage
-  static constexpr size_t LDS_MAIN = (size_t)kStages * STAGE;
-  static constexpr size_t LDS_EPI = (size_t)BM * kCStride * 4;
-  static constexpr size_t RHO = LDS_MAIN > LDS_EPI ? LDS_MAIN : LDS_EPI;      // rotary frequencies (64 doubles) sit behind both
-  static constexpr size_t LDS = RHO + kRhoBytes;
-  static_assert(32 * TN * WGN == kBN, "a workgroup covers 128 output columns");
-  static_assert((BM / 8) % NWAVE == 0 && (kBN / 8) % NWAVE == 0, "load split");
-};
+// What the epilogue does with a block: rotary embedding (half-split pairs of 128- or 64-wide heads, interleaved
+// pairs), nothing, a residual, or the gated SiLU.  A template parameter: with all of them behind branches in one
+// kernel the compiler moves accumulators of the k-loop to scratch.
+enum Epi { kRopeHalf128, kRopeHalf64, kRopeInter, kPlain, kAdd, kGlu };
+constexpr bool is_rope(int epi) { return epi <= kRopeInter; }
 
-// Where a 128-column tile of the fused projection goes.
+// Where a 128-column block of the product goes.
 struct OutTile {
   bf16_t* out;
   bf16_t* fused;          // second destination, addressed through dst_rows (K and V tiles of the fused call)
   int out_cols, out_col0;
   bool rotate;
 };
-__device__ __forceinline__ OutTile out_tile_of(const QkvArgs& a, int col0) {
-  const int q_cols = a.H * a.D, kv_cols = a.Hkv * a.D;
+template <int EPI>
+__device__ __forceinline__ OutTile out_tile_of(const QkvArgs& a, int block) {
   OutTile o;
-  o.rotate = !a.plain;
+  o.rotate = is_rope(EPI);
   o.fused = nullptr;
+  if (EPI == kGlu) {
+    o.out = a.q; o.out_cols = a.glu; o.out_col0 = block * (kBN / 2);
+    return o;
+  }
+  const int col0 = block * kBN;
+  const int q_cols = a.H * a.D, kv_cols = a.Hkv * a.D;
   if (col0 < q_cols) { o.out = a.q; o.out_cols = q_cols; o.out_col0 = col0; }
   else if (col0 < q_cols + kv_cols) { o.out = a.k; o.fused = a.k_fused; o.out_cols = kv_cols; o.out_col0 = col0 - q_cols; }
   else { o.out = a.v; o.fused = a.v_fused; o.out_cols = kv_cols; o.out_col0 = col0 - q_cols - kv_cols; o.rotate = false; }
   return o;
 }
-
-// Epilogue, first half: a wave drops its accumulators (32*TM rows from row_base, 32*TN columns from
-// col_base) into the fp32 tile in LDS.
-template <int TM, int TN>
-__device__ __forceinline__ void acc_to_lds(float* sC, const floatx16 (&acc)[TM][TN], int row_base, int col_base,
-                                           int lane) {
-  const int hf = lane >> 5, l32 = lane & 31;
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int r = row_base + i * 32 + 8 * (v >> 2) + 4 * hf + (v & 3);
-        const int c = col_base + j * 32 + l32;
-        sC[r * kCStride + c] = acc[i][j][v];
-      }
+// first weight row of a 128-column block, and the distance from it to the weight row of column c
+template <int EPI>
+__device__ __forceinline__ int64_t block_w_row(int block) {
+  return (int64_t)block * (EPI == kGlu ? kBN / 2 : kBN);
+}
+template <int EPI>
+__device__ __forceinline__ uint32_t block_w_step(const QkvArgs& a, int c) {
+  return (uint32_t)((EPI == kGlu && c >= kBN / 2) ? a.glu + c - kBN / 2 : c);
 }
 
 // Rotary frequencies in turns per position, theta_i / (2 pi) = 2^(i * c) / (2 pi), for the d/2 pairs of a head:
 // computed in float64 and kept as two floats, high + low (written by 64 threads before the barrier that precedes
-// store_tile).
+// the epilogue).
 __device__ __forceinline__ void fill_rho(const QkvArgs& a, float2* sRho, int i) {
   if (i < a.D / 2) {
     const double rho = exp2(a.neg2_over_d_log2base * (double)i) * 0.15915494309189535;
@@ -306,132 +296,208 @@ __device__ __forceinline__ void fill_rho(const QkvArgs& a, float2* sRho, int i) 
     sRho[i] = make_float2(hi, (float)(rho - (double)hi));
   }
 }
-// (cos, sin) of pos * theta for one pair.  The angle in turns is p * (hi + lo): the product p * hi is rounded, its
-// error is exact in an FMA, and only the fraction of the rounded part matters, so the sum below is good to about
-// 1e-7 of a turn for positions below 2^24 (exactly representable in a float).
-__device__ __forceinline__ void rotary_factor(int32_t pos, float2 rho, float& c, float& sn) {
+// A position as the nearest float and the (integer) rest.
+struct RowPos { float p, rest; };
+__device__ __forceinline__ RowPos row_pos(int32_t pos) {
+  RowPos r;
+  r.p = (float)pos;
+  r.rest = (float)((int64_t)pos - (int64_t)r.p);
+  return r;
+}
+// (cos, sin) of pos * theta for one pair.  The angle in turns is (p + rest) * (hi + lo): the product p * hi is
+// rounded, its error is exact in an FMA, and only the fraction of the rounded part matters, so the sum below is good
+// to about 1e-7 of a turn for positions below 2^24 (rest = 0) and 2e-6 for any 32-bit position.
+__device__ __forceinline__ void rotary_factor(RowPos pos, float2 rho, float& c, float& sn) {
 #pragma clang fp contract(off)          // the rounded product and its error term must stay two operations
-  float fr;
-  if (pos > -(1 << 24) && pos < (1 << 24)) {
-    const float pf = (float)pos;
-    const float t_hi = pf * rho.x;
-    const float t_lo = __builtin_fmaf(pf, rho.y, __builtin_fmaf(pf, rho.x, -t_hi));
-    fr = (t_hi - floorf(t_hi)) + t_lo;
-  } else {
-    const double turns = (double)pos * ((double)rho.x + (double)rho.y);
-    fr = (float)(turns - floor(turns));
-  }
+  const float t_hi = pos.p * rho.x;
+  const float t_lo = __builtin_fmaf(pos.rest, rho.x, __builtin_fmaf(pos.p, rho.y, __builtin_fmaf(pos.p, rho.x, -t_hi)));
+  const float fr = __builtin_amdgcn_fractf(t_hi) + t_lo;
   c = __builtin_amdgcn_cosf(fr);
   sn = __builtin_amdgcn_sinf(fr);
 }
 
-// Epilogue, second half (after a barrier): each thread takes the same 16 columns (8 rotary pairs) of
-// BM*8/NTHR rows.  It first requests the gather indices and rotary factors of all its rows, then rotates
-// and stores two 16-byte vectors per row.
-// Column task tk (0..7) of a 128-column tile: 16 columns = 8 rotary pairs.  e0 / e1: first column of the two
-// 8-column pieces; i0: index of the first pair inside its head.
-template <int STYLE>
-__device__ __forceinline__ void column_task(const QkvArgs& a, int tk, int& e0, int& e1, int& i0) {
-  if (STYLE == 0) {
-    const int per_head = a.D / 16;                     // tasks per head
-    const int hd = tk / per_head;
-    i0 = (tk - hd * per_head) * 8;
-    e0 = hd * a.D + i0;
-    e1 = e0 + a.D / 2;
-  } else {
-    e0 = tk * 16;
-    e1 = e0 + 8;
-    i0 = (e0 % a.D) / 2;
+typedef float float4v __attribute__((ext_vector_type(4)));
+
+// Four consecutive columns of a row in the epilogue's LDS tile: columns 32 j + 8 q + 4 hf .. + 3 of row 32 i + l32.
+// Chunk c (16 bytes) of row r sits in slot c ^ (r % 16): eight-byte pieces of 32 rows and 16-byte pieces of 4 whole
+// rows both touch every bank once.
+__device__ __forceinline__ u32x2* epi_piece(unsigned char* lds, int lane, int i, int j, int q) {
+  const int r = 32 * i + (lane & 31), g = 8 * j + 2 * q + (lane >> 5);
+  return reinterpret_cast<u32x2*>(lds + r * 256 + (((g >> 1) ^ (r & 15)) * 16) + (g & 1) * 8);
+}
+__device__ __forceinline__ void epi_put(unsigned char* lds, int lane, int i, int j, int q, bool zero, float4v o) {
+  const u32x2 t = {cvt_pk_bf16(o[0], o[1]), cvt_pk_bf16(o[2], o[3])};
+  *epi_piece(lds, lane, i, j, q) = zero ? u32x2{0u, 0u} : t;
+}
+
+// What the epilogue needs to know of this lane's rows, requested at the start of the kernel.
+template <int TM>
+struct EpiRows {
+  RowPos pos[TM];
+  bool zero[TM];                       // an index outside x produces a zero row
+};
+template <int TM, int EPI>
+__device__ __forceinline__ void load_epi_rows(const QkvArgs& a, int64_t m0, int lane, EpiRows<TM>& rows) {
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int64_t m = min(m0 + 32 * i + (lane & 31), a.M - 1);
+    const int64_t idx = a.gather ? (int64_t)a.gather[m] : 0;
+    rows.zero[i] = idx < 0 || idx >= a.x_rows;
+    if (is_rope(EPI)) rows.pos[i] = row_pos(a.pos[m]);
   }
 }
 
-template <int BM, int NTHR, int STYLE>
-__device__ __forceinline__ void store_tile(const QkvArgs& a, const float* sC, const float2* sRho, int64_t m0,
-                                           const OutTile& ot, int tid) {
-  constexpr int NT = BM * 8 / NTHR;                    // rows per thread
-  constexpr int RSTEP = NTHR / 8;                      // row distance between a thread's tasks
-  static_assert(BM * 8 % NTHR == 0, "rows per thread");
-  const int tk = tid & 7, r0 = tid >> 3;
-  int e0, e1, i0;
-  column_task<STYLE>(a, tk, e0, e1, i0);
-  bool zero[NT];
-  int32_t posv[NT];
-  int64_t fdst[NT];                                    // row of the fused cache (-1: none)
-  u32x4 w4[NT][2];                                     // the row's 16 residual values
-  float2 rho[8];                                       // frequencies of this thread's 8 pairs, in turns per position
-  if (ot.rotate) {
+// Rotation of the 128 columns held by a wave; the pair of a column is in the same lane.  JP: 32-column blocks of half
+// a head (half-split pairs), or 0: interleaved pairs.
+template <int TM, int JP>
+__device__ __forceinline__ void epi_rotate(floatx16 (&acc)[TM][4], const float2* sRho, unsigned char* lds, int lane, int D,
+                                           const EpiRows<TM>& rows) {
+  const int hf = lane >> 5;
+  if constexpr (JP > 0) {
 #pragma unroll
-    for (int p = 0; p < 8; ++p) rho[p] = sRho[i0 + p];
+    for (int jj = 0; jj < 2; ++jj) {
+      const int j = JP == 2 ? jj : 2 * jj;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float2 rho[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) rho[c] = sRho[32 * (j % JP) + 8 * q + 4 * hf + c];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          float4v o0, o1;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            float wx, wy;
+            rotary_factor(rows.pos[i], rho[c], wx, wy);
+            const float f0 = acc[i][j][4 * q + c], f1 = acc[i][j + JP][4 * q + c];
+            o0[c] = f0 * wx - f1 * wy;
+            o1[c] = f1 * wx + f0 * wy;
+          }
+          epi_put(lds, lane, i, j, q, rows.zero[i], o0);
+          epi_put(lds, lane, i, j + JP, q, rows.zero[i], o1);
+        }
+      }
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int p0 = (((32 * j) & (D - 1)) >> 1) + 4 * q + 2 * hf;
+        const float2 rho0 = sRho[p0], rho1 = sRho[p0 + 1];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          float wx, wy, vx, vy;
+          rotary_factor(rows.pos[i], rho0, wx, wy);
+          rotary_factor(rows.pos[i], rho1, vx, vy);
+          const float f0 = acc[i][j][4 * q], f1 = acc[i][j][4 * q + 1], f2 = acc[i][j][4 * q + 2], f3 = acc[i][j][4 * q + 3];
+          epi_put(lds, lane, i, j, q, rows.zero[i], float4v{f0 * wx - f1 * wy, f1 * wx + f0 * wy, f2 * vx - f3 * vy, f3 * vx + f2 * vy});
+        }
+      }
   }
+}
+
+// Epilogue of a wave that holds 32*TM rows x 128 columns of the product: acc[i][j] register v of a lane is row
+// 32 i + lane%32, column 32 j + 8 (v / 4) + 4 (lane / 32) + v % 4 (weights as the A operand, activations as B).
+// The rotary partner of a column, or the gate of an up column, is then in the same lane, and a lane needs the
+// position of one row per 32.  The wave works alone in 32*TM * 256 bytes of LDS: residual rows come in through it
+// with 16-byte loads, results are rounded to bf16 and leave through it with 16-byte stores.
+// (With the tile going through LDS as fp32 for the whole workgroup, 128 columns at a time, a 256 x 256 tile spent
+// about 20 us behind its last k-tile; now about 8.)
+template <int TM, int EPI>
+__device__ __forceinline__ void wave_epilogue(const QkvArgs& a, const OutTile& ot, floatx16 (&acc)[TM][4],
+                                              const float2* sRho, unsigned char* lds, int64_t m0, int lane,
+                                              const EpiRows<TM>& rows) {
+  if constexpr (EPI == kAdd) {
+    const int ch = lane & 15, rq = lane >> 4;
+    const bf16_t* res = a.residual + ot.out_col0 + ch * 8;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int64_t m = m0 + r0 + t * RSTEP;
-    zero[t] = false;
-    posv[t] = 0;
-    fdst[t] = -1;
-    if (m < a.M) {
-      if (ot.fused) {
-        const int64_t d = a.dst_rows[m];
-        if (d >= 0 && d < a.fused_rows) fdst[t] = d;
+    for (int b = 0; b < TM; ++b) {
+      __builtin_amdgcn_sched_barrier(0);
+      u32x4 t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int64_t m = min(m0 + 32 * b + 4 * u + rq, a.M - 1);      // (no branches while the accumulators are live)
+        t[u] = *reinterpret_cast<const u32x4*>(res + m * ot.out_cols);
       }
-      if (a.gather) {                                  // an index outside x produces a zero row
-        const int64_t idx = a.gather[m];
-        zero[t] = idx < 0 || idx >= a.x_rows;
-      }
-      if (ot.rotate) {
-        posv[t] = a.pos[m];
-      } else if (a.residual) {
-        const bf16_t* res = a.residual + m * ot.out_cols + ot.out_col0;
-        w4[t][0] = *reinterpret_cast<const u32x4*>(res + e0);
-        w4[t][1] = *reinterpret_cast<const u32x4*>(res + e1);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int r = 32 * b + 4 * u + rq;
+        *reinterpret_cast<u32x4*>(lds + r * 256 + ((ch ^ (r & 15)) * 16)) = t[u];
       }
     }
   }
+  if constexpr (EPI == kGlu) {
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int r = r0 + t * RSTEP;
-    const int64_t m = m0 + r;
-    if (m >= a.M) continue;
-    float f[16], o[16];
-    const float* row = sC + r * kCStride;
-    {
-      const u32x4 c0 = *reinterpret_cast<const u32x4*>(row + e0), c1 = *reinterpret_cast<const u32x4*>(row + e0 + 4);
-      const u32x4 c2 = *reinterpret_cast<const u32x4*>(row + e1), c3 = *reinterpret_cast<const u32x4*>(row + e1 + 4);
-      Vec16<float>::unpack(c0, f); Vec16<float>::unpack(c1, f + 4);
-      Vec16<float>::unpack(c2, f + 8); Vec16<float>::unpack(c3, f + 12);
-    }
-    if (zero[t]) {
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int p = 0; p < 16; ++p) f[p] = 0.f;
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float4v o;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {          // gate and up are rounded to bf16 first, as the separate calls store them
+            const float g = bf16_to_f32(f32_to_bf16(acc[i][j][4 * q + c])), u = bf16_to_f32(f32_to_bf16(acc[i][j + 2][4 * q + c]));
+            o[c] = g / (1.f + __expf(-g)) * u;
+          }
+          epi_put(lds, lane, i, j, q, rows.zero[i], o);
+        }
+    const int ch = lane & 7, rq = lane >> 3;     // 64 columns: eight rows per store
+    bf16_t* dst = ot.out + ot.out_col0 + ch * 8;
+#pragma unroll
+    for (int u = 0; u < 4 * TM; ++u) {
+      const int r = 8 * u + rq;
+      const int64_t m = m0 + r;
+      if (m < a.M) *reinterpret_cast<u32x4*>(dst + m * ot.out_cols) = *reinterpret_cast<const u32x4*>(lds + r * 256 + ((ch ^ (r & 15)) * 16));
     }
+    return;
+  }
+  bool rotated = false;
+  if constexpr (is_rope(EPI)) {
     if (ot.rotate) {
-#pragma unroll
-      for (int p = 0; p < 8; ++p) {
-        float wx, wy;
-        rotary_factor(posv[t], rho[p], wx, wy);
-        const int ia = (STYLE == 0) ? p : 2 * p;
-        const int ib = (STYLE == 0) ? p + 8 : 2 * p + 1;
-        o[ia] = f[ia] * wx - f[ib] * wy;
-        o[ib] = f[ib] * wx + f[ia] * wy;
-      }
-    } else if (a.residual) {
-      float res[16];
-      Vec16<bf16_t>::unpack(w4[t][0], res);
-      Vec16<bf16_t>::unpack(w4[t][1], res + 8);
-#pragma unroll
-      for (int p = 0; p < 16; ++p) o[p] = f[p] + res[p];
-    } else {
-#pragma unroll
-      for (int p = 0; p < 16; ++p) o[p] = f[p];
+      constexpr int JP = EPI == kRopeHalf128 ? 2 : EPI == kRopeHalf64 ? 1 : 0;
+      epi_rotate<TM, JP>(acc, sRho, lds, lane, a.D, rows);
+      rotated = true;
     }
-    const u32x4 lo16 = Vec16<bf16_t>::pack(o), hi16 = Vec16<bf16_t>::pack(o + 8);
-    bf16_t* dst = ot.out + m * ot.out_cols + ot.out_col0;
-    *reinterpret_cast<u32x4*>(dst + e0) = lo16;
-    *reinterpret_cast<u32x4*>(dst + e1) = hi16;
-    if (fdst[t] >= 0) {
-      bf16_t* fd = ot.fused + fdst[t] * ot.out_cols + ot.out_col0;
-      *reinterpret_cast<u32x4*>(fd + e0) = lo16;
-      *reinterpret_cast<u32x4*>(fd + e1) = hi16;
+  }
+  if (!rotated) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        __builtin_amdgcn_sched_barrier(0);       // (else every LDS read of the residual is hoisted, and spilled)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float4v o = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+          if constexpr (EPI == kAdd) {
+            const u32x2 t = *epi_piece(lds, lane, i, j, q);
+            o[0] += __uint_as_float(t.x << 16); o[1] += __uint_as_float(t.x & 0xffff0000u);
+            o[2] += __uint_as_float(t.y << 16); o[3] += __uint_as_float(t.y & 0xffff0000u);
+          }
+          epi_put(lds, lane, i, j, q, rows.zero[i], o);
+        }
+      }
+  }
+  const int ch = lane & 15, rq = lane >> 4;
+  bf16_t* dst = ot.out + ot.out_col0 + ch * 8;
+  bf16_t* fus = ot.fused + ot.out_col0 + ch * 8;
+#pragma unroll
+  for (int b = 0; b < TM; ++b) {
+    int32_t d[8];                      // (requested together, before the first store waits for one)
+    if (is_rope(EPI) && ot.fused) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) d[u] = a.dst_rows[min(m0 + 32 * b + 4 * u + rq, a.M - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int r = 32 * b + 4 * u + rq;
+      const int64_t m = m0 + r;
+      if (m < a.M) {
+        const u32x4 t = *reinterpret_cast<const u32x4*>(lds + r * 256 + ((ch ^ (r & 15)) * 16));
+        *reinterpret_cast<u32x4*>(dst + m * ot.out_cols) = t;
+        if (is_rope(EPI) && ot.fused && d[u] >= 0 && d[u] < a.fused_rows)
+          *reinterpret_cast<u32x4*>(fus + (int64_t)d[u] * ot.out_cols) = t;
+      }
     }
   }
 }
@@ -439,186 +505,69 @@ __device__ __forceinline__ void store_tile(const QkvArgs& a, const float* sC, co
 // Staged tiles have rows of 128 bytes (8 chunks of 16 bytes) without padding; chunk c of row r sits in
 // slot c ^ ((r / 2) % 8), so the 16-byte fragment reads of 16 consecutive rows touch 16 different bank
 // groups.  One load instruction of a wave fills 8 rows (1 KB): lane L fills slot L%8 of row L/8.
-template <int TM, int TN, int WGM, int WGN, int STYLE>
-__global__ __launch_bounds__(64 * WGM * WGN) void qkv_mfma_kernel(QkvArgs a) {
-  using C = Tile<TM, TN, WGM, WGN>;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WGN, wn = wave % WGN;
-  const int hf = lane >> 5, l32 = lane & 31;
-  // consecutive workgroup ids land on different XCDs: all row tiles of a column tile share an XCD, so
-  // the weight tile is fetched into one L2 only
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int m_tile = slot % a.m_tiles, n_tile = (slot / a.m_tiles) * 8 + xcd;
-  if (n_tile >= a.n_tiles) return;
-  const int64_t m0 = (int64_t)m_tile * C::BM;
-  const int col0 = n_tile * kBN;
 
-  const OutTile ot = out_tile_of(a, col0);
-  if (!ot.out) return;
-
-  // load instruction i of this wave covers tile rows 8*(wave + NWAVE*i) .. +7
-  const int ld_r = lane >> 3;                                    // row inside the 8-row group
-  const bf16_t* a_src[C::A_LD];                                  // per-lane source of chunk (lane%8)^swz at k = 0
-#pragma unroll
-  for (int i = 0; i < C::A_LD; ++i) {
-    const int row = 8 * (wave + C::NWAVE * i) + ld_r;
-    const int chunk = (lane & 7) ^ ((row >> 1) & 7);
-    const int64_t m = m0 + row;
-    int64_t idx = 0;                                             // rows past M read row 0; never stored
-    if (m < a.M) {
-      idx = a.gather ? (int64_t)a.gather[m] : m;
-      if (idx < 0 || idx >= a.x_rows) idx = 0;                   // stored as zeros in the epilogue
-    }
-    a_src[i] = a.x + idx * a.d_model + chunk * 8;
-  }
-  uint32_t b_off[C::B_LD];                                       // byte offset from w + col0 * d_model
-#pragma unroll
-  for (int i = 0; i < C::B_LD; ++i) {
-    const int row = 8 * (wave + C::NWAVE * i) + ld_r;
-    const int chunk = (lane & 7) ^ ((row >> 1) & 7);
-    b_off[i] = (uint32_t)row * (uint32_t)a.d_model * 2u + (uint32_t)chunk * 16u;
-  }
-  const char* b_base = reinterpret_cast<const char*>(a.w + (int64_t)col0 * a.d_model);
-  auto issue = [&](int kt, int st) {
-    unsigned char* sA = smem + (size_t)st * C::STAGE;
-    unsigned char* sB = sA + C::BM * kBK * 2;
-#pragma unroll
-    for (int i = 0; i < C::A_LD; ++i) load_to_lds_addr(a_src[i] + (int64_t)kt * kBK, sA + (wave + C::NWAVE * i) * 1024);
-#pragma unroll
-    for (int i = 0; i < C::B_LD; ++i)
-      load_to_lds(b_base + (int64_t)kt * kBK * 2, b_off[i], sB + (wave + C::NWAVE * i) * 1024);
-  };
-
-  // the same loads split in four parts (part p issues every 4th instruction), so that they can be spread
-  // between the MFMAs of a k-tile
-  auto issue_part = [&](int kt, int st, int part) {
-    unsigned char* sA = smem + (size_t)st * C::STAGE;
-    unsigned char* sB = sA + C::BM * kBK * 2;
-#pragma unroll
-    for (int i = 0; i < C::A_LD; ++i)
-      if ((i & 3) == part) load_to_lds_addr_nf(a_src[i] + (int64_t)kt * kBK, sA + (wave + C::NWAVE * i) * 1024);
-#pragma unroll
-    for (int i = 0; i < C::B_LD; ++i)
-      if ((i & 3) == part) load_to_lds_nf(b_base + (int64_t)kt * kBK * 2, b_off[i], sB + (wave + C::NWAVE * i) * 1024);
-  };
-
-  // fragment addresses inside a stage: row (32-row tile base + l32), chunk 2*ks + hf in slot
-  // (2*ks + hf) ^ ((l32 / 2) % 8); the address of step ks is base ^ (32 * ks)
-  const int swz = (l32 >> 1) & 7;
-  const int fb0 = l32 * 128 + ((hf ^ (swz & 1)) * 16) + ((swz & 6) * 16);
-  const int a_frag = wm * 32 * TM * 128 + fb0;
-  const int b_frag = C::BM * kBK * 2 + wn * 32 * TN * 128 + fb0;
-
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = floatx16{0};
-
-  const int nk = a.d_model / kBK;
-  issue(0, 0);
-  if (nk > 1) issue(1, 1);
-  for (int kt = 0; kt < nk; ++kt) {
-    // every wave has at most two stages of its own loads in flight; wait for the older one
-    if (kt + 1 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(C::A_LD + C::B_LD) : "memory");
-    else __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();                       // stage kt%3 is complete; stage (kt+2)%3 is free again
-    const bool more = kt + 2 < nk;
-    const int st_next = (kt + 2) % kStages;
-    const unsigned char* stage = smem + (size_t)(kt % kStages) * C::STAGE;
-    // fragments of step ks+1 are requested before the MFMAs of step ks are issued
-    u32x4 af[2][TM], bfr[2][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) af[0][i] = *reinterpret_cast<const u32x4*>(stage + (a_frag + i * 32 * 128));
-#pragma unroll
-    for (int j = 0; j < TN; ++j) bfr[0][j] = *reinterpret_cast<const u32x4*>(stage + (b_frag + j * 32 * 128));
-#pragma unroll
-    for (int ks = 0; ks < kBK / 16; ++ks) {
-      if (ks + 1 < kBK / 16) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-          af[(ks + 1) & 1][i] = *reinterpret_cast<const u32x4*>(stage + ((a_frag + i * 32 * 128) ^ (32 * (ks + 1))));
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          bfr[(ks + 1) & 1][j] = *reinterpret_cast<const u32x4*>(stage + ((b_frag + j * 32 * 128) ^ (32 * (ks + 1))));
-      }
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        // a quarter of the next-but-one stage per k-step, requested while the matrix unit is busy
-        if (i == TM / 2 && more) issue_part(kt + 2, st_next, ks);
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[ks & 1][i]),
-                                                               __builtin_bit_cast(bf16x8, bfr[ks & 1][j]), acc[i][j], 0, 0, 0);
-      }
-    }
-  }
-  __syncthreads();                         // all fragment reads done before the epilogue reuses the LDS
-
-  // epilogue: the whole BM x 128 tile goes through LDS as fp32 (it fits in the ring's space)
-  float* sC = reinterpret_cast<float*>(smem);
-  float2* sRho = reinterpret_cast<float2*>(smem + C::RHO);
-  if (ot.rotate && tid < 64) fill_rho(a, sRho, tid);
-  acc_to_lds<TM, TN>(sC, acc, wm * 32 * TM, wn * 32 * TN, lane);
-  __syncthreads();
-  store_tile<C::BM, C::NTHR, STYLE>(a, sC, sRho, m0, ot, tid);
-}
-
-// ---- specialised variant for 256-row tiles (TM = 2) and 128-row tiles (TM = 1) ----------------------
-// Four compute waves (one per SIMD, 32*TM x 128 outputs each) issue only fragment reads and MFMAs; four more
-// waves only issue the asynchronous global-to-LDS loads.  A wave that issues such a load can stall on the
-// memory pipeline's queue, and a stalled wave issues no MFMAs either: with the two roles in different
-// waves the matrix unit keeps running meanwhile.
+// ---- load/compute-split kernel: 32*TM*NC-row tiles x 128 columns ---------------------------------------
+// NC compute waves (32*TM x 128 outputs each) issue only fragment reads and MFMAs; four more waves only issue the
+// asynchronous global-to-LDS loads.  A wave that issues such a load can stall on the memory pipeline's queue, and a
+// stalled wave issues no MFMAs either: with the two roles in different waves the matrix unit keeps running meanwhile.
+// S stages: S - 1 k-tiles are on their way while one is used (the deeper rings belong to the small tiles, whose
+// launches stream the weights from HBM: 64 x 128 tiles keep 120 KB in flight per compute unit).
 //
 // Synchronisation, one barrier per k-tile (barrier number kt + 1 is crossed while tile kt is computed):
-//   compute wave: steps 0..2 of tile kt, wait for its last fragment reads of stage kt%3, barrier,
+//   compute wave: steps 0..2 of tile kt, wait for its last fragment reads of stage kt%S, barrier,
 //                 request the first fragments of tile kt+1, step 3 of tile kt;
-//   load wave:    after barrier kt it requests tile kt+2 into stage (kt+2)%3 == (kt-1)%3 (free: every
+//   load wave:    after barrier kt it requests tile kt+S-1 into stage (kt+S-1)%S == (kt-1)%S (free: every
 //                 compute wave finished reading tile kt-1 before barrier kt), waits until its loads of
 //                 tile kt+1 have landed, barrier.
-template <int TM_>
+template <int TM_, int NC_, int S_>
 struct WsTile {
-  static constexpr int TM = TM_, TN = 4, NC = 4, NL = 4;          // compute waves stacked along M
-  static constexpr int BM = 32 * TM * NC;                         // 256 (TM = 2) or 128 (TM = 1)
+  static constexpr int TM = TM_, TN = 4, NC = NC_, NL = 4, S = S_;
+  static constexpr int BM = 32 * TM * NC;
   static constexpr int NTHR = 64 * (NC + NL);
   static constexpr int A_LD = BM / 8 / NL;                        // 1 KB load instructions per load wave and stage
   static constexpr int B_LD = kBN / 8 / NL;
   static constexpr int STAGE = (BM + kBN) * kBK * 2;
-  static constexpr size_t LDS_MAIN = (size_t)kStages * STAGE;
-  static constexpr size_t LDS_EPI = (size_t)BM * kCStride * 4;
-  static constexpr size_t RHO = LDS_MAIN > LDS_EPI ? LDS_MAIN : LDS_EPI;
-  static constexpr size_t LDS = RHO + kRhoBytes;
+  static constexpr size_t LDS_MAIN = (size_t)S * STAGE;
+  static constexpr size_t LDS = LDS_MAIN + kRhoBytes;
   static_assert(32 * TN == kBN, "a compute wave covers the 128 output columns");
+  static_assert(NC * TM * 8192 <= (int)LDS_MAIN, "the epilogue works in the ring");
 };
 
-template <int TM_, int STYLE>
-__global__ __launch_bounds__(WsTile<TM_>::NTHR) void qkv_ws_kernel(QkvArgs a) {
-  using C = WsTile<TM_>;
-  constexpr int TM = C::TM, TN = C::TN;
+// WIDE: x is 4 GiB or larger (64-bit addresses per lane instead of 32-bit offsets)
+template <typename C, int EPI, bool WIDE>
+__global__ __launch_bounds__(C::NTHR) void qkv_ws_kernel(QkvArgs a) {
+  constexpr int TM = C::TM, TN = C::TN, S = C::S;
   extern __shared__ __align__(16) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hf = lane >> 5, l32 = lane & 31;
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;        // same workgroup order as above
-  int m_tile = slot % a.m_tiles, n_tile = (slot / a.m_tiles) * 8 + xcd;
+  // consecutive workgroup ids land on different XCDs: all row tiles of a (column block, contraction range) share an
+  // XCD, so its weights are fetched into one L2 only
+  const int units = a.n_tiles * a.splits;
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  int m_tile = slot % a.m_tiles, unit = (slot / a.m_tiles) * 8 + xcd;
   if (a.rows_over_xcds) {          // many row tiles: row tiles are dealt to the XCDs, column tiles run side by side
-    m_tile = (slot / a.n_tiles) * 8 + xcd;
-    n_tile = slot % a.n_tiles;
+    m_tile = (slot / units) * 8 + xcd;
+    unit = slot % units;
   }
-  if (n_tile >= a.n_tiles || m_tile >= a.m_tiles) return;
+  if (unit >= units || m_tile >= a.m_tiles) return;
+  const int split = unit / a.n_tiles, n_tile = unit - split * a.n_tiles;
   const int64_t m0 = (int64_t)m_tile * C::BM;
-  const int col0 = n_tile * kBN;
-  const OutTile ot = out_tile_of(a, col0);
+  const int block = a.n_tile0 + n_tile;
+  const OutTile ot = out_tile_of<EPI>(a, block);
   if (!ot.out) return;
-  const int nk = a.d_model / kBK;
-  float* sC = reinterpret_cast<float*>(smem);
-  float2* sRho = reinterpret_cast<float2*>(smem + C::RHO);
+  const int kt0 = split * a.split_len;
+  const int nk = min(a.d_model / kBK - kt0, a.split_len);
+  float2* sRho = reinterpret_cast<float2*>(smem + C::LDS_MAIN);
 
   if (wave >= C::NC) {
     // ---------------- load wave lw: instruction i covers tile rows 8*(lw + NL*i) .. +7
     const int lw = wave - C::NC;
     const int ld_r = lane >> 3;
-    uint32_t a_off[C::A_LD];                                     // byte offset from x (x is below 4 GiB here)
+    const uint32_t row_bytes = (uint32_t)a.d_model * 2u;
+    uint32_t a_off[WIDE ? 1 : C::A_LD];                          // byte offset from x
+    const char* a_ptr[WIDE ? C::A_LD : 1];
+    const char* a_base = reinterpret_cast<const char*>(a.x) + (int64_t)kt0 * kBK * 2;
 #pragma unroll
     for (int i = 0; i < C::A_LD; ++i) {
       const int row = 8 * (lw + C::NL * i) + ld_r;
@@ -629,53 +578,55 @@ __global__ __launch_bounds__(WsTile<TM_>::NTHR) void qkv_ws_kernel(QkvArgs a) {
         idx = a.gather ? (int64_t)a.gather[m] : m;
         if (idx < 0 || idx >= a.x_rows) idx = 0;                 // stored as zeros in the epilogue
       }
-      a_off[i] = (uint32_t)idx * (uint32_t)a.d_model * 2u + (uint32_t)chunk * 16u;
+      if constexpr (WIDE) a_ptr[i] = a_base + idx * (int64_t)row_bytes + chunk * 16;
+      else a_off[i] = (uint32_t)idx * row_bytes + (uint32_t)chunk * 16u;
     }
-    const char* a_base = reinterpret_cast<const char*>(a.x);
     uint32_t b_off[C::B_LD];
 #pragma unroll
     for (int i = 0; i < C::B_LD; ++i) {
       const int row = 8 * (lw + C::NL * i) + ld_r;
       const int chunk = (lane & 7) ^ ((row >> 1) & 7);
-      b_off[i] = (uint32_t)row * (uint32_t)a.d_model * 2u + (uint32_t)chunk * 16u;
+      b_off[i] = block_w_step<EPI>(a, row) * row_bytes + (uint32_t)chunk * 16u;
     }
-    const char* b_base = reinterpret_cast<const char*>(a.w + (int64_t)col0 * a.d_model);
+    const char* b_base = reinterpret_cast<const char*>(a.w + block_w_row<EPI>(block) * a.d_model) + (int64_t)kt0 * kBK * 2;
     auto issue = [&](int kt) {
-      unsigned char* sA = smem + (size_t)(kt % kStages) * C::STAGE;
+      unsigned char* sA = smem + (size_t)(kt % S) * C::STAGE;
       unsigned char* sB = sA + C::BM * kBK * 2;
 #pragma unroll
       for (int i = 0; i < C::B_LD; ++i)
         load_to_lds(b_base + (int64_t)kt * kBK * 2, b_off[i], sB + (lw + C::NL * i) * 1024);
 #pragma unroll
-      for (int i = 0; i < C::A_LD; ++i)
-        load_to_lds(a_base + (int64_t)kt * kBK * 2, a_off[i], sA + (lw + C::NL * i) * 1024);
+      for (int i = 0; i < C::A_LD; ++i) {
+        if constexpr (WIDE) load_to_lds_addr(a_ptr[i] + (int64_t)kt * kBK * 2, sA + (lw + C::NL * i) * 1024);
+        else load_to_lds(a_base + (int64_t)kt * kBK * 2, a_off[i], sA + (lw + C::NL * i) * 1024);
+      }
     };
-    issue(0);
-    if (nk > 1) {
-      issue(1);
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(C::A_LD + C::B_LD) : "memory");
-    } else {
-      __builtin_amdgcn_s_waitcnt(0);
-    }
+    constexpr int kFlight = (S - 2) * (C::A_LD + C::B_LD);       // loads that may stay on their way: all but the next tile's
+    static_assert(kFlight <= 63, "the wait counter holds 6 bits");
+    for (int kt = 0; kt < min(S - 1, nk); ++kt) issue(kt);
+    if (nk >= S - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kFlight) : "memory");
+    else __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();                                             // barrier 0: tile 0 has landed
     for (int kt = 0; kt < nk; ++kt) {
-      if (kt + 2 < nk) {
-        issue(kt + 2);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(C::A_LD + C::B_LD) : "memory");
+      if (kt + S - 1 < nk) {
+        issue(kt + S - 1);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kFlight) : "memory");
       } else {
         __builtin_amdgcn_s_waitcnt(0);
       }
       __syncthreads();                                           // barrier kt + 1: tile kt + 1 has landed
     }
-    if (ot.rotate && lw == 0) fill_rho(a, sRho, lane);           // (behind the ring: no stage is touched)
-    __syncthreads();                                             // the accumulators are in LDS
+    if (is_rope(EPI) && lw == 0) fill_rho(a, sRho, lane);           // (behind the ring: no stage is touched)
+    __syncthreads();                                             // the ring is free, the frequencies are there
   } else {
-    // ---------------- compute wave: rows 64*wave .. +63 of the tile, all 128 columns
+    // ---------------- compute wave: rows 32*TM*wave .. of the tile, all 128 columns
     __builtin_amdgcn_s_setprio(2);                               // its instructions go first when both roles are ready
     const int swz = (l32 >> 1) & 7;
     const int fb0 = l32 * 128 + ((hf ^ (swz & 1)) * 16) + ((swz & 6) * 16);
     const int a_frag = wave * 32 * TM * 128 + fb0;
     const int b_frag = C::BM * kBK * 2 + fb0;
+    EpiRows<TM> rows;
+    load_epi_rows<TM, EPI>(a, m0 + wave * 32 * TM, lane, rows);
     floatx16 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -695,8 +646,8 @@ __global__ __launch_bounds__(WsTile<TM_>::NTHR) void qkv_ws_kernel(QkvArgs a) {
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[buf][i]),
-                                                               __builtin_bit_cast(bf16x8, bfr[buf][j]), acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bfr[buf][j]),
+                                                               __builtin_bit_cast(bf16x8, af[buf][i]), acc[i][j], 0, 0, 0);
     };
     // issue order of one k-step: every fragment read sits behind an MFMA, so that the matrix unit is
     // already busy while the read is issued
@@ -713,7 +664,7 @@ __global__ __launch_bounds__(WsTile<TM_>::NTHR) void qkv_ws_kernel(QkvArgs a) {
     __syncthreads();                                             // barrier 0
     fetch(smem, 0, 0);
     for (int kt = 0; kt < nk; ++kt) {
-      const unsigned char* stage = smem + (size_t)(kt % kStages) * C::STAGE;
+      const unsigned char* stage = smem + (size_t)(kt % S) * C::STAGE;
 #pragma unroll
       for (int ks = 0; ks < 3; ++ks) {
         fetch(stage, ks + 1, (ks + 1) & 1);
@@ -723,27 +674,284 @@ __global__ __launch_bounds__(WsTile<TM_>::NTHR) void qkv_ws_kernel(QkvArgs a) {
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // the last fragments of this stage are in registers
       __syncthreads();                                           // barrier kt + 1
       // (after the last tile this re-reads the current stage; the values are not used)
-      fetch(smem + (size_t)((kt + 1 < nk ? kt + 1 : kt) % kStages) * C::STAGE, 0, 0);
+      fetch(smem + (size_t)((kt + 1 < nk ? kt + 1 : kt) % S) * C::STAGE, 0, 0);
       mfmas(1);
       interleave();
     }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_setprio(0);
-    acc_to_lds<TM, TN>(sC, acc, wave * 32 * TM, 0, lane);
     __syncthreads();
+    if (a.splits > 1) {
+      if constexpr (TM == 1) {        // partial sums in register order: 1 KB per store
+        float4* dst = a.part + ((((int64_t)split * a.n_tiles + n_tile) * a.m_tiles + m_tile) * C::NC + wave) * 1024 + lane;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            dst[(4 * j + q) * 64] = make_float4(acc[0][j][4 * q], acc[0][j][4 * q + 1], acc[0][j][4 * q + 2], acc[0][j][4 * q + 3]);
+      }
+      return;
+    }
+    wave_epilogue<TM, EPI>(a, ot, acc, sRho, smem + wave * TM * 8192, m0 + wave * 32 * TM, lane, rows);
   }
-  store_tile<C::BM, C::NTHR, STYLE>(a, sC, sRho, m0, ot, tid);
 }
 
-// 256-row or 128-row tiles (both load/compute-split)?  Both run one workgroup per compute unit, so
-// the launch takes (rounds of workgroups) x (time of one workgroup); the per-k-tile and fixed costs are the
-// measured ones of the two kernels on MI355X (microseconds).
-bool prefer_256_rows(int64_t M, int n_col_tiles, int K) {
-  const int cus = compute_unit_count();
-  const double k_tiles = (double)K / kBK;
-  const int64_t wg256 = ((M + 255) / 256) * n_col_tiles, wg128 = ((M + 127) / 128) * n_col_tiles;
-  const double t256 = (double)((wg256 + cus - 1) / cus) * (0.8 * k_tiles + 15.0);
-  const double t128 = (double)((wg128 + cus - 1) / cus) * (0.47 * k_tiles + 12.0);
-  return t256 < t128;
+// Sums the partial results of a split contraction, in range order, and finishes them: one workgroup per 32 rows x
+// 128 columns; wave w adds column block w, the first wave does the epilogue.
+template <int EPI>
+__global__ __launch_bounds__(256) void qkv_split_reduce(QkvArgs a, int n_groups) {
+  __shared__ __align__(16) float4 sSum[1024];
+  __shared__ __align__(16) unsigned char sOut[8192];
+  __shared__ float2 sRho[64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int grp = blockIdx.x;                                    // 32-row group
+  const int n_tile = blockIdx.y;
+  const OutTile ot = out_tile_of<EPI>(a, a.n_tile0 + n_tile);
+  if (!ot.out) return;
+  EpiRows<1> rows;
+  load_epi_rows<1, EPI>(a, (int64_t)grp * 32, lane, rows);
+  const float4* src = a.part + ((int64_t)n_tile * n_groups + grp) * 1024 + wave * 256 + lane;
+  const int64_t stride = (int64_t)a.n_tiles * n_groups * 1024;
+  float4 sum[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) sum[q] = src[q * 64];
+#pragma unroll 4
+  for (int s = 1; s < a.splits; ++s) {
+    src += stride;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 t = src[q * 64];
+      sum[q].x += t.x; sum[q].y += t.y; sum[q].z += t.z; sum[q].w += t.w;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) sSum[(4 * wave + q) * 64 + lane] = sum[q];
+  if (is_rope(EPI) && tid < 64) fill_rho(a, sRho, tid);
+  __syncthreads();
+  if (wave != 0) return;
+  floatx16 acc[1][4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 t = sSum[(4 * j + q) * 64 + lane];
+      acc[0][j][4 * q] = t.x; acc[0][j][4 * q + 1] = t.y; acc[0][j][4 * q + 2] = t.z; acc[0][j][4 * q + 3] = t.w;
+    }
+  wave_epilogue<1, EPI>(a, ot, acc, sRho, sOut, (int64_t)grp * 32, lane, rows);
+}
+
+// ---- 256 x 256 tiles, four waves of 128 x 128 -----------------------------------------------------
+// One wave per SIMD, so that a wave can hold 128 x 128 outputs (256 accumulation registers) and an LDS fragment
+// feeds four MFMAs.  Both operands of a k-tile are kept as two units of 128 rows (the rows 64 u .. 64 u + 63 of both
+// wave rows / wave columns), and a k-tile runs as four phases of 16 MFMAs over the operand halves
+//     phase 0: A0 x B0     phase 1: A0 x B1     phase 2: A1 x B1     phase 3: A1 x B0
+// with the fragments of a half (two 32-row blocks, four k-steps) in registers.  Phase p reads the half that phase
+// p + 1 adds - B1(t), A1(t), A0(t+1), B0(t+1) - so every unit is read in one phase only and its LDS can be refilled
+// right behind it: the loads of a unit have seven phases (about 2 us) to arrive although the ring holds just two
+// k-tiles.  One barrier per phase publishes the unit that the next phase reads and frees the one this phase read.
+// 1024 x 1024 blocks of workgroups keep to an XCD (locate_big_tile).  Measured at M 23891, K 4096, N 6144: 870 us,
+// 1.38 PFLOP/s (256 x 128 tiles: 1080 us); the clock settles at 1.75 GHz under this load, the matrix unit is busy
+// 80 % of the cycles of the k-loop.
+struct QuadTile {
+  static constexpr int BM = 256, BN = 256, NTHR = 256;
+  static constexpr int UNIT = 128 * kBK * 2;                       // 16 KB: 128 rows of one operand
+  static constexpr int STAGE = 4 * UNIT;                           // A0 A1 B0 B1
+  static constexpr size_t LDS = 2 * STAGE + kRhoBytes;
+};
+
+// End of a phase: this wave's fragment reads are back and at most N of its loads are still on their way.
+template <int N>
+__device__ __forceinline__ void wait_and_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (N >= 0) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+  else asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Tile order: workgroups with the same id modulo 8 share an XCD and its 32 compute units run 32 of them at a time.
+// Tiles are numbered row first inside groups of m_group row tiles, and each XCD takes 32 consecutive ones, i.e. a
+// roughly square block whose operands fit its L2; the last, incomplete round is dealt out evenly.
+__device__ __forceinline__ bool locate_big_tile(int m_tiles, int n_bt, int gm, int id, int& m_tile, int& b_tile) {
+  const int total = m_tiles * n_bt;
+  const int xcd = id & 7, slot = id >> 3;
+  const int full = total / 256;
+  int p;
+  if (slot < 32 * full) {
+    p = (slot >> 5) * 256 + xcd * 32 + (slot & 31);
+  } else {
+    const int q = (total - full * 256 + 7) >> 3, i = slot - 32 * full;
+    if (i >= q) return false;
+    p = full * 256 + xcd * q + i;
+  }
+  if (p >= total) return false;
+  const int per_group = gm * n_bt;
+  const int grp = p / per_group, r = p - grp * per_group;
+  const int rows = min(gm, m_tiles - grp * gm);
+  b_tile = r / rows;
+  m_tile = grp * gm + (r - b_tile * rows);
+  return true;
+}
+
+template <int EPI>
+__global__ __launch_bounds__(256, 1) void qkv_quad_kernel(QkvArgs a) {
+  using C = QuadTile;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int hf = lane >> 5, l32 = lane & 31;
+  const int n_bt = (a.n_tiles + 1) / 2;
+  int m_tile, b_tile;
+  if (!locate_big_tile(a.m_tiles, n_bt, a.m_group, (int)blockIdx.x, m_tile, b_tile)) return;
+  const int64_t m0 = (int64_t)m_tile * C::BM;
+  const int block0 = a.n_tile0 + 2 * b_tile;
+  const bool second = 2 * b_tile + 1 < a.n_tiles;                // (else the tile's second 128 columns repeat the first)
+  const int nk = a.d_model / kBK;                                // even (launcher)
+  const uint32_t row_bytes = (uint32_t)a.d_model * 2u;
+
+  // byte offsets of this lane's 16 bytes inside k-tile 0: load i of unit u fills unit rows 8*wave + 32*i .. +7
+  uint32_t a_off[2][4], b_off[2][4];
+  {
+    const int ld_r = lane >> 3;
+    const uint32_t chunk = (uint32_t)(((lane & 7) ^ ((4 * wave + (ld_r >> 1)) & 7)) * 16);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = u * 64 + (i & 1) * 32 + 8 * wave + ld_r;
+        const int64_t m = m0 + (i >> 1) * 128 + r;
+        int64_t idx = 0;                                         // rows past M read row 0; never stored
+        if (m < a.M) {
+          idx = a.gather ? (int64_t)a.gather[m] : m;
+          if (idx < 0 || idx >= a.x_rows) idx = 0;               // stored as zeros in the epilogue
+        }
+        a_off[u][i] = (uint32_t)idx * row_bytes + chunk;
+        const uint32_t blk_rows = second && i >= 2 ? (uint32_t)block_w_row<EPI>(1) : 0u;
+        b_off[u][i] = (blk_rows + block_w_step<EPI>(a, r)) * row_bytes + chunk;
+      }
+  }
+  const uint32_t lds0 = lds_offset_of(smem);
+  const uint32_t lds_w = __builtin_amdgcn_readfirstlane((int)(lds0 + (uint32_t)wave * 1024u));
+  const char* a_base = reinterpret_cast<const char*>(a.x);
+  const char* b_base = reinterpret_cast<const char*>(a.w + block_w_row<EPI>(block0) * a.d_model);
+  auto load_a1 = [&](auto u_c, auto i_c, auto sl_c, const char* src) {
+    constexpr int u = decltype(u_c)::value, i = decltype(i_c)::value, sl = decltype(sl_c)::value;
+    load_to_lds_const<sl * C::STAGE + u * C::UNIT + i * 4096>(src, a_off[u][i], lds_w);
+  };
+  auto load_b1 = [&](auto u_c, auto i_c, auto sl_c, const char* src) {
+    constexpr int u = decltype(u_c)::value, i = decltype(i_c)::value, sl = decltype(sl_c)::value;
+    load_to_lds_const<sl * C::STAGE + (2 + u) * C::UNIT + i * 4096>(src, b_off[u][i], lds_w);
+  };
+  std::integral_constant<int, 0> c0;
+  std::integral_constant<int, 1> c1;
+  std::integral_constant<int, 2> c2;
+  std::integral_constant<int, 3> c3;
+  // (the last tiles load the last k-tile again, into slots that nothing reads any more: one loop body for all tiles)
+  auto k_off = [&](int t) { return (int64_t)min(t, nk - 1) * (kBK * 2); };
+  auto load_a = [&](auto u, auto sl, int t) {
+    const char* p = a_base + k_off(t);
+    load_a1(u, c0, sl, p); load_a1(u, c1, sl, p); load_a1(u, c2, sl, p); load_a1(u, c3, sl, p);
+  };
+  auto load_b = [&](auto u, auto sl, int t) {
+    const char* p = b_base + k_off(t);
+    load_b1(u, c0, sl, p); load_b1(u, c1, sl, p); load_b1(u, c2, sl, p); load_b1(u, c3, sl, p);
+  };
+
+  const int swz = (l32 >> 1) & 7;
+  const uint32_t fb0 = l32 * 128 + ((hf ^ (swz & 1)) * 16) + ((swz & 6) * 16);
+  uint32_t fa[2][4], fb[2][4];                                   // fragment addresses: [slot][k-step], half 0
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      fa[s][ks] = lds0 + s * C::STAGE + wm * 8192 + (fb0 ^ (32 * ks));
+      fb[s][ks] = lds0 + s * C::STAGE + 2 * C::UNIT + wn * 8192 + (fb0 ^ (32 * ks));
+    }
+  auto lds16 = [](uint32_t addr) { return *(const u32x4 __attribute__((address_space(3)))*)(uintptr_t)addr; };
+
+  EpiRows<4> rows;
+  load_epi_rows<4, EPI>(a, m0 + wm * 128, lane, rows);
+  floatx16 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = floatx16{0};
+  u32x4 ra[2][2][4], rb[2][2][4];      // [register set][32-row block][k-step]; B half u of tile t is in set u ^ (t & 1)
+
+  load_a(c0, c0, 0); load_b(c0, c0, 0); load_b(c1, c0, 0); load_a(c1, c0, 0);
+  load_a(c0, c1, 1); load_b(c0, c1, 1); load_b(c1, c1, 1); load_a(c1, c1, 1);
+  wait_and_barrier<24>();              // A0(0) and B0(0) have landed
+#pragma unroll
+  for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      ra[0][ii][ks] = lds16(fa[0][ks] + ii * 4096);
+      rb[0][ii][ks] = lds16(fb[0][ks] + ii * 4096);
+    }
+  wait_and_barrier<-1>();
+  load_a(c0, c0, 2);
+  wait_and_barrier<24>();              // B1(0) has landed
+
+  auto phase = [&](auto par_c, auto ph_c, const char* src) {
+    constexpr int PAR = decltype(par_c)::value, ph = decltype(ph_c)::value;
+    std::integral_constant<int, PAR> sl;
+    std::integral_constant<int, PAR ^ 1> sln;
+    constexpr int UA = ph >= 2 ? 1 : 0, UB = (ph == 1 || ph == 2) ? 1 : 0;      // operand halves of this phase
+    auto rd = [&](auto n_c) {                                    // fragments for the next phase
+      constexpr int n = decltype(n_c)::value, ks = n >> 1, ii = n & 1;
+      if (ph == 0) rb[1 ^ PAR][ii][ks] = lds16(fb[PAR][ks] + C::UNIT + ii * 4096);           // B1(t)
+      if (ph == 1) ra[1][ii][ks] = lds16(fa[PAR][ks] + C::UNIT + ii * 4096);                 // A1(t)
+      if (ph == 2) ra[0][ii][ks] = lds16(fa[PAR ^ 1][ks] + ii * 4096);                       // A0(t+1)
+      if (ph == 3) rb[1 ^ PAR][ii][ks] = lds16(fb[PAR ^ 1][ks] + ii * 4096);                 // B0(t+1)
+    };
+    auto load1 = [&](auto i) {                                   // refill of the unit the previous phase read
+      if (ph == 0) load_b1(c0, i, sl, src);                      // B0(t+2)
+      if (ph == 1) load_b1(c1, i, sl, src);                      // B1(t+2)
+      if (ph == 2) load_a1(c1, i, sl, src);                      // A1(t+2)
+      if (ph == 3) load_a1(c0, i, sln, src);                     // A0(t+3)
+    };
+    auto step = [&](auto n_c) {                                  // issue order: an LDS read or a load behind each MFMA
+      constexpr int n = decltype(n_c)::value, ks = n >> 2, j = (n >> 1) & 1, i = (n & 1) ^ j;
+      acc[2 * UA + i][2 * UB + j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+          __builtin_bit_cast(bf16x8, rb[UB ^ PAR][j][ks]), __builtin_bit_cast(bf16x8, ra[UA][i][ks]),
+          acc[2 * UA + i][2 * UB + j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (n < 12) {
+        if constexpr (n % 3 == 2) load1(std::integral_constant<int, n / 3>{});
+        else rd(std::integral_constant<int, n - n / 3>{});
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    step(std::integral_constant<int, 0>{}); step(std::integral_constant<int, 1>{}); step(std::integral_constant<int, 2>{}); step(std::integral_constant<int, 3>{});
+    step(std::integral_constant<int, 4>{}); step(std::integral_constant<int, 5>{}); step(std::integral_constant<int, 6>{}); step(std::integral_constant<int, 7>{});
+    step(std::integral_constant<int, 8>{}); step(std::integral_constant<int, 9>{}); step(std::integral_constant<int, 10>{}); step(std::integral_constant<int, 11>{});
+    step(std::integral_constant<int, 12>{}); step(std::integral_constant<int, 13>{}); step(std::integral_constant<int, 14>{}); step(std::integral_constant<int, 15>{});
+    wait_and_barrier<24>();            // six phases' loads may be on their way; the unit read next is older
+  };
+  auto tile = [&](auto par, int t) {
+    const int64_t k2 = k_off(t + 2), k3 = k_off(t + 3);
+    phase(par, c0, b_base + k2);
+    phase(par, c1, b_base + k2);
+    phase(par, c2, a_base + k2);
+    phase(par, c3, a_base + k3);
+  };
+#pragma unroll 1
+  for (int t = 0; t < nk; t += 2) {
+    tile(c0, t);
+    tile(c1, t + 1);
+  }
+  wait_and_barrier<0>();
+#pragma unroll
+  for (int i = 0; i < 4; ++i)          // (in accumulation registers until here, whatever the epilogue wants)
+    asm volatile("" : "+a"(acc[i][0]), "+a"(acc[i][1]), "+a"(acc[i][2]), "+a"(acc[i][3]));
+
+  // epilogue, every wave by itself in 32 KB of the ring's space (nobody reads or fills the ring any more)
+  float2* sRho = reinterpret_cast<float2*>(smem + 2 * C::STAGE);
+  if (is_rope(EPI) && tid < 64) fill_rho(a, sRho, tid);
+  wait_and_barrier<-1>();
+  if (wn == 1 && !second) return;
+  const OutTile ot = out_tile_of<EPI>(a, block0 + wn);
+  if (ot.out) wave_epilogue<4, EPI>(a, ot, acc, sRho, smem + wave * 32768, m0 + wm * 128, lane, rows);
 }
 
 bool use_mfma(const qcf_layer_desc& L) {
@@ -754,49 +962,147 @@ size_t cs_bytes(const qcf_layer_desc& L, int64_t M) {
   return align_up((size_t)M * (L.head_dim / 2) * sizeof(float2), 256);
 }
 
-template <int TM, int TN, int WGM, int WGN>
-qcf_status run_mfma(const qcf_layer_desc& L, const QkvArgs& a_in, hipStream_t st) {
-  using C = Tile<TM, TN, WGM, WGN>;
-  const int64_t mt = (a_in.M + C::BM - 1) / C::BM;
-  const int nt = (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim / kBN;
-  const int64_t n_wg = mt * ((nt + 7) / 8) * 8;
-  if (mt > 0x7fffffff || n_wg > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "qkv: grid too large");
-  const dim3 grid((unsigned)n_wg), block(C::NTHR);
-  QkvArgs a = a_in;
-  a.m_tiles = (int)mt;
-  a.n_tiles = nt;
-  static std::atomic<uint64_t> lds_ok[2];
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&qkv_mfma_kernel<TM, TN, WGM, WGN, 0>), C::LDS, lds_ok[0]));
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&qkv_mfma_kernel<TM, TN, WGM, WGN, 1>), C::LDS, lds_ok[1]));
-  if (L.rope_style == 0) qkv_mfma_kernel<TM, TN, WGM, WGN, 0><<<grid, block, C::LDS, st>>>(a);
-  else qkv_mfma_kernel<TM, TN, WGM, WGN, 1><<<grid, block, C::LDS, st>>>(a);
-  return check_launch("qkv gemm");
+// ---- choice of the tile --------------------------------------------------------------------------
+typedef WsTile<2, 4, 3> Ws256;         // 256 x 128
+typedef WsTile<1, 4, 4> Ws128;         // 128 x 128
+typedef WsTile<1, 2, 6> Ws64;          //  64 x 128
+
+// One workgroup per compute unit, so a launch takes (rounds of workgroups) x (time of one workgroup); the costs per
+// k-tile and per workgroup are measured ones (microseconds, all compute units busy).  A split contraction adds the
+// writing and reading of its partial sums and a launch.
+enum GemmKind { kQuad, kWs256, kWs128, kWs64 };
+struct GemmPlan { GemmKind kind; int splits; double us; };
+
+double rounds_of(int64_t wgs) {
+  const int cus = compute_unit_count();
+  return (double)((wgs + cus - 1) / cus);
+}
+double quad_us(int64_t mt, int nb, int nk) { return rounds_of(mt * ((nb + 1) / 2)) * (1.40 * nk + 12.0); }
+
+// the load/compute-split kernels, over nb column blocks
+GemmPlan plan_ws(int64_t M, int nb, int nk, bool may_split) {
+  GemmPlan best{kWs256, 1, rounds_of((M + 255) / 256 * nb) * (0.75 * nk + 10.0)};
+  const double t128 = rounds_of((M + 127) / 128 * nb) * (0.45 * nk + 8.0);
+  if (t128 < best.us) best = GemmPlan{kWs128, 1, t128};
+  const int bm = M <= 64 ? 64 : 128;
+  const int64_t tiles = (M + bm - 1) / bm * nb;
+  const double c = bm == 64 ? 0.40 : 0.45;
+  for (int s = 1; s <= 16 && s * 4 <= nk; ++s) {
+    if (s > 1 && !may_split) break;
+    const int len = (nk + s - 1) / s;
+    if ((nk + len - 1) / len != s) continue;                     // (a range would be empty)
+    double t = std::max(rounds_of(tiles * s) * c * len, (double)nb * nk * (kBN * kBK * 2) / 4.6e6) + rounds_of(tiles * s) * 6.0;
+    if (s > 1) t += 4.0 + (double)tiles * bm * kBN * 8.0 * s / 4.0e6;
+    if (t < best.us) best = GemmPlan{bm == 64 ? kWs64 : kWs128, s, t};
+  }
+  return best;
 }
 
-template <int TM>
-qcf_status run_ws(const qcf_layer_desc& L, const QkvArgs& a_in, hipStream_t st) {
-  using C = WsTile<TM>;
-  const int64_t mt = (a_in.M + C::BM - 1) / C::BM;
-  const int nt = (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim / kBN;
+size_t split_part_bytes(int64_t M, int nb, const GemmPlan& p) {
+  if (p.splits <= 1) return 0;
+  const int bm = p.kind == kWs64 ? 64 : 128;
+  return (size_t)p.splits * nb * ((M + bm - 1) / bm) * bm * kBN * sizeof(float);
+}
+
+// workspace a product of M rows x nb column blocks x nk k-tiles can use (not needed: without it the contraction stays whole)
+size_t gemm_part_bytes(int64_t M, int nb, int nk) { return split_part_bytes(M, nb, plan_ws(M, nb, nk, true)); }
+
+template <typename C, int EPI, bool WIDE>
+qcf_status run_ws(QkvArgs a, int splits, hipStream_t st) {
+  const int64_t mt = (a.M + C::BM - 1) / C::BM;
+  const int nk = a.d_model / kBK;
+  a.m_tiles = (int)mt;
+  a.splits = splits;
+  a.split_len = (nk + splits - 1) / splits;
+  const int64_t units = (int64_t)a.n_tiles * splits;
   // Workgroup order.  Few row tiles: all row tiles of a column tile share an XCD, so a weight tile is fetched into
   // one L2 only and the XCD's concurrent workgroups share the row tiles of x.  Many row tiles: an XCD's concurrent
   // workgroups would all belong to one column tile and x would be streamed once per column tile (6 times at 48
   // column tiles); then the row tiles are dealt to the XCDs instead, a row tile of x stays in L2 and the weights
   // are streamed once per row tile (measured at 73 row tiles: 1127 -> 945 us, at 20: 964 -> 912 us).
   const bool rows_over_xcds = mt >= 16;
-  const int64_t n_wg = rows_over_xcds ? ((mt + 7) / 8) * 8 * nt : mt * ((nt + 7) / 8) * 8;
-  if (mt > 0x7fffffff || n_wg > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "qkv: grid too large");
-  const dim3 grid((unsigned)n_wg), block(C::NTHR);
-  QkvArgs a = a_in;
-  a.m_tiles = (int)mt;
-  a.n_tiles = nt;
   a.rows_over_xcds = rows_over_xcds ? 1 : 0;
-  static std::atomic<uint64_t> lds_ok[2];
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&qkv_ws_kernel<TM, 0>), C::LDS, lds_ok[0]));
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&qkv_ws_kernel<TM, 1>), C::LDS, lds_ok[1]));
-  if (L.rope_style == 0) qkv_ws_kernel<TM, 0><<<grid, block, C::LDS, st>>>(a);
-  else qkv_ws_kernel<TM, 1><<<grid, block, C::LDS, st>>>(a);
+  const int64_t n_wg = rows_over_xcds ? ((mt + 7) / 8) * 8 * units : mt * ((units + 7) / 8) * 8;
+  if (mt > 0x7fffffff || n_wg > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "qkv: grid too large");
+  static std::atomic<uint64_t> lds_ok;
+  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&qkv_ws_kernel<C, EPI, WIDE>), C::LDS, lds_ok));
+  qkv_ws_kernel<C, EPI, WIDE><<<dim3((unsigned)n_wg), dim3(C::NTHR), C::LDS, st>>>(a);
+  QCF_TRY_LAUNCH("qkv gemm");
+  if (splits > 1) {
+    const dim3 rgrid((unsigned)(mt * C::NC), (unsigned)a.n_tiles);
+    qkv_split_reduce<EPI><<<rgrid, dim3(256), 0, st>>>(a, (int)(mt * C::NC));
+    return check_launch("qkv split reduce");
+  }
+  return QCF_OK;
+}
+
+template <int EPI>
+qcf_status run_quad(QkvArgs a, hipStream_t st) {
+  using C = QuadTile;
+  const int64_t mt = (a.M + C::BM - 1) / C::BM;
+  const int64_t n_wg = (mt * ((a.n_tiles + 1) / 2) + 255) / 256 * 256;
+  if (n_wg > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "qkv: grid too large");
+  a.m_tiles = (int)mt;
+  const int64_t groups = (mt + 5) / 6;                           // groups of up to six row tiles, of equal size
+  a.m_group = (int)((mt + groups - 1) / groups);
+  a.splits = 1;
+  static std::atomic<uint64_t> lds_ok;
+  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&qkv_quad_kernel<EPI>), C::LDS, lds_ok));
+  qkv_quad_kernel<EPI><<<dim3((unsigned)n_wg), dim3(C::NTHR), C::LDS, st>>>(a);
   return check_launch("qkv gemm");
+}
+
+// The whole product.  256 x 256 tiles have the best rate but fill whole rounds of compute units only: where their
+// last round would be thin, they take as many column blocks as full rounds hold and smaller tiles the rest.
+template <int EPI>
+qcf_status run_gemm(const QkvArgs& a_in, int nb, void* ws, size_t ws_bytes, hipStream_t st) {
+  QkvArgs a = a_in;
+  const int nk = a.d_model / kBK;
+  const bool wide = (uint64_t)a.x_rows * (uint64_t)a.d_model * 2u >= (1ull << 32);
+  a.n_tile0 = 0;
+  a.n_tiles = nb;
+  a.part = static_cast<float4*>(ws);
+  if (nb > 65535) return fail(QCF_ERR_UNSUPPORTED, "qkv: too many columns");
+  // (x of 4 GiB and more needs 64-bit addresses per lane: one variant, such calls have plenty of rows)
+  if (wide) return run_ws<Ws128, EPI, true>(a, 1, st);
+  GemmPlan p = plan_ws(a.M, nb, nk, true);
+  if (split_part_bytes(a.M, nb, p) > ws_bytes) p = plan_ws(a.M, nb, nk, false);
+  int quad_blocks = 0;
+  if (nk % 2 == 0) {
+    const int64_t mt = (a.M + 255) / 256;
+    const int per_round = (int)std::min<int64_t>(nb, compute_unit_count() / mt * 2);     // column blocks of one full round
+    double best = p.us;
+    const double whole = quad_us(mt, nb, nk);
+    if (whole < best) { best = whole; quad_blocks = nb; }
+    if (per_round > 0) {
+      for (int r = nb / per_round; r >= 1 && r >= nb / per_round - 1; --r) {
+        const int qb = r * per_round;
+        if (qb >= nb) continue;
+        const double t = quad_us(mt, qb, nk) + plan_ws(a.M, nb - qb, nk, false).us + 2.0;
+        if (t < best) { best = t; quad_blocks = qb; }
+      }
+    } else {
+      const int64_t rounds = mt * ((nb + 1) / 2) / compute_unit_count();
+      const int qb = (int)(rounds * compute_unit_count() / mt * 2);
+      if (qb > 0 && qb < nb) {
+        const double t = quad_us(mt, qb, nk) + plan_ws(a.M, nb - qb, nk, false).us + 2.0;
+        if (t < best) { best = t; quad_blocks = qb; }
+      }
+    }
+  }
+  if (quad_blocks > 0) {
+    a.n_tiles = quad_blocks;
+    QCF_TRY(run_quad<EPI>(a, st));
+    if (quad_blocks == nb) return QCF_OK;
+    a.n_tile0 = quad_blocks;
+    a.n_tiles = nb - quad_blocks;
+    p = plan_ws(a.M, a.n_tiles, nk, false);
+  }
+  switch (p.kind) {
+    case kWs64: return run_ws<Ws64, EPI, false>(a, p.splits, st);
+    case kWs128: return run_ws<Ws128, EPI, false>(a, p.splits, st);
+    default: return run_ws<Ws256, EPI, false>(a, p.splits, st);
+  }
 }
 
 }  // namespace
@@ -812,18 +1118,21 @@ qcf_status launch_rope_table(const int32_t* pos, int64_t M, int head_dim, double
 }
 
 size_t qkv_workspace(const qcf_layer_desc& L, int64_t M) {
-  if (use_mfma(L)) return 0;                       // the GEMM's epilogue forms the rotary factors itself
+  // (the MFMA path needs none; what it asks for lets small M split the contraction)
+  if (use_mfma(L)) return gemm_part_bytes(M, (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim / kBN, L.d_model / kBK);
   return cs_bytes(L, M) + align_up((size_t)M * (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim * sizeof(float), 256);
 }
+
+size_t qkv_workspace_needed(const qcf_layer_desc& L, int64_t M) { return use_mfma(L) ? 0 : qkv_workspace(L, M); }
 
 qcf_status launch_qkv(const qcf_layer_desc& L, const void* x, int64_t x_rows, const int32_t* gather,
                       int64_t M, const void* w, const int32_t* pos, void* q, void* k, void* v,
                       const int32_t* dst_rows, void* k_fused, void* v_fused, int64_t fused_rows, void* ws,
-                      hipStream_t st) {
+                      size_t ws_bytes, hipStream_t st) {
   const int H = L.n_q_heads, Hkv = L.n_kv_heads, D = L.head_dim;
   const int Ntot = (H + 2 * Hkv) * D;
   if (use_mfma(L)) {
-    QkvArgs a;
+    QkvArgs a{};
     a.x = static_cast<const bf16_t*>(x);
     a.w = static_cast<const bf16_t*>(w);
     a.gather = gather;
@@ -832,18 +1141,12 @@ qcf_status launch_qkv(const qcf_layer_desc& L, const void* x, int64_t x_rows, co
     a.x_rows = x_rows;
     a.M = M;
     a.d_model = L.d_model; a.H = H; a.Hkv = Hkv; a.D = D;
-    a.m_tiles = 0; a.n_tiles = 0; a.rows_over_xcds = 0;
     a.q = static_cast<bf16_t*>(q); a.k = static_cast<bf16_t*>(k); a.v = static_cast<bf16_t*>(v);
-    a.plain = 0; a.residual = nullptr;
     a.dst_rows = dst_rows; a.k_fused = static_cast<bf16_t*>(k_fused); a.v_fused = static_cast<bf16_t*>(v_fused);
     a.fused_rows = fused_rows;
-    const bool big = prefer_256_rows(M, Ntot / kBN, L.d_model);
-    // (the specialised kernels address x with 32-bit byte offsets)
-    const bool ws_ok = (uint64_t)x_rows * (uint64_t)L.d_model * 2u < (1ull << 32);
-    if (big && ws_ok) return run_ws<2>(L, a, st);
-    if (big) return run_mfma<2, 4, 4, 1>(L, a, st);
-    if (ws_ok) return run_ws<1>(L, a, st);
-    return run_mfma<2, 2, 2, 2>(L, a, st);
+    if (L.rope_style != 0) return run_gemm<kRopeInter>(a, Ntot / kBN, ws, ws_bytes, st);
+    if (D == 128) return run_gemm<kRopeHalf128>(a, Ntot / kBN, ws, ws_bytes, st);
+    return run_gemm<kRopeHalf64>(a, Ntot / kBN, ws, ws_bytes, st);
   }
   float2* cs = static_cast<float2*>(ws);
   QCF_TRY(launch_rope_table(pos, M, L.head_dim, L.rope_base, cs, st));
@@ -881,36 +1184,27 @@ static bool linear_uses_mfma(const qcf_layer_desc& L, int32_t K, int32_t N) {
 }
 
 size_t linear_workspace(const qcf_layer_desc& L, int64_t M, int32_t K, int32_t N) {
-  if (linear_uses_mfma(L, K, N)) return 0;
+  if (linear_uses_mfma(L, K, N)) return gemm_part_bytes(M, N / kBN, K / kBK);       // (optional, see qkv_workspace)
   return align_up((size_t)M * N * sizeof(float), 256);
 }
 
+size_t linear_workspace_needed(const qcf_layer_desc& L, int64_t M, int32_t K, int32_t N) {
+  return linear_uses_mfma(L, K, N) ? 0 : linear_workspace(L, M, K, N);
+}
+
 qcf_status launch_linear(const qcf_layer_desc& L, const void* x, int64_t M, int32_t K, const void* w, int32_t N,
-                         const void* residual, void* out, void* ws, hipStream_t st) {
+                         const void* residual, void* out, void* ws, size_t ws_bytes, hipStream_t st) {
   if (linear_uses_mfma(L, K, N)) {
     // the projection GEMM with one "query" output of N / 128 heads of 128 columns and no rotation
-    qcf_layer_desc LL = L;
-    LL.d_model = K; LL.n_q_heads = N / kBN; LL.n_kv_heads = 0; LL.head_dim = kBN; LL.rope_style = 0;
-    QkvArgs a;
+    QkvArgs a{};
     a.x = static_cast<const bf16_t*>(x);
     a.w = static_cast<const bf16_t*>(w);
-    a.gather = nullptr;
-    a.pos = nullptr;
-    a.neg2_over_d_log2base = 0.0;
     a.x_rows = M;
     a.M = M;
-    a.d_model = K; a.H = N / kBN; a.Hkv = 0; a.D = kBN;
-    a.m_tiles = 0; a.n_tiles = 0; a.rows_over_xcds = 0;
-    a.q = static_cast<bf16_t*>(out); a.k = nullptr; a.v = nullptr;
-    a.plain = 1;
+    a.d_model = K; a.H = N / kBN; a.D = kBN;
+    a.q = static_cast<bf16_t*>(out);
     a.residual = static_cast<const bf16_t*>(residual);
-    a.dst_rows = nullptr; a.k_fused = nullptr; a.v_fused = nullptr; a.fused_rows = 0;
-    const bool big = prefer_256_rows(M, N / kBN, K);
-    const bool ws_ok = (uint64_t)M * (uint64_t)K * 2u < (1ull << 32);
-    if (big && ws_ok) return run_ws<2>(LL, a, st);
-    if (big) return run_mfma<2, 4, 4, 1>(LL, a, st);
-    if (ws_ok) return run_ws<1>(LL, a, st);
-    return run_mfma<2, 2, 2, 2>(LL, a, st);
+    return residual ? run_gemm<kAdd>(a, N / kBN, ws, ws_bytes, st) : run_gemm<kPlain>(a, N / kBN, ws, ws_bytes, st);
   }
   float* y = static_cast<float*>(ws);
   const int64_t mb = (M + 63) / 64;
