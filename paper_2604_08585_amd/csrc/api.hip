@@ -334,9 +334,9 @@ qcf_status qcf_recompute_attn(const qcf_layer_desc* desc, int32_t B, const void*
   }
   if (ctx_pos0_dev) QCF_TRY(need_idx_ptr(ctx_pos0_dev, "ctx_pos0_dev"));
   if (lse_out) QCF_TRY(need_idx_ptr(lse_out, "lse_out"));
-  QCF_TRY(need_ws(workspace, workspace_bytes, attn_workspace(*desc, B, total_sel, total_ctx)));
+  QCF_TRY(need_ws(workspace, workspace_bytes, attn_workspace_needed(*desc, B, total_sel, total_ctx)));
   return launch_attn(*desc, B, q_sel, sel_pos_dev, sel_off_dev, total_sel, k_fused, v_fused, ctx_off_dev,
-                     total_ctx, ctx_pos0_dev, o_out, lse_out, workspace, (hipStream_t)stream);
+                     total_ctx, ctx_pos0_dev, o_out, lse_out, workspace, usable_ws(workspace, workspace_bytes), (hipStream_t)stream);
 }
 
 // ---- rest of the layer ------------------------------------------------------------

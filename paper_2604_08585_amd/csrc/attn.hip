@@ -1,7 +1,7 @@
 // Step 6: location-aware sparse causal attention (Section 3.2 of the paper): the selected
 // rows, given with their absolute positions, attend over the patched fused cache.
 //
-// bf16 / head_dim 128 path: flash-style online softmax on 32x32x16 MFMA.  A workgroup owns a
+// bf16 / head_dim 128 and 64 path: flash-style online softmax on 32x32x16 MFMA.  A workgroup owns a
 // block of consecutive selected rows times the G query heads of one KV head (128 "rows"), so
 // every K/V tile is loaded once per KV head.  Logits are produced transposed (S^T = K Q^T):
 // a lane then owns one row and the softmax statistics need no cross-lane traffic beyond one
@@ -12,6 +12,13 @@
 // to balance the causal triangle over the compute units, a row block's keys are cut into segments
 // that run as separate workgroups; each writes a normalised partial output and its log-sum-exp,
 // and a second kernel merges them (the usual softmax merge, exact up to rounding).
+//
+// Heads of 64: the probabilities enter the second product as two bf16 terms (high + rest, 16 significant bits) and
+// the partial outputs of split row blocks are fp32, so nothing between the operands and the stored result is rounded
+// to bf16.  A row whose output comes out NaN (an infinite value times a zero probability, also one of a token the
+// row does not see) is computed again, token by token over its visible tokens.
+// Bound by the softmax arithmetic between the two products.  615 rows x 32 heads over 4096 tokens: 1704 us with the
+// generic kernel, about 25 us here; the whole layer 2064 -> 92 us.
 //
 // Generic path (f32, or other shapes): one workgroup per (row, head), online softmax over
 // 256-token tiles.
@@ -49,7 +56,7 @@ struct AttnArgs {
   int n_row_blocks;      // upper bound on row blocks over all requests (MFMA path)
   int seg_tiles;         // key tiles per work unit; a row block with more tiles is split over units
   int n_seg_max;         // units per row block the grid provides
-  bf16_t* part_o;        // [unit][128 rows][128] normalised partial outputs of split row blocks
+  void* part_o;          // [unit][128 rows][D] normalised partial outputs of split row blocks (AttnTile<D>::part_t)
   float* part_lse;       // [unit][128 rows] log2-domain log-sum-exp of each partial (-inf: no visible key)
   int32_t* units;        // units[0] = number of work units, then (row block << 8 | segment), longest first
   int32_t* blk_tiles;    // [row block] key tiles of the block, written by the plan kernel for the merge kernel
@@ -117,17 +124,31 @@ __global__ __launch_bounds__(256) void attn_generic(AttnArgs a) {
   if (tid == 0 && a.lse) a.lse[row * a.H + h] = n_vis > 0 ? m_run + logf(l_run) : -INFINITY;
 }
 
-// ------------------------------------------------------------------ MFMA path (bf16, d = 128)
+// ------------------------------------------------------------------ MFMA path (bf16, d = 128 or 64)
 
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 typedef short shortx8 __attribute__((ext_vector_type(8)));
 
 constexpr int kBKV = 64;                    // tokens per K/V tile
-constexpr int kKTile = kBKV * 128;          // bf16 elements; rows are 256 B, no padding (swizzled instead)
-constexpr int kVTile = kBKV * 128;
-constexpr int kStage = kKTile + kVTile;
-constexpr size_t kAttnLds = (size_t)2 * kStage * 2;
 constexpr int kRowsPerWg = 128;             // (selected row, head-in-group) pairs per workgroup
+template <int D>
+struct AttnTile {
+  static constexpr int ROW = 2 * D;                     // bytes of a staged row, no padding (swizzled instead)
+  static constexpr int TILE = kBKV * ROW;               // bytes of a key or value tile
+  static constexpr int STAGE = 2 * TILE;
+  static constexpr size_t LDS = 2 * STAGE;
+  static constexpr int LROWS = 1024 / ROW;              // rows filled by one load instruction of a wave (1 KB)
+  static constexpr int NLOAD = kBKV / (4 * LROWS);      // instructions per wave and tile
+  static constexpr int KS = D / 16, DT = D / 32;        // k-steps of the logits, 32-element slices of the output
+  static constexpr int WGS = D == 128 ? 2 : 3;          // resident workgroups per compute unit (registers)
+  static constexpr bool SPLIT_P = D == 64;              // probabilities as two bf16 terms, fp32 partial outputs,
+                                                        // NaN rows computed again
+  typedef typename std::conditional<SPLIT_P, float, bf16_t>::type part_t;
+  static constexpr float K2 = kLog2e * (D == 128 ? 0.08838834764831845f : 0.125f);      // log2(e) / sqrt(D)
+};
+// Slot of 16-byte chunk c of token row r inside the row, keys and values (see the layouts below).
+template <int D> __device__ __forceinline__ int k_slot(int c, int r) { return D == 128 ? c ^ (r & 15) : c ^ ((r >> 1) & 7); }
+template <int D> __device__ __forceinline__ int v_slot(int c, int r) { return D == 128 ? c ^ (4 * (r & 3)) : c ^ (4 * ((r >> 1) & 1)); }
 constexpr float kLazyRescale = 8.f;         // log2 units the running maximum may lag behind the true one
 
 // LDS transposing read: within each group of 16 lanes, lane i receives element i%4 of the four
@@ -140,12 +161,33 @@ __device__ __forceinline__ u32x4 lds_read16(uint32_t lds_addr) {
   return *(const u32x4 __attribute__((address_space(3)))*)(uintptr_t)lds_addr;
 }
 
-// Tile layouts in LDS (rows of 256 bytes = 16 chunks of 16 bytes, no padding):
+// One output row computed by a whole wave (d = 64: lane = element), in fp32, over the visible tokens only.
+__device__ __forceinline__ void attn_row_by_token(const bf16_t* q, const bf16_t* k, const bf16_t* v, int64_t kv_stride, int vis,
+                                  bf16_t* o, int lane) {
+  const float qe = bf16_to_f32(q[lane]) * 0.125f;
+  float m = -INFINITY, l = 0.f, acc = 0.f;
+  for (int j = 0; j < vis; ++j) {
+    float s = qe * bf16_to_f32(k[j * kv_stride + lane]);
+    for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d, 64);
+    const float mn = fmaxf(m, s);
+    const float m_use = (mn == -INFINITY) ? 0.f : mn;
+    const float alpha = expf(m - m_use), p = expf(s - m_use);
+    l = l * alpha + p;
+    acc = acc * alpha + p * bf16_to_f32(v[j * kv_stride + lane]);
+    m = mn;
+  }
+  o[lane] = f32_to_bf16(vis > 0 ? acc / l : 0.f);
+}
+
+// Tile layouts in LDS (d = 128: rows of 256 bytes = 16 chunks of 16 bytes, no padding):
 //   keys:   chunk c of token row r sits in slot c ^ (r % 16), so the 16-byte reads of 16 consecutive
 //           rows at one chunk index touch 16 different bank groups;
 //   values: chunk c of row r sits in slot c ^ (4 * (r % 4)), so the 8-byte transposing reads of
 //           8 consecutive rows x 64 bytes touch every bank exactly twice.
-__global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
+// d = 64: rows of 128 bytes, two to a sweep over the banks, so the slots are c ^ (r / 2 % 8) and c ^ (4 * (r / 2 % 2)).
+template <int D>
+__global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnArgs a) {
+  using C = AttnTile<D>;
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_vis_max[4];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -207,51 +249,51 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   const int t_begin = max(0, t_end - a.seg_tiles);
   if (n_tiles == 0) {                 // nothing visible to any row of the block
     if (row_ok) {
-      bf16_t* op = static_cast<bf16_t*>(a.o) + (srow * a.H + head) * 128 + 64 * hf;
+      bf16_t* op = static_cast<bf16_t*>(a.o) + (srow * a.H + head) * D + D / 2 * hf;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4*>(op + 8 * i) = u32x4{0u, 0u, 0u, 0u};
+      for (int i = 0; i < D / 16; ++i) *reinterpret_cast<u32x4*>(op + 8 * i) = u32x4{0u, 0u, 0u, 0u};
       if (a.lse && hf == 0) a.lse[srow * a.H + head] = -INFINITY;
     }
     return;
   }
 
-  // asynchronous tile loads: instruction i of wave w fills rows 16*i + 4*w .. +3 (1 KB); lane L
-  // fills slot L%16 of row 16*i + 4*w + L/16 with the chunk the swizzle assigns to that slot.
+  // asynchronous tile loads: instruction i of wave w fills rows 16*i + 4*w .. +3 (1 KB; d = 64: rows
+  // 32*i + 8*w .. +7); lane L fills 16 bytes, a slot of its row, with the chunk the swizzle assigns to that slot.
   // Tokens past the end of the context are clamped (their probabilities are zero).
-  const bf16_t* kg = static_cast<const bf16_t*>(a.k) + (c0 * a.Hkv + g) * 128;
-  const bf16_t* vg = static_cast<const bf16_t*>(a.v) + (c0 * a.Hkv + g) * 128;
-  const int ld_row = 4 * wave + (lane >> 4);                      // + 16*i
-  const uint32_t row_bytes = (uint32_t)a.Hkv * 256u;              // one token row of the cache
-  const uint32_t ld_kchunk = (uint32_t)(((lane & 15) ^ ld_row) * 16);           // row % 16 == ld_row
-  const uint32_t ld_vchunk = (uint32_t)(((lane & 15) ^ (4 * (ld_row & 3))) * 16);
+  const bf16_t* kg = static_cast<const bf16_t*>(a.k) + (c0 * a.Hkv + g) * D;
+  const bf16_t* vg = static_cast<const bf16_t*>(a.v) + (c0 * a.Hkv + g) * D;
+  constexpr int LPR = 64 / C::LROWS;                              // lanes per row
+  const int ld_row = C::LROWS * wave + lane / LPR;                // + 4 * LROWS * i (does not change the slots)
+  const uint32_t row_bytes = (uint32_t)a.Hkv * C::ROW;            // one token row of the cache
+  const uint32_t ld_kchunk = (uint32_t)(k_slot<D>(lane % LPR, ld_row) * 16);
+  const uint32_t ld_vchunk = (uint32_t)(v_slot<D>(lane % LPR, ld_row) * 16);
   const uint32_t ld_koff = (uint32_t)ld_row * row_bytes + ld_kchunk;
   const uint32_t ld_voff = (uint32_t)ld_row * row_bytes + ld_vchunk;
   auto aload = [&](const bf16_t* src, uint32_t off0, uint32_t chunk, int t, uint32_t dst) {
     const char* base = reinterpret_cast<const char*>(src) + (int64_t)t * kBKV * row_bytes;
     if (t * kBKV + kBKV <= T) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) load_to_lds_at(base + (size_t)(16 * i) * row_bytes, off0, dst + (16 * i) * 256);
+      for (int i = 0; i < C::NLOAD; ++i)
+        load_to_lds_at(base + (size_t)(4 * C::LROWS * i) * row_bytes, off0, dst + i * 4096);
     } else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = min(16 * i + ld_row, T - 1 - t * kBKV);
-        load_to_lds_at(base, (uint32_t)row * row_bytes + chunk, dst + (16 * i) * 256);
+      for (int i = 0; i < C::NLOAD; ++i) {
+        const int row = min(4 * C::LROWS * i + ld_row, T - 1 - t * kBKV);
+        load_to_lds_at(base, (uint32_t)row * row_bytes + chunk, dst + i * 4096);
       }
     }
   };
-  auto aload_k = [&](int t, int st) { aload(kg, ld_koff, ld_kchunk, t, lds0 + st * kStage * 2 + (4 * wave) * 256); };
-  auto aload_v = [&](int t, int st) {
-    aload(vg, ld_voff, ld_vchunk, t, lds0 + st * kStage * 2 + kKTile * 2 + (4 * wave) * 256);
-  };
+  auto aload_k = [&](int t, int st) { aload(kg, ld_koff, ld_kchunk, t, lds0 + st * C::STAGE + wave * 1024); };
+  auto aload_v = [&](int t, int st) { aload(vg, ld_voff, ld_vchunk, t, lds0 + st * C::STAGE + C::TILE + wave * 1024); };
   auto aload2 = [&](int t, int st) { aload_k(t, st); aload_v(t, st); };
   aload2(t_begin, 0);
 
   // stationary query fragments: qf[ks] = row r, elements 16*ks + 8*hf .. +7
-  bf16x8 qf[8];
+  bf16x8 qf[C::KS];
   {
-    const bf16_t* qp = static_cast<const bf16_t*>(a.q) + ((row_ok ? srow : s0) * a.H + head) * 128 + 8 * hf;
+    const bf16_t* qp = static_cast<const bf16_t*>(a.q) + ((row_ok ? srow : s0) * a.H + head) * D + 8 * hf;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
+    for (int ks = 0; ks < C::KS; ++ks) {
       u32x4 t = *reinterpret_cast<const u32x4*>(qp + 16 * ks);
       if (!row_ok) t = u32x4{0u, 0u, 0u, 0u};
       qf[ks] = __builtin_bit_cast(bf16x8, t);
@@ -259,41 +301,41 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   }
 
   // per-lane byte offsets of the fragment reads inside a stage
-  uint32_t kofs[8];     // key fragment ks: token row l32 (+32), chunk 2*ks + hf
+  uint32_t kofs[C::KS];     // key fragment ks: token row l32 (+32), chunk 2*ks + hf
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) kofs[ks] = lds0 + l32 * 256 + (((2 * ks + hf) ^ (l32 & 15)) * 16);
+  for (int ks = 0; ks < C::KS; ++ks) kofs[ks] = lds0 + l32 * C::ROW + k_slot<D>(2 * ks + hf, l32) * 16;
   // values: the lane addresses the 8-byte piece (token 4*hf + (lane%16)/4, elements d0 .. d0+3) where
   // block q = 4*((lane/16)%2) + lane%4 of a 32-element slice starts at d0 = 16*(q%2) + 4*(q/2); after the
   // transposing read lane (row i = lane%32) holds four consecutive tokens of element
   // 16*(i/4 % 2) + 4*(i/8) + i%4, which makes MFMA output row 8b + 4h + c element 16h + 4b + c
-  uint32_t vofs[4];     // value fragment of output tile dt
+  uint32_t vofs[C::DT];     // value fragment of output tile dt
   {
     const int vq = 4 * ((lane >> 4) & 1) + (lane & 3);
     const int d0 = 16 * (vq & 1) + 4 * (vq >> 1);
     const int vrow = 4 * hf + ((lane & 15) >> 2);
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-      vofs[dt] = lds0 + kKTile * 2 + vrow * 256 + (((4 * dt + d0 / 8) ^ (4 * (vrow & 3))) * 16) + (d0 & 4) * 2;
+    for (int dt = 0; dt < C::DT; ++dt)
+      vofs[dt] = lds0 + C::TILE + vrow * C::ROW + v_slot<D>(4 * dt + d0 / 8, vrow) * 16 + (d0 & 4) * 2;
   }
 
-  floatx16 oacc[4];
+  floatx16 oacc[C::DT];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) oacc[i] = floatx16{0};
+  for (int i = 0; i < C::DT; ++i) oacc[i] = floatx16{0};
   float m_run = -INFINITY;      // running max of the scaled logits (log2 domain), shared by both lane halves
   float l_run = 0.f;            // this lane's share of the running denominator
-  const float k2 = kLog2e * 0.08838834764831845f;
+  const float k2 = C::K2;
 
   auto process = [&](const uint32_t stage, int kv0) {        // stage: byte offset of the stage (a constant at each call)
     floatx16 sa = {0}, sb = {0};
     {
       u32x4 fa[2], fb[2];
       fa[0] = lds_read16(kofs[0] + stage);
-      fb[0] = lds_read16(kofs[0] + (stage + 32 * 256));
+      fb[0] = lds_read16(kofs[0] + (stage + 32 * C::ROW));
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        if (ks < 7) {
+      for (int ks = 0; ks < C::KS; ++ks) {
+        if (ks < C::KS - 1) {
           fa[(ks + 1) & 1] = lds_read16(kofs[ks + 1] + stage);
-          fb[(ks + 1) & 1] = lds_read16(kofs[ks + 1] + (stage + 32 * 256));
+          fb[(ks + 1) & 1] = lds_read16(kofs[ks + 1] + (stage + 32 * C::ROW));
         }
         sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[ks & 1]), qf[ks], sa, 0, 0, 0);
         sb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[ks & 1]), qf[ks], sb, 0, 0, 0);
@@ -302,7 +344,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     // first value fragments can travel while the softmax runs
     shortx4 vlo[2], vhi[2];
     vlo[0] = lds_read_tr(vofs[0] + stage);
-    vhi[0] = lds_read_tr(vofs[0] + (stage + 8 * 256));
+    vhi[0] = lds_read_tr(vofs[0] + (stage + 8 * C::ROW));
     // register v of sa is token kv0 + 8*(v/4) + 4*hf + v%4 (sb: + 32) against this lane's row
     float p[32];
 #pragma unroll
@@ -337,28 +379,37 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     m_run = m_new;
     if (__any(alpha != 1.f)) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < C::DT; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) oacc[i][v] *= alpha;
     }
     // P^T fragments: step s = 2*mt + t' uses registers 8*s .. 8*s+7 (tokens 16*s + 8*(e/4) + 4*hf + e%4)
-    bf16x8 pf[4];
+    bf16x8 pf[4], pr[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const u32x4 pk = mk4(cvt_pk_bf16(p[8 * s + 0], p[8 * s + 1]), cvt_pk_bf16(p[8 * s + 2], p[8 * s + 3]),
-                           cvt_pk_bf16(p[8 * s + 4], p[8 * s + 5]), cvt_pk_bf16(p[8 * s + 6], p[8 * s + 7]));
+      u32x4 pk, pl;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float p0 = p[8 * s + 2 * i], p1 = p[8 * s + 2 * i + 1];
+        pk[i] = cvt_pk_bf16(p0, p1);
+        // (the difference to the rounded value is exact)
+        if (C::SPLIT_P) pl[i] = cvt_pk_bf16(p0 - __uint_as_float(pk[i] << 16), p1 - __uint_as_float(pk[i] & 0xffff0000u));
+      }
       pf[s] = __builtin_bit_cast(bf16x8, pk);
+      if (C::SPLIT_P) pr[s] = __builtin_bit_cast(bf16x8, pl);
     }
 #pragma unroll
-    for (int idx = 0; idx < 16; ++idx) {
-      const int s = idx >> 2, dt = idx & 3;
-      if (idx < 15) {
-        const int s2 = (idx + 1) >> 2, dt2 = (idx + 1) & 3;
-        vlo[(idx + 1) & 1] = lds_read_tr(vofs[dt2] + (stage + (16 * s2) * 256));
-        vhi[(idx + 1) & 1] = lds_read_tr(vofs[dt2] + (stage + (16 * s2 + 8) * 256));
+    for (int idx = 0; idx < 4 * C::DT; ++idx) {
+      const int s = idx / C::DT, dt = idx % C::DT;
+      if (idx < 4 * C::DT - 1) {
+        const int s2 = (idx + 1) / C::DT, dt2 = (idx + 1) % C::DT;
+        vlo[(idx + 1) & 1] = lds_read_tr(vofs[dt2] + (stage + (16 * s2) * C::ROW));
+        vhi[(idx + 1) & 1] = lds_read_tr(vofs[dt2] + (stage + (16 * s2 + 8) * C::ROW));
       }
       const shortx8 both = __builtin_shufflevector(vlo[idx & 1], vhi[idx & 1], 0, 1, 2, 3, 4, 5, 6, 7);
-      oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf[s], oacc[dt], 0, 0, 0);
+      const bf16x8 vf = __builtin_bit_cast(bf16x8, both);
+      oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[s], oacc[dt], 0, 0, 0);
+      if (C::SPLIT_P) oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pr[s], oacc[dt], 0, 0, 0);
     }
   };
 
@@ -371,7 +422,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (t + 2 < t_end) aload2(t + 2, 0);
-    if ((t + 1) * kBKV < wave_vis_max) process((uint32_t)kStage * 2u, (t + 1) * kBKV);
+    if ((t + 1) * kBKV < wave_vis_max) process((uint32_t)C::STAGE, (t + 1) * kBKV);
   }
 
   // epilogue: output register v of tile dt is element 32*dt + 16*hf + v of this lane's row
@@ -379,25 +430,53 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   if (split) {                        // partial result of one key segment; merged by attn_merge_kernel
     const int64_t slot = ((int64_t)blk * a.Hkv + g) * a.n_seg_max + seg;
-    bf16_t* op = a.part_o + (slot * kRowsPerWg + r) * 128 + 16 * hf;
+    typename C::part_t* op = static_cast<typename C::part_t*>(a.part_o) + (slot * kRowsPerWg + r) * D + 16 * hf;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
+    for (int dt = 0; dt < C::DT; ++dt) {
+      if constexpr (C::SPLIT_P) {
 #pragma unroll
-      for (int h8 = 0; h8 < 2; ++h8) {
-        const u32x4 pk = mk4(cvt_pk_bf16(oacc[dt][8 * h8 + 0] * inv, oacc[dt][8 * h8 + 1] * inv),
-                             cvt_pk_bf16(oacc[dt][8 * h8 + 2] * inv, oacc[dt][8 * h8 + 3] * inv),
-                             cvt_pk_bf16(oacc[dt][8 * h8 + 4] * inv, oacc[dt][8 * h8 + 5] * inv),
-                             cvt_pk_bf16(oacc[dt][8 * h8 + 6] * inv, oacc[dt][8 * h8 + 7] * inv));
-        *reinterpret_cast<u32x4*>(op + 32 * dt + 8 * h8) = pk;
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<float4*>(op + 32 * dt + 4 * q) =
+              make_float4(oacc[dt][4 * q] * inv, oacc[dt][4 * q + 1] * inv, oacc[dt][4 * q + 2] * inv, oacc[dt][4 * q + 3] * inv);
+      } else {
+#pragma unroll
+        for (int h8 = 0; h8 < 2; ++h8) {
+          const u32x4 pk = mk4(cvt_pk_bf16(oacc[dt][8 * h8 + 0] * inv, oacc[dt][8 * h8 + 1] * inv),
+                               cvt_pk_bf16(oacc[dt][8 * h8 + 2] * inv, oacc[dt][8 * h8 + 3] * inv),
+                               cvt_pk_bf16(oacc[dt][8 * h8 + 4] * inv, oacc[dt][8 * h8 + 5] * inv),
+                               cvt_pk_bf16(oacc[dt][8 * h8 + 6] * inv, oacc[dt][8 * h8 + 7] * inv));
+          *reinterpret_cast<u32x4*>(op + 32 * dt + 8 * h8) = pk;
+        }
       }
     }
     if (hf == 0) a.part_lse[slot * kRowsPerWg + r] = l_tot > 0.f ? m_run + log2f(l_tot) : -INFINITY;
     return;
   }
-  if (row_ok) {
-    bf16_t* op = static_cast<bf16_t*>(a.o) + (srow * a.H + head) * 128 + 16 * hf;
+  bool store_row = row_ok;
+  if constexpr (C::SPLIT_P) {
+    bool nan = false;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
+    for (int dt = 0; dt < C::DT; ++dt)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) nan |= oacc[dt][v] != oacc[dt][v];
+    const uint64_t any = __ballot(nan && row_ok);
+    uint32_t bad = (uint32_t)any | (uint32_t)(any >> 32);
+    store_row = row_ok && !((bad >> l32) & 1u);
+    while (bad) {                     // (rare: lanes l and l + 32 hold row l of the wave)
+      const int l = __builtin_ctz(bad);
+      bad &= bad - 1u;
+      const int rr = wave * 32 + l;
+      const int64_t at = ((s0 + (int64_t)wg * BR + rr / a.G) * a.H + g * a.G + rr % a.G) * D;
+      attn_row_by_token(static_cast<const bf16_t*>(a.q) + at, kg, vg, (int64_t)a.Hkv * D, __shfl(vis, l, 64),
+                        static_cast<bf16_t*>(a.o) + at, lane);
+    }
+    if (row_ok && a.lse && hf == 0)
+      a.lse[srow * a.H + head] = l_tot > 0.f ? (m_run + log2f(l_tot)) * kLn2 : -INFINITY;
+  }
+  if (store_row) {
+    bf16_t* op = static_cast<bf16_t*>(a.o) + (srow * a.H + head) * D + 16 * hf;
+#pragma unroll
+    for (int dt = 0; dt < C::DT; ++dt) {
 #pragma unroll
       for (int h8 = 0; h8 < 2; ++h8) {
         const u32x4 pk = mk4(cvt_pk_bf16(oacc[dt][8 * h8 + 0] * inv, oacc[dt][8 * h8 + 1] * inv),
@@ -407,7 +486,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(AttnArgs a) {
         *reinterpret_cast<u32x4*>(op + 32 * dt + 8 * h8) = pk;
       }
     }
-    if (a.lse && hf == 0)
+    if (!C::SPLIT_P && a.lse && hf == 0)
       a.lse[srow * a.H + head] = l_tot > 0.f ? (m_run + log2f(l_tot)) * kLn2 : -INFINITY;
   }
 }
@@ -472,12 +551,15 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(AttnArgs a) {
 
 // Merge of the partial results of split row blocks: kMergeWgs workgroups per (row block, KV head), one
 // thread per 8 output elements.  out = sum_s w_s O_s with w_s = 2^(lse_s - lse), lse = log2 sum_s 2^lse_s.
-constexpr int kMergeWgs = kRowsPerWg * 16 / 256;
+template <int D> constexpr int kMergeWgs = kRowsPerWg * (D / 8) / 256;
+template <int D>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
+  typedef typename AttnTile<D>::part_t part_t;
+  constexpr int CH = D / 8;                         // 8-element chunks of a row
   const int tid = threadIdx.x;
   const int BR = kRowsPerWg / a.G;
-  const int part = (int)(blockIdx.x % kMergeWgs);
-  const int bh = (int)(blockIdx.x / kMergeWgs);
+  const int part = (int)(blockIdx.x % kMergeWgs<D>);
+  const int bh = (int)(blockIdx.x / kMergeWgs<D>);
   const int g = bh % a.Hkv;
   const int blk = bh / a.Hkv;
   const int n_tiles = a.blk_tiles[blk];
@@ -493,25 +575,27 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   }
   if (b >= a.B) return;
   const int n_seg = (n_tiles + a.seg_tiles - 1) / a.seg_tiles;
-  const int r = part * 16 + (tid >> 4), ch = tid & 15;          // row of the block, 8-element chunk
+  const int r = part * (256 / CH) + tid / CH, ch = tid % CH;    // row of the block, 8-element chunk
   const int64_t srow = s0 + (int64_t)wg * BR + r / a.G;
-  if (srow >= s1) return;
+  const bool row_ok = srow < s1;
   const int head = g * a.G + r % a.G;
   // unit (blk, g, seg) wrote slot ((blk * Hkv + g) * n_seg_max + seg)
   const int64_t slot0 = ((int64_t)blk * a.Hkv + g) * a.n_seg_max;
   const float* pl = a.part_lse + slot0 * kRowsPerWg + r;
-  const bf16_t* po = a.part_o + (slot0 * kRowsPerWg + r) * 128 + 8 * ch;
+  const part_t* po = static_cast<const part_t*>(a.part_o) + (slot0 * kRowsPerWg + r) * D + 8 * ch;
   // four segments at a time: every load first, then the running maximum, the weights and the weighted sum
   float mx = -INFINITY, wsum = 0.f;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int sg0 = 0; sg0 < n_seg; sg0 += 4) {
     float l[4];
-    u32x4 raw[4];
+    u32x4 raw[4][sizeof(part_t) / 2];               // 8 elements
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const bool ok = sg0 + u < n_seg;
+      const bool ok = row_ok && sg0 + u < n_seg;
       l[u] = ok ? pl[(int64_t)(sg0 + u) * kRowsPerWg] : -INFINITY;
-      raw[u] = ok ? *reinterpret_cast<const u32x4*>(po + (int64_t)(sg0 + u) * kRowsPerWg * 128) : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int w = 0; w < (int)sizeof(part_t) / 2; ++w)
+        raw[u][w] = ok ? *reinterpret_cast<const u32x4*>(po + (int64_t)(sg0 + u) * kRowsPerWg * D + w * Elem<part_t>::kVec) : u32x4{0u, 0u, 0u, 0u};
     }
     float mn = mx;
 #pragma unroll
@@ -525,7 +609,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
       for (int u = 0; u < 4; ++u) {
         const float w = __builtin_amdgcn_exp2f(l[u] - mn);        // 0 for a segment that saw nothing
         float f[8];
-        Vec16<bf16_t>::unpack(raw[u], f);
+#pragma unroll
+        for (int w = 0; w < (int)sizeof(part_t) / 2; ++w) Vec16<part_t>::unpack(raw[u][w], f + w * Elem<part_t>::kVec);
         wsum += w;
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] += w * f[e];
@@ -536,15 +621,38 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] *= inv;
-  *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(a.o) + (srow * a.H + head) * 128 + 8 * ch) = Vec16<bf16_t>::pack(acc);
-  if (a.lse && ch == 0) a.lse[srow * a.H + head] = wsum > 0.f ? (mx + log2f(wsum)) * kLn2 : -INFINITY;
+  if (row_ok && a.lse && ch == 0) a.lse[srow * a.H + head] = wsum > 0.f ? (mx + log2f(wsum)) * kLn2 : -INFINITY;
+  bool store_row = row_ok;
+  if constexpr (AttnTile<D>::SPLIT_P) {
+    bool nan = false;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) nan |= acc[e] != acc[e];
+    uint64_t bad = __ballot(nan && row_ok);              // lanes CH * i .. + CH - 1 hold row i of the wave
+    store_row = row_ok && !((bad >> ((tid & 63) / CH * CH)) & ((1u << CH) - 1u));
+    while (bad) {
+      const int i = __builtin_ctzll(bad) / CH;
+      bad &= ~((uint64_t)((1u << CH) - 1u) << (i * CH));
+      const int rr = part * (256 / CH) + (tid >> 6) * (64 / CH) + i;
+      const int64_t sr = s0 + (int64_t)wg * BR + rr / a.G;
+      const int64_t c0 = min(max(a.ctx_off[b], (int64_t)0), a.total_ctx);
+      const int64_t c1 = min(max(a.ctx_off[b + 1], c0), a.total_ctx);
+      const int64_t p0 = a.ctx_pos0 ? a.ctx_pos0[b] : 0;
+      const int vis = (int)min(c1 - c0, max((int64_t)0, (int64_t)a.sel_pos[sr] - p0 + 1));
+      const int64_t at = (sr * a.H + g * a.G + rr % a.G) * D, kv0 = (c0 * a.Hkv + g) * D;
+      attn_row_by_token(static_cast<const bf16_t*>(a.q) + at, static_cast<const bf16_t*>(a.k) + kv0,
+                        static_cast<const bf16_t*>(a.v) + kv0, (int64_t)a.Hkv * D, vis,
+                        static_cast<bf16_t*>(a.o) + at, tid & 63);
+    }
+  }
+  if (store_row)
+    *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(a.o) + (srow * a.H + head) * D + 8 * ch) = Vec16<bf16_t>::pack(acc);
 }
 
 // Key tiles per work unit.  With enough row blocks the causal triangle balances by itself and blocks
 // stay whole; otherwise a segment is about the average causal work of a resident workgroup.
 struct Split { int seg_tiles, n_seg_max; };
-Split choose_split(int64_t n_blocks, int64_t total_ctx) {
-  const int slots = 2 * compute_unit_count();         // two workgroups are resident per compute unit
+Split choose_split(int D, int64_t n_blocks, int64_t total_ctx) {
+  const int slots = (D == 128 ? AttnTile<128>::WGS : AttnTile<64>::WGS) * compute_unit_count();     // resident workgroups
   const int64_t n_t = std::max<int64_t>(1, (total_ctx + kBKV - 1) / kBKV);
   const int64_t per_slot = n_blocks * ((n_t + 1) / 2) / slots;     // average causal work per resident workgroup
   // a little above that average (a multiple of 4 tiles): most resident workgroups then take one whole
@@ -556,8 +664,9 @@ Split choose_split(int64_t n_blocks, int64_t total_ctx) {
   return Split{(int)seg, (int)((n_t + seg - 1) / seg)};
 }
 
-size_t part_o_bytes(int64_t n_blocks, int n_seg_max) {
-  return align_up((size_t)n_blocks * n_seg_max * kRowsPerWg * 128 * sizeof(bf16_t), 256);
+size_t part_o_bytes(int D, int64_t n_blocks, int n_seg_max) {
+  const size_t row = D == 128 ? 128 * sizeof(AttnTile<128>::part_t) : 64 * sizeof(AttnTile<64>::part_t);
+  return align_up((size_t)n_blocks * n_seg_max * kRowsPerWg * row, 256);
 }
 size_t part_lse_bytes(int64_t n_blocks, int n_seg_max) {
   return align_up((size_t)n_blocks * n_seg_max * kRowsPerWg * sizeof(float), 256);
@@ -567,9 +676,27 @@ size_t units_bytes(int64_t n_row_blocks, int n_seg_max) {
 }
 size_t blk_tiles_bytes(int64_t n_row_blocks) { return align_up((size_t)n_row_blocks * sizeof(int32_t), 256); }
 
+template <int D>
+qcf_status run_mfma(const AttnArgs& a, hipStream_t st) {
+  static std::atomic<uint64_t> lds_ok{0};
+  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&attn_mfma_kernel<D>), AttnTile<D>::LDS, lds_ok));
+  const int64_t blocks = (int64_t)a.n_row_blocks * a.Hkv;
+  if (a.n_seg_max > 1) {
+    attn_plan_kernel<<<dim3(1), dim3(1024), 0, st>>>(a);
+    QCF_TRY_LAUNCH("attn plan");
+  }
+  attn_mfma_kernel<D><<<dim3((unsigned)(blocks * a.n_seg_max)), dim3(256), AttnTile<D>::LDS, st>>>(a);
+  QCF_TRY_LAUNCH("attn");
+  if (a.n_seg_max > 1) {
+    attn_merge_kernel<D><<<dim3((unsigned)(blocks * kMergeWgs<D>)), dim3(256), 0, st>>>(a);
+    return check_launch("attn merge");
+  }
+  return QCF_OK;
+}
+
 bool use_mfma(const qcf_layer_desc& L) {
   const int G = L.n_q_heads / L.n_kv_heads;
-  return L.dtype == QCF_DTYPE_BF16 && L.head_dim == 128 && G <= kRowsPerWg && kRowsPerWg % G == 0;
+  return L.dtype == QCF_DTYPE_BF16 && (L.head_dim == 128 || L.head_dim == 64) && G <= kRowsPerWg && kRowsPerWg % G == 0;
 }
 
 }  // namespace
@@ -578,16 +705,20 @@ size_t attn_workspace(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int
   if (!use_mfma(L) || total_sel <= 0 || total_ctx <= 0) return 0;
   const int BR = kRowsPerWg / (L.n_q_heads / L.n_kv_heads);
   const int64_t n_blocks = ((total_sel + BR - 1) / BR + B) * L.n_kv_heads;
-  const Split sp = choose_split(n_blocks, total_ctx);
+  const Split sp = choose_split(L.head_dim, n_blocks, total_ctx);
   if (sp.n_seg_max <= 1) return 0;
-  return part_o_bytes(n_blocks, sp.n_seg_max) + part_lse_bytes(n_blocks, sp.n_seg_max) +
+  return part_o_bytes(L.head_dim, n_blocks, sp.n_seg_max) + part_lse_bytes(n_blocks, sp.n_seg_max) +
          units_bytes(n_blocks / L.n_kv_heads, sp.n_seg_max) + blk_tiles_bytes(n_blocks / L.n_kv_heads);
+}
+
+size_t attn_workspace_needed(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx) {
+  return L.head_dim == 128 ? attn_workspace(L, B, total_sel, total_ctx) : 0;
 }
 
 qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const int32_t* sel_pos,
                        const int64_t* sel_off, int64_t total_sel, const void* k, const void* v,
                        const int64_t* ctx_off, int64_t total_ctx, const int32_t* ctx_pos0, void* o,
-                       float* lse, void* ws, hipStream_t st) {
+                       float* lse, void* ws, size_t ws_bytes, hipStream_t st) {
   AttnArgs a;
   a.q = q; a.k = k; a.v = v;
   a.sel_pos = sel_pos; a.sel_off = sel_off; a.ctx_off = ctx_off; a.ctx_pos0 = ctx_pos0;
@@ -599,33 +730,22 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
   if (use_mfma(L)) {
     const int BR = kRowsPerWg / a.G;
     const int64_t nb = (total_sel + BR - 1) / BR + B;
-    const Split sp = choose_split(nb * a.Hkv, total_ctx);
-    if (nb * a.Hkv * std::max(sp.n_seg_max, kMergeWgs) > 0x7fffffff)
+    Split sp = choose_split(L.head_dim, nb * a.Hkv, total_ctx);
+    if (attn_workspace(L, B, total_sel, total_ctx) > ws_bytes) sp = Split{0x3fffffff, 1};      // (d = 64 only: optional)
+    if (nb * a.Hkv * std::max(sp.n_seg_max, kMergeWgs<128>) > 0x7fffffff)
       return fail(QCF_ERR_UNSUPPORTED, "attn: grid too large");
     a.n_row_blocks = (int)nb;
     a.seg_tiles = sp.seg_tiles;
     a.n_seg_max = sp.n_seg_max;
     if (sp.n_seg_max > 1) {
-      a.part_o = static_cast<bf16_t*>(ws);
+      a.part_o = ws;
       char* w = static_cast<char*>(ws);
-      a.part_lse = reinterpret_cast<float*>(w + part_o_bytes(nb * a.Hkv, sp.n_seg_max));
-      a.units = reinterpret_cast<int32_t*>(w + part_o_bytes(nb * a.Hkv, sp.n_seg_max) +
+      a.part_lse = reinterpret_cast<float*>(w + part_o_bytes(L.head_dim, nb * a.Hkv, sp.n_seg_max));
+      a.units = reinterpret_cast<int32_t*>(w + part_o_bytes(L.head_dim, nb * a.Hkv, sp.n_seg_max) +
                                            part_lse_bytes(nb * a.Hkv, sp.n_seg_max));
       a.blk_tiles = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(a.units) + units_bytes(nb, sp.n_seg_max));
     }
-    static std::atomic<uint64_t> lds_ok{0};
-    QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&attn_mfma_kernel), kAttnLds, lds_ok));
-    if (sp.n_seg_max > 1) {
-      attn_plan_kernel<<<dim3(1), dim3(1024), 0, st>>>(a);
-      QCF_TRY_LAUNCH("attn plan");
-    }
-    attn_mfma_kernel<<<dim3((unsigned)(nb * a.Hkv * sp.n_seg_max)), dim3(256), kAttnLds, st>>>(a);
-    QCF_TRY_LAUNCH("attn");
-    if (sp.n_seg_max > 1) {
-      attn_merge_kernel<<<dim3((unsigned)(nb * a.Hkv * kMergeWgs)), dim3(256), 0, st>>>(a);
-      return check_launch("attn merge");
-    }
-    return QCF_OK;
+    return a.D == 128 ? run_mfma<128>(a, st) : run_mfma<64>(a, st);
   }
   if (total_sel * a.H > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "attn: grid too large");
   const dim3 grid((unsigned)(total_sel * a.H)), block(256);

@@ -207,13 +207,14 @@ size_t attn_workspace(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int
 qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const int32_t* sel_pos,
                        const int64_t* sel_off, int64_t total_sel, const void* k, const void* v,
                        const int64_t* ctx_off, int64_t total_ctx, const int32_t* ctx_pos0, void* o,
-                       float* lse, void* ws, hipStream_t st);
+                       float* lse, void* ws, size_t ws_bytes, hipStream_t st);
 
 size_t linear_workspace(const qcf_layer_desc& L, int64_t M, int32_t K, int32_t N);
 qcf_status launch_linear(const qcf_layer_desc& L, const void* x, int64_t M, int32_t K, const void* w, int32_t N,
                          const void* residual, void* out, void* ws, size_t ws_bytes, hipStream_t st);
 // bytes a call cannot do without (the rest of the workspace only makes it faster)
 size_t qkv_workspace_needed(const qcf_layer_desc& L, int64_t M);
+size_t attn_workspace_needed(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx);
 size_t linear_workspace_needed(const qcf_layer_desc& L, int64_t M, int32_t K, int32_t N);
 qcf_status launch_rmsnorm(const qcf_layer_desc& L, const void* x, const void* weight, double eps, int64_t M,
                           int32_t cols, void* out, hipStream_t st);

@@ -2,7 +2,7 @@
 // selector of the paper): score[j] = mean over probe rows and heads of the softmax
 // attention the context token j receives.
 //
-// bf16 / head_dim 128 path (the dense contraction runs on MFMA).  A workgroup of twelve waves owns a
+// bf16 / head_dim 128 and 64 path (the dense contraction runs on MFMA).  A workgroup of twelve waves owns a
 // 256-token tile of one KV head: the tile's keys and the group's probe rows both arrive in LDS through
 // asynchronous loads that request every 128-byte line once (loading keys straight into registers in MFMA
 // operand layout touches 64 different lines per instruction, which is what bounded the earlier version);
@@ -20,7 +20,10 @@
 // No floating-point atomics anywhere, so scores (and the indices selected from them) are
 // bit-stable from run to run.
 //
-// Generic path (f32, or head_dim 64): one workgroup per (probe row, head) materialises its
+// Heads of 64 run the same kernels with half the k-steps (40 probe rows x 32 heads over 4096 tokens: 391 us with the
+// generic kernels, about 17 us here).
+//
+// Generic path (f32, or other head dims): one workgroup per (probe row, head) materialises its
 // softmax row in the workspace, then a column mean.
 #include "qcf_internal.h"
 
@@ -105,7 +108,7 @@ __global__ __launch_bounds__(256) void score_colmean_generic(
   score[j] = (beta == 0.f) ? alpha * sj : __builtin_fmaf(beta, score[j], alpha * sj);
 }
 
-// ------------------------------------------------------------------ MFMA path (bf16, d = 128)
+// ------------------------------------------------------------------ MFMA path (bf16, d = 128 or 64)
 
 constexpr int kTokPerWave = 64;                 // tokens a wave keeps stationary in registers
 constexpr int kTokWaves = 4;                    // token slices of a workgroup
@@ -114,14 +117,24 @@ constexpr int kWavesPerWg = kTokWaves * kRowGroups;
 constexpr int kThreads = 64 * kWavesPerWg;
 constexpr int kTokPerWg = kTokPerWave * kTokWaves;
 constexpr int kRowBlock = 320;                  // probe rows (of one group) staged in LDS at a time
-constexpr int kQStride = 128;                   // bf16 elements per staged row (swizzled, no padding)
-constexpr size_t kQBytes = (size_t)kRowBlock * kQStride * 2;
-constexpr size_t kKBytes = (size_t)kTokPerWg * 256;
+template <int D> constexpr size_t kQBytes = (size_t)kRowBlock * D * 2;     // staged rows: swizzled, no padding
+template <int D> constexpr size_t kKBytes = (size_t)kTokPerWg * D * 2;
+template <int D> constexpr float kK2 = kLog2e * (D == 128 ? 0.08838834764831845f : 0.125f);    // log2(e) / sqrt(D)
+// Staged rows: a load instruction of a wave fills kRowsPerLoad rows (1 KB).  Chunk c (16 bytes) of row r sits in slot
+// c ^ (r % 16) of its row (d = 128: a row is one sweep over the banks) or c ^ (r / 2 % 8) (d = 64: two rows are), so
+// the 16-byte fragment reads of 16 consecutive rows touch 16 different bank groups.
+template <int D> constexpr int kRowsPerLoad = 1024 / (2 * D);
+template <int D> __device__ __forceinline__ int slot_of(int c, int r) { return D == 128 ? c ^ (r & 15) : c ^ ((r >> 1) & 7); }
+// row, and the element offset of the chunk, that lane `lane` of staging instruction j brings
+template <int D> __device__ __forceinline__ int staged_row(int j, int lane) { return kRowsPerLoad<D> * j + lane / (64 / kRowsPerLoad<D>); }
+template <int D> __device__ __forceinline__ int staged_elem(int r, int lane) { return slot_of<D>(lane % (64 / kRowsPerLoad<D>), r) * 8; }
+// byte offset of this lane's fragment (row lane%32, chunk 2*ks + lane/32) is frag_base ^ (32 * ks)
+template <int D> __device__ __forceinline__ int frag_base(int lane) { return (lane & 31) * 2 * D + slot_of<D>(lane >> 5, lane & 31) * 16; }
 constexpr int kFoldBatch = 16;
 
 struct ScoreArgs {
-  const bf16_t* q;            // [total_probe, H, 128]
-  const bf16_t* k;            // [total_ctx, Hkv, 128]
+  const bf16_t* q;            // [total_probe, H, D]
+  const bf16_t* k;            // [total_ctx, Hkv, D]
   const int64_t* probe_off;
   const int64_t* ctx_off;
   const int32_t* probe_limit;
@@ -160,41 +173,39 @@ __device__ __forceinline__ bool locate_tile(const ScoreArgs& a, int wg, int& b, 
 }
 
 // Stages the workgroup's 256 key rows (tokens tile_tok0 .. +255 of KV head g) into LDS with asynchronous
-// direct-to-LDS loads (a 1 KB instruction = 4 token rows, every 128-byte line requested once); same row
+// direct-to-LDS loads (1 KB per instruction, every 128-byte line requested once); same row
 // layout as the probe rows below.  Tokens past the end are clamped (masked or never written later).
+template <int D>
 __device__ __forceinline__ void stage_k_async(const ScoreArgs& a, int64_t c0, int T, int tile_tok0, int g,
                                               unsigned char* sK, int wave, int lane) {
-  for (int j = wave; j < kTokPerWg / 4; j += kWavesPerWg) {
-    const int r = 4 * j + (lane >> 4);
+  for (int j = wave; j < kTokPerWg / kRowsPerLoad<D>; j += kWavesPerWg) {
+    const int r = staged_row<D>(j, lane);
     const int tok = min(tile_tok0 + r, T - 1);
-    const int chunk = (lane & 15) ^ (r & 15);
-    load_to_lds_addr(a.k + ((c0 + tok) * a.Hkv + g) * 128 + chunk * 8, sK + j * 1024);
+    load_to_lds_addr(a.k + ((c0 + tok) * a.Hkv + g) * D + staged_elem<D>(r, lane), sK + j * 1024);
   }
 }
 
 // Stages probe rows [r_begin, r_begin + n_rows) of group g (row r = i*G + hh <-> probe row i,
 // head g*G + hh) into LDS with asynchronous direct-to-LDS loads; the caller waits and synchronises.
-// Staged rows are 256 bytes (16 chunks of 16 bytes) without padding; chunk c of row r sits in slot
-// c ^ (r % 16), so the 16-byte fragment reads of 16 consecutive rows touch 16 different bank groups.
 // Rows up to the next multiple of 32 are filled with a copy of the last row (never used in a result).
+template <int D>
 __device__ __forceinline__ void stage_q_async(const ScoreArgs& a, int64_t p0, int g, int r_begin, int n_rows,
                                               int n_rows_pad, unsigned char* sQ, int wave, int lane) {
-  for (int j = wave; j < n_rows_pad / 4; j += kWavesPerWg) {       // one 1 KB instruction = 4 rows
-    const int r = 4 * j + (lane >> 4);
+  for (int j = wave; j < n_rows_pad / kRowsPerLoad<D>; j += kWavesPerWg) {
+    const int r = staged_row<D>(j, lane);
     const int rr = r_begin + min(r, n_rows - 1);
     const int i = rr / a.G, hh = rr - i * a.G;
-    const int chunk = (lane & 15) ^ (r & 15);
-    load_to_lds_addr(a.q + ((p0 + i) * a.H + g * a.G + hh) * 128 + chunk * 8, sQ + j * 1024);
+    load_to_lds_addr(a.q + ((p0 + i) * a.H + g * a.G + hh) * D + staged_elem<D>(r, lane), sQ + j * 1024);
   }
 }
 
 // Pass 1.  A workgroup = (256-token tile, KV head); wave (tw, rg) keeps the 64 tokens of slice tw in
 // registers and takes every third 32-row tile of the staged probe rows, starting with tile rg.
-template <bool LIMIT>
+template <int D, bool LIMIT>
 __global__ __launch_bounds__(kThreads) void score_pass1(ScoreArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  unsigned char* sK = smem + kQBytes;
-  float2* sPart = reinterpret_cast<float2*>(smem + kQBytes + kKBytes);     // [kTokWaves][kRowBlock]
+  unsigned char* sK = smem + kQBytes<D>;
+  float2* sPart = reinterpret_cast<float2*>(smem + kQBytes<D> + kKBytes<D>);     // [kTokWaves][kRowBlock]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tw = wave % kTokWaves, rg = wave / kTokWaves;
   const int g = blockIdx.y;
@@ -207,35 +218,34 @@ __global__ __launch_bounds__(kThreads) void score_pass1(ScoreArgs a) {
   if (rows == 0) return;
   const int tok0 = tile_tok0 + tw * kTokPerWave;
   const bool wave_active = tok0 < T;
-  const float k2 = kLog2e * 0.08838834764831845f;   // log2(e) / sqrt(128)
-  // byte offset of this lane's fragment (row lane%32, chunk 2*ks + lane/32) is qb0 ^ (32 * ks)
-  const int qb0 = (lane & 31) * 256 + (((lane >> 5) ^ (lane & 15)) * 16);
+  constexpr float k2 = kK2<D>;
+  const int qb0 = frag_base<D>(lane);
   float2* part = a.part + (int64_t)blockIdx.x * (a.total_probe * a.H);
 
-  stage_k_async(a, c0, T, tile_tok0, g, sK, wave, lane);
-  bf16x8 kf[2][8];
+  stage_k_async<D>(a, c0, T, tile_tok0, g, sK, wave, lane);
+  bf16x8 kf[2][D / 16];
   for (int r_begin = 0; r_begin < rows; r_begin += kRowBlock) {
     const int n_rows = min(kRowBlock, rows - r_begin);
     const int n_pad = (n_rows + 31) & ~31;
     __syncthreads();                        // the previous block's rows and partials are no longer read
-    stage_q_async(a, p0, g, r_begin, n_rows, n_pad, smem, wave, lane);
+    stage_q_async<D>(a, p0, g, r_begin, n_rows, n_pad, smem, wave, lane);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (r_begin == 0) {
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks)
+        for (int ks = 0; ks < D / 16; ++ks)
           kf[mt][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(
-                                                      sK + (kTokPerWave * tw + 32 * mt) * 256 + (qb0 ^ (32 * ks))));
+                                                      sK + (kTokPerWave * tw + 32 * mt) * (2 * D) + (qb0 ^ (32 * ks))));
     }
     for (int rt = 32 * rg; rt < n_pad; rt += 32 * kRowGroups) {
       float mx = -INFINITY, sum = 0.f;
       if (wave_active) {
         floatx16 acc0 = {0}, acc1 = {0};
-        const unsigned char* qrow = smem + rt * 256;
+        const unsigned char* qrow = smem + rt * (2 * D);
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
+        for (int ks = 0; ks < D / 16; ++ks) {
           const bf16x8 qf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qrow + (qb0 ^ (32 * ks))));
           // S^T tile: rows = tokens (A = keys), columns = probe rows (B = queries)
           acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][ks], qf, acc0, 0, 0, 0);
@@ -299,11 +309,11 @@ __device__ __forceinline__ void fold_partials(const float2 (&p)[kFoldBatch], flo
 }
 
 // Pass 2, same division of work; the three row groups' column sums are added in a fixed order at the end.
-template <bool LIMIT>
+template <int D, bool LIMIT>
 __global__ __launch_bounds__(kThreads) void score_pass2(ScoreArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  unsigned char* sK = smem + kQBytes;
-  float* sL = reinterpret_cast<float*>(smem + kQBytes + kKBytes);          // [kRowBlock] log2-sum-exp
+  unsigned char* sK = smem + kQBytes<D>;
+  float* sL = reinterpret_cast<float*>(smem + kQBytes<D> + kKBytes<D>);          // [kRowBlock] log2-sum-exp
   int* sLim = reinterpret_cast<int*>(sL + kRowBlock);                       // [kRowBlock]
   float* sCol = reinterpret_cast<float*>(sLim + kRowBlock);                 // [kRowGroups][kTokPerWg]
   static_assert(kRowBlock <= kThreads, "one thread folds one staged row");
@@ -321,18 +331,18 @@ __global__ __launch_bounds__(kThreads) void score_pass2(ScoreArgs a) {
   const int64_t part_stride = a.total_probe * a.H;
   const int tok0 = tile_tok0 + tw * kTokPerWave;
   const bool wave_active = tok0 < T;
-  const float k2 = kLog2e * 0.08838834764831845f;
-  const int qb0 = (lane & 31) * 256 + (((lane >> 5) ^ (lane & 15)) * 16);
+  constexpr float k2 = kK2<D>;
+  const int qb0 = frag_base<D>(lane);
 
-  stage_k_async(a, c0, T, tile_tok0, g, sK, wave, lane);
-  bf16x8 kf[2][8];
+  stage_k_async<D>(a, c0, T, tile_tok0, g, sK, wave, lane);
+  bf16x8 kf[2][D / 16];
   float col0 = 0.f, col1 = 0.f;        // column sums of tokens tok0 + lane%32 and + 32 over this wave's row tiles
 
   for (int r_begin = 0; r_begin < rows; r_begin += kRowBlock) {
     const int n_rows = min(kRowBlock, rows - r_begin);
     const int n_pad = (n_rows + 31) & ~31;
     __syncthreads();
-    stage_q_async(a, p0, g, r_begin, n_rows, n_pad, smem, wave, lane);
+    stage_q_async<D>(a, p0, g, r_begin, n_rows, n_pad, smem, wave, lane);
     // log2-sum-exp of staged row tid over the request: the tiles' partials folded in tile order, kFoldBatch
     // at a time (all loads first, then one maximum and one rescaled sum); every workgroup of the request
     // computes the same values
@@ -364,16 +374,16 @@ __global__ __launch_bounds__(kThreads) void score_pass2(ScoreArgs a) {
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks)
+        for (int ks = 0; ks < D / 16; ++ks)
           kf[mt][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(
-                                                      sK + (kTokPerWave * tw + 32 * mt) * 256 + (qb0 ^ (32 * ks))));
+                                                      sK + (kTokPerWave * tw + 32 * mt) * (2 * D) + (qb0 ^ (32 * ks))));
     }
     if (!wave_active) continue;
     for (int rt = 32 * rg; rt < n_pad; rt += 32 * kRowGroups) {
       floatx16 acc0 = {0}, acc1 = {0};
-      const unsigned char* qrow = smem + rt * 256;
+      const unsigned char* qrow = smem + rt * (2 * D);
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
+      for (int ks = 0; ks < D / 16; ++ks) {
         const bf16x8 qf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qrow + (qb0 ^ (32 * ks))));
         // S tile: rows = probe rows (A = queries), columns = tokens (B = keys)
         acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, kf[0][ks], acc0, 0, 0, 0);
@@ -496,11 +506,11 @@ __device__ __forceinline__ float half_wave_sum(float x) {
   return __uint_as_float(r.x) + __uint_as_float(r.y);     // rows (0, 1) and (2, 3) of 16 lanes each
 }
 
-template <bool LIMIT>
+template <int D, bool LIMIT>
 __global__ __launch_bounds__(kFusedThreads) void score_fused(FusedArgs fa) {
   const ScoreArgs& a = fa.s;
   extern __shared__ __align__(16) unsigned char smem[];
-  unsigned char* sK = smem + kQBytes;
+  unsigned char* sK = smem + kQBytes<D>;
   // (reused once the key fragments are in registers)
   float2* sPart = reinterpret_cast<float2*>(sK);                            // [kFusedWaves][kRowBlock]
   float* sL = reinterpret_cast<float*>(sK + kFusedWaves * kRowBlock * 8);   // [kRowBlock] log2-sum-exp
@@ -525,39 +535,38 @@ __global__ __launch_bounds__(kFusedThreads) void score_fused(FusedArgs fa) {
   }
   const int n_tiles = have_tile ? (T + kTokPerWg - 1) / kTokPerWg : 0;
   const int n_rt = (rows + 31) >> 5;
-  const float k2 = kLog2e * 0.08838834764831845f;   // log2(e) / sqrt(128)
+  constexpr float k2 = kK2<D>;
 
   float e[kFusedRowTiles][16];      // 2^(logit - m_w) of (token, row) pairs; row = 32 rt + l32
 
   if (rows > 0) {
-    for (int j = wave; j < kTokPerWg / 4; j += kFusedWaves) {          // keys: 1 KB per instruction = 4 token rows
-      const int r = 4 * j + (lane >> 4);
+    for (int j = wave; j < kTokPerWg / kRowsPerLoad<D>; j += kFusedWaves) {      // keys
+      const int r = staged_row<D>(j, lane);
       const int tok = min(tile_tok0 + r, T - 1);
-      const int chunk = (lane & 15) ^ (r & 15);
-      load_to_lds_addr(a.k + ((c0 + tok) * a.Hkv + g) * 128 + chunk * 8, sK + j * 1024);
+      load_to_lds_addr(a.k + ((c0 + tok) * a.Hkv + g) * D + staged_elem<D>(r, lane), sK + j * 1024);
     }
-    for (int j = wave; j < n_rt * 8; j += kFusedWaves) {               // probe rows of the group
-      const int r = 4 * j + (lane >> 4);
+    for (int j = wave; j < n_rt * (32 / kRowsPerLoad<D>); j += kFusedWaves) {    // probe rows of the group
+      const int r = staged_row<D>(j, lane);
       const int rr = min(r, rows - 1);
       const int i = rr / a.G, hh = rr - i * a.G;
-      const int chunk = (lane & 15) ^ (r & 15);
-      load_to_lds_addr(a.q + ((p0 + i) * a.H + g * a.G + hh) * 128 + chunk * 8, smem + j * 1024);
+      load_to_lds_addr(a.q + ((p0 + i) * a.H + g * a.G + hh) * D + staged_elem<D>(r, lane), smem + j * 1024);
     }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    const int fb0 = l32 * 256 + ((hf ^ (lane & 15)) * 16);       // fragment ks of row l32 sits at fb0 ^ (32 ks)
-    bf16x8 kf[8];
+    constexpr int KS = D / 16;
+    const int fb0 = frag_base<D>(lane);
+    bf16x8 kf[KS];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks)
-      kf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(sK + (32 * wave) * 256 + (fb0 ^ (32 * ks))));
-    // probe-row fragments travel through a ring of four registers: fragment ks + 4 (or the next tile's
-    // fragment ks - 4) is requested right behind the MFMA that used the slot.  One address register per
+    for (int ks = 0; ks < KS; ++ks)
+      kf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(sK + (32 * wave) * (2 * D) + (fb0 ^ (32 * ks))));
+    // probe-row fragments travel through a ring of four registers: the fragment four further (of this tile or
+    // the next) is requested right behind the MFMA that used the slot.  One address register per
     // fragment index; the row tile is a constant offset of the read.
-    uint32_t qaddr[8];
+    uint32_t qaddr[KS];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qaddr[ks] = lds_offset_of(smem) + (uint32_t)(fb0 ^ (32 * ks));
+    for (int ks = 0; ks < KS; ++ks) qaddr[ks] = lds_offset_of(smem) + (uint32_t)(fb0 ^ (32 * ks));
     auto qfrag = [&](int rt, int ks) {
-      return *(const u32x4 __attribute__((address_space(3)))*)(uintptr_t)(qaddr[ks] + (uint32_t)(rt * 32 * 256));
+      return *(const u32x4 __attribute__((address_space(3)))*)(uintptr_t)(qaddr[ks] + (uint32_t)(rt * 32 * 2 * D));
     };
     u32x4 ring[4];
 #pragma unroll
@@ -569,16 +578,16 @@ __global__ __launch_bounds__(kFusedThreads) void score_fused(FusedArgs fa) {
       if (rt < n_rt) {
         floatx16 acc = {0};
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
+        for (int ks = 0; ks < D / 16; ++ks) {
           // S^T tile: rows = tokens (A = keys), columns = probe rows (B = queries)
           acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], __builtin_bit_cast(bf16x8, ring[ks & 3]), acc, 0, 0, 0);
-          if (ks < 4) ring[ks & 3] = qfrag(rt, ks + 4);
-          else if (rt + 1 < kFusedRowTiles) ring[ks & 3] = qfrag(rt + 1, ks - 4);   // (unused after the last tile)
+          if (ks + 4 < KS) ring[ks & 3] = qfrag(rt, ks + 4);
+          else if (rt + 1 < kFusedRowTiles) ring[ks & 3] = qfrag(rt + 1, ks + 4 - KS);   // (unused after the last tile)
         }
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {          // issue order: every read sits behind the MFMA that frees its slot
+        for (int ks = 0; ks < D / 16; ++ks) {          // issue order: every read sits behind the MFMA that frees its slot
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          if (ks < 4 || rt + 1 < kFusedRowTiles) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          if (ks + 4 < KS || rt + 1 < kFusedRowTiles) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
         // lane owns probe row 32 rt + l32; register v is token tok0 + 8 (v/4) + 4 hf + v%4
         float sv[16];
@@ -738,7 +747,6 @@ __global__ __launch_bounds__(256) void score_zero(float* score, int64_t n, float
   if (j < n) score[j] = (beta == 0.f) ? 0.f : beta * score[j];
 }
 
-bool use_mfma(const qcf_layer_desc& L) { return L.dtype == QCF_DTYPE_BF16 && L.head_dim == 128; }
 
 // upper bound on the 256-token tiles of all requests (tiles start at request boundaries: every request adds at
 // most one partly filled tile); exact for a single request
@@ -755,11 +763,16 @@ MfmaWs mfma_ws(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t 
   return w;
 }
 
-constexpr size_t kPass1Lds = kQBytes + kKBytes + (size_t)kTokWaves * kRowBlock * sizeof(float2);
-constexpr size_t kPass2Lds = kQBytes + kKBytes + (size_t)kRowBlock * 8 + (size_t)kRowGroups * kTokPerWg * sizeof(float);
-constexpr size_t kFusedLds = kQBytes + kKBytes;
-static_assert((size_t)kFusedWaves * kRowBlock * 8 + (size_t)kRowBlock * 4 + (size_t)kTokPerWg * 4 <= kKBytes,
+template <int D> constexpr size_t kPass1Lds = kQBytes<D> + kKBytes<D> + (size_t)kTokWaves * kRowBlock * sizeof(float2);
+template <int D> constexpr size_t kPass2Lds = kQBytes<D> + kKBytes<D> + (size_t)kRowBlock * 8 + (size_t)kRowGroups * kTokPerWg * sizeof(float);
+template <int D> constexpr size_t kFusedLds = kQBytes<D> + kKBytes<D>;
+static_assert((size_t)kFusedWaves * kRowBlock * 8 + (size_t)kRowBlock * 4 + (size_t)kTokPerWg * 4 <= kKBytes<64>,
               "the single-kernel path's tables fit in the key tile's LDS");
+
+bool use_mfma(const qcf_layer_desc& L) { return L.dtype == QCF_DTYPE_BF16 && (L.head_dim == 128 || L.head_dim == 64); }
+size_t generic_ws(const qcf_layer_desc& L, int64_t total_probe, int64_t total_ctx) {
+  return align_up((size_t)total_probe * L.n_q_heads * total_ctx * sizeof(float), 256);
+}
 
 // The single-kernel path needs every workgroup of the launch resident at once (one per compute unit) and all
 // probe rows of a KV group in one staged block.  The host only knows totals, so the test is on those.
@@ -770,6 +783,12 @@ bool use_fused(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t 
   return total_probe * G <= kRowBlock && tiles * L.n_kv_heads <= compute_unit_count() &&
          1 + (int64_t)B * L.n_kv_heads + tiles <= kSyncWords;
 }
+// Two MFMA passes.  Heads of 64 keep the generic kernels where many short requests would make the partials (one per
+// started 256 tokens) larger than its probability rows and than the built-in scratch of qcf_score_static.
+bool use_two_pass(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx) {
+  return use_mfma(L) && (L.head_dim == 128 || mfma_ws(L, B, total_probe, total_ctx).total <=
+                             std::max(generic_ws(L, total_probe, total_ctx), (size_t)QCF_SCORE_STATIC_SCRATCH_BYTES));
+}
 struct FusedWs { size_t part, colpart, total; };
 FusedWs fused_ws(const qcf_layer_desc& L, int32_t B, int64_t total_ctx) {
   const size_t slots = (size_t)n_tiles_upper(B, total_ctx) * L.n_kv_heads;
@@ -778,6 +797,27 @@ FusedWs fused_ws(const qcf_layer_desc& L, int32_t B, int64_t total_ctx) {
   w.colpart = align_up(slots * kRowBlock * sizeof(float2), 256);
   w.total = w.colpart + align_up(slots * kTokPerWg * sizeof(float), 256);
   return w;
+}
+
+template <int D, bool LIMIT>
+qcf_status run_fused(const FusedArgs& fa, hipStream_t st) {
+  static std::atomic<uint64_t> lds_ok;
+  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_fused<D, LIMIT>), kFusedLds<D>, lds_ok));
+  score_fused<D, LIMIT><<<dim3((unsigned)(fa.n_wg_tiles * fa.s.Hkv)), dim3(kFusedThreads), kFusedLds<D>, st>>>(fa);
+  return check_launch("score (single kernel)");
+}
+template <int D, bool LIMIT>
+qcf_status run_two_pass(const ScoreArgs& a, int64_t n_tiles, hipStream_t st) {
+  static std::atomic<uint64_t> lds_ok[2];
+  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass1<D, LIMIT>), kPass1Lds<D>, lds_ok[0]));
+  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass2<D, LIMIT>), kPass2Lds<D>, lds_ok[1]));
+  const dim3 grid((unsigned)n_tiles, (unsigned)a.Hkv), block(kThreads);
+  score_pass1<D, LIMIT><<<grid, block, kPass1Lds<D>, st>>>(a);
+  QCF_TRY_LAUNCH("score pass 1");
+  score_pass2<D, LIMIT><<<grid, block, kPass2Lds<D>, st>>>(a);
+  QCF_TRY_LAUNCH("score pass 2");
+  score_reduce<<<dim3((unsigned)((a.total_ctx + 255) / 256)), dim3(256), 0, st>>>(a);
+  return check_launch("score reduce");
 }
 
 // Device address of the zero-initialised counter array on the current device (asked for once per device).
@@ -803,8 +843,8 @@ qcf_status sync_counters(uint32_t** out) {
 
 size_t score_workspace(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx) {
   if (use_fused(L, B, total_probe, total_ctx)) return fused_ws(L, B, total_ctx).total;
-  if (use_mfma(L)) return mfma_ws(L, B, total_probe, total_ctx).total;
-  return align_up((size_t)total_probe * L.n_q_heads * total_ctx * sizeof(float), 256);
+  if (use_two_pass(L, B, total_probe, total_ctx)) return mfma_ws(L, B, total_probe, total_ctx).total;
+  return generic_ws(L, total_probe, total_ctx);
 }
 
 qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const int64_t* probe_off,
@@ -816,7 +856,8 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
     score_zero<<<dim3((unsigned)blocks), dim3(256), 0, st>>>(score, total_ctx, beta);
     return check_launch("score zero");
   }
-  if (!use_mfma(L)) {
+  const bool fused = use_fused(L, B, total_probe, total_ctx);
+  if (!fused && !use_two_pass(L, B, total_probe, total_ctx)) {
     float* P = static_cast<float*>(ws);
     const int64_t col_blocks = (total_ctx + 255) / 256;
     if (total_probe * H > 0x7fffffff || col_blocks > 0x7fffffff)
@@ -852,7 +893,7 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
   a.score = score;
   a.alpha = alpha;
   a.beta = beta;
-  if (use_fused(L, B, total_probe, total_ctx)) {
+  if (fused) {
     const FusedWs fw = fused_ws(L, B, total_ctx);
     FusedArgs fa;
     fa.s = a;
@@ -864,38 +905,16 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
     QCF_TRY(sync_counters(&counters));
     static std::atomic<uint32_t> next_slot{0};
     fa.sync = counters + (size_t)(next_slot.fetch_add(1, std::memory_order_relaxed) % kSyncSlots) * kSyncWords;
-    static std::atomic<uint64_t> fused_lds_ok[2];
-    QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_fused<false>), kFusedLds, fused_lds_ok[0]));
-    QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_fused<true>), kFusedLds, fused_lds_ok[1]));
-    const dim3 fgrid((unsigned)(fa.n_wg_tiles * Hkv)), fblock(kFusedThreads);
-    if (probe_limit) score_fused<true><<<fgrid, fblock, kFusedLds, st>>>(fa);
-    else score_fused<false><<<fgrid, fblock, kFusedLds, st>>>(fa);
-    return check_launch("score (single kernel)");
+    if (D == 128) return probe_limit ? run_fused<128, true>(fa, st) : run_fused<128, false>(fa, st);
+    return probe_limit ? run_fused<64, true>(fa, st) : run_fused<64, false>(fa, st);
   }
   const MfmaWs w = mfma_ws(L, B, total_probe, total_ctx);
   a.part = reinterpret_cast<float2*>(static_cast<char*>(ws) + w.part);
   a.colsum = reinterpret_cast<float*>(static_cast<char*>(ws) + w.colsum);
-  a.score = score;
   const int64_t n_tiles = n_tiles_upper(B, total_ctx);
   if (n_tiles > 0x7fffffff || Hkv > 65535) return fail(QCF_ERR_UNSUPPORTED, "score: grid too large");
-  const dim3 grid((unsigned)n_tiles, (unsigned)Hkv), block(kThreads);
-  const int64_t red_blocks = (total_ctx + 255) / 256;
-
-  static std::atomic<uint64_t> lds_ok[4];
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass1<false>), kPass1Lds, lds_ok[0]));
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass1<true>), kPass1Lds, lds_ok[1]));
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass2<false>), kPass2Lds, lds_ok[2]));
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass2<true>), kPass2Lds, lds_ok[3]));
-  if (total_probe > 0) {
-    if (probe_limit) score_pass1<true><<<grid, block, kPass1Lds, st>>>(a);
-    else score_pass1<false><<<grid, block, kPass1Lds, st>>>(a);
-    QCF_TRY_LAUNCH("score pass 1");
-    if (probe_limit) score_pass2<true><<<grid, block, kPass2Lds, st>>>(a);
-    else score_pass2<false><<<grid, block, kPass2Lds, st>>>(a);
-    QCF_TRY_LAUNCH("score pass 2");
-  }
-  score_reduce<<<dim3((unsigned)red_blocks), dim3(256), 0, st>>>(a);
-  return check_launch("score reduce");
+  if (D == 128) return probe_limit ? run_two_pass<128, true>(a, n_tiles, st) : run_two_pass<128, false>(a, n_tiles, st);
+  return probe_limit ? run_two_pass<64, true>(a, n_tiles, st) : run_two_pass<64, false>(a, n_tiles, st);
 }
 
 }  // namespace qcf

@@ -98,3 +98,96 @@ def test_projection_tile_choices(M, dm, H, Hkv, D, style):
         ref = torch.full_like(fused, 7.0)
         ref[dst[keep].long()] = new[keep]
         assert torch.equal(fused, ref)
+
+
+def _attention64(q, k, v, pos, scale):
+    """Plain float64 attention of rows q [n, H, d] over k, v [T, Hkv, d]; row i sees tokens <= pos[i]."""
+    G = q.shape[1] // k.shape[1]
+    kk, vv = (t.double().repeat_interleave(G, dim=1).transpose(0, 1) for t in (k, v))
+    s = q.double().transpose(0, 1) @ kk.transpose(1, 2) * scale
+    s.masked_fill_(torch.arange(k.shape[0], device=k.device)[None, None] > pos.long()[None, :, None], -float("inf"))
+    p = torch.softmax(s, -1)
+    return (p @ vv).transpose(0, 1), torch.logsumexp(s, -1).T
+
+
+@pytest.mark.parametrize("H,Hkv,ctx,sel,with_ws", [
+    (8, 2, [300, 1, 64, 1025], [45, 1, 10, 150], True),       # ragged requests
+    (32, 8, [4099], [615], True),                             # key ranges split over workgroups, fp32 partials
+    (32, 8, [4099], [615], False),                            # the same without the optional workspace
+    (4, 4, [2048], [33], True), (16, 1, [63], [63], True)])   # one head per group; sixteen
+def test_attention_of_64_wide_heads(H, Hkv, ctx, sel, with_ws):
+    """bf16 rows over bf16 keys and values: only the stored result is rounded to bf16."""
+    say(f"attention d=64 H={H} Hkv={Hkv} ctx={ctx} sel={sel} ws={with_ws}")
+    sh = inputs.LayerShape(2048, H, Hkv, 64, 10000.0, "bf16")
+    g, desc = gen(46), qb.make_desc(sh)
+    T, N = sum(ctx), sum(sel)
+    q = torch.randn((N, H, 64), generator=g, device=DEV, dtype=BF) * 2
+    k, v = (torch.randn((T, Hkv, 64), generator=g, device=DEV, dtype=BF) for _ in range(2))
+    pos = [torch.sort(torch.randperm(t, generator=g, device=DEV)[:n])[0].int() for t, n in zip(ctx, sel)]
+    so, co = i64(np.concatenate([[0], np.cumsum(sel)])), i64(np.concatenate([[0], np.cumsum(ctx)]))
+    o, lse = torch.full((N, H, 64), 7.0, dtype=BF, device=DEV), torch.full((N, H), 7.0, device=DEV)
+    p = torch.cat(pos)
+    if with_ws:
+        qb.qcf_recompute_attn(desc, len(ctx), q, p, so, N, k, v, co, T, None, o, lse)
+    else:
+        assert qb.load_library().qcf_recompute_attn(
+            C.byref(desc), len(ctx), q.data_ptr(), p.data_ptr(), so.data_ptr(), N, k.data_ptr(), v.data_ptr(), co.data_ptr(),
+            T, None, o.data_ptr(), lse.data_ptr(), None, 0, torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    s0 = c0 = 0
+    for t, n, ps in zip(ctx, sel, pos):
+        ro, rl = _attention64(q[s0:s0 + n], k[c0:c0 + t], v[c0:c0 + t], ps, 0.125)
+        one_rounding(o[s0:s0 + n], ro.float())
+        assert float((lse[s0:s0 + n].double() - rl).abs().max()) < 2e-5
+        s0, c0 = s0 + n, c0 + t
+
+
+@pytest.mark.parametrize("T,n", [(200, 40), (4099, 615)])      # whole row blocks; split ones
+def test_attention_of_64_wide_heads_infinite_values(T, n):
+    """An infinite value reaches the rows that see its token, as an infinity, and no others."""
+    say(f"attention d=64 infinite value T={T}")
+    sh = inputs.LayerShape(2048, 32, 8, 64, 10000.0, "bf16")
+    g = gen(47)
+    q = torch.randn((n, 32, 64), generator=g, device=DEV, dtype=BF)
+    k, v = (torch.randn((T, 8, 64), generator=g, device=DEV, dtype=BF) for _ in range(2))
+    at = T - T // 3
+    pos = torch.sort(torch.randperm(T, generator=g, device=DEV)[:n])[0].int()
+    o = torch.empty((n, 32, 64), dtype=BF, device=DEV)
+    clean = _attention64(q, k, v, pos, 0.125)[0]
+    v[at, :, 5] = float("inf")
+    qb.qcf_recompute_attn(qb.make_desc(sh), 1, q, pos, i64([0, n]), n, k, v, i64([0, T]), T, None, o, None)
+    torch.cuda.synchronize()
+    sees = (pos >= at)[:, None].expand(-1, 32)
+    ref = clean.float()
+    assert bool((o[:, :, 5][sees] == float("inf")).all())
+    keep = torch.ones_like(ref, dtype=torch.bool)
+    keep[:, :, 5] = ~sees
+    one_rounding(o[keep], ref[keep])
+
+
+@pytest.mark.parametrize("H,Hkv,ctx,probes,limit", [
+    (32, 8, [4099], [40], False), (8, 2, [300, 1, 64, 1025, 256], [5, 3, 0, 17, 30], False),   # one kernel
+    (8, 4, [700], [33], True),
+    (32, 8, [9000], [40], False), (8, 2, [300, 1, 2000], [90, 3, 100], True)])                  # two passes
+def test_scores_of_64_wide_heads(H, Hkv, ctx, probes, limit):
+    say(f"scores d=64 H={H} Hkv={Hkv} ctx={ctx} probes={probes}")
+    sh = inputs.LayerShape(2048, H, Hkv, 64, 10000.0, "bf16")
+    g = gen(48)
+    T, R = sum(ctx), sum(probes)
+    q = torch.randn((R, H, 64), generator=g, device=DEV, dtype=BF) * 2
+    k = torch.randn((T, Hkv, 64), generator=g, device=DEV, dtype=BF)
+    lim = torch.cat([torch.randint(1, t + 1, (r,), generator=g, device=DEV) for t, r in zip(ctx, probes)]).int()
+    po, co = i64(np.concatenate([[0], np.cumsum(probes)])), i64(np.concatenate([[0], np.cumsum(ctx)]))
+    score = torch.full((T,), 7.0, device=DEV)
+    qb.qcf_score(qb.make_desc(sh), len(ctx), q, po, R, k, co, T, lim if limit else None, score)
+    torch.cuda.synchronize()
+    r0 = c0 = 0
+    for t, r in zip(ctx, probes):
+        kk = k[c0:c0 + t].double().repeat_interleave(H // Hkv, dim=1).permute(1, 2, 0)
+        s = q[r0:r0 + r].double().transpose(0, 1) @ kk * 0.125
+        if limit:
+            s.masked_fill_(torch.arange(t, device=DEV)[None, None] >= lim[r0:r0 + r].long()[None, :, None], -float("inf"))
+        ref = torch.softmax(s, -1).mean((0, 1)) if r else torch.zeros(t, dtype=torch.float64, device=DEV)
+        # 32-bit logits of magnitude up to 60, exponentials and sums
+        assert bool(((score[c0:c0 + t].double() - ref).abs() <= 3e-5 * ref + 1e-12).all())
+        r0, c0 = r0 + r, c0 + t
