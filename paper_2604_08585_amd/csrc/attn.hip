@@ -140,7 +140,7 @@ struct AttnTile {
   static constexpr int LROWS = 1024 / ROW;              // rows filled by one load instruction of a wave (1 KB)
   static constexpr int NLOAD = kBKV / (4 * LROWS);      // instructions per wave and tile
   static constexpr int KS = D / 16, DT = D / 32;        // k-steps of the logits, 32-element slices of the output
-  static constexpr int WGS = D == 128 ? 2 : 3;          // resident workgroups per compute unit (registers)
+  static constexpr int WGS = 2;                         // resident workgroups per compute unit (registers)
   static constexpr bool SPLIT_P = D == 64;              // probabilities as two bf16 terms, fp32 partial outputs,
                                                         // NaN rows computed again
   typedef typename std::conditional<SPLIT_P, float, bf16_t>::type part_t;
@@ -325,40 +325,34 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
   float l_run = 0.f;            // this lane's share of the running denominator
   const float k2 = C::K2;
 
-  auto process = [&](const uint32_t stage, int kv0) {        // stage: byte offset of the stage (a constant at each call)
-    floatx16 sa = {0}, sb = {0};
-    {
-      u32x4 fa[2], fb[2];
-      fa[0] = lds_read16(kofs[0] + stage);
-      fb[0] = lds_read16(kofs[0] + (stage + 32 * C::ROW));
+  // logits of one 64-token tile, its softmax, and its share of the output.  The logits are computed one tile ahead
+  // (register v of s[0] is token kv0 + 8*(v/4) + 4*hf + v%4 against this lane's row, s[1]: + 32), so that their MFMAs
+  // run between the exponentials of the current tile; `stage` and `next` are byte offsets of the ring slots of this
+  // tile and of the one behind it.
+  auto k_frag = [&](const uint32_t stage, int ks, int h) { return lds_read16(kofs[ks] + (stage + (uint32_t)h * 32 * C::ROW)); };
+  auto logits = [&](const uint32_t stage, floatx16 (&s)[2]) {
+    s[0] = floatx16{0};
+    s[1] = floatx16{0};
 #pragma unroll
-      for (int ks = 0; ks < C::KS; ++ks) {
-        if (ks < C::KS - 1) {
-          fa[(ks + 1) & 1] = lds_read16(kofs[ks + 1] + stage);
-          fb[(ks + 1) & 1] = lds_read16(kofs[ks + 1] + (stage + 32 * C::ROW));
-        }
-        sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[ks & 1]), qf[ks], sa, 0, 0, 0);
-        sb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[ks & 1]), qf[ks], sb, 0, 0, 0);
-      }
-    }
-    // first value fragments can travel while the softmax runs
-    shortx4 vlo[2], vhi[2];
-    vlo[0] = lds_read_tr(vofs[0] + stage);
-    vhi[0] = lds_read_tr(vofs[0] + (stage + 8 * C::ROW));
-    // register v of sa is token kv0 + 8*(v/4) + 4*hf + v%4 (sb: + 32) against this lane's row
-    float p[32];
+    for (int ks = 0; ks < C::KS; ++ks)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) { p[v] = sa[v]; p[16 + v] = sb[v]; }
+      for (int h = 0; h < 2; ++h)
+        s[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k_frag(stage, ks, h)), qf[ks], s[h], 0, 0, 0);
+  };
+  auto process = [&](const uint32_t stage, const uint32_t next, int kv0, floatx16 (&cur)[2], floatx16 (&nxt)[2]) {
     if (kv0 + kBKV > wave_vis_min) {
 #pragma unroll
       for (int v = 0; v < 32; ++v) {
         const int j = kv0 + 32 * (v >> 4) + 8 * ((v & 15) >> 2) + 4 * hf + (v & 3);
-        p[v] = (j < vis) ? p[v] : -INFINITY;
+        cur[v >> 4][v & 15] = (j < vis) ? cur[v >> 4][v & 15] : -INFINITY;
       }
     }
-    float mx = p[0];
+    u32x4 kf[2][2];                    // key fragments of the next tile, one k-step ahead
+    kf[0][0] = k_frag(next, 0, 0);
+    kf[0][1] = k_frag(next, 0, 1);
+    float mx = cur[0][0];
 #pragma unroll
-    for (int v = 1; v < 32; ++v) mx = fmaxf(mx, p[v]);
+    for (int v = 1; v < 32; ++v) mx = fmaxf(mx, cur[v >> 4][v & 15]);
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
     // The reference point of the exponentials only moves when the maximum grows by more than 2^8: until
     // then probabilities up to 256 are accumulated against the old one (the final division by the
@@ -369,13 +363,6 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
     const float m_new = bump ? m_cand : m_run;
     const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
     const float alpha = bump ? __builtin_amdgcn_exp2f(m_run - m_use) : 1.f;
-    float sum = 0.f;
-#pragma unroll
-    for (int v = 0; v < 32; ++v) {
-      p[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(p[v], k2, -m_use));
-      sum += p[v];
-    }
-    l_run = l_run * alpha + sum;
     m_run = m_new;
     if (__any(alpha != 1.f)) {
 #pragma unroll
@@ -383,46 +370,70 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
 #pragma unroll
         for (int v = 0; v < 16; ++v) oacc[i][v] *= alpha;
     }
-    // P^T fragments: step s = 2*mt + t' uses registers 8*s .. 8*s+7 (tokens 16*s + 8*(e/4) + 4*hf + e%4)
-    bf16x8 pf[4], pr[4];
+    // One MFMA of the next tile's logits, then the exponentials of 32 / (2 KS) elements.  P^T fragments: step
+    // s = v / 8 uses registers 8*s .. 8*s+7 (tokens 16*s + 8*(e/4) + 4*hf + e%4).
+    constexpr int NM = 2 * C::KS, PER = 32 / NM;
+    u32x4 pf[4], pr[4];
+    shortx4 vlo[4], vhi[4];            // value fragments, up to three ahead
+    auto v_read = [&](int idx) {
+      const int s2 = idx / C::DT, dt2 = idx % C::DT;
+      vlo[idx & 3] = lds_read_tr(vofs[dt2] + (stage + (16 * s2) * C::ROW));
+      vhi[idx & 3] = lds_read_tr(vofs[dt2] + (stage + (16 * s2 + 8) * C::ROW));
+    };
+    float sum = 0.f;
+    nxt[0] = floatx16{0};
+    nxt[1] = floatx16{0};
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      u32x4 pk, pl;
+    for (int n = 0; n < NM; ++n) {
+      const int ks = n >> 1, h = n & 1;
+      __builtin_amdgcn_sched_barrier(0);
+      nxt[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[ks & 1][h]), qf[ks], nxt[h], 0, 0, 0);
+      if (ks + 1 < C::KS) kf[(ks + 1) & 1][h] = k_frag(next, ks + 1, h);
+      if (n >= NM - 3) v_read(n - (NM - 3));
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float p0 = p[8 * s + 2 * i], p1 = p[8 * s + 2 * i + 1];
-        pk[i] = cvt_pk_bf16(p0, p1);
+      for (int v = n * PER; v < (n + 1) * PER; v += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[v >> 4][v & 15], k2, -m_use));
+        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[v >> 4][(v & 15) + 1], k2, -m_use));
+        sum += p0;
+        sum += p1;
+        const uint32_t pk = cvt_pk_bf16(p0, p1);
+        pf[v >> 3][(v & 7) >> 1] = pk;
         // (the difference to the rounded value is exact)
-        if (C::SPLIT_P) pl[i] = cvt_pk_bf16(p0 - __uint_as_float(pk[i] << 16), p1 - __uint_as_float(pk[i] & 0xffff0000u));
+        if (C::SPLIT_P) pr[v >> 3][(v & 7) >> 1] = cvt_pk_bf16(p0 - __uint_as_float(pk << 16), p1 - __uint_as_float(pk & 0xffff0000u));
       }
-      pf[s] = __builtin_bit_cast(bf16x8, pk);
-      if (C::SPLIT_P) pr[s] = __builtin_bit_cast(bf16x8, pl);
     }
+    l_run = l_run * alpha + sum;
 #pragma unroll
     for (int idx = 0; idx < 4 * C::DT; ++idx) {
       const int s = idx / C::DT, dt = idx % C::DT;
-      if (idx < 4 * C::DT - 1) {
-        const int s2 = (idx + 1) / C::DT, dt2 = (idx + 1) % C::DT;
-        vlo[(idx + 1) & 1] = lds_read_tr(vofs[dt2] + (stage + (16 * s2) * C::ROW));
-        vhi[(idx + 1) & 1] = lds_read_tr(vofs[dt2] + (stage + (16 * s2 + 8) * C::ROW));
-      }
-      const shortx8 both = __builtin_shufflevector(vlo[idx & 1], vhi[idx & 1], 0, 1, 2, 3, 4, 5, 6, 7);
+      __builtin_amdgcn_sched_barrier(0);
+      if (idx + 3 < 4 * C::DT) v_read(idx + 3);
+      const shortx8 both = __builtin_shufflevector(vlo[idx & 3], vhi[idx & 3], 0, 1, 2, 3, 4, 5, 6, 7);
       const bf16x8 vf = __builtin_bit_cast(bf16x8, both);
-      oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[s], oacc[dt], 0, 0, 0);
-      if (C::SPLIT_P) oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pr[s], oacc[dt], 0, 0, 0);
+      oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8, pf[s]), oacc[dt], 0, 0, 0);
+      if (C::SPLIT_P) oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8, pr[s]), oacc[dt], 0, 0, 0);
     }
   };
 
+  // Ring of two slots for keys and two for values; while tile t is processed, keys up to t + 2 and values up to
+  // t + 1 are on their way (the keys of tile t have been used one tile earlier).
+  floatx16 s_a[2], s_b[2];
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();                                    // tile t_begin has landed
+  if (t_begin + 1 < t_end) aload_k(t_begin + 1, 1);
+  if (t_begin * kBKV < wave_vis_max) logits(0u, s_a);
   for (int t = t_begin; t < t_end; t += 2) {
     __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();                                  // tile t has landed; stage 1 is free again
-    if (t + 1 < t_end) aload2(t + 1, 1);
-    if (t * kBKV < wave_vis_max) process(0u, t * kBKV);
+    __syncthreads();                                  // keys of t + 1 and values of t have landed; keys of t are used
+    if (t + 2 < t_end) aload_k(t + 2, 0);
+    if (t + 1 < t_end) aload_v(t + 1, 1);
+    if (t * kBKV < wave_vis_max) process(0u, (uint32_t)C::STAGE, t * kBKV, s_a, s_b);
     if (t + 1 >= t_end) break;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (t + 2 < t_end) aload2(t + 2, 0);
-    if ((t + 1) * kBKV < wave_vis_max) process((uint32_t)C::STAGE, (t + 1) * kBKV);
+    if (t + 3 < t_end) aload_k(t + 3, 1);
+    if (t + 2 < t_end) aload_v(t + 2, 0);
+    if ((t + 1) * kBKV < wave_vis_max) process((uint32_t)C::STAGE, 0u, (t + 1) * kBKV, s_b, s_a);
   }
 
   // epilogue: output register v of tile dt is element 32*dt + 16*hf + v of this lane's row
