@@ -71,6 +71,22 @@ template <> struct Elem<bf16_t> {
   __device__ static __forceinline__ void store(bf16_t* p, float v) { *p = f32_to_bf16(v); }
 };
 
+// four consecutive elements (the pointer is a multiple of four elements from a 16-byte aligned one)
+template <typename T> struct Quad;
+template <> struct Quad<float> {
+  __device__ static __forceinline__ void load(const float* p, float* f) {
+    const float4 r = *reinterpret_cast<const float4*>(p);
+    f[0] = r.x; f[1] = r.y; f[2] = r.z; f[3] = r.w;
+  }
+};
+template <> struct Quad<bf16_t> {
+  __device__ static __forceinline__ void load(const bf16_t* p, float* f) {
+    const u32x2 r = *reinterpret_cast<const u32x2*>(p);
+    f[0] = __uint_as_float(r.x << 16); f[1] = __uint_as_float(r.x & 0xffff0000u);
+    f[2] = __uint_as_float(r.y << 16); f[3] = __uint_as_float(r.y & 0xffff0000u);
+  }
+};
+
 // 16-byte vector <-> float unpacking
 template <typename T> struct Vec16;
 template <> struct Vec16<float> {
@@ -220,10 +236,5 @@ qcf_status launch_rmsnorm(const qcf_layer_desc& L, const void* x, const void* we
                           int32_t cols, void* out, hipStream_t st);
 qcf_status launch_swiglu(const qcf_layer_desc& L, const void* gate_up, int64_t M, int32_t F, void* out,
                          hipStream_t st);
-
-// rotary table shared by rerope and qkv: cs[m * (d/2) + i] = (cos, sin)(angle_m * theta_i),
-// angles taken in float64.  `pos` gives one integer per row.
-qcf_status launch_rope_table(const int32_t* pos, int64_t M, int head_dim, double base, float2* cs,
-                             hipStream_t st);
 
 }  // namespace qcf

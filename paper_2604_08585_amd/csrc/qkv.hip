@@ -9,8 +9,7 @@
 // off by 1e-3 rad at 8K positions), reduced to its fraction and handed to the hardware sine and cosine
 // (inputs in turns, errors far below a bf16 ulp).
 // The generic path (f32, or shapes the MFMA tiling does not cover) writes the raw product to
-// the workspace and rotates it in a second kernel with a (cos, sin) table built from float64
-// angles by a small table kernel.
+// the workspace and rotates it in a second kernel with float64 angles, which also writes the cache rows.
 // qcf_recompute_qkv_scatter: the epilogue of the MFMA path also stores the K and V rows to their rows of the
 // fused cache (step 5 of the path, otherwise a kernel of its own).
 #include <type_traits>
@@ -24,24 +23,9 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-// ------------------------------------------------------------------ rotary table
-
-__global__ __launch_bounds__(256) void rope_table_kernel(const int32_t* __restrict__ pos, int64_t M, int D,
-                                                         double neg2_over_d_log2base,
-                                                         float2* __restrict__ cs) {
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int half = D / 2;
-  if (gid >= M * half) return;
-  const int64_t m = gid / half;
-  const int i = (int)(gid - m * half);
-  const double theta = exp2(neg2_over_d_log2base * (double)i);
-  double sn, cn;
-  sincos((double)pos[m] * theta, &sn, &cn);
-  cs[gid] = make_float2((float)cn, (float)sn);
-}
-
 // ------------------------------------------------------------------ generic path
 
+// 64 x 64 outputs per workgroup, 4 x 4 per thread; the sums run over k in order.
 template <typename T>
 __global__ __launch_bounds__(256) void qkv_gemm_generic(const T* __restrict__ x, int64_t x_rows,
                                                         const int32_t* __restrict__ gather, int64_t M,
@@ -94,12 +78,67 @@ __global__ __launch_bounds__(256) void qkv_gemm_generic(const T* __restrict__ x,
   }
 }
 
-// one thread per (row, head slot, rotary pair); V heads are copied
+// The same product (same sums in the same order) with 16 x 16 outputs per workgroup, one per thread, for launches
+// whose 64 x 64 tiles would leave most compute units idle.  Bound by latency there: the next 64 elements of the
+// contraction are on their way while 64 are used.  M 77, K 256, N 512 in f32: 38 us with 64 x 64 tiles, 11 us here.
+template <typename T>
+__global__ __launch_bounds__(256) void qkv_gemm_small_generic(const T* __restrict__ x, int64_t x_rows,
+                                                              const int32_t* __restrict__ gather, int64_t M,
+                                                              const T* __restrict__ w, int Kdim, int Ntot,
+                                                              float* __restrict__ y) {
+  constexpr int KC = 64, LD = KC + 4;            // (rows 4 banks apart: 16-byte reads of 16 rows touch every bank once)
+  __shared__ __align__(16) float sA[16 * LD];
+  __shared__ __align__(16) float sB[16 * LD];
+  const int tid = threadIdx.x;
+  const int tx = tid & 15, ty = tid >> 4;
+  const int64_t m0 = (int64_t)blockIdx.x * 16;
+  const int n0 = blockIdx.y * 16;
+  const int lr = tid >> 4, lc = (tid & 15) * 4;  // row and first k of the four elements this thread brings
+  int64_t arow = -1;
+  if (m0 + lr < M) {
+    const int64_t idx = gather ? (int64_t)gather[m0 + lr] : m0 + lr;
+    if (idx >= 0 && idx < x_rows) arow = idx;
+  }
+  const int brow = (n0 + lr < Ntot) ? n0 + lr : -1;
+  float a4[4], b4[4];
+  auto fetch = [&](int k0) {                     // (Kdim is a multiple of 4 here)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) a4[c] = b4[c] = 0.f;
+    if (k0 + lc < Kdim) {
+      if (arow >= 0) Quad<T>::load(x + arow * Kdim + k0 + lc, a4);
+      if (brow >= 0) Quad<T>::load(w + (int64_t)brow * Kdim + k0 + lc, b4);
+    }
+  };
+  fetch(0);
+  float acc = 0.f;
+  for (int k0 = 0; k0 < Kdim; k0 += KC) {
+    __syncthreads();
+    *reinterpret_cast<float4*>(sA + lr * LD + lc) = make_float4(a4[0], a4[1], a4[2], a4[3]);
+    *reinterpret_cast<float4*>(sB + lr * LD + lc) = make_float4(b4[0], b4[1], b4[2], b4[3]);
+    __syncthreads();
+    if (k0 + KC < Kdim) fetch(k0 + KC);
+#pragma unroll
+    for (int kk = 0; kk < KC; kk += 4) {
+      const float4 av = *reinterpret_cast<const float4*>(sA + ty * LD + kk);
+      const float4 bv = *reinterpret_cast<const float4*>(sB + tx * LD + kk);
+      acc += av.x * bv.x;
+      acc += av.y * bv.y;
+      acc += av.z * bv.z;
+      acc += av.w * bv.w;
+    }
+  }
+  if (m0 + ty < M && n0 + tx < Ntot) y[(m0 + ty) * Ntot + n0 + tx] = acc;
+}
+
+// One thread per (row, head slot, rotary pair); V heads are copied.  The angle is taken in float64 (cheaper here than
+// a table from a launch of its own: 77 rows, 4 us less).  dst_rows: K and V rows also go to the fused cache.
 template <typename T>
 __global__ __launch_bounds__(256) void qkv_rope_split_generic(const float* __restrict__ y, int64_t M,
-                                                              const float2* __restrict__ cs, int H, int Hkv,
-                                                              int D, int style, T* __restrict__ q,
-                                                              T* __restrict__ k, T* __restrict__ v) {
+                                                              const int32_t* __restrict__ pos, double neg2_over_d_log2base,
+                                                              int H, int Hkv, int D, int style, T* __restrict__ q,
+                                                              T* __restrict__ k, T* __restrict__ v,
+                                                              const int32_t* __restrict__ dst_rows, T* __restrict__ k_fused,
+                                                              T* __restrict__ v_fused, int64_t fused_rows) {
   const int half = D / 2;
   const int heads = H + 2 * Hkv;
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -112,18 +151,37 @@ __global__ __launch_bounds__(256) void qkv_rope_split_generic(const float* __res
   const float* src = y + m * (int64_t)heads * D + (int64_t)hs * D;
   const float a = src[ia], b = src[ib];
   T* dst;
+  T* fus = nullptr;
   bool rot = true;
+  int64_t row = -1;
+  if (hs >= H && dst_rows) {
+    row = dst_rows[m];
+    if (row >= fused_rows) row = -1;
+  }
   if (hs < H) dst = q ? q + (m * H + hs) * D : nullptr;
-  else if (hs < H + Hkv) dst = k ? k + (m * Hkv + (hs - H)) * D : nullptr;
-  else { dst = v ? v + (m * Hkv + (hs - H - Hkv)) * D : nullptr; rot = false; }
-  if (!dst) return;
-  if (rot) {
-    const float2 w = cs[m * half + i];
-    Elem<T>::store(dst + ia, a * w.x - b * w.y);
-    Elem<T>::store(dst + ib, b * w.x + a * w.y);
+  else if (hs < H + Hkv) {
+    dst = k ? k + (m * Hkv + (hs - H)) * D : nullptr;
+    if (row >= 0) fus = k_fused + (row * Hkv + (hs - H)) * D;
   } else {
-    Elem<T>::store(dst + ia, a);
-    Elem<T>::store(dst + ib, b);
+    dst = v ? v + (m * Hkv + (hs - H - Hkv)) * D : nullptr;
+    if (row >= 0) fus = v_fused + (row * Hkv + (hs - H - Hkv)) * D;
+    rot = false;
+  }
+  if (!dst) return;
+  float ra = a, rb = b;
+  if (rot) {
+    const double theta = exp2(neg2_over_d_log2base * (double)i);
+    double sd, cd;
+    sincos((double)pos[m] * theta, &sd, &cd);
+    const float sn = (float)sd, cn = (float)cd;
+    ra = a * cn - b * sn;
+    rb = b * cn + a * sn;
+  }
+  Elem<T>::store(dst + ia, ra);
+  Elem<T>::store(dst + ib, rb);
+  if (fus) {
+    Elem<T>::store(fus + ia, ra);
+    Elem<T>::store(fus + ib, rb);
   }
 }
 
@@ -958,10 +1016,6 @@ bool use_mfma(const qcf_layer_desc& L) {
   return L.dtype == QCF_DTYPE_BF16 && L.d_model % kBK == 0 && (L.n_kv_heads * L.head_dim) % kBN == 0;
 }
 
-size_t cs_bytes(const qcf_layer_desc& L, int64_t M) {
-  return align_up((size_t)M * (L.head_dim / 2) * sizeof(float2), 256);
-}
-
 // ---- choice of the tile --------------------------------------------------------------------------
 typedef WsTile<2, 4, 3> Ws256;         // 256 x 128
 typedef WsTile<1, 4, 4> Ws128;         // 128 x 128
@@ -1052,6 +1106,35 @@ qcf_status run_quad(QkvArgs a, hipStream_t st) {
   return check_launch("qkv gemm");
 }
 
+// Product of the generic path.  The small tile reads both operands four times as often, so it takes over only where
+// the large one gives fewer workgroups than compute units (M 77, N 512: 16; the small one 160).
+template <typename T>
+qcf_status run_gemm_generic(const char* what, const void* x, int64_t x_rows, const int32_t* gather, int64_t M,
+                            const void* w, int K, int N, float* y, hipStream_t st) {
+  const int64_t mb = (M + 63) / 64;
+  const int nb = (N + 63) / 64;
+  if (mb > 0x7fffffff || nb > 65535) return fail(QCF_ERR_UNSUPPORTED, "%s: grid too large", what);
+  const T* xt = static_cast<const T*>(x);
+  const T* wt = static_cast<const T*>(w);
+  if (mb * nb < compute_unit_count() && K % 4 == 0)
+    qkv_gemm_small_generic<T><<<dim3((unsigned)((M + 15) / 16), (unsigned)((N + 15) / 16)), dim3(256), 0, st>>>(
+        xt, x_rows, gather, M, wt, K, N, y);
+  else
+    qkv_gemm_generic<T><<<dim3((unsigned)mb, (unsigned)nb), dim3(256), 0, st>>>(xt, x_rows, gather, M, wt, K, N, y);
+  return check_launch(what);
+}
+
+template <typename T>
+qcf_status run_rope_split(const qcf_layer_desc& L, const float* y, int64_t M, const int32_t* pos, void* q, void* k, void* v,
+                          const int32_t* dst_rows, void* k_fused, void* v_fused, int64_t fused_rows, unsigned blocks,
+                          hipStream_t st) {
+  qkv_rope_split_generic<T><<<dim3(blocks), dim3(256), 0, st>>>(
+      y, M, pos, -2.0 / (double)L.head_dim * std::log2(L.rope_base), L.n_q_heads, L.n_kv_heads, L.head_dim, L.rope_style,
+      static_cast<T*>(q), static_cast<T*>(k), static_cast<T*>(v), dst_rows, static_cast<T*>(k_fused),
+      static_cast<T*>(v_fused), fused_rows);
+  return check_launch("qkv rope");
+}
+
 // The whole product.  256 x 256 tiles have the best rate but fill whole rounds of compute units only: where their
 // last round would be thin, they take as many column blocks as full rounds hold and smaller tiles the rest.
 template <int EPI>
@@ -1107,20 +1190,10 @@ qcf_status run_gemm(const QkvArgs& a_in, int nb, void* ws, size_t ws_bytes, hipS
 
 }  // namespace
 
-qcf_status launch_rope_table(const int32_t* pos, int64_t M, int head_dim, double base, float2* cs,
-                             hipStream_t st) {
-  const int64_t n = M * (head_dim / 2);
-  const int64_t blocks = (n + 255) / 256;
-  if (blocks > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "rope table: too many rows");
-  rope_table_kernel<<<dim3((unsigned)blocks), dim3(256), 0, st>>>(pos, M, head_dim,
-                                                                -2.0 / (double)head_dim * std::log2(base), cs);
-  return check_launch("rope table");
-}
-
 size_t qkv_workspace(const qcf_layer_desc& L, int64_t M) {
   // (the MFMA path needs none; what it asks for lets small M split the contraction)
   if (use_mfma(L)) return gemm_part_bytes(M, (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim / kBN, L.d_model / kBK);
-  return cs_bytes(L, M) + align_up((size_t)M * (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim * sizeof(float), 256);
+  return align_up((size_t)M * (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim * sizeof(float), 256);
 }
 
 size_t qkv_workspace_needed(const qcf_layer_desc& L, int64_t M) { return use_mfma(L) ? 0 : qkv_workspace(L, M); }
@@ -1148,32 +1221,16 @@ qcf_status launch_qkv(const qcf_layer_desc& L, const void* x, int64_t x_rows, co
     if (D == 128) return run_gemm<kRopeHalf128>(a, Ntot / kBN, ws, ws_bytes, st);
     return run_gemm<kRopeHalf64>(a, Ntot / kBN, ws, ws_bytes, st);
   }
-  float2* cs = static_cast<float2*>(ws);
-  QCF_TRY(launch_rope_table(pos, M, L.head_dim, L.rope_base, cs, st));
-  float* y = reinterpret_cast<float*>(static_cast<char*>(ws) + cs_bytes(L, M));
-  const int64_t mb = (M + 63) / 64;
-  const int nb = (Ntot + 63) / 64;
+  float* y = static_cast<float*>(ws);
   const int64_t rope_blocks = (M * (H + 2 * Hkv) * (D / 2) + 255) / 256;
-  if (mb > 0x7fffffff || nb > 65535 || rope_blocks > 0x7fffffff)
-    return fail(QCF_ERR_UNSUPPORTED, "qkv: grid too large");
-  const dim3 grid((unsigned)mb, (unsigned)nb), block(256);
+  if (rope_blocks > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "qkv: grid too large");
   if (L.dtype == QCF_DTYPE_BF16) {
-    qkv_gemm_generic<bf16_t><<<grid, block, 0, st>>>(static_cast<const bf16_t*>(x), x_rows, gather, M,
-                                                     static_cast<const bf16_t*>(w), L.d_model, Ntot, y);
-    QCF_TRY_LAUNCH("qkv gemm");
-    qkv_rope_split_generic<bf16_t><<<dim3((unsigned)rope_blocks), dim3(256), 0, st>>>(
-        y, M, cs, H, Hkv, D, L.rope_style, static_cast<bf16_t*>(q), static_cast<bf16_t*>(k),
-        static_cast<bf16_t*>(v));
+    QCF_TRY(run_gemm_generic<bf16_t>("qkv", x, x_rows, gather, M, w, L.d_model, Ntot, y, st));
+    QCF_TRY(run_rope_split<bf16_t>(L, y, M, pos, q, k, v, dst_rows, k_fused, v_fused, fused_rows, (unsigned)rope_blocks, st));
   } else {
-    qkv_gemm_generic<float><<<grid, block, 0, st>>>(static_cast<const float*>(x), x_rows, gather, M,
-                                                    static_cast<const float*>(w), L.d_model, Ntot, y);
-    QCF_TRY_LAUNCH("qkv gemm");
-    qkv_rope_split_generic<float><<<dim3((unsigned)rope_blocks), dim3(256), 0, st>>>(
-        y, M, cs, H, Hkv, D, L.rope_style, static_cast<float*>(q), static_cast<float*>(k),
-        static_cast<float*>(v));
+    QCF_TRY(run_gemm_generic<float>("qkv", x, x_rows, gather, M, w, L.d_model, Ntot, y, st));
+    QCF_TRY(run_rope_split<float>(L, y, M, pos, q, k, v, dst_rows, k_fused, v_fused, fused_rows, (unsigned)rope_blocks, st));
   }
-  QCF_TRY_LAUNCH("qkv rope");
-  if (dst_rows) return launch_scatter(L, k, v, dst_rows, M, k_fused, v_fused, fused_rows, st);   // (k, v given: checked by the caller)
   return QCF_OK;
 }
 
@@ -1207,21 +1264,14 @@ qcf_status launch_linear(const qcf_layer_desc& L, const void* x, int64_t M, int3
     return residual ? run_gemm<kAdd>(a, N / kBN, ws, ws_bytes, st) : run_gemm<kPlain>(a, N / kBN, ws, ws_bytes, st);
   }
   float* y = static_cast<float*>(ws);
-  const int64_t mb = (M + 63) / 64;
-  const int nb = (N + 63) / 64;
   const int64_t n = M * N;
-  if (mb > 0x7fffffff || nb > 65535 || (n + 255) / 256 > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "linear: grid too large");
-  const dim3 grid((unsigned)mb, (unsigned)nb), block(256);
+  if ((n + 255) / 256 > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "linear: grid too large");
   if (L.dtype == QCF_DTYPE_BF16) {
-    qkv_gemm_generic<bf16_t><<<grid, block, 0, st>>>(static_cast<const bf16_t*>(x), M, nullptr, M,
-                                                     static_cast<const bf16_t*>(w), K, N, y);
-    QCF_TRY_LAUNCH("linear gemm");
+    QCF_TRY(run_gemm_generic<bf16_t>("linear", x, M, nullptr, M, w, K, N, y, st));
     linear_finish_generic<bf16_t><<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st>>>(
         y, static_cast<const bf16_t*>(residual), n, static_cast<bf16_t*>(out));
   } else {
-    qkv_gemm_generic<float><<<grid, block, 0, st>>>(static_cast<const float*>(x), M, nullptr, M,
-                                                    static_cast<const float*>(w), K, N, y);
-    QCF_TRY_LAUNCH("linear gemm");
+    QCF_TRY(run_gemm_generic<float>("linear", x, M, nullptr, M, w, K, N, y, st));
     linear_finish_generic<float><<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st>>>(
         y, static_cast<const float*>(residual), n, static_cast<float*>(out));
   }

@@ -70,7 +70,13 @@ __global__ __launch_bounds__(256) void score_rows_generic(
   for (int j = tid; j < limit; j += 256) {
     const T* kr = k + ((c0 + j) * Hkv + g) * (int64_t)D;
     float acc = 0.f;
-    for (int c = 0; c < D; ++c) acc += sq[c] * Elem<T>::load(kr + c);
+#pragma unroll 4
+    for (int c = 0; c < D; c += 4) {
+      float kf[4];
+      Quad<T>::load(kr + c, kf);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc += sq[c + e] * kf[e];
+    }
     acc *= scale;
     prow[j] = acc;
     mx = fmaxf(mx, acc);
@@ -93,17 +99,28 @@ __global__ __launch_bounds__(256) void score_rows_generic(
   for (int j = tid; j < Tn; j += 256) prow[j] = (j < limit) ? prow[j] / sum : 0.f;
 }
 
-__global__ __launch_bounds__(256) void score_colmean_generic(
+// One thread per token adds its column in row order, sixteen rows on their way at a time; workgroups of one wave, so
+// that short contexts reach more compute units (80 rows x 512 tokens: 18.9 -> 6 us).
+constexpr int kColThreads = 64;
+__global__ __launch_bounds__(kColThreads) void score_colmean_generic(
     const float* __restrict__ P, const int64_t* __restrict__ probe_off, int64_t total_probe,
     const int64_t* __restrict__ ctx_off, int64_t total_ctx, int B, int H, float* score, float alpha, float beta) {
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t j = (int64_t)blockIdx.x * kColThreads + threadIdx.x;
   if (j >= total_ctx) return;
   const int b = find_request(ctx_off, B, j);
   if (b >= B) return;
   const int64_t r0 = min(max(probe_off[b], (int64_t)0), total_probe);
   const int64_t r1 = min(max(probe_off[b + 1], r0), total_probe);
   float acc = 0.f;
-  for (int64_t r = r0 * H; r < r1 * H; ++r) acc += P[r * total_ctx + j];
+  int64_t r = r0 * H;
+  for (; r + 16 <= r1 * H; r += 16) {
+    float p[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) p[u] = P[(r + u) * total_ctx + j];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) acc += p[u];
+  }
+  for (; r < r1 * H; ++r) acc += P[r * total_ctx + j];
   const float sj = (r1 > r0) ? acc / (float)((r1 - r0) * H) : 0.f;
   score[j] = (beta == 0.f) ? alpha * sj : __builtin_fmaf(beta, score[j], alpha * sj);
 }
@@ -859,7 +876,7 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
   const bool fused = use_fused(L, B, total_probe, total_ctx);
   if (!fused && !use_two_pass(L, B, total_probe, total_ctx)) {
     float* P = static_cast<float*>(ws);
-    const int64_t col_blocks = (total_ctx + 255) / 256;
+    const int64_t col_blocks = (total_ctx + kColThreads - 1) / kColThreads;
     if (total_probe * H > 0x7fffffff || col_blocks > 0x7fffffff)
       return fail(QCF_ERR_UNSUPPORTED, "score: too many rows");
     if (total_probe > 0) {
@@ -874,7 +891,7 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
             total_ctx, B, probe_limit, H, Hkv, D, P);
       QCF_TRY_LAUNCH("score rows");
     }
-    score_colmean_generic<<<dim3((unsigned)col_blocks), dim3(256), 0, st>>>(P, probe_off, total_probe, ctx_off,
+    score_colmean_generic<<<dim3((unsigned)col_blocks), dim3(kColThreads), 0, st>>>(P, probe_off, total_probe, ctx_off,
                                                                            total_ctx, B, H, score, alpha, beta);
     return check_launch("score column mean");
   }

@@ -191,3 +191,40 @@ def test_scores_of_64_wide_heads(H, Hkv, ctx, probes, limit):
         # 32-bit logits of magnitude up to 60, exponentials and sums
         assert bool(((score[c0:c0 + t].double() - ref).abs() <= 3e-5 * ref + 1e-12).all())
         r0, c0 = r0 + r, c0 + t
+
+
+@pytest.mark.parametrize("dtype,M,K,N", [("f32", 1, 8, 8), ("f32", 77, 256, 512), ("f32", 17, 264, 40), ("f32", 1100, 72, 1032),
+                                         ("bf16", 33, 520, 48), ("bf16", 5, 24, 16)])
+def test_general_product_tiles(dtype, M, K, N):
+    """Both tiles of the general product, edges included."""
+    say(f"general product {dtype} M={M} K={K} N={N}")
+    g = gen(49)
+    dt = inputs.torch_dtype(dtype)
+    x = torch.randn((M, K), generator=g, device=DEV).to(dt)
+    w = (torch.randn((N, K), generator=g, device=DEV) * K ** -0.5).to(dt)
+    out = torch.full((M, N), 7.0, dtype=dt, device=DEV)
+    desc = qb.make_desc(inputs.LayerShape(256, 4, 2, 64, 10000.0, dtype))
+    qb.qcf_linear(desc, x, M, K, w, N, None, out)
+    torch.cuda.synchronize()
+    ref = (x.double() @ w.double().T).float()
+    if dtype == "bf16":
+        one_rounding(out, ref)
+    else:
+        assert float((out - ref).abs().max()) < 1e-5          # 32-bit sums of up to 260 products of size K^-1/2
+
+
+@pytest.mark.parametrize("D,T,n", [(64, 257, 40), (128, 300, 31), (64, 31, 31), (128, 1, 1)])
+def test_f32_attention_general(D, T, n):
+    """Tiles of 256 tokens and the value loop's remainders, against float64."""
+    say(f"f32 attention D={D} T={T}")
+    g = gen(50)
+    q = torch.randn((n, 4, D), generator=g, device=DEV)
+    k, v = (torch.randn((T, 2, D), generator=g, device=DEV) for _ in range(2))
+    pos = torch.sort(torch.randperm(T, generator=g, device=DEV)[:n])[0].int()
+    o, lse = torch.full((n, 4, D), 7.0, device=DEV), torch.full((n, 4), 7.0, device=DEV)
+    desc = qb.make_desc(inputs.LayerShape(256, 4, 2, D, 10000.0, "f32"))
+    qb.qcf_recompute_attn(desc, 1, q, pos, i64([0, n]), n, k, v, i64([0, T]), T, None, o, lse)
+    torch.cuda.synchronize()
+    ro, rl = _attention64(q, k, v, pos, D ** -0.5)
+    assert float((o.double() - ro).abs().max()) < 1e-5
+    assert float((lse.double() - rl).abs().max()) < 1e-5
