@@ -32,47 +32,40 @@ __device__ __forceinline__ uint64_t wave_incl_scan(uint64_t v, int lane) {
   return v;
 }
 
-// SEG > 0: each thread keeps up to SEG keys of its contiguous segment in registers.
+struct SelectLds {
+  uint32_t merged[kBins];
+  uint64_t wave_tot[kWaves];
+  uint32_t red_lo[kWaves], red_hi[kWaves];
+  uint32_t digit, k;
+};
+
+// One request: T scores, N of them to select (0 < N <= T), written from sel_*[o0] on.
+// SEG > 0: each thread keeps up to SEG keys of its contiguous segment of seg keys in registers.
 // SEG == 0: keys are re-read from global memory in every pass (any length).
 template <int SEG>
-__global__ __launch_bounds__(kThreads) void select_kernel(
-    const float* __restrict__ score, const int64_t* __restrict__ ctx_off, int64_t total_ctx,
-    const int64_t* __restrict__ sel_off, int64_t total_sel, const int32_t* __restrict__ ctx_pos0,
-    int32_t* __restrict__ sel_idx, int32_t* __restrict__ sel_row, int32_t* __restrict__ sel_pos) {
-  __shared__ uint32_t merged[kBins];
-  __shared__ uint64_t wave_tot[kWaves];
-  __shared__ uint32_t red_lo[kWaves], red_hi[kWaves];
-  __shared__ uint32_t s_digit, s_k;
-
-  const int b = blockIdx.x;
+__device__ __forceinline__ void select_request(SelectLds& lds, const float* __restrict__ s, int64_t c0, int T, int N, int seg,
+                                               int64_t o0, int base_pos, int32_t* __restrict__ sel_idx,
+                                               int32_t* __restrict__ sel_row, int32_t* __restrict__ sel_pos) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int64_t c0 = ctx_off[b], c1 = ctx_off[b + 1];
-  c0 = min(max(c0, (int64_t)0), total_ctx);
-  c1 = min(max(c1, c0), total_ctx);
-  int64_t o0 = sel_off[b], o1 = sel_off[b + 1];
-  o0 = min(max(o0, (int64_t)0), total_sel);
-  o1 = min(max(o1, o0), total_sel);
-  const int T = (int)(c1 - c0);
-  const int N = (int)min((int64_t)T, o1 - o0);
-  if (N <= 0) return;
-  const float* s = score + c0;
-
-  const int seg = (T + kThreads - 1) / kThreads;
-  const int j0 = min(T, tid * seg), j1 = min(T, j0 + seg);
+  const int j0 = (int)min((int64_t)T, (int64_t)tid * seg), j1 = min(T, j0 + seg);
   const int cnt = j1 - j0;
-  if (SEG > 0 && seg > SEG) return;          // launcher guarantees this cannot happen
 
   uint32_t keys[SEG > 0 ? SEG : 1];
   if (SEG > 0) {
-    // a full, 16-byte aligned segment is read as vectors (a quarter of the memory instructions)
-    if (SEG % 4 == 0 && cnt == SEG && ((reinterpret_cast<uintptr_t>(s + j0) & 15u) == 0)) {
+    // segments start at multiples of four: with an aligned request every whole quad is one load
+    if (SEG % 4 == 0 && (reinterpret_cast<uintptr_t>(s) & 15u) == 0) {
 #pragma unroll
-      for (int i = 0; i < SEG / 4; ++i) {
-        const float4 v = *reinterpret_cast<const float4*>(s + j0 + 4 * i);
-        keys[4 * i + 0] = order_key(v.x);
-        keys[4 * i + 1] = order_key(v.y);
-        keys[4 * i + 2] = order_key(v.z);
-        keys[4 * i + 3] = order_key(v.w);
+      for (int i = 0; i < SEG; i += 4) {
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (i + 3 < cnt) v = *reinterpret_cast<const float4*>(s + j0 + i);
+        else {
+          if (i < cnt) v.x = s[j0 + i];
+          if (i + 1 < cnt) v.y = s[j0 + i + 1];
+          if (i + 2 < cnt) v.z = s[j0 + i + 2];
+        }
+        const float q[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int c = 0; c < 4 && i + c < SEG; ++c) keys[i + c] = order_key(q[c]);
       }
     } else {
 #pragma unroll
@@ -89,7 +82,6 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
     for (int i = 0; i < cnt; ++i) { __VA_ARGS__ }              \
   }
 
-  const int base_pos = ctx_pos0 ? ctx_pos0[b] : 0;
   uint32_t tau = 0;       // key of the N-th largest score
   uint32_t k = (uint32_t)N;   // how many keys equal to tau are admitted
 
@@ -102,12 +94,12 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
       lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
       hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
     }
-    if (lane == 0) { red_lo[wave] = lo; red_hi[wave] = hi; }
-    for (int i = tid; i < kBins; i += kThreads) merged[i] = 0u;
+    if (lane == 0) { lds.red_lo[wave] = lo; lds.red_hi[wave] = hi; }
+    for (int i = tid; i < kBins; i += kThreads) lds.merged[i] = 0u;
     __syncthreads();
-    lo = red_lo[0]; hi = red_hi[0];
+    lo = lds.red_lo[0]; hi = lds.red_hi[0];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) { lo = min(lo, red_lo[w]); hi = max(hi, red_hi[w]); }
+    for (int w = 1; w < kWaves; ++w) { lo = min(lo, lds.red_lo[w]); hi = max(hi, lds.red_hi[w]); }
 
     const uint32_t diff = lo ^ hi;
     int bits = diff ? 32 - __clz((int)diff) : 0;     // low bits in which keys may differ
@@ -116,11 +108,11 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
       const int w = min(kDigitBits, bits);
       const int shift = bits - w;
       const uint32_t mask = (1u << w) - 1u;
-      // (merged[] was cleared before the loop and is cleared again by wave 0 after each pass)
+      // (lds.merged[] was cleared before the loop and is cleared again by wave 0 after each pass)
       QCF_FOR_KEYS(i, {
         const uint32_t key = QCF_KEY(i);
         const uint32_t high = (bits >= 32) ? 0u : (key >> bits);
-        if (high == prefix) atomicAdd(&merged[(key >> shift) & mask], 1u);
+        if (high == prefix) atomicAdd(&lds.merged[(key >> shift) & mask], 1u);
       })
       __syncthreads();
       if (wave == 0) {
@@ -128,9 +120,9 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
         uint32_t tot = 0;
 #pragma unroll
         for (int q = 0; q < kBinsPerLane; ++q) {
-          c[q] = merged[kBinsPerLane * lane + q];
+          c[q] = lds.merged[kBinsPerLane * lane + q];
           tot += c[q];
-          merged[kBinsPerLane * lane + q] = 0u;
+          lds.merged[kBinsPerLane * lane + q] = 0u;
         }
         uint32_t suffix = tot;               // sum over lanes >= this one
 #pragma unroll
@@ -141,13 +133,13 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
         uint32_t above = suffix - tot;       // keys with a larger digit than this lane's bins
 #pragma unroll
         for (int q = kBinsPerLane - 1; q >= 0; --q) {
-          if (above < k && k <= above + c[q]) { s_digit = kBinsPerLane * lane + q; s_k = k - above; }
+          if (above < k && k <= above + c[q]) { lds.digit = kBinsPerLane * lane + q; lds.k = k - above; }
           above += c[q];
         }
       }
       __syncthreads();
-      prefix = (prefix << w) | s_digit;
-      k = s_k;
+      prefix = (prefix << w) | lds.digit;
+      k = lds.k;
       bits = shift;
     }
     tau = prefix;
@@ -162,10 +154,10 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
   }
   const uint64_t mine = ((uint64_t)n_eq << 32) | n_gt;
   const uint64_t incl = wave_incl_scan(mine, lane);
-  if (lane == 63) wave_tot[wave] = incl;
+  if (lane == 63) lds.wave_tot[wave] = incl;
   __syncthreads();
   uint64_t before = incl - mine;
-  for (int w = 0; w < wave; ++w) before += wave_tot[w];
+  for (int w = 0; w < wave; ++w) before += lds.wave_tot[w];
   uint32_t gt_before = (uint32_t)before, eq_before = (uint32_t)(before >> 32);
   const int64_t out0 = o0;
 #define QCF_EMIT(j, pos)                                            \
@@ -191,6 +183,38 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
 #undef QCF_FOR_KEYS
 }
 
+// Keys per thread are chosen by the length of each request (the host knows only the total): a batch of requests whose
+// total exceeds what registers hold no longer re-reads every key in every pass (sixteen requests of 2K-16K tokens: 56
+// -> 16 us), and short requests in a long total carry no registers for keys they do not have.
+__global__ __launch_bounds__(kThreads) void select_kernel(
+    const float* __restrict__ score, const int64_t* __restrict__ ctx_off, int64_t total_ctx,
+    const int64_t* __restrict__ sel_off, int64_t total_sel, const int32_t* __restrict__ ctx_pos0,
+    int32_t* __restrict__ sel_idx, int32_t* __restrict__ sel_row, int32_t* __restrict__ sel_pos) {
+  __shared__ SelectLds lds;
+  const int b = blockIdx.x;
+  int64_t c0 = ctx_off[b], c1 = ctx_off[b + 1];
+  c0 = min(max(c0, (int64_t)0), total_ctx);
+  c1 = min(max(c1, c0), total_ctx);
+  int64_t o0 = sel_off[b], o1 = sel_off[b + 1];
+  o0 = min(max(o0, (int64_t)0), total_sel);
+  o1 = min(max(o1, o0), total_sel);
+  const int T = (int)(c1 - c0);
+  const int N = (int)min((int64_t)T, o1 - o0);
+  if (N <= 0) return;
+  const float* s = score + c0;
+  const int base_pos = ctx_pos0 ? ctx_pos0[b] : 0;
+  int seg = (T + kThreads - 1) / kThreads;
+  if (seg > 1) seg = (seg + 3) & ~3;
+#define QCF_SELECT(SEG) select_request<SEG>(lds, s, c0, T, N, seg, o0, base_pos, sel_idx, sel_row, sel_pos)
+  if (seg <= 1) QCF_SELECT(1);
+  else if (seg <= 4) QCF_SELECT(4);
+  else if (seg <= 8) QCF_SELECT(8);
+  else if (seg <= 16) QCF_SELECT(16);
+  else if (seg <= 32) QCF_SELECT(32);
+  else QCF_SELECT(0);
+#undef QCF_SELECT
+}
+
 }  // namespace
 
 size_t select_workspace(int32_t, int64_t) { return 0; }
@@ -199,16 +223,7 @@ qcf_status launch_select(int32_t B, const float* score, const int64_t* ctx_off, 
                          const int64_t* sel_off, int64_t total_sel, const int32_t* ctx_pos0,
                          int32_t* sel_idx, int32_t* sel_row, int32_t* sel_pos, void*, hipStream_t st) {
   const dim3 grid((unsigned)B), block(kThreads);
-  // a request is never longer than total_ctx, which bounds the per-thread segment
-  if (total_ctx <= 8 * kThreads)
-    select_kernel<8><<<grid, block, 0, st>>>(score, ctx_off, total_ctx, sel_off, total_sel, ctx_pos0,
-                                             sel_idx, sel_row, sel_pos);
-  else if (total_ctx <= 32 * kThreads)
-    select_kernel<32><<<grid, block, 0, st>>>(score, ctx_off, total_ctx, sel_off, total_sel, ctx_pos0,
-                                              sel_idx, sel_row, sel_pos);
-  else
-    select_kernel<0><<<grid, block, 0, st>>>(score, ctx_off, total_ctx, sel_off, total_sel, ctx_pos0,
-                                             sel_idx, sel_row, sel_pos);
+  select_kernel<<<grid, block, 0, st>>>(score, ctx_off, total_ctx, sel_off, total_sel, ctx_pos0, sel_idx, sel_row, sel_pos);
   return check_launch("select");
 }
 

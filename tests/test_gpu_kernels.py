@@ -228,3 +228,26 @@ def test_f32_attention_general(D, T, n):
     ro, rl = _attention64(q, k, v, pos, D ** -0.5)
     assert float((o.double() - ro).abs().max()) < 1e-5
     assert float((lse.double() - rl).abs().max()) < 1e-5
+
+
+@pytest.mark.parametrize("lens", [[1, 1024, 1025, 3], [4096, 4097, 8192, 8193, 16384], [16385, 7, 32768], [32769, 1023, 40001]])
+def test_select_keys_per_thread(lens):
+    """Every number of keys per thread, requests that start at any alignment, ties: exactly the N largest, ties to the
+    lower index, ascending."""
+    say(f"select {lens}")
+    g = gen(51)
+    lens = [2] + lens                                        # (shifts the starts)
+    T = sum(lens)
+    score = torch.exp(torch.randn(T, generator=g, device=DEV) * 2)
+    score[::7] = score[0]                                    # ties
+    counts = [max(1, int(0.15 * n)) for n in lens]
+    co, so = i64(np.concatenate([[0], np.cumsum(lens)])), i64(np.concatenate([[0], np.cumsum(counts)]))
+    N = sum(counts)
+    idx, row, pos = (torch.full((N,), -7, dtype=torch.int32, device=DEV) for _ in range(3))
+    qb.qcf_select(len(lens), score, co, T, so, N, None, idx, row, pos)
+    torch.cuda.synchronize()
+    c0 = s0 = 0
+    for n, m in zip(lens, counts):
+        ref = torch.sort(torch.sort(score[c0:c0 + n], descending=True, stable=True)[1][:m])[0].int()
+        assert torch.equal(idx[s0:s0 + m], ref) and torch.equal(pos[s0:s0 + m], ref) and torch.equal(row[s0:s0 + m], ref + c0)
+        c0, s0 = c0 + n, s0 + m
