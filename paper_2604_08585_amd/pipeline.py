@@ -268,11 +268,16 @@ def extract_anchors(desc, k: torch.Tensor, v: torch.Tensor, chunk_lens: List[int
     total = int(sum(n_per_chunk))
     norm = torch.empty(max(rows, 1), dtype=torch.float32, device=dev)
     qb.qcf_key_norm(desc, k, rows, norm)
-    ctx_off = torch.tensor(np.concatenate([[0], np.cumsum(chunk_lens)]), dtype=torch.int64, device=dev)
-    sel_off = torch.tensor(np.concatenate([[0], np.cumsum(n_per_chunk)]), dtype=torch.int64, device=dev)
+    # both offset tables in one pinned block and one asynchronous copy (two pageable copies made the host wait twice)
+    n = len(chunk_lens)
+    off = torch.zeros(2, n + 1, dtype=torch.int64, pin_memory=dev.type == "cuda")
+    offs = off.numpy()
+    np.cumsum(np.asarray(chunk_lens, dtype=np.int64), out=offs[0, 1:])
+    np.cumsum(np.asarray(n_per_chunk, dtype=np.int64), out=offs[1, 1:])
+    ctx_off, sel_off = off.to(dev, non_blocking=True)
     idx = torch.empty(max(total, 1), dtype=torch.int32, device=dev)
     row = torch.empty(max(total, 1), dtype=torch.int32, device=dev)
-    qb.qcf_select(len(chunk_lens), norm, ctx_off, rows, sel_off, total, None, idx, row, None)
+    qb.qcf_select(n, norm, ctx_off, rows, sel_off, total, None, idx, row, None)
     ak = torch.empty((max(total, 1),) + tuple(k.shape[1:]), dtype=k.dtype, device=dev)
     av = torch.empty_like(ak)
     qb.qcf_gather(desc, k, v, row, total, rows, ak, av)
