@@ -26,6 +26,8 @@ EXPORTS = [
     "qcf_linear_workspace_bytes", "qcf_linear", "qcf_rmsnorm", "qcf_swiglu",
     "qcf_key_norm", "qcf_gather",
 ]
+# declared in qcf_ffn.h
+FFN_EXPORTS = ["qcf_linear_swiglu_workspace_bytes", "qcf_linear_swiglu"]
 
 
 class QcfError(RuntimeError):
@@ -101,6 +103,10 @@ def load_library() -> C.CDLL:
     lib.qcf_rmsnorm.argtypes = [dp, vp, vp, dbl, i64, i32, vp, vp]
     lib.qcf_swiglu.restype = C.c_int
     lib.qcf_swiglu.argtypes = [dp, vp, i64, i32, vp, vp]
+    lib.qcf_linear_swiglu_workspace_bytes.restype = sz
+    lib.qcf_linear_swiglu_workspace_bytes.argtypes = [dp, i64, i32, i32]
+    lib.qcf_linear_swiglu.restype = C.c_int
+    lib.qcf_linear_swiglu.argtypes = [dp, vp, i64, i32, vp, i32, vp, vp, sz, vp]
     lib.qcf_key_norm.restype = C.c_int
     lib.qcf_key_norm.argtypes = [dp, vp, i64, vp, vp]
     lib.qcf_gather.restype = C.c_int
@@ -303,6 +309,15 @@ def qcf_rmsnorm(desc: LayerDesc, x: torch.Tensor, weight: torch.Tensor, eps: flo
 
 def qcf_swiglu(desc: LayerDesc, gate_up: torch.Tensor, M: int, F: int, out: torch.Tensor) -> None:
     _check(load_library().qcf_swiglu(C.byref(desc), _ptr(gate_up), M, F, _ptr(out), _stream()))
+
+
+def qcf_linear_swiglu(desc: LayerDesc, x: torch.Tensor, M: int, K: int, w_gate_up: torch.Tensor, F: int,
+                      out: torch.Tensor, workspace: Optional[torch.Tensor] = None) -> None:
+    lib = load_library()
+    if workspace is None:
+        workspace = _workspace(int(lib.qcf_linear_swiglu_workspace_bytes(C.byref(desc), M, K, F)), x.device)
+    wp, wn = _ws_args(workspace)
+    _check(lib.qcf_linear_swiglu(C.byref(desc), _ptr(x), M, K, _ptr(w_gate_up), F, _ptr(out), wp, wn, _stream()))
 
 
 def qcf_key_norm(desc: LayerDesc, k: torch.Tensor, rows: int, norm: torch.Tensor) -> None:

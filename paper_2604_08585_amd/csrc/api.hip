@@ -396,6 +396,28 @@ qcf_status qcf_swiglu(const qcf_layer_desc* desc, const void* gate_up, int64_t M
   return launch_swiglu(*desc, gate_up, M, F, out, (hipStream_t)stream);
 }
 
+size_t qcf_linear_swiglu_workspace_bytes(const qcf_layer_desc* desc, int64_t M, int32_t K, int32_t F) {
+  if (check_dtype(desc) != QCF_OK || M <= 0 || K <= 0 || F <= 0 || F > INT32_MAX / 2) return 0;
+  return linear_swiglu_workspace(*desc, M, K, F);
+}
+
+qcf_status qcf_linear_swiglu(const qcf_layer_desc* desc, const void* x, int64_t M, int32_t K, const void* w,
+                             int32_t F, void* out, void* workspace, size_t workspace_bytes, void* stream) {
+  QCF_TRY(check_dtype(desc));
+  if (M < 0) return fail(QCF_ERR_INVALID_ARG, "negative size");
+  if (M > kMaxRows) return fail(QCF_ERR_UNSUPPORTED, "too many rows");
+  if (K <= 0 || F <= 0 || K % 8 != 0 || F % 8 != 0)
+    return fail(QCF_ERR_INVALID_ARG, "K = %d and F = %d must be positive multiples of 8", K, F);
+  if (F > INT32_MAX / 2) return fail(QCF_ERR_UNSUPPORTED, "F = %d is too large", F);
+  if (M == 0) return QCF_OK;
+  QCF_TRY(need_ptr(x, "x"));
+  QCF_TRY(need_ptr(w, "w"));
+  QCF_TRY(need_ptr(out, "out"));
+  QCF_TRY(need_ws(workspace, workspace_bytes, linear_swiglu_workspace_needed(*desc, M, K, F)));
+  return launch_linear_swiglu(*desc, x, M, K, w, F, out, workspace, usable_ws(workspace, workspace_bytes),
+                              (hipStream_t)stream);
+}
+
 // ---- anchor extraction ------------------------------------------------------------
 qcf_status qcf_key_norm(const qcf_layer_desc* desc, const void* k, int64_t rows, float* norm, void* stream) {
   QCF_TRY(check_desc(desc));

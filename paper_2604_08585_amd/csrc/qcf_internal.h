@@ -9,6 +9,7 @@
 #include <atomic>
 
 #include "qcf.h"
+#include "qcf_ffn.h"
 
 namespace qcf {
 
@@ -228,10 +229,14 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
 size_t linear_workspace(const qcf_layer_desc& L, int64_t M, int32_t K, int32_t N);
 qcf_status launch_linear(const qcf_layer_desc& L, const void* x, int64_t M, int32_t K, const void* w, int32_t N,
                          const void* residual, void* out, void* ws, size_t ws_bytes, hipStream_t st);
+size_t linear_swiglu_workspace(const qcf_layer_desc& L, int64_t M, int32_t K, int32_t F);
+qcf_status launch_linear_swiglu(const qcf_layer_desc& L, const void* x, int64_t M, int32_t K, const void* w, int32_t F,
+                                void* out, void* ws, size_t ws_bytes, hipStream_t st);
 // bytes a call cannot do without (the rest of the workspace only makes it faster)
 size_t qkv_workspace_needed(const qcf_layer_desc& L, int64_t M);
 size_t attn_workspace_needed(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx);
 size_t linear_workspace_needed(const qcf_layer_desc& L, int64_t M, int32_t K, int32_t N);
+size_t linear_swiglu_workspace_needed(const qcf_layer_desc& L, int64_t M, int32_t K, int32_t F);
 qcf_status launch_rmsnorm(const qcf_layer_desc& L, const void* x, const void* weight, double eps, int64_t M,
                           int32_t cols, void* out, hipStream_t st);
 qcf_status launch_swiglu(const qcf_layer_desc& L, const void* gate_up, int64_t M, int32_t F, void* out,

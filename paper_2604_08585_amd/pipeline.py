@@ -238,7 +238,7 @@ class TailWeights:
 
 def layer_tail(desc, h_in: torch.Tensor, o_rows: torch.Tensor, tw: TailWeights) -> torch.Tensor:
     """Hidden states of the recomputed rows after the block: h1 = h_in + o w_o^T,
-    h_out = h1 + (silu(n w_gate^T) * (n w_up^T)) w_down^T with n = rmsnorm(h1).  Five library calls."""
+    h_out = h1 + (silu(n w_gate^T) * (n w_up^T)) w_down^T with n = rmsnorm(h1).  Four library calls."""
     M, dm = h_in.shape
     hd = tw.w_o.shape[1]
     F2 = tw.w_gate_up.shape[0]
@@ -247,10 +247,8 @@ def layer_tail(desc, h_in: torch.Tensor, o_rows: torch.Tensor, tw: TailWeights) 
     qb.qcf_linear(desc, o_rows.reshape(M, hd), M, hd, tw.w_o, dm, h_in, h1)
     n = torch.empty_like(h1)
     qb.qcf_rmsnorm(desc, h1, tw.norm_weight, tw.eps, M, dm, n)
-    gu = torch.empty((M, F2), dtype=dt, device=dev)
-    qb.qcf_linear(desc, n, M, dm, tw.w_gate_up, F2, None, gu)
     act = torch.empty((M, F2 // 2), dtype=dt, device=dev)
-    qb.qcf_swiglu(desc, gu, M, F2 // 2, act)
+    qb.qcf_linear_swiglu(desc, n, M, dm, tw.w_gate_up, F2 // 2, act)
     out = torch.empty_like(h1)
     qb.qcf_linear(desc, act, M, F2 // 2, tw.w_down, dm, h1, out)
     return out

@@ -127,3 +127,24 @@ def test_binding_fails_loudly_without_the_library(monkeypatch, tmp_path):
     monkeypatch.setattr(qb, "LIB_PATH", str(tmp_path / "missing.so"))
     with pytest.raises(qb.QcfError):
         qb.load_library()
+
+
+def test_linear_swiglu_arguments_and_workspace():
+    lib = qb.load_library()
+    text = re.sub(r"/\*.*?\*/", "", open(os.path.join(ROOT, "include", "qcf_ffn.h")).read(), flags=re.S)
+    assert sorted(set(re.findall(r"\b(qcf_[a-z_]+)\s*\(", text))) == sorted(qb.FFN_EXPORTS)
+    fake = 0x1000
+    d, bf = _desc(), _desc(dtype="bf16")
+    bad = _desc()
+    bad.dtype = 5
+    assert lib.qcf_linear_swiglu(C.byref(d), fake, 4, 20, fake, 64, fake, None, 0, None) == 1
+    assert lib.qcf_linear_swiglu(C.byref(d), fake, 4, 64, fake, 12, fake, None, 0, None) == 1
+    assert lib.qcf_linear_swiglu(C.byref(bf), fake, 4, 64, fake, 64, None, None, 0, None) == 1
+    assert lib.qcf_linear_swiglu(C.byref(bad), fake, 4, 64, fake, 64, fake, None, 0, None) == 2
+    assert lib.qcf_linear_swiglu(C.byref(bf), fake, 4, 64, fake, 1 << 30, fake, None, 0, None) == 2
+    assert lib.qcf_linear_swiglu(C.byref(d), None, 0, 64, None, 64, None, None, 0, None) == 0
+    # the product and the generic path's float32 sums go through the workspace where the tiles do not fit
+    for desc, size, K, F in [(d, 4, 24, 40), (bf, 2, 24, 40), (bf, 2, 64, 40), (bf, 2, 8192, 1 << 19)]:
+        need = lib.qcf_linear_swiglu_workspace_bytes(C.byref(desc), 4, K, F)
+        assert need >= 4 * 2 * F * size + lib.qcf_linear_workspace_bytes(C.byref(desc), 4, K, 2 * F)
+        assert lib.qcf_linear_swiglu(C.byref(desc), fake, 4, K, fake, F, fake, fake, 4 * 2 * F * size - 1, None) == 3

@@ -53,6 +53,63 @@ def test_linear_tile_choices(M, K, N, res):
     one_rounding(plain, ref)
 
 
+@pytest.mark.parametrize("M,K,F", [
+    (1300, 2048, 8256),              # 256 x 256 tiles, an odd number of 128-column blocks
+    (2600, 4096, 3072),              # 256 x 256 tiles for the full rounds, smaller tiles for the rest
+    (1, 1088, 64), (61, 4096, 1408), (100, 2048, 512),         # one block; split contraction with 64- and 128-row tiles
+    (130, 64, 192),                  # a single k-tile
+    (33, 72, 128), (33, 128, 72)])   # K or F that the tiles do not cover: through the workspace
+def test_linear_swiglu(M, K, F):
+    """The activation in the product's epilogue gives what the two separate calls give (the sums of an element run in
+    the same order and gate and up are rounded to bf16 first: bit for bit), with and without the optional workspace."""
+    say(f"linear + swiglu M={M} K={K} F={F}")
+    g = gen(46)
+    x = torch.randn((M, K), generator=g, device=DEV, dtype=BF)
+    w = torch.randn((2 * F, K), generator=g, device=DEV, dtype=BF) * (3.0 * K ** -0.5)
+    desc = qb.make_desc(inputs.LayerShape(4096, 32, 8, 128, 500000.0, "bf16"))
+    gu = torch.empty((M, 2 * F), dtype=BF, device=DEV)
+    want = torch.empty((M, F), dtype=BF, device=DEV)
+    out = torch.full((M, F), 7.0, dtype=BF, device=DEV)
+    qb.qcf_linear(desc, x, M, K, w, 2 * F, None, gu)
+    qb.qcf_swiglu(desc, gu, M, F, want)
+    qb.qcf_linear_swiglu(desc, x, M, K, w, F, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+    lib = qb.load_library()
+    plain = torch.full((M, F), 7.0, dtype=BF, device=DEV)
+    rc = lib.qcf_linear_swiglu(C.byref(desc), x.data_ptr(), M, K, w.data_ptr(), F, plain.data_ptr(), None, 0,
+                               torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    if K % 64 or F % 64:
+        assert rc == 3                # QCF_ERR_WORKSPACE_TOO_SMALL
+    else:
+        assert rc == 0
+        # one contraction instead of several ranges: gate and up may round to the neighbouring bf16 value, and
+        # silu's slope is at most 1.1
+        lim = 2.0 ** -7 * (1.1 * gu[:, :F].float().abs() * gu[:, F:].float().abs() + want.float().abs()) + 2.0 ** -8 * want.float().abs() + 1e-3
+        assert bool(((plain.float() - want.float()).abs() <= lim).all())
+
+
+def test_swiglu_over_the_float_range():
+    """Against float64: the argument of the exponential carries a rounding (relative error |g| 2^-24 of the exponential),
+    the other operations a few of 2^-24; results below 2^-110 may be flushed.  Infinities and NaN as g / (1 + exp(-g))
+    gives them."""
+    g = torch.cat([torch.linspace(-95, 95, 4001), torch.tensor([0.0, -0.0, 1e-30, -1e-30, 3e38, -3e38, -87.4, -88.5, -89.0])])
+    g = torch.cat([g, torch.zeros(-g.numel() % 8)])
+    F = g.numel()
+    out = torch.empty((1, F), dtype=torch.float32, device=DEV)
+    desc = qb.make_desc(inputs.LayerShape(256, 4, 2, 64, 10000.0, "f32"))
+    qb.qcf_swiglu(desc, torch.cat([g, torch.full((F,), 1.0)]).to(DEV), 1, F, out)
+    ref = g.double() / (1.0 + torch.exp(-g.double()))
+    err = (out[0].cpu().double() - ref).abs()
+    assert bool((err <= (6.0 + 2.0 * g.abs().clamp(max=100.0).double()) * 2.0 ** -24 * ref.abs() + 2.0 ** -110).all())
+    special = torch.tensor([float("inf"), -float("inf"), float("nan"), 0.0, 0.0, 0.0, 0.0, 0.0])
+    out = torch.empty((1, 8), dtype=torch.float32, device=DEV)
+    qb.qcf_swiglu(desc, torch.cat([special, torch.ones(8)]).to(DEV), 1, 8, out)
+    got = out[0].cpu()
+    assert float(got[0]) == float("inf") and bool(got[1:3].isnan().all()) and bool((got[3:] == 0).all())
+
+
 def _rotate(y, pos, base, style):
     """Rotary embedding of y [M, heads, d] in float64 angles."""
     d = y.shape[-1]
