@@ -1043,17 +1043,29 @@ double rounds_of(int64_t wgs) {
   return (double)((wgs + cus - 1) / cus);
 }
 double quad_us(int64_t mt, int nb, int nk) { return rounds_of(mt * ((nb + 1) / 2)) * (1.40 * nk + 12.0); }
+double ws256_us(int64_t mt, int nb, int nk) { return rounds_of(mt * nb) * (0.75 * nk + 10.0); }
+// 128 x 128 tiles over three and more rounds wait for their operands: 2400 rows, K 8192, N 10240 take 0.7 us per k-tile.
+// (With 0.45 there they were chosen: that layer took 1262 us, with two rounds of 256 x 256 tiles 1037.)
+double ws128_tile_us(double rounds) { return rounds > 2 ? 0.65 : 0.45; }
+double ws128_us(int64_t mt, int nb, int nk) {
+  const double r = rounds_of(mt * nb);
+  return r * (ws128_tile_us(r) * nk + 8.0);
+}
 
-// the load/compute-split kernels, over nb column blocks
-GemmPlan plan_ws(int64_t M, int nb, int nk, bool may_split) {
-  GemmPlan best{kWs256, 1, rounds_of((M + 255) / 256 * nb) * (0.75 * nk + 10.0)};
-  const double t128 = rounds_of((M + 127) / 128 * nb) * (0.45 * nk + 8.0);
+size_t split_part_bytes(int64_t M, int nb, int bm, int splits) {
+  return splits <= 1 ? 0 : (size_t)splits * nb * ((M + bm - 1) / bm) * bm * kBN * sizeof(float);
+}
+
+// the load/compute-split kernels, over nb column blocks, with at most part_bytes of partial sums
+GemmPlan plan_ws(int64_t M, int nb, int nk, size_t part_bytes) {
+  GemmPlan best{kWs256, 1, ws256_us((M + 255) / 256, nb, nk)};
+  const double t128 = ws128_us((M + 127) / 128, nb, nk);
   if (t128 < best.us) best = GemmPlan{kWs128, 1, t128};
   const int bm = M <= 64 ? 64 : 128;
   const int64_t tiles = (M + bm - 1) / bm * nb;
-  const double c = bm == 64 ? 0.40 : 0.45;
+  const double c = bm == 64 ? 0.40 : ws128_tile_us(rounds_of(tiles));
   for (int s = 1; s <= 16 && s * 4 <= nk; ++s) {
-    if (s > 1 && !may_split) break;
+    if (split_part_bytes(M, nb, bm, s) > part_bytes) break;
     const int len = (nk + s - 1) / s;
     if ((nk + len - 1) / len != s) continue;                     // (a range would be empty)
     double t = std::max(rounds_of(tiles * s) * c * len, (double)nb * nk * (kBN * kBK * 2) / 4.6e6) + rounds_of(tiles * s) * 6.0;
@@ -1063,14 +1075,59 @@ GemmPlan plan_ws(int64_t M, int nb, int nk, bool may_split) {
   return best;
 }
 
-size_t split_part_bytes(int64_t M, int nb, const GemmPlan& p) {
-  if (p.splits <= 1) return 0;
-  const int bm = p.kind == kWs64 ? 64 : 128;
-  return (size_t)p.splits * nb * ((M + bm - 1) / bm) * bm * kBN * sizeof(float);
+// The whole product: up to two launches.  The first, in tiles of `kind`, covers `rows` rows of all blocks or `blocks`
+// blocks of all rows (rows == M and blocks == nb: everything); `rest` is the rest.
+//
+// A tile fills whole rounds of compute units only, so where the last round would be thin the first launch takes what
+// full rounds hold and smaller tiles the rest: the column blocks that are left (256 x 256 tiles), or the rows that are
+// left (tiles of 256 rows), whose contraction may be split because they are few.  Measured, without the division by
+// rows and with it: layer tail (d_model 4096, F 14336) of 2100 rows 889 and 716 us, of 2458 rows 1004 and 852; layer of
+// 64 heads, d_model 8192, over 32768 tokens 3346 and 3294.  (128 x 128 tiles for the whole rounds lose: tail of 1229
+// rows 483 us in one launch, 492 that way.)
+struct ProductPlan { GemmKind kind; int64_t rows; int blocks; GemmPlan rest; double us; };
+
+ProductPlan plan_product(int64_t M, int nb, int nk, bool by_rows, size_t part_bytes) {
+  const GemmPlan one = plan_ws(M, nb, nk, part_bytes);
+  ProductPlan best{one.kind, 0, 0, one, one.us};                 // (rows and blocks 0: `rest` is everything)
+  const int cus = compute_unit_count();
+  const int64_t mt = (M + 255) / 256;
+  if (nk % 2 == 0) {                                             // (the 256 x 256 kernel takes k-tiles in pairs)
+    const double whole = quad_us(mt, nb, nk);
+    if (whole < best.us) best = ProductPlan{kQuad, M, nb, one, whole};
+    const int64_t rounds = mt * ((nb + 1) / 2) / cus;
+    for (int64_t r = rounds; r >= 1 && r >= rounds - 1; --r) {
+      const int qb = (int)(r * cus / mt * 2);
+      if (qb <= 0 || qb >= nb) continue;
+      const GemmPlan rest = plan_ws(M, nb - qb, nk, 0);
+      const double t = quad_us(mt, qb, nk) + rest.us + 2.0;
+      if (t < best.us) best = ProductPlan{kQuad, M, qb, rest, t};
+    }
+  }
+  if (!by_rows) return best;
+  for (GemmKind kind : {kQuad, kWs256}) {
+    if (kind == kQuad && nk % 2 != 0) continue;
+    const int64_t units = kind == kQuad ? (nb + 1) / 2 : nb;     // workgroups of a row tile
+    const int64_t rounds = mt * units / cus;
+    for (int64_t r = rounds; r >= 1 && r >= rounds - 1; --r) {
+      const int64_t tiles = r * cus / units;
+      if (tiles <= 0 || tiles >= mt) continue;
+      const GemmPlan rest = plan_ws(M - tiles * 256, nb, nk, part_bytes);
+      const double t = (kind == kQuad ? quad_us(tiles, nb, nk) : ws256_us(tiles, nb, nk)) + rest.us + 2.0;
+      // (256 x 256 tiles that fill half a round run faster than estimated, 256 x 128 tiles over several rounds slower:
+      // 4200 rows, K 4096, N 6144 lost 28 us where 3 us were promised, 1500 rows 7 us where 14 were)
+      if (t < best.us * (kind == kQuad ? 1.0 : 0.85)) best = ProductPlan{kind, tiles * 256, nb, rest, t};
+    }
+  }
+  return best;
 }
 
 // workspace a product of M rows x nb column blocks x nk k-tiles can use (not needed: without it the contraction stays whole)
-size_t gemm_part_bytes(int64_t M, int nb, int nk) { return split_part_bytes(M, nb, plan_ws(M, nb, nk, true)); }
+size_t gemm_part_bytes(int64_t M, int nb, int nk) {
+  const ProductPlan p = plan_product(M, nb, nk, true, SIZE_MAX);
+  if (p.blocks == nb && p.rows == M) return 0;
+  return split_part_bytes(p.blocks == nb ? M - p.rows : M, p.blocks > 0 && p.blocks < nb ? nb - p.blocks : nb,
+                          p.rest.kind == kWs64 ? 64 : 128, p.rest.splits);
+}
 
 template <typename C, int EPI, bool WIDE>
 qcf_status run_ws(QkvArgs a, int splits, hipStream_t st) {
@@ -1146,8 +1203,31 @@ qcf_status run_rope_split(const qcf_layer_desc& L, const float* y, int64_t M, co
   return check_launch("qkv rope");
 }
 
-// The whole product.  256 x 256 tiles have the best rate but fill whole rounds of compute units only: where their
-// last round would be thin, they take as many column blocks as full rounds hold and smaller tiles the rest.
+// The arguments of the same product without its first `rows` rows (a multiple of 256, so alignments stay).
+template <int EPI>
+QkvArgs rows_from(QkvArgs a, int64_t rows) {
+  const int64_t q_cols = EPI == kGlu ? a.glu : (int64_t)a.H * a.D, kv_cols = (int64_t)a.Hkv * a.D;
+  if (a.gather) a.gather += rows;
+  else { a.x += rows * a.d_model; a.x_rows -= rows; }
+  if (a.pos) a.pos += rows;
+  if (a.dst_rows) a.dst_rows += rows;
+  a.q += rows * q_cols;
+  if (a.residual) a.residual += rows * q_cols;
+  if (is_rope(EPI)) { a.k += rows * kv_cols; a.v += rows * kv_cols; }
+  a.M -= rows;
+  return a;
+}
+
+template <int EPI>
+qcf_status run_kind(const QkvArgs& a, GemmKind kind, int splits, hipStream_t st) {
+  switch (kind) {
+    case kQuad: return run_quad<EPI>(a, st);
+    case kWs64: return run_ws<Ws64, EPI, false>(a, splits, st);
+    case kWs128: return run_ws<Ws128, EPI, false>(a, splits, st);
+    default: return run_ws<Ws256, EPI, false>(a, splits, st);
+  }
+}
+
 template <int EPI>
 qcf_status run_gemm(const QkvArgs& a_in, int nb, void* ws, size_t ws_bytes, hipStream_t st) {
   QkvArgs a = a_in;
@@ -1159,44 +1239,18 @@ qcf_status run_gemm(const QkvArgs& a_in, int nb, void* ws, size_t ws_bytes, hipS
   if (nb > 65535) return fail(QCF_ERR_UNSUPPORTED, "qkv: too many columns");
   // (x of 4 GiB and more needs 64-bit addresses per lane: one variant, such calls have plenty of rows)
   if (wide) return run_ws<Ws128, EPI, true>(a, 1, st);
-  GemmPlan p = plan_ws(a.M, nb, nk, true);
-  if (split_part_bytes(a.M, nb, p) > ws_bytes) p = plan_ws(a.M, nb, nk, false);
-  int quad_blocks = 0;
-  if (nk % 2 == 0) {
-    const int64_t mt = (a.M + 255) / 256;
-    const int per_round = (int)std::min<int64_t>(nb, compute_unit_count() / mt * 2);     // column blocks of one full round
-    double best = p.us;
-    const double whole = quad_us(mt, nb, nk);
-    if (whole < best) { best = whole; quad_blocks = nb; }
-    if (per_round > 0) {
-      for (int r = nb / per_round; r >= 1 && r >= nb / per_round - 1; --r) {
-        const int qb = r * per_round;
-        if (qb >= nb) continue;
-        const double t = quad_us(mt, qb, nk) + plan_ws(a.M, nb - qb, nk, false).us + 2.0;
-        if (t < best) { best = t; quad_blocks = qb; }
-      }
-    } else {
-      const int64_t rounds = mt * ((nb + 1) / 2) / compute_unit_count();
-      const int qb = (int)(rounds * compute_unit_count() / mt * 2);
-      if (qb > 0 && qb < nb) {
-        const double t = quad_us(mt, qb, nk) + plan_ws(a.M, nb - qb, nk, false).us + 2.0;
-        if (t < best) { best = t; quad_blocks = qb; }
-      }
-    }
-  }
-  if (quad_blocks > 0) {
-    a.n_tiles = quad_blocks;
-    QCF_TRY(run_quad<EPI>(a, st));
-    if (quad_blocks == nb) return QCF_OK;
-    a.n_tile0 = quad_blocks;
-    a.n_tiles = nb - quad_blocks;
-    p = plan_ws(a.M, a.n_tiles, nk, false);
-  }
-  switch (p.kind) {
-    case kWs64: return run_ws<Ws64, EPI, false>(a, p.splits, st);
-    case kWs128: return run_ws<Ws128, EPI, false>(a, p.splits, st);
-    default: return run_ws<Ws256, EPI, false>(a, p.splits, st);
-  }
+  // (rows that x does not have read its first row: x must not be moved then)
+  const ProductPlan p = plan_product(a.M, nb, nk, a.gather || a.x_rows >= a.M, ws_bytes);
+  if (p.blocks == 0) return run_kind<EPI>(a, p.rest.kind, p.rest.splits, st);
+  QkvArgs first = a;
+  first.M = p.rows;
+  first.n_tiles = p.blocks;
+  QCF_TRY(run_kind<EPI>(first, p.kind, 1, st));
+  if (p.rows < a.M) return run_kind<EPI>(rows_from<EPI>(a, p.rows), p.rest.kind, p.rest.splits, st);
+  if (p.blocks == nb) return QCF_OK;
+  a.n_tile0 = p.blocks;
+  a.n_tiles = nb - p.blocks;
+  return run_kind<EPI>(a, p.rest.kind, p.rest.splits, st);
 }
 
 }  // namespace

@@ -32,6 +32,7 @@ def one_rounding(got, ref):
 @pytest.mark.parametrize("M,K,N,res", [
     (5000, 2048, 8320, True),        # 256 x 256 tiles: ragged rows, an odd number of column blocks
     (2600, 4096, 6144, False),       # 256 x 256 tiles for the full rounds, smaller tiles for the rest
+    (2458, 14336, 4096, True), (2300, 4160, 4096, True), (4916, 4096, 10240, False),   # whole rounds of row tiles, then the rows left
     (61, 2048, 1024, True), (64, 4096, 4096, False), (65, 4096, 1024, True), (128, 4096, 6144, False),   # split contraction
     (1, 1088, 384, True)])           # 17 k-tiles: ranges of unequal length
 def test_linear_tile_choices(M, K, N, res):
@@ -56,6 +57,7 @@ def test_linear_tile_choices(M, K, N, res):
 @pytest.mark.parametrize("M,K,F", [
     (1300, 2048, 8256),              # 256 x 256 tiles, an odd number of 128-column blocks
     (2600, 4096, 3072),              # 256 x 256 tiles for the full rounds, smaller tiles for the rest
+    (4916, 4096, 5120),              # whole rounds of row tiles, then the rows left
     (1, 1088, 64), (61, 4096, 1408), (100, 2048, 512),         # one block; split contraction with 64- and 128-row tiles
     (130, 64, 192),                  # a single k-tile
     (33, 72, 128), (33, 128, 72)])   # K or F that the tiles do not cover: through the workspace
@@ -124,6 +126,7 @@ def _rotate(y, pos, base, style):
 
 @pytest.mark.parametrize("M,dm,H,Hkv,D,style", [
     (4700, 2048, 32, 8, 128, 0), (4700, 2048, 32, 8, 128, 1), (4700, 2048, 64, 16, 64, 0),   # 256 x 256 tiles
+    (4916, 4096, 64, 8, 128, 0), (4916, 4096, 64, 8, 128, 1),                                # rows left for a second launch
     (60, 2048, 8, 2, 128, 0), (60, 2048, 8, 2, 64, 1), (127, 2048, 8, 2, 64, 0)])             # split contraction
 def test_projection_tile_choices(M, dm, H, Hkv, D, style):
     """Rotation, gathering (indices outside x give zero rows), and the write-back, for positions up to 2^31."""
