@@ -15,6 +15,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "gemm_args.h"
 #include "qcf_internal.h"
 
 namespace qcf {
@@ -285,42 +286,6 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const T* __restrict__ gate_
 constexpr int kBK = 64;                  // contraction elements per LDS stage (rows of 128 bytes)
 constexpr int kBN = 128;                 // columns of an output block: whole heads, or 64 gate + 64 up columns
 constexpr size_t kRhoBytes = 64 * sizeof(float2);   // theta_i / (2 pi) of up to 64 rotary pairs, as (high, low) floats
-
-struct QkvArgs {
-  const bf16_t* x;
-  const bf16_t* w;
-  const int32_t* gather;
-  const int32_t* pos;            // [M] absolute positions (rotary embedding; unused by the plain linear map)
-  double neg2_over_d_log2base;   // theta_i = 2^(i * this)
-  int64_t x_rows, M;
-  int d_model, H, Hkv, D;
-  int m_tiles, n_tiles;          // row tiles and 128-column blocks of this launch
-  int n_tile0;                   // first block of this launch
-  int m_group;                   // row tiles walked together (workgroup order of the 256 x 256 kernel)
-  int rows_over_xcds;            // workgroup order of the load/compute-split kernel (see there)
-  int splits, split_len;         // the contraction is cut into `splits` ranges of split_len k-tiles
-  float4* part;                  // their partial sums (splits > 1)
-  bf16_t* q;
-  bf16_t* k;
-  bf16_t* v;
-  // plain linear map (qcf_linear): all H*D columns go to q without rotation, or with the residual added (kAdd)
-  const bf16_t* residual;
-  // gated SiLU: block b holds weight rows 64 b .. +63 (gate) and glu + 64 b .. +63 (up) and gives
-  // 64 output columns
-  int glu;
-  // projection fused with the write-back: row m of the K and V tiles also goes to row dst_rows[m] of the fused
-  // cache (rows outside [0, fused_rows) are skipped); all null / 0 otherwise
-  const int32_t* dst_rows;
-  bf16_t* k_fused;
-  bf16_t* v_fused;
-  int64_t fused_rows;
-};
-
-// What the epilogue does with a block: rotary embedding (half-split pairs of 128- or 64-wide heads, interleaved
-// pairs), nothing, a residual, or the gated SiLU.  A template parameter: with all of them behind branches in one
-// kernel the compiler moves accumulators of the k-loop to scratch.
-enum Epi { kRopeHalf128, kRopeHalf64, kRopeInter, kPlain, kAdd, kGlu };
-constexpr bool is_rope(int epi) { return epi <= kRopeInter; }
 
 // Where a 128-column block of the product goes.
 struct OutTile {
@@ -752,7 +717,7 @@ __global__ __launch_bounds__(C::NTHR) void qkv_ws_kernel(QkvArgs a) {
     __syncthreads();
     if (a.splits > 1) {
       if constexpr (TM == 1) {        // partial sums in register order: 1 KB per store
-        float4* dst = a.part + ((((int64_t)split * a.n_tiles + n_tile) * a.m_tiles + m_tile) * C::NC + wave) * 1024 + lane;
+        float4* dst = static_cast<float4*>(a.part) + ((((int64_t)split * a.n_tiles + n_tile) * a.m_tiles + m_tile) * C::NC + wave) * 1024 + lane;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -779,7 +744,7 @@ __global__ __launch_bounds__(256) void qkv_split_reduce(QkvArgs a, int n_groups)
   if (!ot.out) return;
   EpiRows<1> rows;
   load_epi_rows<1, EPI>(a, (int64_t)grp * 32, lane, rows);
-  const float4* src = a.part + ((int64_t)n_tile * n_groups + grp) * 1024 + wave * 256 + lane;
+  const float4* src = static_cast<const float4*>(a.part) + ((int64_t)n_tile * n_groups + grp) * 1024 + wave * 256 + lane;
   const int64_t stride = (int64_t)a.n_tiles * n_groups * 1024;
   float4 sum[4];
 #pragma unroll
@@ -1203,21 +1168,6 @@ qcf_status run_rope_split(const qcf_layer_desc& L, const float* y, int64_t M, co
   return check_launch("qkv rope");
 }
 
-// The arguments of the same product without its first `rows` rows (a multiple of 256, so alignments stay).
-template <int EPI>
-QkvArgs rows_from(QkvArgs a, int64_t rows) {
-  const int64_t q_cols = EPI == kGlu ? a.glu : (int64_t)a.H * a.D, kv_cols = (int64_t)a.Hkv * a.D;
-  if (a.gather) a.gather += rows;
-  else { a.x += rows * a.d_model; a.x_rows -= rows; }
-  if (a.pos) a.pos += rows;
-  if (a.dst_rows) a.dst_rows += rows;
-  a.q += rows * q_cols;
-  if (a.residual) a.residual += rows * q_cols;
-  if (is_rope(EPI)) { a.k += rows * kv_cols; a.v += rows * kv_cols; }
-  a.M -= rows;
-  return a;
-}
-
 template <int EPI>
 qcf_status run_kind(const QkvArgs& a, GemmKind kind, int splits, hipStream_t st) {
   switch (kind) {
@@ -1235,7 +1185,7 @@ qcf_status run_gemm(const QkvArgs& a_in, int nb, void* ws, size_t ws_bytes, hipS
   const bool wide = (uint64_t)a.x_rows * (uint64_t)a.d_model * 2u >= (1ull << 32);
   a.n_tile0 = 0;
   a.n_tiles = nb;
-  a.part = static_cast<float4*>(ws);
+  a.part = ws;
   if (nb > 65535) return fail(QCF_ERR_UNSUPPORTED, "qkv: too many columns");
   // (x of 4 GiB and more needs 64-bit addresses per lane: one variant, such calls have plenty of rows)
   if (wide) return run_ws<Ws128, EPI, true>(a, 1, st);

@@ -1,0 +1,61 @@
+"""Host arithmetic of the product's division by rows (csrc/gemm_args.h), compiled and run on the CPU."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include "gemm_args.h"
+using namespace qcf;
+
+// every pattern of outputs that are not wanted (bits: q, k, v, fused cache, gather, residual)
+template <int EPI> int check(int64_t rows) {
+  static bf16_t buf[1];
+  static int32_t idx[1];
+  int bad = 0;
+  for (int m = 0; m < 64; ++m) {
+    QkvArgs a{};
+    a.x = buf; a.w = buf; a.M = a.x_rows = rows + 77; a.d_model = 512; a.H = 4; a.Hkv = is_rope(EPI) ? 2 : 0; a.D = 128; a.glu = 320;
+    a.q = m & 1 ? nullptr : buf;
+    a.k = m & 2 || !is_rope(EPI) ? nullptr : buf;
+    a.v = m & 4 || !is_rope(EPI) ? nullptr : buf;
+    a.pos = is_rope(EPI) ? idx : nullptr;
+    if (!(m & 8)) { a.dst_rows = idx; a.k_fused = buf; a.v_fused = buf; }
+    if (!(m & 16)) a.gather = idx;
+    if (!(m & 32)) a.residual = buf;
+    const QkvArgs b = rows_from<EPI>(a, rows);
+    const int64_t qc = EPI == kGlu ? 320 : 512;
+    bad += b.q != (a.q ? a.q + rows * qc : nullptr);
+    bad += b.k != (a.k ? a.k + rows * 256 : nullptr);
+    bad += b.v != (a.v ? a.v + rows * 256 : nullptr);
+    bad += b.residual != (a.residual ? a.residual + rows * qc : nullptr);
+    bad += b.dst_rows != (a.dst_rows ? a.dst_rows + rows : nullptr);
+    bad += b.pos != (a.pos ? a.pos + rows : nullptr);
+    bad += b.gather != (a.gather ? a.gather + rows : nullptr);
+    bad += a.gather ? b.x != a.x || b.x_rows != a.x_rows : b.x != a.x + rows * 512 || b.x_rows != 77;
+    bad += b.k_fused != a.k_fused || b.v_fused != a.v_fused || b.w != a.w || b.M != 77;
+  }
+  return bad;
+}
+
+int main() {
+  int bad = 0;
+  const int64_t cuts[] = {256, 1280, 4864};
+  for (int64_t rows : cuts) {
+    bad += check<kRopeHalf128>(rows) + check<kRopeHalf64>(rows) + check<kRopeInter>(rows);
+    bad += check<kPlain>(rows) + check<kAdd>(rows) + check<kGlu>(rows);
+  }
+  std::printf("%d\n", bad);
+  return bad != 0;
+}
+"""
+
+
+def test_a_null_output_stays_null_when_rows_are_cut_off(tmp_path):
+    src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-I" + os.path.join(ROOT, "paper_2604_08585_amd", "csrc"), str(src), "-o",
+                    str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout

@@ -160,6 +160,39 @@ def test_projection_tile_choices(M, dm, H, Hkv, D, style):
         assert torch.equal(fused, ref)
 
 
+@pytest.mark.parametrize("M,dm,H,Hkv", [
+    (1300, 4096, 32, 8),             # whole rounds of row tiles, then 20 rows with a split contraction
+    (4916, 8192, 64, 8),             # the same, more rows left
+    (61, 4096, 32, 8)])              # one launch
+@pytest.mark.parametrize("want", ["q", "kv", "v", "scatter"])
+def test_projection_outputs_that_are_not_wanted(M, dm, H, Hkv, want):
+    """A NULL output is skipped in every launch of a divided product; the others are those of the full call."""
+    say(f"projection without some outputs M={M} H={H} want={want}")
+    sh = inputs.LayerShape(dm, H, Hkv, 128, 500000.0, "bf16")
+    g, desc = gen(52), qb.make_desc(sh)
+    x = torch.randn((M, dm), generator=g, device=DEV, dtype=BF)
+    w = torch.randn((sh.qkv_rows, dm), generator=g, device=DEV, dtype=BF) * dm ** -0.5
+    pos, dst = torch.arange(M, device=DEV).int(), torch.randperm(M, generator=g, device=DEV).int()
+    new = lambda: [torch.full((M, h, 128), 7.0, dtype=BF, device=DEV) for h in (H, Hkv, Hkv)]
+    full, part = new(), new()
+    qb.qcf_recompute_qkv(desc, x, M, None, M, w, pos, *full)
+    if want == "scatter":
+        kf, vf = torch.full_like(part[1], 7.0), torch.full_like(part[2], 7.0)
+        qb.qcf_recompute_qkv_scatter(desc, x, M, None, M, w, pos, None, part[1], part[2], dst, kf, vf, M)
+        got, kept = (1, 2), (0,)
+    else:
+        got = {"q": (0,), "kv": (1, 2), "v": (2,)}[want]
+        kept = tuple(i for i in range(3) if i not in got)
+        qb.qcf_recompute_qkv(desc, x, M, None, M, w, pos, *(part[i] if i in got else None for i in range(3)))
+    torch.cuda.synchronize()
+    for i in got:
+        assert torch.equal(part[i], full[i])
+    for i in kept:
+        assert bool((part[i] == 7.0).all())
+    if want == "scatter":
+        assert torch.equal(kf[dst.long()], full[1]) and torch.equal(vf[dst.long()], full[2])
+
+
 def _attention64(q, k, v, pos, scale):
     """Plain float64 attention of rows q [n, H, d] over k, v [T, Hkv, d]; row i sees tokens <= pos[i]."""
     G = q.shape[1] // k.shape[1]
