@@ -285,7 +285,8 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const T* __restrict__ gate_
 
 constexpr int kBK = 64;                  // contraction elements per LDS stage (rows of 128 bytes)
 constexpr int kBN = 128;                 // columns of an output block: whole heads, or 64 gate + 64 up columns
-constexpr size_t kRhoBytes = 64 * sizeof(float2);   // theta_i / (2 pi) of up to 64 rotary pairs, as (high, low) floats
+constexpr int kRho16 = 64;               // rotary pairs of a head, at most
+constexpr size_t kRhoBytes = 2 * kRho16 * sizeof(float2);      // their frequencies (fill_rho)
 
 // Where a 128-column block of the product goes.
 struct OutTile {
@@ -321,31 +322,46 @@ __device__ __forceinline__ uint32_t block_w_step(const QkvArgs& a, int c) {
 }
 
 // Rotary frequencies in turns per position, theta_i / (2 pi) = 2^(i * c) / (2 pi), for the d/2 pairs of a head:
-// computed in float64 and kept as two floats, high + low (written by 64 threads before the barrier that precedes
-// the epilogue).
+// computed in float64 and kept as two floats, high + low; kRho16 entries further the fraction of 2^16 times each
+// (written by 64 threads before the barrier that precedes the epilogue).
+__device__ __forceinline__ float2 two_floats(double x) {
+  const float hi = (float)x;
+  return make_float2(hi, (float)(x - (double)hi));
+}
 __device__ __forceinline__ void fill_rho(const QkvArgs& a, float2* sRho, int i) {
   if (i < a.D / 2) {
     const double rho = exp2(a.neg2_over_d_log2base * (double)i) * 0.15915494309189535;
-    const float hi = (float)rho;
-    sRho[i] = make_float2(hi, (float)(rho - (double)hi));
+    sRho[i] = two_floats(rho);
+    sRho[kRho16 + i] = two_floats(rho * 65536.0 - floor(rho * 65536.0));
   }
 }
-// A position as the nearest float and the (integer) rest.
-struct RowPos { float p, rest; };
+// A position for the rotation: a whole float below 2^24; from there on 2^16 * p16 + p.
+constexpr int32_t kNearPos = 1 << 24;
+__device__ __forceinline__ bool is_far(int32_t pos) { return pos <= -kNearPos || pos >= kNearPos; }
+struct RowPos { float p, p16; };
+template <bool FAR>
 __device__ __forceinline__ RowPos row_pos(int32_t pos) {
-  RowPos r;
-  r.p = (float)pos;
-  r.rest = (float)((int64_t)pos - (int64_t)r.p);
-  return r;
+  const bool far = FAR && is_far(pos);
+  return RowPos{(float)(far ? pos & 0xffff : pos), far ? (float)(pos >> 16) : 0.f};
 }
-// (cos, sin) of pos * theta for one pair.  The angle in turns is (p + rest) * (hi + lo): the product p * hi is
-// rounded, its error is exact in an FMA, and only the fraction of the rounded part matters, so the sum below is good
-// to about 1e-7 of a turn for positions below 2^24 (rest = 0) and 2e-6 for any 32-bit position.
-__device__ __forceinline__ void rotary_factor(RowPos pos, float2 rho, float& c, float& sn) {
+// fraction (plus a small error term) of p * (hi + lo): the product p * hi is rounded, its error is exact in an FMA, and
+// only the fraction of the rounded part matters, so the sum is good to about 1e-7 for a whole |p| < 2^24
+__device__ __forceinline__ float turn_fraction(float p, float2 rho) {
 #pragma clang fp contract(off)          // the rounded product and its error term must stay two operations
-  const float t_hi = pos.p * rho.x;
-  const float t_lo = __builtin_fmaf(pos.rest, rho.x, __builtin_fmaf(pos.p, rho.y, __builtin_fmaf(pos.p, rho.x, -t_hi)));
-  const float fr = __builtin_amdgcn_fractf(t_hi) + t_lo;
+  const float t_hi = p * rho.x;
+  const float t_lo = __builtin_fmaf(p, rho.y, __builtin_fmaf(p, rho.x, -t_hi));
+  return __builtin_amdgcn_fractf(t_hi) + t_lo;
+}
+// (cos, sin) of pos * theta for one pair, the angle in turns.  FAR (a wave with a position from 2^24 on): plus the turns
+// of p16 times the fraction of 2^16 frequencies, which are exactly 0 for the other positions.  One float product with
+// the rest of the position in another was off by up to 4e-6 of a turn there; this stays at 2e-7.
+template <bool FAR> struct Rho { float2 lo; __device__ Rho(const float2* t) : lo(*t) {} };
+template <> struct Rho<true> { float2 lo, hi; __device__ Rho(const float2* t) : lo(*t), hi(t[kRho16]) {} };
+template <bool FAR>
+__device__ __forceinline__ void rotary_factor(int32_t pos, const Rho<FAR>& rho, float& c, float& sn) {
+  const RowPos r = row_pos<FAR>(pos);
+  float fr = turn_fraction(r.p, rho.lo);
+  if constexpr (FAR) fr += turn_fraction(r.p16, rho.hi);
   c = __builtin_amdgcn_cosf(fr);
   sn = __builtin_amdgcn_sinf(fr);
 }
@@ -367,7 +383,7 @@ __device__ __forceinline__ void epi_put(unsigned char* lds, int lane, int i, int
 // What the epilogue needs to know of this lane's rows, requested at the start of the kernel.
 template <int TM>
 struct EpiRows {
-  RowPos pos[TM];
+  int32_t pos[TM];
   bool zero[TM];                       // an index outside x produces a zero row
 };
 template <int TM, int EPI>
@@ -377,13 +393,13 @@ __device__ __forceinline__ void load_epi_rows(const QkvArgs& a, int64_t m0, int 
     const int64_t m = min(m0 + 32 * i + (lane & 31), a.M - 1);
     const int64_t idx = a.gather ? (int64_t)a.gather[m] : 0;
     rows.zero[i] = idx < 0 || idx >= a.x_rows;
-    if (is_rope(EPI)) rows.pos[i] = row_pos(a.pos[m]);
+    if (is_rope(EPI)) rows.pos[i] = a.pos[m];
   }
 }
 
 // Rotation of the 128 columns held by a wave; the pair of a column is in the same lane.  JP: 32-column blocks of half
 // a head (half-split pairs), or 0: interleaved pairs.
-template <int TM, int JP>
+template <int TM, int JP, bool FAR>
 __device__ __forceinline__ void epi_rotate(floatx16 (&acc)[TM][4], const float2* sRho, unsigned char* lds, int lane, int D,
                                            const EpiRows<TM>& rows) {
   const int hf = lane >> 5;
@@ -393,16 +409,16 @@ __device__ __forceinline__ void epi_rotate(floatx16 (&acc)[TM][4], const float2*
       const int j = JP == 2 ? jj : 2 * jj;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        float2 rho[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) rho[c] = sRho[32 * (j % JP) + 8 * q + 4 * hf + c];
+        if constexpr (FAR) __builtin_amdgcn_sched_barrier(0);
+        const float2* t = sRho + 32 * (j % JP) + 8 * q + 4 * hf;
+        const Rho<FAR> rho[4] = {t, t + 1, t + 2, t + 3};
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
           float4v o0, o1;
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
             float wx, wy;
-            rotary_factor(rows.pos[i], rho[c], wx, wy);
+            rotary_factor<FAR>(rows.pos[i], rho[c], wx, wy);
             const float f0 = acc[i][j][4 * q + c], f1 = acc[i][j + JP][4 * q + c];
             o0[c] = f0 * wx - f1 * wy;
             o1[c] = f1 * wx + f0 * wy;
@@ -418,12 +434,13 @@ __device__ __forceinline__ void epi_rotate(floatx16 (&acc)[TM][4], const float2*
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int p0 = (((32 * j) & (D - 1)) >> 1) + 4 * q + 2 * hf;
-        const float2 rho0 = sRho[p0], rho1 = sRho[p0 + 1];
+        if constexpr (FAR) __builtin_amdgcn_sched_barrier(0);
+        const Rho<FAR> rho0(sRho + p0), rho1(sRho + p0 + 1);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
           float wx, wy, vx, vy;
-          rotary_factor(rows.pos[i], rho0, wx, wy);
-          rotary_factor(rows.pos[i], rho1, vx, vy);
+          rotary_factor<FAR>(rows.pos[i], rho0, wx, wy);
+          rotary_factor<FAR>(rows.pos[i], rho1, vx, vy);
           const float f0 = acc[i][j][4 * q], f1 = acc[i][j][4 * q + 1], f2 = acc[i][j][4 * q + 2], f3 = acc[i][j][4 * q + 3];
           epi_put(lds, lane, i, j, q, rows.zero[i], float4v{f0 * wx - f1 * wy, f1 * wx + f0 * wy, f2 * vx - f3 * vy, f3 * vx + f2 * vy});
         }
@@ -490,7 +507,11 @@ __device__ __forceinline__ void wave_epilogue(const QkvArgs& a, const OutTile& o
   if constexpr (is_rope(EPI)) {
     if (ot.rotate) {
       constexpr int JP = EPI == kRopeHalf128 ? 2 : EPI == kRopeHalf64 ? 1 : 0;
-      epi_rotate<TM, JP>(acc, sRho, lds, lane, a.D, rows);
+      bool far = false;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) far |= is_far(rows.pos[i]);
+      if (__builtin_expect(__any(far), 0)) epi_rotate<TM, JP, true>(acc, sRho, lds, lane, a.D, rows);
+      else epi_rotate<TM, JP, false>(acc, sRho, lds, lane, a.D, rows);
       rotated = true;
     }
   }
@@ -736,7 +757,7 @@ template <int EPI>
 __global__ __launch_bounds__(256) void qkv_split_reduce(QkvArgs a, int n_groups) {
   __shared__ __align__(16) float4 sSum[1024];
   __shared__ __align__(16) unsigned char sOut[8192];
-  __shared__ float2 sRho[64];
+  __shared__ float2 sRho[2 * kRho16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int grp = blockIdx.x;                                    // 32-row group
   const int n_tile = blockIdx.y;

@@ -112,8 +112,8 @@ def test_swiglu_over_the_float_range():
     assert float(got[0]) == float("inf") and bool(got[1:3].isnan().all()) and bool((got[3:] == 0).all())
 
 
-def _rotate(y, pos, base, style):
-    """Rotary embedding of y [M, heads, d] in float64 angles."""
+def _rotate64(y, pos, base, style):
+    """Rotary embedding of y [M, heads, d] in float64."""
     d = y.shape[-1]
     theta = base ** (-2.0 * torch.arange(d // 2, device=y.device, dtype=torch.float64) / d)
     ang = pos.double()[:, None] * theta
@@ -121,7 +121,11 @@ def _rotate(y, pos, base, style):
     a, b = (y[..., :d // 2], y[..., d // 2:]) if style == 0 else (y[..., 0::2], y[..., 1::2])
     a, b = a.double(), b.double()
     ra, rb = a * c - b * s, b * c + a * s
-    return torch.cat([ra, rb], -1).float() if style == 0 else torch.stack([ra, rb], -1).flatten(-2).float()
+    return torch.cat([ra, rb], -1) if style == 0 else torch.stack([ra, rb], -1).flatten(-2)
+
+
+def _rotate(y, pos, base, style):
+    return _rotate64(y, pos, base, style).float()
 
 
 @pytest.mark.parametrize("M,dm,H,Hkv,D,style", [
@@ -158,6 +162,33 @@ def test_projection_tile_choices(M, dm, H, Hkv, D, style):
         ref = torch.full_like(fused, 7.0)
         ref[dst[keep].long()] = new[keep]
         assert torch.equal(fused, ref)
+
+
+@pytest.mark.parametrize("M,K,D,style", [(4700, 2048, 128, 0), (4700, 2048, 64, 0), (4700, 2048, 128, 1),      # 256 x 256 tiles
+                                         (1500, 2048, 128, 0), (60, 2048, 128, 0), (60, 2048, 64, 1)])      # smaller; split
+def test_rotation_at_positions_from_2_24_on(M, K, D, style):
+    """Pairs (1, 0) become (cos, sin) of the angle: where one of them is small its bf16 rounding does not hide the angle's
+    error.  Bound: one rounding to bf16 plus 3e-7 of a turn."""
+    say(f"far positions M={M} D={D} style={style}")
+    H, Hkv = 4096 // D, 1024 // D
+    sh = inputs.LayerShape(K, H, Hkv, D, 500000.0, "bf16", style)
+    x = torch.zeros((M, K), dtype=BF, device=DEV)
+    x[:, 5] = 1
+    w = torch.zeros((H + 2 * Hkv, D, K), dtype=BF, device=DEV)
+    (w[:, :D // 2] if style == 0 else w[:, 0::2])[..., 5] = 1
+    pos = torch.randint(1 << 24, (1 << 31) - 1, (M,), generator=gen(53), device=DEV)
+    pos[::3] *= -1
+    pos[::5] %= 40000                                        # near ones in the same waves
+    pos[:4] = torch.tensor([1 << 24, -(1 << 24), (1 << 31) - 1, -(1 << 31)], device=DEV)
+    q, k, v = (torch.empty((M, h, D), dtype=BF, device=DEV) for h in (H, Hkv, Hkv))
+    qb.qcf_recompute_qkv(qb.make_desc(sh), x, M, None, M, w, pos.int(), q, k, v)
+    torch.cuda.synchronize()
+    y = torch.zeros((M, 1, D), dtype=torch.float64, device=DEV)
+    (y[..., :D // 2] if style == 0 else y[..., 0::2])[:] = 1
+    ref = _rotate64(y, pos, 500000.0, style)
+    for got in (q, k):
+        excess = float(((got.double() - ref).abs() - 2.0 ** -8 * ref.abs()).max())
+        assert excess <= 2 * np.pi * 3e-7
 
 
 @pytest.mark.parametrize("M,dm,H,Hkv", [
