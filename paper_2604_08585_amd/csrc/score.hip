@@ -20,8 +20,8 @@
 // No floating-point atomics anywhere, so scores (and the indices selected from them) are
 // bit-stable from run to run.
 //
-// Heads of 64 run the same kernels with half the k-steps (40 probe rows x 32 heads over 4096 tokens: 391 us with the
-// generic kernels, about 17 us here).
+// Heads of 64 run the two MFMA passes with half the k-steps (40 probe rows x 32 heads over 4096 tokens: 391 us with the
+// generic kernels, 15 us here), never the single kernel (see use_fused).
 //
 // Generic path (f32, or other head dims): one workgroup per (probe row, head) materialises its
 // softmax row in the workspace, then a column mean.
@@ -523,8 +523,9 @@ __device__ __forceinline__ float half_wave_sum(float x) {
   return __uint_as_float(r.x) + __uint_as_float(r.y);     // rows (0, 1) and (2, 3) of 16 lanes each
 }
 
-template <int D, bool LIMIT>
+template <bool LIMIT>
 __global__ __launch_bounds__(kFusedThreads) void score_fused(FusedArgs fa) {
+  constexpr int D = 128;
   const ScoreArgs& a = fa.s;
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* sK = smem + kQBytes<D>;
@@ -782,8 +783,8 @@ MfmaWs mfma_ws(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t 
 
 template <int D> constexpr size_t kPass1Lds = kQBytes<D> + kKBytes<D> + (size_t)kTokWaves * kRowBlock * sizeof(float2);
 template <int D> constexpr size_t kPass2Lds = kQBytes<D> + kKBytes<D> + (size_t)kRowBlock * 8 + (size_t)kRowGroups * kTokPerWg * sizeof(float);
-template <int D> constexpr size_t kFusedLds = kQBytes<D> + kKBytes<D>;
-static_assert((size_t)kFusedWaves * kRowBlock * 8 + (size_t)kRowBlock * 4 + (size_t)kTokPerWg * 4 <= kKBytes<64>,
+constexpr size_t kFusedLds = kQBytes<128> + kKBytes<128>;
+static_assert((size_t)kFusedWaves * kRowBlock * 8 + (size_t)kRowBlock * 4 + (size_t)kTokPerWg * 4 <= kKBytes<128>,
               "the single-kernel path's tables fit in the key tile's LDS");
 
 bool use_mfma(const qcf_layer_desc& L) { return L.dtype == QCF_DTYPE_BF16 && (L.head_dim == 128 || L.head_dim == 64); }
@@ -792,9 +793,11 @@ size_t generic_ws(const qcf_layer_desc& L, int64_t total_probe, int64_t total_ct
 }
 
 // The single-kernel path needs every workgroup of the launch resident at once (one per compute unit) and all
-// probe rows of a KV group in one staged block.  The host only knows totals, so the test is on those.
+// probe rows of a KV group in one staged block.  The host only knows totals, so the test is on those.  Heads of 64 never
+// take it: their calls may overlap on any number of streams, which the counter sets of this path (kSyncSlots) and its wait
+// for workgroups that another launch may keep off the chip do not allow.
 bool use_fused(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx) {
-  if (!use_mfma(L) || total_probe <= 0) return false;
+  if (!use_mfma(L) || L.head_dim != 128 || total_probe <= 0) return false;
   const int64_t G = L.n_q_heads / L.n_kv_heads;
   const int64_t tiles = n_tiles_upper(B, total_ctx);
   return total_probe * G <= kRowBlock && tiles * L.n_kv_heads <= compute_unit_count() &&
@@ -816,11 +819,11 @@ FusedWs fused_ws(const qcf_layer_desc& L, int32_t B, int64_t total_ctx) {
   return w;
 }
 
-template <int D, bool LIMIT>
+template <bool LIMIT>
 qcf_status run_fused(const FusedArgs& fa, hipStream_t st) {
   static std::atomic<uint64_t> lds_ok;
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_fused<D, LIMIT>), kFusedLds<D>, lds_ok));
-  score_fused<D, LIMIT><<<dim3((unsigned)(fa.n_wg_tiles * fa.s.Hkv)), dim3(kFusedThreads), kFusedLds<D>, st>>>(fa);
+  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_fused<LIMIT>), kFusedLds, lds_ok));
+  score_fused<LIMIT><<<dim3((unsigned)(fa.n_wg_tiles * fa.s.Hkv)), dim3(kFusedThreads), kFusedLds, st>>>(fa);
   return check_launch("score (single kernel)");
 }
 template <int D, bool LIMIT>
@@ -922,8 +925,7 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
     QCF_TRY(sync_counters(&counters));
     static std::atomic<uint32_t> next_slot{0};
     fa.sync = counters + (size_t)(next_slot.fetch_add(1, std::memory_order_relaxed) % kSyncSlots) * kSyncWords;
-    if (D == 128) return probe_limit ? run_fused<128, true>(fa, st) : run_fused<128, false>(fa, st);
-    return probe_limit ? run_fused<64, true>(fa, st) : run_fused<64, false>(fa, st);
+    return probe_limit ? run_fused<true>(fa, st) : run_fused<false>(fa, st);
   }
   const MfmaWs w = mfma_ws(L, B, total_probe, total_ctx);
   a.part = reinterpret_cast<float2*>(static_cast<char*>(ws) + w.part);

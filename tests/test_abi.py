@@ -148,3 +148,12 @@ def test_linear_swiglu_arguments_and_workspace():
         need = lib.qcf_linear_swiglu_workspace_bytes(C.byref(desc), 4, K, F)
         assert need >= 4 * 2 * F * size + lib.qcf_linear_workspace_bytes(C.byref(desc), 4, K, 2 * F)
         assert lib.qcf_linear_swiglu(C.byref(desc), fake, 4, K, fake, F, fake, fake, 4 * 2 * F * size - 1, None) == 3
+
+
+def test_scores_of_64_wide_heads_share_no_state_between_calls():
+    """The single scoring kernel hands data from workgroup to workgroup through counters that calls on other streams may
+    share; heads of 64 take the two passes, whose partials (in the caller's workspace) grow with the probe rows."""
+    for H, Hkv, T in [(32, 8, 4096), (8, 2, 300), (16, 16, 64)]:
+        for hd, grows in [(64, True), (128, False)]:
+            d = _desc(d_model=2048, n_q_heads=H, n_kv_heads=Hkv, head_dim=hd, dtype="bf16")
+            assert (qb.qcf_score_workspace_bytes(d, 1, 80, T) > qb.qcf_score_workspace_bytes(d, 1, 8, T)) == grows

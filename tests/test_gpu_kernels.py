@@ -290,9 +290,9 @@ def test_attention_of_64_wide_heads_infinite_values(T, n):
 
 
 @pytest.mark.parametrize("H,Hkv,ctx,probes,limit", [
-    (32, 8, [4099], [40], False), (8, 2, [300, 1, 64, 1025, 256], [5, 3, 0, 17, 30], False),   # one kernel
+    (32, 8, [4099], [40], False), (8, 2, [300, 1, 64, 1025, 256], [5, 3, 0, 17, 30], False),
     (8, 4, [700], [33], True),
-    (32, 8, [9000], [40], False), (8, 2, [300, 1, 2000], [90, 3, 100], True)])                  # two passes
+    (32, 8, [9000], [40], False), (8, 2, [300, 1, 2000], [90, 3, 100], True)])                  # several blocks of rows
 def test_scores_of_64_wide_heads(H, Hkv, ctx, probes, limit):
     say(f"scores d=64 H={H} Hkv={Hkv} ctx={ctx} probes={probes}")
     sh = inputs.LayerShape(2048, H, Hkv, 64, 10000.0, "bf16")
@@ -315,6 +315,32 @@ def test_scores_of_64_wide_heads(H, Hkv, ctx, probes, limit):
         # 32-bit logits of magnitude up to 60, exponentials and sums
         assert bool(((score[c0:c0 + t].double() - ref).abs() <= 3e-5 * ref + 1e-12).all())
         r0, c0 = r0 + r, c0 + t
+
+
+def test_scores_of_64_wide_heads_on_many_streams():
+    """Calls that overlap on more streams than the library has counter sets: each gets what it gets alone, bit for bit."""
+    say("scores d=64 on 12 streams")
+    sh = inputs.LayerShape(2048, 32, 8, 64, 10000.0, "bf16")
+    g, desc, T, R, n = gen(54), qb.make_desc(sh), 4099, 40, 12
+    q = [torch.randn((R, 32, 64), generator=g, device=DEV, dtype=BF) for _ in range(n)]
+    k = [torch.randn((T, 8, 64), generator=g, device=DEV, dtype=BF) for _ in range(n)]
+    po, co = i64([0, R]), i64([0, T])
+    need = qb.qcf_score_workspace_bytes(desc, 1, R, T)
+    ws = [torch.empty(need, dtype=torch.uint8, device=DEV) for _ in range(n)]
+    alone, many = (torch.empty((n, T + 1), device=DEV)[:, :T] for _ in range(2))       # (rows 16-byte aligned)
+    assert alone.stride(0) % 4 == 0
+    for i in range(n):
+        qb.qcf_score(desc, 1, q[i], po, R, k[i], co, T, None, alone[i], ws[i])
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(n)]
+    for _ in range(4):
+        many.fill_(7.0)
+        torch.cuda.synchronize()
+        for i in range(n):
+            with torch.cuda.stream(streams[i]):
+                qb.qcf_score(desc, 1, q[i], po, R, k[i], co, T, None, many[i], ws[i])
+        torch.cuda.synchronize()
+        assert torch.equal(alone, many)
 
 
 @pytest.mark.parametrize("dtype,M,K,N", [("f32", 1, 8, 8), ("f32", 77, 256, 512), ("f32", 17, 264, 40), ("f32", 1100, 72, 1032),
