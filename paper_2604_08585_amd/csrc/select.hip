@@ -47,25 +47,35 @@ __device__ __forceinline__ void select_request(SelectLds& lds, const float* __re
                                                int64_t o0, int base_pos, int32_t* __restrict__ sel_idx,
                                                int32_t* __restrict__ sel_row, int32_t* __restrict__ sel_pos) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int j0 = (int)min((int64_t)T, (int64_t)tid * seg), j1 = min(T, j0 + seg);
+  const int j0 = min(T, tid * seg), j1 = min(T, j0 + seg);      // (T is at most 2^30)
   const int cnt = j1 - j0;
 
   uint32_t keys[SEG > 0 ? SEG : 1];
   if (SEG > 0) {
     // segments start at multiples of four: with an aligned request every whole quad is one load
     if (SEG % 4 == 0 && (reinterpret_cast<uintptr_t>(s) & 15u) == 0) {
+      if (cnt == SEG) {
 #pragma unroll
-      for (int i = 0; i < SEG; i += 4) {
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (i + 3 < cnt) v = *reinterpret_cast<const float4*>(s + j0 + i);
-        else {
-          if (i < cnt) v.x = s[j0 + i];
-          if (i + 1 < cnt) v.y = s[j0 + i + 1];
-          if (i + 2 < cnt) v.z = s[j0 + i + 2];
+        for (int i = 0; i < SEG; i += 4) {
+          const float4 v = *reinterpret_cast<const float4*>(s + j0 + i);
+          const float q[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int c = 0; c < 4 && i + c < SEG; ++c) keys[i + c] = order_key(q[c]);
         }
-        const float q[4] = {v.x, v.y, v.z, v.w};
+      } else {
 #pragma unroll
-        for (int c = 0; c < 4 && i + c < SEG; ++c) keys[i + c] = order_key(q[c]);
+        for (int i = 0; i < SEG; i += 4) {
+          float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (i + 3 < cnt) v = *reinterpret_cast<const float4*>(s + j0 + i);
+          else {
+            if (i < cnt) v.x = s[j0 + i];
+            if (i + 1 < cnt) v.y = s[j0 + i + 1];
+            if (i + 2 < cnt) v.z = s[j0 + i + 2];
+          }
+          const float q[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int c = 0; c < 4 && i + c < SEG; ++c) keys[i + c] = order_key(q[c]);
+        }
       }
     } else {
 #pragma unroll
@@ -183,9 +193,10 @@ __device__ __forceinline__ void select_request(SelectLds& lds, const float* __re
 #undef QCF_FOR_KEYS
 }
 
-// Keys per thread are chosen by the length of each request (the host knows only the total): a batch of requests whose
-// total exceeds what registers hold no longer re-reads every key in every pass (sixteen requests of 2K-16K tokens: 56
-// -> 16 us), and short requests in a long total carry no registers for keys they do not have.
+// Keys per thread follow the length of each request: a batch of requests whose total exceeds what registers hold does not
+// re-read every key in every pass (sixteen requests of 2K-16K tokens: 56 -> 16 us).  MAX: the most keys per thread that
+// registers are kept for (they are allocated for the kernel as a whole); 0: and any longer request.
+template <int MAX>
 __global__ __launch_bounds__(kThreads) void select_kernel(
     const float* __restrict__ score, const int64_t* __restrict__ ctx_off, int64_t total_ctx,
     const int64_t* __restrict__ sel_off, int64_t total_sel, const int32_t* __restrict__ ctx_pos0,
@@ -206,12 +217,16 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
   int seg = (T + kThreads - 1) / kThreads;
   if (seg > 1) seg = (seg + 3) & ~3;
 #define QCF_SELECT(SEG) select_request<SEG>(lds, s, c0, T, N, seg, o0, base_pos, sel_idx, sel_row, sel_pos)
-  if (seg <= 1) QCF_SELECT(1);
-  else if (seg <= 4) QCF_SELECT(4);
-  else if (seg <= 8) QCF_SELECT(8);
-  else if (seg <= 16) QCF_SELECT(16);
-  else if (seg <= 32) QCF_SELECT(32);
-  else QCF_SELECT(0);
+  if constexpr (MAX > 0 && MAX <= 8) {
+    if (seg <= MAX) QCF_SELECT(MAX);     // (always so: a request is never longer than the total)
+  } else {
+    if (seg <= 1) QCF_SELECT(1);
+    else if (seg <= 4) QCF_SELECT(4);
+    else if (seg <= 8) QCF_SELECT(8);
+    else if (seg <= 16) QCF_SELECT(16);
+    else if (seg <= 32) QCF_SELECT(32);
+    else if constexpr (MAX == 0) QCF_SELECT(0);
+  }
 #undef QCF_SELECT
 }
 
@@ -223,7 +238,16 @@ qcf_status launch_select(int32_t B, const float* score, const int64_t* ctx_off, 
                          const int64_t* sel_off, int64_t total_sel, const int32_t* ctx_pos0,
                          int32_t* sel_idx, int32_t* sel_row, int32_t* sel_pos, void*, hipStream_t st) {
   const dim3 grid((unsigned)B), block(kThreads);
-  select_kernel<<<grid, block, 0, st>>>(score, ctx_off, total_ctx, sel_off, total_sel, ctx_pos0, sel_idx, sel_row, sel_pos);
+#define QCF_LAUNCH(MAX) \
+  select_kernel<MAX><<<grid, block, 0, st>>>(score, ctx_off, total_ctx, sel_off, total_sel, ctx_pos0, sel_idx, sel_row, sel_pos)
+  // A request is never longer than total_ctx.  Up to eight keys per thread the instance of the total serves every request
+  // (8192 tokens: 11.1 us, with the choice by length inside one kernel 11.5).
+  if (total_ctx <= kThreads) QCF_LAUNCH(1);
+  else if (total_ctx <= 4 * kThreads) QCF_LAUNCH(4);
+  else if (total_ctx <= 8 * kThreads) QCF_LAUNCH(8);
+  else if (total_ctx <= 32 * kThreads) QCF_LAUNCH(32);
+  else QCF_LAUNCH(0);
+#undef QCF_LAUNCH
   return check_launch("select");
 }
 

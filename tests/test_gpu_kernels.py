@@ -380,7 +380,7 @@ def test_f32_attention_general(D, T, n):
     assert float((lse.double() - rl).abs().max()) < 1e-5
 
 
-@pytest.mark.parametrize("lens", [[1, 1024, 1025, 3], [4096, 4097, 8192, 8193, 16384], [16385, 7, 32768], [32769, 1023, 40001]])
+@pytest.mark.parametrize("lens", [[300], [1, 1021], [4094], [5000, 3190], [1, 1024, 1025, 3], [4096, 4097, 8192, 8193, 16384], [16385, 7, 32768], [32769, 1023, 40001]])
 def test_select_keys_per_thread(lens):
     """Every number of keys per thread, requests that start at any alignment, ties: exactly the N largest, ties to the
     lower index, ascending."""
