@@ -252,16 +252,10 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const T* x, const T* __res
   for (int v = tid + kNormVecs * 256; v < n_vec; v += 256) emit(v, *reinterpret_cast<const u32x4*>(xr + v * VEC));
 }
 
-// silu(g) * u.  The quotient is one reciprocal with a Newton step (a compiled division is ten instructions, which
-// weighs in the epilogue of a product); where the step has no finite remainder (g or exp(-g) infinite) the plain
-// product stands: 0 for g below -89, infinity and NaN as a division gives them.
-__device__ __forceinline__ float silu_mul(float g, float u) {
-  const float d = 1.f + __expf(-g);
-  const float r = __builtin_amdgcn_rcpf(d);
-  const float q = g * r;
-  const float e = __builtin_fmaf(-q, d, g);
-  return (e == e ? __builtin_fmaf(e, r, q) : q) * u;
-}
+// silu(g) * u.  A true division: one reciprocal with a Newton step in its place made the gate / up product 1 % faster
+// (1229 rows, K 4096, F 14336: 241.7 us, 244.4 with the division) but flushed quotients whose divisor passes 2^126, i.e.
+// g below -87.3, where they are still normal numbers.
+__device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.f + __expf(-g)) * u; }
 
 // out[m, f] = silu(gate_up[m, f]) * gate_up[m, F + f]; one 16-byte output vector per thread
 template <typename T>

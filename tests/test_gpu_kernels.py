@@ -94,8 +94,8 @@ def test_linear_swiglu(M, K, F):
 
 def test_swiglu_over_the_float_range():
     """Against float64: the argument of the exponential carries a rounding (relative error |g| 2^-24 of the exponential),
-    the other operations a few of 2^-24; results below 2^-110 may be flushed.  Infinities and NaN as g / (1 + exp(-g))
-    gives them."""
+    the other operations a few of 2^-24; where the exponential overflows (g < -88.72, a result below 2^-121) it is 0.
+    Infinities and NaN as g / (1 + exp(-g)) gives them."""
     g = torch.cat([torch.linspace(-95, 95, 4001), torch.tensor([0.0, -0.0, 1e-30, -1e-30, 3e38, -3e38, -87.4, -88.5, -89.0])])
     g = torch.cat([g, torch.zeros(-g.numel() % 8)])
     F = g.numel()
@@ -104,7 +104,7 @@ def test_swiglu_over_the_float_range():
     qb.qcf_swiglu(desc, torch.cat([g, torch.full((F,), 1.0)]).to(DEV), 1, F, out)
     ref = g.double() / (1.0 + torch.exp(-g.double()))
     err = (out[0].cpu().double() - ref).abs()
-    assert bool((err <= (6.0 + 2.0 * g.abs().clamp(max=100.0).double()) * 2.0 ** -24 * ref.abs() + 2.0 ** -110).all())
+    assert bool((err <= (6.0 + 2.0 * g.abs().clamp(max=100.0).double()) * 2.0 ** -24 * ref.abs() + 2.0 ** -121).all())
     special = torch.tensor([float("inf"), -float("inf"), float("nan"), 0.0, 0.0, 0.0, 0.0, 0.0])
     out = torch.empty((1, 8), dtype=torch.float32, device=DEV)
     qb.qcf_swiglu(desc, torch.cat([special, torch.ones(8)]).to(DEV), 1, 8, out)
