@@ -13,12 +13,13 @@
 // that run as separate workgroups; each writes a normalised partial output and its log-sum-exp,
 // and a second kernel merges them (the usual softmax merge, exact up to rounding).
 //
-// Heads of 64: the probabilities enter the second product as two bf16 terms (high + rest, 16 significant bits) and
-// the partial outputs of split row blocks are fp32, so nothing between the operands and the stored result is rounded
-// to bf16.  A row whose output comes out NaN (an infinite value times a zero probability, also one of a token the
-// row does not see) is computed again, token by token over its visible tokens.
-// Bound by the softmax arithmetic between the two products.  615 rows x 32 heads over 4096 tokens: 1704 us with the
-// generic kernel, about 25 us here; the whole layer 2064 -> 92 us.
+// Heads of 64: the probabilities enter the second product as three bf16 terms that add up to the float, and the partial
+// outputs of split row blocks are fp32, so nothing between the operands and the stored result is rounded to bf16 (with two
+// terms 3.1 times as many results were not the bf16 nearest to the exact one as with float32 products: 3893 to 1237 of
+// 4.4 million; with three 723).  Rows that come out infinite or NaN are computed again in a second sweep over the same
+// tiles (see there).
+// Bound by the softmax arithmetic between the two products and by the splitting into terms.  615 rows x 32 heads over 4096
+// tokens: 1580 us with the generic kernel, 48.4 us here (41.7 with two terms); the whole layer 96.6 us (2074 before).
 //
 // Generic path (f32, or other shapes): one workgroup per (row, head), online softmax over
 // 256-token tiles.  Bound by the latency of its key and value loads (77 rows x 4 heads over 512 tokens in f32: 39 us with
@@ -162,8 +163,8 @@ struct AttnTile {
   static constexpr int NLOAD = kBKV / (4 * LROWS);      // instructions per wave and tile
   static constexpr int KS = D / 16, DT = D / 32;        // k-steps of the logits, 32-element slices of the output
   static constexpr int WGS = 2;                         // resident workgroups per compute unit (registers)
-  static constexpr bool SPLIT_P = D == 64;              // probabilities as two bf16 terms, fp32 partial outputs,
-                                                        // NaN rows computed again
+  static constexpr bool SPLIT_P = D == 64;              // probabilities as three bf16 terms, fp32 partial outputs,
+                                                        // rows that are not finite computed again
   typedef typename std::conditional<SPLIT_P, float, bf16_t>::type part_t;
   static constexpr float K2 = kLog2e * (D == 128 ? 0.08838834764831845f : 0.125f);      // log2(e) / sqrt(D)
 };
@@ -182,22 +183,38 @@ __device__ __forceinline__ u32x4 lds_read16(uint32_t lds_addr) {
   return *(const u32x4 __attribute__((address_space(3)))*)(uintptr_t)lds_addr;
 }
 
-// One output row computed by a whole wave (d = 64: lane = element), in fp32, over the visible tokens only.
-__device__ __forceinline__ void attn_row_by_token(const bf16_t* q, const bf16_t* k, const bf16_t* v, int64_t kv_stride, int vis,
-                                  bf16_t* o, int lane) {
-  const float qe = bf16_to_f32(q[lane]) * 0.125f;
-  float m = -INFINITY, l = 0.f, acc = 0.f;
-  for (int j = 0; j < vis; ++j) {
-    float s = qe * bf16_to_f32(k[j * kv_stride + lane]);
-    for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d, 64);
-    const float mn = fmaxf(m, s);
-    const float m_use = (mn == -INFINITY) ? 0.f : mn;
-    const float alpha = expf(m - m_use), p = expf(s - m_use);
-    l = l * alpha + p;
-    acc = acc * alpha + p * bf16_to_f32(v[j * kv_stride + lane]);
-    m = mn;
+// Second and third bf16 term of two probabilities whose first terms are `pk`: a float has 24 significant bits, each term
+// takes eight and the differences are exact, so the three terms add up to the float.
+__device__ __forceinline__ void split_rest(float p0, float p1, uint32_t pk, uint32_t& second, uint32_t& third) {
+  const float r0 = p0 - __uint_as_float(pk << 16), r1 = p1 - __uint_as_float(pk & 0xffff0000u);
+  second = cvt_pk_bf16(r0, r1);
+  third = cvt_pk_bf16(r0 - __uint_as_float(second << 16), r1 - __uint_as_float(second & 0xffff0000u));
+}
+
+__device__ __forceinline__ bool all_finite(const u32x4& v) {       // eight bf16 values: no exponent field is all ones
+  uint32_t x = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) x |= (v[w] & 0x7f807f80u) + 0x00800080u;
+  return (x & 0x80008000u) == 0u;
+}
+// Classes of eight bf16 values (as four pairs): `code` gets 1 for +infinity, 128 for -infinity and 16384 for NaN, as bf16,
+// and 0 for finite ones (sums over the 64 tokens of a tile keep the classes apart); `fin` the finite values, 0 for the
+// others.
+__device__ __forceinline__ void split_classes(const u32x4& v, u32x4& fin, u32x4& code) {
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    uint32_t f = 0, c = 0;
+#pragma unroll
+    for (int h = 0; h < 32; h += 16) {
+      const uint32_t x = (v[w] >> h) & 0xffffu;
+      const bool finite = (x & 0x7f80u) != 0x7f80u;
+      const uint32_t cls = (x & 0x7fu) ? 0x4680u : (x & 0x8000u) ? 0x4300u : 0x3f80u;
+      f |= (finite ? x : 0u) << h;
+      c |= (finite ? 0u : cls) << h;
+    }
+    fin[w] = f;
+    code[w] = c;
   }
-  o[lane] = f32_to_bf16(vis > 0 ? acc / l : 0.f);
 }
 
 // Tile layouts in LDS (d = 128: rows of 256 bytes = 16 chunks of 16 bytes, no padding):
@@ -394,7 +411,7 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
     // One MFMA of the next tile's logits, then the exponentials of 32 / (2 KS) elements.  P^T fragments: step
     // s = v / 8 uses registers 8*s .. 8*s+7 (tokens 16*s + 8*(e/4) + 4*hf + e%4).
     constexpr int NM = 2 * C::KS, PER = 32 / NM;
-    u32x4 pf[4], pr[4];
+    u32x4 pf[4], pr[4], ps[4];
     shortx4 vlo[4], vhi[4];            // value fragments, up to three ahead
     auto v_read = [&](int idx) {
       const int s2 = idx / C::DT, dt2 = idx % C::DT;
@@ -419,8 +436,12 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
         sum += p1;
         const uint32_t pk = cvt_pk_bf16(p0, p1);
         pf[v >> 3][(v & 7) >> 1] = pk;
-        // (the difference to the rounded value is exact)
-        if (C::SPLIT_P) pr[v >> 3][(v & 7) >> 1] = cvt_pk_bf16(p0 - __uint_as_float(pk << 16), p1 - __uint_as_float(pk & 0xffff0000u));
+        if constexpr (C::SPLIT_P) {
+          uint32_t second, third;
+          split_rest(p0, p1, pk, second, third);
+          pr[v >> 3][(v & 7) >> 1] = second;
+          ps[v >> 3][(v & 7) >> 1] = third;
+        }
       }
     }
     l_run = l_run * alpha + sum;
@@ -432,7 +453,10 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
       const shortx8 both = __builtin_shufflevector(vlo[idx & 3], vhi[idx & 3], 0, 1, 2, 3, 4, 5, 6, 7);
       const bf16x8 vf = __builtin_bit_cast(bf16x8, both);
       oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8, pf[s]), oacc[dt], 0, 0, 0);
-      if (C::SPLIT_P) oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8, pr[s]), oacc[dt], 0, 0, 0);
+      if (C::SPLIT_P) {
+        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8, pr[s]), oacc[dt], 0, 0, 0);
+        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8, ps[s]), oacc[dt], 0, 0, 0);
+      }
     }
   };
 
@@ -460,66 +484,157 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
   // epilogue: output register v of tile dt is element 32*dt + 16*hf + v of this lane's row
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  if (split) {                        // partial result of one key segment; merged by attn_merge_kernel
-    const int64_t slot = ((int64_t)blk * a.Hkv + g) * a.n_seg_max + seg;
-    typename C::part_t* op = static_cast<typename C::part_t*>(a.part_o) + (slot * kRowsPerWg + r) * D + 16 * hf;
+  const int64_t part_row = (((int64_t)blk * a.Hkv + g) * a.n_seg_max + seg) * kRowsPerWg + r;    // of a split block
+  typename C::part_t* part = static_cast<typename C::part_t*>(a.part_o) + part_row * D + 16 * hf;
+  bf16_t* orow = static_cast<bf16_t*>(a.o) + (srow * a.H + head) * D + 16 * hf;
+  // x(dt, v): value of this lane's element 32 dt + 16 hf + v; lse in log2 units
+  auto store_split = [&](auto x, float lse2) {         // partial result of one key segment; merged by attn_merge_kernel
 #pragma unroll
     for (int dt = 0; dt < C::DT; ++dt) {
       if constexpr (C::SPLIT_P) {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<float4*>(op + 32 * dt + 4 * q) =
-              make_float4(oacc[dt][4 * q] * inv, oacc[dt][4 * q + 1] * inv, oacc[dt][4 * q + 2] * inv, oacc[dt][4 * q + 3] * inv);
+          *reinterpret_cast<float4*>(part + 32 * dt + 4 * q) = make_float4(x(dt, 4 * q), x(dt, 4 * q + 1), x(dt, 4 * q + 2), x(dt, 4 * q + 3));
       } else {
 #pragma unroll
-        for (int h8 = 0; h8 < 2; ++h8) {
-          const u32x4 pk = mk4(cvt_pk_bf16(oacc[dt][8 * h8 + 0] * inv, oacc[dt][8 * h8 + 1] * inv),
-                               cvt_pk_bf16(oacc[dt][8 * h8 + 2] * inv, oacc[dt][8 * h8 + 3] * inv),
-                               cvt_pk_bf16(oacc[dt][8 * h8 + 4] * inv, oacc[dt][8 * h8 + 5] * inv),
-                               cvt_pk_bf16(oacc[dt][8 * h8 + 6] * inv, oacc[dt][8 * h8 + 7] * inv));
-          *reinterpret_cast<u32x4*>(op + 32 * dt + 8 * h8) = pk;
-        }
+        for (int h8 = 0; h8 < 16; h8 += 8)
+          *reinterpret_cast<u32x4*>(part + 32 * dt + h8) = mk4(cvt_pk_bf16(x(dt, h8), x(dt, h8 + 1)), cvt_pk_bf16(x(dt, h8 + 2), x(dt, h8 + 3)),
+                                                               cvt_pk_bf16(x(dt, h8 + 4), x(dt, h8 + 5)), cvt_pk_bf16(x(dt, h8 + 6), x(dt, h8 + 7)));
       }
     }
-    if (hf == 0) a.part_lse[slot * kRowsPerWg + r] = l_tot > 0.f ? m_run + log2f(l_tot) : -INFINITY;
-    return;
-  }
-  bool store_row = row_ok;
-  if constexpr (C::SPLIT_P) {
-    bool nan = false;
+    if (hf == 0) a.part_lse[part_row] = lse2;
+  };
+  auto store_whole = [&](auto x, float lse2) {
 #pragma unroll
     for (int dt = 0; dt < C::DT; ++dt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) nan |= oacc[dt][v] != oacc[dt][v];
-    const uint64_t any = __ballot(nan && row_ok);
-    uint32_t bad = (uint32_t)any | (uint32_t)(any >> 32);
-    store_row = row_ok && !((bad >> l32) & 1u);
-    while (bad) {                     // (rare: lanes l and l + 32 hold row l of the wave)
-      const int l = __builtin_ctz(bad);
-      bad &= bad - 1u;
-      const int rr = wave * 32 + l;
-      const int64_t at = ((s0 + (int64_t)wg * BR + rr / a.G) * a.H + g * a.G + rr % a.G) * D;
-      attn_row_by_token(static_cast<const bf16_t*>(a.q) + at, kg, vg, (int64_t)a.Hkv * D, __shfl(vis, l, 64),
-                        static_cast<bf16_t*>(a.o) + at, lane);
-    }
-    if (row_ok && a.lse && hf == 0)
-      a.lse[srow * a.H + head] = l_tot > 0.f ? (m_run + log2f(l_tot)) * kLn2 : -INFINITY;
+      for (int h8 = 0; h8 < 16; h8 += 8)
+        *reinterpret_cast<u32x4*>(orow + 32 * dt + h8) = mk4(cvt_pk_bf16(x(dt, h8), x(dt, h8 + 1)), cvt_pk_bf16(x(dt, h8 + 2), x(dt, h8 + 3)),
+                                                             cvt_pk_bf16(x(dt, h8 + 4), x(dt, h8 + 5)), cvt_pk_bf16(x(dt, h8 + 6), x(dt, h8 + 7)));
+    if (a.lse && hf == 0) a.lse[srow * a.H + head] = lse2 * kLn2;
+  };
+  bool bad = false;                                    // this row is computed again below
+  if constexpr (C::SPLIT_P) {
+    const bool sees = vis > t_begin * kBKV;
+    bad = sees && !(l_tot > 0.f && l_tot < INFINITY);
+#pragma unroll
+    for (int dt = 0; dt < C::DT; ++dt)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) bad |= sees && !(fabsf(oacc[dt][v]) < INFINITY);
+    const uint64_t lanes = __ballot(bad);               // (lanes l and l + 32 hold one row)
+    bad = ((lanes >> l32) | (lanes >> (l32 + 32))) & 1u;
   }
-  if (store_row) {
-    bf16_t* op = static_cast<bf16_t*>(a.o) + (srow * a.H + head) * D + 16 * hf;
+  {
+    auto x = [&](int dt, int v) { return oacc[dt][v] * inv; };
+    const float lse2 = l_tot > 0.f ? m_run + log2f(l_tot) : -INFINITY;
+    if (split) {
+      if (!bad) store_split(x, lse2);
+    } else if (row_ok && !bad) {
+      store_whole(x, lse2);
+    }
+  }
+  if constexpr (C::SPLIT_P) {
+    if (!__syncthreads_or(bad)) return;
+    // Some row came out infinite or NaN: the tiles once more, with the finite values in the product and the classes of the
+    // others (of tokens that the row sees) beside it, against a reference point that follows the maximum at once.  So a
+    // value that a row does not see leaves no trace, and a visible infinity stays one.  Only the rows in question are
+    // stored.  Costs a few times the first sweep (615 rows x 32 heads over 4096 tokens, every value NaN: 132 us, one
+    // infinite value 81).
+    uint32_t cls[C::DT][16];                             // 1: +infinity seen, 2: -infinity, 4: NaN
 #pragma unroll
     for (int dt = 0; dt < C::DT; ++dt) {
+      oacc[dt] = floatx16{0};
 #pragma unroll
-      for (int h8 = 0; h8 < 2; ++h8) {
-        const u32x4 pk = mk4(cvt_pk_bf16(oacc[dt][8 * h8 + 0] * inv, oacc[dt][8 * h8 + 1] * inv),
-                             cvt_pk_bf16(oacc[dt][8 * h8 + 2] * inv, oacc[dt][8 * h8 + 3] * inv),
-                             cvt_pk_bf16(oacc[dt][8 * h8 + 4] * inv, oacc[dt][8 * h8 + 5] * inv),
-                             cvt_pk_bf16(oacc[dt][8 * h8 + 6] * inv, oacc[dt][8 * h8 + 7] * inv));
-        *reinterpret_cast<u32x4*>(op + 32 * dt + 8 * h8) = pk;
+      for (int v = 0; v < 16; ++v) cls[dt][v] = 0u;
+    }
+    m_run = -INFINITY;
+    l_run = 0.f;
+    aload2(t_begin, 0);
+    for (int t = t_begin; t < t_end; ++t) {
+      const int slot = (t - t_begin) & 1, kv0 = t * kBKV;
+      const uint32_t stage = (uint32_t)(slot * C::STAGE);
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();                                   // tile t has landed, the other slot has been read
+      if (t + 1 < t_end) aload2(t + 1, slot ^ 1);
+      if (kv0 >= wave_vis_max) continue;                 // (wave-uniform; the barrier is at the top)
+      logits(stage, s_a);
+      float mx = -INFINITY;
+#pragma unroll
+      for (int v = 0; v < 32; ++v) {
+        const int j = kv0 + 32 * (v >> 4) + 8 * ((v & 15) >> 2) + 4 * hf + (v & 3);
+        s_a[v >> 4][v & 15] = (j < vis) ? s_a[v >> 4][v & 15] : -INFINITY;
+        mx = fmaxf(mx, s_a[v >> 4][v & 15]);
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float m_new = fmaxf(m_run, mx * k2);
+      const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < C::DT; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) oacc[dt][v] *= alpha;
+      floatx16 n[C::DT];                                 // sums of the class codes of this tile's tokens that a row sees
+#pragma unroll
+      for (int dt = 0; dt < C::DT; ++dt) n[dt] = floatx16{0};
+      bool any_cls = false;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {                      // 16 tokens: registers 8 s .. 8 s + 7
+        u32x4 pf, pr, ps, seen;
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          const int v = 8 * s + e, j = kv0 + 16 * s + 8 * (e >> 2) + 4 * hf + (e & 3);
+          const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_a[v >> 4][v & 15], k2, -m_use));
+          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_a[v >> 4][(v & 15) + 1], k2, -m_use));
+          l_run += p0;
+          l_run += p1;
+          pf[e >> 1] = cvt_pk_bf16(p0, p1);
+          uint32_t second, third;
+          split_rest(p0, p1, pf[e >> 1], second, third);
+          pr[e >> 1] = second;
+          ps[e >> 1] = third;
+          seen[e >> 1] = (j < vis ? 0x3f80u : 0u) | (j + 1 < vis ? 0x3f800000u : 0u);
+        }
+#pragma unroll
+        for (int dt = 0; dt < C::DT; ++dt) {
+          const shortx4 lo = lds_read_tr(vofs[dt] + (stage + (16 * s) * C::ROW)),
+                        hi = lds_read_tr(vofs[dt] + (stage + (16 * s + 8) * C::ROW));
+          u32x4 fin = __builtin_bit_cast(u32x4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+          if (__any(!all_finite(fin))) {
+            u32x4 code;
+            split_classes(fin, fin, code);
+            n[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, code), __builtin_bit_cast(bf16x8, seen), n[dt], 0, 0, 0);
+            any_cls = true;
+          }
+          const bf16x8 vf = __builtin_bit_cast(bf16x8, fin);
+          oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8, pf), oacc[dt], 0, 0, 0);
+          oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8, pr), oacc[dt], 0, 0, 0);
+          oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8, ps), oacc[dt], 0, 0, 0);
+        }
+      }
+      if (any_cls) {
+#pragma unroll
+        for (int dt = 0; dt < C::DT; ++dt)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const int c = (int)n[dt][v];
+            cls[dt][v] |= ((c & 0x7f) ? 1u : 0u) | ((c & 0x3f80) ? 2u : 0u) | ((c >> 14) ? 4u : 0u);
+          }
       }
     }
-    if (!C::SPLIT_P && a.lse && hf == 0)
-      a.lse[srow * a.H + head] = l_tot > 0.f ? (m_run + log2f(l_tot)) * kLn2 : -INFINITY;
+    if (!bad) return;
+    const float l = l_run + __shfl_xor(l_run, 32, 64);
+    // no weight at all (every visible logit is -infinity): NaN, unless other segments may have some
+    const float den = l != 0.f ? 1.f / l : split ? 0.f : __builtin_nanf("");
+    auto x = [&](int dt, int v) {
+      const uint32_t c = l > 0.f ? cls[dt][v] : 0u;
+      const float w = oacc[dt][v] * den;
+      return c == 0u ? w : c == 1u ? INFINITY : c == 2u ? -INFINITY : __builtin_nanf("");
+    };
+    const float lse2 = l != 0.f ? m_run + log2f(l) : split ? -INFINITY : __builtin_nanf("");
+    if (split) store_split(x, lse2);
+    else store_whole(x, lse2);
   }
 }
 
@@ -583,6 +698,12 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(AttnArgs a) {
 
 // Merge of the partial results of split row blocks: kMergeWgs workgroups per (row block, KV head), one
 // thread per 8 output elements.  out = sum_s w_s O_s with w_s = 2^(lse_s - lse), lse = log2 sum_s 2^lse_s.
+// weight * value; an infinite or NaN value keeps its class also where the weight has underflowed to 0 (SPLIT_P)
+template <bool SPLIT_P>
+__device__ __forceinline__ float weighted(float w, float f) {
+  if (SPLIT_P) return fabsf(f) < INFINITY ? w * f : f;
+  return w * f;
+}
 template <int D> constexpr int kMergeWgs = kRowsPerWg * (D / 8) / 256;
 template <int D>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
@@ -616,6 +737,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   const float* pl = a.part_lse + slot0 * kRowsPerWg + r;
   const part_t* po = static_cast<const part_t*>(a.part_o) + (slot0 * kRowsPerWg + r) * D + 8 * ch;
   // four segments at a time: every load first, then the running maximum, the weights and the weighted sum
+  constexpr bool SPLIT_P = AttnTile<D>::SPLIT_P;
+  bool nan = false;                                 // (SPLIT_P) the denominator of some segment is NaN
   float mx = -INFINITY, wsum = 0.f;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int sg0 = 0; sg0 < n_seg; sg0 += 4) {
@@ -631,12 +754,15 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     }
     float mn = mx;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) mn = fmaxf(mn, l[u]);
+    for (int u = 0; u < 4; ++u) {
+      mn = fmaxf(mn, l[u]);
+      nan |= l[u] != l[u];
+    }
     if (mn > -INFINITY) {
       const float resc = __builtin_amdgcn_exp2f(mx - mn);        // 0 while nothing was visible so far
       wsum *= resc;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] *= resc;
+      for (int e = 0; e < 8; ++e) acc[e] = weighted<SPLIT_P>(resc, acc[e]);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const float w = __builtin_amdgcn_exp2f(l[u] - mn);        // 0 for a segment that saw nothing
@@ -645,7 +771,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
         for (int w = 0; w < (int)sizeof(part_t) / 2; ++w) Vec16<part_t>::unpack(raw[u][w], f + w * Elem<part_t>::kVec);
         wsum += w;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] += w * f[e];
+        for (int e = 0; e < 8; ++e) acc[e] += weighted<SPLIT_P>(w, f[e]);
       }
       mx = mn;
     }
@@ -653,30 +779,21 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] *= inv;
-  if (row_ok && a.lse && ch == 0) a.lse[srow * a.H + head] = wsum > 0.f ? (mx + log2f(wsum)) * kLn2 : -INFINITY;
-  bool store_row = row_ok;
-  if constexpr (AttnTile<D>::SPLIT_P) {
-    bool nan = false;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) nan |= acc[e] != acc[e];
-    uint64_t bad = __ballot(nan && row_ok);              // lanes CH * i .. + CH - 1 hold row i of the wave
-    store_row = row_ok && !((bad >> ((tid & 63) / CH * CH)) & ((1u << CH) - 1u));
-    while (bad) {
-      const int i = __builtin_ctzll(bad) / CH;
-      bad &= ~((uint64_t)((1u << CH) - 1u) << (i * CH));
-      const int rr = part * (256 / CH) + (tid >> 6) * (64 / CH) + i;
-      const int64_t sr = s0 + (int64_t)wg * BR + rr / a.G;
+  float lse = wsum > 0.f ? (mx + log2f(wsum)) * kLn2 : -INFINITY;
+  if constexpr (SPLIT_P) {
+    if (row_ok && !nan && wsum == 0.f) {            // no weight although tokens are visible
       const int64_t c0 = min(max(a.ctx_off[b], (int64_t)0), a.total_ctx);
       const int64_t c1 = min(max(a.ctx_off[b + 1], c0), a.total_ctx);
-      const int64_t p0 = a.ctx_pos0 ? a.ctx_pos0[b] : 0;
-      const int vis = (int)min(c1 - c0, max((int64_t)0, (int64_t)a.sel_pos[sr] - p0 + 1));
-      const int64_t at = (sr * a.H + g * a.G + rr % a.G) * D, kv0 = (c0 * a.Hkv + g) * D;
-      attn_row_by_token(static_cast<const bf16_t*>(a.q) + at, static_cast<const bf16_t*>(a.k) + kv0,
-                        static_cast<const bf16_t*>(a.v) + kv0, (int64_t)a.Hkv * D, vis,
-                        static_cast<bf16_t*>(a.o) + at, tid & 63);
+      nan = c1 > c0 && (int64_t)a.sel_pos[srow] >= (a.ctx_pos0 ? a.ctx_pos0[b] : 0);
+    }
+    if (nan) {
+      lse = __builtin_nanf("");
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] = lse;
     }
   }
-  if (store_row)
+  if (row_ok && a.lse && ch == 0) a.lse[srow * a.H + head] = lse;
+  if (row_ok)
     *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(a.o) + (srow * a.H + head) * D + 8 * ch) = Vec16<bf16_t>::pack(acc);
 }
 

@@ -289,6 +289,60 @@ def test_attention_of_64_wide_heads_infinite_values(T, n):
     one_rounding(o[keep], ref[keep])
 
 
+@pytest.mark.parametrize("T,n", [(200, 40), (4099, 615)])      # whole row blocks; split ones
+@pytest.mark.parametrize("what", ["nan key", "nan values", "both infinities", "minus infinity", "large", "no weight"])
+def test_attention_of_64_wide_heads_special_values(T, n, what):
+    """What a row does not see leaves no trace; what it sees gives NaN, an infinity or (large finite values) a finite
+    number as the sum over its visible tokens does, and a NaN log-sum-exp where a logit is NaN."""
+    say(f"attention d=64 {what} T={T}")
+    sh = inputs.LayerShape(2048, 32, 8, 64, 10000.0, "bf16")
+    g, inf, nan = gen(55), float("inf"), float("nan")
+    q = torch.randn((n, 32, 64), generator=g, device=DEV, dtype=BF)
+    k, v = (torch.randn((T, 8, 64), generator=g, device=DEV, dtype=BF) for _ in range(2))
+    pos = torch.sort(torch.randperm(T, generator=g, device=DEV)[:n])[0].int()
+    pos[0] = 0
+    at = T // 3
+    if what == "large":                  # logits that rise by 5 after the first tokens: less than the reference point may lag
+        q[:], k[:], v[:] = 1.0, 0.0, 0.0
+        k[at:, :, 0] = 40.0
+        v[at, :, 7] = 3.0e38
+    if what == "no weight":              # the first token's logit is -infinity, and row 0 sees nothing else
+        q[:, :, 9] = q[:, :, 9].abs() + 0.5
+        k[0, :, 9] = -inf
+    ro, rl = _attention64(q, k, v, pos, 0.125)
+    ref, lse_ref = ro.float(), rl.float()
+    sees = pos >= at
+    if what == "nan key":
+        k[at, :, 11] = nan
+        ref[sees], lse_ref[sees] = nan, nan
+    elif what == "nan values":
+        v[at:] = nan
+        ref[sees] = nan
+    elif what == "both infinities":
+        v[at, :, 5], v[at + 3, :, 5], v[at + 3, :, 6] = inf, -inf, -inf
+        ref[:, :, 5][pos >= at] = inf
+        ref[:, :, 5][pos >= at + 3] = nan
+        ref[:, :, 6][pos >= at + 3] = -inf
+    elif what == "minus infinity":
+        v[at, 3, 63] = -inf
+        ref[:, 12:16, 63][sees] = -inf
+    elif what == "no weight":
+        ref[pos == 0], lse_ref[pos == 0] = nan, nan
+    else:
+        assert bool(ref.isfinite().all()) and float(ref.max()) > 1e35
+    o, lse = torch.full((n, 32, 64), 7.0, dtype=BF, device=DEV), torch.full((n, 32), 7.0, device=DEV)
+    qb.qcf_recompute_attn(qb.make_desc(sh), 1, q, pos, i64([0, n]), n, k, v, i64([0, T]), T, None, o, lse)
+    torch.cuda.synchronize()
+    of = o.float()
+    assert torch.equal(of.isnan(), ref.isnan()) and torch.equal(lse.isnan(), lse_ref.isnan())
+    assert torch.equal(of.isinf(), ref.isinf()) and torch.equal(of[ref.isinf()], ref[ref.isinf()])
+    fin = ref.isfinite()
+    err = (of[fin] - ref[fin]).abs() - 2.0 ** -8 * ref[fin].abs()
+    assert float(err.max()) <= 2e-4
+    fin = lse_ref.isfinite()
+    assert float((lse[fin] - lse_ref[fin]).abs().max()) < 2e-5
+
+
 @pytest.mark.parametrize("H,Hkv,ctx,probes,limit", [
     (32, 8, [4099], [40], False), (8, 2, [300, 1, 64, 1025, 256], [5, 3, 0, 17, 30], False),
     (8, 4, [700], [33], True),
