@@ -391,6 +391,11 @@ __device__ __forceinline__ void load_epi_rows(const QkvArgs& a, int64_t m0, int 
   }
 }
 
+// a * c + b * s with one rounding of the second product (stated, so that every tile rounds alike)
+__device__ __forceinline__ float turned(float a, float c, float b, float s) {
+#pragma clang fp contract(off)
+  return __builtin_fmaf(a, c, b * s);
+}
 // Rotation of the 128 columns held by a wave; the pair of a column is in the same lane.  JP: 32-column blocks of half
 // a head (half-split pairs), or 0: interleaved pairs.
 template <int TM, int JP, bool FAR>
@@ -414,8 +419,8 @@ __device__ __forceinline__ void epi_rotate(floatx16 (&acc)[TM][4], const float2*
             float wx, wy;
             rotary_factor<FAR>(rows.pos[i], rho[c], wx, wy);
             const float f0 = acc[i][j][4 * q + c], f1 = acc[i][j + JP][4 * q + c];
-            o0[c] = f0 * wx - f1 * wy;
-            o1[c] = f1 * wx + f0 * wy;
+            o0[c] = turned(f0, wx, -f1, wy);
+            o1[c] = turned(f1, wx, f0, wy);
           }
           epi_put(lds, lane, i, j, q, rows.zero[i], o0);
           epi_put(lds, lane, i, j + JP, q, rows.zero[i], o1);
@@ -436,7 +441,8 @@ __device__ __forceinline__ void epi_rotate(floatx16 (&acc)[TM][4], const float2*
           rotary_factor<FAR>(rows.pos[i], rho0, wx, wy);
           rotary_factor<FAR>(rows.pos[i], rho1, vx, vy);
           const float f0 = acc[i][j][4 * q], f1 = acc[i][j][4 * q + 1], f2 = acc[i][j][4 * q + 2], f3 = acc[i][j][4 * q + 3];
-          epi_put(lds, lane, i, j, q, rows.zero[i], float4v{f0 * wx - f1 * wy, f1 * wx + f0 * wy, f2 * vx - f3 * vy, f3 * vx + f2 * vy});
+          epi_put(lds, lane, i, j, q, rows.zero[i],
+                  float4v{turned(f0, wx, -f1, wy), turned(f1, wx, f0, wy), turned(f2, vx, -f3, vy), turned(f3, vx, f2, vy)});
         }
       }
   }

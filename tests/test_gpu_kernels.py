@@ -191,6 +191,29 @@ def test_rotation_at_positions_from_2_24_on(M, K, D, style):
         assert excess <= 2 * np.pi * 3e-7
 
 
+@pytest.mark.parametrize("D,style", [(128, 0), (64, 0), (128, 1), (64, 1)])
+def test_projection_rounds_alike_in_every_tile(D, style):
+    """Without the optional workspace (one contraction per element) a row's bits do not depend on the tile it falls in."""
+    say(f"projection bits D={D} style={style}")
+    M, dm, H, Hkv = 4700, 2048, 4096 // D, 1024 // D
+    sh = inputs.LayerShape(dm, H, Hkv, D, 500000.0, "bf16", style)
+    g, desc, lib = gen(56), qb.make_desc(sh), qb.load_library()
+    x = torch.randn((M, dm), generator=g, device=DEV, dtype=BF)
+    w = torch.randn((sh.qkv_rows, dm), generator=g, device=DEV, dtype=BF) * dm ** -0.5
+    pos = torch.randint(0, 40000, (M,), generator=g, device=DEV).int()
+    pos[7] = 1 << 25                                         # its wave takes the far path, the other rows keep their bits
+    outs = []
+    for m in (M, 1229, 300, 60):                             # 256 x 256, 256 x 128, 128 x 128 and 64 x 128 tiles
+        q, k, v = (torch.full((m, h, D), 7.0, dtype=BF, device=DEV) for h in (H, Hkv, Hkv))
+        assert lib.qcf_recompute_qkv(C.byref(desc), x.data_ptr(), m, None, m, w.data_ptr(), pos.data_ptr(), q.data_ptr(),
+                                     k.data_ptr(), v.data_ptr(), None, 0, torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        outs.append((q, k, v))
+    for o in outs[1:]:
+        for a, b in zip(o, outs[0]):
+            assert torch.equal(a, b[:a.shape[0]])
+
+
 @pytest.mark.parametrize("M,dm,H,Hkv", [
     (1300, 4096, 32, 8),             # whole rounds of row tiles, then 20 rows with a split contraction
     (4916, 8192, 64, 8),             # the same, more rows left
