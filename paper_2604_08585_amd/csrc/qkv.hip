@@ -1051,7 +1051,7 @@ GemmPlan plan_ws(int64_t M, int nb, int nk, size_t part_bytes) {
   const int64_t tiles = (M + bm - 1) / bm * nb;
   const double c = bm == 64 ? 0.40 : ws128_tile_us(rounds_of(tiles));
   for (int s = 1; s <= 16 && s * 4 <= nk; ++s) {
-    if (split_part_bytes(M, nb, bm, s) > part_bytes) break;
+    if (split_part_bytes(M, nb, bm, s) > part_bytes || (s > 1 && nb > 65535)) break;      // (grid.y of the reduction)
     const int len = (nk + s - 1) / s;
     if ((nk + len - 1) / len != s) continue;                     // (a range would be empty)
     double t = std::max(rounds_of(tiles * s) * c * len, (double)nb * nk * (kBN * kBK * 2) / 4.6e6) + rounds_of(tiles * s) * 6.0;
@@ -1207,7 +1207,6 @@ qcf_status run_gemm(const QkvArgs& a_in, int nb, void* ws, size_t ws_bytes, hipS
   a.n_tile0 = 0;
   a.n_tiles = nb;
   a.part = ws;
-  if (nb > 65535) return fail(QCF_ERR_UNSUPPORTED, "qkv: too many columns");
   // (x of 4 GiB and more needs 64-bit addresses per lane: one variant, such calls have plenty of rows)
   if (wide) return run_ws<Ws128, EPI, true>(a, 1, st);
   // (rows that x does not have read its first row: x must not be moved then)

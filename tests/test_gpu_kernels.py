@@ -92,6 +92,18 @@ def test_linear_swiglu(M, K, F):
         assert bool(((plain.float() - want.float()).abs() <= lim).all())
 
 
+def test_linear_of_more_column_blocks_than_a_grid_dimension_holds():
+    say("linear N=2^23")
+    M, K, N = 3, 64, 128 * 65536
+    g = gen(57)
+    x = torch.randn((M, K), generator=g, device=DEV, dtype=BF)
+    w = torch.randn((N, K), generator=g, device=DEV, dtype=BF) * K ** -0.5
+    out = torch.full((M, N), 7.0, dtype=BF, device=DEV)
+    qb.qcf_linear(qb.make_desc(inputs.LayerShape(4096, 32, 8, 128, 500000.0, "bf16")), x, M, K, w, N, None, out)
+    torch.cuda.synchronize()
+    one_rounding(out, x.float() @ w.float().T)
+
+
 def test_swiglu_over_the_float_range():
     """Against float64: the argument of the exponential carries a rounding (relative error |g| 2^-24 of the exponential),
     the other operations a few of 2^-24; where the exponential overflows (g < -88.72, a result below 2^-121) it is 0.
