@@ -1072,12 +1072,15 @@ GemmPlan plan_ws(int64_t M, int nb, int nk, size_t part_bytes) {
 // rows 483 us in one launch, 492 that way.)
 struct ProductPlan { GemmKind kind; int64_t rows; int blocks; GemmPlan rest; double us; };
 
+// The 256 x 256 kernel takes k-tiles in pairs, and its lanes address 256 weight rows with 32-bit byte offsets.
+bool quad_ok(int nk) { return nk % 2 == 0 && (uint64_t)nk * kBK * 2 * QuadTile::BN <= (1ull << 32); }
+
 ProductPlan plan_product(int64_t M, int nb, int nk, bool by_rows, size_t part_bytes) {
   const GemmPlan one = plan_ws(M, nb, nk, part_bytes);
   ProductPlan best{one.kind, 0, 0, one, one.us};                 // (rows and blocks 0: `rest` is everything)
   const int cus = compute_unit_count();
   const int64_t mt = (M + 255) / 256;
-  if (nk % 2 == 0) {                                             // (the 256 x 256 kernel takes k-tiles in pairs)
+  if (quad_ok(nk)) {
     const double whole = quad_us(mt, nb, nk);
     if (whole < best.us) best = ProductPlan{kQuad, M, nb, one, whole};
     const int64_t rounds = mt * ((nb + 1) / 2) / cus;
@@ -1091,7 +1094,7 @@ ProductPlan plan_product(int64_t M, int nb, int nk, bool by_rows, size_t part_by
   }
   if (!by_rows) return best;
   for (GemmKind kind : {kQuad, kWs256}) {
-    if (kind == kQuad && nk % 2 != 0) continue;
+    if (kind == kQuad && !quad_ok(nk)) continue;
     const int64_t units = kind == kQuad ? (nb + 1) / 2 : nb;     // workgroups of a row tile
     const int64_t rounds = mt * units / cus;
     for (int64_t r = rounds; r >= 1 && r >= rounds - 1; --r) {

@@ -104,6 +104,25 @@ def test_linear_of_more_column_blocks_than_a_grid_dimension_holds():
     one_rounding(out, x.float() @ w.float().T)
 
 
+def test_projection_of_very_long_rows():
+    """256 weight rows of more than 4 GiB: no tile may address them with 32-bit offsets."""
+    say("projection d_model=8500096")
+    M, K = 65536, 8500096                # (a size whose cost would speak for the 256 x 256 tiles)
+    sh = inputs.LayerShape(K, 2, 1, 128, 500000.0, "bf16")
+    g = gen(58)
+    x = torch.zeros((2, K), dtype=BF, device=DEV)
+    w = torch.zeros((512, K), dtype=BF, device=DEV)
+    x[:, -64:] = torch.randn((2, 64), generator=g, device=DEV).to(BF)
+    w[:, -64:] = (torch.randn((512, 64), generator=g, device=DEV) * 0.125).to(BF)
+    gather = (torch.arange(M, device=DEV) % 2).int()
+    q, k, v = (torch.full((M, h, 128), 7.0, dtype=BF, device=DEV) for h in (2, 1, 1))
+    qb.qcf_recompute_qkv(qb.make_desc(sh), x, 2, gather, M, w, torch.zeros(M, dtype=torch.int32, device=DEV), q, k, v)
+    torch.cuda.synchronize()
+    ref = (x[:, -64:].float() @ w[:, -64:].float().T).reshape(2, 4, 128)
+    for t, r in ((q, ref[:, :2]), (k, ref[:, 2:3]), (v, ref[:, 3:])):
+        one_rounding(t, r[gather.long()])
+
+
 def test_swiglu_over_the_float_range():
     """Against float64: the argument of the exponential carries a rounding (relative error |g| 2^-24 of the exponential),
     the other operations a few of 2^-24; where the exponential overflows (g < -88.72, a result below 2^-121) it is 0.
