@@ -261,6 +261,9 @@ def extract_anchors(desc, k: torch.Tensor, v: torch.Tensor, chunk_lens: List[int
     norm.  Returns (rows into k / v, ascending inside each chunk; anchor K rows; anchor V rows).  Three library
     calls: key norm, Top-N per chunk (the selection kernel with one "request" per chunk), gather."""
     dev = k.device
+    if dev.type == "cuda" and torch.cuda.is_current_stream_capturing():
+        # a replay would copy the offsets from host memory that has been given back by then
+        raise RuntimeError("extract_anchors cannot be captured into a graph: it copies its offsets from the host")
     rows = int(sum(chunk_lens))
     n_per_chunk = [min(int(n), int(l)) for n, l in zip(n_per_chunk, chunk_lens)]
     total = int(sum(n_per_chunk))

@@ -509,3 +509,24 @@ def test_select_keys_per_thread(lens):
         ref = torch.sort(torch.sort(score[c0:c0 + n], descending=True, stable=True)[1][:m])[0].int()
         assert torch.equal(idx[s0:s0 + m], ref) and torch.equal(pos[s0:s0 + m], ref) and torch.equal(row[s0:s0 + m], ref + c0)
         c0, s0 = c0 + n, s0 + m
+
+
+def test_anchor_extraction_is_refused_under_capture():
+    """Its offsets come from a pinned block that is handed back after the call; a replay would read whatever is there."""
+    say("anchors under capture")
+    sh = inputs.LayerShape(4096, 32, 8, 128, 500000.0, "bf16")
+    k, v = (torch.randn((96, 8, 128), generator=gen(59), device=DEV, dtype=BF) for _ in range(2))
+    desc, graph = qb.make_desc(sh), torch.cuda.CUDAGraph()
+    want = pipeline.extract_anchors(desc, k, v, [64, 32], [4, 2])        # (allocations are warm, the pinned block is free again)
+    torch.cuda.synchronize()
+    refused = False
+    with torch.cuda.graph(graph):
+        t = k * 1.0
+        try:
+            pipeline.extract_anchors(desc, k, v, [64, 32], [4, 2])
+        except RuntimeError:
+            refused = True
+    assert refused
+    got = pipeline.extract_anchors(desc, k, v, [64, 32], [4, 2])
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
