@@ -111,7 +111,12 @@ qcf_status qcf_rerope(const qcf_layer_desc* desc, const qcf_chunk* chunks_dev, i
  * contributes 0 (it still counts in the mean).  score [total_ctx] float32; each request's
  * scores sum to 1 when every probe row sees at least one token (always, without
  * probe_limit); a request without probe rows gets zeros.  Deterministic: no
- * floating-point atomics. */
+ * floating-point atomics.
+ * bf16 with head_dim 128, where total_probe * H / H_kv <= 320 and the launch fits the GPU at once: one kernel whose
+ * workgroups wait for each other, with counters in the library (eight sets per GPU, taken in turn).  At most eight such
+ * calls may be in flight on one GPU (streams, graphs replayed side by side); a workgroup whose wait exceeds its bound,
+ * seconds, because another launch keeps the rest off the GPU gives up, and the scores are wrong.  All other calls keep
+ * everything in the workspace and may overlap freely. */
 size_t qcf_score_workspace_bytes(const qcf_layer_desc* desc, int32_t B, int64_t total_probe,
                                  int64_t total_ctx);
 qcf_status qcf_score(const qcf_layer_desc* desc, int32_t B,
@@ -169,7 +174,11 @@ qcf_status qcf_select(int32_t B, const float* score, const int64_t* ctx_off_dev,
  * heads, H_kv key heads, H_kv value heads; rotary embedding at pos[m] on Q and K.
  * x [x_rows, d_model]; w_qkv [(H + 2 H_kv) d, d_model]; outputs q_out [M, H, d],
  * k_out / v_out [M, H_kv, d]; any output pointer may be NULL to skip that part
- * (e.g. only Q for probe rows).  fp32 accumulation, outputs stored in desc->dtype. */
+ * (e.g. only Q for probe rows).  fp32 accumulation, outputs stored in desc->dtype.
+ * bf16 MFMA path (d_model % 64 == 0, H_kv * d % 128 == 0), here and in qcf_linear: the workspace is optional.  With it the
+ * contraction of a small number of rows (or of the rows that full rounds of tiles leave over) is cut into ranges whose
+ * fp32 sums are added in a fixed order, which is faster; the last bits of a row then depend on M and on whether the
+ * workspace is given.  Without it they do not.  Either way the same call gives the same bits. */
 size_t qcf_recompute_qkv_workspace_bytes(const qcf_layer_desc* desc, int64_t M);
 qcf_status qcf_recompute_qkv(const qcf_layer_desc* desc, const void* x, int64_t x_rows,
                              const int32_t* x_gather_dev, int64_t M, const void* w_qkv,
