@@ -60,8 +60,8 @@ struct AttnArgs {
   int n_seg_max;         // units per row block the grid provides
   void* part_o;          // [unit][128 rows][D] normalised partial outputs of split row blocks (AttnTile<D>::part_t)
   float* part_lse;       // [unit][128 rows] log2-domain log-sum-exp of each partial (-inf: no visible key)
-  int32_t* units;        // units[0] = number of work units, then (row block << 8 | segment), longest first
-  int32_t* blk_tiles;    // [row block] key tiles of the block, written by the plan kernel for the merge kernel
+  int32_t* units;        // units[0] = number of work units, then (row block << 8 | segment), longest first (null: no plan)
+  int32_t* blk_tiles;    // [row block] key tiles of the block, written by the plan kernel for the merge kernel (null: no plan)
 };
 
 // ------------------------------------------------------------------ generic path
@@ -236,12 +236,12 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
 
   // consecutive workgroup ids land on different XCDs: give each XCD its own KV heads so that a
   // head's keys and values stay in one L2; later row blocks (longer key ranges) are scheduled first
-  // Unsplit launches take the row blocks from the last (longest key range) to the first.  Split launches
+  // Launches without a plan take the row blocks from the last (longest key range) to the first.  The others
   // read the unit list attn_plan_kernel sorted by length; segments are counted from the top of a block's
   // key range, so a block's remainder segment is the one at the start of the context.
   const int g = (int)(blockIdx.x % a.Hkv);
   const int unit = (int)(blockIdx.x / a.Hkv);
-  int seg = 0, blk = a.n_row_blocks - 1 - unit;
+  int seg = unit % a.n_seg_max, blk = a.n_row_blocks - 1 - unit / a.n_seg_max;
   if (a.units) {
     if (unit >= a.units[0]) return;
     const int code = a.units[1 + unit];
@@ -715,8 +715,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   const int bh = (int)(blockIdx.x / kMergeWgs<D>);
   const int g = bh % a.Hkv;
   const int blk = bh / a.Hkv;
-  const int n_tiles = a.blk_tiles[blk];
-  if (n_tiles <= a.seg_tiles) return;               // not split: the main kernel wrote the result
+  int n_tiles = a.blk_tiles ? a.blk_tiles[blk] : 0;
+  if (a.blk_tiles && n_tiles <= a.seg_tiles) return;      // not split: the main kernel wrote the result
   int wg = blk, b = 0;
   int64_t s0 = 0, s1 = 0;
   for (; b < a.B; ++b) {
@@ -727,6 +727,22 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     wg -= nb;
   }
   if (b >= a.B) return;
+  if (!a.blk_tiles) {                               // no plan: the key tiles of this block, as the main kernel counts them
+    __shared__ int s_vis[4];
+    const int64_t sr = s0 + (int64_t)wg * BR + tid;
+    int vis = 0;
+    if (tid < BR && sr < s1) {
+      const int64_t c0 = min(max(a.ctx_off[b], (int64_t)0), a.total_ctx);
+      const int64_t c1 = min(max(a.ctx_off[b + 1], c0), a.total_ctx);
+      const int64_t p0 = a.ctx_pos0 ? a.ctx_pos0[b] : 0;
+      vis = (int)min(c1 - c0, max((int64_t)0, (int64_t)a.sel_pos[sr] - p0 + 1));
+    }
+    for (int d = 32; d >= 1; d >>= 1) vis = max(vis, __shfl_xor(vis, d, 64));
+    if ((tid & 63) == 0) s_vis[tid >> 6] = vis;
+    __syncthreads();
+    n_tiles = (max(max(s_vis[0], s_vis[1]), max(s_vis[2], s_vis[3])) + kBKV - 1) / kBKV;
+    if (n_tiles <= a.seg_tiles) return;
+  }
   const int n_seg = (n_tiles + a.seg_tiles - 1) / a.seg_tiles;
   const int r = part * (256 / CH) + tid / CH, ch = tid % CH;    // row of the block, 8-element chunk
   const int64_t srow = s0 + (int64_t)wg * BR + r / a.G;
@@ -799,9 +815,10 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 
 // Key tiles per work unit.  With enough row blocks the causal triangle balances by itself and blocks
 // stay whole; otherwise a segment is about the average causal work of a resident workgroup.
+int resident_workgroups(int D) { return (D == 128 ? AttnTile<128>::WGS : AttnTile<64>::WGS) * compute_unit_count(); }
 struct Split { int seg_tiles, n_seg_max; };
 Split choose_split(int D, int64_t n_blocks, int64_t total_ctx) {
-  const int slots = (D == 128 ? AttnTile<128>::WGS : AttnTile<64>::WGS) * compute_unit_count();     // resident workgroups
+  const int slots = resident_workgroups(D);
   const int64_t n_t = std::max<int64_t>(1, (total_ctx + kBKV - 1) / kBKV);
   const int64_t per_slot = n_blocks * ((n_t + 1) / 2) / slots;     // average causal work per resident workgroup
   // a little above that average (a multiple of 4 tiles): most resident workgroups then take one whole
@@ -830,7 +847,7 @@ qcf_status run_mfma(const AttnArgs& a, hipStream_t st) {
   static std::atomic<uint64_t> lds_ok{0};
   QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&attn_mfma_kernel<D>), AttnTile<D>::LDS, lds_ok));
   const int64_t blocks = (int64_t)a.n_row_blocks * a.Hkv;
-  if (a.n_seg_max > 1) {
+  if (a.units) {
     attn_plan_kernel<<<dim3(1), dim3(1024), 0, st>>>(a);
     QCF_TRY_LAUNCH("attn plan");
   }
@@ -890,9 +907,13 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
       a.part_o = ws;
       char* w = static_cast<char*>(ws);
       a.part_lse = reinterpret_cast<float*>(w + part_o_bytes(L.head_dim, nb * a.Hkv, sp.n_seg_max));
-      a.units = reinterpret_cast<int32_t*>(w + part_o_bytes(L.head_dim, nb * a.Hkv, sp.n_seg_max) +
-                                           part_lse_bytes(nb * a.Hkv, sp.n_seg_max));
-      a.blk_tiles = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(a.units) + units_bytes(nb, sp.n_seg_max));
+      // The plan sorts the units for the compute units to take in turn.  Where all of them start at once their order does
+      // not matter, and the launch is saved: 110 rows over 731 tokens 22.3 -> 19.0 us, 40 rows over 8192 30.4 -> 23.5.
+      if (nb * a.Hkv * sp.n_seg_max > resident_workgroups(a.D)) {
+        a.units = reinterpret_cast<int32_t*>(w + part_o_bytes(L.head_dim, nb * a.Hkv, sp.n_seg_max) +
+                                             part_lse_bytes(nb * a.Hkv, sp.n_seg_max));
+        a.blk_tiles = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(a.units) + units_bytes(nb, sp.n_seg_max));
+      }
     }
     return a.D == 128 ? run_mfma<128>(a, st) : run_mfma<64>(a, st);
   }

@@ -320,6 +320,37 @@ def test_attention_of_64_wide_heads(H, Hkv, ctx, sel, with_ws):
         s0, c0 = s0 + n, c0 + t
 
 
+@pytest.mark.parametrize("D,H,Hkv,ctx,sel", [
+    (128, 32, 8, [731], [110]), (128, 32, 8, [600, 30, 1500], [40, 3, 90]), (128, 4, 4, [1100], [300]), (128, 32, 1, [2000], [5]),
+    (64, 32, 8, [731], [110]), (64, 32, 8, [600, 30, 1500], [40, 3, 90]),      # units that all start at once: no plan
+    (128, 32, 8, [6000], [300])])                                                # more than that: sorted by length
+def test_attention_of_split_row_blocks(D, H, Hkv, ctx, sel):
+    """Key ranges cut into segments, with and without the plan kernel; some rows see nothing."""
+    say(f"split attention D={D} H={H} ctx={ctx} sel={sel}")
+    sh = inputs.LayerShape(2048, H, Hkv, D, 10000.0, "bf16")
+    g, desc = gen(60), qb.make_desc(sh)
+    T, N = sum(ctx), sum(sel)
+    assert qb.qcf_recompute_attn_workspace_bytes(desc, len(ctx), N, T) > 0
+    q = torch.randn((N, H, D), generator=g, device=DEV, dtype=BF)
+    k, v = (torch.randn((T, Hkv, D), generator=g, device=DEV, dtype=BF) for _ in range(2))
+    pos = [torch.sort(torch.randperm(t, generator=g, device=DEV)[:n])[0].int() for t, n in zip(ctx, sel)]
+    pos[0][:2] = -1                                          # sees nothing
+    so, co = i64(np.concatenate([[0], np.cumsum(sel)])), i64(np.concatenate([[0], np.cumsum(ctx)]))
+    o, lse = torch.full((N, H, D), 7.0, dtype=BF, device=DEV), torch.full((N, H), 7.0, device=DEV)
+    qb.qcf_recompute_attn(desc, len(ctx), q, torch.cat(pos), so, N, k, v, co, T, None, o, lse)
+    torch.cuda.synchronize()
+    s0 = c0 = 0
+    for t, n, ps in zip(ctx, sel, pos):
+        ro, rl = _attention64(q[s0:s0 + n], k[c0:c0 + t], v[c0:c0 + t], ps, D ** -0.5)
+        none = ps < 0
+        ro[none] = 0.0
+        got, glse = o[s0:s0 + n], lse[s0:s0 + n].double()
+        # d = 128: probabilities and partial outputs are bf16, values up to about 4
+        assert float((got.double() - ro).abs().max()) < (2e-2 if D == 128 else 1.6e-2)
+        assert bool((glse[none] == -float("inf")).all()) and float((glse - rl)[~none].abs().max()) < 2e-5
+        s0, c0 = s0 + n, c0 + t
+
+
 @pytest.mark.parametrize("T,n", [(200, 40), (4099, 615)])      # whole row blocks; split ones
 def test_attention_of_64_wide_heads_infinite_values(T, n):
     """An infinite value reaches the rows that see its token, as an infinity, and no others."""
