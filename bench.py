@@ -137,7 +137,7 @@ def cpu_baseline(cfg, ratio, sample_rows, budget_s=25.0):
 
 def tail_leg(L, shape, d_ff, dev, steps=20):
     """Not part of the metric: the rest of the block for the N recomputed rows (random weights of the
-    8B-shaped block), five library calls, timed call by call with events."""
+    8B-shaped block), the four library calls of pipeline.layer_tail, timed call by call with events."""
     import numpy as np
     import torch
     from paper_2604_08585_amd import binding as qb
@@ -153,14 +153,12 @@ def tail_leg(L, shape, d_ff, dev, steps=20):
     h_in = w(M, dm, 1.0)
     o = L.o_sel[:M].reshape(M, hd)
     bufs = dict(h1=torch.empty((M, dm), dtype=dt, device=dev), n=torch.empty((M, dm), dtype=dt, device=dev),
-                gu=torch.empty((M, 2 * d_ff), dtype=dt, device=dev), act=torch.empty((M, d_ff), dtype=dt, device=dev),
-                out=torch.empty((M, dm), dtype=dt, device=dev))
+                act=torch.empty((M, d_ff), dtype=dt, device=dev), out=torch.empty((M, dm), dtype=dt, device=dev))
     calls = [
         ("o_proj", lambda: qb.qcf_linear(L.desc, o, M, hd, tw.w_o, dm, h_in, bufs["h1"]), 2 * M * hd * dm),
         ("rmsnorm", lambda: qb.qcf_rmsnorm(L.desc, bufs["h1"], tw.norm_weight, tw.eps, M, dm, bufs["n"]), 0),
-        ("gate_up", lambda: qb.qcf_linear(L.desc, bufs["n"], M, dm, tw.w_gate_up, 2 * d_ff, None, bufs["gu"]),
+        ("gate_up_swiglu", lambda: qb.qcf_linear_swiglu(L.desc, bufs["n"], M, dm, tw.w_gate_up, d_ff, bufs["act"]),
          2 * M * dm * 2 * d_ff),
-        ("swiglu", lambda: qb.qcf_swiglu(L.desc, bufs["gu"], M, d_ff, bufs["act"]), 0),
         ("down", lambda: qb.qcf_linear(L.desc, bufs["act"], M, d_ff, tw.w_down, dm, bufs["h1"], bufs["out"]),
          2 * M * d_ff * dm),
     ]

@@ -7,7 +7,7 @@
 // rotation itself: the angle pos * theta_i is taken in turns, with the frequency split in two floats
 // and the product's rounding error recovered by a fused multiply-add (a plain float32 product would be
 // off by 1e-3 rad at 8K positions), reduced to its fraction and handed to the hardware sine and cosine
-// (inputs in turns, errors far below a bf16 ulp).
+// (inputs in turns, errors far below a bf16 ulp).  Positions from 2^24 on are taken in two parts.
 // The generic path (f32, or shapes the MFMA tiling does not cover) writes the raw product to
 // the workspace and rotates it in a second kernel with float64 angles, which also writes the cache rows.
 // qcf_recompute_qkv_scatter: the epilogue of the MFMA path also stores the K and V rows to their rows of the
@@ -1066,10 +1066,12 @@ GemmPlan plan_ws(int64_t M, int nb, int nk, size_t part_bytes) {
 //
 // A tile fills whole rounds of compute units only, so where the last round would be thin the first launch takes what
 // full rounds hold and smaller tiles the rest: the column blocks that are left (256 x 256 tiles), or the rows that are
-// left (tiles of 256 rows), whose contraction may be split because they are few.  Measured, without the division by
-// rows and with it: layer tail (d_model 4096, F 14336) of 2100 rows 889 and 716 us, of 2458 rows 1004 and 852; layer of
-// 64 heads, d_model 8192, over 32768 tokens 3346 and 3294.  (128 x 128 tiles for the whole rounds lose: tail of 1229
-// rows 483 us in one launch, 492 that way.)
+// left (tiles of 256 rows), whose contraction may be split because they are few.  Without the division by rows and with
+// it, both sides in turn: K 4096, N 6144 of 1281 .. 1408 rows 75.2 .. 76.8 and 71.3 .. 74.5 us (its nearest edge; weights
+// not in any cache: 77.0 and 74.2 .. 77.1), 2561 rows 126.8 and 115.2, 5377 rows 227.3 and 218.8; K 8192, N 10240 of 769
+// rows 139.3 and 130.8, 4916 rows 627 and 594; K 14336, N 4096 of 2100 rows 235 and 205.  Where the rest is too long to
+// be split the estimates are less good: 1500 and 2100 rows of the first shape lose 2.7 and 3.7 us.
+// (128 x 128 tiles for the whole rounds lose: tail of 1229 rows 483 us in one launch, 492 that way.)
 struct ProductPlan { GemmKind kind; int64_t rows; int blocks; GemmPlan rest; double us; };
 
 // The 256 x 256 kernel takes k-tiles in pairs, and its lanes address 256 weight rows with 32-bit byte offsets.
