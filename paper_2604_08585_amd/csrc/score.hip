@@ -21,7 +21,7 @@
 // bit-stable from run to run.
 //
 // Heads of 64 run the two MFMA passes with half the k-steps (40 probe rows x 32 heads over 4096 tokens: 391 us with the
-// generic kernels, 15 us here), never the single kernel (see use_fused).
+// generic kernels, 15.7 us here), never the single kernel (see use_fused).
 //
 // Generic path (f32, or other head dims): one workgroup per (probe row, head) materialises its
 // softmax row in the workspace, then a column mean.
@@ -148,6 +148,17 @@ template <int D> __device__ __forceinline__ int staged_elem(int r, int lane) { r
 // byte offset of this lane's fragment (row lane%32, chunk 2*ks + lane/32) is frag_base ^ (32 * ks)
 template <int D> __device__ __forceinline__ int frag_base(int lane) { return (lane & 31) * 2 * D + slot_of<D>(lane >> 5, lane & 31) * 16; }
 constexpr int kFoldBatch = 16;
+// Heads of 64 keep a row's maximum and the reciprocal of its sum apart instead of one log-sum-exp, whose rounding weighs
+// once logits reach a hundred (largest logit 586: 8.7e-6 off in the 2-norm, now 1.7e-6, the general kernels 1.9e-6; largest 12: 1.6e-7, 8.3e-8, 5.3e-7), and
+// a NaN in either reaches every token that the row sees.  The maximum is that of the unscaled logits and is taken off
+// before they are scaled, so that the largest one gives exactly 1 at any magnitude.
+template <int D> constexpr bool kPairs = D == 64;
+template <int D> constexpr float kMaxScale = kPairs<D> ? kK2<D> : 1.f;      // from a kept maximum to log2 units
+template <int D> __device__ __forceinline__ float exp_of(float logit, float m) {
+  if (kPairs<D>) return __builtin_amdgcn_exp2f((logit - m) * kK2<D>);
+  return __builtin_amdgcn_exp2f(__builtin_fmaf(logit, kK2<D>, -m));
+}
+template <int D> constexpr size_t kRowWords = kPairs<D> ? 3 : 2;       // words of LDS per staged row in pass 2
 
 struct ScoreArgs {
   const bf16_t* q;            // [total_probe, H, D]
@@ -235,7 +246,6 @@ __global__ __launch_bounds__(kThreads) void score_pass1(ScoreArgs a) {
   if (rows == 0) return;
   const int tok0 = tile_tok0 + tw * kTokPerWave;
   const bool wave_active = tok0 < T;
-  constexpr float k2 = kK2<D>;
   const int qb0 = frag_base<D>(lane);
   float2* part = a.part + (int64_t)blockIdx.x * (a.total_probe * a.H);
 
@@ -285,10 +295,11 @@ __global__ __launch_bounds__(kThreads) void score_pass1(ScoreArgs a) {
         mx = s[0];
 #pragma unroll
         for (int v = 1; v < 32; ++v) mx = fmaxf(mx, s[v]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * k2;          // k2 > 0: scaling commutes with the maximum
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        if (!kPairs<D>) mx *= kK2<D>;                         // (positive: scaling commutes with the maximum)
         const float m_use = (mx == -INFINITY) ? 0.f : mx;
 #pragma unroll
-        for (int v = 0; v < 32; ++v) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[v], k2, -m_use));
+        for (int v = 0; v < 32; ++v) sum += exp_of<D>(s[v], m_use);
         sum += __shfl_xor(sum, 32, 64);
       }
       if (lane < 32) sPart[tw * kRowBlock + rt + lane] = make_float2(mx, sum);
@@ -303,7 +314,7 @@ __global__ __launch_bounds__(kThreads) void score_pass1(ScoreArgs a) {
       float z = 0.f;
 #pragma unroll
       for (int w = 0; w < kTokWaves; ++w)
-        if (p[w].x > -INFINITY) z += p[w].y * exp2f(p[w].x - m);
+        if (p[w].x > -INFINITY || (kPairs<D> && p[w].y != p[w].y)) z += p[w].y * exp2f((p[w].x - m) * kMaxScale<D>);
       const int rr = r_begin + r;
       const int i = rr / a.G, hh = rr - i * a.G;
       part[(p0 + i) * a.H + g * a.G + hh] = make_float2(m, z);
@@ -311,16 +322,17 @@ __global__ __launch_bounds__(kThreads) void score_pass1(ScoreArgs a) {
   }
 }
 
-// Folds a batch of (max2, sumexp2) partials, in order, into the running pair (m, z).  A partial that saw
+// Folds a batch of (maximum, sumexp2) partials, in order, into the running pair (m, z).  A partial that saw
 // nothing is (-inf, 0) and contributes 0 * exp2(-inf) = 0.
+template <int D>
 __device__ __forceinline__ void fold_partials(const float2 (&p)[kFoldBatch], float& m, float& z) {
   float mn = m;
 #pragma unroll
   for (int u = 0; u < kFoldBatch; ++u) mn = fmaxf(mn, p[u].x);
   if (mn > -INFINITY) {
-    z *= __builtin_amdgcn_exp2f(m - mn);
+    z *= __builtin_amdgcn_exp2f((m - mn) * kMaxScale<D>);
 #pragma unroll
-    for (int u = 0; u < kFoldBatch; ++u) z = __builtin_fmaf(p[u].y, __builtin_amdgcn_exp2f(p[u].x - mn), z);
+    for (int u = 0; u < kFoldBatch; ++u) z = __builtin_fmaf(p[u].y, __builtin_amdgcn_exp2f((p[u].x - mn) * kMaxScale<D>), z);
     m = mn;
   }
 }
@@ -330,8 +342,9 @@ template <int D, bool LIMIT>
 __global__ __launch_bounds__(kThreads) void score_pass2(ScoreArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* sK = smem + kQBytes<D>;
-  float* sL = reinterpret_cast<float*>(smem + kQBytes<D> + kKBytes<D>);          // [kRowBlock] log2-sum-exp
-  int* sLim = reinterpret_cast<int*>(sL + kRowBlock);                       // [kRowBlock]
+  float* sL = reinterpret_cast<float*>(smem + kQBytes<D> + kKBytes<D>);          // [kRowBlock] log2-sum-exp, or maximum
+  float* sRz = sL + (kPairs<D> ? kRowBlock : 0);                            // [kRowBlock] 1 / sum (kPairs)
+  int* sLim = reinterpret_cast<int*>(sL + (kRowWords<D> - 1) * kRowBlock);  // [kRowBlock]
   float* sCol = reinterpret_cast<float*>(sLim + kRowBlock);                 // [kRowGroups][kTokPerWg]
   static_assert(kRowBlock <= kThreads, "one thread folds one staged row");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -348,7 +361,6 @@ __global__ __launch_bounds__(kThreads) void score_pass2(ScoreArgs a) {
   const int64_t part_stride = a.total_probe * a.H;
   const int tok0 = tile_tok0 + tw * kTokPerWave;
   const bool wave_active = tok0 < T;
-  constexpr float k2 = kK2<D>;
   const int qb0 = frag_base<D>(lane);
 
   stage_k_async<D>(a, c0, T, tile_tok0, g, sK, wave, lane);
@@ -365,6 +377,7 @@ __global__ __launch_bounds__(kThreads) void score_pass2(ScoreArgs a) {
     // computes the same values
     if (tid < n_pad) {
       float l = INFINITY;               // rows that do not exist or see nothing: exp2(logit - lse) = 0
+      float rz = 0.f;
       int lim = 0;
       if (tid < n_rows) {
         const int rr = r_begin + tid, i = rr / a.G, hh = rr - i * a.G;
@@ -377,12 +390,20 @@ __global__ __launch_bounds__(kThreads) void score_pass2(ScoreArgs a) {
             p[u] = (t0 + u < n_tiles) ? *pp : make_float2(-INFINITY, 0.f);
             pp += part_stride;          // (stays inside the workspace: n_tiles <= the tiles allocated)
           }
-          fold_partials(p, m, z);
+          fold_partials<D>(p, m, z);
         }
-        if (z > 0.f) l = m + log2f(z);
         lim = LIMIT ? min(T, max(0, a.probe_limit[p0 + i])) : T;
+        if (kPairs<D>) {
+          if (lim > 0) {                // (no weight although tokens are visible, or a NaN sum: NaN)
+            l = m;
+            rz = z > 0.f ? 1.f / z : __builtin_nanf("");
+          }
+        } else if (z > 0.f) {
+          l = m + log2f(z);
+        }
       }
       sL[tid] = l;
+      if (kPairs<D>) sRz[tid] = rz;
       sLim[tid] = lim;
     }
     __builtin_amdgcn_s_waitcnt(0);
@@ -414,6 +435,11 @@ __global__ __launch_bounds__(kThreads) void score_pass2(ScoreArgs a) {
         const int rbase = rt + 8 * q4 + 4 * (lane >> 5);
         const float4 l4 = *reinterpret_cast<const float4*>(sL + rbase);
         const float ls[4] = {l4.x, l4.y, l4.z, l4.w};
+        float rz[4];
+        if (kPairs<D>) {
+          const float4 z4 = *reinterpret_cast<const float4*>(sRz + rbase);
+          rz[0] = z4.x; rz[1] = z4.y; rz[2] = z4.z; rz[3] = z4.w;
+        }
         int lims[4] = {T, T, T, T};
         if (LIMIT) {
           const int4 m4 = *reinterpret_cast<const int4*>(sLim + rbase);
@@ -422,14 +448,20 @@ __global__ __launch_bounds__(kThreads) void score_pass2(ScoreArgs a) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           const int v = 4 * q4 + c;
-          float pa = __builtin_amdgcn_exp2f(__builtin_fmaf(acc0[v], k2, -ls[c]));
-          float pb = __builtin_amdgcn_exp2f(__builtin_fmaf(acc1[v], k2, -ls[c]));
+          float pa = exp_of<D>(acc0[v], ls[c]);
+          float pb = exp_of<D>(acc1[v], ls[c]);
+          if (kPairs<D> && LIMIT) { pa *= rz[c]; pb *= rz[c]; }
           if (LIMIT) {
             if (tA >= lims[c]) pa = 0.f;
             if (tB >= lims[c]) pb = 0.f;
           }
-          col0 += pa;
-          col1 += pb;
+          if (kPairs<D> && !LIMIT) {
+            col0 = __builtin_fmaf(pa, rz[c], col0);
+            col1 = __builtin_fmaf(pb, rz[c], col1);
+          } else {
+            col0 += pa;
+            col1 += pb;
+          }
         }
       }
     }
@@ -679,8 +711,8 @@ __global__ __launch_bounds__(kFusedThreads) void score_fused(FusedArgs fa) {
           pb[u] = (t0 + kFoldBatch + u < n_tiles) ? fetch(pp + (kFoldBatch + u) * stride) : make_float2(-INFINITY, 0.f);
         }
         pp += 2 * kFoldBatch * stride;
-        fold_partials(pa, m, z);
-        fold_partials(pb, m, z);
+        fold_partials<D>(pa, m, z);
+        fold_partials<D>(pb, m, z);
       }
       sL[r] = (z > 0.f) ? m + log2f(z) : INFINITY;      // a row that sees nothing: every weight is 0
     }
@@ -782,7 +814,7 @@ MfmaWs mfma_ws(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t 
 }
 
 template <int D> constexpr size_t kPass1Lds = kQBytes<D> + kKBytes<D> + (size_t)kTokWaves * kRowBlock * sizeof(float2);
-template <int D> constexpr size_t kPass2Lds = kQBytes<D> + kKBytes<D> + (size_t)kRowBlock * 8 + (size_t)kRowGroups * kTokPerWg * sizeof(float);
+template <int D> constexpr size_t kPass2Lds = kQBytes<D> + kKBytes<D> + kRowBlock * 4 * kRowWords<D> + (size_t)kRowGroups * kTokPerWg * sizeof(float);
 constexpr size_t kFusedLds = kQBytes<128> + kKBytes<128>;
 static_assert((size_t)kFusedWaves * kRowBlock * 8 + (size_t)kRowBlock * 4 + (size_t)kTokPerWg * 4 <= kKBytes<128>,
               "the single-kernel path's tables fit in the key tile's LDS");

@@ -394,6 +394,8 @@ def test_attention_of_64_wide_heads_special_values(T, n, what):
     if what == "no weight":              # the first token's logit is -infinity, and row 0 sees nothing else
         q[:, :, 9] = q[:, :, 9].abs() + 0.5
         k[0, :, 9] = -inf
+    if what == "huge logits":            # one token takes all of a row's weight
+        q, k = q * 1e18, k * 1e18
     ro, rl = _attention64(q, k, v, pos, 0.125)
     ref, lse_ref = ro.float(), rl.float()
     sees = pos >= at
@@ -413,7 +415,7 @@ def test_attention_of_64_wide_heads_special_values(T, n, what):
         ref[:, 12:16, 63][sees] = -inf
     elif what == "no weight":
         ref[pos == 0], lse_ref[pos == 0] = nan, nan
-    else:
+    elif what == "large":
         assert bool(ref.isfinite().all()) and float(ref.max()) > 1e35
     o, lse = torch.full((n, 32, 64), 7.0, dtype=BF, device=DEV), torch.full((n, 32), 7.0, device=DEV)
     qb.qcf_recompute_attn(qb.make_desc(sh), 1, q, pos, i64([0, n]), n, k, v, i64([0, T]), T, None, o, lse)
@@ -425,7 +427,8 @@ def test_attention_of_64_wide_heads_special_values(T, n, what):
     err = (of[fin] - ref[fin]).abs() - 2.0 ** -8 * ref[fin].abs()
     assert float(err.max()) <= 2e-4
     fin = lse_ref.isfinite()
-    assert float((lse[fin] - lse_ref[fin]).abs().max()) < 2e-5
+    # (huge: 64 products of size up to 2e37 / 8, each sum rounded to 2^-24 of at most 1e37)
+    assert float((lse[fin] - lse_ref[fin]).abs().max()) < (64 * 2.0 ** -24 * 1e37 if what == "huge logits" else 2e-5)
 
 
 @pytest.mark.parametrize("H,Hkv,ctx,probes,limit", [
@@ -454,6 +457,57 @@ def test_scores_of_64_wide_heads(H, Hkv, ctx, probes, limit):
         # 32-bit logits of magnitude up to 60, exponentials and sums
         assert bool(((score[c0:c0 + t].double() - ref).abs() <= 3e-5 * ref + 1e-12).all())
         r0, c0 = r0 + r, c0 + t
+
+
+@pytest.mark.parametrize("T,R", [(300, 12), (4099, 40), (1000, 100)])
+@pytest.mark.parametrize("what", ["nan key", "nan key beyond the limits", "infinite key", "one token at minus infinity",
+                                  "no weight", "a row that sees nothing", "large logits", "huge logits"])
+def test_scores_of_64_wide_heads_special_values(T, R, what):
+    """A NaN or infinite logit makes its row's softmax, and so every score, NaN, unless no row sees it; so does a row whose
+    visible logits are all -infinity.  Large logits: the error of a float32 logit (2^-24 of it, and of its 64 products)."""
+    say(f"scores d=64 {what} T={T}")
+    H, Hkv = 8, 2
+    sh = inputs.LayerShape(512, H, Hkv, 64, 10000.0, "bf16")
+    g, inf = gen(61), float("inf")
+    q = torch.randn((R, H, 64), generator=g, device=DEV).to(BF)
+    k = torch.randn((T, Hkv, 64), generator=g, device=DEV).to(BF)
+    q[:, :, 3] = q[:, :, 3].abs() + 0.1
+    lim = None
+    clean = k.clone()
+    if what == "nan key":
+        k[T // 2, 1, 3] = float("nan")
+    elif what == "nan key beyond the limits":
+        k[T // 2, 1, 3] = float("nan")
+        lim = torch.full((R,), T // 2, dtype=torch.int32, device=DEV)
+    elif what == "infinite key":
+        k[T // 2, 0, 3] = inf
+    elif what == "one token at minus infinity":
+        k[T // 2, :, 3] = -inf
+        clean = k
+    elif what == "no weight":
+        k[:, :, 3] = -inf
+    elif what == "a row that sees nothing":
+        lim = torch.full((R,), T // 3, dtype=torch.int32, device=DEV)
+        lim[:3] = 0
+    else:
+        q *= 100 if what == "large logits" else 1e18
+        k *= 1 if what == "large logits" else 1e18
+        clean = k
+    score = torch.full((T,), 7.0, device=DEV)
+    qb.qcf_score(qb.make_desc(sh), 1, q, i64([0, R]), R, k, i64([0, T]), T, lim, score)
+    torch.cuda.synchronize()
+    if what in ("nan key", "infinite key", "no weight"):
+        assert bool(score.isnan().all())
+        return
+    s = q.double().transpose(0, 1) @ clean.double().repeat_interleave(H // Hkv, dim=1).permute(1, 2, 0) * 0.125
+    if lim is not None:
+        s.masked_fill_(torch.arange(T, device=DEV)[None, None] >= lim.long()[None, :, None], -inf)
+    ref = torch.softmax(s, -1).nan_to_num(0.0).mean((0, 1))
+    if what == "large logits":
+        # random roundings: the error of the sum over rows stays near 1e-6; one rounded log-sum-exp gave 4e-6 to 9e-6
+        assert float((score.double() - ref).norm() / ref.norm()) < 3e-6
+    else:
+        assert bool(((score.double() - ref).abs() <= 3e-5 * ref + 1e-12).all())
 
 
 def test_scores_of_64_wide_heads_on_many_streams():
