@@ -566,9 +566,9 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
         mx = fmaxf(mx, s_a[v >> 4][v & 15]);
       }
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = fmaxf(m_run, mx * k2);
+      const float m_new = fmaxf(m_run, mx);              // (unscaled here, so that the largest logit gives exactly 1)
       const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
+      const float alpha = __builtin_amdgcn_exp2f((m_run - m_use) * k2);
       m_run = m_new;
       l_run *= alpha;
 #pragma unroll
@@ -585,8 +585,8 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
 #pragma unroll
         for (int e = 0; e < 8; e += 2) {
           const int v = 8 * s + e, j = kv0 + 16 * s + 8 * (e >> 2) + 4 * hf + (e & 3);
-          const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_a[v >> 4][v & 15], k2, -m_use));
-          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_a[v >> 4][(v & 15) + 1], k2, -m_use));
+          const float p0 = __builtin_amdgcn_exp2f((s_a[v >> 4][v & 15] - m_use) * k2);
+          const float p1 = __builtin_amdgcn_exp2f((s_a[v >> 4][(v & 15) + 1] - m_use) * k2);
           l_run += p0;
           l_run += p1;
           pf[e >> 1] = cvt_pk_bf16(p0, p1);
@@ -632,7 +632,7 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
       const float w = oacc[dt][v] * den;
       return c == 0u ? w : c == 1u ? INFINITY : c == 2u ? -INFINITY : __builtin_nanf("");
     };
-    const float lse2 = l != 0.f ? m_run + log2f(l) : split ? -INFINITY : __builtin_nanf("");
+    const float lse2 = l != 0.f ? m_run * k2 + log2f(l) : split ? -INFINITY : __builtin_nanf("");
     if (split) store_split(x, lse2);
     else store_whole(x, lse2);
   }

@@ -375,7 +375,7 @@ def test_attention_of_64_wide_heads_infinite_values(T, n):
 
 
 @pytest.mark.parametrize("T,n", [(200, 40), (4099, 615)])      # whole row blocks; split ones
-@pytest.mark.parametrize("what", ["nan key", "nan values", "both infinities", "minus infinity", "large", "no weight"])
+@pytest.mark.parametrize("what", ["nan key", "nan values", "both infinities", "minus infinity", "large", "no weight", "huge logits"])
 def test_attention_of_64_wide_heads_special_values(T, n, what):
     """What a row does not see leaves no trace; what it sees gives NaN, an infinity or (large finite values) a finite
     number as the sum over its visible tokens does, and a NaN log-sum-exp where a logit is NaN."""
