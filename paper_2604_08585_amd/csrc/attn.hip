@@ -16,7 +16,7 @@
 // Heads of 64: the probabilities enter the second product as three bf16 terms that add up to the float, and the partial
 // outputs of split row blocks are fp32, so nothing between the operands and the stored result is rounded to bf16 (with two
 // terms 3.1 times as many results were not the bf16 nearest to the exact one as with float32 products: 3893 to 1237 of
-// 4.4 million; with three 723).  Rows that come out infinite or NaN are computed again in a second sweep over the same
+// 4.4 million; with three 642).  Rows that come out infinite or NaN are computed again in a second sweep over the same
 // tiles (see there).
 // Bound by the softmax arithmetic between the two products and by the splitting into terms.  615 rows x 32 heads over 4096
 // tokens: 1580 us with the generic kernel, 48.4 us here (41.7 with two terms); the whole layer 96.6 us (2074 before).
@@ -59,7 +59,8 @@ struct AttnArgs {
   int seg_tiles;         // key tiles per work unit; a row block with more tiles is split over units
   int n_seg_max;         // units per row block the grid provides
   void* part_o;          // [unit][128 rows][D] normalised partial outputs of split row blocks (AttnTile<D>::part_t)
-  float* part_lse;       // [unit][128 rows] log2-domain log-sum-exp of each partial (-inf: no visible key)
+  float* part_lse;       // [unit][128 rows] log2-domain log-sum-exp of each partial (-inf: no visible key); d = 64: pairs of
+                         // reference point (log2 units) and denominator against it
   int32_t* units;        // units[0] = number of work units, then (row block << 8 | segment), longest first (null: no plan)
   int32_t* blk_tiles;    // [row block] key tiles of the block, written by the plan kernel for the merge kernel (null: no plan)
 };
@@ -183,6 +184,15 @@ __device__ __forceinline__ u32x4 lds_read16(uint32_t lds_addr) {
   return *(const u32x4 __attribute__((address_space(3)))*)(uintptr_t)lds_addr;
 }
 
+// Log-sum-exp of logits whose maximum is m / kLog2e and whose sum against it is 2^lz.  EXACT (heads of 64): rounded once,
+// and with the reciprocal of the kLog2e that m was scaled by (as two floats), not with ln 2.
+template <bool EXACT>
+__device__ __forceinline__ float natural_lse(float m, float lz) {
+  if (!EXACT) return (m + lz) * kLn2;
+  if (m == -INFINITY) return m;
+  constexpr float lo = (float)(1.0 / (double)kLog2e - (double)kLn2);
+  return __builtin_fmaf(m, kLn2, __builtin_fmaf(m, lo, lz * kLn2));
+}
 // Second and third bf16 term of two probabilities whose first terms are `pk`: a float has 24 significant bits, each term
 // takes eight and the differences are exact, so the three terms add up to the float.
 __device__ __forceinline__ void split_rest(float p0, float p1, uint32_t pk, uint32_t& second, uint32_t& third) {
@@ -487,8 +497,8 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
   const int64_t part_row = (((int64_t)blk * a.Hkv + g) * a.n_seg_max + seg) * kRowsPerWg + r;    // of a split block
   typename C::part_t* part = static_cast<typename C::part_t*>(a.part_o) + part_row * D + 16 * hf;
   bf16_t* orow = static_cast<bf16_t*>(a.o) + (srow * a.H + head) * D + 16 * hf;
-  // x(dt, v): value of this lane's element 32 dt + 16 hf + v; lse in log2 units
-  auto store_split = [&](auto x, float lse2) {         // partial result of one key segment; merged by attn_merge_kernel
+  // x(dt, v): value of this lane's element 32 dt + 16 hf + v; m + log2(z): log2-sum-exp
+  auto store_split = [&](auto x, float m, float z) {         // partial result of one key segment; merged by attn_merge_kernel
 #pragma unroll
     for (int dt = 0; dt < C::DT; ++dt) {
       if constexpr (C::SPLIT_P) {
@@ -502,16 +512,19 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
                                                                cvt_pk_bf16(x(dt, h8 + 4), x(dt, h8 + 5)), cvt_pk_bf16(x(dt, h8 + 6), x(dt, h8 + 7)));
       }
     }
-    if (hf == 0) a.part_lse[part_row] = lse2;
+    if (hf == 0) {
+      if (C::SPLIT_P) reinterpret_cast<float2*>(a.part_lse)[part_row] = make_float2(m, z);
+      else a.part_lse[part_row] = m + log2f(z);
+    }
   };
-  auto store_whole = [&](auto x, float lse2) {
+  auto store_whole = [&](auto x, float m, float z) {
 #pragma unroll
     for (int dt = 0; dt < C::DT; ++dt)
 #pragma unroll
       for (int h8 = 0; h8 < 16; h8 += 8)
         *reinterpret_cast<u32x4*>(orow + 32 * dt + h8) = mk4(cvt_pk_bf16(x(dt, h8), x(dt, h8 + 1)), cvt_pk_bf16(x(dt, h8 + 2), x(dt, h8 + 3)),
                                                              cvt_pk_bf16(x(dt, h8 + 4), x(dt, h8 + 5)), cvt_pk_bf16(x(dt, h8 + 6), x(dt, h8 + 7)));
-    if (a.lse && hf == 0) a.lse[srow * a.H + head] = lse2 * kLn2;
+    if (a.lse && hf == 0) a.lse[srow * a.H + head] = natural_lse<C::SPLIT_P>(m, log2f(z));
   };
   bool bad = false;                                    // this row is computed again below
   if constexpr (C::SPLIT_P) {
@@ -526,11 +539,11 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
   }
   {
     auto x = [&](int dt, int v) { return oacc[dt][v] * inv; };
-    const float lse2 = l_tot > 0.f ? m_run + log2f(l_tot) : -INFINITY;
+    const float m = l_tot > 0.f ? m_run : -INFINITY, z = l_tot > 0.f ? l_tot : 1.f;
     if (split) {
-      if (!bad) store_split(x, lse2);
+      if (!bad) store_split(x, m, z);
     } else if (row_ok && !bad) {
-      store_whole(x, lse2);
+      store_whole(x, m, z);
     }
   }
   if constexpr (C::SPLIT_P) {
@@ -632,9 +645,9 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
       const float w = oacc[dt][v] * den;
       return c == 0u ? w : c == 1u ? INFINITY : c == 2u ? -INFINITY : __builtin_nanf("");
     };
-    const float lse2 = l != 0.f ? m_run * k2 + log2f(l) : split ? -INFINITY : __builtin_nanf("");
-    if (split) store_split(x, lse2);
-    else store_whole(x, lse2);
+    const float m = l != 0.f ? m_run * k2 : split ? -INFINITY : __builtin_nanf(""), z = l != 0.f ? l : 1.f;
+    if (split) store_split(x, m, z);
+    else store_whole(x, m, z);
   }
 }
 
@@ -750,7 +763,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   const int head = g * a.G + r % a.G;
   // unit (blk, g, seg) wrote slot ((blk * Hkv + g) * n_seg_max + seg)
   const int64_t slot0 = ((int64_t)blk * a.Hkv + g) * a.n_seg_max;
-  const float* pl = a.part_lse + slot0 * kRowsPerWg + r;
+  constexpr int PL = AttnTile<D>::SPLIT_P ? 2 : 1;   // floats per row
+  const float* pl = a.part_lse + (slot0 * kRowsPerWg + r) * PL;
   const part_t* po = static_cast<const part_t*>(a.part_o) + (slot0 * kRowsPerWg + r) * D + 8 * ch;
   // four segments at a time: every load first, then the running maximum, the weights and the weighted sum
   constexpr bool SPLIT_P = AttnTile<D>::SPLIT_P;
@@ -758,12 +772,13 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   float mx = -INFINITY, wsum = 0.f;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int sg0 = 0; sg0 < n_seg; sg0 += 4) {
-    float l[4];
+    float l[4], z[4];
     u32x4 raw[4][sizeof(part_t) / 2];               // 8 elements
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const bool ok = row_ok && sg0 + u < n_seg;
-      l[u] = ok ? pl[(int64_t)(sg0 + u) * kRowsPerWg] : -INFINITY;
+      l[u] = ok ? pl[(int64_t)(sg0 + u) * kRowsPerWg * PL] : -INFINITY;
+      z[u] = !SPLIT_P || !ok ? 1.f : pl[(int64_t)(sg0 + u) * kRowsPerWg * PL + 1];
 #pragma unroll
       for (int w = 0; w < (int)sizeof(part_t) / 2; ++w)
         raw[u][w] = ok ? *reinterpret_cast<const u32x4*>(po + (int64_t)(sg0 + u) * kRowsPerWg * D + w * Elem<part_t>::kVec) : u32x4{0u, 0u, 0u, 0u};
@@ -772,7 +787,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       mn = fmaxf(mn, l[u]);
-      nan |= l[u] != l[u];
+      nan |= z[u] != z[u];
     }
     if (mn > -INFINITY) {
       const float resc = __builtin_amdgcn_exp2f(mx - mn);        // 0 while nothing was visible so far
@@ -781,7 +796,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
       for (int e = 0; e < 8; ++e) acc[e] = weighted<SPLIT_P>(resc, acc[e]);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const float w = __builtin_amdgcn_exp2f(l[u] - mn);        // 0 for a segment that saw nothing
+        float w = __builtin_amdgcn_exp2f(l[u] - mn);              // 0 for a segment that saw nothing
+        if (SPLIT_P) w *= z[u];
         float f[8];
 #pragma unroll
         for (int w = 0; w < (int)sizeof(part_t) / 2; ++w) Vec16<part_t>::unpack(raw[u][w], f + w * Elem<part_t>::kVec);
@@ -795,7 +811,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] *= inv;
-  float lse = wsum > 0.f ? (mx + log2f(wsum)) * kLn2 : -INFINITY;
+  float lse = wsum > 0.f ? natural_lse<SPLIT_P>(mx, log2f(wsum)) : -INFINITY;
   if constexpr (SPLIT_P) {
     if (row_ok && !nan && wsum == 0.f) {            // no weight although tokens are visible
       const int64_t c0 = min(max(a.ctx_off[b], (int64_t)0), a.total_ctx);
@@ -834,8 +850,8 @@ size_t part_o_bytes(int D, int64_t n_blocks, int n_seg_max) {
   const size_t row = D == 128 ? 128 * sizeof(AttnTile<128>::part_t) : 64 * sizeof(AttnTile<64>::part_t);
   return align_up((size_t)n_blocks * n_seg_max * kRowsPerWg * row, 256);
 }
-size_t part_lse_bytes(int64_t n_blocks, int n_seg_max) {
-  return align_up((size_t)n_blocks * n_seg_max * kRowsPerWg * sizeof(float), 256);
+size_t part_lse_bytes(int D, int64_t n_blocks, int n_seg_max) {
+  return align_up((size_t)n_blocks * n_seg_max * kRowsPerWg * (D == 128 ? 1 : 2) * sizeof(float), 256);
 }
 size_t units_bytes(int64_t n_row_blocks, int n_seg_max) {
   return align_up((size_t)(n_row_blocks * n_seg_max + 1) * sizeof(int32_t), 256);
@@ -873,7 +889,7 @@ size_t attn_workspace(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int
   const int64_t n_blocks = ((total_sel + BR - 1) / BR + B) * L.n_kv_heads;
   const Split sp = choose_split(L.head_dim, n_blocks, total_ctx);
   if (sp.n_seg_max <= 1) return 0;
-  return part_o_bytes(L.head_dim, n_blocks, sp.n_seg_max) + part_lse_bytes(n_blocks, sp.n_seg_max) +
+  return part_o_bytes(L.head_dim, n_blocks, sp.n_seg_max) + part_lse_bytes(L.head_dim, n_blocks, sp.n_seg_max) +
          units_bytes(n_blocks / L.n_kv_heads, sp.n_seg_max) + blk_tiles_bytes(n_blocks / L.n_kv_heads);
 }
 
@@ -911,7 +927,7 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
       // not matter, and the launch is saved: 110 rows over 731 tokens 22.3 -> 19.0 us, 40 rows over 8192 30.4 -> 23.5.
       if (nb * a.Hkv * sp.n_seg_max > resident_workgroups(a.D)) {
         a.units = reinterpret_cast<int32_t*>(w + part_o_bytes(L.head_dim, nb * a.Hkv, sp.n_seg_max) +
-                                             part_lse_bytes(nb * a.Hkv, sp.n_seg_max));
+                                             part_lse_bytes(L.head_dim, nb * a.Hkv, sp.n_seg_max));
         a.blk_tiles = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(a.units) + units_bytes(nb, sp.n_seg_max));
       }
     }
