@@ -19,7 +19,7 @@
 // 4.4 million; with three 642).  Rows that come out infinite or NaN are computed again in a second sweep over the same
 // tiles (see there).
 // Bound by the softmax arithmetic between the two products and by the splitting into terms.  615 rows x 32 heads over 4096
-// tokens: 1580 us with the generic kernel, 48.4 us here (41.7 with two terms); the whole layer 96.6 us (2074 before).
+// tokens: 1580 us with the generic kernel, 48.0 us here (41.7 with two terms); the whole layer 96.6 us (2074 before).
 //
 // Generic path (f32, or other shapes): one workgroup per (row, head), online softmax over
 // 256-token tiles.  Bound by the latency of its key and value loads (77 rows x 4 heads over 512 tokens in f32: 39 us with
