@@ -29,6 +29,9 @@ EXPORTS = [
 # declared in qcf_ffn.h
 FFN_EXPORTS = ["qcf_linear_swiglu_workspace_bytes", "qcf_linear_swiglu"]
 
+# declared in qcf_layers.h
+LAYERS_EXPORTS = ["qcf_score_layers_workspace_bytes", "qcf_score_layers"]
+
 
 class QcfError(RuntimeError):
     pass
@@ -107,6 +110,11 @@ def load_library() -> C.CDLL:
     lib.qcf_linear_swiglu_workspace_bytes.argtypes = [dp, i64, i32, i32]
     lib.qcf_linear_swiglu.restype = C.c_int
     lib.qcf_linear_swiglu.argtypes = [dp, vp, i64, i32, vp, i32, vp, vp, sz, vp]
+    pp = C.POINTER(vp)
+    lib.qcf_score_layers_workspace_bytes.restype = sz
+    lib.qcf_score_layers_workspace_bytes.argtypes = [dp, i32, i32, i64, i64]
+    lib.qcf_score_layers.restype = C.c_int
+    lib.qcf_score_layers.argtypes = [dp, i32, i32, pp, vp, i64, pp, vp, i64, vp, C.POINTER(C.c_float), vp, vp, sz, vp]
     lib.qcf_key_norm.restype = C.c_int
     lib.qcf_key_norm.argtypes = [dp, vp, i64, vp, vp]
     lib.qcf_gather.restype = C.c_int
@@ -207,6 +215,23 @@ def qcf_score_accumulate(desc: LayerDesc, B: int, q_probe: torch.Tensor, probe_o
     _check(lib.qcf_score_accumulate(C.byref(desc), B, _ptr(q_probe), _ptr(probe_off), total_probe, _ptr(k_fused),
                                     _ptr(ctx_off), total_ctx, _ptr(probe_limit), float(alpha), float(beta),
                                     _ptr(score), wp, wn, _stream()))
+
+
+def qcf_score_layers(desc: LayerDesc, B: int, q_probe: Sequence[torch.Tensor], probe_off: torch.Tensor, total_probe: int,
+                     k_fused: Sequence[torch.Tensor], ctx_off: torch.Tensor, total_ctx: int,
+                     probe_limit: Optional[torch.Tensor], weights: Sequence[float], score: torch.Tensor,
+                     workspace: Optional[torch.Tensor] = None) -> None:
+    """score = sum over layers of weights[l] * (mean attention of layer l's probe rows over its keys)."""
+    lib = load_library()
+    n = len(weights)
+    if workspace is None:
+        workspace = _workspace(int(lib.qcf_score_layers_workspace_bytes(C.byref(desc), n, B, total_probe, total_ctx)),
+                               score.device)
+    wp, wn = _ws_args(workspace)
+    q = (C.c_void_p * n)(*[_ptr(q_probe[l]) for l in range(n)])
+    k = (C.c_void_p * n)(*[_ptr(k_fused[l]) for l in range(n)])
+    _check(lib.qcf_score_layers(C.byref(desc), n, B, q, _ptr(probe_off), total_probe, k, _ptr(ctx_off), total_ctx,
+                                _ptr(probe_limit), (C.c_float * n)(*weights), _ptr(score), wp, wn, _stream()))
 
 
 def qcf_score_static(desc: LayerDesc, B: int, q_probe: torch.Tensor, probe_off: torch.Tensor, total_probe: int,

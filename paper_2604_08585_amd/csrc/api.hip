@@ -201,6 +201,31 @@ qcf_status qcf_score_accumulate(const qcf_layer_desc* desc, int32_t B, const voi
                       probe_limit_dev, score, alpha, beta, workspace, (hipStream_t)stream);
 }
 
+size_t qcf_score_layers_workspace_bytes(const qcf_layer_desc* desc, int32_t n_layers, int32_t B, int64_t total_probe,
+                                        int64_t total_ctx) {
+  if (check_desc(desc) != QCF_OK || n_layers <= 0 || B <= 0 || total_probe <= 0 || total_ctx <= 0) return 0;
+  return score_layers_workspace(*desc, n_layers, B, total_probe, total_ctx);
+}
+
+qcf_status qcf_score_layers(const qcf_layer_desc* desc, int32_t n_layers, int32_t B, const void* const* q_probe,
+                            const int64_t* probe_off_dev, int64_t total_probe, const void* const* k_fused,
+                            const int64_t* ctx_off_dev, int64_t total_ctx, const int32_t* probe_limit_dev,
+                            const float* weights, float* score, void* workspace, size_t workspace_bytes, void* stream) {
+  if (n_layers < 1) return fail(QCF_ERR_INVALID_ARG, "n_layers %d < 1", n_layers);
+  if (!q_probe || !k_fused || !weights) return fail(QCF_ERR_INVALID_ARG, "q_probe, k_fused or weights is NULL");
+  bool empty = false;
+  for (int32_t l = 0; l < n_layers; ++l) {
+    QCF_TRY(check_score_args(desc, B, q_probe[l], probe_off_dev, total_probe, k_fused[l], ctx_off_dev, total_ctx,
+                             probe_limit_dev, score, &empty));
+    if (!std::isfinite(weights[l])) return fail(QCF_ERR_INVALID_ARG, "weights must be finite");
+  }
+  if (empty) return QCF_OK;
+  QCF_TRY(need_ws(workspace, workspace_bytes,
+                  total_probe > 0 ? score_layers_workspace(*desc, n_layers, B, total_probe, total_ctx) : 0));
+  return launch_score_layers(*desc, n_layers, B, q_probe, probe_off_dev, total_probe, k_fused, ctx_off_dev, total_ctx,
+                             probe_limit_dev, weights, score, workspace, (hipStream_t)stream);
+}
+
 // ---- select ---------------------------------------------------------------------
 size_t qcf_select_workspace_bytes(int32_t B, int64_t total_ctx) {
   if (B <= 0 || total_ctx <= 0) return 0;

@@ -10,6 +10,7 @@
 
 #include "qcf.h"
 #include "qcf_ffn.h"
+#include "qcf_layers.h"
 
 namespace qcf {
 
@@ -158,15 +159,17 @@ __device__ __forceinline__ void load_to_lds_at(const void* base, uint32_t lane_o
                : "v"(lane_off), "s"(sb), "s"(lds_addr)
                : "memory");
 }
-// Form 2: a full 64-bit address per lane.
-__device__ __forceinline__ void load_to_lds_addr(const void* gptr, void* lds) {
-  const uint32_t lds_addr = __builtin_amdgcn_readfirstlane((int)lds_offset_of(lds));
+// Form 2: a full 64-bit address per lane; the LDS destination as a pointer or as a byte address.
+__device__ __forceinline__ void load_to_lds_addr_at(const void* gptr, uint32_t lds_addr_in) {
+  const uint32_t lds_addr = __builtin_amdgcn_readfirstlane((int)lds_addr_in);
   uint32_t saved_m0;
   asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
                : "=&s"(saved_m0)
                : "v"(gptr), "s"(lds_addr)
                : "memory");
 }
+
+__device__ __forceinline__ void load_to_lds_addr(const void* gptr, void* lds) { load_to_lds_addr_at(gptr, lds_offset_of(lds)); }
 
 // Form 1 without the compiler-level memory fence (ordinary LDS accesses may be scheduled across it: for loops that
 // interleave these loads with fragment reads of another stage and order everything with their own waits and
@@ -198,6 +201,12 @@ size_t score_workspace(const qcf_layer_desc& L, int32_t B, int64_t total_probe, 
 qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const int64_t* probe_off,
                         int64_t total_probe, const void* k, const int64_t* ctx_off, int64_t total_ctx,
                         const int32_t* probe_limit, float* score, float alpha, float beta, void* ws, hipStream_t st);
+
+size_t score_layers_workspace(const qcf_layer_desc& L, int32_t n_layers, int32_t B, int64_t total_probe, int64_t total_ctx);
+qcf_status launch_score_layers(const qcf_layer_desc& L, int32_t n_layers, int32_t B, const void* const* q,
+                               const int64_t* probe_off, int64_t total_probe, const void* const* k, const int64_t* ctx_off,
+                               int64_t total_ctx, const int32_t* probe_limit, const float* weights, float* score, void* ws,
+                               hipStream_t st);
 
 size_t select_workspace(int32_t B, int64_t total_ctx);
 qcf_status launch_select(int32_t B, const float* score, const int64_t* ctx_off, int64_t total_ctx,

@@ -2,17 +2,24 @@
 // selector of the paper): score[j] = mean over probe rows and heads of the softmax
 // attention the context token j receives.
 //
-// bf16 / head_dim 128 and 64 path (the dense contraction runs on MFMA).  A workgroup of twelve waves owns a
-// 256-token tile of one KV head: the tile's keys and the group's probe rows both arrive in LDS through
-// asynchronous loads that request every 128-byte line once (loading keys straight into registers in MFMA
+// bf16 / head_dim 128 and 64 path (the dense contraction runs on MFMA).  A workgroup of twelve waves takes a unit of
+// 256-token tiles of one KV head: the group's probe rows arrive in LDS once per unit, the keys of one tile after the
+// other, through asynchronous loads that request every 128-byte line once (loading keys straight into registers in MFMA
 // operand layout touches 64 different lines per instruction, which is what bounded the earlier version);
-// wave (tw, rg) keeps the 64 tokens of slice tw in registers and takes every third 32-row tile of the rows.
-//   pass 1  logits of the probe rows against the tile -> per-row (max, sum-exp) of the tile, in the log2
+// wave (tw, rg) keeps the 64 tokens of slice tw in registers and takes every third 32-row tile of the rows.  The keys of
+// the next tile travel while the current one is used.
+//   pass 1  logits of the probe rows against the tiles -> per-row (max, sum-exp) of the unit, in the log2
 //           domain (the four token slices folded in LDS);
-//   pass 2  every workgroup first folds the partials of its group's rows over the request's tiles into
-//           a log2-sum-exp per row (in a fixed order, so all workgroups get the same value); logits
-//           again, p = exp2(logit - lse), summed over the rows of the group -> per-KV-head column sums;
-//   reduce  fixed-order sum over KV heads, times 1/(R*H).
+//   pass 2  every workgroup first folds the partials of its group's rows over the request's units into
+//           a maximum and a sum per row (in a fixed order, so all workgroups get the same values); logits
+//           again, p = exp2(logit - max) / sum, summed over the rows of the group -> per-KV-head column sums;
+//   reduce  fixed-order sum over KV heads, times 1/(R*H), and over layers where several are scored at once.
+// Bound by the exponentials and what goes with them (about 205 vector instructions, 1200 cycles of a SIMD, per 64 tokens x
+// 32 rows and pass, against 512 of MFMAs) and, with few probe rows, by the keys: 8 layers, 48 rows x 32 heads over 6001
+// tokens 170 us in eight launches of the single kernel below, 36 + 36 + 5 us here, where the loads alone take 21 + 22; 80
+// rows x 64 heads over 32768 tokens 85 + 149 us with one tile to a workgroup, whose every workgroup of pass 2 folded 128
+// partials per row, 67 + 71 here.  A wave's next MFMAs between the exponentials of its last rows (two waves to a SIMD, no
+// registers for a third): 77 + 82.
 // Launches that are resident at once (one workgroup per compute unit at most, up to 320 probe rows per KV
 // group) take a single kernel instead (score_fused, further down): the exponentials of pass 1 stay in registers
 // across a grid-wide exchange of the per-row partials, so the keys are read once and no second pass or reduce
@@ -129,7 +136,7 @@ __global__ __launch_bounds__(kColThreads) void score_colmean_generic(
 
 constexpr int kTokPerWave = 64;                 // tokens a wave keeps stationary in registers
 constexpr int kTokWaves = 4;                    // token slices of a workgroup
-constexpr int kRowGroups = 3;                   // waves per token slice; they share out the row tiles
+constexpr int kRowGroups = 3;                   // waves per token slice, which share a SIMD and share out the row tiles
 constexpr int kWavesPerWg = kTokWaves * kRowGroups;
 constexpr int kThreads = 64 * kWavesPerWg;
 constexpr int kTokPerWg = kTokPerWave * kTokWaves;
@@ -148,17 +155,18 @@ template <int D> __device__ __forceinline__ int staged_elem(int r, int lane) { r
 // byte offset of this lane's fragment (row lane%32, chunk 2*ks + lane/32) is frag_base ^ (32 * ks)
 template <int D> __device__ __forceinline__ int frag_base(int lane) { return (lane & 31) * 2 * D + slot_of<D>(lane >> 5, lane & 31) * 16; }
 constexpr int kFoldBatch = 16;
-// Heads of 64 keep a row's maximum and the reciprocal of its sum apart instead of one log-sum-exp, whose rounding weighs
-// once logits reach a hundred (largest logit 586: 8.7e-6 off in the 2-norm, now 1.7e-6, the general kernels 1.9e-6; largest 12: 1.6e-7, 8.3e-8, 5.3e-7), and
-// a NaN in either reaches every token that the row sees.  The maximum is that of the unscaled logits and is taken off
-// before they are scaled, so that the largest one gives exactly 1 at any magnitude.
+constexpr int kMaxLayers = 16;                  // layers scored by one set of launches
+// The passes keep a row's maximum and the reciprocal of its sum apart instead of one log-sum-exp, whose rounding weighs
+// once logits reach a hundred (heads of 64, largest logit 586: 8.7e-6 off in the 2-norm, now 1.7e-6, the general kernels
+// 1.9e-6; largest 12: 1.6e-7, 8.3e-8, 5.3e-7; heads of 128, 80 rows over 32768 tokens: 1.9e-7, 7.0e-8).  Heads of 64: a NaN
+// in either reaches every token that the row sees, the maximum is that of the unscaled logits and is taken off before they
+// are scaled, so that the largest one gives exactly 1 at any magnitude.
 template <int D> constexpr bool kPairs = D == 64;
 template <int D> constexpr float kMaxScale = kPairs<D> ? kK2<D> : 1.f;      // from a kept maximum to log2 units
 template <int D> __device__ __forceinline__ float exp_of(float logit, float m) {
   if (kPairs<D>) return __builtin_amdgcn_exp2f((logit - m) * kK2<D>);
   return __builtin_amdgcn_exp2f(__builtin_fmaf(logit, kK2<D>, -m));
 }
-template <int D> constexpr size_t kRowWords = kPairs<D> ? 3 : 2;       // words of LDS per staged row in pass 2
 
 struct ScoreArgs {
   const bf16_t* q;            // [total_probe, H, D]
@@ -168,15 +176,16 @@ struct ScoreArgs {
   const int32_t* probe_limit;
   int64_t total_probe, total_ctx;
   int B, H, Hkv, G;
-  float2* part;               // [n_tiles][total_probe * H] (max2, sumexp2) per 256-token tile
-  float* colsum;              // [Hkv][total_ctx]
+  float2* part;               // [layer][unit][total_probe * H] (max2, sumexp2) per unit of tiles
+  float* colsum;              // [layer][Hkv][total_ctx]
   float* score;
   float alpha, beta;          // score = beta * score + alpha * (this call's mean attention); beta == 0: plain store
 };
 
-// the one place a score is written: plain store, or blended into what is there (accumulation over layers)
+// plain store, or blended into what is there (accumulation over layers)
+__device__ __forceinline__ float blended(float beta, float old, float s) { return (beta == 0.f) ? s : __builtin_fmaf(beta, old, s); }
 __device__ __forceinline__ void write_score(const ScoreArgs& a, int64_t j, float s) {
-  a.score[j] = (a.beta == 0.f) ? a.alpha * s : __builtin_fmaf(a.beta, a.score[j], a.alpha * s);
+  a.score[j] = blended(a.beta, (a.beta == 0.f) ? 0.f : a.score[j], a.alpha * s);
 }
 
 // Maps a workgroup index (= tile number over all requests) to (request, first token of its 256-token
@@ -200,16 +209,68 @@ __device__ __forceinline__ bool locate_tile(const ScoreArgs& a, int wg, int& b, 
   return false;
 }
 
-// Stages the workgroup's 256 key rows (tokens tile_tok0 .. +255 of KV head g) into LDS with asynchronous
-// direct-to-LDS loads (1 KB per instruction, every 128-byte line requested once); same row
-// layout as the probe rows below.  Tokens past the end are clamped (masked or never written later).
+// Brings the 256 key rows of a tile (tokens 256 * tile .. + 255 of KV head g) into LDS with asynchronous direct-to-LDS
+// loads (1 KB per instruction, every 128-byte line requested once); same row layout as the probe rows below.  Tokens past
+// the end of the request are clamped (masked or never written later).
 template <int D>
-__device__ __forceinline__ void stage_k_async(const ScoreArgs& a, int64_t c0, int T, int tile_tok0, int g,
-                                              unsigned char* sK, int wave, int lane) {
-  for (int j = wave; j < kTokPerWg / kRowsPerLoad<D>; j += kWavesPerWg) {
-    const int r = staged_row<D>(j, lane);
-    const int tok = min(tile_tok0 + r, T - 1);
-    load_to_lds_addr(a.k + ((c0 + tok) * a.Hkv + g) * D + staged_elem<D>(r, lane), sK + j * 1024);
+struct KeyLoader {
+  static constexpr int kLoads = kTokPerWg / kRowsPerLoad<D>;     // of the workgroup, per tile
+  static constexpr int kStep = kRowsPerLoad<D> * kWavesPerWg;    // rows between those of a wave (the slots repeat)
+  const char* base;                  // head g of the request's first token
+  uint32_t row_bytes, row0, chunk, lds;
+  int T;
+  __device__ __forceinline__ KeyLoader(const bf16_t* head, int Hkv, int T_, uint32_t lds_k, int wave, int lane)
+      : base(reinterpret_cast<const char*>(head)), row_bytes((uint32_t)Hkv * D * 2), row0((uint32_t)staged_row<D>(wave, lane)),
+        chunk((uint32_t)staged_elem<D>((int)row0, lane) * 2), lds(lds_k + (uint32_t)wave * 1024), T(T_) {
+    static_assert(kStep % 16 == 0, "rows kStep apart have the same slots");
+  }
+  __device__ __forceinline__ void load(int tile, int wave) const {
+    const char* src = base + (int64_t)tile * kTokPerWg * row_bytes;
+    const bool whole = tile * kTokPerWg + kTokPerWg <= T;
+#pragma unroll
+    for (int i = 0; i * kWavesPerWg < kLoads; ++i) {
+      if ((i + 1) * kWavesPerWg > kLoads && i * kWavesPerWg + wave >= kLoads) break;
+      const uint32_t row = row0 + (uint32_t)(kStep * i), dst = lds + (uint32_t)i * kWavesPerWg * 1024;
+      if (whole) load_to_lds_at(src + (int64_t)(kStep * i) * row_bytes, row0 * row_bytes + chunk, dst);
+      else load_to_lds_at(src, min(row, (uint32_t)(T - 1 - tile * kTokPerWg)) * row_bytes + chunk, dst);
+    }
+  }
+};
+
+// Key fragments of a wave's 64 tokens, from the first of their staged rows.
+template <int D>
+__device__ __forceinline__ void load_key_frags(const unsigned char* rows, int qb0, bf16x8 (&kf)[2][D / 16]) {
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks)
+      kf[mt][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(rows + 32 * mt * (2 * D) + (qb0 ^ (32 * ks))));
+}
+
+// Logits of a wave's 64 tokens (key fragments kf) against the 32 staged probe rows at `rows` (LDS address of this lane's
+// first fragment): the row fragments are requested up to four k-steps ahead of the MFMAs that use them.  TOKENS_FIRST: the
+// result's rows are tokens (A = keys) and its columns probe rows (B = queries), else the other way round.
+template <int D, bool TOKENS_FIRST>
+__device__ __forceinline__ void logit_tile(const bf16x8 (&kf)[2][D / 16], uint32_t rows, floatx16& acc0, floatx16& acc1) {
+  constexpr int KS = D / 16;
+  auto read = [&](int ks) { return *(const u32x4 __attribute__((address_space(3)))*)(uintptr_t)(rows ^ (uint32_t)(32 * ks)); };
+  u32x4 ring[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) ring[i] = read(i);
+  acc0 = floatx16{0};
+  acc1 = floatx16{0};
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    __builtin_amdgcn_sched_barrier(0);
+    const bf16x8 qf = __builtin_bit_cast(bf16x8, ring[ks & 3]);
+    if (TOKENS_FIRST) {
+      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][ks], qf, acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][ks], qf, acc1, 0, 0, 0);
+    } else {
+      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, kf[0][ks], acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, kf[1][ks], acc1, 0, 0, 0);
+    }
+    if (ks + 4 < KS) ring[ks & 3] = read(ks + 4);
   }
 }
 
@@ -217,95 +278,161 @@ __device__ __forceinline__ void stage_k_async(const ScoreArgs& a, int64_t c0, in
 // head g*G + hh) into LDS with asynchronous direct-to-LDS loads; the caller waits and synchronises.
 // Rows up to the next multiple of 32 are filled with a copy of the last row (never used in a result).
 template <int D>
-__device__ __forceinline__ void stage_q_async(const ScoreArgs& a, int64_t p0, int g, int r_begin, int n_rows,
-                                              int n_rows_pad, unsigned char* sQ, int wave, int lane) {
+__device__ __forceinline__ void stage_q_async(const ScoreArgs& a, const bf16_t* q, int64_t p0, int g, int r_begin, int n_rows,
+                                              int n_rows_pad, uint32_t sQ, int wave, int lane) {
   for (int j = wave; j < n_rows_pad / kRowsPerLoad<D>; j += kWavesPerWg) {
     const int r = staged_row<D>(j, lane);
     const int rr = r_begin + min(r, n_rows - 1);
     const int i = rr / a.G, hh = rr - i * a.G;
-    load_to_lds_addr(a.q + ((p0 + i) * a.H + g * a.G + hh) * D + staged_elem<D>(r, lane), sQ + j * 1024);
+    load_to_lds_addr_at(q + ((p0 + i) * a.H + g * a.G + hh) * D + staged_elem<D>(r, lane), sQ + j * 1024);
   }
 }
 
-// Pass 1.  A workgroup = (256-token tile, KV head); wave (tw, rg) keeps the 64 tokens of slice tw in
-// registers and takes every third 32-row tile of the staged probe rows, starting with tile rg.
+// exchange between the two 32-lane halves of a wave (one vector instruction, no LDS round trip):
+// returns the value the lane 32 away holds
+__device__ __forceinline__ float other_half(float x) {
+  typedef unsigned u2v __attribute__((ext_vector_type(2)));
+  const u2v r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  // r.x = (lower half's value in both halves), r.y = (upper half's value in both halves)
+  return (threadIdx.x & 32) ? __uint_as_float(r.x) : __uint_as_float(r.y);
+}
+// Both passes run over a set of layers at once (qcf_score_layers; one layer otherwise).  A workgroup takes the
+// (up to unit_tiles) 256-token tiles of one unit of one request, for one KV head of one layer: the probe rows are
+// staged once per unit, and the keys of the next tile travel while the current one, already in registers, is used.
+struct PassArgs {
+  ScoreArgs s;                       // (s.q, s.k and s.alpha belong to layer 0; the arrays below are used)
+  const bf16_t* q[kMaxLayers];
+  const bf16_t* k[kMaxLayers];
+  float alpha[kMaxLayers];
+  int n_layers;
+  int unit_tiles;                    // most tiles of a unit
+  int n_units;                       // units the grid provides (upper bound on the units of all requests)
+};
+struct Unit {
+  int layer, g, b, T;
+  int64_t c0;
+  int tile0, tile1;                  // tiles of the request
+  int64_t slot;                      // this unit's partials
+  int64_t slot_first;                // partials of the request's first unit, and how many units it has
+  int n_units;
+};
+// The tiles of a request are dealt evenly to its units.  Consecutive workgroups take the KV heads in turn, so that with
+// eight of them the units of a head, which read the same probe rows, share an XCD.
+__device__ __forceinline__ bool locate_unit(const PassArgs& a, Unit& u) {
+  const ScoreArgs& s = a.s;
+  u.g = (int)(blockIdx.x % (unsigned)s.Hkv);
+  const int rest = (int)(blockIdx.x / (unsigned)s.Hkv);
+  u.layer = rest % a.n_layers;
+  int idx = rest / a.n_layers, first = 0;
+  for (u.b = 0; u.b < s.B; ++u.b) {
+    u.c0 = min(max(s.ctx_off[u.b], (int64_t)0), s.total_ctx);
+    const int64_t c1 = min(max(s.ctx_off[u.b + 1], u.c0), s.total_ctx);
+    u.T = (int)(c1 - u.c0);
+    const int nt = (u.T + kTokPerWg - 1) / kTokPerWg;
+    u.n_units = (nt + a.unit_tiles - 1) / a.unit_tiles;
+    if (idx < u.n_units) {
+      u.tile0 = (int)((int64_t)idx * nt / u.n_units);
+      u.tile1 = (int)((int64_t)(idx + 1) * nt / u.n_units);
+      u.slot_first = (int64_t)u.layer * a.n_units + first;
+      u.slot = u.slot_first + idx;
+      return true;
+    }
+    idx -= u.n_units;
+    first += u.n_units;
+  }
+  return false;
+}
+
+constexpr int kTilesPerWave = (kRowBlock / 32 + kRowGroups - 1) / kRowGroups;      // row tiles of a wave, at most
+
+// Pass 1.  Wave (tw, rg) keeps the 64 tokens of slice tw in registers and takes every third 32-row tile of the staged
+// probe rows, starting with tile rg; a lane keeps the running (max, sum-exp) of its rows over the unit's tiles.
 template <int D, bool LIMIT>
-__global__ __launch_bounds__(kThreads) void score_pass1(ScoreArgs a) {
+__global__ __launch_bounds__(kThreads) void score_pass1(PassArgs pa) {
+  const ScoreArgs& a = pa.s;
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* sK = smem + kQBytes<D>;
   float2* sPart = reinterpret_cast<float2*>(smem + kQBytes<D> + kKBytes<D>);     // [kTokWaves][kRowBlock]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tw = wave % kTokWaves, rg = wave / kTokWaves;
-  const int g = blockIdx.y;
-  int b, T, tile_tok0, tile_first;
-  int64_t c0;
-  if (!locate_tile(a, blockIdx.x, b, c0, T, tile_tok0, tile_first)) return;
-  const int64_t p0 = min(max(a.probe_off[b], (int64_t)0), a.total_probe);
-  const int64_t p1 = min(max(a.probe_off[b + 1], p0), a.total_probe);
+  const uint32_t lds0 = lds_offset_of(smem);
+  Unit u;
+  if (!locate_unit(pa, u)) return;
+  const int64_t p0 = min(max(a.probe_off[u.b], (int64_t)0), a.total_probe);
+  const int64_t p1 = min(max(a.probe_off[u.b + 1], p0), a.total_probe);
   const int rows = (int)(p1 - p0) * a.G;         // probe rows x heads of the group
   if (rows == 0) return;
-  const int tok0 = tile_tok0 + tw * kTokPerWave;
-  const bool wave_active = tok0 < T;
+  const bf16_t* q = pa.q[u.layer];
+  const KeyLoader<D> keys(pa.k[u.layer] + (u.c0 * a.Hkv + u.g) * D, a.Hkv, u.T, lds0 + (uint32_t)kQBytes<D>, wave, lane);
   const int qb0 = frag_base<D>(lane);
-  float2* part = a.part + (int64_t)blockIdx.x * (a.total_probe * a.H);
+  float2* part = a.part + u.slot * (a.total_probe * a.H);
 
-  stage_k_async<D>(a, c0, T, tile_tok0, g, sK, wave, lane);
-  bf16x8 kf[2][D / 16];
   for (int r_begin = 0; r_begin < rows; r_begin += kRowBlock) {
     const int n_rows = min(kRowBlock, rows - r_begin);
     const int n_pad = (n_rows + 31) & ~31;
     __syncthreads();                        // the previous block's rows and partials are no longer read
-    stage_q_async<D>(a, p0, g, r_begin, n_rows, n_pad, smem, wave, lane);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (r_begin == 0) {
+    stage_q_async<D>(a, q, p0, u.g, r_begin, n_rows, n_pad, lds0, wave, lane);
+    keys.load(u.tile0, wave);
+    float m_run[kTilesPerWave], z_run[kTilesPerWave];      // lane's row: r_begin + 32 (rg + 3 i) + lane%32
+    int lim[kTilesPerWave];
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks)
-          kf[mt][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(
-                                                      sK + (kTokPerWave * tw + 32 * mt) * (2 * D) + (qb0 ^ (32 * ks))));
+    for (int i = 0; i < kTilesPerWave; ++i) {
+      m_run[i] = -INFINITY;
+      z_run[i] = 0.f;
+      lim[i] = u.T;
+      const int r = r_begin + 32 * (rg + kRowGroups * i) + (lane & 31);
+      if (LIMIT && r < r_begin + n_rows) lim[i] = min(u.T, max(0, a.probe_limit[p0 + r / a.G]));
     }
-    for (int rt = 32 * rg; rt < n_pad; rt += 32 * kRowGroups) {
-      float mx = -INFINITY, sum = 0.f;
-      if (wave_active) {
-        floatx16 acc0 = {0}, acc1 = {0};
-        const unsigned char* qrow = smem + rt * (2 * D);
+    for (int tile = u.tile0; tile < u.tile1; ++tile) {
+      const int tok0 = tile * kTokPerWg + tw * kTokPerWave;
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();                      // the tile's keys (and the rows) have landed
+      bf16x8 kf[2][D / 16];
+      load_key_frags<D>(sK + kTokPerWave * tw * (2 * D), qb0, kf);
+      __syncthreads();                      // every wave has its keys
+      if (tile + 1 < u.tile1) keys.load(tile + 1, wave);
+      if (tok0 >= u.T) continue;
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) {
-          const bf16x8 qf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qrow + (qb0 ^ (32 * ks))));
-          // S^T tile: rows = tokens (A = keys), columns = probe rows (B = queries)
-          acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][ks], qf, acc0, 0, 0, 0);
-          acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][ks], qf, acc1, 0, 0, 0);
-        }
-        // lane owns probe row rt + lane%32; its registers hold tokens 8*(v/4) + 4*(lane/32) + v%4
-        const int r = r_begin + rt + (lane & 31);
-        int lim = T;
-        if (LIMIT && r < rows) lim = min(T, max(0, a.probe_limit[p0 + r / a.G]));
-        float s[32];
+      for (int i = 0; i < kTilesPerWave; ++i) {
+        const int rt = 32 * (rg + kRowGroups * i);
+        if (rt < n_pad) {
+          floatx16 acc0, acc1;
+          logit_tile<D, true>(kf, lds0 + (uint32_t)(rt * 2 * D + qb0), acc0, acc1);
+          // lane owns probe row rt + lane%32; its registers hold tokens 8*(v/4) + 4*(lane/32) + v%4
+          float s[32];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) { s[v] = acc0[v]; s[16 + v] = acc1[v]; }
-        if (LIMIT || tok0 + kTokPerWave > T) {        // wave-uniform: only ragged or limited tiles compare
+          for (int v = 0; v < 16; ++v) { s[v] = acc0[v]; s[16 + v] = acc1[v]; }
+          if (LIMIT || tok0 + kTokPerWave > u.T) {        // wave-uniform: only ragged or limited tiles compare
+            const int left = lim[i] - tok0 - 4 * (lane >> 5);
 #pragma unroll
-          for (int v = 0; v < 32; ++v) {
-            const int t0 = tok0 + 32 * (v >> 4) + 8 * ((v & 15) >> 2) + 4 * (lane >> 5) + (v & 3);
-            s[v] = (t0 < lim) ? s[v] : -INFINITY;
+            for (int v = 0; v < 32; ++v) s[v] = (32 * (v >> 4) + 8 * ((v & 15) >> 2) + (v & 3) < left) ? s[v] : -INFINITY;
           }
+          float mx = s[0];
+#pragma unroll
+          for (int v = 1; v < 32; ++v) mx = fmaxf(mx, s[v]);
+          mx = fmaxf(mx, other_half(mx));
+          if (!kPairs<D>) mx *= kK2<D>;                         // (positive: scaling commutes with the maximum)
+          const float m_new = fmaxf(m_run[i], mx);
+          const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+          float sum = z_run[i] * __builtin_amdgcn_exp2f((m_run[i] - m_use) * kMaxScale<D>);
+#pragma unroll
+          for (int v = 0; v < 32; ++v) sum += exp_of<D>(s[v], m_use);
+          m_run[i] = m_new;
+          z_run[i] = sum;                       // (of this lane's half of the tokens)
         }
-        mx = s[0];
-#pragma unroll
-        for (int v = 1; v < 32; ++v) mx = fmaxf(mx, s[v]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        if (!kPairs<D>) mx *= kK2<D>;                         // (positive: scaling commutes with the maximum)
-        const float m_use = (mx == -INFINITY) ? 0.f : mx;
-#pragma unroll
-        for (int v = 0; v < 32; ++v) sum += exp_of<D>(s[v], m_use);
-        sum += __shfl_xor(sum, 32, 64);
       }
-      if (lane < 32) sPart[tw * kRowBlock + rt + lane] = make_float2(mx, sum);
+    }
+#pragma unroll
+    for (int i = 0; i < kTilesPerWave; ++i) {
+      const int rt = 32 * (rg + kRowGroups * i);
+      if (rt < n_pad) {
+        const float z = z_run[i] + other_half(z_run[i]);
+        if (lane < 32) sPart[tw * kRowBlock + rt + lane] = make_float2(m_run[i], z);
+      }
     }
     __syncthreads();
-    // the four token slices' partials of a row fold, in slice order, into the tile's partial
+    // the four token slices' partials of a row fold, in slice order, into the unit's partial
     for (int r = tid; r < n_rows; r += kThreads) {
       float2 p[kTokWaves];
       float m = -INFINITY;
@@ -317,7 +444,7 @@ __global__ __launch_bounds__(kThreads) void score_pass1(ScoreArgs a) {
         if (p[w].x > -INFINITY || (kPairs<D> && p[w].y != p[w].y)) z += p[w].y * exp2f((p[w].x - m) * kMaxScale<D>);
       const int rr = r_begin + r;
       const int i = rr / a.G, hh = rr - i * a.G;
-      part[(p0 + i) * a.H + g * a.G + hh] = make_float2(m, z);
+      part[(p0 + i) * a.H + u.g * a.G + hh] = make_float2(m, z);
     }
   }
 }
@@ -337,148 +464,135 @@ __device__ __forceinline__ void fold_partials(const float2 (&p)[kFoldBatch], flo
   }
 }
 
-// Pass 2, same division of work; the three row groups' column sums are added in a fixed order at the end.
+// Pass 2, same division of work; the three row groups' column sums are added in a fixed order at the end of a tile.
 template <int D, bool LIMIT>
-__global__ __launch_bounds__(kThreads) void score_pass2(ScoreArgs a) {
+__global__ __launch_bounds__(kThreads) void score_pass2(PassArgs pa) {
+  const ScoreArgs& a = pa.s;
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* sK = smem + kQBytes<D>;
-  float* sL = reinterpret_cast<float*>(smem + kQBytes<D> + kKBytes<D>);          // [kRowBlock] log2-sum-exp, or maximum
-  float* sRz = sL + (kPairs<D> ? kRowBlock : 0);                            // [kRowBlock] 1 / sum (kPairs)
-  int* sLim = reinterpret_cast<int*>(sL + (kRowWords<D> - 1) * kRowBlock);  // [kRowBlock]
+  float* sL = reinterpret_cast<float*>(smem + kQBytes<D> + kKBytes<D>);          // [kRowBlock] maximum
+  float* sRz = sL + kRowBlock;                                              // [kRowBlock] 1 / sum
+  int* sLim = reinterpret_cast<int*>(sRz + kRowBlock);                      // [kRowBlock]
   float* sCol = reinterpret_cast<float*>(sLim + kRowBlock);                 // [kRowGroups][kTokPerWg]
   static_assert(kRowBlock <= kThreads, "one thread folds one staged row");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tw = wave % kTokWaves, rg = wave / kTokWaves;
-  const int g = blockIdx.y;
-  int b, T, tile_tok0, tile_first;
-  int64_t c0;
-  if (!locate_tile(a, blockIdx.x, b, c0, T, tile_tok0, tile_first)) return;
-  const int64_t p0 = min(max(a.probe_off[b], (int64_t)0), a.total_probe);
-  const int64_t p1 = min(max(a.probe_off[b + 1], p0), a.total_probe);
+  const uint32_t lds0 = lds_offset_of(smem);
+  Unit u;
+  if (!locate_unit(pa, u)) return;
+  const int64_t p0 = min(max(a.probe_off[u.b], (int64_t)0), a.total_probe);
+  const int64_t p1 = min(max(a.probe_off[u.b + 1], p0), a.total_probe);
   const int rows = (int)(p1 - p0) * a.G;
   if (rows == 0) return;                 // (the reduce kernel gives such a request zeros without reading the sums)
-  const int n_tiles = (T + kTokPerWg - 1) / kTokPerWg;
+  const bf16_t* q = pa.q[u.layer];
+  const KeyLoader<D> keys(pa.k[u.layer] + (u.c0 * a.Hkv + u.g) * D, a.Hkv, u.T, lds0 + (uint32_t)kQBytes<D>, wave, lane);
   const int64_t part_stride = a.total_probe * a.H;
-  const int tok0 = tile_tok0 + tw * kTokPerWave;
-  const bool wave_active = tok0 < T;
   const int qb0 = frag_base<D>(lane);
-
-  stage_k_async<D>(a, c0, T, tile_tok0, g, sK, wave, lane);
-  bf16x8 kf[2][D / 16];
-  float col0 = 0.f, col1 = 0.f;        // column sums of tokens tok0 + lane%32 and + 32 over this wave's row tiles
+  float* colsum = a.colsum + ((int64_t)u.layer * a.Hkv + u.g) * a.total_ctx + u.c0;
 
   for (int r_begin = 0; r_begin < rows; r_begin += kRowBlock) {
     const int n_rows = min(kRowBlock, rows - r_begin);
     const int n_pad = (n_rows + 31) & ~31;
     __syncthreads();
-    stage_q_async<D>(a, p0, g, r_begin, n_rows, n_pad, smem, wave, lane);
-    // log2-sum-exp of staged row tid over the request: the tiles' partials folded in tile order, kFoldBatch
-    // at a time (all loads first, then one maximum and one rescaled sum); every workgroup of the request
-    // computes the same values
+    stage_q_async<D>(a, q, p0, u.g, r_begin, n_rows, n_pad, lds0, wave, lane);
+    keys.load(u.tile0, wave);
+    // maximum and sum of staged row tid over the request: the units' partials folded in order, kFoldBatch at a
+    // time (all loads first, then one maximum and one rescaled sum); every workgroup of the request computes the
+    // same values
     if (tid < n_pad) {
-      float l = INFINITY;               // rows that do not exist or see nothing: exp2(logit - lse) = 0
+      float l = INFINITY;               // rows that do not exist or see nothing: exp2(logit - inf) = 0
       float rz = 0.f;
       int lim = 0;
       if (tid < n_rows) {
         const int rr = r_begin + tid, i = rr / a.G, hh = rr - i * a.G;
-        const float2* pp = a.part + (int64_t)tile_first * part_stride + (p0 + i) * a.H + g * a.G + hh;
+        const float2* pp = a.part + u.slot_first * part_stride + (p0 + i) * a.H + u.g * a.G + hh;
         float m = -INFINITY, z = 0.f;
-        for (int t0 = 0; t0 < n_tiles; t0 += kFoldBatch) {
+        for (int t0 = 0; t0 < u.n_units; t0 += kFoldBatch) {
           float2 p[kFoldBatch];
 #pragma unroll
-          for (int u = 0; u < kFoldBatch; ++u) {
-            p[u] = (t0 + u < n_tiles) ? *pp : make_float2(-INFINITY, 0.f);
-            pp += part_stride;          // (stays inside the workspace: n_tiles <= the tiles allocated)
-          }
+          for (int v = 0; v < kFoldBatch; ++v)
+            p[v] = (t0 + v < u.n_units) ? pp[v * part_stride] : make_float2(-INFINITY, 0.f);
+          pp += kFoldBatch * part_stride;
           fold_partials<D>(p, m, z);
         }
-        lim = LIMIT ? min(T, max(0, a.probe_limit[p0 + i])) : T;
+        lim = LIMIT ? min(u.T, max(0, a.probe_limit[p0 + i])) : u.T;
         if (kPairs<D>) {
           if (lim > 0) {                // (no weight although tokens are visible, or a NaN sum: NaN)
             l = m;
             rz = z > 0.f ? 1.f / z : __builtin_nanf("");
           }
         } else if (z > 0.f) {
-          l = m + log2f(z);
+          l = m;
+          rz = 1.f / z;
         }
       }
       sL[tid] = l;
-      if (kPairs<D>) sRz[tid] = rz;
+      sRz[tid] = rz;
       sLim[tid] = lim;
     }
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (r_begin == 0) {
+    for (int tile = u.tile0; tile < u.tile1; ++tile) {
+      const int tok0 = tile * kTokPerWg + tw * kTokPerWave;
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();                    // the tile's keys (and the rows and their sums) have landed
+      bf16x8 kf[2][D / 16];
+      load_key_frags<D>(sK + kTokPerWave * tw * (2 * D), qb0, kf);
+      __syncthreads();                    // every wave has its keys, and the previous tile's column sums are out
+      if (tile + 1 < u.tile1) keys.load(tile + 1, wave);
+      float col0 = 0.f, col1 = 0.f;       // column sums of tokens tok0 + lane%32 and + 32 over this wave's row tiles
+      if (tok0 < u.T)
+        for (int rt = 32 * rg; rt < n_pad; rt += 32 * kRowGroups) {
+          floatx16 acc0, acc1;
+          logit_tile<D, false>(kf, lds0 + (uint32_t)(rt * 2 * D + qb0), acc0, acc1);
+          // lane owns tokens tok0 + lane%32 (acc0) and + 32 (acc1); register v is probe row
+          // rt + 8*(v/4) + 4*(lane/32) + v%4
+          const int tA = tok0 + (lane & 31), tB = tA + 32;
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
+          for (int q4 = 0; q4 < 4; ++q4) {
+            const int rbase = rt + 8 * q4 + 4 * (lane >> 5);
+            const float4 l4 = *reinterpret_cast<const float4*>(sL + rbase);
+            const float4 z4 = *reinterpret_cast<const float4*>(sRz + rbase);
+            const float ls[4] = {l4.x, l4.y, l4.z, l4.w};
+            const float rz[4] = {z4.x, z4.y, z4.z, z4.w};
+            int lims[4] = {u.T, u.T, u.T, u.T};
+            if (LIMIT) {
+              const int4 m4 = *reinterpret_cast<const int4*>(sLim + rbase);
+              lims[0] = m4.x; lims[1] = m4.y; lims[2] = m4.z; lims[3] = m4.w;
+            }
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks)
-          kf[mt][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(
-                                                      sK + (kTokPerWave * tw + 32 * mt) * (2 * D) + (qb0 ^ (32 * ks))));
-    }
-    if (!wave_active) continue;
-    for (int rt = 32 * rg; rt < n_pad; rt += 32 * kRowGroups) {
-      floatx16 acc0 = {0}, acc1 = {0};
-      const unsigned char* qrow = smem + rt * (2 * D);
-#pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks) {
-        const bf16x8 qf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qrow + (qb0 ^ (32 * ks))));
-        // S tile: rows = probe rows (A = queries), columns = tokens (B = keys)
-        acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, kf[0][ks], acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, kf[1][ks], acc1, 0, 0, 0);
-      }
-      // lane owns tokens tok0 + lane%32 (acc0) and + 32 (acc1); register v is probe row
-      // rt + 8*(v/4) + 4*(lane/32) + v%4
-      const int tA = tok0 + (lane & 31), tB = tA + 32;
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int rbase = rt + 8 * q4 + 4 * (lane >> 5);
-        const float4 l4 = *reinterpret_cast<const float4*>(sL + rbase);
-        const float ls[4] = {l4.x, l4.y, l4.z, l4.w};
-        float rz[4];
-        if (kPairs<D>) {
-          const float4 z4 = *reinterpret_cast<const float4*>(sRz + rbase);
-          rz[0] = z4.x; rz[1] = z4.y; rz[2] = z4.z; rz[3] = z4.w;
-        }
-        int lims[4] = {T, T, T, T};
-        if (LIMIT) {
-          const int4 m4 = *reinterpret_cast<const int4*>(sLim + rbase);
-          lims[0] = m4.x; lims[1] = m4.y; lims[2] = m4.z; lims[3] = m4.w;
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const int v = 4 * q4 + c;
-          float pa = exp_of<D>(acc0[v], ls[c]);
-          float pb = exp_of<D>(acc1[v], ls[c]);
-          if (kPairs<D> && LIMIT) { pa *= rz[c]; pb *= rz[c]; }
-          if (LIMIT) {
-            if (tA >= lims[c]) pa = 0.f;
-            if (tB >= lims[c]) pb = 0.f;
-          }
-          if (kPairs<D> && !LIMIT) {
-            col0 = __builtin_fmaf(pa, rz[c], col0);
-            col1 = __builtin_fmaf(pb, rz[c], col1);
-          } else {
-            col0 += pa;
-            col1 += pb;
+            for (int c = 0; c < 4; ++c) {
+              const int v = 4 * q4 + c;
+              float pa_ = exp_of<D>(acc0[v], ls[c]);
+              float pb_ = exp_of<D>(acc1[v], ls[c]);
+              if (LIMIT) {                 // (a row that sees nothing may have a NaN weight: the product first)
+                pa_ = tA < lims[c] ? pa_ * rz[c] : 0.f;
+                pb_ = tB < lims[c] ? pb_ * rz[c] : 0.f;
+                col0 += pa_;
+                col1 += pb_;
+              } else {
+                col0 = __builtin_fmaf(pa_, rz[c], col0);
+                col1 = __builtin_fmaf(pb_, rz[c], col1);
+              }
+            }
           }
         }
+      col0 += other_half(col0);
+      col1 += other_half(col1);
+      if (lane < 32) {
+        float* sc = sCol + rg * kTokPerWg + tw * kTokPerWave;
+        sc[lane] = col0;                      // (zero for a slice past the end of the request)
+        sc[32 + lane] = col1;
+      }
+      __syncthreads();
+      const int t = tile * kTokPerWg + tid;
+      if (tid < kTokPerWg && t < u.T) {
+        float sum = sCol[tid];
+#pragma unroll
+        for (int r3 = 1; r3 < kRowGroups; ++r3) sum += sCol[r3 * kTokPerWg + tid];
+        if (r_begin > 0) sum += colsum[t];    // (this thread's own sum over the rows before)
+        colsum[t] = sum;
       }
     }
-  }
-  col0 += __shfl_xor(col0, 32, 64);
-  col1 += __shfl_xor(col1, 32, 64);
-  if (lane < 32) {
-    float* sc = sCol + rg * kTokPerWg + tw * kTokPerWave;
-    sc[lane] = col0;                      // (zero for a slice past the end of the request)
-    sc[32 + lane] = col1;
-  }
-  __syncthreads();
-  if (tid < kTokPerWg && tile_tok0 + tid < T) {
-    float sum = sCol[tid];
-#pragma unroll
-    for (int r3 = 1; r3 < kRowGroups; ++r3) sum += sCol[r3 * kTokPerWg + tid];
-    a.colsum[(int64_t)g * a.total_ctx + c0 + tile_tok0 + tid] = sum;
   }
 }
 
@@ -536,14 +650,6 @@ __device__ __forceinline__ float fetch(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// exchange between the two 32-lane halves of a wave (one vector instruction, no LDS round trip):
-// returns the value the lane 32 away holds
-__device__ __forceinline__ float other_half(float x) {
-  typedef unsigned u2v __attribute__((ext_vector_type(2)));
-  const u2v r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  // r.x = (lower half's value in both halves), r.y = (upper half's value in both halves)
-  return (threadIdx.x & 32) ? __uint_as_float(r.x) : __uint_as_float(r.y);
-}
 // sum over the 32 lanes of each half of a wave, in a fixed order; every lane of the half gets the total
 __device__ __forceinline__ float half_wave_sum(float x) {
   x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x128, 0xf, 0xf, false));   // row_ror:8
@@ -780,16 +886,25 @@ __global__ __launch_bounds__(kFusedThreads) void score_fused(FusedArgs fa) {
   }
 }
 
-__global__ __launch_bounds__(256) void score_reduce(ScoreArgs a) {
+// Adds the KV heads of every layer in order, and the layers, in order, into the score.
+__global__ __launch_bounds__(256) void score_reduce(PassArgs pa) {
+  const ScoreArgs& a = pa.s;
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (j >= a.total_ctx) return;
   const int b = find_request(a.ctx_off, a.B, j);
   if (b >= a.B) return;
   const int64_t p0 = min(max(a.probe_off[b], (int64_t)0), a.total_probe);
   const int64_t p1 = min(max(a.probe_off[b + 1], p0), a.total_probe);
-  float acc = 0.f;
-  for (int g = 0; g < a.Hkv; ++g) acc += a.colsum[(int64_t)g * a.total_ctx + j];
-  write_score(a, j, (p1 > p0) ? acc / (float)((p1 - p0) * a.H) : 0.f);
+  const float n = (float)((p1 - p0) * a.H);
+  float score = a.beta == 0.f ? 0.f : a.score[j];
+  for (int l = 0; l < pa.n_layers; ++l) {
+    const float* col = a.colsum + (int64_t)l * a.Hkv * a.total_ctx + j;
+    float acc = 0.f;
+#pragma unroll 8
+    for (int g = 0; g < a.Hkv; ++g) acc += col[g * a.total_ctx];
+    score = blended(l == 0 ? a.beta : 1.f, score, pa.alpha[l] * (p1 > p0 ? acc / n : 0.f));
+  }
+  a.score[j] = score;
 }
 
 __global__ __launch_bounds__(256) void score_zero(float* score, int64_t n, float beta) {
@@ -814,7 +929,7 @@ MfmaWs mfma_ws(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t 
 }
 
 template <int D> constexpr size_t kPass1Lds = kQBytes<D> + kKBytes<D> + (size_t)kTokWaves * kRowBlock * sizeof(float2);
-template <int D> constexpr size_t kPass2Lds = kQBytes<D> + kKBytes<D> + kRowBlock * 4 * kRowWords<D> + (size_t)kRowGroups * kTokPerWg * sizeof(float);
+template <int D> constexpr size_t kPass2Lds = kQBytes<D> + kKBytes<D> + kRowBlock * 4 * 3 + (size_t)kRowGroups * kTokPerWg * sizeof(float);
 constexpr size_t kFusedLds = kQBytes<128> + kKBytes<128>;
 static_assert((size_t)kFusedWaves * kRowBlock * 8 + (size_t)kRowBlock * 4 + (size_t)kTokPerWg * 4 <= kKBytes<128>,
               "the single-kernel path's tables fit in the key tile's LDS");
@@ -858,18 +973,87 @@ qcf_status run_fused(const FusedArgs& fa, hipStream_t st) {
   score_fused<LIMIT><<<dim3((unsigned)(fa.n_wg_tiles * fa.s.Hkv)), dim3(kFusedThreads), kFusedLds, st>>>(fa);
   return check_launch("score (single kernel)");
 }
+// Tiles that a workgroup of the two passes takes in turn.  A workgroup spends about as long on staging probe rows and on its
+// sums as on kUnitCost tiles; where a launch is a few rounds long whole rounds count, otherwise the tail is about half a
+// unit.  (32768 tokens, 8 KV heads: units of four tiles, one round; with one tile to a unit pass 2 alone took 149 us, now 71.)
+constexpr double kUnitCost = 1.5;
+int unit_tiles_for(int32_t B, int64_t total_ctx, int64_t heads_layers) {
+  const int64_t nt = n_tiles_upper(B, total_ctx);
+  const double cus = compute_unit_count();
+  int best = 1;
+  double best_cost = 0;
+  for (int ul = 1; ul <= 64 && ul <= nt; ++ul) {
+    const double per_cu = (double)((nt + ul - 1) / ul + (B - 1) / 2) * (double)heads_layers / cus;
+    const double cost = (per_cu <= 3.0 ? std::ceil(per_cu) : per_cu + 0.5) * (ul + kUnitCost);
+    if (ul == 1 || cost < best_cost) { best = ul; best_cost = cost; }
+  }
+  return best;
+}
+struct PassWs { int unit_tiles; int64_t n_units; size_t colsum, total; };
+PassWs pass_ws(const qcf_layer_desc& L, int n_layers, int32_t B, int64_t total_probe, int64_t total_ctx) {
+  PassWs w;
+  w.unit_tiles = unit_tiles_for(B, total_ctx, (int64_t)L.n_kv_heads * n_layers);
+  // (every request may end in a unit that is not full; with one tile per unit these are the tiles themselves)
+  w.n_units = (n_tiles_upper(B, total_ctx) + (int64_t)B * (w.unit_tiles - 1)) / w.unit_tiles;
+  w.colsum = align_up((size_t)n_layers * w.n_units * total_probe * L.n_q_heads * sizeof(float2), 256);
+  w.total = w.colsum + align_up((size_t)n_layers * L.n_kv_heads * total_ctx * sizeof(float), 256);
+  return w;
+}
+
 template <int D, bool LIMIT>
-qcf_status run_two_pass(const ScoreArgs& a, int64_t n_tiles, hipStream_t st) {
+qcf_status run_two_pass(const PassArgs& a, hipStream_t st) {
   static std::atomic<uint64_t> lds_ok[2];
   QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass1<D, LIMIT>), kPass1Lds<D>, lds_ok[0]));
   QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass2<D, LIMIT>), kPass2Lds<D>, lds_ok[1]));
-  const dim3 grid((unsigned)n_tiles, (unsigned)a.Hkv), block(kThreads);
+  const dim3 grid((unsigned)((int64_t)a.n_units * a.n_layers * a.s.Hkv)), block(kThreads);
   score_pass1<D, LIMIT><<<grid, block, kPass1Lds<D>, st>>>(a);
   QCF_TRY_LAUNCH("score pass 1");
   score_pass2<D, LIMIT><<<grid, block, kPass2Lds<D>, st>>>(a);
   QCF_TRY_LAUNCH("score pass 2");
-  score_reduce<<<dim3((unsigned)((a.total_ctx + 255) / 256)), dim3(256), 0, st>>>(a);
+  score_reduce<<<dim3((unsigned)((a.s.total_ctx + 255) / 256)), dim3(256), 0, st>>>(a);
   return check_launch("score reduce");
+}
+
+// The two passes over n_layers layers (up to kMaxLayers); a: everything but the layers and the workspace.
+qcf_status launch_two_pass(const qcf_layer_desc& L, const ScoreArgs& a, int n_layers, const void* const* q,
+                           const void* const* k, const float* alpha, void* ws, hipStream_t st) {
+  const PassWs w = pass_ws(L, n_layers, a.B, a.total_probe, a.total_ctx);
+  if (w.n_units * n_layers * a.Hkv > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "score: grid too large");
+  PassArgs pa;
+  pa.s = a;
+  pa.s.part = static_cast<float2*>(ws);
+  pa.s.colsum = reinterpret_cast<float*>(static_cast<char*>(ws) + w.colsum);
+  for (int l = 0; l < kMaxLayers; ++l) {
+    const int i = std::min(l, n_layers - 1);
+    pa.q[l] = static_cast<const bf16_t*>(q[i]);
+    pa.k[l] = static_cast<const bf16_t*>(k[i]);
+    pa.alpha[l] = alpha[i];
+  }
+  pa.n_layers = n_layers;
+  pa.unit_tiles = w.unit_tiles;
+  pa.n_units = (int)w.n_units;
+  if (L.head_dim == 128) return a.probe_limit ? run_two_pass<128, true>(pa, st) : run_two_pass<128, false>(pa, st);
+  return a.probe_limit ? run_two_pass<64, true>(pa, st) : run_two_pass<64, false>(pa, st);
+}
+
+ScoreArgs score_args(const qcf_layer_desc& L, int32_t B, const void* q, const int64_t* probe_off, int64_t total_probe,
+                     const void* k, const int64_t* ctx_off, int64_t total_ctx, const int32_t* probe_limit, float* score,
+                     float alpha, float beta) {
+  ScoreArgs a;
+  a.q = static_cast<const bf16_t*>(q);
+  a.k = static_cast<const bf16_t*>(k);
+  a.probe_off = probe_off;
+  a.ctx_off = ctx_off;
+  a.probe_limit = probe_limit;
+  a.total_probe = total_probe;
+  a.total_ctx = total_ctx;
+  a.B = B; a.H = L.n_q_heads; a.Hkv = L.n_kv_heads; a.G = a.H / a.Hkv;
+  a.part = nullptr;
+  a.colsum = nullptr;
+  a.score = score;
+  a.alpha = alpha;
+  a.beta = beta;
+  return a;
 }
 
 // Device address of the zero-initialised counter array on the current device (asked for once per device).
@@ -931,20 +1115,7 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
     return check_launch("score column mean");
   }
 
-  ScoreArgs a;
-  a.q = static_cast<const bf16_t*>(q);
-  a.k = static_cast<const bf16_t*>(k);
-  a.probe_off = probe_off;
-  a.ctx_off = ctx_off;
-  a.probe_limit = probe_limit;
-  a.total_probe = total_probe;
-  a.total_ctx = total_ctx;
-  a.B = B; a.H = H; a.Hkv = Hkv; a.G = H / Hkv;
-  a.part = nullptr;
-  a.colsum = nullptr;
-  a.score = score;
-  a.alpha = alpha;
-  a.beta = beta;
+  const ScoreArgs a = score_args(L, B, q, probe_off, total_probe, k, ctx_off, total_ctx, probe_limit, score, alpha, beta);
   if (fused) {
     const FusedWs fw = fused_ws(L, B, total_ctx);
     FusedArgs fa;
@@ -959,13 +1130,45 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
     fa.sync = counters + (size_t)(next_slot.fetch_add(1, std::memory_order_relaxed) % kSyncSlots) * kSyncWords;
     return probe_limit ? run_fused<true>(fa, st) : run_fused<false>(fa, st);
   }
-  const MfmaWs w = mfma_ws(L, B, total_probe, total_ctx);
-  a.part = reinterpret_cast<float2*>(static_cast<char*>(ws) + w.part);
-  a.colsum = reinterpret_cast<float*>(static_cast<char*>(ws) + w.colsum);
-  const int64_t n_tiles = n_tiles_upper(B, total_ctx);
-  if (n_tiles > 0x7fffffff || Hkv > 65535) return fail(QCF_ERR_UNSUPPORTED, "score: grid too large");
-  if (D == 128) return probe_limit ? run_two_pass<128, true>(a, n_tiles, st) : run_two_pass<128, false>(a, n_tiles, st);
-  return probe_limit ? run_two_pass<64, true>(a, n_tiles, st) : run_two_pass<64, false>(a, n_tiles, st);
+  // (qcf_score_workspace_bytes gives the partials of every tile room; with several tiles to a unit less is used)
+  return launch_two_pass(L, a, 1, &q, &k, &alpha, ws, st);
+}
+
+// ---- several layers --------------------------------------------------------------------------------
+// Layers scored by one set of launches: as many as keep the workspace within that of a single call, or 64 MiB.  One where
+// the two passes do not apply.
+static int layers_at_once(const qcf_layer_desc& L, int32_t n_layers, int32_t B, int64_t total_probe, int64_t total_ctx) {
+  if (total_probe <= 0 || L.head_dim != 128 || !use_two_pass(L, B, total_probe, total_ctx)) return 1;
+  const size_t limit = std::max(score_workspace(L, B, total_probe, total_ctx), (size_t)64 << 20);
+  int n = std::min(n_layers, kMaxLayers);
+  while (n > 1 && pass_ws(L, n, B, total_probe, total_ctx).total > limit) --n;
+  return n;
+}
+
+size_t score_layers_workspace(const qcf_layer_desc& L, int32_t n_layers, int32_t B, int64_t total_probe, int64_t total_ctx) {
+  const int n = layers_at_once(L, n_layers, B, total_probe, total_ctx);
+  size_t need = score_workspace(L, B, total_probe, total_ctx);
+  if (n > 1) need = std::max(need, pass_ws(L, n, B, total_probe, total_ctx).total);
+  if (n > 1 && n_layers % n > 1) need = std::max(need, pass_ws(L, n_layers % n, B, total_probe, total_ctx).total);
+  return need;
+}
+
+qcf_status launch_score_layers(const qcf_layer_desc& L, int32_t n_layers, int32_t B, const void* const* q,
+                               const int64_t* probe_off, int64_t total_probe, const void* const* k, const int64_t* ctx_off,
+                               int64_t total_ctx, const int32_t* probe_limit, const float* weights, float* score, void* ws,
+                               hipStream_t st) {
+  const int at_once = layers_at_once(L, n_layers, B, total_probe, total_ctx);
+  for (int32_t l = 0; l < n_layers; l += at_once) {
+    const int n = std::min(at_once, n_layers - l);
+    const float beta = l == 0 ? 0.f : 1.f;
+    if (n == 1) {
+      QCF_TRY(launch_score(L, B, q[l], probe_off, total_probe, k[l], ctx_off, total_ctx, probe_limit, score, weights[l], beta, ws, st));
+    } else {
+      const ScoreArgs a = score_args(L, B, q[l], probe_off, total_probe, k[l], ctx_off, total_ctx, probe_limit, score, weights[l], beta);
+      QCF_TRY(launch_two_pass(L, a, n, q + l, k + l, weights + l, ws, st));
+    }
+  }
+  return QCF_OK;
 }
 
 }  // namespace qcf
