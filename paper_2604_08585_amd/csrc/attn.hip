@@ -24,46 +24,11 @@
 // Generic path (f32, or other shapes): one workgroup per (row, head), online softmax over
 // 256-token tiles.  Bound by the latency of its key and value loads (77 rows x 4 heads over 512 tokens in f32: 39 us with
 // one load at a time, 14 us with 16-byte key loads and the values shared out over all threads).
-#include <type_traits>
-
-#include "qcf_internal.h"
+#include "attn_common.h"
 
 namespace qcf {
+using namespace attn;
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
-
-__device__ __forceinline__ int find_request(const int64_t* __restrict__ off, int B, int64_t row) {
-  int b = 0;
-  while (b < B && row >= off[b + 1]) ++b;
-  return b;
-}
-
-struct AttnArgs {
-  const void* q;
-  const void* k;
-  const void* v;
-  const int32_t* sel_pos;
-  const int64_t* sel_off;
-  const int64_t* ctx_off;
-  const int32_t* ctx_pos0;
-  int64_t total_sel, total_ctx;
-  int B, H, Hkv, G, D;
-  void* o;
-  float* lse;
-  int n_row_blocks;      // upper bound on row blocks over all requests (MFMA path)
-  int seg_tiles;         // key tiles per work unit; a row block with more tiles is split over units
-  int n_seg_max;         // units per row block the grid provides
-  void* part_o;          // [unit][128 rows][D] normalised partial outputs of split row blocks (AttnTile<D>::part_t)
-  float* part_lse;       // [unit][128 rows] log2-domain log-sum-exp of each partial (-inf: no visible key); d = 64: pairs of
-                         // reference point (log2 units) and denominator against it
-  int32_t* units;        // units[0] = number of work units, then (row block << 8 | segment), longest first (null: no plan)
-  int32_t* blk_tiles;    // [row block] key tiles of the block, written by the plan kernel for the merge kernel (null: no plan)
-};
 
 // ------------------------------------------------------------------ generic path
 
@@ -149,50 +114,6 @@ __global__ __launch_bounds__(256) void attn_generic(AttnArgs a) {
 
 // ------------------------------------------------------------------ MFMA path (bf16, d = 128 or 64)
 
-typedef short shortx4 __attribute__((ext_vector_type(4)));
-typedef short shortx8 __attribute__((ext_vector_type(8)));
-
-constexpr int kBKV = 64;                    // tokens per K/V tile
-constexpr int kRowsPerWg = 128;             // (selected row, head-in-group) pairs per workgroup
-template <int D>
-struct AttnTile {
-  static constexpr int ROW = 2 * D;                     // bytes of a staged row, no padding (swizzled instead)
-  static constexpr int TILE = kBKV * ROW;               // bytes of a key or value tile
-  static constexpr int STAGE = 2 * TILE;
-  static constexpr size_t LDS = 2 * STAGE;
-  static constexpr int LROWS = 1024 / ROW;              // rows filled by one load instruction of a wave (1 KB)
-  static constexpr int NLOAD = kBKV / (4 * LROWS);      // instructions per wave and tile
-  static constexpr int KS = D / 16, DT = D / 32;        // k-steps of the logits, 32-element slices of the output
-  static constexpr int WGS = 2;                         // resident workgroups per compute unit (registers)
-  static constexpr bool SPLIT_P = D == 64;              // probabilities as three bf16 terms, fp32 partial outputs,
-                                                        // rows that are not finite computed again
-  typedef typename std::conditional<SPLIT_P, float, bf16_t>::type part_t;
-  static constexpr float K2 = kLog2e * (D == 128 ? 0.08838834764831845f : 0.125f);      // log2(e) / sqrt(D)
-};
-// Slot of 16-byte chunk c of token row r inside the row, keys and values (see the layouts below).
-template <int D> __device__ __forceinline__ int k_slot(int c, int r) { return D == 128 ? c ^ (r & 15) : c ^ ((r >> 1) & 7); }
-template <int D> __device__ __forceinline__ int v_slot(int c, int r) { return D == 128 ? c ^ (4 * (r & 3)) : c ^ (4 * ((r >> 1) & 1)); }
-constexpr float kLazyRescale = 8.f;         // log2 units the running maximum may lag behind the true one
-
-// LDS transposing read: within each group of 16 lanes, lane i receives element i%4 of the four
-// 8-byte rows addressed by lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4 of the group.
-__device__ __forceinline__ shortx4 lds_read_tr(uint32_t lds_addr) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((shortx4 __attribute__((address_space(3)))*)(uintptr_t)lds_addr);
-}
-// 16-byte LDS read at a byte address (a register plus a compile-time constant becomes the offset field)
-__device__ __forceinline__ u32x4 lds_read16(uint32_t lds_addr) {
-  return *(const u32x4 __attribute__((address_space(3)))*)(uintptr_t)lds_addr;
-}
-
-// Log-sum-exp of logits whose maximum is m / kLog2e and whose sum against it is 2^lz.  EXACT (heads of 64): rounded once,
-// and with the reciprocal of the kLog2e that m was scaled by (as two floats), not with ln 2.
-template <bool EXACT>
-__device__ __forceinline__ float natural_lse(float m, float lz) {
-  if (!EXACT) return (m + lz) * kLn2;
-  if (m == -INFINITY) return m;
-  constexpr float lo = (float)(1.0 / (double)kLog2e - (double)kLn2);
-  return __builtin_fmaf(m, kLn2, __builtin_fmaf(m, lo, lz * kLn2));
-}
 // Second and third bf16 term of two probabilities whose first terms are `pk`: a float has 24 significant bits, each term
 // takes eight and the differences are exact, so the three terms add up to the float.
 __device__ __forceinline__ void split_rest(float p0, float p1, uint32_t pk, uint32_t& second, uint32_t& third) {
@@ -241,7 +162,7 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);    // wave-uniform: keeps tile addresses in scalar registers
   const int hf = lane >> 5, l32 = lane & 31;
-  const int BR = kRowsPerWg / a.G;           // selected rows per workgroup
+  const int BR = a.block_rows;
   const uint32_t lds0 = lds_offset_of(smem);
 
   // consecutive workgroup ids land on different XCDs: give each XCD its own KV heads so that a
@@ -494,7 +415,7 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
   // epilogue: output register v of tile dt is element 32*dt + 16*hf + v of this lane's row
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  const int64_t part_row = (((int64_t)blk * a.Hkv + g) * a.n_seg_max + seg) * kRowsPerWg + r;    // of a split block
+  const int64_t part_row = (((int64_t)blk * a.Hkv + g) * a.n_seg_max + seg) * C::WG_ROWS + r;    // of a split block
   typename C::part_t* part = static_cast<typename C::part_t*>(a.part_o) + part_row * D + 16 * hf;
   bf16_t* orow = static_cast<bf16_t*>(a.o) + (srow * a.H + head) * D + 16 * hf;
   // x(dt, v): value of this lane's element 32 dt + 16 hf + v; m + log2(z): log2-sum-exp
@@ -662,7 +583,7 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(AttnArgs a) {
   __shared__ int s_cnt[kPlanBins + 1];
   __shared__ int s_off[kPlanBins + 1];
   const int tid = threadIdx.x;
-  const int BR = kRowsPerWg / a.G;
+  const int BR = a.block_rows;
   for (int i = tid; i < a.n_row_blocks; i += 1024) s_vis[i] = 0;
   for (int i = tid; i <= kPlanBins; i += 1024) s_cnt[i] = 0;
   __syncthreads();
@@ -717,15 +638,18 @@ __device__ __forceinline__ float weighted(float w, float f) {
   if (SPLIT_P) return fabsf(f) < INFINITY ? w * f : f;
   return w * f;
 }
-template <int D> constexpr int kMergeWgs = kRowsPerWg * (D / 8) / 256;
-template <int D>
+// element of the partial outputs
+template <int D, int ROWS> struct PartOf { typedef typename AttnTile<D>::part_t type; };
+template <> struct PartOf<128, kWideRows> { typedef float type; };
+template <int D, int ROWS> constexpr int kMergeWgs = ROWS * (D / 8) / 256;
+template <int D, int ROWS>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
-  typedef typename AttnTile<D>::part_t part_t;
+  typedef typename PartOf<D, ROWS>::type part_t;
   constexpr int CH = D / 8;                         // 8-element chunks of a row
   const int tid = threadIdx.x;
-  const int BR = kRowsPerWg / a.G;
-  const int part = (int)(blockIdx.x % kMergeWgs<D>);
-  const int bh = (int)(blockIdx.x / kMergeWgs<D>);
+  const int BR = a.block_rows;
+  const int part = (int)(blockIdx.x % kMergeWgs<D, ROWS>);
+  const int bh = (int)(blockIdx.x / kMergeWgs<D, ROWS>);
   const int g = bh % a.Hkv;
   const int blk = bh / a.Hkv;
   int n_tiles = a.blk_tiles ? a.blk_tiles[blk] : 0;
@@ -764,8 +688,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   // unit (blk, g, seg) wrote slot ((blk * Hkv + g) * n_seg_max + seg)
   const int64_t slot0 = ((int64_t)blk * a.Hkv + g) * a.n_seg_max;
   constexpr int PL = AttnTile<D>::SPLIT_P ? 2 : 1;   // floats per row
-  const float* pl = a.part_lse + (slot0 * kRowsPerWg + r) * PL;
-  const part_t* po = static_cast<const part_t*>(a.part_o) + (slot0 * kRowsPerWg + r) * D + 8 * ch;
+  const float* pl = a.part_lse + (slot0 * ROWS + r) * PL;
+  const part_t* po = static_cast<const part_t*>(a.part_o) + (slot0 * ROWS + r) * D + 8 * ch;
   // four segments at a time: every load first, then the running maximum, the weights and the weighted sum
   constexpr bool SPLIT_P = AttnTile<D>::SPLIT_P;
   bool nan = false;                                 // (SPLIT_P) the denominator of some segment is NaN
@@ -777,11 +701,11 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const bool ok = row_ok && sg0 + u < n_seg;
-      l[u] = ok ? pl[(int64_t)(sg0 + u) * kRowsPerWg * PL] : -INFINITY;
-      z[u] = !SPLIT_P || !ok ? 1.f : pl[(int64_t)(sg0 + u) * kRowsPerWg * PL + 1];
+      l[u] = ok ? pl[(int64_t)(sg0 + u) * ROWS * PL] : -INFINITY;
+      z[u] = !SPLIT_P || !ok ? 1.f : pl[(int64_t)(sg0 + u) * ROWS * PL + 1];
 #pragma unroll
       for (int w = 0; w < (int)sizeof(part_t) / 2; ++w)
-        raw[u][w] = ok ? *reinterpret_cast<const u32x4*>(po + (int64_t)(sg0 + u) * kRowsPerWg * D + w * Elem<part_t>::kVec) : u32x4{0u, 0u, 0u, 0u};
+        raw[u][w] = ok ? *reinterpret_cast<const u32x4*>(po + (int64_t)(sg0 + u) * ROWS * D + w * Elem<part_t>::kVec) : u32x4{0u, 0u, 0u, 0u};
     }
     float mn = mx;
 #pragma unroll
@@ -831,10 +755,10 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 
 // Key tiles per work unit.  With enough row blocks the causal triangle balances by itself and blocks
 // stay whole; otherwise a segment is about the average causal work of a resident workgroup.
-int resident_workgroups(int D) { return (D == 128 ? AttnTile<128>::WGS : AttnTile<64>::WGS) * compute_unit_count(); }
+int resident_workgroups(int rows) { return (rows == kWideRows ? 1 : 2) * compute_unit_count(); }
 struct Split { int seg_tiles, n_seg_max; };
-Split choose_split(int D, int64_t n_blocks, int64_t total_ctx) {
-  const int slots = resident_workgroups(D);
+Split choose_split(int rows, int64_t n_blocks, int64_t total_ctx) {
+  const int slots = resident_workgroups(rows);
   const int64_t n_t = std::max<int64_t>(1, (total_ctx + kBKV - 1) / kBKV);
   const int64_t per_slot = n_blocks * ((n_t + 1) / 2) / slots;     // average causal work per resident workgroup
   // a little above that average (a multiple of 4 tiles): most resident workgroups then take one whole
@@ -846,31 +770,64 @@ Split choose_split(int D, int64_t n_blocks, int64_t total_ctx) {
   return Split{(int)seg, (int)((n_t + seg - 1) / seg)};
 }
 
-size_t part_o_bytes(int D, int64_t n_blocks, int n_seg_max) {
-  const size_t row = D == 128 ? 128 * sizeof(AttnTile<128>::part_t) : 64 * sizeof(AttnTile<64>::part_t);
-  return align_up((size_t)n_blocks * n_seg_max * kRowsPerWg * row, 256);
+// How a launch is divided: rows of a workgroup, row blocks of all requests (upper bound), key segments.
+struct Division { int rows; int64_t n_row_blocks; Split split; };
+int64_t row_blocks(const qcf_layer_desc& L, int rows, int32_t B, int64_t total_sel) {
+  const int br = rows / (L.n_q_heads / L.n_kv_heads);
+  return (total_sel + br - 1) / br + B;
 }
-size_t part_lse_bytes(int D, int64_t n_blocks, int n_seg_max) {
-  return align_up((size_t)n_blocks * n_seg_max * kRowsPerWg * (D == 128 ? 1 : 2) * sizeof(float), 256);
+// 128 or 256 rows to a workgroup (heads of 128).  The wide workgroups read every key and value fragment half as often, but
+// one of them fills a compute unit, so nothing hides the start and the end of its unit, a unit is the grain of the balance,
+// and their partial outputs are fp32.  They take over where a compute unit's average causal work is long enough.  Narrow
+// and wide, us, one request: 1228 rows x 32 heads over 12288 tokens (63 tiles to a compute unit) 149 and 153, 819 over
+// 16384 (56) 139 and 140, 1228 over 8192 (42) 114 and 113; 2457 over 8192 (80) 192 and 187, 1843 over 12288 (90) 206 and
+// 196, 2457 over 16384 (157) 358 and 339; 4915 rows x 64 heads over 32768 2468 and 2262.  Several requests, whose lengths
+// the host does not know (the longest may be most of the launch): eight of 2K to 16K tokens with 544 wide blocks 445 and
+// 472, with 1248 blocks 882 and 803; sixteen of 1000 tokens 60 and 78.
+constexpr int64_t kWideTiles = 72;          // average causal work of a compute unit, in tiles (one request)
+constexpr int64_t kWideBlocks = 4;          // row blocks to a compute unit (several requests)
+Division divide(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx) {
+  auto of = [&](int rows) {
+    const int64_t nb = row_blocks(L, rows, B, total_sel);
+    return Division{rows, nb, choose_split(rows, nb * L.n_kv_heads, total_ctx)};
+  };
+  if (L.head_dim == 128) {
+    const Division wide = of(kWideRows);
+    const int64_t blocks = wide.n_row_blocks * L.n_kv_heads, cus = compute_unit_count(), n_t = (total_ctx + kBKV - 1) / kBKV;
+    if (B == 1 ? blocks * ((n_t + 1) / 2) >= kWideTiles * cus : blocks >= kWideBlocks * cus) return wide;
+  }
+  return of(AttnTile<128>::WG_ROWS);
+}
+
+size_t part_o_bytes(int D, const Division& d, int Hkv) {
+  const size_t elem = D == 64 ? sizeof(PartOf<64, 128>::type) : d.rows == kWideRows ? sizeof(PartOf<128, kWideRows>::type) : sizeof(PartOf<128, 128>::type);
+  return align_up((size_t)d.n_row_blocks * Hkv * d.split.n_seg_max * d.rows * D * elem, 256);
+}
+size_t part_lse_bytes(int D, const Division& d, int Hkv) {
+  return align_up((size_t)d.n_row_blocks * Hkv * d.split.n_seg_max * d.rows * (D == 128 ? 1 : 2) * sizeof(float), 256);
 }
 size_t units_bytes(int64_t n_row_blocks, int n_seg_max) {
   return align_up((size_t)(n_row_blocks * n_seg_max + 1) * sizeof(int32_t), 256);
 }
 size_t blk_tiles_bytes(int64_t n_row_blocks) { return align_up((size_t)n_row_blocks * sizeof(int32_t), 256); }
 
-template <int D>
+template <int D, int ROWS>
 qcf_status run_mfma(const AttnArgs& a, hipStream_t st) {
-  static std::atomic<uint64_t> lds_ok{0};
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&attn_mfma_kernel<D>), AttnTile<D>::LDS, lds_ok));
   const int64_t blocks = (int64_t)a.n_row_blocks * a.Hkv;
   if (a.units) {
     attn_plan_kernel<<<dim3(1), dim3(1024), 0, st>>>(a);
     QCF_TRY_LAUNCH("attn plan");
   }
-  attn_mfma_kernel<D><<<dim3((unsigned)(blocks * a.n_seg_max)), dim3(256), AttnTile<D>::LDS, st>>>(a);
-  QCF_TRY_LAUNCH("attn");
+  if constexpr (ROWS == kWideRows) {
+    QCF_TRY(run_attn128(a, blocks * a.n_seg_max, st));
+  } else {
+    static std::atomic<uint64_t> lds_ok{0};
+    QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&attn_mfma_kernel<D>), AttnTile<D>::LDS, lds_ok));
+    attn_mfma_kernel<D><<<dim3((unsigned)(blocks * a.n_seg_max)), dim3(256), AttnTile<D>::LDS, st>>>(a);
+    QCF_TRY_LAUNCH("attn");
+  }
   if (a.n_seg_max > 1) {
-    attn_merge_kernel<D><<<dim3((unsigned)(blocks * kMergeWgs<D>)), dim3(256), 0, st>>>(a);
+    attn_merge_kernel<D, ROWS><<<dim3((unsigned)(blocks * kMergeWgs<D, ROWS>)), dim3(256), 0, st>>>(a);
     return check_launch("attn merge");
   }
   return QCF_OK;
@@ -878,19 +835,17 @@ qcf_status run_mfma(const AttnArgs& a, hipStream_t st) {
 
 bool use_mfma(const qcf_layer_desc& L) {
   const int G = L.n_q_heads / L.n_kv_heads;
-  return L.dtype == QCF_DTYPE_BF16 && (L.head_dim == 128 || L.head_dim == 64) && G <= kRowsPerWg && kRowsPerWg % G == 0;
+  return L.dtype == QCF_DTYPE_BF16 && (L.head_dim == 128 || L.head_dim == 64) && G <= 128 && 128 % G == 0;
 }
 
 }  // namespace
 
 size_t attn_workspace(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx) {
   if (!use_mfma(L) || total_sel <= 0 || total_ctx <= 0) return 0;
-  const int BR = kRowsPerWg / (L.n_q_heads / L.n_kv_heads);
-  const int64_t n_blocks = ((total_sel + BR - 1) / BR + B) * L.n_kv_heads;
-  const Split sp = choose_split(L.head_dim, n_blocks, total_ctx);
-  if (sp.n_seg_max <= 1) return 0;
-  return part_o_bytes(L.head_dim, n_blocks, sp.n_seg_max) + part_lse_bytes(L.head_dim, n_blocks, sp.n_seg_max) +
-         units_bytes(n_blocks / L.n_kv_heads, sp.n_seg_max) + blk_tiles_bytes(n_blocks / L.n_kv_heads);
+  const Division d = divide(L, B, total_sel, total_ctx);
+  if (d.split.n_seg_max <= 1) return 0;
+  return part_o_bytes(L.head_dim, d, L.n_kv_heads) + part_lse_bytes(L.head_dim, d, L.n_kv_heads) +
+         units_bytes(d.n_row_blocks, d.split.n_seg_max) + blk_tiles_bytes(d.n_row_blocks);
 }
 
 size_t attn_workspace_needed(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx) {
@@ -908,30 +863,32 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
   a.B = B; a.H = L.n_q_heads; a.Hkv = L.n_kv_heads; a.G = L.n_q_heads / L.n_kv_heads; a.D = L.head_dim;
   a.o = o; a.lse = lse;
   a.n_row_blocks = 0;
+  a.block_rows = 0;
   a.seg_tiles = 0x3fffffff; a.n_seg_max = 1; a.part_o = nullptr; a.part_lse = nullptr; a.units = nullptr; a.blk_tiles = nullptr;
   if (use_mfma(L)) {
-    const int BR = kRowsPerWg / a.G;
-    const int64_t nb = (total_sel + BR - 1) / BR + B;
-    Split sp = choose_split(L.head_dim, nb * a.Hkv, total_ctx);
+    const Division d = divide(L, B, total_sel, total_ctx);
+    Split sp = d.split;
     if (attn_workspace(L, B, total_sel, total_ctx) > ws_bytes) sp = Split{0x3fffffff, 1};      // (d = 64 only: optional)
-    if (nb * a.Hkv * std::max(sp.n_seg_max, kMergeWgs<128>) > 0x7fffffff)
+    const int64_t nb = d.n_row_blocks;
+    if (nb * a.Hkv * std::max(sp.n_seg_max, d.rows * 16 / 256) > 0x7fffffff)
       return fail(QCF_ERR_UNSUPPORTED, "attn: grid too large");
+    a.block_rows = d.rows / a.G;
     a.n_row_blocks = (int)nb;
     a.seg_tiles = sp.seg_tiles;
     a.n_seg_max = sp.n_seg_max;
     if (sp.n_seg_max > 1) {
       a.part_o = ws;
       char* w = static_cast<char*>(ws);
-      a.part_lse = reinterpret_cast<float*>(w + part_o_bytes(L.head_dim, nb * a.Hkv, sp.n_seg_max));
+      a.part_lse = reinterpret_cast<float*>(w + part_o_bytes(L.head_dim, d, a.Hkv));
       // The plan sorts the units for the compute units to take in turn.  Where all of them start at once their order does
       // not matter, and the launch is saved: 110 rows over 731 tokens 22.3 -> 19.0 us, 40 rows over 8192 30.4 -> 23.5.
-      if (nb * a.Hkv * sp.n_seg_max > resident_workgroups(a.D)) {
-        a.units = reinterpret_cast<int32_t*>(w + part_o_bytes(L.head_dim, nb * a.Hkv, sp.n_seg_max) +
-                                             part_lse_bytes(L.head_dim, nb * a.Hkv, sp.n_seg_max));
+      if (nb * a.Hkv * sp.n_seg_max > resident_workgroups(d.rows)) {
+        a.units = reinterpret_cast<int32_t*>(w + part_o_bytes(L.head_dim, d, a.Hkv) + part_lse_bytes(L.head_dim, d, a.Hkv));
         a.blk_tiles = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(a.units) + units_bytes(nb, sp.n_seg_max));
       }
     }
-    return a.D == 128 ? run_mfma<128>(a, st) : run_mfma<64>(a, st);
+    if (a.D == 64) return run_mfma<64, 128>(a, st);
+    return d.rows == kWideRows ? run_mfma<128, kWideRows>(a, st) : run_mfma<128, 128>(a, st);
   }
   if (total_sel * a.H > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "attn: grid too large");
   const dim3 grid((unsigned)(total_sel * a.H)), block(256);

@@ -350,7 +350,7 @@ constexpr int kTilesPerWave = (kRowBlock / 32 + kRowGroups - 1) / kRowGroups;   
 template <int D, bool LIMIT>
 __global__ __launch_bounds__(kThreads) void score_pass1(PassArgs pa) {
   const ScoreArgs& a = pa.s;
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(256) unsigned char smem[];      // (fragment addresses are formed with XORs below 256)
   unsigned char* sK = smem + kQBytes<D>;
   float2* sPart = reinterpret_cast<float2*>(smem + kQBytes<D> + kKBytes<D>);     // [kTokWaves][kRowBlock]
   const int tid = threadIdx.x, lane = tid & 63;
@@ -468,7 +468,7 @@ __device__ __forceinline__ void fold_partials(const float2 (&p)[kFoldBatch], flo
 template <int D, bool LIMIT>
 __global__ __launch_bounds__(kThreads) void score_pass2(PassArgs pa) {
   const ScoreArgs& a = pa.s;
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(256) unsigned char smem[];      // (fragment addresses are formed with XORs below 256)
   unsigned char* sK = smem + kQBytes<D>;
   float* sL = reinterpret_cast<float*>(smem + kQBytes<D> + kKBytes<D>);          // [kRowBlock] maximum
   float* sRz = sL + kRowBlock;                                              // [kRowBlock] 1 / sum
