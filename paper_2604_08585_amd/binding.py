@@ -142,8 +142,15 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """Handle of the current stream of the current device.  torch.cuda.current_stream() builds an object around it, 2.5 us
+    of the 7 to 8 us that a call of one launch takes; the handle itself takes 0.3."""
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch._C._cuda_getDevice())
 
 
 def _workspace(nbytes: int, device) -> Optional[torch.Tensor]:

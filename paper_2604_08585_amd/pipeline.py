@@ -261,17 +261,16 @@ def extract_anchors(desc, k: torch.Tensor, v: torch.Tensor, chunk_lens: List[int
     if dev.type == "cuda" and torch.cuda.is_current_stream_capturing():
         # a replay would copy the offsets from host memory that has been given back by then
         raise RuntimeError("extract_anchors cannot be captured into a graph: it copies its offsets from the host")
-    rows = int(sum(chunk_lens))
-    n_per_chunk = [min(int(n), int(l)) for n, l in zip(n_per_chunk, chunk_lens)]
-    total = int(sum(n_per_chunk))
-    norm = torch.empty(max(rows, 1), dtype=torch.float32, device=dev)
-    qb.qcf_key_norm(desc, k, rows, norm)
     # both offset tables in one pinned block and one asynchronous copy (two pageable copies made the host wait twice)
     n = len(chunk_lens)
     off = torch.zeros(2, n + 1, dtype=torch.int64, pin_memory=dev.type == "cuda")
     offs = off.numpy()
-    np.cumsum(np.asarray(chunk_lens, dtype=np.int64), out=offs[0, 1:])
-    np.cumsum(np.asarray(n_per_chunk, dtype=np.int64), out=offs[1, 1:])
+    lens = np.asarray(chunk_lens, dtype=np.int64)
+    np.cumsum(lens, out=offs[0, 1:])
+    np.cumsum(np.minimum(np.asarray(n_per_chunk[:n], dtype=np.int64), lens), out=offs[1, 1:])
+    rows, total = int(offs[0, n]), int(offs[1, n])
+    norm = torch.empty(max(rows, 1), dtype=torch.float32, device=dev)
+    qb.qcf_key_norm(desc, k, rows, norm)
     ctx_off, sel_off = off.to(dev, non_blocking=True)
     idx = torch.empty(max(total, 1), dtype=torch.int32, device=dev)
     row = torch.empty(max(total, 1), dtype=torch.int32, device=dev)
