@@ -168,14 +168,18 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
   // consecutive workgroup ids land on different XCDs: give each XCD its own KV heads so that a
   // head's keys and values stay in one L2; later row blocks (longer key ranges) are scheduled first
   // Launches without a plan take the row blocks from the last (longest key range) to the first.  The others
-  // read the unit list attn_plan_kernel sorted by length; segments are counted from the top of a block's
-  // key range, so a block's remainder segment is the one at the start of the context.
+  // read the unit list attn_plan_kernel sorted by length, or find their place in it themselves; segments are counted from the top of
+  // a block's key range, so a block's remainder segment is the one at the start of the context.
   const int g = (int)(blockIdx.x % a.Hkv);
   const int unit = (int)(blockIdx.x / a.Hkv);
   int seg = unit % a.n_seg_max, blk = a.n_row_blocks - 1 - unit / a.n_seg_max;
   if (a.units) {
     if (unit >= a.units[0]) return;
     const int code = a.units[1 + unit];
+    blk = code >> 8;
+    seg = code & 255;
+  } else if (a.own_order) {
+    const int code = ordered_unit(a, unit, smem);
     blk = code >> 8;
     seg = code & 255;
   }
@@ -572,7 +576,7 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
   }
 }
 
-// Work list of a split launch: one entry per (row block, key segment) that has tiles, bucket-sorted by
+// Work list of a split launch of several requests, or of more units than ordered_unit handles: one entry per (row block, key segment) that has tiles, bucket-sorted by
 // length (longest first) so that the short remainders fill the tail of the schedule.  The order inside a
 // bucket depends on the race for the slots; results do not, because every unit's output location is given
 // by its (row block, segment).
@@ -865,6 +869,7 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
   a.n_row_blocks = 0;
   a.block_rows = 0;
   a.seg_tiles = 0x3fffffff; a.n_seg_max = 1; a.part_o = nullptr; a.part_lse = nullptr; a.units = nullptr; a.blk_tiles = nullptr;
+  a.own_order = 0;
   if (use_mfma(L)) {
     const Division d = divide(L, B, total_sel, total_ctx);
     Split sp = d.split;
@@ -882,7 +887,16 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
       a.part_lse = reinterpret_cast<float*>(w + part_o_bytes(L.head_dim, d, a.Hkv));
       // The plan sorts the units for the compute units to take in turn.  Where all of them start at once their order does
       // not matter, and the launch is saved: 110 rows over 731 tokens 22.3 -> 19.0 us, 40 rows over 8192 30.4 -> 23.5.
-      if (nb * a.Hkv * sp.n_seg_max > resident_workgroups(d.rows)) {
+      // The workgroups of one request find their places themselves (ordered_unit) up to 512 units, which covers the split
+      // launches of a request whose blocks are few enough to need the order.  With the launch that writes the list and
+      // without, us: 615 rows x 32 heads over 4096 tokens 45.0 and 40.9, the last 615 positions in the place of spread ones
+      // 63.4 and 58.7, heads of 64 49.4 and 45.8; 410 rows over 8192 50.7 and 46.9, 1229 over 8192 116.0 and 110.2.  An
+      // order from the host, for rows taken to be spread evenly, was 2 us faster still on such rows and up to 18 % slower
+      // than the list on rows gathered in two places.
+      if (nb * a.Hkv * sp.n_seg_max <= resident_workgroups(d.rows)) {
+      } else if (B == 1 && nb * sp.n_seg_max <= kOrderMax && nb <= kOrderBlocks) {
+        a.own_order = 1;
+      } else {
         a.units = reinterpret_cast<int32_t*>(w + part_o_bytes(L.head_dim, d, a.Hkv) + part_lse_bytes(L.head_dim, d, a.Hkv));
         a.blk_tiles = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(a.units) + units_bytes(nb, sp.n_seg_max));
       }

@@ -69,6 +69,10 @@ __global__ __launch_bounds__(256, 1) void attn128_kernel(AttnArgs a) {
     const int code = a.units[1 + unit];
     blk = code >> 8;
     seg = code & 255;
+  } else if (a.own_order) {
+    const int code = ordered_unit(a, unit, smem);
+    blk = code >> 8;
+    seg = code & 255;
   }
   int wg = blk, b = 0;
   int64_t s0 = 0, s1 = 0;

@@ -42,6 +42,7 @@ struct AttnArgs {
   float* part_lse;       // [unit][rows of a workgroup] log2-domain log-sum-exp of each partial (-inf: no visible key); d = 64: pairs of
                          // reference point (log2 units) and denominator against it
   int32_t* units;        // units[0] = number of work units, then (row block << 8 | segment), longest first (null: no plan)
+  int own_order;         // without a plan, 1: every workgroup finds its unit in that order itself (ordered_unit)
   int32_t* blk_tiles;    // [row block] key tiles of the block, written by the plan kernel for the merge kernel (null: no plan)
 };
 
@@ -86,6 +87,67 @@ __device__ __forceinline__ float natural_lse(float m, float lz) {
   constexpr float lo = (float)(1.0 / (double)kLog2e - (double)kLn2);
   return __builtin_fmaf(m, kLn2, __builtin_fmaf(m, lo, lz * kLn2));
 }
+// Unit number `rank` of a split launch of one request, as (row block << 8 | segment), where the units are ordered by length
+// (longest first) and from the last row block to the first among those of one length bucket.  Every workgroup of the launch
+// works the same order out from the positions, which takes it about a microsecond (a launch that writes the order down takes
+// five to six, in which nothing else runs).  A row block's length is taken from its last row; it bears on the order alone,
+// so that rows in any order of positions are right.  All pairs that there may be have a place: those without tiles come last.
+// `lds` is scratch of kOrderLds bytes, free again on return.
+constexpr int kOrderMax = 512;              // units (row blocks x segments)
+constexpr int kOrderBlocks = 256;           // row blocks, one to a thread
+constexpr int kOrderBins = 64;              // lengths in 63rds of a segment: one to a lane
+constexpr int kOrderLds = (kOrderBlocks + kOrderMax + kOrderBins) * 4;
+__device__ __forceinline__ int ordered_unit(const AttnArgs& a, int rank, void* lds) {
+  int* s_tiles = static_cast<int*>(lds);
+  int* s_bin = s_tiles + kOrderBlocks;
+  int* s_count = s_bin + kOrderMax;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int64_t s0 = min(max(a.sel_off[0], (int64_t)0), a.total_sel), s1 = min(max(a.sel_off[1], s0), a.total_sel);
+  const int64_t c0 = min(max(a.ctx_off[0], (int64_t)0), a.total_ctx), c1 = min(max(a.ctx_off[1], c0), a.total_ctx);
+  if (tid < a.n_row_blocks) {
+    const int64_t first = s0 + (int64_t)tid * a.block_rows, last = min(first + a.block_rows, s1) - 1;
+    int64_t vis = 0;
+    if (last >= first) vis = min(c1 - c0, max((int64_t)0, (int64_t)a.sel_pos[last] - (a.ctx_pos0 ? a.ctx_pos0[0] : 0) + 1));
+    s_tiles[tid] = (int)((vis + kBKV - 1) / kBKV);
+  }
+  if (tid < kOrderBins) s_count[tid] = 0;
+  __syncthreads();
+  const int n = a.n_row_blocks * a.n_seg_max;
+  for (int u = tid; u < kOrderMax; u += 256) {
+    int bin = -1;
+    if (u < n) {
+      const int len = s_tiles[a.n_row_blocks - 1 - u / a.n_seg_max] - u % a.n_seg_max * a.seg_tiles;
+      bin = kOrderBins - 1 - (int)((float)min(max(len, 0), a.seg_tiles) * (float)(kOrderBins - 1) / (float)a.seg_tiles);
+      bin = min(max(bin, 0), kOrderBins - 1);
+      atomicAdd(&s_count[bin], 1);
+    }
+    s_bin[u] = bin;
+  }
+  __syncthreads();
+  const int count = s_count[lane];
+  int before = count;                                   // units of the buckets up to this lane's
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int t = __shfl_up(before, d, 64);
+    if (lane >= d) before += t;
+  }
+  before -= count;
+  const int bin = __popcll(__ballot(before <= rank)) - 1;      // the last bucket that starts at or before the rank: not an
+  int left = rank - __shfl(before, bin, 64);                   // empty one, as rank < n
+  int unit = 0;
+#pragma unroll
+  for (int i = 0; i < kOrderMax / 64; ++i) {
+    const bool mine = s_bin[64 * i + lane] == bin;
+    const uint64_t m = __ballot(mine);
+    const uint64_t hit = __ballot(mine && (int)__popcll(m & ((1ull << lane) - 1)) == left);
+    if (hit) unit = 64 * i + (int)__builtin_ctzll(hit);
+    left -= (int)__popcll(m);
+  }
+  __syncthreads();
+  unit = __builtin_amdgcn_readfirstlane(unit);
+  return (a.n_row_blocks - 1 - unit / a.n_seg_max) << 8 | unit % a.n_seg_max;
+}
+
 // Main kernel for heads of 128 with 256 rows to a workgroup, one workgroup to a compute unit (attn128.hip).
 constexpr int kWideRows = 256;
 qcf_status run_attn128(const AttnArgs& a, int64_t n_wg, hipStream_t st);
