@@ -847,7 +847,9 @@ __device__ __forceinline__ bool locate_big_tile(int m_tiles, int n_bt, int gm, i
   return true;
 }
 
-template <int EPI>
+// SPLIT: column tiles are numbered once per range of the contraction, and the tile's sums leave as they are for
+// qkv_split_reduce, straight from the accumulators (a template parameter, so that the whole product's registers stay)
+template <int EPI, bool SPLIT>
 __global__ __launch_bounds__(256, 1) void qkv_quad_kernel(QkvArgs a) {
   using C = QuadTile;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -857,11 +859,17 @@ __global__ __launch_bounds__(256, 1) void qkv_quad_kernel(QkvArgs a) {
   const int hf = lane >> 5, l32 = lane & 31;
   const int n_bt = (a.n_tiles + 1) / 2;
   int m_tile, b_tile;
-  if (!locate_big_tile(a.m_tiles, n_bt, a.m_group, (int)blockIdx.x, m_tile, b_tile)) return;
+  if (!locate_big_tile(a.m_tiles, SPLIT ? n_bt * a.splits : n_bt, a.m_group, (int)blockIdx.x, m_tile, b_tile)) return;
+  int split = 0, nk = a.d_model / kBK;                           // even (launcher)
+  if constexpr (SPLIT) {
+    split = b_tile / n_bt;
+    b_tile -= split * n_bt;
+    nk = min(nk - split * a.split_len, a.split_len);             // even as well: split_len is
+  }
+  const int64_t k0 = SPLIT ? (int64_t)split * a.split_len * (kBK * 2) : 0;       // bytes of a row in front of the range
   const int64_t m0 = (int64_t)m_tile * C::BM;
   const int block0 = a.n_tile0 + 2 * b_tile;
   const bool second = 2 * b_tile + 1 < a.n_tiles;                // (else the tile's second 128 columns repeat the first)
-  const int nk = a.d_model / kBK;                                // even (launcher)
   const uint32_t row_bytes = (uint32_t)a.d_model * 2u;
 
   // byte offsets of this lane's 16 bytes inside k-tile 0: load i of unit u fills unit rows 8*wave + 32*i .. +7
@@ -887,8 +895,8 @@ __global__ __launch_bounds__(256, 1) void qkv_quad_kernel(QkvArgs a) {
   }
   const uint32_t lds0 = lds_offset_of(smem);
   const uint32_t lds_w = __builtin_amdgcn_readfirstlane((int)(lds0 + (uint32_t)wave * 1024u));
-  const char* a_base = reinterpret_cast<const char*>(a.x);
-  const char* b_base = reinterpret_cast<const char*>(a.w + block_w_row<EPI>(block0) * a.d_model);
+  const char* a_base = reinterpret_cast<const char*>(a.x) + k0;
+  const char* b_base = reinterpret_cast<const char*>(a.w + block_w_row<EPI>(block0) * a.d_model) + k0;
   auto load_a1 = [&](auto u_c, auto i_c, auto sl_c, const char* src) {
     constexpr int u = decltype(u_c)::value, i = decltype(i_c)::value, sl = decltype(sl_c)::value;
     load_to_lds_const<sl * C::STAGE + u * C::UNIT + i * 4096>(src, a_off[u][i], lds_w);
@@ -925,7 +933,7 @@ __global__ __launch_bounds__(256, 1) void qkv_quad_kernel(QkvArgs a) {
   auto lds16 = [](uint32_t addr) { return *(const u32x4 __attribute__((address_space(3)))*)(uintptr_t)addr; };
 
   EpiRows<4> rows;
-  load_epi_rows<4, EPI>(a, m0 + wm * 128, lane, rows);
+  if constexpr (!SPLIT) load_epi_rows<4, EPI>(a, m0 + wm * 128, lane, rows);
   floatx16 acc[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -1000,6 +1008,19 @@ __global__ __launch_bounds__(256, 1) void qkv_quad_kernel(QkvArgs a) {
   for (int i = 0; i < 4; ++i)          // (in accumulation registers until here, whatever the epilogue wants)
     asm volatile("" : "+a"(acc[i][0]), "+a"(acc[i][1]), "+a"(acc[i][2]), "+a"(acc[i][3]));
 
+  if constexpr (SPLIT) {               // partial sums in register order: 1 KB per store
+    if (wn == 1 && !second) return;
+    float4* dst = static_cast<float4*>(a.part) +
+                  (((int64_t)split * a.n_tiles + 2 * b_tile + wn) * (8 * a.m_tiles) + 8 * m_tile + 4 * wm) * 1024 + lane;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          dst[i * 1024 + (4 * j + q) * 64] = make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+    return;
+  }
   // epilogue, every wave by itself in 32 KB of the ring's space (nobody reads or fills the ring any more)
   float2* sRho = reinterpret_cast<float2*>(smem + 2 * C::STAGE);
   if (is_rope(EPI) && tid < 64) fill_rho(a, sRho, tid);
@@ -1038,6 +1059,27 @@ double ws128_us(int64_t mt, int nb, int nk) {
   return r * (ws128_tile_us(r) * nk + 8.0);
 }
 
+// 256 x 256 tiles with the contraction in `s` ranges of an even number of k-tiles.  The partial sums leave all at once and
+// are read again by the reduction (7 TB/s both ways: a hundred megabytes stay in the memory-side cache).  Few row tiles
+// wait for their weights instead of the matrix unit; of two rounds the second's products hide the first's stores.
+// Taken from 128 k-tiles on, over two rounds in three ranges or more (two would give a compute unit what the undivided tile
+// gives it) of at least 64.  Product calls without and with it, us: K 14336, N 4096 of
+// 400 rows 78 and 64, 768 rows 132 and 90, 1229 rows 178 and 130, 2458 rows 278 and 251; K 14336, N 9088 of 400 rows 181
+// and 119; K 8192, N 10240 of 129 rows 69 and 55, 512 rows 111 and 89.  The other side of the line: K 4096, N 4096 of 1229
+// rows 44 and 56, N 6144 of 700 rows 52 and 53 (a range of 22 k-tiles does not pay for its sums); K 8192, N 10240 of 900
+// rows, two rounds of ranges of 44, 159 and 162; K 14336, N 4096 of 3300 rows, two rounds of two ranges, 303 and 338.
+int quad_split_len(int nk, int s) { return (nk / 2 + s - 1) / s * 2; }
+bool quad_split_pays(int64_t mt, int nb, int nk, int s) {
+  const double r = rounds_of(mt * ((nb + 1) / 2) * s);
+  return nk >= 128 && (r <= 1 || (r <= 2 && s >= 3 && quad_split_len(nk, s) >= 64));
+}
+double quad_split_us(int64_t mt, int nb, int nk, int s) {
+  const double r = rounds_of(mt * ((nb + 1) / 2) * s);
+  const double t = std::max(r * 1.36 * quad_split_len(nk, s), (double)nb * nk * (kBN * kBK * 2) / 4.6e6) + r * 6.0 + 4.0 +
+                   (double)mt * nb * (256 * kBN * 8) * s / 7.0e6;
+  return r > 1 ? 0.92 * t : t;
+}
+
 size_t split_part_bytes(int64_t M, int nb, int bm, int splits) {
   return splits <= 1 ? 0 : (size_t)splits * nb * ((M + bm - 1) / bm) * bm * kBN * sizeof(float);
 }
@@ -1062,7 +1104,7 @@ GemmPlan plan_ws(int64_t M, int nb, int nk, size_t part_bytes) {
 }
 
 // The whole product: up to two launches.  The first, in tiles of `kind`, covers `rows` rows of all blocks or `blocks`
-// blocks of all rows (rows == M and blocks == nb: everything); `rest` is the rest.
+// blocks of all rows (rows == M and blocks == nb: everything, and only then in several ranges, `splits`); `rest` is the rest.
 //
 // A tile fills whole rounds of compute units only, so where the last round would be thin the first launch takes what
 // full rounds hold and smaller tiles the rest: the column blocks that are left (256 x 256 tiles), or the rows that are
@@ -1072,7 +1114,7 @@ GemmPlan plan_ws(int64_t M, int nb, int nk, size_t part_bytes) {
 // rows 139.3 and 130.8, 4916 rows 627 and 594; K 14336, N 4096 of 2100 rows 235 and 205.  Where the rest is too long to
 // be split the estimates are less good: 1500 and 2100 rows of the first shape lose 2.7 and 3.7 us.
 // (128 x 128 tiles for the whole rounds lose: tail of 1229 rows 483 us in one launch, 492 that way.)
-struct ProductPlan { GemmKind kind; int64_t rows; int blocks; GemmPlan rest; double us; };
+struct ProductPlan { GemmKind kind; int64_t rows; int blocks; GemmPlan rest; double us; int splits = 1; };
 
 // The 256 x 256 kernel takes k-tiles in pairs, and its lanes address 256 weight rows with 32-bit byte offsets.
 bool quad_ok(int nk) { return nk % 2 == 0 && (uint64_t)nk * kBK * 2 * QuadTile::BN <= (1ull << 32); }
@@ -1085,6 +1127,13 @@ ProductPlan plan_product(int64_t M, int nb, int nk, bool by_rows, size_t part_by
   if (quad_ok(nk)) {
     const double whole = quad_us(mt, nb, nk);
     if (whole < best.us) best = ProductPlan{kQuad, M, nb, one, whole};
+    for (int s = 2; s <= 8 && nb <= 65535; ++s) {                // (grid.y of the reduction)
+      if (split_part_bytes(M, nb, 256, s) > part_bytes) break;
+      const int len = quad_split_len(nk, s);
+      if ((nk + len - 1) / len != s || !quad_split_pays(mt, nb, nk, s)) continue;      // (a range would be empty)
+      const double t = quad_split_us(mt, nb, nk, s);
+      if (t < best.us) best = ProductPlan{kQuad, M, nb, one, t, s};
+    }
     const int64_t rounds = mt * ((nb + 1) / 2) / cus;
     for (int64_t r = rounds; r >= 1 && r >= rounds - 1; --r) {
       const int qb = (int)(r * cus / mt * 2);
@@ -1115,9 +1164,17 @@ ProductPlan plan_product(int64_t M, int nb, int nk, bool by_rows, size_t part_by
 // workspace a product of M rows x nb column blocks x nk k-tiles can use (not needed: without it the contraction stays whole)
 size_t gemm_part_bytes(int64_t M, int nb, int nk) {
   const ProductPlan p = plan_product(M, nb, nk, true, SIZE_MAX);
-  if (p.blocks == nb && p.rows == M) return 0;
+  if (p.blocks == nb && p.rows == M) return split_part_bytes(M, nb, 256, p.splits);
   return split_part_bytes(p.blocks == nb ? M - p.rows : M, p.blocks > 0 && p.blocks < nb ? nb - p.blocks : nb,
                           p.rest.kind == kWs64 ? 64 : 128, p.rest.splits);
+}
+
+// finishes a split launch whose partial sums lie in n_groups groups of 32 rows
+template <int EPI>
+qcf_status run_split_reduce(const QkvArgs& a, int64_t n_groups, hipStream_t st) {
+  const dim3 grid((unsigned)((a.M + 31) / 32), (unsigned)a.n_tiles);
+  qkv_split_reduce<EPI><<<grid, dim3(256), 0, st>>>(a, (int)n_groups);
+  return check_launch("qkv split reduce");
 }
 
 template <typename C, int EPI, bool WIDE>
@@ -1141,28 +1198,25 @@ qcf_status run_ws(QkvArgs a, int splits, hipStream_t st) {
   QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&qkv_ws_kernel<C, EPI, WIDE>), C::LDS, lds_ok));
   qkv_ws_kernel<C, EPI, WIDE><<<dim3((unsigned)n_wg), dim3(C::NTHR), C::LDS, st>>>(a);
   QCF_TRY_LAUNCH("qkv gemm");
-  if (splits > 1) {
-    const dim3 rgrid((unsigned)(mt * C::NC), (unsigned)a.n_tiles);
-    qkv_split_reduce<EPI><<<rgrid, dim3(256), 0, st>>>(a, (int)(mt * C::NC));
-    return check_launch("qkv split reduce");
-  }
-  return QCF_OK;
+  return splits > 1 ? run_split_reduce<EPI>(a, mt * C::NC, st) : QCF_OK;
 }
 
-template <int EPI>
-qcf_status run_quad(QkvArgs a, hipStream_t st) {
+template <int EPI, bool SPLIT>
+qcf_status run_quad(QkvArgs a, int splits, hipStream_t st) {
   using C = QuadTile;
   const int64_t mt = (a.M + C::BM - 1) / C::BM;
-  const int64_t n_wg = (mt * ((a.n_tiles + 1) / 2) + 255) / 256 * 256;
+  const int64_t n_wg = (mt * ((a.n_tiles + 1) / 2) * splits + 255) / 256 * 256;
   if (n_wg > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "qkv: grid too large");
   a.m_tiles = (int)mt;
   const int64_t groups = (mt + 5) / 6;                           // groups of up to six row tiles, of equal size
   a.m_group = (int)((mt + groups - 1) / groups);
-  a.splits = 1;
+  a.splits = splits;
+  a.split_len = quad_split_len(a.d_model / kBK, splits);
   static std::atomic<uint64_t> lds_ok;
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&qkv_quad_kernel<EPI>), C::LDS, lds_ok));
-  qkv_quad_kernel<EPI><<<dim3((unsigned)n_wg), dim3(C::NTHR), C::LDS, st>>>(a);
-  return check_launch("qkv gemm");
+  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&qkv_quad_kernel<EPI, SPLIT>), C::LDS, lds_ok));
+  qkv_quad_kernel<EPI, SPLIT><<<dim3((unsigned)n_wg), dim3(C::NTHR), C::LDS, st>>>(a);
+  QCF_TRY_LAUNCH("qkv gemm");
+  return SPLIT ? run_split_reduce<EPI>(a, mt * 8, st) : QCF_OK;
 }
 
 // Product of the generic path.  The small tile reads both operands four times as often, so it takes over only where
@@ -1197,7 +1251,7 @@ qcf_status run_rope_split(const qcf_layer_desc& L, const float* y, int64_t M, co
 template <int EPI>
 qcf_status run_kind(const QkvArgs& a, GemmKind kind, int splits, hipStream_t st) {
   switch (kind) {
-    case kQuad: return run_quad<EPI>(a, st);
+    case kQuad: return splits > 1 ? run_quad<EPI, true>(a, splits, st) : run_quad<EPI, false>(a, 1, st);
     case kWs64: return run_ws<Ws64, EPI, false>(a, splits, st);
     case kWs128: return run_ws<Ws128, EPI, false>(a, splits, st);
     default: return run_ws<Ws256, EPI, false>(a, splits, st);
@@ -1220,7 +1274,7 @@ qcf_status run_gemm(const QkvArgs& a_in, int nb, void* ws, size_t ws_bytes, hipS
   QkvArgs first = a;
   first.M = p.rows;
   first.n_tiles = p.blocks;
-  QCF_TRY(run_kind<EPI>(first, p.kind, 1, st));
+  QCF_TRY(run_kind<EPI>(first, p.kind, p.splits, st));
   if (p.rows < a.M) return run_kind<EPI>(rows_from<EPI>(a, p.rows), p.rest.kind, p.rest.splits, st);
   if (p.blocks == nb) return QCF_OK;
   a.n_tile0 = p.blocks;

@@ -1,0 +1,97 @@
+"""Products whose contraction is split over 256 x 256 tiles, against float32: ragged rows, an odd number of column blocks,
+ranges of unequal length, the rotation and the gated SiLU behind the reduction."""
+import pytest
+import torch
+
+from paper_2604_08585_amd import binding as qb
+from paper_2604_08585_amd import inputs
+from gpu_util import DEV
+
+pytestmark = pytest.mark.gpu
+BF = torch.bfloat16
+DESC = inputs.LayerShape(4096, 32, 8, 128, 500000.0, "bf16")
+
+
+def _normal(seed, *size, std=1.0):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    return (torch.randn(size, generator=g, device=DEV) * std).to(BF)
+
+
+def _one_rounding(got, ref, slack=2e-4):
+    err = (got.float() - ref).abs()
+    assert bool((err <= 2.0 ** -8 * ref.abs() + slack).all()), float(err.max())
+
+
+def _sums(M, N, splits):
+    """Workspace of a contraction in `splits` ranges over 256 x 256 tiles."""
+    return splits * ((M + 255) // 256 * 256) * N * 4
+
+
+@pytest.mark.parametrize("M,K,N,splits,res", [
+    (1229, 14336, 4096, 3, True),        # 76, 76 and 72 k-tiles; 205 rows in the last row tile
+    (765, 14336, 3456, 6, True),         # an odd number of column blocks, a last range of 34
+    (1025, 14336, 3712, 3, False),       # one row in the last row tile
+    (129, 14336, 8448, 6, False),        # one row tile
+    (512, 8192, 10240, 3, True)])
+def test_linear(M, K, N, splits, res):
+    print(f"split product M={M} K={K} N={N}", flush=True)
+    desc = qb.make_desc(DESC)
+    assert qb.qcf_linear_workspace_bytes(desc, M, K, N) == _sums(M, N, splits)
+    x, w = _normal(1, M, K), _normal(2, N, K, std=K ** -0.5)
+    r = _normal(3, M, N) if res else None
+    ref = x.float() @ w.float().T + (r.float() if res else 0.0)
+    outs = []
+    for _ in range(2):
+        out = torch.full((M + 1, N), 7.0, dtype=BF, device=DEV)
+        qb.qcf_linear(desc, x, M, K, w, N, r, out)
+        outs.append(out)
+    torch.cuda.synchronize()
+    _one_rounding(outs[0][:M], ref)
+    assert torch.equal(outs[0], outs[1]) and bool((outs[0][M] == 7.0).all())
+
+
+def test_projection_with_write_back():
+    M, dm, H, Hkv, D = 400, 8192, 64, 8, 128
+    print(f"split projection M={M} H={H}", flush=True)
+    sh = inputs.LayerShape(dm, H, Hkv, D, 500000.0, "bf16")
+    desc = qb.make_desc(sh)
+    assert qb.qcf_recompute_qkv_workspace_bytes(desc, M) == _sums(M, sh.qkv_rows, 3)
+    x, w = _normal(4, M + 50, dm), _normal(5, sh.qkv_rows, dm, std=dm ** -0.5)
+    g = torch.Generator(device=DEV).manual_seed(6)
+    gather = torch.randperm(M + 50, generator=g, device=DEV)[:M].int()
+    gather[17] = -1                                          # outside x: a zero row
+    pos = torch.randint(0, 40000, (M,), generator=g, device=DEV).int()
+    dst = torch.randperm(M + 50, generator=g, device=DEV)[:M].int()
+    q, k, v = (torch.full((M, h, D), 7.0, dtype=BF, device=DEV) for h in (H, Hkv, Hkv))
+    kf, vf = (torch.full((M + 50, Hkv, D), 7.0, dtype=BF, device=DEV) for _ in range(2))
+    qb.qcf_recompute_qkv_scatter(desc, x, M + 50, gather, M, w, pos, q, k, v, dst, kf, vf, M + 50)
+    torch.cuda.synchronize()
+    xs = x[gather.clamp(min=0).long()].float()
+    xs[17] = 0
+    y = (xs @ w.float().T).reshape(M, H + 2 * Hkv, D)
+    theta = 500000.0 ** (-torch.arange(0, D, 2, device=DEV, dtype=torch.float64) / D)
+    ang = pos.double()[:, None, None] * theta
+    a, b = y[:, :H + Hkv, :D // 2].double(), y[:, :H + Hkv, D // 2:].double()
+    y[:, :H + Hkv] = torch.cat([a * ang.cos() - b * ang.sin(), b * ang.cos() + a * ang.sin()], -1).float()
+    for got, ref in ((q, y[:, :H]), (k, y[:, H:H + Hkv]), (v, y[:, H + Hkv:])):
+        _one_rounding(got, ref)
+    for fused, new in ((kf, k), (vf, v)):
+        ref = torch.full_like(fused, 7.0)
+        ref[dst.long()] = new
+        assert torch.equal(fused, ref)
+
+
+def test_gated_silu():
+    """Gate and up are rounded to bf16 before the activation: |error| <= 3 roundings of the product of their sizes."""
+    M, K, F = 512, 8192, 5120
+    print(f"split gated product M={M} F={F}", flush=True)
+    desc = qb.make_desc(DESC)
+    x, w = _normal(7, M, K), _normal(8, 2 * F, K, std=K ** -0.5)
+    out = torch.full((M, F), 7.0, dtype=BF, device=DEV)
+    qb.qcf_linear_swiglu(desc, x, M, K, w, F, out)
+    torch.cuda.synchronize()
+    y = (x.float() @ w.float().T).to(BF).float()             # (a sum near a rounding boundary may round the other way)
+    gate, up = y[:, :F], y[:, F:]
+    ref = torch.nn.functional.silu(gate) * up
+    err = (out.float() - ref).abs()
+    assert bool((err <= 2.0 ** -8 * ref.abs() + 2.0 ** -7 * (1.1 * gate.abs() * up.abs()) + 2e-4).all()), float(err.max())
