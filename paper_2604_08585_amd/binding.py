@@ -7,6 +7,7 @@ import ctypes as C
 import os
 from typing import List, Optional, Sequence
 
+import numpy as np
 import torch
 
 from .inputs import LayerShape
@@ -31,6 +32,9 @@ FFN_EXPORTS = ["qcf_linear_swiglu_workspace_bytes", "qcf_linear_swiglu"]
 
 # declared in qcf_layers.h
 LAYERS_EXPORTS = ["qcf_score_layers_workspace_bytes", "qcf_score_layers"]
+
+# declared in qcf_anchors.h
+ANCHORS_EXPORTS = ["qcf_extract_anchors_workspace_bytes", "qcf_extract_anchors"]
 
 
 class QcfError(RuntimeError):
@@ -115,6 +119,11 @@ def load_library() -> C.CDLL:
     lib.qcf_score_layers_workspace_bytes.argtypes = [dp, i32, i32, i64, i64]
     lib.qcf_score_layers.restype = C.c_int
     lib.qcf_score_layers.argtypes = [dp, i32, i32, pp, vp, i64, pp, vp, i64, vp, C.POINTER(C.c_float), vp, vp, sz, vp]
+    op = C.POINTER(i64)
+    lib.qcf_extract_anchors_workspace_bytes.restype = sz
+    lib.qcf_extract_anchors_workspace_bytes.argtypes = [dp, i32, i64]
+    lib.qcf_extract_anchors.restype = C.c_int
+    lib.qcf_extract_anchors.argtypes = [dp, vp, vp, i32, op, op, vp, vp, vp, vp, sz, vp]
     lib.qcf_key_norm.restype = C.c_int
     lib.qcf_key_norm.argtypes = [dp, vp, i64, vp, vp]
     lib.qcf_gather.restype = C.c_int
@@ -350,6 +359,20 @@ def qcf_linear_swiglu(desc: LayerDesc, x: torch.Tensor, M: int, K: int, w_gate_u
         workspace = _workspace(int(lib.qcf_linear_swiglu_workspace_bytes(C.byref(desc), M, K, F)), x.device)
     wp, wn = _ws_args(workspace)
     _check(lib.qcf_linear_swiglu(C.byref(desc), _ptr(x), M, K, _ptr(w_gate_up), F, _ptr(out), wp, wn, _stream()))
+
+
+def qcf_extract_anchors(desc: LayerDesc, k: torch.Tensor, v: torch.Tensor, ctx_off: np.ndarray, sel_off: np.ndarray,
+                        rows: torch.Tensor, k_out: torch.Tensor, v_out: torch.Tensor,
+                        workspace: Optional[torch.Tensor] = None) -> None:
+    """Key norm, Top-N per chunk and gather; the offsets are contiguous int64 arrays of the host."""
+    lib = load_library()
+    n = ctx_off.size - 1
+    if workspace is None:
+        workspace = _workspace(int(lib.qcf_extract_anchors_workspace_bytes(C.byref(desc), n, int(ctx_off[n]))), k.device)
+    wp, wn = _ws_args(workspace)
+    op = C.POINTER(C.c_int64)
+    _check(lib.qcf_extract_anchors(C.byref(desc), _ptr(k), _ptr(v), n, ctx_off.ctypes.data_as(op), sel_off.ctypes.data_as(op),
+                                   _ptr(rows), _ptr(k_out), _ptr(v_out), wp, wn, _stream()))
 
 
 def qcf_key_norm(desc: LayerDesc, k: torch.Tensor, rows: int, norm: torch.Tensor) -> None:

@@ -470,4 +470,33 @@ qcf_status qcf_gather(const qcf_layer_desc* desc, const void* k_src, const void*
   return launch_gather(*desc, k_src, v_src, src_rows_dev, M, total_rows, k_out, v_out, (hipStream_t)stream);
 }
 
+size_t qcf_extract_anchors_workspace_bytes(const qcf_layer_desc* desc, int32_t n_chunks, int64_t total_rows) {
+  if (check_desc(desc) != QCF_OK || n_chunks <= 0 || total_rows <= 0) return 0;
+  return align_up((size_t)total_rows * sizeof(float), 256);
+}
+
+qcf_status qcf_extract_anchors(const qcf_layer_desc* desc, const void* k, const void* v, int32_t n_chunks,
+                               const int64_t* ctx_off, const int64_t* sel_off, int32_t* rows, void* k_out, void* v_out,
+                               void* workspace, size_t workspace_bytes, void* stream) {
+  QCF_TRY(check_desc(desc));
+  if (n_chunks < 0) return fail(QCF_ERR_INVALID_ARG, "negative size");
+  if (n_chunks > 65535) return fail(QCF_ERR_UNSUPPORTED, "%d chunks > 65535", n_chunks);
+  if (n_chunks == 0) return QCF_OK;
+  if (!ctx_off || !sel_off) return fail(QCF_ERR_INVALID_ARG, "offsets are NULL");
+  const int64_t total = ctx_off[n_chunks], total_sel = sel_off[n_chunks];
+  if (total < 0 || total_sel < 0) return fail(QCF_ERR_INVALID_ARG, "negative size");
+  if (total > kMaxRows) return fail(QCF_ERR_UNSUPPORTED, "too many rows");
+  if (total_sel > total) return fail(QCF_ERR_INVALID_ARG, "%lld anchors > %lld rows", (long long)total_sel, (long long)total);
+  if (total_sel == 0) return QCF_OK;
+  QCF_TRY(need_ptr(k, "k"));
+  QCF_TRY(need_ptr(v, "v"));
+  QCF_TRY(need_idx_ptr(rows, "rows"));
+  QCF_TRY(need_ptr(k_out, "k_out"));
+  QCF_TRY(need_ptr(v_out, "v_out"));
+  QCF_TRY(need_ws(workspace, workspace_bytes, qcf_extract_anchors_workspace_bytes(desc, n_chunks, total)));
+  float* norm = static_cast<float*>(workspace);
+  QCF_TRY(launch_key_norm(*desc, k, total, norm, (hipStream_t)stream));
+  return launch_select_gather(*desc, norm, n_chunks, ctx_off, sel_off, k, v, rows, k_out, v_out, (hipStream_t)stream);
+}
+
 }  // extern "C"

@@ -11,6 +11,7 @@
 #include "qcf.h"
 #include "qcf_ffn.h"
 #include "qcf_layers.h"
+#include "qcf_anchors.h"
 
 namespace qcf {
 
@@ -213,6 +214,11 @@ qcf_status launch_select(int32_t B, const float* score, const int64_t* ctx_off, 
                          const int64_t* sel_off, int64_t total_sel, const int32_t* ctx_pos0,
                          int32_t* sel_idx, int32_t* sel_row, int32_t* sel_pos, void* ws,
                          hipStream_t st);
+
+// Top-N of every chunk and the gather of its key and value rows; the offsets are host arrays
+qcf_status launch_select_gather(const qcf_layer_desc& L, const float* score, int32_t n_chunks, const int64_t* ctx_off,
+                                const int64_t* sel_off, const void* k, const void* v, int32_t* rows, void* k_out, void* v_out,
+                                hipStream_t st);
 
 size_t qkv_workspace(const qcf_layer_desc& L, int64_t M);
 // dst_rows / k_fused / v_fused (all or none): the K/V rows are also written to rows dst_rows[m] of the fused cache

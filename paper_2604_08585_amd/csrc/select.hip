@@ -172,7 +172,7 @@ __device__ __forceinline__ void select_request(SelectLds& lds, const float* __re
   const int64_t out0 = o0;
 #define QCF_EMIT(j, pos)                                            \
   {                                                                 \
-    sel_idx[out0 + (pos)] = (j);                                    \
+    if (sel_idx) sel_idx[out0 + (pos)] = (j);                       \
     if (sel_row) sel_row[out0 + (pos)] = (int32_t)(c0 + (j));       \
     if (sel_pos) sel_pos[out0 + (pos)] = base_pos + (j);            \
   }
@@ -230,6 +230,50 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
 #undef QCF_SELECT
 }
 
+// Offline anchors: Top-N of a chunk, then its key and value rows, by the workgroup that selected them.  Bound by latency: the
+// offsets of up to kAnchorChunks chunks travel as kernel arguments (3.6 of the 4 KB a launch can have), so that no copy to
+// the device stands in front of the first kernel and no launch between the selection and the gather.  Whole extraction,
+// us, with four operations on the stream and now: 64 chunks of 512, 26 rows each, 46 and 27; 4 chunks of 64 40 and 27.
+constexpr int kAnchorChunks = 448;
+struct AnchorChunks {
+  int32_t ctx[kAnchorChunks + 1], sel[kAnchorChunks + 1];        // inside the totals (at most 2^30 rows)
+};
+
+template <int MAX>
+__global__ __launch_bounds__(kThreads) void select_gather_kernel(const float* __restrict__ score, AnchorChunks ch,
+                                                                 const u32x4* __restrict__ k, const u32x4* __restrict__ v,
+                                                                 int vec_per_row, int32_t* rows, u32x4* __restrict__ k_out,
+                                                                 u32x4* __restrict__ v_out) {
+  __shared__ SelectLds lds;
+  const int b = blockIdx.x, tid = threadIdx.x;
+  const int64_t c0 = ch.ctx[b], o0 = ch.sel[b];
+  const int T = ch.ctx[b + 1] - ch.ctx[b];
+  const int N = min(T, ch.sel[b + 1] - ch.sel[b]);
+  if (N <= 0) return;
+  int seg = (T + kThreads - 1) / kThreads;
+  if (seg > 1) seg = (seg + 3) & ~3;
+  select_request<MAX>(lds, score + c0, c0, T, N, seg, o0, 0, nullptr, rows, nullptr);
+  if (!k_out) return;                                            // (rows only: the gather is a launch of its own)
+  __syncthreads();                                               // this workgroup's rows are written
+  const int64_t out = o0 * vec_per_row;
+  const int items = N * vec_per_row;                             // (at most kGatherVecs)
+  for (int i0 = tid; i0 < items; i0 += 4 * kThreads) {
+    u32x4 kk[4], vv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = min(i0 + u * kThreads, items - 1), m = i / vec_per_row;
+      const int64_t src = (int64_t)rows[o0 + m] * vec_per_row + (i - m * vec_per_row);
+      kk[u] = k[src];
+      vv[u] = v[src];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + u * kThreads;
+      if (i < items) { k_out[out + i] = kk[u]; v_out[out + i] = vv[u]; }
+    }
+  }
+}
+
 }  // namespace
 
 size_t select_workspace(int32_t, int64_t) { return 0; }
@@ -249,6 +293,45 @@ qcf_status launch_select(int32_t B, const float* score, const int64_t* ctx_off, 
   else QCF_LAUNCH(0);
 #undef QCF_LAUNCH
   return check_launch("select");
+}
+
+// A workgroup copies what its chunk selected up to this many 16-byte vectors of keys (64 rows of 8 heads of 128); with more
+// the copy is a launch over all of them (64 chunks of 1024, 128 rows each: 56 us by the workgroups, 44 with the launch; 64
+// rows each: 43 both ways).
+constexpr int64_t kGatherVecs = 8192;
+
+qcf_status launch_select_gather(const qcf_layer_desc& L, const float* score, int32_t n_chunks, const int64_t* ctx_off,
+                                const int64_t* sel_off, const void* k, const void* v, int32_t* rows, void* k_out, void* v_out,
+                                hipStream_t st) {
+  const int vec_per_row = L.n_kv_heads * L.head_dim * elem_size(L.dtype) / 16;
+  const int64_t total_ctx = ctx_off[n_chunks], total_sel = sel_off[n_chunks];
+  auto ctx = [&](int32_t c) { return std::min(std::max(ctx_off[c], (int64_t)0), total_ctx); };
+  auto sel = [&](int32_t c) { return std::min(std::max(sel_off[c], (int64_t)0), total_sel); };
+  int64_t longest = 0, most = 0;
+  for (int32_t c = 0; c < n_chunks; ++c) {
+    longest = std::max(longest, ctx(c + 1) - ctx(c));
+    most = std::max(most, std::min(ctx(c + 1) - ctx(c), sel(c + 1) - sel(c)));
+  }
+  const bool gather = most * vec_per_row <= kGatherVecs;
+  for (int32_t first = 0; first < n_chunks; first += kAnchorChunks) {
+    const int n = std::min(kAnchorChunks, n_chunks - first);
+    AnchorChunks ch;
+    for (int i = 0; i <= n; ++i) {
+      ch.ctx[i] = (int32_t)ctx(first + i);
+      ch.sel[i] = (int32_t)sel(first + i);
+    }
+#define QCF_LAUNCH(MAX)                                                                              \
+  select_gather_kernel<MAX><<<dim3((unsigned)n), dim3(kThreads), 0, st>>>(                           \
+      score, ch, static_cast<const u32x4*>(k), static_cast<const u32x4*>(v), vec_per_row, rows,      \
+      gather ? static_cast<u32x4*>(k_out) : nullptr, static_cast<u32x4*>(v_out))
+    if (longest <= kThreads) QCF_LAUNCH(1);
+    else if (longest <= 8 * kThreads) QCF_LAUNCH(8);
+    else if (longest <= 32 * kThreads) QCF_LAUNCH(32);
+    else QCF_LAUNCH(0);
+#undef QCF_LAUNCH
+    QCF_TRY_LAUNCH("anchor select");
+  }
+  return gather ? QCF_OK : launch_gather(L, k, v, rows, total_sel, total_ctx, k_out, v_out, st);
 }
 
 }  // namespace qcf

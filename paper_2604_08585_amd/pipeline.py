@@ -255,29 +255,22 @@ def layer_tail(desc, h_in: torch.Tensor, o_rows: torch.Tensor, tw: TailWeights) 
 
 def extract_anchors(desc, k: torch.Tensor, v: torch.Tensor, chunk_lens: List[int], n_per_chunk: List[int]):
     """For chunks stored back to back in k / v [sum len, H_kv, d]: the n_c tokens of chunk c with the largest key
-    norm.  Returns (rows into k / v, ascending inside each chunk; anchor K rows; anchor V rows).  Three library
-    calls: key norm, Top-N per chunk (the selection kernel with one "request" per chunk), gather."""
+    norm.  Returns (rows into k / v, ascending inside each chunk; anchor K rows; anchor V rows).  One library call:
+    key norm, then one workgroup per chunk that selects and copies."""
     dev = k.device
     if dev.type == "cuda" and torch.cuda.is_current_stream_capturing():
-        # a replay would copy the offsets from host memory that has been given back by then
-        raise RuntimeError("extract_anchors cannot be captured into a graph: it copies its offsets from the host")
-    # both offset tables in one pinned block and one asynchronous copy (two pageable copies made the host wait twice)
+        # a replay would take the offsets of this call whatever the chunks have become
+        raise RuntimeError("extract_anchors cannot be captured into a graph: its offsets come from the host")
     n = len(chunk_lens)
-    off = torch.zeros(2, n + 1, dtype=torch.int64, pin_memory=dev.type == "cuda")
-    offs = off.numpy()
+    off = np.zeros((2, n + 1), dtype=np.int64)
     lens = np.asarray(chunk_lens, dtype=np.int64)
-    np.cumsum(lens, out=offs[0, 1:])
-    np.cumsum(np.minimum(np.asarray(n_per_chunk[:n], dtype=np.int64), lens), out=offs[1, 1:])
-    rows, total = int(offs[0, n]), int(offs[1, n])
-    norm = torch.empty(max(rows, 1), dtype=torch.float32, device=dev)
-    qb.qcf_key_norm(desc, k, rows, norm)
-    ctx_off, sel_off = off.to(dev, non_blocking=True)
-    idx = torch.empty(max(total, 1), dtype=torch.int32, device=dev)
+    np.cumsum(lens, out=off[0, 1:])
+    np.cumsum(np.minimum(np.asarray(n_per_chunk[:n], dtype=np.int64), lens), out=off[1, 1:])
+    total = int(off[1, n])
     row = torch.empty(max(total, 1), dtype=torch.int32, device=dev)
-    qb.qcf_select(n, norm, ctx_off, rows, sel_off, total, None, idx, row, None)
     ak = torch.empty((max(total, 1),) + tuple(k.shape[1:]), dtype=k.dtype, device=dev)
     av = torch.empty_like(ak)
-    qb.qcf_gather(desc, k, v, row, total, rows, ak, av)
+    qb.qcf_extract_anchors(desc, k, v, off[0], off[1], row, ak, av)
     return row[:total], ak[:total], av[:total]
 
 
