@@ -151,7 +151,8 @@ def score_over_layers(desc, probes: List[torch.Tensor], keys: List[torch.Tensor]
     selector), all layers in one call.  probes[l] [total_probe, H, d] and
     keys[l] [total_ctx, H_kv, d] belong to layer l; weights default to the mean."""
     n = len(keys)
-    w = [1.0 / n] * n if weights is None else [float(weights[l]) for l in range(n)]
+    w = [1.0 / n] * n if weights is None else list(weights)
+    w = [float(w[l]) for l in range(n)]
     total_probe, total_ctx = int(probes[0].shape[0]), int(keys[0].shape[0])
     B = int(probe_off.numel()) - 1
     score = torch.empty(max(total_ctx, 1), dtype=torch.float32, device=keys[0].device)
@@ -253,6 +254,17 @@ def layer_tail(desc, h_in: torch.Tensor, o_rows: torch.Tensor, tw: TailWeights) 
 
 # ------------------------------------------------------------------ anchor extraction (offline)
 
+def _counts(values, n: int) -> np.ndarray:
+    """The first n of some whole numbers: a list, an array, a tensor on any device, or anything that can be iterated."""
+    try:
+        a = np.asarray(values[:n], dtype=np.int64)
+    except TypeError:                                     # (no slices, or elements that NumPy does not take)
+        a = np.asarray([int(v) for _, v in zip(range(n), values)], dtype=np.int64)
+    if a.shape != (n,):                                   # (one value would be broadcast)
+        raise ValueError(f"{a.shape} values for {n} chunks")
+    return a
+
+
 def extract_anchors(desc, k: torch.Tensor, v: torch.Tensor, chunk_lens: List[int], n_per_chunk: List[int]):
     """For chunks stored back to back in k / v [sum len, H_kv, d]: the n_c tokens of chunk c with the largest key
     norm.  Returns (rows into k / v, ascending inside each chunk; anchor K rows; anchor V rows).  One library call:
@@ -265,7 +277,7 @@ def extract_anchors(desc, k: torch.Tensor, v: torch.Tensor, chunk_lens: List[int
     off = np.zeros((2, n + 1), dtype=np.int64)
     lens = np.asarray(chunk_lens, dtype=np.int64)
     np.cumsum(lens, out=off[0, 1:])
-    np.cumsum(np.minimum(np.asarray(n_per_chunk[:n], dtype=np.int64), lens), out=off[1, 1:])
+    np.cumsum(np.minimum(_counts(n_per_chunk, n), lens), out=off[1, 1:])
     total = int(off[1, n])
     row = torch.empty(max(total, 1), dtype=torch.int32, device=dev)
     ak = torch.empty((max(total, 1),) + tuple(k.shape[1:]), dtype=k.dtype, device=dev)
