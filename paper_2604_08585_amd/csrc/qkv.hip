@@ -1084,6 +1084,20 @@ size_t split_part_bytes(int64_t M, int nb, int bm, int splits) {
   return splits <= 1 ? 0 : (size_t)splits * nb * ((M + bm - 1) / bm) * bm * kBN * sizeof(float);
 }
 
+// Main launch of a contraction in `s` ranges of `len` k-tiles over one row tile, which streams its weights: a workgroup waits
+// for memory (0.44 and 0.55 us per k-tile of 64 and 128 rows), all together for its bandwidth (the more compute units load,
+// the more there is; ranges that start 4 KB, 32 k-tiles, apart get a fifth less), and the reduction takes a quarter of a
+// microsecond per range beside what the partial sums take.  Calls in ranges, us, 61 rows: K 14336, N 4096 in 4, 6, 7, 8 and
+// 12 of them 37.2, 31.1, 34.8, 29.0, 36.5; K 8192, N 8192 in 2, 3, 4 42.2, 34.1, 40.7; K 2048, N 2048 in 4 and 8 10.1, 11.2.
+// 110 rows: 44.1, 37.3, 38.9, 37.2, 41.7; 49.6, 39.9, 43.3; K 4096, N 6144 in 3, 4, 5 21.5, 19.7, 21.9.  (With 4.6 TB/s for
+// any launch, behind its start, the first of each three to five were chosen, and 8 of K 2048.)
+double stream_us(int bm, int nb, int nk, int s, int len) {
+  const double r = rounds_of((int64_t)nb * s), share = std::min(1.0, (double)nb * s / compute_unit_count());
+  const double tb_s = (3.6 + 1.5 * share) * (s > 1 && len % 32 == 0 ? 0.82 : 1.0);
+  return std::max(r * (bm == 64 ? 0.44 : 0.55) * len + r * 6.0, (double)nb * nk * (kBN * kBK * 2) / (tb_s * 1e6)) +
+         (s > 1 ? 0.25 * s : 0.0);
+}
+
 // the load/compute-split kernels, over nb column blocks, with at most part_bytes of partial sums
 GemmPlan plan_ws(int64_t M, int nb, int nk, size_t part_bytes) {
   GemmPlan best{kWs256, 1, ws256_us((M + 255) / 256, nb, nk)};
@@ -1096,7 +1110,8 @@ GemmPlan plan_ws(int64_t M, int nb, int nk, size_t part_bytes) {
     if (split_part_bytes(M, nb, bm, s) > part_bytes || (s > 1 && nb > 65535)) break;      // (grid.y of the reduction)
     const int len = (nk + s - 1) / s;
     if ((nk + len - 1) / len != s) continue;                     // (a range would be empty)
-    double t = std::max(rounds_of(tiles * s) * c * len, (double)nb * nk * (kBN * kBK * 2) / 4.6e6) + rounds_of(tiles * s) * 6.0;
+    double t = tiles == nb ? stream_us(bm, nb, nk, s, len)
+                           : std::max(rounds_of(tiles * s) * c * len, (double)nb * nk * (kBN * kBK * 2) / 4.6e6) + rounds_of(tiles * s) * 6.0;
     if (s > 1) t += 4.0 + (double)tiles * bm * kBN * 8.0 * s / 4.0e6;
     if (t < best.us) best = GemmPlan{bm == 64 ? kWs64 : kWs128, s, t};
   }
