@@ -1,5 +1,5 @@
-"""Products whose contraction is split over 256 x 256 tiles, against float32: ragged rows, an odd number of column blocks,
-ranges of unequal length, the rotation and the gated SiLU behind the reduction."""
+"""Products whose contraction is split, against float32: over 256 x 256 tiles (ragged rows, an odd number of column blocks,
+ranges of unequal length, the rotation and the gated SiLU behind the reduction), and weight streams for few rows."""
 import pytest
 import torch
 
@@ -48,6 +48,22 @@ def test_linear(M, K, N, splits, res):
     torch.cuda.synchronize()
     _one_rounding(outs[0][:M], ref)
     assert torch.equal(outs[0], outs[1]) and bool((outs[0][M] == 7.0).all())
+
+
+@pytest.mark.parametrize("M,K,N,splits", [
+    (1, 14336, 4096, 8), (61, 14336, 4096, 8), (64, 8192, 8192, 3),      # 43, 43 and 42 k-tiles
+    (65, 4096, 6144, 4), (110, 8192, 8192, 3), (128, 14336, 2048, 14)])
+def test_weight_stream(M, K, N, splits):
+    """One row tile of 64 or 128 rows: the ranges that its weight stream is cut into."""
+    print(f"weight stream M={M} K={K} N={N}", flush=True)
+    desc = qb.make_desc(DESC)
+    assert qb.qcf_linear_workspace_bytes(desc, M, K, N) == splits * (64 if M <= 64 else 128) * N * 4
+    x, w, r = _normal(9, M, K), _normal(10, N, K, std=K ** -0.5), _normal(11, M, N)
+    out = torch.full((M + 1, N), 7.0, dtype=BF, device=DEV)
+    qb.qcf_linear(desc, x, M, K, w, N, r, out)
+    torch.cuda.synchronize()
+    _one_rounding(out[:M], x.float() @ w.float().T + r.float())
+    assert bool((out[M] == 7.0).all())
 
 
 def test_projection_with_write_back():
