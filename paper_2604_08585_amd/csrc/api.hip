@@ -4,6 +4,7 @@
 #include <cmath>
 
 #include "qcf_internal.h"
+#include "score_layout.h"
 
 namespace qcf {
 
@@ -170,7 +171,7 @@ qcf_status qcf_rerope(const qcf_layer_desc* desc, const qcf_chunk* chunks_dev, i
 size_t qcf_score_workspace_bytes(const qcf_layer_desc* desc, int32_t B, int64_t total_probe,
                                  int64_t total_ctx) {
   if (check_desc(desc) != QCF_OK || B <= 0 || total_probe <= 0 || total_ctx <= 0) return 0;
-  return score_workspace(*desc, B, total_probe, total_ctx);
+  return scoring::workspace(*desc, B, total_probe, total_ctx);
 }
 
 qcf_status qcf_score(const qcf_layer_desc* desc, int32_t B, const void* q_probe,
@@ -181,7 +182,7 @@ qcf_status qcf_score(const qcf_layer_desc* desc, int32_t B, const void* q_probe,
   QCF_TRY(check_score_args(desc, B, q_probe, probe_off_dev, total_probe, k_fused, ctx_off_dev, total_ctx,
                            probe_limit_dev, score, &empty));
   if (empty) return QCF_OK;
-  QCF_TRY(need_ws(workspace, workspace_bytes, score_workspace(*desc, B, total_probe, total_ctx)));
+  QCF_TRY(need_ws(workspace, workspace_bytes, scoring::workspace(*desc, B, total_probe, total_ctx)));
   return launch_score(*desc, B, q_probe, probe_off_dev, total_probe, k_fused, ctx_off_dev, total_ctx,
                       probe_limit_dev, score, 1.f, 0.f, workspace, (hipStream_t)stream);
 }
@@ -196,7 +197,7 @@ qcf_status qcf_score_accumulate(const qcf_layer_desc* desc, int32_t B, const voi
                            probe_limit_dev, score, &empty));
   if (!std::isfinite(alpha) || !std::isfinite(beta)) return fail(QCF_ERR_INVALID_ARG, "alpha and beta must be finite");
   if (empty) return QCF_OK;
-  QCF_TRY(need_ws(workspace, workspace_bytes, score_workspace(*desc, B, total_probe, total_ctx)));
+  QCF_TRY(need_ws(workspace, workspace_bytes, scoring::workspace(*desc, B, total_probe, total_ctx)));
   return launch_score(*desc, B, q_probe, probe_off_dev, total_probe, k_fused, ctx_off_dev, total_ctx,
                       probe_limit_dev, score, alpha, beta, workspace, (hipStream_t)stream);
 }
@@ -204,7 +205,7 @@ qcf_status qcf_score_accumulate(const qcf_layer_desc* desc, int32_t B, const voi
 size_t qcf_score_layers_workspace_bytes(const qcf_layer_desc* desc, int32_t n_layers, int32_t B, int64_t total_probe,
                                         int64_t total_ctx) {
   if (check_desc(desc) != QCF_OK || n_layers <= 0 || B <= 0 || total_probe <= 0 || total_ctx <= 0) return 0;
-  return score_layers_workspace(*desc, n_layers, B, total_probe, total_ctx);
+  return scoring::layers_workspace(*desc, n_layers, B, total_probe, total_ctx);
 }
 
 qcf_status qcf_score_layers(const qcf_layer_desc* desc, int32_t n_layers, int32_t B, const void* const* q_probe,
@@ -221,7 +222,7 @@ qcf_status qcf_score_layers(const qcf_layer_desc* desc, int32_t n_layers, int32_
   }
   if (empty) return QCF_OK;
   QCF_TRY(need_ws(workspace, workspace_bytes,
-                  total_probe > 0 ? score_layers_workspace(*desc, n_layers, B, total_probe, total_ctx) : 0));
+                  total_probe > 0 ? scoring::layers_workspace(*desc, n_layers, B, total_probe, total_ctx) : 0));
   return launch_score_layers(*desc, n_layers, B, q_probe, probe_off_dev, total_probe, k_fused, ctx_off_dev, total_ctx,
                              probe_limit_dev, weights, score, workspace, (hipStream_t)stream);
 }

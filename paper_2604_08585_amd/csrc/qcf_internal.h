@@ -198,12 +198,10 @@ qcf_status check_score_args(const qcf_layer_desc* desc, int32_t B, const void* q
                             const int64_t* probe_off_dev, int64_t total_probe, const void* k_fused,
                             const int64_t* ctx_off_dev, int64_t total_ctx, const int32_t* probe_limit_dev,
                             float* score, bool* empty);
-size_t score_workspace(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx);
 qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const int64_t* probe_off,
                         int64_t total_probe, const void* k, const int64_t* ctx_off, int64_t total_ctx,
                         const int32_t* probe_limit, float* score, float alpha, float beta, void* ws, hipStream_t st);
 
-size_t score_layers_workspace(const qcf_layer_desc& L, int32_t n_layers, int32_t B, int64_t total_probe, int64_t total_ctx);
 qcf_status launch_score_layers(const qcf_layer_desc& L, int32_t n_layers, int32_t B, const void* const* q,
                                const int64_t* probe_off, int64_t total_probe, const void* const* k, const int64_t* ctx_off,
                                int64_t total_ctx, const int32_t* probe_limit, const float* weights, float* score, void* ws,

@@ -33,8 +33,10 @@
 // Generic path (f32, or other head dims): one workgroup per (probe row, head) materialises its
 // softmax row in the workspace, then a column mean.
 #include "qcf_internal.h"
+#include "score_layout.h"
 
 namespace qcf {
+using namespace scoring;
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -134,13 +136,11 @@ __global__ __launch_bounds__(kColThreads) void score_colmean_generic(
 
 // ------------------------------------------------------------------ MFMA path (bf16, d = 128 or 64)
 
-constexpr int kTokPerWave = 64;                 // tokens a wave keeps stationary in registers
 constexpr int kTokWaves = 4;                    // token slices of a workgroup
+constexpr int kTokPerWave = kTokPerWg / kTokWaves;      // tokens a wave keeps stationary in registers
 constexpr int kRowGroups = 3;                   // waves per token slice, which share a SIMD and share out the row tiles
 constexpr int kWavesPerWg = kTokWaves * kRowGroups;
 constexpr int kThreads = 64 * kWavesPerWg;
-constexpr int kTokPerWg = kTokPerWave * kTokWaves;
-constexpr int kRowBlock = 320;                  // probe rows (of one group) staged in LDS at a time
 template <int D> constexpr size_t kQBytes = (size_t)kRowBlock * D * 2;     // staged rows: swizzled, no padding
 template <int D> constexpr size_t kKBytes = (size_t)kTokPerWg * D * 2;
 template <int D> constexpr float kK2 = kLog2e * (D == 128 ? 0.08838834764831845f : 0.125f);    // log2(e) / sqrt(D)
@@ -155,7 +155,6 @@ template <int D> __device__ __forceinline__ int staged_elem(int r, int lane) { r
 // byte offset of this lane's fragment (row lane%32, chunk 2*ks + lane/32) is frag_base ^ (32 * ks)
 template <int D> __device__ __forceinline__ int frag_base(int lane) { return (lane & 31) * 2 * D + slot_of<D>(lane >> 5, lane & 31) * 16; }
 constexpr int kFoldBatch = 16;
-constexpr int kMaxLayers = 16;                  // layers scored by one set of launches
 // The passes keep a row's maximum and the reciprocal of its sum apart instead of one log-sum-exp, whose rounding weighs
 // once logits reach a hundred (heads of 64, largest logit 586: 8.7e-6 off in the 2-norm, now 1.7e-6, the general kernels
 // 1.9e-6; largest 12: 1.6e-7, 8.3e-8, 5.3e-7; heads of 128, 80 rows over 32768 tokens: 1.9e-7, 7.0e-8).  Heads of 64: a NaN
@@ -621,7 +620,6 @@ constexpr int kFusedWaves = 8;
 constexpr int kFusedThreads = 64 * kFusedWaves;
 constexpr int kFusedRowTiles = kRowBlock / 32;
 constexpr int kSyncSlots = 8;
-constexpr int kSyncWords = 1024;           // counters per slot: [0] finished workgroups, then groups, then tiles
 constexpr uint32_t kSpinLimit = 1u << 20;  // polls (a microsecond or two each) before a workgroup gives up waiting
 
 __device__ uint32_t g_sync[kSyncSlots * kSyncWords];
@@ -912,59 +910,11 @@ __global__ __launch_bounds__(256) void score_zero(float* score, int64_t n, float
   if (j < n) score[j] = (beta == 0.f) ? 0.f : beta * score[j];
 }
 
-
-// upper bound on the 256-token tiles of all requests (tiles start at request boundaries: every request adds at
-// most one partly filled tile); exact for a single request
-int64_t n_tiles_upper(int32_t B, int64_t total_ctx) { return (total_ctx + (int64_t)B * (kTokPerWg - 1)) / kTokPerWg; }
-
-struct MfmaWs { size_t part, colsum, total; };
-MfmaWs mfma_ws(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx) {
-  MfmaWs w;
-  w.part = 0;
-  size_t off = align_up((size_t)n_tiles_upper(B, total_ctx) * total_probe * L.n_q_heads * sizeof(float2), 256);
-  w.colsum = off;
-  off += align_up((size_t)L.n_kv_heads * total_ctx * sizeof(float), 256);
-  w.total = off;
-  return w;
-}
-
 template <int D> constexpr size_t kPass1Lds = kQBytes<D> + kKBytes<D> + (size_t)kTokWaves * kRowBlock * sizeof(float2);
 template <int D> constexpr size_t kPass2Lds = kQBytes<D> + kKBytes<D> + kRowBlock * 4 * 3 + (size_t)kRowGroups * kTokPerWg * sizeof(float);
 constexpr size_t kFusedLds = kQBytes<128> + kKBytes<128>;
 static_assert((size_t)kFusedWaves * kRowBlock * 8 + (size_t)kRowBlock * 4 + (size_t)kTokPerWg * 4 <= kKBytes<128>,
               "the single-kernel path's tables fit in the key tile's LDS");
-
-bool use_mfma(const qcf_layer_desc& L) { return L.dtype == QCF_DTYPE_BF16 && (L.head_dim == 128 || L.head_dim == 64); }
-size_t generic_ws(const qcf_layer_desc& L, int64_t total_probe, int64_t total_ctx) {
-  return align_up((size_t)total_probe * L.n_q_heads * total_ctx * sizeof(float), 256);
-}
-
-// The single-kernel path needs every workgroup of the launch resident at once (one per compute unit) and all
-// probe rows of a KV group in one staged block.  The host only knows totals, so the test is on those.  Heads of 64 never
-// take it: their calls may overlap on any number of streams, which the counter sets of this path (kSyncSlots) and its wait
-// for workgroups that another launch may keep off the chip do not allow.
-bool use_fused(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx) {
-  if (!use_mfma(L) || L.head_dim != 128 || total_probe <= 0) return false;
-  const int64_t G = L.n_q_heads / L.n_kv_heads;
-  const int64_t tiles = n_tiles_upper(B, total_ctx);
-  return total_probe * G <= kRowBlock && tiles * L.n_kv_heads <= compute_unit_count() &&
-         1 + (int64_t)B * L.n_kv_heads + tiles <= kSyncWords;
-}
-// Two MFMA passes.  Heads of 64 keep the generic kernels where many short requests would make the partials (one per
-// started 256 tokens) larger than its probability rows and than the built-in scratch of qcf_score_static.
-bool use_two_pass(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx) {
-  return use_mfma(L) && (L.head_dim == 128 || mfma_ws(L, B, total_probe, total_ctx).total <=
-                             std::max(generic_ws(L, total_probe, total_ctx), (size_t)QCF_SCORE_STATIC_SCRATCH_BYTES));
-}
-struct FusedWs { size_t part, colpart, total; };
-FusedWs fused_ws(const qcf_layer_desc& L, int32_t B, int64_t total_ctx) {
-  const size_t slots = (size_t)n_tiles_upper(B, total_ctx) * L.n_kv_heads;
-  FusedWs w;
-  w.part = 0;
-  w.colpart = align_up(slots * kRowBlock * sizeof(float2), 256);
-  w.total = w.colpart + align_up(slots * kTokPerWg * sizeof(float), 256);
-  return w;
-}
 
 template <bool LIMIT>
 qcf_status run_fused(const FusedArgs& fa, hipStream_t st) {
@@ -972,32 +922,6 @@ qcf_status run_fused(const FusedArgs& fa, hipStream_t st) {
   QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_fused<LIMIT>), kFusedLds, lds_ok));
   score_fused<LIMIT><<<dim3((unsigned)(fa.n_wg_tiles * fa.s.Hkv)), dim3(kFusedThreads), kFusedLds, st>>>(fa);
   return check_launch("score (single kernel)");
-}
-// Tiles that a workgroup of the two passes takes in turn.  A workgroup spends about as long on staging probe rows and on its
-// sums as on kUnitCost tiles; where a launch is a few rounds long whole rounds count, otherwise the tail is about half a
-// unit.  (32768 tokens, 8 KV heads: units of four tiles, one round; with one tile to a unit pass 2 alone took 149 us, now 71.)
-constexpr double kUnitCost = 1.5;
-int unit_tiles_for(int32_t B, int64_t total_ctx, int64_t heads_layers) {
-  const int64_t nt = n_tiles_upper(B, total_ctx);
-  const double cus = compute_unit_count();
-  int best = 1;
-  double best_cost = 0;
-  for (int ul = 1; ul <= 64 && ul <= nt; ++ul) {
-    const double per_cu = (double)((nt + ul - 1) / ul + (B - 1) / 2) * (double)heads_layers / cus;
-    const double cost = (per_cu <= 3.0 ? std::ceil(per_cu) : per_cu + 0.5) * (ul + kUnitCost);
-    if (ul == 1 || cost < best_cost) { best = ul; best_cost = cost; }
-  }
-  return best;
-}
-struct PassWs { int unit_tiles; int64_t n_units; size_t colsum, total; };
-PassWs pass_ws(const qcf_layer_desc& L, int n_layers, int32_t B, int64_t total_probe, int64_t total_ctx) {
-  PassWs w;
-  w.unit_tiles = unit_tiles_for(B, total_ctx, (int64_t)L.n_kv_heads * n_layers);
-  // (every request may end in a unit that is not full; with one tile per unit these are the tiles themselves)
-  w.n_units = (n_tiles_upper(B, total_ctx) + (int64_t)B * (w.unit_tiles - 1)) / w.unit_tiles;
-  w.colsum = align_up((size_t)n_layers * w.n_units * total_probe * L.n_q_heads * sizeof(float2), 256);
-  w.total = w.colsum + align_up((size_t)n_layers * L.n_kv_heads * total_ctx * sizeof(float), 256);
-  return w;
 }
 
 template <int D, bool LIMIT>
@@ -1077,12 +1001,6 @@ qcf_status sync_counters(uint32_t** out) {
 
 }  // namespace
 
-size_t score_workspace(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx) {
-  if (use_fused(L, B, total_probe, total_ctx)) return fused_ws(L, B, total_ctx).total;
-  if (use_two_pass(L, B, total_probe, total_ctx)) return mfma_ws(L, B, total_probe, total_ctx).total;
-  return generic_ws(L, total_probe, total_ctx);
-}
-
 qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const int64_t* probe_off,
                         int64_t total_probe, const void* k, const int64_t* ctx_off, int64_t total_ctx,
                         const int32_t* probe_limit, float* score, float alpha, float beta, void* ws, hipStream_t st) {
@@ -1130,29 +1048,10 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
     fa.sync = counters + (size_t)(next_slot.fetch_add(1, std::memory_order_relaxed) % kSyncSlots) * kSyncWords;
     return probe_limit ? run_fused<true>(fa, st) : run_fused<false>(fa, st);
   }
-  // (qcf_score_workspace_bytes gives the partials of every tile room; with several tiles to a unit less is used)
   return launch_two_pass(L, a, 1, &q, &k, &alpha, ws, st);
 }
 
 // ---- several layers --------------------------------------------------------------------------------
-// Layers scored by one set of launches: as many as keep the workspace within that of a single call, or 64 MiB.  One where
-// the two passes do not apply.
-static int layers_at_once(const qcf_layer_desc& L, int32_t n_layers, int32_t B, int64_t total_probe, int64_t total_ctx) {
-  if (total_probe <= 0 || L.head_dim != 128 || !use_two_pass(L, B, total_probe, total_ctx)) return 1;
-  const size_t limit = std::max(score_workspace(L, B, total_probe, total_ctx), (size_t)64 << 20);
-  int n = std::min(n_layers, kMaxLayers);
-  while (n > 1 && pass_ws(L, n, B, total_probe, total_ctx).total > limit) --n;
-  return n;
-}
-
-size_t score_layers_workspace(const qcf_layer_desc& L, int32_t n_layers, int32_t B, int64_t total_probe, int64_t total_ctx) {
-  const int n = layers_at_once(L, n_layers, B, total_probe, total_ctx);
-  size_t need = score_workspace(L, B, total_probe, total_ctx);
-  if (n > 1) need = std::max(need, pass_ws(L, n, B, total_probe, total_ctx).total);
-  if (n > 1 && n_layers % n > 1) need = std::max(need, pass_ws(L, n_layers % n, B, total_probe, total_ctx).total);
-  return need;
-}
-
 qcf_status launch_score_layers(const qcf_layer_desc& L, int32_t n_layers, int32_t B, const void* const* q,
                                const int64_t* probe_off, int64_t total_probe, const void* const* k, const int64_t* ctx_off,
                                int64_t total_ctx, const int32_t* probe_limit, const float* weights, float* score, void* ws,
@@ -1211,7 +1110,7 @@ extern "C" qcf_status qcf_score_static(const qcf_layer_desc* desc, int32_t B, co
   QCF_TRY(qcf::check_score_args(desc, B, q_probe, probe_off_dev, total_probe, k_fused, ctx_off_dev, total_ctx,
                                 probe_limit_dev, score, &empty));
   if (empty) return QCF_OK;
-  const size_t need = qcf::score_workspace(*desc, B, total_probe, total_ctx);
+  const size_t need = qcf::scoring::workspace(*desc, B, total_probe, total_ctx);
   if (need > (size_t)QCF_SCORE_STATIC_SCRATCH_BYTES)
     return qcf::fail(QCF_ERR_WORKSPACE_TOO_SMALL,
                      "qcf_score_static: this problem needs %zu bytes of scratch, the built-in buffer has %zu; "

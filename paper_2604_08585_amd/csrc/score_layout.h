@@ -1,0 +1,127 @@
+// Which scoring kernels a call takes, and how each of them divides its workspace.  The sizes that the library reports and
+// the ones that its launches use come from the same functions.  Plain host code as well (no HIP header).
+#pragma once
+
+#include <math.h>
+#include <stddef.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "qcf.h"
+
+namespace qcf {
+
+int compute_unit_count();
+
+namespace scoring {
+
+constexpr int kTokPerWg = 256;                  // tokens of a tile
+constexpr int kRowBlock = 320;                  // probe rows (of one group) staged in LDS at a time
+constexpr int kMaxLayers = 16;                  // layers scored by one set of launches
+constexpr int kSyncWords = 1024;                // counters of a single-kernel launch: finished workgroups, groups, tiles
+constexpr size_t kPair = 2 * sizeof(float);     // a row's partial: (maximum, sum)
+
+inline size_t aligned(size_t n) { return (n + 255) / 256 * 256; }
+
+// upper bound on the 256-token tiles of all requests (tiles start at request boundaries: every request adds at
+// most one partly filled tile); exact for a single request
+inline int64_t n_tiles_upper(int32_t B, int64_t total_ctx) { return (total_ctx + (int64_t)B * (kTokPerWg - 1)) / kTokPerWg; }
+
+inline bool use_mfma(const qcf_layer_desc& L) { return L.dtype == QCF_DTYPE_BF16 && (L.head_dim == 128 || L.head_dim == 64); }
+inline size_t generic_ws(const qcf_layer_desc& L, int64_t total_probe, int64_t total_ctx) {
+  return aligned((size_t)total_probe * L.n_q_heads * total_ctx * sizeof(float));
+}
+
+// Two passes: the partials of every unit of tiles, then the column sums.
+struct PassWs { int unit_tiles; int64_t n_units; size_t colsum, total; };
+inline PassWs pass_ws_of(const qcf_layer_desc& L, int n_layers, int unit_tiles, int64_t n_units, int64_t total_probe,
+                         int64_t total_ctx) {
+  PassWs w;
+  w.unit_tiles = unit_tiles;
+  w.n_units = n_units;
+  w.colsum = aligned((size_t)n_layers * n_units * total_probe * L.n_q_heads * kPair);
+  w.total = w.colsum + aligned((size_t)n_layers * L.n_kv_heads * total_ctx * sizeof(float));
+  return w;
+}
+// Tiles that a workgroup of the two passes takes in turn.  A workgroup spends about as long on staging probe rows and on its
+// sums as on kUnitCost tiles; where a launch is a few rounds long whole rounds count, otherwise the tail is about half a
+// unit.  (32768 tokens, 8 KV heads: units of four tiles, one round; with one tile to a unit pass 2 alone took 149 us, now 71.)
+constexpr double kUnitCost = 1.5;
+inline int unit_tiles_for(int32_t B, int64_t total_ctx, int64_t heads_layers) {
+  const int64_t nt = n_tiles_upper(B, total_ctx);
+  const double cus = compute_unit_count();
+  int best = 1;
+  double best_cost = 0;
+  for (int ul = 1; ul <= 64 && ul <= nt; ++ul) {
+    const double per_cu = (double)((nt + ul - 1) / ul + (B - 1) / 2) * (double)heads_layers / cus;
+    const double cost = (per_cu <= 3.0 ? ceil(per_cu) : per_cu + 0.5) * (ul + kUnitCost);
+    if (ul == 1 || cost < best_cost) { best = ul; best_cost = cost; }
+  }
+  return best;
+}
+// What the launches of n_layers layers use.  A request of nt tiles has ceil(nt / unit_tiles) units: every request may end in a
+// unit that is not full, but none has more units than tiles (with more requests than tokens the first bound is the larger).
+inline PassWs pass_ws(const qcf_layer_desc& L, int n_layers, int32_t B, int64_t total_probe, int64_t total_ctx) {
+  const int unit_tiles = unit_tiles_for(B, total_ctx, (int64_t)L.n_kv_heads * n_layers);
+  const int64_t nt = n_tiles_upper(B, total_ctx);
+  const int64_t n_units = std::min(nt, (nt + (int64_t)B * (unit_tiles - 1)) / unit_tiles);
+  return pass_ws_of(L, n_layers, unit_tiles, n_units, total_probe, total_ctx);
+}
+// The size reported for one layer: one tile to a unit, at least what pass_ws gives.
+inline size_t two_pass_bytes(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx) {
+  return pass_ws_of(L, 1, 1, n_tiles_upper(B, total_ctx), total_probe, total_ctx).total;
+}
+// Heads of 64 keep the generic kernels where many short requests would make the partials (one per started 256 tokens)
+// larger than its probability rows and than the built-in scratch of qcf_score_static.
+inline bool use_two_pass(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx) {
+  return use_mfma(L) && (L.head_dim == 128 || two_pass_bytes(L, B, total_probe, total_ctx) <=
+                             std::max(generic_ws(L, total_probe, total_ctx), (size_t)QCF_SCORE_STATIC_SCRATCH_BYTES));
+}
+
+// The single-kernel path needs every workgroup of the launch resident at once (one per compute unit) and all
+// probe rows of a KV group in one staged block.  The host only knows totals, so the test is on those.  Heads of 64 never
+// take it: their calls may overlap on any number of streams, which the counter sets of this path (kSyncSlots) and its wait
+// for workgroups that another launch may keep off the chip do not allow.
+inline bool use_fused(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx) {
+  if (!use_mfma(L) || L.head_dim != 128 || total_probe <= 0) return false;
+  const int64_t G = L.n_q_heads / L.n_kv_heads;
+  const int64_t tiles = n_tiles_upper(B, total_ctx);
+  return total_probe * G <= kRowBlock && tiles * L.n_kv_heads <= compute_unit_count() &&
+         1 + (int64_t)B * L.n_kv_heads + tiles <= kSyncWords;
+}
+struct FusedWs { size_t part, colpart, total; };
+inline FusedWs fused_ws(const qcf_layer_desc& L, int32_t B, int64_t total_ctx) {
+  const size_t slots = (size_t)n_tiles_upper(B, total_ctx) * L.n_kv_heads;
+  FusedWs w;
+  w.part = 0;
+  w.colpart = aligned(slots * kRowBlock * kPair);
+  w.total = w.colpart + aligned(slots * kTokPerWg * sizeof(float));
+  return w;
+}
+
+// One layer.
+inline size_t workspace(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx) {
+  if (use_fused(L, B, total_probe, total_ctx)) return fused_ws(L, B, total_ctx).total;
+  if (use_two_pass(L, B, total_probe, total_ctx)) return two_pass_bytes(L, B, total_probe, total_ctx);
+  return generic_ws(L, total_probe, total_ctx);
+}
+// Layers scored by one set of launches: as many as keep the workspace within that of a single call, or 64 MiB.  One where
+// the two passes do not apply.
+inline int layers_at_once(const qcf_layer_desc& L, int32_t n_layers, int32_t B, int64_t total_probe, int64_t total_ctx) {
+  if (total_probe <= 0 || L.head_dim != 128 || !use_two_pass(L, B, total_probe, total_ctx)) return 1;
+  const size_t limit = std::max(workspace(L, B, total_probe, total_ctx), (size_t)64 << 20);
+  int n = std::min(n_layers, kMaxLayers);
+  while (n > 1 && pass_ws(L, n, B, total_probe, total_ctx).total > limit) --n;
+  return n;
+}
+inline size_t layers_workspace(const qcf_layer_desc& L, int32_t n_layers, int32_t B, int64_t total_probe, int64_t total_ctx) {
+  const int n = layers_at_once(L, n_layers, B, total_probe, total_ctx);
+  size_t need = workspace(L, B, total_probe, total_ctx);
+  if (n > 1) need = std::max(need, pass_ws(L, n, B, total_probe, total_ctx).total);
+  if (n > 1 && n_layers % n > 1) need = std::max(need, pass_ws(L, n_layers % n, B, total_probe, total_ctx).total);
+  return need;
+}
+
+}  // namespace scoring
+}  // namespace qcf
