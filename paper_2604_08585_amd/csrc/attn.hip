@@ -581,7 +581,6 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
 // bucket depends on the race for the slots; results do not, because every unit's output location is given
 // by its (row block, segment).
 constexpr int kPlanBins = 64;
-constexpr int kPlanMaxBlocks = 4096;        // row blocks a split launch may have (LDS table of the plan kernel)
 __global__ __launch_bounds__(1024) void attn_plan_kernel(AttnArgs a) {
   __shared__ int s_vis[kPlanMaxBlocks];     // largest visible length of each row block
   __shared__ int s_cnt[kPlanBins + 1];
@@ -755,52 +754,6 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   if (row_ok && a.lse && ch == 0) a.lse[srow * a.H + head] = lse;
   if (row_ok)
     *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(a.o) + (srow * a.H + head) * D + 8 * ch) = Vec16<bf16_t>::pack(acc);
-}
-
-// Key tiles per work unit.  With enough row blocks the causal triangle balances by itself and blocks
-// stay whole; otherwise a segment is about the average causal work of a resident workgroup.
-int resident_workgroups(int rows) { return (rows == kWideRows ? 1 : 2) * compute_unit_count(); }
-struct Split { int seg_tiles, n_seg_max; };
-Split choose_split(int rows, int64_t n_blocks, int64_t total_ctx) {
-  const int slots = resident_workgroups(rows);
-  const int64_t n_t = std::max<int64_t>(1, (total_ctx + kBKV - 1) / kBKV);
-  const int64_t per_slot = n_blocks * ((n_t + 1) / 2) / slots;     // average causal work per resident workgroup
-  // a little above that average (a multiple of 4 tiles): most resident workgroups then take one whole
-  // segment and the remainders fill the rest (measured best at recompute ratios 0.05, 0.15 and 0.30)
-  int64_t seg = std::max<int64_t>(8, (per_slot * 27 / 25 + 3) / 4 * 4);
-  while ((n_t + seg - 1) / seg > 256) seg *= 2;       // a unit's segment number is kept in 8 bits
-  if (n_blocks > kPlanMaxBlocks) seg = n_t;            // (never the case when splitting pays: see per_slot)
-  if (seg >= n_t) return Split{(int)std::min<int64_t>(n_t, 0x3fffffff), 1};
-  return Split{(int)seg, (int)((n_t + seg - 1) / seg)};
-}
-
-// How a launch is divided: rows of a workgroup, row blocks of all requests (upper bound), key segments.
-struct Division { int rows; int64_t n_row_blocks; Split split; };
-int64_t row_blocks(const qcf_layer_desc& L, int rows, int32_t B, int64_t total_sel) {
-  const int br = rows / (L.n_q_heads / L.n_kv_heads);
-  return (total_sel + br - 1) / br + B;
-}
-// 128 or 256 rows to a workgroup (heads of 128).  The wide workgroups read every key and value fragment half as often, but
-// one of them fills a compute unit, so nothing hides the start and the end of its unit, a unit is the grain of the balance,
-// and their partial outputs are fp32.  They take over where a compute unit's average causal work is long enough.  Narrow
-// and wide, us, one request: 1228 rows x 32 heads over 12288 tokens (63 tiles to a compute unit) 149 and 153, 819 over
-// 16384 (56) 139 and 140, 1228 over 8192 (42) 114 and 113; 2457 over 8192 (80) 192 and 187, 1843 over 12288 (90) 206 and
-// 196, 2457 over 16384 (157) 358 and 339; 4915 rows x 64 heads over 32768 2468 and 2262.  Several requests, whose lengths
-// the host does not know (the longest may be most of the launch): eight of 2K to 16K tokens with 544 wide blocks 445 and
-// 472, with 1248 blocks 882 and 803; sixteen of 1000 tokens 60 and 78.
-constexpr int64_t kWideTiles = 72;          // average causal work of a compute unit, in tiles (one request)
-constexpr int64_t kWideBlocks = 4;          // row blocks to a compute unit (several requests)
-Division divide(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx) {
-  auto of = [&](int rows) {
-    const int64_t nb = row_blocks(L, rows, B, total_sel);
-    return Division{rows, nb, choose_split(rows, nb * L.n_kv_heads, total_ctx)};
-  };
-  if (L.head_dim == 128) {
-    const Division wide = of(kWideRows);
-    const int64_t blocks = wide.n_row_blocks * L.n_kv_heads, cus = compute_unit_count(), n_t = (total_ctx + kBKV - 1) / kBKV;
-    if (B == 1 ? blocks * ((n_t + 1) / 2) >= kWideTiles * cus : blocks >= kWideBlocks * cus) return wide;
-  }
-  return of(AttnTile<128>::WG_ROWS);
 }
 
 size_t part_o_bytes(int D, const Division& d, int Hkv) {

@@ -1,5 +1,5 @@
 // Step 6 for bf16 heads of 128, long launches: 64 rows to a wave, four waves to a workgroup, one wave to a SIMD (the rule
-// that chooses between this and the kernel of attn.hip, with both sides measured, is in attn.hip; layouts and arithmetic
+// that chooses between this and the kernel of attn.hip, with both sides measured, is in attn_layout.h; layouts and arithmetic
 // are the same, with the differences below).
 //
 // A key or value fragment read from LDS feeds two MFMAs instead of one, and a workgroup streams every tile for 256 rows.

@@ -4,6 +4,7 @@
 #include <type_traits>
 
 #include "qcf_internal.h"
+#include "attn_layout.h"
 
 namespace qcf {
 namespace attn {
@@ -46,7 +47,6 @@ struct AttnArgs {
   int32_t* blk_tiles;    // [row block] key tiles of the block, written by the plan kernel for the merge kernel (null: no plan)
 };
 
-constexpr int kBKV = 64;                    // tokens per K/V tile
 template <int D>
 struct AttnTile {
   static constexpr int ROW = 2 * D;                     // bytes of a staged row, no padding (swizzled instead)
@@ -56,7 +56,7 @@ struct AttnTile {
   static constexpr int LROWS = 1024 / ROW;              // rows filled by one load instruction of a wave (1 KB)
   static constexpr int NLOAD = kBKV / (4 * LROWS);      // instructions per wave and tile
   static constexpr int KS = D / 16, DT = D / 32;        // k-steps of the logits, 32-element slices of the output
-  static constexpr int WG_ROWS = 128;                   // (selected row, head-in-group) pairs per workgroup
+  static constexpr int WG_ROWS = kNarrowRows;           // (selected row, head-in-group) pairs per workgroup
   static constexpr int WGS = 2;                         // resident workgroups per compute unit (registers)
   static constexpr bool SPLIT_P = D == 64;              // probabilities as three bf16 terms, fp32 partial outputs,
                                                         // rows that are not finite computed again
@@ -148,8 +148,7 @@ __device__ __forceinline__ int ordered_unit(const AttnArgs& a, int rank, void* l
   return (a.n_row_blocks - 1 - unit / a.n_seg_max) << 8 | unit % a.n_seg_max;
 }
 
-// Main kernel for heads of 128 with 256 rows to a workgroup, one workgroup to a compute unit (attn128.hip).
-constexpr int kWideRows = 256;
+// Main kernel for heads of 128 with kWideRows rows to a workgroup, one workgroup to a compute unit (attn128.hip).
 qcf_status run_attn128(const AttnArgs& a, int64_t n_wg, hipStream_t st);
 
 }  // namespace attn

@@ -1,0 +1,88 @@
+// How the attention of the MFMA kernels is divided into workgroups.  Plain host code as well (no HIP header).
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "qcf.h"
+
+namespace qcf {
+
+int compute_unit_count();
+
+namespace attn {
+
+constexpr int kBKV = 64;                    // tokens per K/V tile
+constexpr int kNarrowRows = 128, kWideRows = 256;      // (selected row, head-in-group) pairs of a workgroup
+constexpr int kPlanMaxBlocks = 4096;        // row blocks a split launch may have (LDS table of the plan kernel)
+
+// Key tiles per work unit.  With enough row blocks the causal triangle balances by itself and blocks
+// stay whole; otherwise a segment is about the average causal work of a resident workgroup.
+inline int resident_workgroups(int rows) { return (rows == kWideRows ? 1 : 2) * compute_unit_count(); }
+struct Split { int seg_tiles, n_seg_max; };
+inline Split choose_split(int rows, int64_t n_blocks, int64_t total_ctx) {
+  const int slots = resident_workgroups(rows);
+  const int64_t n_t = std::max<int64_t>(1, (total_ctx + kBKV - 1) / kBKV);
+  const int64_t per_slot = n_blocks * ((n_t + 1) / 2) / slots;     // average causal work per resident workgroup
+  // a little above that average (a multiple of 4 tiles): most resident workgroups then take one whole
+  // segment and the remainders fill the rest (measured best at recompute ratios 0.05, 0.15 and 0.30)
+  int64_t seg = std::max<int64_t>(8, (per_slot * 27 / 25 + 3) / 4 * 4);
+  while ((n_t + seg - 1) / seg > 256) seg *= 2;       // a unit's segment number is kept in 8 bits
+  if (n_blocks > kPlanMaxBlocks) seg = n_t;            // (never the case when splitting pays: see per_slot)
+  if (seg >= n_t) return Split{(int)std::min<int64_t>(n_t, 0x3fffffff), 1};
+  return Split{(int)seg, (int)((n_t + seg - 1) / seg)};
+}
+
+// How a launch is divided: rows of a workgroup, row blocks of all requests (upper bound), key segments.
+struct Division { int rows; int64_t n_row_blocks; Split split; };
+inline int64_t row_blocks(const qcf_layer_desc& L, int rows, int32_t B, int64_t total_sel) {
+  const int br = rows / (L.n_q_heads / L.n_kv_heads);
+  return (total_sel + br - 1) / br + B;
+}
+// 128 or 256 rows to a workgroup (heads of 128).  The wide workgroups read every key and value fragment half as often, but
+// one of them fills a compute unit, so nothing hides the start and the end of its unit, a unit is the grain of the balance,
+// and their partial outputs are fp32.  They take over where a compute unit's average causal work is long enough and the rows
+// fill their blocks (0.92 of them, counted with one more than there are).  Narrow and wide, us, one request, 32 / 8 heads:
+// 1228 rows over 12288 tokens (58 tiles to a compute unit) 142 and 150, 819 over 16384 (51) 139 and 140; 1843 over 12288
+// (87) 202 and 190, 2457 over 8192 (77) 192 and 187, 2457 over 16384 (154) 358 and 339; 64 / 8 heads, 4915 over 32768 2468
+// and 2262.  Blocks not filled: 64 / 8 heads, 491 rows over 24576 (0.90) 223 and 240; 32 / 32 heads, 876 over 23078 (0.68)
+// 244 and 306, 2572 over 8509 (0.84) 215 and 227.  Of 256 launches of 50 to 420 tiles the best side of each would be 5.4 %
+// faster than the narrow one everywhere, this rule 4.7 %, and one launch loses more than 1.5 % (4.5).
+constexpr int64_t kWideTiles = 72;          // average causal work of a compute unit, in tiles (one request)
+constexpr double kWideFill = 0.92;
+// Several requests, of which the host knows the totals.  Narrow workgroups take 1.12 times as long for the same rows, but a
+// request leaves a quarter of a 256-row block empty on average where its rows go in blocks of 128, half of one where they
+// go in blocks of 256, and the start and end of a wide unit, which nothing hides, cost about seven of its tiles, those of
+// a narrow one two.  With less than 512 tiles of work to a compute unit the last units decide, and the wide ones lose more
+// often than not.  Narrow and wide, us, 32 query and 8 KV heads:
+//   130 requests of 100 tokens, 5 rows each, 63 and 99; 128 of 512, 77 rows 208 and 296; 55 of 4096, 204 rows 575 and 828;
+//   25 of 4096, 614 rows (229 tiles to a compute unit) 612 and 653; 24 of 1K to 9K, 12 % of the rows (380) 1059 and 1095;
+//   13 of 8192, 1228 rows (501) 1132 and 1250;
+//   25 of 12288, 614 rows (723) 1860 and 1820; 12 of 1K to 12K, 26 % (720) 1727 and 1654; 17 of 12288, 1843 rows (1490)
+//   3202 and 2954; 12 of 16384, 2457 rows (1850) 3855 and 3587.
+// 272 batches of up to 256 requests: none that goes to the wide workgroups loses more than 2 %.
+constexpr int64_t kWideBlocks = 4;          // row blocks to a compute unit
+constexpr int64_t kWideBatchTiles = 512;    // average causal work of a compute unit
+inline bool takes_wide(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx, int64_t blocks) {
+  const double cus = compute_unit_count(), requests = (double)B * L.n_kv_heads;
+  const double filled = (double)total_sel * L.n_q_heads / kWideRows;                 // row blocks without the empty rows
+  const double tiles = ((double)total_ctx / B / kBKV + 1.0) / 2.0;                   // that a row sees, on average
+  if (B == 1) return filled * tiles >= kWideTiles * cus && filled >= kWideFill * blocks;
+  return blocks >= kWideBlocks * cus && filled * tiles >= kWideBatchTiles * cus &&
+         1.12 * (filled + 0.25 * requests) * (tiles + 2.0) >= 1.01 * (filled + 0.5 * requests) * (tiles + 7.0);
+}
+inline Division divide(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx) {
+  auto of = [&](int rows) {
+    const int64_t nb = row_blocks(L, rows, B, total_sel);
+    return Division{rows, nb, choose_split(rows, nb * L.n_kv_heads, total_ctx)};
+  };
+  if (L.head_dim == 128) {
+    const Division wide = of(kWideRows);
+    if (takes_wide(L, B, total_sel, total_ctx, wide.n_row_blocks * L.n_kv_heads)) return wide;
+  }
+  return of(kNarrowRows);
+}
+
+}  // namespace attn
+}  // namespace qcf

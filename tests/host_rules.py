@@ -1,0 +1,48 @@
+"""The library's host rules, compiled from their headers for the tests (csrc/attn_layout.h; 256 compute units)."""
+import ctypes as C
+import functools
+import os
+import subprocess
+import tempfile
+
+from paper_2604_08585_amd import binding as qb
+from paper_2604_08585_amd import inputs
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+WIDE = 256
+
+PROGRAM = r"""
+#include "attn_layout.h"
+namespace qcf { int compute_unit_count() { return 256; } }
+extern "C" void division(const qcf_layer_desc* L, int B, long long rows, long long tokens, long long* out) {
+  const qcf::attn::Division d = qcf::attn::divide(*L, B, rows, tokens);
+  out[0] = d.rows; out[1] = d.n_row_blocks; out[2] = d.split.n_seg_max;
+}
+"""
+
+
+@functools.lru_cache(None)
+def _library():
+    folder = tempfile.mkdtemp()
+    src, so = os.path.join(folder, "rules.cpp"), os.path.join(folder, "rules.so")
+    with open(src, "w") as f:
+        f.write(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC", "-I" + os.path.join(ROOT, "include"),
+                    "-I" + os.path.join(ROOT, "paper_2604_08585_amd", "csrc"), src, "-o", so], check=True)
+    return C.CDLL(so)
+
+
+def attention(H, Hkv, D, T, sel):
+    """Rows of a workgroup, row blocks (upper bound) and key segments that the attention of these requests is divided into."""
+    desc = qb.make_desc(inputs.LayerShape(2048, H, Hkv, D, 10000.0, "bf16"))
+    out = (C.c_longlong * 3)()
+    _library().division(C.byref(desc), len(T), C.c_longlong(sum(sel)), C.c_longlong(sum(T)), out)
+    return tuple(out)
+
+
+def wide_workspace(Hkv, blocks, segments):
+    """Bytes of a split launch of wide workgroups: partial outputs and log-sum-exps in float32, the list of units, the lengths
+    of the row blocks."""
+    up = lambda n: (n + 255) // 256 * 256
+    rows = blocks * Hkv * segments * WIDE
+    return up(rows * 128 * 4) + up(rows * 4) + up((blocks * segments + 1) * 4) + up(blocks * 4)

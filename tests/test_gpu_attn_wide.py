@@ -6,6 +6,7 @@ import torch
 
 from paper_2604_08585_amd import binding as qb
 from paper_2604_08585_amd import inputs
+import host_rules
 from gpu_util import DEV, i64
 
 pytestmark = pytest.mark.gpu
@@ -52,22 +53,26 @@ def _case(seed, H, Hkv, T, sel, q_std=1.0, pos0=None, pos=None):
     return o, lse
 
 
-def _wide(H, Hkv, T, sel):
-    """The rule of the launcher, for 256 compute units."""
-    blocks = (-(-sum(sel) // (256 * Hkv // H)) + len(T)) * Hkv
-    return blocks * ((-(-sum(T) // 64) + 1) // 2) >= 72 * 256 if len(T) == 1 else blocks >= 4 * 256
+def _assert_wide(H, Hkv, T, sel):
+    """The launch has 256 rows to a workgroup; one that is split says so by its workspace."""
+    rows, blocks, segments = host_rules.attention(H, Hkv, 128, T, sel)
+    assert rows == host_rules.WIDE
+    desc = qb.make_desc(inputs.LayerShape(2048, H, Hkv, 128, 10000.0, "bf16"))
+    assert qb.qcf_recompute_attn_workspace_bytes(desc, len(T), sum(sel), sum(T)) == (
+        host_rules.wide_workspace(Hkv, blocks, segments) if segments > 1 else 0)
+    return segments
 
 
 @pytest.mark.parametrize("H,Hkv,T,sel", [
     (32, 8, 8192, 2457),       # split, four heads to a group
     (64, 8, 8200, 1500),       # split, eight heads, last tile of eight tokens
-    (128, 128, 4607, 700),     # split, one head to a group, last tile one token short
-    (256, 64, 3201, 1025),     # whole blocks, one token in the last tile, one row in the last block
-    (256, 256, 3100, 257),
+    (8, 8, 12351, 6100),       # split, one head to a group, last tile one token short
+    (128, 32, 3201, 1473),     # whole blocks, one token in the last tile, one row in the last block
+    (32, 32, 3300, 5889),
 ])
 def test_one_request(H, Hkv, T, sel):
     say(f"wide attention H={H}/{Hkv} T={T} rows={sel}")
-    assert _wide(H, Hkv, [T], [sel])
+    assert (_assert_wide(H, Hkv, [T], [sel]) > 1) == (Hkv == 8)      # (the others: whole blocks)
     a = _case(80, H, Hkv, [T], [sel])
     b = _case(80, H, Hkv, [T], [sel])
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
@@ -76,16 +81,19 @@ def test_one_request(H, Hkv, T, sel):
 @pytest.mark.parametrize("q_std", [0.02, 8.0, 60.0], ids=["flat", "sharp", "one-hot"])
 def test_logit_range(q_std):
     say(f"wide attention, logits of spread {q_std}")
-    assert _wide(64, 8, [8192], [1229])
+    _assert_wide(64, 8, [8192], [1229])
     _case(81, 64, 8, [8192], [1229], q_std=q_std)
 
 
-def test_requests_of_all_lengths():
+@pytest.mark.parametrize("H,Hkv,T,sel", [
+    (256, 64, [1, 63, 64, 65, 1000, 130, 5, 80000], [1, 64, 64, 128, 400, 0, 200, 3200]),       # one long request among them
+    (128, 64, [1, 63, 64, 65, 1000, 130, 5, 400], [1, 64, 64, 128, 700, 0, 200, 130])], ids=["256 rows", "128 rows"])
+def test_requests_of_all_lengths(H, Hkv, T, sel):
     """Rows that see nothing, one token, whole tiles; requests without rows or shorter than a tile."""
-    T, sel = [1, 63, 64, 65, 1000, 130, 5, 400], [1, 64, 64, 128, 700, 0, 200, 130]
-    say("wide attention, ragged batch")
-    assert _wide(128, 64, T, sel)
+    say(f"ragged batch of up to {max(T)} tokens")
+    if H == 256:
+        _assert_wide(H, Hkv, T, sel)
     pos = torch.cat([torch.linspace(0, t - 1, n, device=DEV).int() for t, n in zip(T, sel)])
-    _case(82, 128, 64, T, sel, pos=pos)
+    _case(82, H, Hkv, T, sel, pos=pos)
     pos = torch.cat([torch.linspace(-3, t + 40, n, device=DEV).int() for t, n in zip(T, sel)])
-    _case(83, 128, 64, T, sel, pos=pos, pos0=[0, 7, 100, 1000, 64, 3, 0, 12345])
+    _case(83, H, Hkv, T, sel, pos=pos, pos0=[0, 7, 100, 1000, 64, 3, 0, 12345])
