@@ -32,6 +32,8 @@
 //
 // Generic path (f32, or other head dims): one workgroup per (probe row, head) materialises its
 // softmax row in the workspace, then a column mean.
+#include <type_traits>
+
 #include "qcf_internal.h"
 #include "score_layout.h"
 
@@ -315,6 +317,30 @@ struct Unit {
   int64_t slot_first;                // partials of the request's first unit, and how many units it has
   int n_units;
 };
+// One layer in units of one tile, the short launches: the kernels come in a form of their own (ONE) that takes ScoreArgs, in a
+// grid of (tile, head), keeps nothing from tile to tile and runs every row tile through the same code.  Such a launch
+// waits for its arguments, its place and its instructions rather than for its arithmetic.  40 probe rows x 32 heads of 64 over
+// 2048 tokens 17.7 us by the other form, 15.1 so; x 16 heads over 16384 23.0 and 19.1; 200 rows x 32 heads of 128 over 4096
+// 49.5 and 43.8; 80 rows x 64 heads of 128 over 2048 38.6 and 34.7.
+template <bool ONE> using Args = typename std::conditional<ONE, ScoreArgs, PassArgs>::type;
+__host__ __device__ __forceinline__ const ScoreArgs& common(const ScoreArgs& a) { return a; }
+__host__ __device__ __forceinline__ const ScoreArgs& common(const PassArgs& a) { return a.s; }
+__device__ __forceinline__ const bf16_t* probes_of(const ScoreArgs& a, const Unit&) { return a.q; }
+__device__ __forceinline__ const bf16_t* probes_of(const PassArgs& a, const Unit& u) { return a.q[u.layer]; }
+__device__ __forceinline__ const bf16_t* keys_of(const ScoreArgs& a, const Unit&) { return a.k; }
+__device__ __forceinline__ const bf16_t* keys_of(const PassArgs& a, const Unit& u) { return a.k[u.layer]; }
+__device__ __forceinline__ bool locate_unit(const ScoreArgs& a, Unit& u) {
+  int tok0, first;
+  if (!locate_tile(a, (int)blockIdx.x, u.b, u.c0, u.T, tok0, first)) return false;
+  u.layer = 0;
+  u.g = (int)blockIdx.y;
+  u.tile0 = tok0 / kTokPerWg;
+  u.tile1 = u.tile0 + 1;
+  u.slot = blockIdx.x;
+  u.slot_first = first;
+  u.n_units = (u.T + kTokPerWg - 1) / kTokPerWg;
+  return true;
+}
 // The tiles of a request are dealt evenly to its units.  Consecutive workgroups take the KV heads in turn, so that with
 // eight of them the units of a head, which read the same probe rows, share an XCD.
 __device__ __forceinline__ bool locate_unit(const PassArgs& a, Unit& u) {
@@ -346,9 +372,9 @@ constexpr int kTilesPerWave = (kRowBlock / 32 + kRowGroups - 1) / kRowGroups;   
 
 // Pass 1.  Wave (tw, rg) keeps the 64 tokens of slice tw in registers and takes every third 32-row tile of the staged
 // probe rows, starting with tile rg; a lane keeps the running (max, sum-exp) of its rows over the unit's tiles.
-template <int D, bool LIMIT>
-__global__ __launch_bounds__(kThreads) void score_pass1(PassArgs pa) {
-  const ScoreArgs& a = pa.s;
+template <int D, bool LIMIT, bool ONE>
+__global__ __launch_bounds__(kThreads) void score_pass1(Args<ONE> pa) {
+  const ScoreArgs& a = common(pa);
   extern __shared__ __align__(256) unsigned char smem[];      // (fragment addresses are formed with XORs below 256)
   unsigned char* sK = smem + kQBytes<D>;
   float2* sPart = reinterpret_cast<float2*>(smem + kQBytes<D> + kKBytes<D>);     // [kTokWaves][kRowBlock]
@@ -362,8 +388,8 @@ __global__ __launch_bounds__(kThreads) void score_pass1(PassArgs pa) {
   const int64_t p1 = min(max(a.probe_off[u.b + 1], p0), a.total_probe);
   const int rows = (int)(p1 - p0) * a.G;         // probe rows x heads of the group
   if (rows == 0) return;
-  const bf16_t* q = pa.q[u.layer];
-  const KeyLoader<D> keys(pa.k[u.layer] + (u.c0 * a.Hkv + u.g) * D, a.Hkv, u.T, lds0 + (uint32_t)kQBytes<D>, wave, lane);
+  const bf16_t* q = probes_of(pa, u);
+  const KeyLoader<D> keys(keys_of(pa, u) + (u.c0 * a.Hkv + u.g) * D, a.Hkv, u.T, lds0 + (uint32_t)kQBytes<D>, wave, lane);
   const int qb0 = frag_base<D>(lane);
   float2* part = a.part + u.slot * (a.total_probe * a.H);
 
@@ -371,63 +397,84 @@ __global__ __launch_bounds__(kThreads) void score_pass1(PassArgs pa) {
     const int n_rows = min(kRowBlock, rows - r_begin);
     const int n_pad = (n_rows + 31) & ~31;
     __syncthreads();                        // the previous block's rows and partials are no longer read
+    if (ONE && r_begin == 0) keys.load(u.tile0, wave);      // (they stay in LDS)
     stage_q_async<D>(a, q, p0, u.g, r_begin, n_rows, n_pad, lds0, wave, lane);
-    keys.load(u.tile0, wave);
-    float m_run[kTilesPerWave], z_run[kTilesPerWave];      // lane's row: r_begin + 32 (rg + 3 i) + lane%32
-    int lim[kTilesPerWave];
+    if (!ONE) keys.load(u.tile0, wave);
+    // how many tokens the lane's row of row tile rt sees
+    auto limit_of = [&](int rt) {
+      const int r = r_begin + rt + (lane & 31);
+      return LIMIT && r < r_begin + n_rows ? min(u.T, max(0, a.probe_limit[p0 + r / a.G])) : u.T;
+    };
+    // 64 tokens from tok0 on into a lane's running maximum (of the row) and sum (of this half of the tokens)
+    auto add_tokens = [&](const bf16x8 (&kf)[2][D / 16], int rt, int tok0, int lim, float& m_run, float& z_run) {
+      floatx16 acc0, acc1;
+      logit_tile<D, true>(kf, lds0 + (uint32_t)(rt * 2 * D + qb0), acc0, acc1);
+      // lane owns probe row rt + lane%32; its registers hold tokens 8*(v/4) + 4*(lane/32) + v%4
+      float s[32];
 #pragma unroll
-    for (int i = 0; i < kTilesPerWave; ++i) {
-      m_run[i] = -INFINITY;
-      z_run[i] = 0.f;
-      lim[i] = u.T;
-      const int r = r_begin + 32 * (rg + kRowGroups * i) + (lane & 31);
-      if (LIMIT && r < r_begin + n_rows) lim[i] = min(u.T, max(0, a.probe_limit[p0 + r / a.G]));
-    }
-    for (int tile = u.tile0; tile < u.tile1; ++tile) {
-      const int tok0 = tile * kTokPerWg + tw * kTokPerWave;
+      for (int v = 0; v < 16; ++v) { s[v] = acc0[v]; s[16 + v] = acc1[v]; }
+      if (LIMIT || tok0 + kTokPerWave > u.T) {        // wave-uniform: only ragged or limited tiles compare
+        const int left = lim - tok0 - 4 * (lane >> 5);
+#pragma unroll
+        for (int v = 0; v < 32; ++v) s[v] = (32 * (v >> 4) + 8 * ((v & 15) >> 2) + (v & 3) < left) ? s[v] : -INFINITY;
+      }
+      float mx = s[0];
+#pragma unroll
+      for (int v = 1; v < 32; ++v) mx = fmaxf(mx, s[v]);
+      mx = fmaxf(mx, other_half(mx));
+      if (!kPairs<D>) mx *= kK2<D>;                         // (positive: scaling commutes with the maximum)
+      const float m_new = fmaxf(m_run, mx);
+      const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+      float sum = z_run * __builtin_amdgcn_exp2f((m_run - m_use) * kMaxScale<D>);
+#pragma unroll
+      for (int v = 0; v < 32; ++v) sum += exp_of<D>(s[v], m_use);
+      m_run = m_new;
+      z_run = sum;
+    };
+    auto store = [&](int rt, float m, float z) {
+      z += other_half(z);
+      if (lane < 32) sPart[tw * kRowBlock + rt + lane] = make_float2(m, z);
+    };
+    if constexpr (ONE) {
+      const int tok0 = u.tile0 * kTokPerWg + tw * kTokPerWave;
       __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();                      // the tile's keys (and the rows) have landed
+      __syncthreads();                      // the keys and the rows have landed
       bf16x8 kf[2][D / 16];
       load_key_frags<D>(sK + kTokPerWave * tw * (2 * D), qb0, kf);
-      __syncthreads();                      // every wave has its keys
-      if (tile + 1 < u.tile1) keys.load(tile + 1, wave);
-      if (tok0 >= u.T) continue;
+#pragma unroll 1
+      for (int rt = 32 * rg; rt < n_pad; rt += 32 * kRowGroups) {
+        float m = -INFINITY, z = 0.f;
+        if (tok0 < u.T) add_tokens(kf, rt, tok0, limit_of(rt), m, z);
+        store(rt, m, z);
+      }
+    } else {
+      float m_run[kTilesPerWave], z_run[kTilesPerWave];      // of row tile rg + 3 i
+      int lim[kTilesPerWave];
+#pragma unroll
+      for (int i = 0; i < kTilesPerWave; ++i) {
+        m_run[i] = -INFINITY;
+        z_run[i] = 0.f;
+        lim[i] = limit_of(32 * (rg + kRowGroups * i));
+      }
+      for (int tile = u.tile0; tile < u.tile1; ++tile) {
+        const int tok0 = tile * kTokPerWg + tw * kTokPerWave;
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();                      // the tile's keys (and the rows) have landed
+        bf16x8 kf[2][D / 16];
+        load_key_frags<D>(sK + kTokPerWave * tw * (2 * D), qb0, kf);
+        __syncthreads();                      // every wave has its keys
+        if (tile + 1 < u.tile1) keys.load(tile + 1, wave);
+        if (tok0 >= u.T) continue;
+#pragma unroll
+        for (int i = 0; i < kTilesPerWave; ++i) {
+          const int rt = 32 * (rg + kRowGroups * i);
+          if (rt < n_pad) add_tokens(kf, rt, tok0, lim[i], m_run[i], z_run[i]);
+        }
+      }
 #pragma unroll
       for (int i = 0; i < kTilesPerWave; ++i) {
         const int rt = 32 * (rg + kRowGroups * i);
-        if (rt < n_pad) {
-          floatx16 acc0, acc1;
-          logit_tile<D, true>(kf, lds0 + (uint32_t)(rt * 2 * D + qb0), acc0, acc1);
-          // lane owns probe row rt + lane%32; its registers hold tokens 8*(v/4) + 4*(lane/32) + v%4
-          float s[32];
-#pragma unroll
-          for (int v = 0; v < 16; ++v) { s[v] = acc0[v]; s[16 + v] = acc1[v]; }
-          if (LIMIT || tok0 + kTokPerWave > u.T) {        // wave-uniform: only ragged or limited tiles compare
-            const int left = lim[i] - tok0 - 4 * (lane >> 5);
-#pragma unroll
-            for (int v = 0; v < 32; ++v) s[v] = (32 * (v >> 4) + 8 * ((v & 15) >> 2) + (v & 3) < left) ? s[v] : -INFINITY;
-          }
-          float mx = s[0];
-#pragma unroll
-          for (int v = 1; v < 32; ++v) mx = fmaxf(mx, s[v]);
-          mx = fmaxf(mx, other_half(mx));
-          if (!kPairs<D>) mx *= kK2<D>;                         // (positive: scaling commutes with the maximum)
-          const float m_new = fmaxf(m_run[i], mx);
-          const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-          float sum = z_run[i] * __builtin_amdgcn_exp2f((m_run[i] - m_use) * kMaxScale<D>);
-#pragma unroll
-          for (int v = 0; v < 32; ++v) sum += exp_of<D>(s[v], m_use);
-          m_run[i] = m_new;
-          z_run[i] = sum;                       // (of this lane's half of the tokens)
-        }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < kTilesPerWave; ++i) {
-      const int rt = 32 * (rg + kRowGroups * i);
-      if (rt < n_pad) {
-        const float z = z_run[i] + other_half(z_run[i]);
-        if (lane < 32) sPart[tw * kRowBlock + rt + lane] = make_float2(m_run[i], z);
+        if (rt < n_pad) store(rt, m_run[i], z_run[i]);
       }
     }
     __syncthreads();
@@ -464,9 +511,9 @@ __device__ __forceinline__ void fold_partials(const float2 (&p)[kFoldBatch], flo
 }
 
 // Pass 2, same division of work; the three row groups' column sums are added in a fixed order at the end of a tile.
-template <int D, bool LIMIT>
-__global__ __launch_bounds__(kThreads) void score_pass2(PassArgs pa) {
-  const ScoreArgs& a = pa.s;
+template <int D, bool LIMIT, bool ONE>
+__global__ __launch_bounds__(kThreads) void score_pass2(Args<ONE> pa) {
+  const ScoreArgs& a = common(pa);
   extern __shared__ __align__(256) unsigned char smem[];      // (fragment addresses are formed with XORs below 256)
   unsigned char* sK = smem + kQBytes<D>;
   float* sL = reinterpret_cast<float*>(smem + kQBytes<D> + kKBytes<D>);          // [kRowBlock] maximum
@@ -484,18 +531,20 @@ __global__ __launch_bounds__(kThreads) void score_pass2(PassArgs pa) {
   const int64_t p1 = min(max(a.probe_off[u.b + 1], p0), a.total_probe);
   const int rows = (int)(p1 - p0) * a.G;
   if (rows == 0) return;                 // (the reduce kernel gives such a request zeros without reading the sums)
-  const bf16_t* q = pa.q[u.layer];
-  const KeyLoader<D> keys(pa.k[u.layer] + (u.c0 * a.Hkv + u.g) * D, a.Hkv, u.T, lds0 + (uint32_t)kQBytes<D>, wave, lane);
+  const bf16_t* q = probes_of(pa, u);
+  const KeyLoader<D> keys(keys_of(pa, u) + (u.c0 * a.Hkv + u.g) * D, a.Hkv, u.T, lds0 + (uint32_t)kQBytes<D>, wave, lane);
   const int64_t part_stride = a.total_probe * a.H;
   const int qb0 = frag_base<D>(lane);
   float* colsum = a.colsum + ((int64_t)u.layer * a.Hkv + u.g) * a.total_ctx + u.c0;
 
+  float col0 = 0.f, col1 = 0.f;           // column sums of tokens tok0 + lane%32 and + 32 over this wave's row tiles
   for (int r_begin = 0; r_begin < rows; r_begin += kRowBlock) {
     const int n_rows = min(kRowBlock, rows - r_begin);
     const int n_pad = (n_rows + 31) & ~31;
     __syncthreads();
+    if (ONE && r_begin == 0) keys.load(u.tile0, wave);
     stage_q_async<D>(a, q, p0, u.g, r_begin, n_rows, n_pad, lds0, wave, lane);
-    keys.load(u.tile0, wave);
+    if (!ONE) keys.load(u.tile0, wave);
     // maximum and sum of staged row tid over the request: the units' partials folded in order, kFoldBatch at a
     // time (all loads first, then one maximum and one rescaled sum); every workgroup of the request computes the
     // same values
@@ -536,9 +585,11 @@ __global__ __launch_bounds__(kThreads) void score_pass2(PassArgs pa) {
       __syncthreads();                    // the tile's keys (and the rows and their sums) have landed
       bf16x8 kf[2][D / 16];
       load_key_frags<D>(sK + kTokPerWave * tw * (2 * D), qb0, kf);
-      __syncthreads();                    // every wave has its keys, and the previous tile's column sums are out
-      if (tile + 1 < u.tile1) keys.load(tile + 1, wave);
-      float col0 = 0.f, col1 = 0.f;       // column sums of tokens tok0 + lane%32 and + 32 over this wave's row tiles
+      if constexpr (!ONE) {
+        __syncthreads();                  // every wave has its keys, and the previous tile's column sums are out
+        if (tile + 1 < u.tile1) keys.load(tile + 1, wave);
+        col0 = col1 = 0.f;
+      }
       if (tok0 < u.T)
         for (int rt = 32 * rg; rt < n_pad; rt += 32 * kRowGroups) {
           floatx16 acc0, acc1;
@@ -575,6 +626,7 @@ __global__ __launch_bounds__(kThreads) void score_pass2(PassArgs pa) {
             }
           }
         }
+      if (ONE && r_begin + kRowBlock < rows) continue;      // (the sums of all blocks of rows go out together)
       col0 += other_half(col0);
       col1 += other_half(col1);
       if (lane < 32) {
@@ -588,7 +640,7 @@ __global__ __launch_bounds__(kThreads) void score_pass2(PassArgs pa) {
         float sum = sCol[tid];
 #pragma unroll
         for (int r3 = 1; r3 < kRowGroups; ++r3) sum += sCol[r3 * kTokPerWg + tid];
-        if (r_begin > 0) sum += colsum[t];    // (this thread's own sum over the rows before)
+        if (!ONE && r_begin > 0) sum += colsum[t];    // (this thread's own sum over the rows before)
         colsum[t] = sum;
       }
     }
@@ -885,8 +937,9 @@ __global__ __launch_bounds__(kFusedThreads) void score_fused(FusedArgs fa) {
 }
 
 // Adds the KV heads of every layer in order, and the layers, in order, into the score.
-__global__ __launch_bounds__(256) void score_reduce(PassArgs pa) {
-  const ScoreArgs& a = pa.s;
+template <bool ONE>
+__global__ __launch_bounds__(256) void score_reduce(Args<ONE> pa) {
+  const ScoreArgs& a = common(pa);
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (j >= a.total_ctx) return;
   const int b = find_request(a.ctx_off, a.B, j);
@@ -894,15 +947,21 @@ __global__ __launch_bounds__(256) void score_reduce(PassArgs pa) {
   const int64_t p0 = min(max(a.probe_off[b], (int64_t)0), a.total_probe);
   const int64_t p1 = min(max(a.probe_off[b + 1], p0), a.total_probe);
   const float n = (float)((p1 - p0) * a.H);
-  float score = a.beta == 0.f ? 0.f : a.score[j];
-  for (int l = 0; l < pa.n_layers; ++l) {
-    const float* col = a.colsum + (int64_t)l * a.Hkv * a.total_ctx + j;
+  if constexpr (ONE) {
     float acc = 0.f;
+    for (int g = 0; g < a.Hkv; ++g) acc += a.colsum[(int64_t)g * a.total_ctx + j];
+    write_score(a, j, p1 > p0 ? acc / n : 0.f);
+  } else {
+    float score = a.beta == 0.f ? 0.f : a.score[j];
+    for (int l = 0; l < pa.n_layers; ++l) {
+      const float* col = a.colsum + (int64_t)l * a.Hkv * a.total_ctx + j;
+      float acc = 0.f;
 #pragma unroll 8
-    for (int g = 0; g < a.Hkv; ++g) acc += col[g * a.total_ctx];
-    score = blended(l == 0 ? a.beta : 1.f, score, pa.alpha[l] * (p1 > p0 ? acc / n : 0.f));
+      for (int g = 0; g < a.Hkv; ++g) acc += col[g * a.total_ctx];
+      score = blended(l == 0 ? a.beta : 1.f, score, pa.alpha[l] * (p1 > p0 ? acc / n : 0.f));
+    }
+    a.score[j] = score;
   }
-  a.score[j] = score;
 }
 
 __global__ __launch_bounds__(256) void score_zero(float* score, int64_t n, float beta) {
@@ -924,18 +983,24 @@ qcf_status run_fused(const FusedArgs& fa, hipStream_t st) {
   return check_launch("score (single kernel)");
 }
 
-template <int D, bool LIMIT>
-qcf_status run_two_pass(const PassArgs& a, hipStream_t st) {
+template <int D, bool LIMIT, bool ONE>
+qcf_status run_two_pass(const Args<ONE>& a, dim3 grid, hipStream_t st) {
   static std::atomic<uint64_t> lds_ok[2];
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass1<D, LIMIT>), kPass1Lds<D>, lds_ok[0]));
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass2<D, LIMIT>), kPass2Lds<D>, lds_ok[1]));
-  const dim3 grid((unsigned)((int64_t)a.n_units * a.n_layers * a.s.Hkv)), block(kThreads);
-  score_pass1<D, LIMIT><<<grid, block, kPass1Lds<D>, st>>>(a);
+  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass1<D, LIMIT, ONE>), kPass1Lds<D>, lds_ok[0]));
+  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass2<D, LIMIT, ONE>), kPass2Lds<D>, lds_ok[1]));
+  const dim3 block(kThreads);
+  score_pass1<D, LIMIT, ONE><<<grid, block, kPass1Lds<D>, st>>>(a);
   QCF_TRY_LAUNCH("score pass 1");
-  score_pass2<D, LIMIT><<<grid, block, kPass2Lds<D>, st>>>(a);
+  score_pass2<D, LIMIT, ONE><<<grid, block, kPass2Lds<D>, st>>>(a);
   QCF_TRY_LAUNCH("score pass 2");
-  score_reduce<<<dim3((unsigned)((a.s.total_ctx + 255) / 256)), dim3(256), 0, st>>>(a);
+  score_reduce<ONE><<<dim3((unsigned)((common(a).total_ctx + 255) / 256)), dim3(256), 0, st>>>(a);
   return check_launch("score reduce");
+}
+template <bool ONE>
+qcf_status run_passes(int D, const Args<ONE>& a, dim3 grid, hipStream_t st) {
+  const bool limit = common(a).probe_limit != nullptr;
+  if (D == 128) return limit ? run_two_pass<128, true, ONE>(a, grid, st) : run_two_pass<128, false, ONE>(a, grid, st);
+  return limit ? run_two_pass<64, true, ONE>(a, grid, st) : run_two_pass<64, false, ONE>(a, grid, st);
 }
 
 // The two passes over n_layers layers (up to kMaxLayers); a: everything but the layers and the workspace.
@@ -956,8 +1021,9 @@ qcf_status launch_two_pass(const qcf_layer_desc& L, const ScoreArgs& a, int n_la
   pa.n_layers = n_layers;
   pa.unit_tiles = w.unit_tiles;
   pa.n_units = (int)w.n_units;
-  if (L.head_dim == 128) return a.probe_limit ? run_two_pass<128, true>(pa, st) : run_two_pass<128, false>(pa, st);
-  return a.probe_limit ? run_two_pass<64, true>(pa, st) : run_two_pass<64, false>(pa, st);
+  if (n_layers > 1 || w.unit_tiles > 1 || a.Hkv > 65535)
+    return run_passes<false>(L.head_dim, pa, dim3((unsigned)(w.n_units * n_layers * a.Hkv)), st);
+  return run_passes<true>(L.head_dim, pa.s, dim3((unsigned)w.n_units, (unsigned)a.Hkv), st);
 }
 
 ScoreArgs score_args(const qcf_layer_desc& L, int32_t B, const void* q, const int64_t* probe_off, int64_t total_probe,

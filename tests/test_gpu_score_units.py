@@ -66,6 +66,28 @@ def test_units_of_several_tiles(H, Hkv, D, T, R, limited):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("limited", [False, True])
+@pytest.mark.parametrize("H,Hkv,D,T,R", [
+    (32, 8, 128, [257], [81]),                              # 324 rows of a group: a second block of four
+    (12, 3, 128, [1, 256, 1000], [161, 0, 80]),             # three KV heads; one token, a whole tile
+    (8, 8, 64, [255, 2048], [321, 641]),                    # one row past a block, one past two
+    (32, 8, 64, [700], [1])], ids=["two blocks", "batch", "heads64", "one row"])
+def test_units_of_one_tile(H, Hkv, D, T, R, limited):
+    say(f"score units of one tile H={H}/{Hkv} D={D} T={T} R={R} limited={limited}")
+    q, k, oq, ok, g = _inputs(63, 1, H, Hkv, D, T, R)
+    lim = torch.randint(0, max(T) + 1, (sum(R),), generator=g, device=DEV, dtype=torch.int32) if limited else None
+    if limited:
+        lim[0], lim[-1] = max(T), 0
+    desc = qb.make_desc(inputs.LayerShape(2048, H, Hkv, D, 10000.0, "bf16"))
+    score = torch.full((sum(T),), float("nan"), device=DEV)
+    qb.qcf_score(desc, len(T), q[0], i64(oq), sum(R), k[0], i64(ok), sum(T), lim, score)
+    ref = _reference(q[0], k[0], oq, ok, lim)
+    assert bool(((score.double() - ref).abs() <= 1e-5 * ref + 1e-12).all())
+    qb.qcf_score_accumulate(desc, len(T), q[0], i64(oq), sum(R), k[0], i64(ok), sum(T), lim, -0.5, 2.0, score)
+    assert bool(((score.double() - 1.5 * ref).abs() <= 3e-5 * ref + 1e-12).all())
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("n_layers,D,T,R", [
     (2, 128, [1], [1]), (3, 128, [255], [7]), (5, 128, [6001], [48]), (17, 128, [513], [20]),    # 17: a second set of launches
     (33, 128, [40, 700], [2, 9]), (4, 128, [300, 64, 1025], [5, 0, 17]), (3, 64, [400], [12]), (1, 128, [900], [24])])
