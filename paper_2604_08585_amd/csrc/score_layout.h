@@ -44,11 +44,25 @@ inline PassWs pass_ws_of(const qcf_layer_desc& L, int n_layers, int unit_tiles, 
   w.total = w.colsum + aligned((size_t)n_layers * L.n_kv_heads * total_ctx * sizeof(float));
   return w;
 }
+// Units of all requests, upper bound.  A request of nt tiles has ceil(nt / unit_tiles) units: every request may end in a unit
+// that is not full, but none has more units than tiles (with more requests than tokens the first bound is the larger).
+inline int64_t n_units_upper(int32_t B, int64_t total_ctx, int unit_tiles) {
+  const int64_t nt = n_tiles_upper(B, total_ctx);
+  return std::min(nt, (nt + (int64_t)B * (unit_tiles - 1)) / unit_tiles);
+}
 // Tiles that a workgroup of the two passes takes in turn.  A workgroup spends about as long on staging probe rows and on its
 // sums as on kUnitCost tiles; where a launch is a few rounds long whole rounds count, otherwise the tail is about half a
 // unit.  (32768 tokens, 8 KV heads: units of four tiles, one round; with one tile to a unit pass 2 alone took 149 us, now 71.)
+// Of several requests the host knows the totals.  The estimate takes their lengths to be uneven, which counts up to a tile too
+// many for each; requests of one length that fit one round of the chip by that reading are asked for first:
+//   - one tile to a unit fits, and the bound adds no more than a quarter of a round of workgroups without a tile, or the rows
+//     take several blocks, for each of which a larger unit stages its keys again.  4 requests of 4000 tokens x 16 heads of 64:
+//     16 probe rows 17.1 us, with two tiles to a unit 21.2; 160 rows 39 and 57.  16 of 500 x 64 heads of 128: 160 rows 86 and
+//     118, but 16 rows 37 and 32;
+//   - with well over one block of rows, the smallest unit that fits: 16 of 1000, 160 rows x 64 heads of 128, one tile (two
+//     rounds) 148, two 136, four 193; 16 of 2000 285, 245 and 213.
 constexpr double kUnitCost = 1.5;
-inline int unit_tiles_for(int32_t B, int64_t total_ctx, int64_t heads_layers) {
+inline int unit_tiles_for(int32_t B, int64_t total_probe, int64_t total_ctx, int64_t heads_layers, int64_t group) {
   const int64_t nt = n_tiles_upper(B, total_ctx);
   const double cus = compute_unit_count();
   int best = 1;
@@ -58,15 +72,20 @@ inline int unit_tiles_for(int32_t B, int64_t total_ctx, int64_t heads_layers) {
     const double cost = (per_cu <= 3.0 ? ceil(per_cu) : per_cu + 0.5) * (ul + kUnitCost);
     if (ul == 1 || cost < best_cost) { best = ul; best_cost = cost; }
   }
+  if (B == 1) return best;
+  const int64_t tiles = std::max<int64_t>(1, (total_ctx + (int64_t)kTokPerWg * B - 1) / ((int64_t)kTokPerWg * B));
+  const double rows = (double)total_probe * group / B;
+  auto fits = [&](int64_t units) { return (double)units * heads_layers <= cus; };
+  if (fits(B * tiles)) return (double)nt * heads_layers <= 1.25 * cus || rows > kRowBlock ? 1 : best;
+  if (rows > 1.5 * kRowBlock)
+    for (int ul = 2; ul < best; ++ul)
+      if (fits(B * ((tiles + ul - 1) / ul))) return ul;
   return best;
 }
-// What the launches of n_layers layers use.  A request of nt tiles has ceil(nt / unit_tiles) units: every request may end in a
-// unit that is not full, but none has more units than tiles (with more requests than tokens the first bound is the larger).
+// What the launches of n_layers layers use.
 inline PassWs pass_ws(const qcf_layer_desc& L, int n_layers, int32_t B, int64_t total_probe, int64_t total_ctx) {
-  const int unit_tiles = unit_tiles_for(B, total_ctx, (int64_t)L.n_kv_heads * n_layers);
-  const int64_t nt = n_tiles_upper(B, total_ctx);
-  const int64_t n_units = std::min(nt, (nt + (int64_t)B * (unit_tiles - 1)) / unit_tiles);
-  return pass_ws_of(L, n_layers, unit_tiles, n_units, total_probe, total_ctx);
+  const int unit_tiles = unit_tiles_for(B, total_probe, total_ctx, (int64_t)L.n_kv_heads * n_layers, L.n_q_heads / L.n_kv_heads);
+  return pass_ws_of(L, n_layers, unit_tiles, n_units_upper(B, total_ctx, unit_tiles), total_probe, total_ctx);
 }
 // The size reported for one layer: one tile to a unit, at least what pass_ws gives.
 inline size_t two_pass_bytes(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx) {
