@@ -248,7 +248,7 @@ __global__ __launch_bounds__(256, 1) void attn128_kernel(AttnArgs a) {
   // that the compiler would have put in are kept by the order instead: an operand written by a vector instruction needs two
   // instructions before the MFMA (the fragment is formed, if it is moved at all, before the two logit MFMAs in front of its
   // first use; the probabilities half a tile earlier), and other uses of oacc are fenced (`settle`: an MFMA's result may be
-  // read 11 wait states later).
+  // read 11 wait states later).  tests/test_attn128_waits.py looks for both in the assembly.
   bf16x8 vf[2];
   auto v_form = [&](int idx) QCF_INLINE {
     u32x4 t = __builtin_bit_cast(u32x4, __builtin_shufflevector(vlo[idx & 3], vhi[idx & 3], 0, 1, 2, 3, 4, 5, 6, 7));
