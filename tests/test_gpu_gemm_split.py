@@ -1,5 +1,7 @@
 """Products whose contraction is split, against float32: over 256 x 256 tiles (ragged rows, an odd number of column blocks,
 ranges of unequal length, the rotation and the gated SiLU behind the reduction), and weight streams for few rows."""
+import ctypes as C
+
 import pytest
 import torch
 
@@ -102,6 +104,7 @@ def test_gated_silu():
     M, K, F = 512, 8192, 5120
     print(f"split gated product M={M} F={F}", flush=True)
     desc = qb.make_desc(DESC)
+    assert qb.load_library().qcf_linear_swiglu_workspace_bytes(C.byref(desc), M, K, F) == _sums(M, 2 * F, 3)
     x, w = _normal(7, M, K), _normal(8, 2 * F, K, std=K ** -0.5)
     out = torch.full((M, F), 7.0, dtype=BF, device=DEV)
     qb.qcf_linear_swiglu(desc, x, M, K, w, F, out)
