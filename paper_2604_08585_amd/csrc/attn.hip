@@ -157,6 +157,7 @@ __device__ __forceinline__ void split_classes(const u32x4& v, u32x4& fin, u32x4&
 template <int D>
 __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnArgs a) {
   using C = AttnTile<D>;
+  static_assert(kOrderLds <= C::LDS, "ordered_unit works in the tiles' LDS");
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_vis_max[4];
   const int tid = threadIdx.x, lane = tid & 63;

@@ -53,6 +53,7 @@ __device__ __forceinline__ void span(std::integral_constant<int, FROM>, std::int
 }
 
 __global__ __launch_bounds__(256, 1) void attn128_kernel(AttnArgs a) {
+  static_assert(kOrderLds <= 2 * kRing * kTile, "ordered_unit works in the tiles' LDS");
   extern __shared__ __align__(256) unsigned char smem[];      // (fragment addresses are formed with XORs below 256)
   int* s_vis_max = reinterpret_cast<int*>(smem + 2 * kRing * kTile);
   const int tid = threadIdx.x, lane = tid & 63;

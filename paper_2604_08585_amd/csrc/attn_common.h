@@ -78,8 +78,9 @@ __device__ __forceinline__ u32x4 lds_read16(uint32_t lds_addr) {
   return *(const u32x4 __attribute__((address_space(3)))*)(uintptr_t)lds_addr;
 }
 
-// Log-sum-exp of logits whose maximum is m / kLog2e and whose sum against it is 2^lz.  EXACT (heads of 64, and the wide workgroups): rounded once,
-// and with the reciprocal of the kLog2e that m was scaled by (as two floats), not with ln 2.
+// Log-sum-exp of logits whose maximum is m / kLog2e and whose sum against it is 2^lz.  EXACT (heads of 64, and the whole blocks
+// of the wide workgroups; their split ones come from the merge, whose partials hold m + lz rounded once already): rounded
+// once, and with the reciprocal of the kLog2e that m was scaled by (as two floats), not with ln 2.
 template <bool EXACT>
 __device__ __forceinline__ float natural_lse(float m, float lz) {
   if (!EXACT) return (m + lz) * kLn2;
