@@ -178,7 +178,9 @@ qcf_status qcf_select(int32_t B, const float* score, const int64_t* ctx_off_dev,
  * bf16 MFMA path (d_model % 64 == 0, H_kv * d % 128 == 0), here and in qcf_linear: the workspace is optional.  With it the
  * contraction of a small number of rows (or of the rows that full rounds of tiles leave over) is cut into ranges whose
  * fp32 sums are added in a fixed order, which is faster; the last bits of a row then depend on M and on whether the
- * workspace is given.  Without it they do not.  Either way the same call gives the same bits. */
+ * workspace is given.  Without it they do not.  Either way the same call gives the same bits; the sums of a divided
+ * contraction are added in the order of its ranges, whose number follows from M, K and N and is not part of this interface:
+ * results of another number of rows, or of another version, may round the other way in the last bf16 place. */
 size_t qcf_recompute_qkv_workspace_bytes(const qcf_layer_desc* desc, int64_t M);
 qcf_status qcf_recompute_qkv(const qcf_layer_desc* desc, const void* x, int64_t x_rows,
                              const int32_t* x_gather_dev, int64_t M, const void* w_qkv,

@@ -1068,6 +1068,9 @@ double ws128_us(int64_t mt, int nb, int nk) {
 // and 119; K 8192, N 10240 of 129 rows 69 and 55, 512 rows 111 and 89.  The other side of the line: K 4096, N 4096 of 1229
 // rows 44 and 56, N 6144 of 700 rows 52 and 53 (a range of 22 k-tiles does not pay for its sums); K 8192, N 10240 of 900
 // rows, two rounds of ranges of 44, 159 and 162; K 14336, N 4096 of 3300 rows, two rounds of two ranges, 303 and 338.
+// (Weights from memory.  In the memory-side cache, which has room for those of one product at best, the undivided tiles wait less:
+// K 14336, N 4096 of 512 rows 61 and 65 there, 79 and 66 from memory, 1229 rows 145 and 125, 174 and 127; K 8192, N 10240 of
+// 256 rows 51 and 60, 82 and 61.)
 int quad_split_len(int nk, int s) { return (nk / 2 + s - 1) / s * 2; }
 bool quad_split_pays(int64_t mt, int nb, int nk, int s) {
   const double r = rounds_of(mt * ((nb + 1) / 2) * s);
@@ -1091,6 +1094,10 @@ size_t split_part_bytes(int64_t M, int nb, int bm, int splits) {
 // 12 of them 37.2, 31.1, 34.8, 29.0, 36.5; K 8192, N 8192 in 2, 3, 4 42.2, 34.1, 40.7; K 2048, N 2048 in 4 and 8 10.1, 11.2.
 // 110 rows: 44.1, 37.3, 38.9, 37.2, 41.7; 49.6, 39.9, 43.3; K 4096, N 6144 in 3, 4, 5 21.5, 19.7, 21.9.  (With 4.6 TB/s for
 // any launch, behind its start, the first of each three to five were chosen, and 8 of K 2048.)
+// The weights come from memory, as they do where the layers of a model follow each other.  Repeated calls find those of
+// one layer in the memory-side cache (256 MB), where fewer ranges are a little better: 110 rows of K 4096, N 6144 in 3 and 4
+// ranges 24.0 and 22.2 us from memory, 19.2 and 20.0 from the cache; the layer of 731 tokens with that projection 73.8 and
+// 72.0 where twelve layers take turns, 64.2 and 64.8 where one is repeated.
 double stream_us(int bm, int nb, int nk, int s, int len) {
   const double r = rounds_of((int64_t)nb * s), share = std::min(1.0, (double)nb * s / compute_unit_count());
   const double tb_s = (3.6 + 1.5 * share) * (s > 1 && len % 32 == 0 ? 0.82 : 1.0);
