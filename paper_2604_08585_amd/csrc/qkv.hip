@@ -770,15 +770,24 @@ __global__ __launch_bounds__(256) void qkv_split_reduce(QkvArgs a, int n_groups)
   float4 sum[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) sum[q] = src[q * 64];
-#pragma unroll 4
-  for (int s = 1; s < a.splits; ++s) {
-    src += stride;
+  // ranges that are on their way together: four, then two, then one (one after the other they cost 0.3 us each)
+  auto add = [&](auto n_c) {
+    constexpr int N = decltype(n_c)::value;
+    float4 t[N][4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float4 t = src[q * 64];
-      sum[q].x += t.x; sum[q].y += t.y; sum[q].z += t.z; sum[q].w += t.w;
-    }
-  }
+    for (int u = 0; u < N; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) t[u][q] = src[(u + 1) * stride + q * 64];
+    src += N * stride;
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) { sum[q].x += t[u][q].x; sum[q].y += t[u][q].y; sum[q].z += t[u][q].z; sum[q].w += t[u][q].w; }
+  };
+  int left = a.splits - 1;
+  for (; left >= 4; left -= 4) add(std::integral_constant<int, 4>{});
+  if (left & 2) add(std::integral_constant<int, 2>{});
+  if (left & 1) add(std::integral_constant<int, 1>{});
 #pragma unroll
   for (int q = 0; q < 4; ++q) sSum[(4 * wave + q) * 64 + lane] = sum[q];
   if (is_rope(EPI) && tid < 64) fill_rho(a, sRho, tid);
