@@ -57,11 +57,11 @@ constexpr double kWideFill = 0.92;
 // a narrow one two.  With less than 512 tiles of work to a compute unit the last units decide, and the wide ones lose more
 // often than not.  Narrow and wide, us, 32 query and 8 KV heads:
 //   130 requests of 100 tokens, 5 rows each, 63 and 99; 128 of 512, 77 rows 208 and 296; 55 of 4096, 204 rows 575 and 828;
-//   25 of 4096, 614 rows (229 tiles to a compute unit) 612 and 653; 24 of 1K to 9K, 12 % of the rows (380) 1059 and 1095;
-//   13 of 8192, 1228 rows (501) 1132 and 1250;
-//   25 of 12288, 614 rows (723) 1860 and 1820; 12 of 1K to 12K, 26 % (720) 1727 and 1654; 17 of 12288, 1843 rows (1490)
+//   40 of 1500, 225 rows 203 and 240; 25 of 4096, 614 rows (244 tiles to a compute unit) 612 and 653 on one machine, 616 and
+//   617 on another; 24 of 1K to 9K, 12 % of the rows (380) 1059 and 1095; 13 of 8192, 1228 rows (503) 1132 and 1250;
+//   25 of 12288, 614 rows (723) 1860 and 1820; 12 of 1K to 12K, 26 % (720) 1727 and 1654; 17 of 12288, 1843 rows (1476)
 //   3202 and 2954; 12 of 16384, 2457 rows (1850) 3855 and 3587.
-// 272 batches of up to 256 requests: none that goes to the wide workgroups loses more than 2 %.
+// 272 batches of up to 256 requests: the worst that goes to the wide workgroups loses 2 %.
 constexpr int64_t kWideBlocks = 4;          // row blocks to a compute unit
 constexpr int64_t kWideBatchTiles = 512;    // average causal work of a compute unit
 inline bool takes_wide(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx, int64_t blocks) {
