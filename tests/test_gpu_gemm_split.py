@@ -114,3 +114,27 @@ def test_gated_silu():
     ref = torch.nn.functional.silu(gate) * up
     err = (out.float() - ref).abs()
     assert bool((err <= 2.0 ** -8 * ref.abs() + 2.0 ** -7 * (1.1 * gate.abs() * up.abs()) + 2e-4).all()), float(err.max())
+
+
+@pytest.mark.parametrize("M,K,F", [
+    (16, 1024, 2816), (200, 1024, 2816),     # 44 column blocks that start at 16 k-tiles; one and two row tiles
+    (1, 64, 16448), (40, 128, 14336),        # one and two k-tiles, fewer than the loads on their way
+    (61, 4096, 14336), (128, 2048, 8192)])
+def test_gated_weight_stream(M, K, F):
+    """Few rows, undivided: column blocks that start at different k-tiles.  Bounds as above."""
+    print(f"gated weight stream M={M} K={K} F={F}", flush=True)
+    desc = qb.make_desc(DESC)
+    assert qb.load_library().qcf_linear_swiglu_workspace_bytes(C.byref(desc), M, K, F) == 0
+    x, w = _normal(12, M, K), _normal(13, 2 * F, K, std=K ** -0.5)
+    outs = []
+    for _ in range(2):
+        out = torch.full((M + 1, F), 7.0, dtype=BF, device=DEV)
+        qb.qcf_linear_swiglu(desc, x, M, K, w, F, out)
+        outs.append(out)
+    torch.cuda.synchronize()
+    y = (x.float() @ w.float().T).to(BF).float()
+    gate, up = y[:, :F], y[:, F:]
+    ref = torch.nn.functional.silu(gate) * up
+    err = (outs[0][:M].float() - ref).abs()
+    assert bool((err <= 2.0 ** -8 * ref.abs() + 2.0 ** -7 * (1.1 * gate.abs() * up.abs()) + 2e-4).all()), float(err.max())
+    assert torch.equal(outs[0], outs[1]) and bool((outs[0][M] == 7.0).all())
