@@ -154,7 +154,8 @@ __device__ __forceinline__ void split_classes(const u32x4& v, u32x4& fin, u32x4&
 //   values: chunk c of row r sits in slot c ^ (4 * (r % 4)), so the 8-byte transposing reads of
 //           8 consecutive rows x 64 bytes touch every bank exactly twice.
 // d = 64: rows of 128 bytes, two to a sweep over the banks, so the slots are c ^ (r / 2 % 8) and c ^ (4 * (r / 2 % 2)).
-template <int D>
+// F32: partial outputs are float (part_is_f32)
+template <int D, bool F32>
 __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnArgs a) {
   using C = AttnTile<D>;
   static_assert(kOrderLds <= C::LDS, "ordered_unit works in the tiles' LDS");
@@ -168,12 +169,14 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
 
   // consecutive workgroup ids land on different XCDs: give each XCD its own KV heads so that a
   // head's keys and values stay in one L2; later row blocks (longer key ranges) are scheduled first
-  // Launches without a plan take the row blocks from the last (longest key range) to the first.  The others
+  // Launches without a plan take the row blocks from the last (longest key range) to the first, first the top segments of all
+  // of them: the segments that a block does not have, and that end at once, then come last and not among the first 256, one
+  // to a compute unit.  The others
   // read the unit list attn_plan_kernel sorted by length, or find their place in it themselves; segments are counted from the top of
   // a block's key range, so a block's remainder segment is the one at the start of the context.
   const int g = (int)(blockIdx.x % a.Hkv);
   const int unit = (int)(blockIdx.x / a.Hkv);
-  int seg = unit % a.n_seg_max, blk = a.n_row_blocks - 1 - unit / a.n_seg_max;
+  int seg = unit / a.n_row_blocks, blk = a.n_row_blocks - 1 - unit % a.n_row_blocks;
   if (a.units) {
     if (unit >= a.units[0]) return;
     const int code = a.units[1 + unit];
@@ -184,6 +187,8 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
     blk = code >> 8;
     seg = code & 255;
   }
+  blk = __builtin_amdgcn_readfirstlane(blk);            // (wave-uniform, which the compiler does not see of the divisions)
+  seg = __builtin_amdgcn_readfirstlane(seg);
   int wg = blk;
   int b = 0;
   int64_t s0 = 0, s1 = 0;
@@ -420,23 +425,26 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
   // epilogue: output register v of tile dt is element 32*dt + 16*hf + v of this lane's row
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  const int64_t part_row = (((int64_t)blk * a.Hkv + g) * a.n_seg_max + seg) * C::WG_ROWS + r;    // of a split block
-  typename C::part_t* part = static_cast<typename C::part_t*>(a.part_o) + part_row * D + 16 * hf;
+  const int64_t unit_slot = ((int64_t)blk * a.Hkv + g) * a.n_seg_max + seg, part_row = unit_slot * C::WG_ROWS + r;    // of a split block
   bf16_t* orow = static_cast<bf16_t*>(a.o) + (srow * a.H + head) * D + 16 * hf;
   // x(dt, v): value of this lane's element 32 dt + 16 hf + v; m + log2(z): log2-sum-exp
   auto store_split = [&](auto x, float m, float z) {         // partial result of one key segment; merged by attn_merge_kernel
+    const int64_t at = (unit_slot * 4 + wave) * (32 * D);                   // in register order (see attn_merge_kernel)
+    if constexpr (F32) {
+      float* part = static_cast<float*>(a.part_o) + at;
 #pragma unroll
-    for (int dt = 0; dt < C::DT; ++dt) {
-      if constexpr (C::SPLIT_P) {
+      for (int dt = 0; dt < C::DT; ++dt)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<float4*>(part + 32 * dt + 4 * q) = make_float4(x(dt, 4 * q), x(dt, 4 * q + 1), x(dt, 4 * q + 2), x(dt, 4 * q + 3));
-      } else {
+          *reinterpret_cast<float4*>(part + (4 * dt + q) * 256 + lane * 4) = make_float4(x(dt, 4 * q), x(dt, 4 * q + 1), x(dt, 4 * q + 2), x(dt, 4 * q + 3));
+    } else {
+      bf16_t* part = static_cast<bf16_t*>(a.part_o) + at;
+#pragma unroll
+      for (int dt = 0; dt < C::DT; ++dt)
 #pragma unroll
         for (int h8 = 0; h8 < 16; h8 += 8)
-          *reinterpret_cast<u32x4*>(part + 32 * dt + h8) = mk4(cvt_pk_bf16(x(dt, h8), x(dt, h8 + 1)), cvt_pk_bf16(x(dt, h8 + 2), x(dt, h8 + 3)),
-                                                               cvt_pk_bf16(x(dt, h8 + 4), x(dt, h8 + 5)), cvt_pk_bf16(x(dt, h8 + 6), x(dt, h8 + 7)));
-      }
+          *reinterpret_cast<u32x4*>(part + (2 * dt + h8 / 8) * 512 + lane * 8) = mk4(cvt_pk_bf16(x(dt, h8), x(dt, h8 + 1)), cvt_pk_bf16(x(dt, h8 + 2), x(dt, h8 + 3)),
+                                                                          cvt_pk_bf16(x(dt, h8 + 4), x(dt, h8 + 5)), cvt_pk_bf16(x(dt, h8 + 6), x(dt, h8 + 7)));
     }
     if (hf == 0) {
       if (C::SPLIT_P) reinterpret_cast<float2*>(a.part_lse)[part_row] = make_float2(m, z);
@@ -635,21 +643,23 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(AttnArgs a) {
 }
 
 // Merge of the partial results of split row blocks: kMergeWgs workgroups per (row block, KV head), one
-// thread per 8 output elements.  out = sum_s w_s O_s with w_s = 2^(lse_s - lse), lse = log2 sum_s 2^lse_s.
+// thread per 8 output elements.  The partial outputs lie in the order of the registers they came from, 32 rows after the other:
+// vector (16 bytes) v of lane l at 64 v + l, for row l % 32 and elements 32 dt + 16 (l / 32) + 8 h .. + 7, v = 2 dt + h in bf16
+// and 4 dt + 2 h (+ 1) in float, so that a store or load of a wave is 1 KB.
+// out = sum_s w_s O_s with w_s = 2^(lse_s - lse), lse = log2 sum_s 2^lse_s.
 // weight * value; an infinite or NaN value keeps its class also where the weight has underflowed to 0 (SPLIT_P)
 template <bool SPLIT_P>
 __device__ __forceinline__ float weighted(float w, float f) {
   if (SPLIT_P) return fabsf(f) < INFINITY ? w * f : f;
   return w * f;
 }
-// element of the partial outputs
-template <int D, int ROWS> struct PartOf { typedef typename AttnTile<D>::part_t type; };
-template <> struct PartOf<128, kWideRows> { typedef float type; };
+// Element of the partial outputs: float, but for the 128-row workgroups of heads of 128 in launches that are not short, which
+// round them to bf16 (1229 rows x 32 heads over 8192 tokens write and read 20 MB of them so).
+constexpr bool part_is_f32(int D, int rows, const Split& s) { return D == 64 || rows == kWideRows || s.part_f32; }
 template <int D, int ROWS> constexpr int kMergeWgs = ROWS * (D / 8) / 256;
-template <int D, int ROWS>
+template <int D, int ROWS, bool F32>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
-  typedef typename PartOf<D, ROWS>::type part_t;
-  constexpr int CH = D / 8;                         // 8-element chunks of a row
+  typedef typename std::conditional<F32, float, bf16_t>::type part_t;
   const int tid = threadIdx.x;
   const int BR = a.block_rows;
   const int part = (int)(blockIdx.x % kMergeWgs<D, ROWS>);
@@ -685,7 +695,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     if (n_tiles <= a.seg_tiles) return;
   }
   const int n_seg = (n_tiles + a.seg_tiles - 1) / a.seg_tiles;
-  const int r = part * (256 / CH) + tid / CH, ch = tid % CH;    // row of the block, 8-element chunk
+  const int item = part * 256 + tid, w32 = item / (4 * D), v8 = item % (4 * D) / 64, lane = item % 64;
+  const int r = 32 * w32 + lane % 32, elem = 32 * (v8 >> 1) + 16 * (lane >> 5) + 8 * (v8 & 1);    // row of the block, first element
   const int64_t srow = s0 + (int64_t)wg * BR + r / a.G;
   const bool row_ok = srow < s1;
   const int head = g * a.G + r % a.G;
@@ -693,7 +704,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   const int64_t slot0 = ((int64_t)blk * a.Hkv + g) * a.n_seg_max;
   constexpr int PL = AttnTile<D>::SPLIT_P ? 2 : 1;   // floats per row
   const float* pl = a.part_lse + (slot0 * ROWS + r) * PL;
-  const part_t* po = static_cast<const part_t*>(a.part_o) + (slot0 * ROWS + r) * D + 8 * ch;
+  constexpr int VECS = sizeof(part_t) / 2;          // 16-byte vectors of 8 elements
+  const part_t* po = static_cast<const part_t*>(a.part_o) + (slot0 * ROWS + 32 * w32) * D + (VECS * v8 * 64 + lane) * Elem<part_t>::kVec;
   // four segments at a time: every load first, then the running maximum, the weights and the weighted sum
   constexpr bool SPLIT_P = AttnTile<D>::SPLIT_P;
   bool nan = false;                                 // (SPLIT_P) the denominator of some segment is NaN
@@ -701,15 +713,15 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int sg0 = 0; sg0 < n_seg; sg0 += 4) {
     float l[4], z[4];
-    u32x4 raw[4][sizeof(part_t) / 2];               // 8 elements
+    u32x4 raw[4][VECS];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const bool ok = row_ok && sg0 + u < n_seg;
       l[u] = ok ? pl[(int64_t)(sg0 + u) * ROWS * PL] : -INFINITY;
       z[u] = !SPLIT_P || !ok ? 1.f : pl[(int64_t)(sg0 + u) * ROWS * PL + 1];
 #pragma unroll
-      for (int w = 0; w < (int)sizeof(part_t) / 2; ++w)
-        raw[u][w] = ok ? *reinterpret_cast<const u32x4*>(po + (int64_t)(sg0 + u) * ROWS * D + w * Elem<part_t>::kVec) : u32x4{0u, 0u, 0u, 0u};
+      for (int w = 0; w < VECS; ++w)
+        raw[u][w] = ok ? *reinterpret_cast<const u32x4*>(po + (int64_t)(sg0 + u) * ROWS * D + w * 64 * Elem<part_t>::kVec) : u32x4{0u, 0u, 0u, 0u};
     }
     float mn = mx;
 #pragma unroll
@@ -728,7 +740,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
         if (SPLIT_P) w *= z[u];
         float f[8];
 #pragma unroll
-        for (int w = 0; w < (int)sizeof(part_t) / 2; ++w) Vec16<part_t>::unpack(raw[u][w], f + w * Elem<part_t>::kVec);
+        for (int w = 0; w < VECS; ++w) Vec16<part_t>::unpack(raw[u][w], f + w * Elem<part_t>::kVec);
         wsum += w;
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] += weighted<SPLIT_P>(w, f[e]);
@@ -752,13 +764,20 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
       for (int e = 0; e < 8; ++e) acc[e] = lse;
     }
   }
-  if (row_ok && a.lse && ch == 0) a.lse[srow * a.H + head] = lse;
-  if (row_ok)
-    *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(a.o) + (srow * a.H + head) * D + 8 * ch) = Vec16<bf16_t>::pack(acc);
+  if (row_ok && a.lse && elem == 0) a.lse[srow * a.H + head] = lse;
+  // the workgroup's 32 rows x 64 elements leave by whole lines: chunk c (16 bytes) of row r in slot c ^ (r % 8)
+  __shared__ u32x4 s_out[32 * 8];
+  s_out[(r & 31) * 8 + ((elem / 8 & 7) ^ (r & 7))] = Vec16<bf16_t>::pack(acc);
+  __syncthreads();
+  const int r_out = 32 * w32 + tid / 8, ch = tid % 8;
+  const int64_t srow_out = s0 + (int64_t)wg * BR + r_out / a.G;
+  if (srow_out < s1)
+    *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(a.o) + (srow_out * a.H + g * a.G + r_out % a.G) * D + (elem & ~63) + 8 * ch) =
+        s_out[tid / 8 * 8 + (ch ^ (r_out & 7))];
 }
 
 size_t part_o_bytes(int D, const Division& d, int Hkv) {
-  const size_t elem = D == 64 ? sizeof(PartOf<64, 128>::type) : d.rows == kWideRows ? sizeof(PartOf<128, kWideRows>::type) : sizeof(PartOf<128, 128>::type);
+  const size_t elem = part_is_f32(D, d.rows, d.split) ? sizeof(float) : sizeof(bf16_t);
   return align_up((size_t)d.n_row_blocks * Hkv * d.split.n_seg_max * d.rows * D * elem, 256);
 }
 size_t part_lse_bytes(int D, const Division& d, int Hkv) {
@@ -769,7 +788,7 @@ size_t units_bytes(int64_t n_row_blocks, int n_seg_max) {
 }
 size_t blk_tiles_bytes(int64_t n_row_blocks) { return align_up((size_t)n_row_blocks * sizeof(int32_t), 256); }
 
-template <int D, int ROWS>
+template <int D, int ROWS, bool F32>
 qcf_status run_mfma(const AttnArgs& a, hipStream_t st) {
   const int64_t blocks = (int64_t)a.n_row_blocks * a.Hkv;
   if (a.units) {
@@ -780,12 +799,12 @@ qcf_status run_mfma(const AttnArgs& a, hipStream_t st) {
     QCF_TRY(run_attn128(a, blocks * a.n_seg_max, st));
   } else {
     static std::atomic<uint64_t> lds_ok{0};
-    QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&attn_mfma_kernel<D>), AttnTile<D>::LDS, lds_ok));
-    attn_mfma_kernel<D><<<dim3((unsigned)(blocks * a.n_seg_max)), dim3(256), AttnTile<D>::LDS, st>>>(a);
+    QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&attn_mfma_kernel<D, F32>), AttnTile<D>::LDS, lds_ok));
+    attn_mfma_kernel<D, F32><<<dim3((unsigned)(blocks * a.n_seg_max)), dim3(256), AttnTile<D>::LDS, st>>>(a);
     QCF_TRY_LAUNCH("attn");
   }
   if (a.n_seg_max > 1) {
-    attn_merge_kernel<D, ROWS><<<dim3((unsigned)(blocks * kMergeWgs<D, ROWS>)), dim3(256), 0, st>>>(a);
+    attn_merge_kernel<D, ROWS, F32><<<dim3((unsigned)(blocks * kMergeWgs<D, ROWS>)), dim3(256), 0, st>>>(a);
     return check_launch("attn merge");
   }
   return QCF_OK;
@@ -847,7 +866,7 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
       // 63.4 and 58.7, heads of 64 49.4 and 45.8; 410 rows over 8192 50.7 and 46.9, 1229 over 8192 116.0 and 110.2.  An
       // order from the host, for rows taken to be spread evenly, was 2 us faster still on such rows and up to 18 % slower
       // than the list on rows gathered in two places.
-      if (nb * a.Hkv * sp.n_seg_max <= resident_workgroups(d.rows)) {
+      if (nb * a.Hkv * sp.n_seg_max <= resident_workgroups(d.rows) || sp.part_f32) {      // (short launches: segments of one length)
       } else if (B == 1 && nb * sp.n_seg_max <= kOrderMax && nb <= kOrderBlocks) {
         a.own_order = 1;
       } else {
@@ -855,8 +874,9 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
         a.blk_tiles = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(a.units) + units_bytes(nb, sp.n_seg_max));
       }
     }
-    if (a.D == 64) return run_mfma<64, 128>(a, st);
-    return d.rows == kWideRows ? run_mfma<128, kWideRows>(a, st) : run_mfma<128, 128>(a, st);
+    if (a.D == 64) return run_mfma<64, kNarrowRows, true>(a, st);
+    if (d.rows == kWideRows) return run_mfma<128, kWideRows, true>(a, st);
+    return part_is_f32(a.D, d.rows, sp) ? run_mfma<128, kNarrowRows, true>(a, st) : run_mfma<128, kNarrowRows, false>(a, st);
   }
   if (total_sel * a.H > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "attn: grid too large");
   const dim3 grid((unsigned)(total_sel * a.H)), block(256);

@@ -457,16 +457,16 @@ __global__ __launch_bounds__(256, 1) void attn128_kernel(AttnArgs a) {
     if (split) {
       // (fp32: bf16 would be rounded once more than in a whole block; 1229 rows over 8192 tokens 2.22e-3 off in the 2-norm
       // of the difference, 2.33e-3 with bf16)
-      const int64_t part_row = (((int64_t)blk * a.Hkv + g) * a.n_seg_max + seg) * kWgRows + wave * 32 * kRB + 32 * rb + l_end;
-      float* dst = static_cast<float*>(a.part_o) + part_row * D + 16 * hf;
+      const int64_t row0 = (((int64_t)blk * a.Hkv + g) * a.n_seg_max + seg) * kWgRows + wave * 32 * kRB + 32 * rb;
+      float* dst = static_cast<float*>(a.part_o) + row0 * D + (32 * hf + l_end) * 4;      // in register order
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int v = 0; v < 16; v += 4) {
           const floatx16& o = oacc[rb][dt];
-          *reinterpret_cast<float4*>(dst + 32 * dt + v) = make_float4(o[v] * inv, o[v + 1] * inv, o[v + 2] * inv, o[v + 3] * inv);
+          *reinterpret_cast<float4*>(dst + (4 * dt + v / 4) * 256) = make_float4(o[v] * inv, o[v + 1] * inv, o[v + 2] * inv, o[v + 3] * inv);
         }
-      if (hf == 0) a.part_lse[part_row] = l_tot > 0.f ? m_use[rb] + log2f(l_tot) : -INFINITY;
+      if (hf == 0) a.part_lse[row0 + l_end] = l_tot > 0.f ? m_use[rb] + log2f(l_tot) : -INFINITY;
     } else if (row.ok) {
       bf16_t* dst = static_cast<bf16_t*>(a.o) + (row.sel * a.H + row.head) * D + 16 * hf;
 #pragma unroll

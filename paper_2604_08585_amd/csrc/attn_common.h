@@ -39,7 +39,7 @@ struct AttnArgs {
   int n_row_blocks;      // upper bound on row blocks over all requests (MFMA path)
   int seg_tiles;         // key tiles per work unit; a row block with more tiles is split over units
   int n_seg_max;         // units per row block the grid provides
-  void* part_o;          // [unit][rows of a workgroup][D] normalised partial outputs of split row blocks (AttnTile<D>::part_t; float for the wide workgroups)
+  void* part_o;          // [unit][rows of a workgroup][D] normalised partial outputs of split row blocks (PartOf in attn.hip)
   float* part_lse;       // [unit][rows of a workgroup] log2-domain log-sum-exp of each partial (-inf: no visible key); d = 64: pairs of
                          // reference point (log2 units) and denominator against it
   int32_t* units;        // units[0] = number of work units, then (row block << 8 | segment), longest first (null: no plan)
@@ -60,7 +60,6 @@ struct AttnTile {
   static constexpr int WGS = 2;                         // resident workgroups per compute unit (registers)
   static constexpr bool SPLIT_P = D == 64;              // probabilities as three bf16 terms, fp32 partial outputs,
                                                         // rows that are not finite computed again
-  typedef typename std::conditional<SPLIT_P, float, bf16_t>::type part_t;
   static constexpr float K2 = kLog2e * (D == 128 ? 0.08838834764831845f : 0.125f);      // log2(e) / sqrt(D)
 };
 // Slot of 16-byte chunk c of token row r inside the row, keys and values (see the layouts below).

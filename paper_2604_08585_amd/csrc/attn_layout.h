@@ -20,18 +20,45 @@ constexpr int kPlanMaxBlocks = 4096;        // row blocks a split launch may hav
 // Key tiles per work unit.  With enough row blocks the causal triangle balances by itself and blocks
 // stay whole; otherwise a segment is about the average causal work of a resident workgroup.
 inline int resident_workgroups(int rows) { return (rows == kWideRows ? 1 : 2) * compute_unit_count(); }
-struct Split { int seg_tiles, n_seg_max; };
+constexpr int kShortTiles = 8, kShortSegments = 12;
+struct Split { int seg_tiles, n_seg_max; bool part_f32 = false; };      // part_f32: partial outputs of heads of 128 in float
 inline Split choose_split(int rows, int64_t n_blocks, int64_t total_ctx) {
   const int slots = resident_workgroups(rows);
   const int64_t n_t = std::max<int64_t>(1, (total_ctx + kBKV - 1) / kBKV);
   const int64_t per_slot = n_blocks * ((n_t + 1) / 2) / slots;     // average causal work per resident workgroup
   // a little above that average (a multiple of 4 tiles): most resident workgroups then take one whole
   // segment and the remainders fill the rest (measured best at recompute ratios 0.05, 0.15 and 0.30)
-  int64_t seg = std::max<int64_t>(8, (per_slot * 27 / 25 + 3) / 4 * 4);
+  int64_t seg = std::max<int64_t>(kShortTiles, (per_slot * 27 / 25 + 3) / 4 * 4);
   while ((n_t + seg - 1) / seg > 256) seg *= 2;       // a unit's segment number is kept in 8 bits
   if (n_blocks > kPlanMaxBlocks) seg = n_t;            // (never the case when splitting pays: see per_slot)
   if (seg >= n_t) return Split{(int)std::min<int64_t>(n_t, 0x3fffffff), 1};
   return Split{(int)seg, (int)((n_t + seg - 1) / seg)};
+}
+
+// Short launches of one request, which choose_split would give segments of kShortTiles tiles or none: a unit that has a compute
+// unit to itself (half of the block-segment pairs lie above the diagonal and end at once) takes 1.26 us per tile, so shorter
+// segments pay until their partial outputs, the merge's loop over them and its launch weigh more.  Their partial outputs are
+// float: rows that were not divided before are not rounded once more.  Estimate in microseconds behind what every launch takes.
+// Attention calls, us, as choose_split has it and so, 32 query and 8 KV heads of 128: 77 rows over 512 tokens 14.4 and 13.8,
+// 96 over 640 18.9, 15.0; 30 over 731 19.3, 13.5; 110 over 731 19.0, 16.0; 150 over 1000 19.3, 17.4; 60 over 1500 19.5, 16.5;
+// 100 over 2048 20.2, 20.1.  The other side of the line: 40 rows over 448 13.2 whole and in segments of 2; 225 over 1500 20.9 in
+// segments of 8, 21.7 of 6; 307 over 2048 25.8, 27.9; 120 over 3000 22.2, 24.4.  Heads of 64: 110 over 731 20.9, 14.9; 100 over
+// 2048 22.3, 18.9; 307 over 2048 28.8, 27.2; with 16 segments, 60 over 6000, 25.8 and 28.8.
+inline Split short_split(int head_dim, double filled_blocks, int64_t total_ctx, Split general) {
+  const int64_t n_t = std::max<int64_t>(1, (total_ctx + kBKV - 1) / kBKV);
+  const bool whole = general.n_seg_max == 1;
+  if (whole ? n_t > 2 * kShortTiles : general.seg_tiles > kShortTiles) return general;
+  auto segments = [&](int64_t s) { return (int)((n_t + s - 1) / s); };
+  auto units = [&](int64_t s) { return filled_blocks * ((double)n_t / (2.0 * (double)s) + 0.5); };
+  auto us = [&](int64_t s, double per_unit) { return 1.26 * (double)s + per_unit * units(s) + 0.3 * segments(s) + 4.2; };
+  double best = whole ? 1.26 * (double)n_t : us(kShortTiles, head_dim == 128 ? 0.02 : 0.03);
+  Split sp = general;
+  for (int64_t s = 2; s <= kShortTiles && s < n_t; ++s) {
+    if (units(s) > compute_unit_count() || segments(s) > kShortSegments) continue;
+    const double t = us(s, head_dim == 128 ? 0.035 : 0.03) + 0.3;
+    if (t < best) { best = t; sp = Split{(int)s, segments(s), true}; }
+  }
+  return sp;
 }
 
 // How a launch is divided: rows of a workgroup, row blocks of all requests (upper bound), key segments.
@@ -81,7 +108,9 @@ inline Division divide(const qcf_layer_desc& L, int32_t B, int64_t total_sel, in
     const Division wide = of(kWideRows);
     if (takes_wide(L, B, total_sel, total_ctx, wide.n_row_blocks * L.n_kv_heads)) return wide;
   }
-  return of(kNarrowRows);
+  Division d = of(kNarrowRows);
+  if (B == 1) d.split = short_split(L.head_dim, (double)total_sel * L.n_q_heads / kNarrowRows, total_ctx, d.split);
+  return d;
 }
 
 }  // namespace attn
