@@ -5,6 +5,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 from typing import List, Optional, Sequence
 
 import numpy as np
@@ -35,6 +36,9 @@ LAYERS_EXPORTS = ["qcf_score_layers_workspace_bytes", "qcf_score_layers"]
 
 # declared in qcf_anchors.h
 ANCHORS_EXPORTS = ["qcf_extract_anchors_workspace_bytes", "qcf_extract_anchors"]
+
+# declared in qcf_fuse.h
+FUSE_EXPORTS = ["qcf_fuse_layer"]
 
 
 class QcfError(RuntimeError):
@@ -124,6 +128,8 @@ def load_library() -> C.CDLL:
     lib.qcf_extract_anchors_workspace_bytes.argtypes = [dp, i32, i64]
     lib.qcf_extract_anchors.restype = C.c_int
     lib.qcf_extract_anchors.argtypes = [dp, vp, vp, i32, op, op, vp, vp, vp, vp, sz, vp]
+    lib.qcf_fuse_layer.restype = C.c_int
+    lib.qcf_fuse_layer.argtypes = [dp, C.c_char_p, i32, vp]
     lib.qcf_key_norm.restype = C.c_int
     lib.qcf_key_norm.argtypes = [dp, vp, i64, vp, vp]
     lib.qcf_gather.restype = C.c_int
@@ -328,6 +334,41 @@ def qcf_recompute_attn(desc: LayerDesc, B: int, q_sel: torch.Tensor, sel_pos: to
     _check(lib.qcf_recompute_attn(C.byref(desc), B, _ptr(q_sel), _ptr(sel_pos), _ptr(sel_off), total_sel,
                                   _ptr(k_fused), _ptr(v_fused), _ptr(ctx_off), total_ctx, _ptr(ctx_pos0),
                                   _ptr(o_out), _ptr(lse_out), wp, wn, _stream()))
+
+
+# qcf_layer_buffers: 2 counts, 3 totals, 18 pointers, 5 workspaces and their sizes
+_LAYER_BUFFERS = struct.Struct("2i3q18Q5Q5Q")
+
+
+def qcf_fuse_layer(desc: LayerDesc, critical: bool, B: int, n_chunks: int, total_ctx: int, total_probe: int, total_sel: int,
+                   chunks_dev: torch.Tensor, ctx_off: torch.Tensor, probe_off: Optional[torch.Tensor], sel_off: torch.Tensor,
+                   q_probe: Optional[torch.Tensor], x_ctx: torch.Tensor, w_qkv: torch.Tensor, k_fused: torch.Tensor,
+                   v_fused: torch.Tensor, score: Optional[torch.Tensor], sel_idx: Optional[torch.Tensor], sel_row: torch.Tensor,
+                   sel_pos: torch.Tensor, q_sel: torch.Tensor, k_sel: torch.Tensor, v_sel: torch.Tensor, o_sel: torch.Tensor,
+                   lse: Optional[torch.Tensor], ws_rerope: Optional[torch.Tensor] = None, ws_score: Optional[torch.Tensor] = None,
+                   ws_select: Optional[torch.Tensor] = None, ws_qkv: Optional[torch.Tensor] = None,
+                   ws_attn: Optional[torch.Tensor] = None) -> None:
+    """One layer in one call: qcf_rerope [-> qcf_score -> qcf_select at the critical layer] -> qcf_recompute_qkv_scatter ->
+    qcf_recompute_attn.  probe_off, q_probe, score and sel_idx are not looked at elsewhere."""
+    lib = load_library()
+    dev = k_fused.device
+    if not critical:
+        probe_off = q_probe = score = sel_idx = ws_score = ws_select = None
+    elif ws_score is None:
+        ws_score = _workspace(qcf_score_workspace_bytes(desc, B, total_probe, total_ctx), dev)
+    if ws_rerope is None:
+        ws_rerope = _workspace(qcf_rerope_workspace_bytes(desc, n_chunks, total_ctx), dev)
+    if ws_select is None and critical:
+        ws_select = _workspace(qcf_select_workspace_bytes(B, total_ctx), dev)
+    if ws_qkv is None:
+        ws_qkv = _workspace(qcf_recompute_qkv_workspace_bytes(desc, total_sel), dev)
+    if ws_attn is None:
+        ws_attn = _workspace(qcf_recompute_attn_workspace_bytes(desc, B, total_sel, total_ctx), dev)
+    ptrs = [_ptr(t) or 0 for t in (chunks_dev, ctx_off, probe_off, sel_off, q_probe, x_ctx, w_qkv, k_fused, v_fused, score, sel_idx,
+                                   sel_row, sel_pos, q_sel, k_sel, v_sel, o_sel, lse)]
+    ws = [(0, 0) if w is None else (w.data_ptr(), w.numel()) for w in (ws_rerope, ws_score, ws_select, ws_qkv, ws_attn)]
+    args = _LAYER_BUFFERS.pack(B, n_chunks, total_ctx, total_probe, total_sel, *ptrs, *[p for p, _ in ws], *[n for _, n in ws])
+    _check(lib.qcf_fuse_layer(C.byref(desc), args, int(critical), _stream()))
 
 
 def qcf_linear_workspace_bytes(desc: LayerDesc, M: int, K: int, N: int) -> int:

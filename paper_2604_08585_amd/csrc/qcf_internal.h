@@ -12,6 +12,7 @@
 #include "qcf_ffn.h"
 #include "qcf_layers.h"
 #include "qcf_anchors.h"
+#include "qcf_fuse.h"
 
 namespace qcf {
 

@@ -170,9 +170,15 @@ FUSED_STEPS = (("rerope", step_rerope), ("score", step_score), ("select", step_s
 
 
 def enqueue_layer(L: DeviceLayer, critical: bool = True, fused: bool = True) -> None:
-    """rerope -> [score -> select at the critical layer] -> qkv -> scatter -> attn; with `fused` the projection
-    writes the cache rows itself (qcf_recompute_qkv_scatter), otherwise qcf_scatter runs as a call of its own."""
-    for name, fn in (FUSED_STEPS if fused else STEPS):
+    """rerope -> [score -> select at the critical layer] -> qkv -> scatter -> attn; with `fused` one call in which the
+    projection writes the cache rows itself (qcf_fuse_layer; FUSED_STEPS one after the other), otherwise six."""
+    if fused:
+        qb.qcf_fuse_layer(L.desc, critical, L.B, L.n_chunks, L.total_ctx, L.total_probe, L.total_sel, L.chunks_dev, L.ctx_off,
+                          L.probe_off, L.sel_off, L.q_probe, L.x_ctx, L.w_qkv, L.k_fused, L.v_fused, L.score, L.sel_idx,
+                          L.sel_row, L.sel_pos, L.q_sel, L.k_sel, L.v_sel, L.o_sel, L.lse, L.ws_rerope, L.ws_score,
+                          L.ws_select, L.ws_qkv, L.ws_attn)
+        return
+    for name, fn in STEPS:
         if not critical and name in ("score", "select"):
             continue
         fn(L)
