@@ -44,7 +44,8 @@ typedef struct qcf_layer_buffers {
 
 /* qcf_rerope, at the critical layer qcf_score and qcf_select, qcf_recompute_qkv_scatter and qcf_recompute_attn, one after the
  * other: same results, arguments checked call by call.  A call that fails ends the layer; what is in front of it has been
- * enqueued. */
+ * enqueued.  Where qcf_score is the one kernel whose workgroups wait for each other, so is its part here, and one request's keys
+ * and values are re-rotated by that kernel. */
 qcf_status qcf_fuse_layer(const qcf_layer_desc* desc, const qcf_layer_buffers* layer, int32_t critical, void* stream);
 
 #ifdef __cplusplus

@@ -151,9 +151,8 @@ size_t qcf_rerope_workspace_bytes(const qcf_layer_desc* desc, int32_t n_chunks, 
   return rerope_workspace(*desc, n_chunks, total_rows);
 }
 
-qcf_status qcf_rerope(const qcf_layer_desc* desc, const qcf_chunk* chunks_dev, int32_t n_chunks,
-                      int64_t total_rows, void* k_fused, void* v_fused, void* workspace,
-                      size_t workspace_bytes, void* stream) {
+static qcf_status check_rerope_args(const qcf_layer_desc* desc, const qcf_chunk* chunks_dev, int32_t n_chunks, int64_t total_rows,
+                                    const void* k_fused, const void* v_fused, const void* workspace, size_t workspace_bytes) {
   QCF_TRY(check_desc(desc));
   if (n_chunks < 0 || total_rows < 0) return fail(QCF_ERR_INVALID_ARG, "negative size");
   if (total_rows > kMaxRows) return fail(QCF_ERR_UNSUPPORTED, "total_rows %lld too large", (long long)total_rows);
@@ -162,7 +161,14 @@ qcf_status qcf_rerope(const qcf_layer_desc* desc, const qcf_chunk* chunks_dev, i
     return fail(QCF_ERR_INVALID_ARG, "chunks_dev is NULL or misaligned");
   QCF_TRY(need_ptr(k_fused, "k_fused"));
   QCF_TRY(opt_ptr(v_fused, "v_fused"));
-  QCF_TRY(need_ws(workspace, workspace_bytes, rerope_workspace(*desc, n_chunks, total_rows)));
+  return need_ws(workspace, workspace_bytes, rerope_workspace(*desc, n_chunks, total_rows));
+}
+
+qcf_status qcf_rerope(const qcf_layer_desc* desc, const qcf_chunk* chunks_dev, int32_t n_chunks,
+                      int64_t total_rows, void* k_fused, void* v_fused, void* workspace,
+                      size_t workspace_bytes, void* stream) {
+  QCF_TRY(check_rerope_args(desc, chunks_dev, n_chunks, total_rows, k_fused, v_fused, workspace, workspace_bytes));
+  if (n_chunks == 0 || total_rows == 0) return QCF_OK;
   return launch_rerope(*desc, chunks_dev, n_chunks, total_rows, k_fused, v_fused, workspace,
                        (hipStream_t)stream);
 }
@@ -371,10 +377,24 @@ qcf_status qcf_recompute_attn(const qcf_layer_desc* desc, int32_t B, const void*
 qcf_status qcf_fuse_layer(const qcf_layer_desc* desc, const qcf_layer_buffers* layer, int32_t critical, void* stream) {
   if (!layer) return fail(QCF_ERR_INVALID_ARG, "layer buffers are NULL");
   const qcf_layer_buffers& b = *layer;
-  QCF_TRY(qcf_rerope(desc, b.chunks_dev, b.n_chunks, b.total_ctx, b.k_fused, b.v_fused, b.rerope_ws, b.rerope_ws_bytes, stream));
+  // One request in the single scoring kernel: it turns the keys itself.  (Only where scoring will not fail: the cache is whole
+  // otherwise.)
+  bool empty = false;
+  QCF_TRY(check_rerope_args(desc, b.chunks_dev, b.n_chunks, b.total_ctx, b.k_fused, b.v_fused, b.rerope_ws, b.rerope_ws_bytes));
+  const bool joined = critical && b.total_ctx > 0 && b.v_fused &&
+                      score_takes_rerope(*desc, b.B, b.n_chunks, b.total_probe, b.total_ctx) &&
+                      check_score_args(desc, b.B, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.ctx_off_dev, b.total_ctx,
+                                       nullptr, b.score, &empty) == QCF_OK &&
+                      need_ws(b.score_ws, b.score_ws_bytes, scoring::workspace(*desc, b.B, b.total_probe, b.total_ctx)) == QCF_OK;
+  if (joined)
+    QCF_TRY(launch_rerope_score(*desc, b.chunks_dev, b.n_chunks, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.v_fused,
+                                b.ctx_off_dev, b.total_ctx, b.score, b.score_ws, (hipStream_t)stream));
+  else
+    QCF_TRY(qcf_rerope(desc, b.chunks_dev, b.n_chunks, b.total_ctx, b.k_fused, b.v_fused, b.rerope_ws, b.rerope_ws_bytes, stream));
   if (critical) {
-    QCF_TRY(qcf_score(desc, b.B, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.ctx_off_dev, b.total_ctx, nullptr,
-                      b.score, b.score_ws, b.score_ws_bytes, stream));
+    if (!joined)
+      QCF_TRY(qcf_score(desc, b.B, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.ctx_off_dev, b.total_ctx, nullptr,
+                        b.score, b.score_ws, b.score_ws_bytes, stream));
     QCF_TRY(qcf_select(b.B, b.score, b.ctx_off_dev, b.total_ctx, b.sel_off_dev, b.total_sel, nullptr, b.sel_idx, b.sel_row,
                        b.sel_pos, b.select_ws, b.select_ws_bytes, stream));
   }

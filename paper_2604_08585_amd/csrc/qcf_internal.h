@@ -116,6 +116,12 @@ template <> struct Vec16<bf16_t> {
   }
 };
 
+// a rotary pair turned by (cos, sin)
+__device__ __forceinline__ void turn_pair(float a, float b, float2 w, float& oa, float& ob) {
+  oa = a * w.x - b * w.y;
+  ob = b * w.x + a * w.y;
+}
+
 // ---- gfx950 helpers shared by the MFMA kernels ---------------------------------------
 typedef float floatx2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -202,6 +208,12 @@ qcf_status check_score_args(const qcf_layer_desc* desc, int32_t B, const void* q
 qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const int64_t* probe_off,
                         int64_t total_probe, const void* k, const int64_t* ctx_off, int64_t total_ctx,
                         const int32_t* probe_limit, float* score, float alpha, float beta, void* ws, hipStream_t st);
+
+// re-rotation and scoring of one request in one launch, where score_takes_rerope (bf16 heads of 128, no probe_limit)
+bool score_takes_rerope(const qcf_layer_desc& L, int32_t B, int32_t n_chunks, int64_t total_probe, int64_t total_ctx);
+qcf_status launch_rerope_score(const qcf_layer_desc& L, const qcf_chunk* chunks, int32_t n_chunks, const void* q,
+                               const int64_t* probe_off, int64_t total_probe, void* k, void* v, const int64_t* ctx_off,
+                               int64_t total_ctx, float* score, void* ws, hipStream_t st);
 
 qcf_status launch_score_layers(const qcf_layer_desc& L, int32_t n_layers, int32_t B, const void* const* q,
                                const int64_t* probe_off, int64_t total_probe, const void* const* k, const int64_t* ctx_off,

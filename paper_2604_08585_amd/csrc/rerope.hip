@@ -122,8 +122,7 @@ __global__ __launch_bounds__(kThreads) void rerope_fused_kernel(
     const float2 w = my[p];
     const int ia = (STYLE == 0) ? p : 2 * p;
     const int ib = (STYLE == 0) ? p + VEC : 2 * p + 1;
-    o[ia] = f[ia] * w.x - f[ib] * w.y;
-    o[ib] = f[ib] * w.x + f[ia] * w.y;
+    turn_pair(f[ia], f[ib], w, o[ia], o[ib]);
   }
   T* kdst = kf + r * g.row_elems;
   *reinterpret_cast<u32x4*>(kdst + e0) = Vec16<T>::pack(o);
@@ -182,8 +181,7 @@ __global__ __launch_bounds__(kThreads) void rerope_main_kernel(
     const float2 w = my[p];
     const int ia = (STYLE == 0) ? p : 2 * p;
     const int ib = (STYLE == 0) ? p + VEC : 2 * p + 1;
-    o[ia] = f[ia] * w.x - f[ib] * w.y;
-    o[ib] = f[ib] * w.x + f[ia] * w.y;
+    turn_pair(f[ia], f[ib], w, o[ia], o[ib]);
   }
   T* kdst = kf + r * g.row_elems;
   *reinterpret_cast<u32x4*>(kdst + e0) = Vec16<T>::pack(o);

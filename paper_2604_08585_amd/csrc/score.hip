@@ -23,7 +23,7 @@
 // Launches that are resident at once (one workgroup per compute unit at most, up to 320 probe rows per KV
 // group) take a single kernel instead (score_fused, further down): the exponentials of pass 1 stay in registers
 // across a grid-wide exchange of the per-row partials, so the keys are read once and no second pass or reduce
-// kernel runs.
+// kernel runs.  For a layer of one request it turns the keys as well (RR).
 // No floating-point atomics anywhere, so scores (and the indices selected from them) are
 // bit-stable from run to run.
 //
@@ -678,6 +678,16 @@ constexpr uint32_t kSpinLimit = 1u << 20;  // polls (a microsecond or two each) 
 
 __device__ uint32_t g_sync[kSyncSlots * kSyncWords];
 
+// Re-rotation in front of the scoring (RR): the chunks whose keys and values make up the cache that s.k points to.
+constexpr int kMaxRotChunks = 128;        // chunk table in LDS
+struct Rerotation {
+  const qcf_chunk* chunks;
+  int n_chunks, style;
+  double neg2_over_d_log2base;
+  bf16_t* k;                 // the fused cache, keys (s.k) and values
+  bf16_t* v;
+};
+
 struct FusedArgs {
   ScoreArgs s;
   float2* part;        // [tile][Hkv][kRowBlock] (max2, sumexp2) of the tile, published with atomic stores
@@ -685,6 +695,7 @@ struct FusedArgs {
   uint32_t* sync;      // this launch's counter slot
   int n_wg_tiles;      // tiles the grid provides (upper bound on the tiles of all requests)
   uint32_t spin_limit;
+  Rerotation r;
 };
 
 __device__ __forceinline__ void publish(float2* p, float2 v) {
@@ -713,7 +724,91 @@ __device__ __forceinline__ float half_wave_sum(float x) {
   return __uint_as_float(r.x) + __uint_as_float(r.y);     // rows (0, 1) and (2, 3) of 16 lanes each
 }
 
-template <bool LIMIT>
+constexpr size_t kFusedLds = kQBytes<128> + kKBytes<128>;
+// Re-rotation of a tile (RR): the chunk table, each row's chunk, and the (cos, sin) pairs of the tile's chunks, behind the
+// staged rows.
+constexpr int kRotChunks = 8;                     // chunks whose pairs are kept at a time
+struct RotLds {
+  qcf_chunk table[kMaxRotChunks];
+  const char* k[kTokPerWg];                       // source of a row, for this KV head (row of no chunk: itself)
+  const char* v[kTokPerWg];
+  int chunk[kTokPerWg];                           // of a row, -1: none
+  float2 cs[kRotChunks * 64];
+};
+static_assert(sizeof(qcf_chunk) % 8 == 0, "copied in words of 8 bytes");
+constexpr size_t kFusedRotLds = kFusedLds + sizeof(RotLds);
+static_assert(kFusedRotLds + 1024 <= 160 * 1024, "one workgroup's LDS");
+
+// (cos, sin) of pair i for the shift of a chunk, as qcf_rerope takes it
+__device__ __forceinline__ float2 shift_pair(const qcf_chunk& c, double neg2_over_d_log2base, int i) {
+  const double theta = exp2(neg2_over_d_log2base * (double)i);
+  double sn, cn;
+  sincos((double)(c.dst_pos0 - c.src_pos0) * theta, &sn, &cn);
+  return make_float2((float)cn, (float)sn);
+}
+
+// number of the last chunk that starts at or before a row (0 if none)
+__device__ __forceinline__ int chunk_of(const qcf_chunk* table, int n, int64_t row) {
+  int lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (table[mid].dst_row <= row) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
+__device__ __forceinline__ bf16x8 pack8(const float* o) {
+  return __builtin_bit_cast(bf16x8, mk4(cvt_pk_bf16(o[0], o[1]), cvt_pk_bf16(o[2], o[3]), cvt_pk_bf16(o[4], o[5]), cvt_pk_bf16(o[6], o[7])));
+}
+// Turns the key fragments of a lane's row by the pairs at cs: element e of fragment ks is 16 ks + 8 hf + e of the row.
+__device__ __forceinline__ void turn_frags(bf16x8 (&kf)[8], const float2* cs, int hf, bool interleaved) {
+  if (!interleaved) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      float f[16], o[16];
+      Vec16<bf16_t>::unpack(__builtin_bit_cast(u32x4, kf[ks]), f);
+      Vec16<bf16_t>::unpack(__builtin_bit_cast(u32x4, kf[ks + 4]), f + 8);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) turn_pair(f[e], f[e + 8], cs[16 * ks + 8 * hf + e], o[e], o[e + 8]);
+      kf[ks] = pack8(o);
+      kf[ks + 4] = pack8(o + 8);
+    }
+  } else {
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      float f[8], o[8];
+      Vec16<bf16_t>::unpack(__builtin_bit_cast(u32x4, kf[ks]), f);
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) turn_pair(f[e], f[e + 1], cs[8 * ks + 4 * hf + e / 2], o[e], o[e + 1]);
+      kf[ks] = pack8(o);
+    }
+  }
+}
+
+// One row and KV head that no tile covers (cache rows outside the request), by one wave.
+__device__ __forceinline__ void rerotate_row(const Rerotation& r, const qcf_chunk* table, int64_t row, int Hkv, int g, int lane) {
+  const qcf_chunk ch = table[chunk_of(table, r.n_chunks, row)];
+  if (row < ch.dst_row || row >= ch.dst_row + ch.len) return;
+  const int64_t src = (row - ch.dst_row) * Hkv * 128 + g * 128, dst = row * Hkv * 128 + g * 128;
+  const bf16_t* k = static_cast<const bf16_t*>(ch.k_src) + src;
+  const bf16_t* v = static_cast<const bf16_t*>(ch.v_src) + src;
+  const int ia = r.style == 0 ? lane : 2 * lane, ib = r.style == 0 ? lane + 64 : 2 * lane + 1;
+  float a, b;
+  turn_pair(bf16_to_f32(k[ia]), bf16_to_f32(k[ib]), shift_pair(ch, r.neg2_over_d_log2base, lane), a, b);
+  r.k[dst + ia] = f32_to_bf16(a);
+  r.k[dst + ib] = f32_to_bf16(b);
+  r.v[dst + lane] = v[lane];
+  r.v[dst + 64 + lane] = v[64 + lane];
+}
+
+// RR: the keys of the tile come from the chunk caches, are turned to their global positions in the registers that score them
+// and written to the fused cache from there; the values are copied while the first hand-off is on its way.  Saves the launch of qcf_rerope,
+// its pass over the cache and the reading of the keys.  Re-rotation and scoring, us, in two launches and in one: 731 tokens, 96
+// rows of a group 5.7 + 13.9 and 18.9; 4096, 160 rows 8.6 + 17.3 and 22.6; 8192, 320 rows 13.8 + 27.4 and 34.7.  Everything in
+// front of the keys' loads is a chain of latencies (with the rows' sources looked up by every use of them 19.7, 23.8 and 36.9;
+// with the values prefetched into the L2 as well 22.2, 26.0 and 37.5; copied in front of the first hand-off, which then waits
+// for their stores, 23.4, 28.5 and 42.0).
+template <bool LIMIT, bool RR>
 __global__ __launch_bounds__(kFusedThreads) void score_fused(FusedArgs fa) {
   constexpr int D = 128;
   const ScoreArgs& a = fa.s;
@@ -731,6 +826,10 @@ __global__ __launch_bounds__(kFusedThreads) void score_fused(FusedArgs fa) {
   const int wg_tile = (int)(blockIdx.x / a.Hkv);
   const int n_wg = fa.n_wg_tiles * a.Hkv;
 
+  RotLds& rot = *reinterpret_cast<RotLds*>(smem + kFusedLds);  // (RR)
+  if constexpr (RR)
+    for (int i = tid; i < fa.r.n_chunks * (int)(sizeof(qcf_chunk) / 8); i += kFusedThreads)
+      reinterpret_cast<uint64_t*>(rot.table)[i] = reinterpret_cast<const uint64_t*>(fa.r.chunks)[i];
   int b, T, tile_tok0, tile_first;
   int64_t c0;
   const bool have_tile = locate_tile(a, wg_tile, b, c0, T, tile_tok0, tile_first);
@@ -744,29 +843,95 @@ __global__ __launch_bounds__(kFusedThreads) void score_fused(FusedArgs fa) {
   const int n_tiles = have_tile ? (T + kTokPerWg - 1) / kTokPerWg : 0;
   const int n_rt = (rows + 31) >> 5;
   constexpr float k2 = kK2<D>;
+  constexpr int KS = D / 16;
 
   float e[kFusedRowTiles][16];      // 2^(logit - m_w) of (token, row) pairs; row = 32 rt + l32
+  bf16x8 kf[KS];
+  const int fb0 = frag_base<D>(lane);
+  const int64_t row_elems = (int64_t)a.Hkv * D, tile_row0 = c0 + tile_tok0;      // (RR) of the cache
+  auto copy_values = [&]() {
+    constexpr int kPer = kFusedThreads / 16, kVals = kTokPerWg / kPer;           // rows at a time, 16-byte vectors per thread
+    u32x4 vals[kVals];
+#pragma unroll
+    for (int p = 0; p < kVals; ++p) vals[p] = *reinterpret_cast<const u32x4*>(rot.v[p * kPer + (tid >> 4)] + (tid & 15) * 16);
+    bf16_t* dst = fa.r.v + (tile_row0 + (tid >> 4)) * row_elems + g * D + (tid & 15) * 8;
+#pragma unroll
+    for (int p = 0; p < kVals; ++p)
+      if (tile_tok0 + p * kPer + (tid >> 4) < T) *reinterpret_cast<u32x4*>(dst + p * kPer * row_elems) = vals[p];
+  };
 
-  if (rows > 0) {
-    for (int j = wave; j < kTokPerWg / kRowsPerLoad<D>; j += kFusedWaves) {      // keys
-      const int r = staged_row<D>(j, lane);
-      const int tok = min(tile_tok0 + r, T - 1);
-      load_to_lds_addr(a.k + ((c0 + tok) * a.Hkv + g) * D + staged_elem<D>(r, lane), sK + j * 1024);
+  if (rows > 0 || (RR && have_tile)) {
+    if constexpr (RR) {
+      __syncthreads();                                  // the table is there
+      if (tid < kTokPerWg) {
+        const int64_t row = c0 + min(tile_tok0 + tid, T - 1);
+        const int c = chunk_of(rot.table, fa.r.n_chunks, row);
+        const qcf_chunk& ch = rot.table[c];
+        const bool covered = row >= ch.dst_row && row < ch.dst_row + ch.len;
+        const int64_t off = ((covered ? row - ch.dst_row : row) * row_elems + g * D) * 2;
+        rot.k[tid] = static_cast<const char*>(covered ? ch.k_src : fa.r.k) + off;
+        rot.v[tid] = static_cast<const char*>(covered ? ch.v_src : fa.r.v) + off;
+        rot.chunk[tid] = covered ? c : -1;
+      }
+      __syncthreads();
     }
+    constexpr int kKeyLoads = kTokPerWg / kRowsPerLoad<D> / kFusedWaves;         // keys
+    const char* key_src[kKeyLoads];
+#pragma unroll
+    for (int i = 0; i < kKeyLoads; ++i) {
+      const int r = staged_row<D>(wave + i * kFusedWaves, lane);
+      if constexpr (RR) key_src[i] = rot.k[r] + staged_elem<D>(r, lane) * 2;
+      else key_src[i] = reinterpret_cast<const char*>(a.k + ((c0 + min(tile_tok0 + r, T - 1)) * a.Hkv + g) * D + staged_elem<D>(r, lane));
+    }
+#pragma unroll
+    for (int i = 0; i < kKeyLoads; ++i) load_to_lds_addr(key_src[i], sK + (wave + i * kFusedWaves) * 1024);
     for (int j = wave; j < n_rt * (32 / kRowsPerLoad<D>); j += kFusedWaves) {    // probe rows of the group
       const int r = staged_row<D>(j, lane);
       const int rr = min(r, rows - 1);
       const int i = rr / a.G, hh = rr - i * a.G;
       load_to_lds_addr(a.q + ((p0 + i) * a.H + g * a.G + hh) * D + staged_elem<D>(r, lane), smem + j * 1024);
     }
+    int first_chunk = 0, n_mine = 0;                    // (RR) chunks from the tile's first row to its last
+    auto fill_pairs = [&](int from) {                   // pairs of the tile's chunks from .. from + kRotChunks - 1
+      for (int i = tid; i < min(kRotChunks, n_mine - from) * 64; i += kFusedThreads)
+        rot.cs[i] = shift_pair(rot.table[first_chunk + from + i / 64], fa.r.neg2_over_d_log2base, i % 64);
+    };
+    if constexpr (RR) {
+      first_chunk = chunk_of(rot.table, fa.r.n_chunks, tile_row0);
+      n_mine = chunk_of(rot.table, fa.r.n_chunks, c0 + min(tile_tok0 + kTokPerWg, T) - 1) - first_chunk + 1;
+      fill_pairs(0);
+    }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    constexpr int KS = D / 16;
-    const int fb0 = frag_base<D>(lane);
-    bf16x8 kf[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
       kf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(sK + (32 * wave) * (2 * D) + (fb0 ^ (32 * ks))));
+    if constexpr (RR) {
+      const int mine = rot.chunk[32 * wave + l32] - first_chunk;        // (negative: not turned)
+      for (int from = 0;; from += kRotChunks) {
+        if (mine >= from && mine < from + kRotChunks) turn_frags(kf, rot.cs + (mine - from) * 64, hf, fa.r.style != 0);
+        if (from + kRotChunks >= n_mine) break;
+        __syncthreads();
+        fill_pairs(from + kRotChunks);
+        __syncthreads();
+      }
+      if (tile_tok0 + 32 * wave + l32 < T) {
+        bf16_t* dst = fa.r.k + (tile_row0 + 32 * wave + l32) * row_elems + g * D + 8 * hf;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) *reinterpret_cast<u32x4*>(dst + 16 * ks) = __builtin_bit_cast(u32x4, kf[ks]);
+      }
+      if (rows == 0) copy_values();
+    }
+  }
+  if constexpr (RR) {                                   // rows of the cache outside the request (none, as a rule)
+    const int64_t lo = min(max(a.ctx_off[0], (int64_t)0), a.total_ctx), hi = min(max(a.ctx_off[1], lo), a.total_ctx);
+    if (hi - lo < a.total_ctx) {
+      __syncthreads();                                  // (the table, where no tile has waited for it)
+      for (int64_t i = wg_tile * kFusedWaves + wave; i < a.total_ctx - (hi - lo); i += fa.n_wg_tiles * kFusedWaves)
+        rerotate_row(fa.r, rot.table, i < lo ? i : i + (hi - lo), a.Hkv, g, lane);
+    }
+  }
+  if (rows > 0) {
     // probe-row fragments travel through a ring of four registers: the fragment four further (of this tile or
     // the next) is requested right behind the MFMA that used the slot.  One address register per
     // fragment index; the row tile is a constant offset of the read.
@@ -846,9 +1011,10 @@ __global__ __launch_bounds__(kFusedThreads) void score_fused(FusedArgs fa) {
     __builtin_amdgcn_s_waitcnt(0);            // this thread's partials have reached memory
     __syncthreads();
     // hand-off 1: the tiles of (request b, KV head g)
+    uint32_t* cnt = fa.sync + 1 + b * a.Hkv + g;
+    if (tid == 0) __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if constexpr (RR) copy_values();                   // (not earlier: the partials would wait for its stores)
     if (tid == 0) {
-      uint32_t* cnt = fa.sync + 1 + b * a.Hkv + g;
-      __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       uint32_t spins = 0;
       while (__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)n_tiles &&
              ++spins < fa.spin_limit)
@@ -973,15 +1139,15 @@ __global__ __launch_bounds__(256) void score_zero(float* score, int64_t n, float
 
 template <int D> constexpr size_t kPass1Lds = kQBytes<D> + kKBytes<D> + (size_t)kTokWaves * kRowBlock * sizeof(float2);
 template <int D> constexpr size_t kPass2Lds = kQBytes<D> + kKBytes<D> + kRowBlock * 4 * 3 + (size_t)kRowGroups * kTokPerWg * sizeof(float);
-constexpr size_t kFusedLds = kQBytes<128> + kKBytes<128>;
 static_assert((size_t)kFusedWaves * kRowBlock * 8 + (size_t)kRowBlock * 4 + (size_t)kTokPerWg * 4 <= kKBytes<128>,
               "the single-kernel path's tables fit in the key tile's LDS");
 
-template <bool LIMIT>
+template <bool LIMIT, bool RR>
 qcf_status run_fused(const FusedArgs& fa, hipStream_t st) {
   static std::atomic<uint64_t> lds_ok;
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_fused<LIMIT>), kFusedLds, lds_ok));
-  score_fused<LIMIT><<<dim3((unsigned)(fa.n_wg_tiles * fa.s.Hkv)), dim3(kFusedThreads), kFusedLds, st>>>(fa);
+  constexpr size_t lds = RR ? kFusedRotLds : kFusedLds;
+  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_fused<LIMIT, RR>), lds, lds_ok));
+  score_fused<LIMIT, RR><<<dim3((unsigned)(fa.n_wg_tiles * fa.s.Hkv)), dim3(kFusedThreads), lds, st>>>(fa);
   return check_launch("score (single kernel)");
 }
 
@@ -1068,7 +1234,37 @@ qcf_status sync_counters(uint32_t** out) {
   return QCF_OK;
 }
 
+// the arguments of a single-kernel launch, with the next set of counters
+qcf_status fused_args(const qcf_layer_desc& L, const ScoreArgs& a, void* ws, FusedArgs* fa) {
+  const FusedWs fw = fused_ws(L, a.B, a.total_ctx);
+  *fa = FusedArgs{};
+  fa->s = a;
+  fa->part = reinterpret_cast<float2*>(static_cast<char*>(ws) + fw.part);
+  fa->colpart = reinterpret_cast<float*>(static_cast<char*>(ws) + fw.colpart);
+  fa->n_wg_tiles = (int)n_tiles_upper(a.B, a.total_ctx);
+  fa->spin_limit = kSpinLimit;
+  uint32_t* counters = nullptr;
+  QCF_TRY(sync_counters(&counters));
+  static std::atomic<uint32_t> next_slot{0};
+  fa->sync = counters + (size_t)(next_slot.fetch_add(1, std::memory_order_relaxed) % kSyncSlots) * kSyncWords;
+  return QCF_OK;
+}
+
 }  // namespace
+
+bool score_takes_rerope(const qcf_layer_desc& L, int32_t B, int32_t n_chunks, int64_t total_probe, int64_t total_ctx) {
+  return B == 1 && n_chunks > 0 && n_chunks <= kMaxRotChunks && use_fused(L, B, total_probe, total_ctx);
+}
+
+qcf_status launch_rerope_score(const qcf_layer_desc& L, const qcf_chunk* chunks, int32_t n_chunks, const void* q,
+                               const int64_t* probe_off, int64_t total_probe, void* k, void* v, const int64_t* ctx_off,
+                               int64_t total_ctx, float* score, void* ws, hipStream_t st) {
+  FusedArgs fa;
+  QCF_TRY(fused_args(L, score_args(L, 1, q, probe_off, total_probe, k, ctx_off, total_ctx, nullptr, score, 1.f, 0.f), ws, &fa));
+  fa.r = Rerotation{chunks, n_chunks, L.rope_style, -2.0 / (double)L.head_dim * std::log2(L.rope_base), static_cast<bf16_t*>(k),
+                    static_cast<bf16_t*>(v)};
+  return run_fused<false, true>(fa, st);
+}
 
 qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const int64_t* probe_off,
                         int64_t total_probe, const void* k, const int64_t* ctx_off, int64_t total_ctx,
@@ -1104,18 +1300,9 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
 
   const ScoreArgs a = score_args(L, B, q, probe_off, total_probe, k, ctx_off, total_ctx, probe_limit, score, alpha, beta);
   if (fused) {
-    const FusedWs fw = fused_ws(L, B, total_ctx);
     FusedArgs fa;
-    fa.s = a;
-    fa.part = reinterpret_cast<float2*>(static_cast<char*>(ws) + fw.part);
-    fa.colpart = reinterpret_cast<float*>(static_cast<char*>(ws) + fw.colpart);
-    fa.n_wg_tiles = (int)n_tiles_upper(B, total_ctx);
-    fa.spin_limit = kSpinLimit;
-    uint32_t* counters = nullptr;
-    QCF_TRY(sync_counters(&counters));
-    static std::atomic<uint32_t> next_slot{0};
-    fa.sync = counters + (size_t)(next_slot.fetch_add(1, std::memory_order_relaxed) % kSyncSlots) * kSyncWords;
-    return probe_limit ? run_fused<true>(fa, st) : run_fused<false>(fa, st);
+    QCF_TRY(fused_args(L, a, ws, &fa));
+    return probe_limit ? run_fused<true, false>(fa, st) : run_fused<false, false>(fa, st);
   }
   return launch_two_pass(L, a, 1, &q, &k, &alpha, ws, st);
 }

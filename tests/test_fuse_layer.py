@@ -75,3 +75,69 @@ def test_same_bits_as_the_calls_one_after_the_other(cfg, scale, ratio, critical,
     for _ in range(2):
         for name, a, b in zip(OUTS, outputs(lambda: pipeline.enqueue_layer(L, critical)), want):
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+
+
+def _layer(lens, gaps, R, style, H=8, Hkv=2, dm=256, before=0, behind=0, src0=0, probes=True, seed=0):
+    """One request of `lens`-token chunks with gaps[i] uncovered rows in front of chunk i; `before` / `behind` rows of the cache
+    lie outside the request."""
+    dev, dt, D = torch.device("cuda:0"), torch.bfloat16, 128
+    g = torch.Generator(device=dev).manual_seed(seed)
+    rnd = lambda *s: torch.randn(s, generator=g, device=dev, dtype=dt)
+    sh = inputs.LayerShape(dm, H, Hkv, D, 500000.0, "bf16", style)
+    desc = qb.make_desc(sh)
+    table, keep, row = [], [], 0
+    for n, gap in zip(lens, gaps):
+        row += gap
+        k, v = rnd(n, Hkv, D), rnd(n, Hkv, D)
+        keep.append((k, v))
+        table.append(dict(k=k, v=v, src_pos0=src0, dst_row=row, dst_pos0=3 * row + 1))
+        row += n
+    total = row
+    T = total - before - behind
+    N = qb.qcf_select_count(T, 0.2)
+    i64 = lambda v: torch.tensor(v, dtype=torch.int64, device=dev)
+    i32 = lambda: torch.zeros(N, dtype=torch.int32, device=dev)
+    ws = lambda n: torch.empty(max(n, 1), dtype=torch.uint8, device=dev)
+    L = pipeline.DeviceLayer(
+        desc=desc, B=1, total_ctx=total, total_probe=R, total_sel=N, n_chunks=len(table), ctx_lens=[T], sel_counts=[N],
+        chunk_tensors=keep, chunks_dev=qb.chunk_table(table, dev), ctx_off=i64([before, before + T]),
+        probe_off=i64([0, R if probes else 0]), sel_off=i64([0, N]), q_probe=rnd(R, H, D), x_ctx=rnd(total, dm),
+        w_qkv=rnd(sh.qkv_rows, dm), k_fused=rnd(total, Hkv, D), v_fused=rnd(total, Hkv, D),
+        score=torch.zeros(total, device=dev), sel_idx=i32(), sel_row=i32(), sel_pos=i32(), q_sel=rnd(N, H, D), k_sel=rnd(N, Hkv, D),
+        v_sel=rnd(N, Hkv, D), o_sel=rnd(N, H, D), lse=torch.zeros(N, H, device=dev),
+        ws_rerope=ws(qb.qcf_rerope_workspace_bytes(desc, len(table), total)), ws_score=ws(qb.qcf_score_workspace_bytes(desc, 1, R, total)),
+        ws_select=None, ws_qkv=ws(qb.qcf_recompute_qkv_workspace_bytes(desc, N)),
+        ws_attn=ws(qb.qcf_recompute_attn_workspace_bytes(desc, 1, N, total)))
+    return L
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("style", [0, 1])
+@pytest.mark.parametrize("lens,gaps,kw", [
+    ([300, 212], [0, 0], {}),                                    # a chunk that ends inside a tile
+    ([1] * 127 + [200], [0] * 128, {}),                          # more chunks to a tile than pairs are kept for
+    ([1] * 128 + [200], [0] * 129, {}),                          # more chunks than the table holds: in two launches
+    ([17, 5, 256, 90], [3, 0, 40, 300], {}),                     # rows that no chunk covers, a tile without any
+    ([100, 600], [0, 0], dict(before=130, behind=77)),           # cache rows outside the request
+    ([257], [0], dict(R=80, H=16, Hkv=4, src0=9)),               # every row of probes, one token in the last tile
+    ([1], [0], dict(R=1)),
+    ([90, 80], [0, 0], dict(probes=False))],                     # the request has no probe rows
+    ids=["two", "128 chunks", "129 chunks", "gaps", "outside", "edges", "one", "no probes"])
+def test_rerotation_inside_the_scoring(lens, gaps, kw, style):
+    print(f"joined re-rotation {kw} style={style}", flush=True)
+    kw = dict(dict(R=24), **kw)
+    L = _layer(lens, gaps, style=style, **kw)
+    L.chunk_tensors[0][0].view(torch.int16)[0, 0, :4] = torch.tensor([0x7f81, -1, 0x7f80, -128], dtype=torch.int16)
+    # (NaN of two kinds and both infinities in the first key row)
+    k0, v0 = L.k_fused.clone(), L.v_fused.clone()
+    res = []
+    for run in (lambda: [fn(L) for _, fn in pipeline.FUSED_STEPS], lambda: pipeline.enqueue_layer(L)):
+        L.k_fused.copy_(k0)
+        L.v_fused.copy_(v0)
+        for name in OUTS[2:]:
+            getattr(L, name).fill_(1)
+        run()
+        torch.cuda.synchronize()
+        res.append([getattr(L, name).clone() for name in OUTS])
+    for name, a, b in zip(OUTS, *res):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
