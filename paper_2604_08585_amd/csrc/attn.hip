@@ -22,8 +22,8 @@
 // tokens: 1580 us with the generic kernel, 48.0 us here (41.7 with two terms); the whole layer 96.6 us (2074 before).
 //
 // Generic path (f32, or other shapes): one workgroup per (row, head), online softmax over
-// 256-token tiles.  Bound by the latency of its key and value loads (77 rows x 4 heads over 512 tokens in f32: 39 us with
-// one load at a time, 14 us with 16-byte key loads and the values shared out over all threads).
+// 256-token tiles.  Bound by the latency of its loads: 77 rows x 4 heads over 512 tokens in f32 16.6 us with eight values on their
+// way at a time, 11.4 with all of a tile's keys and values.
 #include "attn_common.h"
 
 namespace qcf {
@@ -32,83 +32,104 @@ namespace {
 
 // ------------------------------------------------------------------ generic path
 
-template <typename T>
+// A tile of 256 tokens: the keys (a token to a thread) and the first 16 values of each thread (four elements of every
+// kSlices-th token) are requested together, so that a tile waits for memory once.  (Requested a tile ahead they take all registers
+// and more moves: 15.0 us for the case below.)
+template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_generic(AttnArgs a) {
-  __shared__ float sq[128];
+  constexpr int kQuads = D / 4, kSlices = 256 / kQuads, kVals = 256 / kSlices, kBatch = 16;
+  __shared__ __align__(16) float sq[D];
   __shared__ float sp[256];
-  __shared__ float sacc[256];
-  __shared__ float red[4];
+  __shared__ __align__(16) float sacc[kSlices * D];
+  __shared__ float redm[4], reds[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t row = blockIdx.x / a.H;
   const int h = blockIdx.x - (int)row * a.H;
+  // (everything that does not depend on the request is requested in front of the search for it: one wait instead of three)
+  const float q1 = tid < D ? Elem<T>::load(static_cast<const T*>(a.q) + (row * a.H + h) * D + tid) : 0.f;
+  const int pos = a.sel_pos[row];
+  int64_t ctx0 = a.ctx_off[0], ctx1 = a.ctx_off[1];
   const int b = find_request(a.sel_off, a.B, row);
   if (b >= a.B) return;
-  const int64_t c0 = min(max(a.ctx_off[b], (int64_t)0), a.total_ctx);
-  const int64_t c1 = min(max(a.ctx_off[b + 1], c0), a.total_ctx);
+  if (b > 0) { ctx0 = a.ctx_off[b]; ctx1 = a.ctx_off[b + 1]; }
+  const int64_t c0 = min(max(ctx0, (int64_t)0), a.total_ctx);
+  const int64_t c1 = min(max(ctx1, c0), a.total_ctx);
   const int Tn = (int)(c1 - c0);
   const int64_t p0 = a.ctx_pos0 ? a.ctx_pos0[b] : 0;
-  const int n_vis = (int)min((int64_t)Tn, max((int64_t)0, (int64_t)a.sel_pos[row] - p0 + 1));
-  const int g = h / a.G, D = a.D;
-  const T* q = static_cast<const T*>(a.q) + (row * a.H + h) * D;
+  const int n_vis = (int)min((int64_t)Tn, max((int64_t)0, (int64_t)pos - p0 + 1));
+  const int g = h / a.G;
   const T* kb = static_cast<const T*>(a.k) + (c0 * a.Hkv + g) * D;
   const T* vb = static_cast<const T*>(a.v) + (c0 * a.Hkv + g) * D;
   const int64_t kv_stride = (int64_t)a.Hkv * D;
-  if (tid < D) sq[tid] = Elem<T>::load(q + tid) * rsqrtf((float)D);
+  if (tid < D) sq[tid] = q1 * rsqrtf((float)D);
   __syncthreads();
-  // values: thread = (element, every slices-th token); the slices' sums are added in order at the end
-  const int elem = tid % D, slice = tid / D, slices = 256 / D;
-  float m_run = -INFINITY, l_run = 0.f, acc = 0.f;
+  const int quad = tid % kQuads, slice = tid / kQuads;       // values: the slices' sums are added in order at the end
+  float m_run = -INFINITY, l_run = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
   for (int j0 = 0; j0 < n_vis; j0 += 256) {
-    const int j = j0 + tid;
-    float s = -INFINITY;
-    if (j < n_vis) {
-      const T* kr = kb + j * kv_stride;
-      float d = 0.f;
-#pragma unroll 8
-      for (int c = 0; c < D; c += 4) {
-        float kf[4];
-        Quad<T>::load(kr + c, kf);
+    const int n = min(256, n_vis - j0);
+    const T* kr = kb + (int64_t)(j0 + min(tid, n - 1)) * kv_stride;
+    const T* vt = vb + (int64_t)j0 * kv_stride + 4 * quad;
+    float kf[kBatch][4], vf[kBatch][4];
+    auto load_values = [&](int u0) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) d += sq[c + e] * kf[e];
+      for (int u = 0; u < kBatch; ++u) Quad<T>::load(vt + (int64_t)min(slice + (u0 + u) * kSlices, n - 1) * kv_stride, vf[u]);
+    };
+    float s = 0.f;
+#pragma unroll
+    for (int c = 0; c < kQuads; c += kBatch) {
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) Quad<T>::load(kr + 4 * (c + u), kf[u]);
+      if (c + kBatch == kQuads) load_values(0);
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const float4 w = *reinterpret_cast<const float4*>(sq + 4 * (c + u));
+        s += w.x * kf[u][0];
+        s += w.y * kf[u][1];
+        s += w.z * kf[u][2];
+        s += w.w * kf[u][3];
       }
-      s = d;
     }
+    if (tid >= n) s = -INFINITY;
     float mx = s;
     for (int d = 32; d >= 1; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
-    if (lane == 0) red[wave] = mx;
-    __syncthreads();
-    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    if (lane == 0) redm[wave] = mx;
+    __syncthreads();                               // (and the previous tile's probabilities have been read)
+    mx = fmaxf(fmaxf(redm[0], redm[1]), fmaxf(redm[2], redm[3]));
     const float m_new = fmaxf(m_run, mx);          // finite: the tile has at least one visible token
-    const float p = (j < n_vis) ? expf(s - m_new) : 0.f;
+    const float p = tid < n ? expf(s - m_new) : 0.f;
     sp[tid] = p;
     float sum = p;
     for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    if (lane == 0) reds[wave] = sum;
     __syncthreads();
-    if (lane == 0) red[wave] = sum;
-    __syncthreads();
-    sum = (red[0] + red[1]) + (red[2] + red[3]);
+    sum = (reds[0] + reds[1]) + (reds[2] + reds[3]);
     const float alpha = expf(m_run - m_new);       // 0 on the first tile
     l_run = l_run * alpha + sum;
-    acc *= alpha;
-    const int n = min(256, n_vis - j0);
-    const T* vt = vb + (int64_t)j0 * kv_stride + elem;
-    int jj = slice;
-    for (; jj + 7 * slices < n; jj += 8 * slices) {       // eight tokens on their way at a time
-      float v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = Elem<T>::load(vt + (jj + u * slices) * kv_stride);
+    for (int e = 0; e < 4; ++e) acc[e] *= alpha;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) acc += sp[jj + u * slices] * v[u];
+    for (int u0 = 0; u0 < kVals; u0 += kBatch) {
+      if (slice + u0 * kSlices >= n) break;
+      if (u0 > 0) load_values(u0);
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int jj = slice + (u0 + u) * kSlices;
+        const float w = sp[jj];
+        if (jj < n) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] += w * vf[u][e];
+        }
+      }
     }
-    for (; jj < n; jj += slices) acc += sp[jj] * Elem<T>::load(vt + jj * kv_stride);
     m_run = m_new;
-    __syncthreads();
   }
-  sacc[tid] = acc;
+  *reinterpret_cast<float4*>(sacc + slice * D + 4 * quad) = make_float4(acc[0], acc[1], acc[2], acc[3]);
   __syncthreads();
-  if (tid < D)
-    for (int w = 1; w < slices; ++w) acc += sacc[w * D + tid];
-  if (tid < D) Elem<T>::store(static_cast<T*>(a.o) + (row * a.H + h) * D + tid, n_vis > 0 ? acc / l_run : 0.f);
+  if (tid < D) {
+    float o = sacc[tid];
+    for (int w = 1; w < kSlices; ++w) o += sacc[w * D + tid];
+    Elem<T>::store(static_cast<T*>(a.o) + (row * a.H + h) * D + tid, n_vis > 0 ? o / l_run : 0.f);
+  }
   if (tid == 0 && a.lse) a.lse[row * a.H + h] = n_vis > 0 ? m_run + logf(l_run) : -INFINITY;
 }
 
@@ -880,8 +901,13 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
   }
   if (total_sel * a.H > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "attn: grid too large");
   const dim3 grid((unsigned)(total_sel * a.H)), block(256);
-  if (L.dtype == QCF_DTYPE_BF16) attn_generic<bf16_t><<<grid, block, 0, st>>>(a);
-  else attn_generic<float><<<grid, block, 0, st>>>(a);
+  if (L.dtype == QCF_DTYPE_BF16) {
+    if (a.D == 64) attn_generic<bf16_t, 64><<<grid, block, 0, st>>>(a);
+    else attn_generic<bf16_t, 128><<<grid, block, 0, st>>>(a);
+  } else {
+    if (a.D == 64) attn_generic<float, 64><<<grid, block, 0, st>>>(a);
+    else attn_generic<float, 128><<<grid, block, 0, st>>>(a);
+  }
   return check_launch("attn");
 }
 
