@@ -8,8 +8,8 @@
 // and the product's rounding error recovered by a fused multiply-add (a plain float32 product would be
 // off by 1e-3 rad at 8K positions), reduced to its fraction and handed to the hardware sine and cosine
 // (inputs in turns, errors far below a bf16 ulp).  Positions from 2^24 on are taken in two parts.
-// The generic path (f32, or shapes the MFMA tiling does not cover) writes the raw product to
-// the workspace and rotates it in a second kernel with float64 angles, which also writes the cache rows.
+// The generic path (f32, or shapes the MFMA tiling does not cover) takes float64 angles: in the product's epilogue where it is
+// small, otherwise in a second kernel that finds the raw product in the workspace; both also write the cache rows.
 // qcf_recompute_qkv_scatter: the epilogue of the MFMA path also stores the K and V rows to their rows of the
 // fused cache (step 5 of the path, otherwise a kernel of its own).
 #include <type_traits>
@@ -79,14 +79,54 @@ __global__ __launch_bounds__(256) void qkv_gemm_generic(const T* __restrict__ x,
   }
 }
 
+// Where the heads of a projection row go on the generic path, and its rotation.
+template <typename T>
+struct RopeOut {
+  const int32_t* pos;
+  double neg2_over_d_log2base;
+  int H, Hkv, D, style;
+  T* q;
+  T* k;
+  T* v;
+  const int32_t* dst_rows;       // K and V rows also go to the fused cache
+  T* k_fused;
+  T* v_fused;
+  int64_t fused_rows;
+  // columns of pair i of a head
+  __device__ __forceinline__ int first(int i) const { return style == 0 ? i : 2 * i; }
+  __device__ __forceinline__ int second(int i) const { return style == 0 ? i + D / 2 : 2 * i + 1; }
+  __device__ __forceinline__ bool rotated(int head) const { return head < H + Hkv; }
+  __device__ __forceinline__ float2 factor(int64_t m, int i) const {
+    const double theta = exp2(neg2_over_d_log2base * (double)i);
+    double sd, cd;
+    sincos((double)pos[m] * theta, &sd, &cd);
+    return make_float2((float)cd, (float)sd);
+  }
+  // head `head` of output row m (null: not wanted) and of its row of the cache (null: none)
+  __device__ __forceinline__ T* out(int64_t m, int head) const {
+    if (head < H) return q ? q + (m * H + head) * D : nullptr;
+    T* base = head < H + Hkv ? k : v;
+    return base ? base + (m * Hkv + (head - H) % Hkv) * D : nullptr;
+  }
+  __device__ __forceinline__ T* cache(int64_t m, int head) const {
+    if (head < H || !dst_rows) return nullptr;
+    const int64_t row = dst_rows[m];
+    if (row < 0 || row >= fused_rows) return nullptr;
+    return (head < H + Hkv ? k_fused : v_fused) + (row * Hkv + (head - H) % Hkv) * D;
+  }
+};
+
 // The same product (same sums in the same order) with 16 x 16 outputs per workgroup, one per thread, for launches
 // whose 64 x 64 tiles would leave most compute units idle.  Bound by latency there: the next 64 elements of the
 // contraction are on their way while 64 are used.  M 77, K 256, N 512 in f32: 38 us with 64 x 64 tiles, 11 us here.
-template <typename T>
+// ROPE: the 16 columns are 8 rotary pairs of a head, the columns of a pair 8 threads apart, and the results leave rotated and
+// in the element type; the angles are taken in float64 while the first loads are on their way.  The same product 6.3 us, 4.9 + 3.3
+// with a kernel of its own for the rotation.
+template <typename T, bool ROPE>
 __global__ __launch_bounds__(256) void qkv_gemm_small_generic(const T* __restrict__ x, int64_t x_rows,
                                                               const int32_t* __restrict__ gather, int64_t M,
                                                               const T* __restrict__ w, int Kdim, int Ntot,
-                                                              float* __restrict__ y) {
+                                                              float* __restrict__ y, RopeOut<T> ro) {
   constexpr int KC = 64, LD = KC + 4;            // (rows 4 banks apart: 16-byte reads of 16 rows touch every bank once)
   __shared__ __align__(16) float sA[16 * LD];
   __shared__ __align__(16) float sB[16 * LD];
@@ -94,13 +134,18 @@ __global__ __launch_bounds__(256) void qkv_gemm_small_generic(const T* __restric
   const int tx = tid & 15, ty = tid >> 4;
   const int64_t m0 = (int64_t)blockIdx.x * 16;
   const int n0 = blockIdx.y * 16;
+  const int head = ROPE ? n0 / ro.D : 0, pair0 = ROPE ? n0 % ro.D / 2 : 0;       // (D is a multiple of 16)
+  auto column = [&](int c) {                     // weight row of tile column c
+    if (!ROPE) return n0 + c;
+    return head * ro.D + (c < 8 ? ro.first(pair0 + c) : ro.second(pair0 + c - 8));
+  };
   const int lr = tid >> 4, lc = (tid & 15) * 4;  // row and first k of the four elements this thread brings
   int64_t arow = -1;
   if (m0 + lr < M) {
     const int64_t idx = gather ? (int64_t)gather[m0 + lr] : m0 + lr;
     if (idx >= 0 && idx < x_rows) arow = idx;
   }
-  const int brow = (n0 + lr < Ntot) ? n0 + lr : -1;
+  const int brow = column(lr) < Ntot ? column(lr) : -1;
   float a4[4], b4[4];
   auto fetch = [&](int k0) {                     // (Kdim is a multiple of 4 here)
 #pragma unroll
@@ -111,6 +156,8 @@ __global__ __launch_bounds__(256) void qkv_gemm_small_generic(const T* __restric
     }
   };
   fetch(0);
+  float2 cs = make_float2(1.f, 0.f);
+  if (ROPE && ro.rotated(head) && m0 + ty < M) cs = ro.factor(m0 + ty, pair0 + (tx & 7));
   float acc = 0.f;
   for (int k0 = 0; k0 < Kdim; k0 += KC) {
     __syncthreads();
@@ -128,59 +175,46 @@ __global__ __launch_bounds__(256) void qkv_gemm_small_generic(const T* __restric
       acc += av.w * bv.w;
     }
   }
-  if (m0 + ty < M && n0 + tx < Ntot) y[(m0 + ty) * Ntot + n0 + tx] = acc;
+  if constexpr (!ROPE) {
+    if (m0 + ty < M && n0 + tx < Ntot) y[(m0 + ty) * Ntot + n0 + tx] = acc;
+  } else {
+    const float other = __shfl_xor(acc, 8, 64);
+    float ra = acc, rb = acc;
+    if (ro.rotated(head)) {
+      const float a = tx < 8 ? acc : other, b = tx < 8 ? other : acc;
+      turn_pair(a, b, cs, ra, rb);
+    }
+    const float r = tx < 8 ? ra : rb;
+    if (m0 + ty >= M) return;
+    T* dst = ro.out(m0 + ty, head);
+    if (!dst) return;
+    const int c = column(tx) - head * ro.D;
+    Elem<T>::store(dst + c, r);
+    if (T* fus = ro.cache(m0 + ty, head)) Elem<T>::store(fus + c, r);
+  }
 }
 
 // One thread per (row, head slot, rotary pair); V heads are copied.  The angle is taken in float64 (cheaper here than
-// a table from a launch of its own: 77 rows, 4 us less).  dst_rows: K and V rows also go to the fused cache.
+// a table from a launch of its own: 77 rows, 4 us less).
 template <typename T>
-__global__ __launch_bounds__(256) void qkv_rope_split_generic(const float* __restrict__ y, int64_t M,
-                                                              const int32_t* __restrict__ pos, double neg2_over_d_log2base,
-                                                              int H, int Hkv, int D, int style, T* __restrict__ q,
-                                                              T* __restrict__ k, T* __restrict__ v,
-                                                              const int32_t* __restrict__ dst_rows, T* __restrict__ k_fused,
-                                                              T* __restrict__ v_fused, int64_t fused_rows) {
-  const int half = D / 2;
-  const int heads = H + 2 * Hkv;
+__global__ __launch_bounds__(256) void qkv_rope_split_generic(const float* __restrict__ y, int64_t M, RopeOut<T> ro) {
+  const int half = ro.D / 2;
+  const int heads = ro.H + 2 * ro.Hkv;
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (gid >= M * heads * half) return;
   const int i = (int)(gid % half);
   const int hs = (int)((gid / half) % heads);
   const int64_t m = gid / ((int64_t)half * heads);
-  const int ia = style == 0 ? i : 2 * i;
-  const int ib = style == 0 ? i + half : 2 * i + 1;
-  const float* src = y + m * (int64_t)heads * D + (int64_t)hs * D;
+  const int ia = ro.first(i), ib = ro.second(i);
+  const float* src = y + m * (int64_t)heads * ro.D + (int64_t)hs * ro.D;
   const float a = src[ia], b = src[ib];
-  T* dst;
-  T* fus = nullptr;
-  bool rot = true;
-  int64_t row = -1;
-  if (hs >= H && dst_rows) {
-    row = dst_rows[m];
-    if (row >= fused_rows) row = -1;
-  }
-  if (hs < H) dst = q ? q + (m * H + hs) * D : nullptr;
-  else if (hs < H + Hkv) {
-    dst = k ? k + (m * Hkv + (hs - H)) * D : nullptr;
-    if (row >= 0) fus = k_fused + (row * Hkv + (hs - H)) * D;
-  } else {
-    dst = v ? v + (m * Hkv + (hs - H - Hkv)) * D : nullptr;
-    if (row >= 0) fus = v_fused + (row * Hkv + (hs - H - Hkv)) * D;
-    rot = false;
-  }
+  T* dst = ro.out(m, hs);
   if (!dst) return;
   float ra = a, rb = b;
-  if (rot) {
-    const double theta = exp2(neg2_over_d_log2base * (double)i);
-    double sd, cd;
-    sincos((double)pos[m] * theta, &sd, &cd);
-    const float sn = (float)sd, cn = (float)cd;
-    ra = a * cn - b * sn;
-    rb = b * cn + a * sn;
-  }
+  if (ro.rotated(hs)) turn_pair(a, b, ro.factor(m, i), ra, rb);
   Elem<T>::store(dst + ia, ra);
   Elem<T>::store(dst + ib, rb);
-  if (fus) {
+  if (T* fus = ro.cache(m, hs)) {
     Elem<T>::store(fus + ia, ra);
     Elem<T>::store(fus + ib, rb);
   }
@@ -1265,30 +1299,36 @@ qcf_status run_quad(QkvArgs a, int splits, hipStream_t st) {
 
 // Product of the generic path.  The small tile reads both operands four times as often, so it takes over only where
 // the large one gives fewer workgroups than compute units (M 77, N 512: 16; the small one 160).
-template <typename T>
+bool small_generic(int64_t M, int K, int N) { return (M + 63) / 64 * ((N + 63) / 64) < compute_unit_count() && K % 4 == 0; }
+template <typename T, bool ROPE = false>
 qcf_status run_gemm_generic(const char* what, const void* x, int64_t x_rows, const int32_t* gather, int64_t M,
-                            const void* w, int K, int N, float* y, hipStream_t st) {
+                            const void* w, int K, int N, float* y, hipStream_t st, const RopeOut<T>& ro = RopeOut<T>{}) {
   const int64_t mb = (M + 63) / 64;
   const int nb = (N + 63) / 64;
   if (mb > 0x7fffffff || nb > 65535) return fail(QCF_ERR_UNSUPPORTED, "%s: grid too large", what);
   const T* xt = static_cast<const T*>(x);
   const T* wt = static_cast<const T*>(w);
-  if (mb * nb < compute_unit_count() && K % 4 == 0)
-    qkv_gemm_small_generic<T><<<dim3((unsigned)((M + 15) / 16), (unsigned)((N + 15) / 16)), dim3(256), 0, st>>>(
-        xt, x_rows, gather, M, wt, K, N, y);
+  if (small_generic(M, K, N))
+    qkv_gemm_small_generic<T, ROPE><<<dim3((unsigned)((M + 15) / 16), (unsigned)((N + 15) / 16)), dim3(256), 0, st>>>(
+        xt, x_rows, gather, M, wt, K, N, y, ro);
   else
     qkv_gemm_generic<T><<<dim3((unsigned)mb, (unsigned)nb), dim3(256), 0, st>>>(xt, x_rows, gather, M, wt, K, N, y);
   return check_launch(what);
 }
 
 template <typename T>
-qcf_status run_rope_split(const qcf_layer_desc& L, const float* y, int64_t M, const int32_t* pos, void* q, void* k, void* v,
-                          const int32_t* dst_rows, void* k_fused, void* v_fused, int64_t fused_rows, unsigned blocks,
-                          hipStream_t st) {
-  qkv_rope_split_generic<T><<<dim3(blocks), dim3(256), 0, st>>>(
-      y, M, pos, -2.0 / (double)L.head_dim * std::log2(L.rope_base), L.n_q_heads, L.n_kv_heads, L.head_dim, L.rope_style,
-      static_cast<T*>(q), static_cast<T*>(k), static_cast<T*>(v), dst_rows, static_cast<T*>(k_fused),
-      static_cast<T*>(v_fused), fused_rows);
+qcf_status run_qkv_generic(const qcf_layer_desc& L, const void* x, int64_t x_rows, const int32_t* gather, int64_t M, const void* w,
+                           const int32_t* pos, void* q, void* k, void* v, const int32_t* dst_rows, void* k_fused, void* v_fused,
+                           int64_t fused_rows, float* y, hipStream_t st) {
+  const int heads = L.n_q_heads + 2 * L.n_kv_heads, N = heads * L.head_dim;
+  const int64_t rope_blocks = (M * heads * (L.head_dim / 2) + 255) / 256;
+  if (rope_blocks > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "qkv: grid too large");
+  const RopeOut<T> ro{pos, -2.0 / (double)L.head_dim * std::log2(L.rope_base), L.n_q_heads, L.n_kv_heads, L.head_dim, L.rope_style,
+                      static_cast<T*>(q), static_cast<T*>(k), static_cast<T*>(v), dst_rows, static_cast<T*>(k_fused),
+                      static_cast<T*>(v_fused), fused_rows};
+  if (small_generic(M, L.d_model, N)) return run_gemm_generic<T, true>("qkv", x, x_rows, gather, M, w, L.d_model, N, y, st, ro);
+  QCF_TRY(run_gemm_generic<T>("qkv", x, x_rows, gather, M, w, L.d_model, N, y, st));
+  qkv_rope_split_generic<T><<<dim3((unsigned)rope_blocks), dim3(256), 0, st>>>(y, M, ro);
   return check_launch("qkv rope");
 }
 
@@ -1360,16 +1400,9 @@ qcf_status launch_qkv(const qcf_layer_desc& L, const void* x, int64_t x_rows, co
     return run_gemm<kRopeHalf64>(a, Ntot / kBN, ws, ws_bytes, st);
   }
   float* y = static_cast<float*>(ws);
-  const int64_t rope_blocks = (M * (H + 2 * Hkv) * (D / 2) + 255) / 256;
-  if (rope_blocks > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "qkv: grid too large");
-  if (L.dtype == QCF_DTYPE_BF16) {
-    QCF_TRY(run_gemm_generic<bf16_t>("qkv", x, x_rows, gather, M, w, L.d_model, Ntot, y, st));
-    QCF_TRY(run_rope_split<bf16_t>(L, y, M, pos, q, k, v, dst_rows, k_fused, v_fused, fused_rows, (unsigned)rope_blocks, st));
-  } else {
-    QCF_TRY(run_gemm_generic<float>("qkv", x, x_rows, gather, M, w, L.d_model, Ntot, y, st));
-    QCF_TRY(run_rope_split<float>(L, y, M, pos, q, k, v, dst_rows, k_fused, v_fused, fused_rows, (unsigned)rope_blocks, st));
-  }
-  return QCF_OK;
+  if (L.dtype == QCF_DTYPE_BF16)
+    return run_qkv_generic<bf16_t>(L, x, x_rows, gather, M, w, pos, q, k, v, dst_rows, k_fused, v_fused, fused_rows, y, st);
+  return run_qkv_generic<float>(L, x, x_rows, gather, M, w, pos, q, k, v, dst_rows, k_fused, v_fused, fused_rows, y, st);
 }
 
 // ---- plain linear map, RMSNorm, gated SiLU (rest of the layer for the recomputed rows) -----------------
