@@ -350,25 +350,35 @@ def qcf_fuse_layer(desc: LayerDesc, critical: bool, B: int, n_chunks: int, total
                    ws_attn: Optional[torch.Tensor] = None) -> None:
     """One layer in one call: qcf_rerope [-> qcf_score -> qcf_select at the critical layer] -> qcf_recompute_qkv_scatter ->
     qcf_recompute_attn.  probe_off, q_probe, score and sel_idx are not looked at elsewhere."""
-    lib = load_library()
-    dev = k_fused.device
     if not critical:
-        probe_off = q_probe = score = sel_idx = ws_score = ws_select = None
-    elif ws_score is None:
-        ws_score = _workspace(qcf_score_workspace_bytes(desc, B, total_probe, total_ctx), dev)
-    if ws_rerope is None:
-        ws_rerope = _workspace(qcf_rerope_workspace_bytes(desc, n_chunks, total_ctx), dev)
-    if ws_select is None and critical:
-        ws_select = _workspace(qcf_select_workspace_bytes(B, total_ctx), dev)
+        # the re-rotation goes ahead, and runs while the rest is marshalled
+        qcf_rerope(desc, chunks_dev, n_chunks, total_ctx, k_fused, v_fused, ws_rerope)
+        n_chunks = 0
+        ws_rerope = probe_off = q_probe = score = sel_idx = ws_score = ws_select = None
+    else:
+        if ws_rerope is None:
+            ws_rerope = _workspace(qcf_rerope_workspace_bytes(desc, n_chunks, total_ctx), k_fused.device)
+        if ws_score is None:
+            ws_score = _workspace(qcf_score_workspace_bytes(desc, B, total_probe, total_ctx), k_fused.device)
+        if ws_select is None:
+            ws_select = _workspace(qcf_select_workspace_bytes(B, total_ctx), k_fused.device)
     if ws_qkv is None:
-        ws_qkv = _workspace(qcf_recompute_qkv_workspace_bytes(desc, total_sel), dev)
+        ws_qkv = _workspace(qcf_recompute_qkv_workspace_bytes(desc, total_sel), k_fused.device)
     if ws_attn is None:
-        ws_attn = _workspace(qcf_recompute_attn_workspace_bytes(desc, B, total_sel, total_ctx), dev)
-    ptrs = [_ptr(t) or 0 for t in (chunks_dev, ctx_off, probe_off, sel_off, q_probe, x_ctx, w_qkv, k_fused, v_fused, score, sel_idx,
-                                   sel_row, sel_pos, q_sel, k_sel, v_sel, o_sel, lse)]
-    ws = [(0, 0) if w is None else (w.data_ptr(), w.numel()) for w in (ws_rerope, ws_score, ws_select, ws_qkv, ws_attn)]
-    args = _LAYER_BUFFERS.pack(B, n_chunks, total_ctx, total_probe, total_sel, *ptrs, *[p for p, _ in ws], *[n for _, n in ws])
-    _check(lib.qcf_fuse_layer(C.byref(desc), args, int(critical), _stream()))
+        ws_attn = _workspace(qcf_recompute_attn_workspace_bytes(desc, B, total_sel, total_ctx), k_fused.device)
+    words = [B, n_chunks, total_ctx, total_probe, total_sel]
+    for t in (chunks_dev, ctx_off, probe_off, sel_off, q_probe, x_ctx, w_qkv, k_fused, v_fused, score, sel_idx, sel_row, sel_pos,
+              q_sel, k_sel, v_sel, o_sel, lse):
+        if t is None:
+            words.append(0)
+        elif t.is_cuda and t.is_contiguous():
+            words.append(t.data_ptr())
+        else:
+            _ptr(t)
+    ws = (ws_rerope, ws_score, ws_select, ws_qkv, ws_attn)
+    words += [0 if w is None else w.data_ptr() for w in ws]
+    words += [0 if w is None else w.numel() for w in ws]
+    _check(load_library().qcf_fuse_layer(C.byref(desc), _LAYER_BUFFERS.pack(*words), critical, _stream()))
 
 
 def qcf_linear_workspace_bytes(desc: LayerDesc, M: int, K: int, N: int) -> int:
