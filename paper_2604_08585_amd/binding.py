@@ -351,17 +351,14 @@ def qcf_fuse_layer(desc: LayerDesc, critical: bool, B: int, n_chunks: int, total
     """One layer in one call: qcf_rerope [-> qcf_score -> qcf_select at the critical layer] -> qcf_recompute_qkv_scatter ->
     qcf_recompute_attn.  probe_off, q_probe, score and sel_idx are not looked at elsewhere."""
     if not critical:
-        # the re-rotation goes ahead, and runs while the rest is marshalled
-        qcf_rerope(desc, chunks_dev, n_chunks, total_ctx, k_fused, v_fused, ws_rerope)
-        n_chunks = 0
-        ws_rerope = probe_off = q_probe = score = sel_idx = ws_score = ws_select = None
+        probe_off = q_probe = score = sel_idx = ws_score = ws_select = None
     else:
-        if ws_rerope is None:
-            ws_rerope = _workspace(qcf_rerope_workspace_bytes(desc, n_chunks, total_ctx), k_fused.device)
         if ws_score is None:
             ws_score = _workspace(qcf_score_workspace_bytes(desc, B, total_probe, total_ctx), k_fused.device)
         if ws_select is None:
             ws_select = _workspace(qcf_select_workspace_bytes(B, total_ctx), k_fused.device)
+    if ws_rerope is None:
+        ws_rerope = _workspace(qcf_rerope_workspace_bytes(desc, n_chunks, total_ctx), k_fused.device)
     if ws_qkv is None:
         ws_qkv = _workspace(qcf_recompute_qkv_workspace_bytes(desc, total_sel), k_fused.device)
     if ws_attn is None:

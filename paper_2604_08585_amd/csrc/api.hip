@@ -292,11 +292,10 @@ qcf_status qcf_recompute_qkv(const qcf_layer_desc* desc, const void* x, int64_t 
                     nullptr, 0, workspace, usable_ws(workspace, workspace_bytes), (hipStream_t)stream);
 }
 
-qcf_status qcf_recompute_qkv_scatter(const qcf_layer_desc* desc, const void* x, int64_t x_rows,
-                                     const int32_t* x_gather_dev, int64_t M, const void* w_qkv,
-                                     const int32_t* pos_dev, void* q_out, void* k_out, void* v_out,
-                                     const int32_t* dst_rows_dev, void* k_fused, void* v_fused,
-                                     int64_t total_rows, void* workspace, size_t workspace_bytes, void* stream) {
+static qcf_status check_qkv_scatter_args(const qcf_layer_desc* desc, const void* x, int64_t x_rows, const int32_t* x_gather_dev,
+                                         int64_t M, const void* w_qkv, const int32_t* pos_dev, const void* q_out, const void* k_out,
+                                         const void* v_out, const int32_t* dst_rows_dev, const void* k_fused, const void* v_fused,
+                                         int64_t total_rows, const void* workspace, size_t workspace_bytes) {
   QCF_TRY(check_desc(desc));
   if (M < 0 || x_rows < 0 || total_rows < 0) return fail(QCF_ERR_INVALID_ARG, "negative size");
   if (M > kMaxRows || x_rows > kMaxRows || total_rows > kMaxRows) return fail(QCF_ERR_UNSUPPORTED, "too many rows");
@@ -314,7 +313,17 @@ qcf_status qcf_recompute_qkv_scatter(const qcf_layer_desc* desc, const void* x, 
   QCF_TRY(need_idx_ptr(dst_rows_dev, "dst_rows_dev"));
   QCF_TRY(need_ptr(k_fused, "k_fused"));
   QCF_TRY(need_ptr(v_fused, "v_fused"));
-  QCF_TRY(need_ws(workspace, workspace_bytes, qkv_workspace_needed(*desc, M)));
+  return need_ws(workspace, workspace_bytes, qkv_workspace_needed(*desc, M));
+}
+
+qcf_status qcf_recompute_qkv_scatter(const qcf_layer_desc* desc, const void* x, int64_t x_rows,
+                                     const int32_t* x_gather_dev, int64_t M, const void* w_qkv,
+                                     const int32_t* pos_dev, void* q_out, void* k_out, void* v_out,
+                                     const int32_t* dst_rows_dev, void* k_fused, void* v_fused,
+                                     int64_t total_rows, void* workspace, size_t workspace_bytes, void* stream) {
+  QCF_TRY(check_qkv_scatter_args(desc, x, x_rows, x_gather_dev, M, w_qkv, pos_dev, q_out, k_out, v_out, dst_rows_dev, k_fused,
+                                 v_fused, total_rows, workspace, workspace_bytes));
+  if (M == 0) return QCF_OK;
   return launch_qkv(*desc, x, x_rows, x_gather_dev, M, w_qkv, pos_dev, q_out, k_out, v_out, dst_rows_dev, k_fused,
                     v_fused, total_rows, workspace, usable_ws(workspace, workspace_bytes), (hipStream_t)stream);
 }
@@ -386,10 +395,14 @@ qcf_status qcf_fuse_layer(const qcf_layer_desc* desc, const qcf_layer_buffers* l
                       check_score_args(desc, b.B, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.ctx_off_dev, b.total_ctx,
                                        nullptr, b.score, &empty) == QCF_OK &&
                       need_ws(b.score_ws, b.score_ws_bytes, scoring::workspace(*desc, b.B, b.total_probe, b.total_ctx)) == QCF_OK;
+  // A layer that is not scored: beside the projection, where that leaves compute units idle.
+  const bool beside = !critical && b.n_chunks > 0 && b.total_ctx > 0 && b.total_sel > 0 &&
+                      check_qkv_scatter_args(desc, b.x, b.total_ctx, b.sel_row, b.total_sel, b.w_qkv, b.sel_pos, b.q_sel, b.k_sel, b.v_sel,
+                                             b.sel_row, b.k_fused, b.v_fused, b.total_ctx, b.qkv_ws, b.qkv_ws_bytes) == QCF_OK;
   if (joined)
     QCF_TRY(launch_rerope_score(*desc, b.chunks_dev, b.n_chunks, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.v_fused,
                                 b.ctx_off_dev, b.total_ctx, b.score, b.score_ws, (hipStream_t)stream));
-  else
+  else if (!beside)
     QCF_TRY(qcf_rerope(desc, b.chunks_dev, b.n_chunks, b.total_ctx, b.k_fused, b.v_fused, b.rerope_ws, b.rerope_ws_bytes, stream));
   if (critical) {
     if (!joined)
@@ -398,8 +411,13 @@ qcf_status qcf_fuse_layer(const qcf_layer_desc* desc, const qcf_layer_buffers* l
     QCF_TRY(qcf_select(b.B, b.score, b.ctx_off_dev, b.total_ctx, b.sel_off_dev, b.total_sel, nullptr, b.sel_idx, b.sel_row,
                        b.sel_pos, b.select_ws, b.select_ws_bytes, stream));
   }
-  QCF_TRY(qcf_recompute_qkv_scatter(desc, b.x, b.total_ctx, b.sel_row, b.total_sel, b.w_qkv, b.sel_pos, b.q_sel, b.k_sel, b.v_sel,
-                                    b.sel_row, b.k_fused, b.v_fused, b.total_ctx, b.qkv_ws, b.qkv_ws_bytes, stream));
+  if (beside)
+    QCF_TRY(launch_rerope_qkv(*desc, b.chunks_dev, b.n_chunks, b.x, b.total_ctx, b.sel_row, b.total_sel, b.w_qkv, b.sel_pos, b.q_sel,
+                              b.k_sel, b.v_sel, b.sel_row, b.k_fused, b.v_fused, b.total_ctx, b.rerope_ws, b.qkv_ws,
+                              usable_ws(b.qkv_ws, b.qkv_ws_bytes), (hipStream_t)stream));
+  else
+    QCF_TRY(qcf_recompute_qkv_scatter(desc, b.x, b.total_ctx, b.sel_row, b.total_sel, b.w_qkv, b.sel_pos, b.q_sel, b.k_sel, b.v_sel,
+                                      b.sel_row, b.k_fused, b.v_fused, b.total_ctx, b.qkv_ws, b.qkv_ws_bytes, stream));
   return qcf_recompute_attn(desc, b.B, b.q_sel, b.sel_pos, b.sel_off_dev, b.total_sel, b.k_fused, b.v_fused, b.ctx_off_dev,
                             b.total_ctx, nullptr, b.o_sel, b.lse, b.attn_ws, b.attn_ws_bytes, stream);
 }

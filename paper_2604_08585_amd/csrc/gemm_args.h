@@ -3,9 +3,22 @@
 
 #include <stdint.h>
 
+struct qcf_chunk;
+
 namespace qcf {
 
 typedef uint16_t bf16_t;   // raw bfloat16 bits
+
+// Re-rotation of the chunk caches (qcf_rerope) by workgroups behind those of the product, on the compute units that it leaves idle.
+// Rows that the product writes (its dst_rows) are left out.
+struct SideRerope {
+  const qcf_chunk* chunks;
+  int64_t total_rows;
+  int n_chunks, style;
+  int first_wg;                  // workgroups from here on (none: beyond the grid)
+  int rows;                      // of each of them
+};
+constexpr int kSideRows = 192, kSideChunks = 256;      // rows worked on at a time; chunks, at most
 
 struct QkvArgs {
   const bf16_t* x;
@@ -36,6 +49,7 @@ struct QkvArgs {
   bf16_t* k_fused;
   bf16_t* v_fused;
   int64_t fused_rows;
+  SideRerope side;
 };
 
 // What the epilogue does with a block: rotary embedding (half-split pairs of 128- or 64-wide heads, interleaved

@@ -198,7 +198,7 @@ __device__ __forceinline__ void load_to_lds_const(const void* base, uint32_t lan
 
 size_t rerope_workspace(const qcf_layer_desc& L, int32_t n_chunks, int64_t total_rows);
 qcf_status launch_rerope(const qcf_layer_desc& L, const qcf_chunk* chunks, int32_t n_chunks,
-                         int64_t total_rows, void* kf, void* vf, void* ws, hipStream_t st);
+                         int64_t total_rows, void* kf, void* vf, void* ws, hipStream_t st, int64_t row0 = 0);      // rows from row0 on
 
 // host-side validation shared by the two scoring entry points; *empty = nothing to do
 qcf_status check_score_args(const qcf_layer_desc* desc, int32_t B, const void* q_probe,
@@ -236,7 +236,12 @@ size_t qkv_workspace(const qcf_layer_desc& L, int64_t M);
 qcf_status launch_qkv(const qcf_layer_desc& L, const void* x, int64_t x_rows, const int32_t* gather,
                       int64_t M, const void* w, const int32_t* pos, void* q, void* k, void* v,
                       const int32_t* dst_rows, void* k_fused, void* v_fused, int64_t fused_rows,
-                      void* ws, size_t ws_bytes, hipStream_t st);
+                      void* ws, size_t ws_bytes, hipStream_t st, const struct SideRerope* side = nullptr);
+// qcf_rerope (keys and values; rerope_ws) and the same, the one beside the other where the launch has compute units to spare
+qcf_status launch_rerope_qkv(const qcf_layer_desc& L, const qcf_chunk* chunks, int32_t n_chunks, const void* x, int64_t x_rows,
+                             const int32_t* gather, int64_t M, const void* w, const int32_t* pos, void* q, void* k, void* v,
+                             const int32_t* dst_rows, void* k_fused, void* v_fused, int64_t fused_rows, void* rerope_ws, void* ws,
+                             size_t ws_bytes, hipStream_t st);
 
 qcf_status launch_scatter(const qcf_layer_desc& L, const void* k_new, const void* v_new,
                           const int32_t* rows, int64_t M, void* kf, void* vf, int64_t total_rows,

@@ -628,6 +628,102 @@ struct WsTile {
   static_assert(NC * TM * 8192 <= (int)LDS_MAIN, "the epilogue works in the ring");
 };
 
+// Re-rotation of rows r0 .. r0 + n - 1 of the cache (at most kSideRows) by one workgroup.  Their chunks, the rows that the product writes and the
+// (cos, sin) pairs are worked out in LDS, then every thread keeps four pieces of keys and values on their way (two vectors of
+// each, the halves of eight rotary pairs).  64 compute units re-rotate 8192 rows of 8 heads beside a product of 192 workgroups
+// that takes 32.3 us alone and 33.5 so; the launch of its own took 13.9.
+struct SideLds {
+  qcf_chunk table[kSideChunks];
+  int16_t chunk[kSideRows];                       // of a row; -1: none, or a row of the product
+  int first, last;                                // chunks of the first and the last row
+  float2 cs[(kSideRows + 1) * 64];
+};
+static_assert(sizeof(SideLds) <= 128 * 1024, "within the ring of every tile");
+template <int NTHR>
+__device__ __forceinline__ void rerope_rows(const QkvArgs& a, int64_t r0, int n, unsigned char* smem) {
+  SideLds& l = *reinterpret_cast<SideLds*>(smem);
+  const SideRerope& s = a.side;
+  const int tid = threadIdx.x, half = a.D / 2;
+  for (int i = tid; i < s.n_chunks * (int)(sizeof(qcf_chunk) / 8); i += NTHR)
+    reinterpret_cast<uint64_t*>(l.table)[i] = reinterpret_cast<const uint64_t*>(s.chunks)[i];
+  __syncthreads();
+  auto chunk_of = [&](int64_t row) {              // the last that starts at or before the row (0 if none)
+    int lo = 0, hi = s.n_chunks - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (l.table[mid].dst_row <= row) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+  };
+  for (int i = tid; i < n; i += NTHR) {
+    const int c = chunk_of(r0 + i);
+    const qcf_chunk& ch = l.table[c];
+    l.chunk[i] = r0 + i >= ch.dst_row && r0 + i < ch.dst_row + ch.len ? (int16_t)c : (int16_t)-1;
+    if (i == 0) l.first = c;
+    if (i == n - 1) l.last = c;
+  }
+  __syncthreads();
+  for (int64_t i = tid; i < a.M; i += NTHR) {
+    const int64_t row = (int64_t)a.dst_rows[i] - r0;
+    if (row >= 0 && row < n) l.chunk[row] = -1;
+  }
+  const int first = l.first, pairs = (l.last - first + 1) * half;         // (disjoint chunks: at most one more than rows)
+  for (int i = tid; i < min(pairs, (kSideRows + 1) * 64); i += NTHR) {
+    const qcf_chunk& ch = l.table[first + i / half];
+    const double theta = exp2(a.neg2_over_d_log2base * (double)(i % half));
+    double sn, cn;
+    sincos((double)(ch.dst_pos0 - ch.src_pos0) * theta, &sn, &cn);
+    l.cs[i] = make_float2((float)cn, (float)sn);
+  }
+  __syncthreads();
+  const int row_elems = a.Hkv * a.D, per_head = half / 8, slots = a.Hkv * per_head, items = n * slots;
+  constexpr int U = 4;
+  for (int i0 = tid; i0 < items; i0 += U * NTHR) {
+    u32x4 k[U][2], v[U][2];
+    int at[U], c[U], e0[U], e1[U], p0[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * NTHR;
+      at[u] = min(i, items - 1) / slots;
+      const int slot = min(i, items - 1) - at[u] * slots, head = slot / per_head;
+      p0[u] = (slot - head * per_head) * 8;
+      e0[u] = head * a.D + (s.style == 0 ? p0[u] : 2 * p0[u]);
+      e1[u] = e0[u] + (s.style == 0 ? half : 8);
+      c[u] = i < items ? l.chunk[at[u]] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c[u] >= 0) {
+        const qcf_chunk& ch = l.table[c[u]];
+        const int64_t off = (r0 + at[u] - ch.dst_row) * row_elems;
+        const bf16_t* ks = static_cast<const bf16_t*>(ch.k_src) + off;
+        const bf16_t* vs = static_cast<const bf16_t*>(ch.v_src) + off;
+        k[u][0] = *reinterpret_cast<const u32x4*>(ks + e0[u]);
+        k[u][1] = *reinterpret_cast<const u32x4*>(ks + e1[u]);
+        v[u][0] = *reinterpret_cast<const u32x4*>(vs + e0[u]);
+        v[u][1] = *reinterpret_cast<const u32x4*>(vs + e1[u]);
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c[u] >= 0) {
+        float f[16], o[16];
+        Vec16<bf16_t>::unpack(k[u][0], f);
+        Vec16<bf16_t>::unpack(k[u][1], f + 8);
+        const float2* cs = l.cs + (c[u] - first) * half + p0[u];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if (s.style == 0) turn_pair(f[e], f[e + 8], cs[e], o[e], o[e + 8]);
+          else turn_pair(f[2 * e], f[2 * e + 1], cs[e], o[2 * e], o[2 * e + 1]);
+        }
+        const int64_t dst = (r0 + at[u]) * row_elems;
+        *reinterpret_cast<u32x4*>(a.k_fused + dst + e0[u]) = mk4(cvt_pk_bf16(o[0], o[1]), cvt_pk_bf16(o[2], o[3]), cvt_pk_bf16(o[4], o[5]), cvt_pk_bf16(o[6], o[7]));
+        *reinterpret_cast<u32x4*>(a.k_fused + dst + e1[u]) = mk4(cvt_pk_bf16(o[8], o[9]), cvt_pk_bf16(o[10], o[11]), cvt_pk_bf16(o[12], o[13]), cvt_pk_bf16(o[14], o[15]));
+        *reinterpret_cast<u32x4*>(a.v_fused + dst + e0[u]) = v[u][0];
+        *reinterpret_cast<u32x4*>(a.v_fused + dst + e1[u]) = v[u][1];
+      }
+  }
+}
+
 // WIDE: x is 4 GiB or larger (64-bit addresses per lane instead of 32-bit offsets)
 template <typename C, int EPI, bool WIDE>
 __global__ __launch_bounds__(C::NTHR) void qkv_ws_kernel(QkvArgs a) {
@@ -636,6 +732,16 @@ __global__ __launch_bounds__(C::NTHR) void qkv_ws_kernel(QkvArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hf = lane >> 5, l32 = lane & 31;
+  if constexpr (is_rope(EPI)) {
+    if ((int)blockIdx.x >= a.side.first_wg) {
+      const int64_t r0 = ((int)blockIdx.x - a.side.first_wg) * (int64_t)a.side.rows, r1 = min(r0 + a.side.rows, a.side.total_rows);
+      for (int64_t r = r0; r < r1; r += kSideRows) {
+        rerope_rows<C::NTHR>(a, r, (int)min((int64_t)kSideRows, r1 - r), smem);
+        __syncthreads();
+      }
+      return;
+    }
+  }
   // consecutive workgroup ids land on different XCDs: all row tiles of a (column block, contraction range) share an
   // XCD, so its weights are fetched into one L2 only
   const int units = a.n_tiles * a.splits;
@@ -1250,6 +1356,8 @@ qcf_status run_split_reduce(const QkvArgs& a, int64_t n_groups, hipStream_t st) 
   return check_launch("qkv split reduce");
 }
 
+constexpr int64_t kRowsOverXcds = 16;
+int64_t ws_grid(int64_t mt, int64_t units) { return mt >= kRowsOverXcds ? ((mt + 7) / 8) * 8 * units : mt * ((units + 7) / 8) * 8; }
 template <typename C, int EPI, bool WIDE>
 qcf_status run_ws(QkvArgs a, int splits, hipStream_t st) {
   const int64_t mt = (a.M + C::BM - 1) / C::BM;
@@ -1263,10 +1371,11 @@ qcf_status run_ws(QkvArgs a, int splits, hipStream_t st) {
   // workgroups would all belong to one column tile and x would be streamed once per column tile (6 times at 48
   // column tiles); then the row tiles are dealt to the XCDs instead, a row tile of x stays in L2 and the weights
   // are streamed once per row tile (measured at 73 row tiles: 1127 -> 945 us, at 20: 964 -> 912 us).
-  const bool rows_over_xcds = mt >= 16;
-  a.rows_over_xcds = rows_over_xcds ? 1 : 0;
-  const int64_t n_wg = rows_over_xcds ? ((mt + 7) / 8) * 8 * units : mt * ((units + 7) / 8) * 8;
+  a.rows_over_xcds = mt >= kRowsOverXcds;
+  const int64_t n_wg = ws_grid(mt, units);
   if (mt > 0x7fffffff || n_wg > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "qkv: grid too large");
+  const int64_t side = a.side.rows > 0 ? (a.side.total_rows + a.side.rows - 1) / a.side.rows : 0;
+  a.side.first_wg = (int)n_wg;
   // The order of a row's sums then depends on the number of rows, which the projection and the plain linear map promise not
   // to be so without a workspace.  One or two row tiles: from three on the weights are read from the L2s (K 4096, F 14336 of
   // 300 rows 98.9 and 99.8 us).  Other distances between the rows: no difference with one row tile, and K 5120, F 13824 of
@@ -1274,7 +1383,7 @@ qcf_status run_ws(QkvArgs a, int splits, hipStream_t st) {
   a.k_spread = EPI == kGlu && splits == 1 && mt <= 2 && (a.d_model & (a.d_model - 1)) == 0;
   static std::atomic<uint64_t> lds_ok;
   QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&qkv_ws_kernel<C, EPI, WIDE>), C::LDS, lds_ok));
-  qkv_ws_kernel<C, EPI, WIDE><<<dim3((unsigned)n_wg), dim3(C::NTHR), C::LDS, st>>>(a);
+  qkv_ws_kernel<C, EPI, WIDE><<<dim3((unsigned)(n_wg + side)), dim3(C::NTHR), C::LDS, st>>>(a);
   QCF_TRY_LAUNCH("qkv gemm");
   return splits > 1 ? run_split_reduce<EPI>(a, mt * C::NC, st) : QCF_OK;
 }
@@ -1374,16 +1483,42 @@ size_t qkv_workspace(const qcf_layer_desc& L, int64_t M) {
   return align_up((size_t)M * (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim * sizeof(float), 256);
 }
 
+// Re-rotation beside the product: rows of the cache for each workgroup and for all of them, the first ones (0: none; those behind
+// them come from a launch in front).  It goes beside one launch of tiles of 64 to 256 rows that leaves compute units idle: all
+// rows, if those are done with them before a launch of its own and the product would be one after the other, or as many as
+// they get done meanwhile.  Layers of 8B shape that are not scored, us, with the launch and without: 110 rows over 731 tokens 43.9
+// and 35.3, 410 over 4096 73.6, 66.1; 410 over 8192 93.4, 83.5; 480 over 12000 120.6, 111.9; 900 over 3000 (tiles of 256 rows)
+// 105.0, 96.2; with a part of the rows (16 compute units idle) 615 over 4096 85.2, 83.3; 1229 over 8192 179.6, 176.6.
+struct SideRows { int64_t each, all; };
+SideRows side_rows(const qcf_layer_desc& L, int64_t M, int32_t n_chunks, int64_t total_rows, size_t ws_bytes) {
+  const SideRows none{0, 0};
+  if (!use_mfma(L) || M <= 0 || n_chunks > kSideChunks || (uint64_t)total_rows * L.d_model * 2u >= (1ull << 32)) return none;
+  const int nb = (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim / kBN;
+  const ProductPlan p = plan_product(M, nb, L.d_model / kBK, true, ws_bytes);
+  if (p.blocks != 0) return none;
+  const int bm = p.rest.kind == kWs64 ? 64 : p.rest.kind == kWs128 ? 128 : 256;
+  const int64_t idle = compute_unit_count() - ws_grid((M + bm - 1) / bm, (int64_t)nb * p.rest.splits);
+  if (idle < 8) return none;
+  const double row_us = L.n_kv_heads * L.head_dim * 8e-6 / 44e-3, start = 5.0;      // 44 GB/s read and written by a compute unit
+  const double alone = 2.0 + (double)total_rows * row_us / 125.0;                   // (5.5 TB/s by all of them)
+  const int64_t each = (total_rows + idle - 1) / idle;
+  if ((double)((each + kSideRows - 1) / kSideRows) * start + (double)each * row_us <= p.us + alone) return {each, total_rows};
+  const int64_t fit = (int64_t)((0.9 * p.us - start) / (row_us + start / kSideRows));
+  if (fit <= 0 || (double)(fit * idle) * row_us / 125.0 < 2.0) return none;
+  return {fit, fit * idle};
+}
+
 size_t qkv_workspace_needed(const qcf_layer_desc& L, int64_t M) { return use_mfma(L) ? 0 : qkv_workspace(L, M); }
 
 qcf_status launch_qkv(const qcf_layer_desc& L, const void* x, int64_t x_rows, const int32_t* gather,
                       int64_t M, const void* w, const int32_t* pos, void* q, void* k, void* v,
                       const int32_t* dst_rows, void* k_fused, void* v_fused, int64_t fused_rows, void* ws,
-                      size_t ws_bytes, hipStream_t st) {
+                      size_t ws_bytes, hipStream_t st, const SideRerope* side) {
   const int H = L.n_q_heads, Hkv = L.n_kv_heads, D = L.head_dim;
   const int Ntot = (H + 2 * Hkv) * D;
   if (use_mfma(L)) {
     QkvArgs a{};
+    if (side) a.side = *side;
     a.x = static_cast<const bf16_t*>(x);
     a.w = static_cast<const bf16_t*>(w);
     a.gather = gather;
@@ -1403,6 +1538,17 @@ qcf_status launch_qkv(const qcf_layer_desc& L, const void* x, int64_t x_rows, co
   if (L.dtype == QCF_DTYPE_BF16)
     return run_qkv_generic<bf16_t>(L, x, x_rows, gather, M, w, pos, q, k, v, dst_rows, k_fused, v_fused, fused_rows, y, st);
   return run_qkv_generic<float>(L, x, x_rows, gather, M, w, pos, q, k, v, dst_rows, k_fused, v_fused, fused_rows, y, st);
+}
+
+qcf_status launch_rerope_qkv(const qcf_layer_desc& L, const qcf_chunk* chunks, int32_t n_chunks, const void* x, int64_t x_rows,
+                             const int32_t* gather, int64_t M, const void* w, const int32_t* pos, void* q, void* k, void* v,
+                             const int32_t* dst_rows, void* k_fused, void* v_fused, int64_t fused_rows, void* rerope_ws, void* ws,
+                             size_t ws_bytes, hipStream_t st) {
+  const SideRows rows = side_rows(L, M, n_chunks, fused_rows, ws_bytes);
+  if (rows.all < fused_rows) QCF_TRY(launch_rerope(L, chunks, n_chunks, fused_rows, k_fused, v_fused, rerope_ws, st, rows.all));
+  const SideRerope side{chunks, rows.all, n_chunks, L.rope_style, 0, (int)rows.each};
+  return launch_qkv(L, x, x_rows, gather, M, w, pos, q, k, v, dst_rows, k_fused, v_fused, fused_rows, ws, ws_bytes, st,
+                    rows.all > 0 ? &side : nullptr);
 }
 
 // ---- plain linear map, RMSNorm, gated SiLU (rest of the layer for the recomputed rows) -----------------

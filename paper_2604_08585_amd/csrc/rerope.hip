@@ -22,7 +22,7 @@ struct RopeGeom {
 
 __global__ void rerope_plan_kernel(const qcf_chunk* __restrict__ chunks, int n_chunks, int D,
                                    double neg2_over_d_log2base, float2* __restrict__ cs,
-                                   int* __restrict__ block_chunk, int n_blocks, int slots) {
+                                   int* __restrict__ block_chunk, int n_blocks, int slots, int64_t row0) {
   const int gid = blockIdx.x * blockDim.x + threadIdx.x;
   const int half = D / 2;
   if (gid < n_chunks * half) {
@@ -35,7 +35,7 @@ __global__ void rerope_plan_kernel(const qcf_chunk* __restrict__ chunks, int n_c
   }
   if (gid < n_blocks) {
     // last chunk whose first row is <= the block's first row (0 if none)
-    const int64_t row = ((int64_t)gid * kThreads) / slots;
+    const int64_t row = row0 + ((int64_t)gid * kThreads) / slots;
     int lo = 0, hi = n_chunks - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
@@ -51,7 +51,7 @@ constexpr int kMaxWgPairs = 1024;       // (cos, sin) pairs a workgroup keeps: c
 
 template <typename T, int STYLE>
 __global__ __launch_bounds__(kThreads) void rerope_fused_kernel(
-    const qcf_chunk* __restrict__ chunks, int n_chunks, double neg2_over_d_log2base, int64_t total_items,
+    const qcf_chunk* __restrict__ chunks, int n_chunks, double neg2_over_d_log2base, int64_t row0, int64_t total_items,
     int64_t total_rows, RopeGeom g, T* __restrict__ kf, T* __restrict__ vf) {
   constexpr int VEC = Elem<T>::kVec;
   __shared__ int64_t s_row[kMaxLdsChunks];
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kThreads) void rerope_fused_kernel(
   for (int c = tid; c < n_chunks; c += kThreads) { s_row[c] = chunks[c].dst_row; s_len[c] = chunks[c].len; }
   __syncthreads();
   // rows of this workgroup; last chunk whose first row is <= the workgroup's first row (0 if none)
-  const int64_t item0 = (int64_t)blockIdx.x * kThreads;
+  const int64_t item0 = row0 * g.slots + (int64_t)blockIdx.x * kThreads;
   const int64_t r_first = item0 / g.slots;
   const int64_t r_last = min(total_rows - 1, (item0 + kThreads - 1) / g.slots);
   if (tid == 0) {
@@ -138,10 +138,10 @@ __global__ __launch_bounds__(kThreads) void rerope_fused_kernel(
 template <typename T, int STYLE>
 __global__ __launch_bounds__(kThreads) void rerope_main_kernel(
     const qcf_chunk* __restrict__ chunks, int n_chunks, const float2* __restrict__ cs,
-    const int* __restrict__ block_chunk, int64_t total_items, int64_t total_rows, RopeGeom g,
+    const int* __restrict__ block_chunk, int64_t row0, int64_t total_items, int64_t total_rows, RopeGeom g,
     T* __restrict__ kf, T* __restrict__ vf) {
   constexpr int VEC = Elem<T>::kVec;
-  const int64_t item = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int64_t item = row0 * g.slots + (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (item >= total_items) return;
   const int64_t r = item / g.slots;
   const int s = (int)(item - r * g.slots);
@@ -216,9 +216,9 @@ size_t rerope_workspace(const qcf_layer_desc& L, int32_t n_chunks, int64_t total
 }
 
 qcf_status launch_rerope(const qcf_layer_desc& L, const qcf_chunk* chunks, int32_t n_chunks,
-                         int64_t total_rows, void* kf, void* vf, void* ws, hipStream_t st) {
+                         int64_t total_rows, void* kf, void* vf, void* ws, hipStream_t st, int64_t row0) {
   const RopeGeom g = geom(L);
-  const int64_t n_blocks = n_blocks_for(g, total_rows);
+  const int64_t n_blocks = n_blocks_for(g, total_rows - row0);
   if (n_blocks > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "rerope: too many rows");
   const double c = -2.0 / (double)L.head_dim * std::log2(L.rope_base);
   const int64_t items = total_rows * g.slots;
@@ -227,7 +227,7 @@ qcf_status launch_rerope(const qcf_layer_desc& L, const qcf_chunk* chunks, int32
   const int64_t wg_chunks = (kThreads + g.slots - 1) / g.slots + 1;
   if (n_chunks <= kMaxLdsChunks && wg_chunks * (L.head_dim / 2) <= kMaxWgPairs) {
 #define QCF_RF(T, S)                                                                                  \
-  rerope_fused_kernel<T, S><<<grid, block, 0, st>>>(chunks, n_chunks, c, items, total_rows, g,        \
+  rerope_fused_kernel<T, S><<<grid, block, 0, st>>>(chunks, n_chunks, c, row0, items, total_rows, g,  \
                                                     static_cast<T*>(kf), static_cast<T*>(vf))
     if (L.dtype == QCF_DTYPE_BF16) {
       if (L.rope_style == 0) QCF_RF(bf16_t, 0); else QCF_RF(bf16_t, 1);
@@ -242,10 +242,10 @@ qcf_status launch_rerope(const qcf_layer_desc& L, const qcf_chunk* chunks, int32
                                             align_up((size_t)n_chunks * (L.head_dim / 2) * sizeof(float2), 256));
   const int64_t plan_threads = std::max<int64_t>((int64_t)n_chunks * (L.head_dim / 2), n_blocks);
   rerope_plan_kernel<<<dim3((unsigned)((plan_threads + 255) / 256)), dim3(256), 0, st>>>(
-      chunks, n_chunks, L.head_dim, c, cs, block_chunk, (int)n_blocks, g.slots);
+      chunks, n_chunks, L.head_dim, c, cs, block_chunk, (int)n_blocks, g.slots, row0);
   QCF_TRY_LAUNCH("rerope plan");
 #define QCF_RR(T, S)                                                                          \
-  rerope_main_kernel<T, S><<<grid, block, 0, st>>>(chunks, n_chunks, cs, block_chunk, items,  \
+  rerope_main_kernel<T, S><<<grid, block, 0, st>>>(chunks, n_chunks, cs, block_chunk, row0, items,  \
                                                    total_rows, g, static_cast<T*>(kf), static_cast<T*>(vf))
   if (L.dtype == QCF_DTYPE_BF16) {
     if (L.rope_style == 0) QCF_RR(bf16_t, 0); else QCF_RR(bf16_t, 1);

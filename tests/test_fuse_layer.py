@@ -77,10 +77,11 @@ def test_same_bits_as_the_calls_one_after_the_other(cfg, scale, ratio, critical,
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
 
 
-def _layer(lens, gaps, R, style, H=8, Hkv=2, dm=256, before=0, behind=0, src0=0, probes=True, seed=0):
+def _layer(lens, gaps, R, style, H=8, Hkv=2, dm=256, before=0, behind=0, src0=0, probes=True, seed=0, D=128,
+           N=None):
     """One request of `lens`-token chunks with gaps[i] uncovered rows in front of chunk i; `before` / `behind` rows of the cache
     lie outside the request."""
-    dev, dt, D = torch.device("cuda:0"), torch.bfloat16, 128
+    dev, dt = torch.device("cuda:0"), torch.bfloat16
     g = torch.Generator(device=dev).manual_seed(seed)
     rnd = lambda *s: torch.randn(s, generator=g, device=dev, dtype=dt)
     sh = inputs.LayerShape(dm, H, Hkv, D, 500000.0, "bf16", style)
@@ -94,7 +95,7 @@ def _layer(lens, gaps, R, style, H=8, Hkv=2, dm=256, before=0, behind=0, src0=0,
         row += n
     total = row
     T = total - before - behind
-    N = qb.qcf_select_count(T, 0.2)
+    N = N or qb.qcf_select_count(T, 0.2)
     i64 = lambda v: torch.tensor(v, dtype=torch.int64, device=dev)
     i32 = lambda: torch.zeros(N, dtype=torch.int32, device=dev)
     ws = lambda n: torch.empty(max(n, 1), dtype=torch.uint8, device=dev)
@@ -135,6 +136,45 @@ def test_rerotation_inside_the_scoring(lens, gaps, kw, style):
         L.k_fused.copy_(k0)
         L.v_fused.copy_(v0)
         for name in OUTS[2:]:
+            getattr(L, name).fill_(1)
+        run()
+        torch.cuda.synchronize()
+        res.append([getattr(L, name).clone() for name in OUTS])
+    for name, a, b in zip(OUTS, *res):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("style", [0, 1])
+@pytest.mark.parametrize("lens,gaps,kw", [
+    ([300, 212], [0, 0], {}),
+    ([1] * 255 + [200], [0] * 256, {}),                          # as many chunks as the table holds
+    ([1] * 256 + [200], [0] * 257, {}),                          # more: in a launch of its own
+    ([17, 5, 256, 90], [3, 0, 40, 300], {}),                     # rows that no chunk covers
+    ([257], [0], dict(H=16, Hkv=4, src0=9)),
+    ([3000, 9001], [0, 7], dict(dm=1024, N=1500)),               # several tiles of rows, workgroups with more than one block
+    ([4000, 4192], [0, 0], dict(dm=4096, H=32, Hkv=8, N=620)),   # 16 compute units to spare: a part of the rows
+    ([20, 21], [0, 0], dict(D=64, Hkv=4)), ([2], [0], {})],
+    ids=["two", "256 chunks", "257 chunks", "gaps", "edges", "long", "part", "heads of 64", "one"])
+def test_rerotation_beside_the_projection(lens, gaps, kw, style):
+    print(f"re-rotation beside the projection {kw} style={style}", flush=True)
+    L = _layer(lens, gaps, R=4, style=style, **kw)
+    N, total = L.total_sel, L.total_ctx
+    g = torch.Generator(device="cuda:0").manual_seed(8)
+    sel = torch.randperm(total, generator=g, device="cuda:0")[:N].sort()[0].int()
+    row = sel.clone()
+    row[N // 3] = -1                                             # not in the cache
+    L.sel_idx.copy_(sel)
+    L.sel_row.copy_(row)
+    L.sel_pos.copy_(sel)
+    L.chunk_tensors[0][0].view(torch.int16)[0, 0, :4] = torch.tensor([0x7f81, -1, 0x7f80, -128], dtype=torch.int16)
+    k0, v0 = L.k_fused.clone(), L.v_fused.clone()
+    res = []
+    for run in (lambda: [fn(L) for name, fn in pipeline.FUSED_STEPS if name not in ("score", "select")],
+                lambda: pipeline.enqueue_layer(L, critical=False)):
+        L.k_fused.copy_(k0)
+        L.v_fused.copy_(v0)
+        for name in OUTS[6:]:
             getattr(L, name).fill_(1)
         run()
         torch.cuda.synchronize()
