@@ -16,9 +16,9 @@
 //   reduce  fixed-order sum over KV heads, times 1/(R*H), and over layers where several are scored at once.
 // Bound by the exponentials and what goes with them (about 205 vector instructions, 1200 cycles of a SIMD, per 64 tokens x
 // 32 rows and pass, against 512 of MFMAs) and, with few probe rows, by the keys: 8 layers, 48 rows x 32 heads over 6001
-// tokens 170 us in eight launches of the single kernel below, 36 + 36 + 5 us here, where the loads alone take 21 + 22; 80
+// tokens 170 us in eight launches of the single kernel below, 32 + 33 + 5 us here, where the loads alone take 21 + 22; 80
 // rows x 64 heads over 32768 tokens 85 + 149 us with one tile to a workgroup, whose every workgroup of pass 2 folded 128
-// partials per row, 67 + 71 here.  A wave's next MFMAs between the exponentials of its last rows (two waves to a SIMD, no
+// partials per row, 60 + 61 here.  A wave's next MFMAs between the exponentials of its last rows (two waves to a SIMD, no
 // registers for a third): 77 + 82.
 // Launches that are resident at once (one workgroup per compute unit at most, up to 320 probe rows per KV
 // group) take a single kernel instead (score_fused, further down): the exponentials of pass 1 stay in registers
@@ -1104,30 +1104,49 @@ __global__ __launch_bounds__(kFusedThreads) void score_fused(FusedArgs fa) {
   }
 }
 
-// Adds the KV heads of every layer in order, and the layers, in order, into the score.
+// Adds the KV heads of every layer in order, and the layers, in order, into the score.  Several layers: layers_at a time by as
+// many groups of threads, 256 / layers_at tokens to a workgroup, so that the loads of all of them are on their way together (8
+// layers of 6001 tokens, 24 workgroups with one layer after the other: 6.4 us, now 4.6).
+__host__ __device__ __forceinline__ int layers_at(int n_layers) { return n_layers >= 4 ? 4 : n_layers >= 2 ? 2 : 1; }
 template <bool ONE>
 __global__ __launch_bounds__(256) void score_reduce(Args<ONE> pa) {
   const ScoreArgs& a = common(pa);
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (j >= a.total_ctx) return;
-  const int b = find_request(a.ctx_off, a.B, j);
-  if (b >= a.B) return;
-  const int64_t p0 = min(max(a.probe_off[b], (int64_t)0), a.total_probe);
-  const int64_t p1 = min(max(a.probe_off[b + 1], p0), a.total_probe);
+  __shared__ float s_sum[ONE ? 1 : kMaxLayers * 256 / 4];        // [layer][token]
+  int at = 1;
+  if constexpr (!ONE) at = layers_at(pa.n_layers);
+  const int toks = 256 / at, tok = (int)threadIdx.x % toks;
+  const int64_t j = (int64_t)blockIdx.x * toks + tok;
+  const int b = j < a.total_ctx ? find_request(a.ctx_off, a.B, j) : a.B;
+  int64_t p0 = 0, p1 = 0;
+  if (b < a.B) {
+    p0 = min(max(a.probe_off[b], (int64_t)0), a.total_probe);
+    p1 = min(max(a.probe_off[b + 1], p0), a.total_probe);
+  }
   const float n = (float)((p1 - p0) * a.H);
   if constexpr (ONE) {
+    if (b >= a.B) return;
     float acc = 0.f;
     for (int g = 0; g < a.Hkv; ++g) acc += a.colsum[(int64_t)g * a.total_ctx + j];
     write_score(a, j, p1 > p0 ? acc / n : 0.f);
   } else {
-    float score = a.beta == 0.f ? 0.f : a.score[j];
-    for (int l = 0; l < pa.n_layers; ++l) {
+    auto layer_sum = [&](int l) {
       const float* col = a.colsum + (int64_t)l * a.Hkv * a.total_ctx + j;
       float acc = 0.f;
 #pragma unroll 8
       for (int g = 0; g < a.Hkv; ++g) acc += col[g * a.total_ctx];
-      score = blended(l == 0 ? a.beta : 1.f, score, pa.alpha[l] * (p1 > p0 ? acc / n : 0.f));
+      return p1 > p0 ? acc / n : 0.f;
+    };
+    float score = b < a.B && a.beta != 0.f ? a.score[j] : 0.f;
+    if (at == 1) {
+      if (b < a.B) a.score[j] = blended(a.beta, score, pa.alpha[0] * layer_sum(0));
+      return;
     }
+    if (b < a.B)
+#pragma unroll 2
+      for (int l = (int)threadIdx.x / toks; l < pa.n_layers; l += at) s_sum[l * toks + tok] = layer_sum(l);
+    __syncthreads();
+    if ((int)threadIdx.x >= toks || b >= a.B) return;
+    for (int l = 0; l < pa.n_layers; ++l) score = blended(l == 0 ? a.beta : 1.f, score, pa.alpha[l] * s_sum[l * toks + tok]);
     a.score[j] = score;
   }
 }
@@ -1161,7 +1180,9 @@ qcf_status run_two_pass(const Args<ONE>& a, dim3 grid, hipStream_t st) {
   QCF_TRY_LAUNCH("score pass 1");
   score_pass2<D, LIMIT, ONE><<<grid, block, kPass2Lds<D>, st>>>(a);
   QCF_TRY_LAUNCH("score pass 2");
-  score_reduce<ONE><<<dim3((unsigned)((common(a).total_ctx + 255) / 256)), dim3(256), 0, st>>>(a);
+  int toks = 256;
+  if constexpr (!ONE) toks /= layers_at(a.n_layers);
+  score_reduce<ONE><<<dim3((unsigned)((common(a).total_ctx + toks - 1) / toks)), dim3(256), 0, st>>>(a);
   return check_launch("score reduce");
 }
 template <bool ONE>
