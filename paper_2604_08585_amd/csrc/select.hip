@@ -1,10 +1,13 @@
 // Step 3: Top-N selection (Section 3.1 Phase 3 / Section 3.2 token selector of the paper).
 //
-// One 1024-thread workgroup per request.  Scores map to order-preserving 32-bit keys; an
-// MSB-first radix select over the bits in which the keys actually differ finds the N-th
-// largest key and how many of its ties to admit; a block-wide prefix scan then compacts the
-// admitted indices in index order, so the output is ascending and ties go to the lower index.
-// Integer work only: exact and deterministic.
+// One 1024-thread workgroup per request.  Scores map to order-preserving 32-bit keys; a histogram over the range that the
+// keys span finds the bin of the N-th largest, the few keys of that bin are ranked against each other (or, where they are
+// many, split by a histogram over their own range), and a block-wide prefix count then compacts the admitted indices in index
+// order, so the output is ascending and ties go to the lower index.  Integer work only: exact and deterministic.
+// Bound by the chain of barriers and latencies (an empty selection takes 1.8 us) and, from about 8192 keys, by the vector
+// instructions of one compute unit.  One launch of many, 15 % of T keys selected, us, with a radix select of 9 bits to a pass
+// over all keys, contiguous keys per thread and outputs stored one by one, and now: 731 keys 5.9 and 3.8, 4096 8.5 and 5.1,
+// 8192 10.5 and 6.5, 32768 25.8 and 14.7, 40000 137 and 26.9; 18 requests of 2000 to 16000 21.0 and 12.0.
 #include "qcf_internal.h"
 
 namespace qcf {
@@ -12,9 +15,12 @@ namespace {
 
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
-constexpr int kDigitBits = 9;                 // bits resolved per pass (measured best of 8..11 at 8192 keys)
+constexpr int kDigitBits = 10;               // bits resolved per histogram (8192 keys: 9 bits 6.8 us, 10 6.4)
 constexpr int kBins = 1 << kDigitBits;
-constexpr int kBinsPerLane = kBins / 64;     // the first wave scans the histogram
+static_assert(kBins == kThreads && kWaves == 16, "a thread has one bin, a row of lanes the waves' sums");
+constexpr int kRanked = 128;                 // keys of one bin that are ranked against each other, and not split further (64 and 256 alike)
+constexpr int kListed = kThreads;            // keys of one bin that are listed, one to a thread, and not looked for again
+constexpr int kStage = 8192;                 // outputs that leave together
 
 __device__ __forceinline__ uint32_t order_key(float s) {
   uint32_t u = __float_as_uint(s);
@@ -22,175 +28,284 @@ __device__ __forceinline__ uint32_t order_key(float s) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-__device__ __forceinline__ uint64_t wave_incl_scan(uint64_t v, int lane) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t lo = __shfl_up((uint32_t)v, d, 64);
-    const uint32_t hi = __shfl_up((uint32_t)(v >> 32), d, 64);
-    if (lane >= d) v += ((uint64_t)hi << 32) | lo;
-  }
-  return v;
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ uint32_t dpp(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
+}
+// Least and largest value of the 16 lanes of a row (row_ror).
+__device__ __forceinline__ uint32_t row_min(uint32_t x) {
+  x = min(x, dpp<0x128>(x)); x = min(x, dpp<0x124>(x)); x = min(x, dpp<0x122>(x));
+  return min(x, dpp<0x121>(x));
+}
+__device__ __forceinline__ uint32_t row_max(uint32_t x) {
+  x = max(x, dpp<0x128>(x)); x = max(x, dpp<0x124>(x)); x = max(x, dpp<0x122>(x));
+  return max(x, dpp<0x121>(x));
+}
+__device__ __forceinline__ uint32_t from_lane(uint32_t x, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)x, lane); }
+// Inclusive sum over the lanes of a wave: within rows (row_shr), then across them (row_bcast).
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
+  x += dpp<0x111>(x); x += dpp<0x112>(x); x += dpp<0x114>(x); x += dpp<0x118>(x);
+  x += dpp<0x142, 0xa>(x);
+  return x + dpp<0x143, 0xc>(x);
+}
+// Sum of x over the first i + 1 of 16 lanes, where every row of the wave has the same sixteen values.
+__device__ __forceinline__ uint32_t row_incl_scan_at(uint32_t x, int i) {
+  x += dpp<0x111>(x); x += dpp<0x112>(x); x += dpp<0x114>(x); x += dpp<0x118>(x);
+  return from_lane(x, i);
+}
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {    // set bits of the lanes before this one
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 struct SelectLds {
   uint32_t merged[kBins];
-  uint64_t wave_tot[kWaves];
+  uint32_t listed[kListed];
+  uint32_t wave_sum[kWaves], wave_gt[kWaves], wave_eq[kWaves];
   uint32_t red_lo[kWaves], red_hi[kWaves];
-  uint32_t digit, k;
+  uint32_t digit, k, count, n_listed;
+  int32_t list[kStage];              // the selected indices of the last window, from which they leave
 };
 
-// One request: T scores, N of them to select (0 < N <= T), written from sel_*[o0] on.
-// SEG > 0: each thread keeps up to SEG keys of its contiguous segment of seg keys in registers.
-// SEG == 0: keys are re-read from global memory in every pass (any length).
+// One request: T scores, N of them to select (0 < N <= T), written from sel_*[o0] on.  Wave w has the keys from w * 64 * seg
+// on, in rows of 64 (seg == 1) or 256 (seg a multiple of four: 4 to a lane), so that loads are whole lines.
+// SEG > 0: each thread keeps up to SEG keys in registers.  SEG == 0: keys are re-read in every pass (any length).
 template <int SEG>
 __device__ __forceinline__ void select_request(SelectLds& lds, const float* __restrict__ s, int64_t c0, int T, int N, int seg,
                                                int64_t o0, int base_pos, int32_t* __restrict__ sel_idx,
                                                int32_t* __restrict__ sel_row, int32_t* __restrict__ sel_pos) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int j0 = min(T, tid * seg), j1 = min(T, j0 + seg);      // (T is at most 2^30)
-  const int cnt = j1 - j0;
-
-  uint32_t keys[SEG > 0 ? SEG : 1];
-  if (SEG > 0) {
-    // segments start at multiples of four: with an aligned request every whole quad is one load
-    if (SEG % 4 == 0 && (reinterpret_cast<uintptr_t>(s) & 15u) == 0) {
-      if (cnt == SEG) {
+  constexpr int C = SEG == 1 ? 1 : 4, kRows = SEG / C;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto emit = [&](int pos, int j) {
+    if (sel_idx) sel_idx[o0 + pos] = j;
+    if (sel_row) sel_row[o0 + pos] = (int32_t)(c0 + j);
+    if (sel_pos) sel_pos[o0 + pos] = base_pos + j;
+  };
+  if (N == T) {
+    for (int j = tid; j < T; j += kThreads) emit(j, j);
+    return;
+  }
+  seg = max(seg, C);
+  const int first = wave * 64 * seg + lane * C;                  // this lane's first key (T is at most 2^30)
+  const int left = min(T, (wave + 1) * 64 * seg) - first;        // key c of row q exists: 64 * C * q + c < left
+  const int rows = min(seg / C, (max(0, T - wave * 64 * seg) + 64 * C - 1) / (64 * C));
+  const int rows_full = min(seg / C, max(0, T - wave * 64 * seg) / (64 * C));
+  const bool quads = C == 4 && (reinterpret_cast<uintptr_t>(s) & 15u) == 0;
+  auto load_row = [&](int q, uint32_t (&bits)[C]) {              // (branches of whole waves: the loads stay in flight)
+    const int j = first + 64 * C * q;
+    if (q < rows_full && quads) {
+      const u32x4 v = *reinterpret_cast<const u32x4*>(s + j);
 #pragma unroll
-        for (int i = 0; i < SEG; i += 4) {
-          const float4 v = *reinterpret_cast<const float4*>(s + j0 + i);
-          const float q[4] = {v.x, v.y, v.z, v.w};
+      for (int c = 0; c < C; ++c) bits[c] = v[c];
+    } else if (q < rows) {
 #pragma unroll
-          for (int c = 0; c < 4 && i + c < SEG; ++c) keys[i + c] = order_key(q[c]);
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < SEG; i += 4) {
-          float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (i + 3 < cnt) v = *reinterpret_cast<const float4*>(s + j0 + i);
-          else {
-            if (i < cnt) v.x = s[j0 + i];
-            if (i + 1 < cnt) v.y = s[j0 + i + 1];
-            if (i + 2 < cnt) v.z = s[j0 + i + 2];
-          }
-          const float q[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-          for (int c = 0; c < 4 && i + c < SEG; ++c) keys[i + c] = order_key(q[c]);
-        }
-      }
+      for (int c = 0; c < C; ++c) bits[c] = __float_as_uint(s[min(j + c, T - 1)]);
     } else {
 #pragma unroll
-      for (int i = 0; i < SEG; ++i) keys[i] = (i < cnt) ? order_key(s[j0 + i]) : 0u;
+      for (int c = 0; c < C; ++c) bits[c] = 0u;
+    }
+  };
+  // A key that is not there is 0, what no score but one NaN maps to, and so never among the N < T largest unless that NaN is.
+  const bool full = rows_full == (SEG > 0 ? kRows : seg / C);    // (of the whole wave)
+  uint32_t keys[SEG > 0 ? kRows : 1][C];
+  uint32_t lo = 0xffffffffu, hi = 0u;                            // range of the keys
+  auto order_row = [&](int q, uint32_t (&key)[C]) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) key[c] = order_key(__uint_as_float(key[c]));
+    if (!full) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) key[c] = 64 * C * q + c < left ? key[c] : 0u;
+    }
+  };
+  auto range_row = [&](int q, const uint32_t (&key)[C]) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      lo = full || 64 * C * q + c < left ? min(lo, key[c]) : lo;
+      hi = max(hi, key[c]);
+    }
+  };
+  if constexpr (SEG > 0) {
+#pragma unroll
+    for (int q = 0; q < kRows; ++q) load_row(q, keys[q]);
+    if (full) {
+#pragma unroll
+      for (int q = 0; q < kRows; ++q) { order_row(q, keys[q]); range_row(q, keys[q]); }
+    } else {
+#pragma unroll
+      for (int q = 0; q < kRows; ++q) { order_row(q, keys[q]); range_row(q, keys[q]); }
     }
   }
-#define QCF_KEY(i) (SEG > 0 ? keys[i] : order_key(s[j0 + (i)]))
-#define QCF_FOR_KEYS(i, ...)                                   \
-  if (SEG > 0) {                                               \
-    _Pragma("unroll") for (int i = 0; i < SEG; ++i) {          \
-      if (i < cnt) { __VA_ARGS__ }                             \
-    }                                                          \
-  } else {                                                     \
-    for (int i = 0; i < cnt; ++i) { __VA_ARGS__ }              \
-  }
-
-  uint32_t tau = 0;       // key of the N-th largest score
-  uint32_t k = (uint32_t)N;   // how many keys equal to tau are admitted
-
-  if (N < T) {
-    // range of the keys
-    uint32_t lo = 0xffffffffu, hi = 0u;
-    QCF_FOR_KEYS(i, { const uint32_t key = QCF_KEY(i); lo = min(lo, key); hi = max(hi, key); })
+  // f(q, key[C]), row by row
+  auto walk = [&](auto&& f) {
+    if constexpr (SEG > 0) {
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
-      hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
-    }
-    if (lane == 0) { lds.red_lo[wave] = lo; lds.red_hi[wave] = hi; }
-    for (int i = tid; i < kBins; i += kThreads) lds.merged[i] = 0u;
-    __syncthreads();
-    lo = lds.red_lo[0]; hi = lds.red_hi[0];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) { lo = min(lo, lds.red_lo[w]); hi = max(hi, lds.red_hi[w]); }
-
-    const uint32_t diff = lo ^ hi;
-    int bits = diff ? 32 - __clz((int)diff) : 0;     // low bits in which keys may differ
-    uint32_t prefix = (bits >= 32) ? 0u : (hi >> bits);   // common high part
-    while (bits > 0) {
-      const int w = min(kDigitBits, bits);
-      const int shift = bits - w;
-      const uint32_t mask = (1u << w) - 1u;
-      // (lds.merged[] was cleared before the loop and is cleared again by wave 0 after each pass)
-      QCF_FOR_KEYS(i, {
-        const uint32_t key = QCF_KEY(i);
-        const uint32_t high = (bits >= 32) ? 0u : (key >> bits);
-        if (high == prefix) atomicAdd(&lds.merged[(key >> shift) & mask], 1u);
-      })
-      __syncthreads();
-      if (wave == 0) {
-        uint32_t c[kBinsPerLane];
-        uint32_t tot = 0;
-#pragma unroll
-        for (int q = 0; q < kBinsPerLane; ++q) {
-          c[q] = lds.merged[kBinsPerLane * lane + q];
-          tot += c[q];
-          lds.merged[kBinsPerLane * lane + q] = 0u;
-        }
-        uint32_t suffix = tot;               // sum over lanes >= this one
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-          const uint32_t o = __shfl_down(suffix, d, 64);
-          if (lane + d < 64) suffix += o;
-        }
-        uint32_t above = suffix - tot;       // keys with a larger digit than this lane's bins
-#pragma unroll
-        for (int q = kBinsPerLane - 1; q >= 0; --q) {
-          if (above < k && k <= above + c[q]) { lds.digit = kBinsPerLane * lane + q; lds.k = k - above; }
-          above += c[q];
-        }
+      for (int q = 0; q < kRows; ++q) f(q, keys[q]);
+    } else {
+      for (int q = 0; q < rows; ++q) {
+        load_row(q, keys[0]);
+        order_row(q, keys[0]);
+        f(q, keys[0]);
       }
-      __syncthreads();
-      prefix = (prefix << w) | lds.digit;
-      k = lds.k;
-      bits = shift;
     }
-    tau = prefix;
-  }
+  };
+  if constexpr (SEG == 0) walk(range_row);
 
-  // compaction in index order
-  uint32_t n_gt = 0, n_eq = 0;
-  if (N < T) {
-    QCF_FOR_KEYS(i, { const uint32_t key = QCF_KEY(i); n_gt += key > tau; n_eq += key == tau; })
-  } else {
-    n_gt = (uint32_t)cnt;
-  }
-  const uint64_t mine = ((uint64_t)n_eq << 32) | n_gt;
-  const uint64_t incl = wave_incl_scan(mine, lane);
-  if (lane == 63) lds.wave_tot[wave] = incl;
+  lo = row_min(lo);
+  hi = row_max(hi);
+  lo = min(min(from_lane(lo, 0), from_lane(lo, 16)), min(from_lane(lo, 32), from_lane(lo, 48)));   // (by all lanes: the rows'
+  hi = max(max(from_lane(hi, 0), from_lane(hi, 16)), max(from_lane(hi, 32), from_lane(hi, 48)));   // values are there)
+  if (lane == 0) { lds.red_lo[wave] = lo; lds.red_hi[wave] = hi; }
+  lds.merged[tid] = 0u;
+  if (tid == 0) lds.n_listed = 0u;
   __syncthreads();
-  uint64_t before = incl - mine;
-  for (int w = 0; w < wave; ++w) before += lds.wave_tot[w];
-  uint32_t gt_before = (uint32_t)before, eq_before = (uint32_t)(before >> 32);
-  const int64_t out0 = o0;
-#define QCF_EMIT(j, pos)                                            \
-  {                                                                 \
-    if (sel_idx) sel_idx[out0 + (pos)] = (j);                       \
-    if (sel_row) sel_row[out0 + (pos)] = (int32_t)(c0 + (j));       \
-    if (sel_pos) sel_pos[out0 + (pos)] = base_pos + (j);            \
+  lo = __builtin_amdgcn_readfirstlane(row_min(lds.red_lo[lane & 15]));
+  hi = __builtin_amdgcn_readfirstlane(row_max(lds.red_hi[lane & 15]));
+
+  // The N-th largest key is top - d for a d of fewer than bits bits: one of count keys, the k-th largest of them.
+  uint32_t top = hi, k = (uint32_t)N, tau = hi;
+  int bits = hi > lo ? 32 - __clz((int)(hi - lo)) : 0;
+  bool listed = SEG == 1;                    // one key to a thread, ones of them (otherwise keys that are not there count too)
+  uint32_t one = SEG == 1 ? keys[0][0] : 0u;
+  int ones = T;
+  uint32_t count = SEG == 1 ? (uint32_t)T : (uint32_t)max(T, kListed + 1);
+  while (bits > 0) {
+    // (no key is more than 2^bits below the first top, so that top - key of a key above top has a bit above)
+    auto in_bin = [&](uint32_t key) { return bits >= 32 || (top - key) >> bits == 0u; };
+    if (count <= (uint32_t)(listed ? kRanked : kListed)) {
+      auto list = [&](uint32_t key) {
+        if (in_bin(key)) {
+          const uint32_t at = atomicAdd(&lds.n_listed, 1u);
+          if (at < (uint32_t)kListed) lds.listed[at] = key;
+        }
+      };
+      if (listed) {
+        if (tid < ones) list(one);
+      } else walk([&](int, const uint32_t (&key)[C]) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) list(key[c]);
+      });
+      __syncthreads();
+      ones = (int)count;
+      one = tid < ones ? lds.listed[tid] : 0u;
+      listed = true;
+      if (count <= (uint32_t)kRanked) {
+        if (tid < ones) {
+          uint32_t gt = 0, eq = 0;
+#pragma unroll 8
+          for (int i = 0; i < ones; ++i) {
+            const uint32_t o = lds.listed[i];
+            gt += o > one;
+            eq += o == one;
+          }
+          if (gt < k && k <= gt + eq) { lds.digit = one; lds.k = k - gt; }     // (the same by all that are equal)
+        }
+        __syncthreads();
+        tau = lds.digit;
+        k = lds.k;
+        break;
+      }
+    }
+    const int w = min(kDigitBits, bits), shift = bits - w;
+    auto add = [&](uint32_t key) {
+      const uint32_t bin = (top - key) >> shift;
+      if (bin >> w == 0u) atomicAdd(&lds.merged[bin], 1u);
+    };
+    if (listed) {
+      if (tid < ones) add(one);
+    } else walk([&](int, const uint32_t (&key)[C]) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) add(key[c]);
+    });
+    __syncthreads();
+    const uint32_t here = lds.merged[tid], incl = wave_incl_scan(here);
+    if (lane == 63) lds.wave_sum[wave] = incl;
+    __syncthreads();
+    const uint32_t before = row_incl_scan_at(lds.wave_sum[lane & 15], wave) - from_lane(incl, 63) + incl - here;   // larger keys
+    if (before < k && k <= before + here) { lds.digit = (uint32_t)tid; lds.k = k - before; lds.count = here; }
+    lds.merged[tid] = 0u;
+    if (tid == 0) lds.n_listed = 0u;
+    __syncthreads();
+    top -= lds.digit << shift;
+    k = lds.k;
+    count = lds.count;
+    bits = shift;
+    tau = top;
   }
-  if (N < T) {
-    QCF_FOR_KEYS(i, {
-      const uint32_t key = QCF_KEY(i);
-      const bool gt = key > tau, eq = key == tau;
-      const uint32_t pos = gt_before + min(eq_before, k);
-      if ((gt || (eq && eq_before < k)) && pos < (uint32_t)N) QCF_EMIT(j0 + i, pos)
-      gt_before += gt;
-      eq_before += eq;
-    })
-  } else {
-    for (int i = 0; i < cnt; ++i) QCF_EMIT(j0 + i, gt_before + i)
+  tau = __builtin_amdgcn_readfirstlane(tau);             // key of the N-th largest score; of those equal to it k are admitted
+  k = __builtin_amdgcn_readfirstlane(k);
+
+  // Compaction in index order: the waves' counts, then ballots within a wave.  Where every tie is admitted, as nearly always,
+  // the keys from tau on; otherwise the larger ones and the first k of the equal ones.
+  uint32_t n_ge = 0;
+  walk([&](int, const uint32_t (&key)[C]) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) n_ge += (uint32_t)__popcll(__ballot(key[c] >= tau));
+  });
+  if (lane == 0) lds.wave_gt[wave] = n_ge;
+  __syncthreads();
+  uint32_t gt0 = row_incl_scan_at(lds.wave_gt[lane & 15], wave) - n_ge, eq0 = 0;
+  const bool ties = row_incl_scan_at(lds.wave_gt[lane & 15], kWaves - 1) != (uint32_t)N;
+  if (ties) {
+    uint32_t n_gt = 0, n_eq = 0;
+    walk([&](int q, const uint32_t (&key)[C]) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        n_gt += (uint32_t)__popcll(__ballot(key[c] > tau));
+        n_eq += (uint32_t)__popcll(__ballot(key[c] == tau && 64 * C * q + c < left));
+      }
+    });
+    __syncthreads();
+    if (lane == 0) { lds.wave_gt[wave] = n_gt; lds.wave_eq[wave] = n_eq; }
+    __syncthreads();
+    gt0 = row_incl_scan_at(lds.wave_gt[lane & 15], wave) - n_gt;
+    eq0 = row_incl_scan_at(lds.wave_eq[lane & 15], wave) - n_eq;
   }
-#undef QCF_EMIT
-#undef QCF_KEY
-#undef QCF_FOR_KEYS
+  for (int w0 = 0; w0 < N; w0 += kStage) {
+    uint32_t gt_run = gt0 - (uint32_t)w0, eq_run = eq0, tau_now = tau;
+    asm volatile("" : "+s"(tau_now));                            // (compared anew: the masks of the counts are not kept)
+    if (!ties) {
+      walk([&](int q, const uint32_t (&key)[C]) {
+        uint32_t pos = gt_run;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          const uint64_t ge = __ballot(key[c] >= tau_now);
+          pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(ge >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ge, pos));
+          gt_run += (uint32_t)__popcll(ge);
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          const bool ge = key[c] >= tau_now;
+          if (ge && pos < (uint32_t)kStage) lds.list[pos] = first + 64 * C * q + c;
+          pos += ge;
+        }
+      });
+    } else {
+      int left_now = left;
+      asm volatile("" : "+v"(left_now));
+      walk([&](int q, const uint32_t (&key)[C]) {
+        uint32_t gt = gt_run, eq = eq_run;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          const uint64_t bg = __ballot(key[c] > tau_now), be = __ballot(key[c] == tau_now && 64 * C * q + c < left_now);
+          gt += lanes_below(bg);
+          eq += lanes_below(be);
+          gt_run += (uint32_t)__popcll(bg);
+          eq_run += (uint32_t)__popcll(be);
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          const bool is_gt = key[c] > tau_now, is_eq = key[c] == tau_now && 64 * C * q + c < left_now;
+          const uint32_t pos = gt + min(eq, k);
+          if ((is_gt || (is_eq && eq < k)) && pos < (uint32_t)kStage) lds.list[pos] = first + 64 * C * q + c;
+          gt += is_gt;
+          eq += is_eq;
+        }
+      });
+    }
+    __syncthreads();
+    const int n = min(N - w0, kStage);
+    for (int i = tid; i < n; i += kThreads) emit(w0 + i, lds.list[i]);
+    if (w0 + kStage < N) __syncthreads();
+  }
 }
 
 // Keys per thread follow the length of each request: a batch of requests whose total exceeds what registers hold does not
@@ -254,7 +369,6 @@ __global__ __launch_bounds__(kThreads) void select_gather_kernel(const float* __
   if (seg > 1) seg = (seg + 3) & ~3;
   select_request<MAX>(lds, score + c0, c0, T, N, seg, o0, 0, nullptr, rows, nullptr);
   if (!k_out) return;                                            // (rows only: the gather is a launch of its own)
-  __syncthreads();                                               // this workgroup's rows are written
   const int64_t out = o0 * vec_per_row;
   const int items = N * vec_per_row;                             // (at most kGatherVecs)
   for (int i0 = tid; i0 < items; i0 += 4 * kThreads) {
@@ -262,7 +376,7 @@ __global__ __launch_bounds__(kThreads) void select_gather_kernel(const float* __
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int i = min(i0 + u * kThreads, items - 1), m = i / vec_per_row;
-      const int64_t src = (int64_t)rows[o0 + m] * vec_per_row + (i - m * vec_per_row);
+      const int64_t src = (c0 + (N < T ? lds.list[m] : m)) * vec_per_row + (i - m * vec_per_row);
       kk[u] = k[src];
       vv[u] = v[src];
     }
@@ -299,6 +413,7 @@ qcf_status launch_select(int32_t B, const float* score, const int64_t* ctx_off, 
 // the copy is a launch over all of them (64 chunks of 1024, 128 rows each: 56 us by the workgroups, 44 with the launch; 64
 // rows each: 43 both ways).
 constexpr int64_t kGatherVecs = 8192;
+static_assert(kGatherVecs <= kStage, "the rows are read from the one window that they leave in");
 
 qcf_status launch_select_gather(const qcf_layer_desc& L, const float* score, int32_t n_chunks, const int64_t* ctx_off,
                                 const int64_t* sel_off, const void* k, const void* v, int32_t* rows, void* k_out, void* v_out,

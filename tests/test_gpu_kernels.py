@@ -596,6 +596,33 @@ def test_select_keys_per_thread(lens):
         c0, s0 = c0 + n, s0 + m
 
 
+@pytest.mark.parametrize("T", [127, 129, 1000, 1025, 3001, 9001, 40001])
+def test_select_crowded_bins_and_extreme_keys(T):
+    """Keys that crowd one bin, the whole range of 32 bits, the NaN of the lowest key, more outputs than leave together:
+    the N largest by their order-preserving keys, ties to the lower index."""
+    say(f"select extremes {T}")
+    rng = np.random.default_rng(T)
+    low = np.array([0xFFFFFFFF], np.uint32).view(np.float32)[0]
+    crowd = (0x3F000000 + rng.integers(0, max(T // 3, 2), T)).astype(np.uint32).view(np.float32)
+    crowd[T // 2] = 1e-30
+    wide = rng.integers(0, 2 ** 32, T, dtype=np.uint64).astype(np.uint32).view(np.float32)
+    wide[1::5] = wide[0]
+    lowest = np.where(rng.random(T) < 0.3, low, wide).astype(np.float32)
+    lowest.view(np.uint32)[3] = 0xFFFFFFFF
+    for s in (crowd, wide, lowest, rng.choice(np.float32([np.inf, -np.inf, 0.0, -0.0, 2.0]), T)):
+        u = s.view(np.uint32).copy()
+        u[u == 0x80000000] = 0
+        key = np.where(u >> 31 != 0, ~u, u | 0x80000000).astype(np.int64)
+        order = np.argsort(-key, kind="stable")
+        for n in sorted({1, T // 7, T // 2, T - 2, T - 1}):
+            want = np.sort(order[:n]).astype(np.int32)
+            d = torch.from_numpy(s.view(np.int32).copy()).to(DEV).view(torch.float32)
+            idx, row, pos = (torch.full((n,), -7, dtype=torch.int32, device=DEV) for _ in range(3))
+            qb.qcf_select(1, d, i64([0, T]), T, i64([0, n]), n, None, idx, row, pos)
+            torch.cuda.synchronize()
+            assert all(np.array_equal(x.cpu().numpy(), want) for x in (idx, row, pos)), (T, n)
+
+
 def test_anchor_extraction_is_refused_under_capture():
     """Its offsets come from a pinned block that is handed back after the call; a replay would read whatever is there."""
     say("anchors under capture")
