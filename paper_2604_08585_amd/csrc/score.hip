@@ -53,18 +53,45 @@ __device__ __forceinline__ int find_request(const int64_t* __restrict__ off, int
   return b;
 }
 
+// sums over the 16 lanes of each row and the 32 of each half of a wave, in a fixed order; every lane gets the total
+__device__ __forceinline__ float row_sum(float x) {
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x128, 0xf, 0xf, false));   // row_ror:8
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x124, 0xf, 0xf, false));   // row_ror:4
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x122, 0xf, 0xf, false));   // row_ror:2
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x121, 0xf, 0xf, false));   // row_ror:1
+  return x;
+}
+__device__ __forceinline__ float half_wave_sum(float x) {
+  x = row_sum(x);
+  typedef unsigned u2v __attribute__((ext_vector_type(2)));
+  const u2v r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r.x) + __uint_as_float(r.y);     // rows (0, 1) and (2, 3) of 16 lanes each
+}
+
 // ------------------------------------------------------------------ generic path
 
-template <typename T>
-__global__ __launch_bounds__(256) void score_rows_generic(
+// D / 4 lanes take a token, so that a load brings whole key rows, and a wave has eight of its loads on their way.  Up to
+// kKeptLogits tokens the row's logits and exponentials stay in LDS; through the workspace every step waits for the stores of
+// the one before.  Both kernels of a call, us, with one thread to a token and the row in the workspace, and so: 20 rows x 8 heads of
+// 64 over 512 tokens 12.8 and 10.1, over 2000 25.9 and 15.9; 80 rows x 8 heads of 128 over 1000 tokens 63.5 and 38.6.
+constexpr int kRowThreads = 512, kRowWaves = kRowThreads / 64;
+constexpr int kRowLoads = 8;
+constexpr int kKeptLogits = 2048;
+
+template <typename T, int D>
+__global__ __launch_bounds__(kRowThreads) void score_rows_generic(
     const T* __restrict__ q, const int64_t* __restrict__ probe_off, int64_t /*total_probe*/,
     const T* __restrict__ k, const int64_t* __restrict__ ctx_off, int64_t total_ctx, int B,
-    const int32_t* __restrict__ probe_limit, int H, int Hkv, int D, float* __restrict__ P) {
-  __shared__ float sq[128];
-  __shared__ float red[4];
+    const int32_t* __restrict__ probe_limit, int H, int Hkv, float* __restrict__ P) {
+  constexpr int kLanes = D / 4, kTokens = 64 / kLanes;           // lanes of a token, tokens of a load
+  static_assert(D == 64 || D == 128, "a row of 16 lanes, or two");
+  __shared__ float red[2][kRowWaves];
+  __shared__ float kept[kKeptLogits];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t row = blockIdx.x / H;
   const int h = blockIdx.x - (int)row * H;
+  float qf[4];
+  Quad<T>::load(q + ((int64_t)row * H + h) * D + 4 * (lane % kLanes), qf);
   const int b = find_request(probe_off, B, row);
   if (b >= B) return;
   int64_t c0 = min(max(ctx_off[b], (int64_t)0), total_ctx);
@@ -74,40 +101,50 @@ __global__ __launch_bounds__(256) void score_rows_generic(
   if (probe_limit) limit = min(Tn, max(0, probe_limit[row]));
   float* prow = P + ((int64_t)row * H + h) * total_ctx + c0;
   const int g = h / (H / Hkv);
-  if (tid < D) sq[tid] = Elem<T>::load(q + ((int64_t)row * H + h) * D + tid);
-  __syncthreads();
   const float scale = rsqrtf((float)D);
-  float mx = -INFINITY;
-  for (int j = tid; j < limit; j += 256) {
-    const T* kr = k + ((c0 + j) * Hkv + g) * (int64_t)D;
-    float acc = 0.f;
-#pragma unroll 4
-    for (int c = 0; c < D; c += 4) {
-      float kf[4];
-      Quad<T>::load(kr + c, kf);
+  auto softmax_row = [&](float* w) {
+    const int step = kTokens * kRowLoads;
+    for (int j0 = wave * step; j0 < limit; j0 += kRowWaves * step) {
+      float kf[kRowLoads][4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc += sq[c + e] * kf[e];
+      for (int u = 0; u < kRowLoads; ++u) {
+        const int j = min(j0 + u * kTokens + lane / kLanes, limit - 1);
+        Quad<T>::load(k + ((c0 + j) * Hkv + g) * (int64_t)D + 4 * (lane % kLanes), kf[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < kRowLoads; ++u) {
+        float acc = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc += qf[e] * kf[u][e];
+        acc = kLanes == 16 ? row_sum(acc) : half_wave_sum(acc);
+        const int j = j0 + u * kTokens + lane / kLanes;
+        if (lane % kLanes == 0 && j < limit) w[j] = acc * scale;
+      }
     }
-    acc *= scale;
-    prow[j] = acc;
-    mx = fmaxf(mx, acc);
-  }
-  for (int d = 32; d >= 1; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
-  if (lane == 0) red[wave] = mx;
-  __syncthreads();
-  mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  __syncthreads();
-  float sum = 0.f;
-  for (int j = tid; j < limit; j += 256) {
-    const float e = expf(prow[j] - mx);
-    prow[j] = e;
-    sum += e;
-  }
-  for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
-  if (lane == 0) red[wave] = sum;
-  __syncthreads();
-  sum = (red[0] + red[1]) + (red[2] + red[3]);
-  for (int j = tid; j < Tn; j += 256) prow[j] = (j < limit) ? prow[j] / sum : 0.f;
+    __syncthreads();
+    float mx = -INFINITY;
+    for (int j = tid; j < limit; j += kRowThreads) mx = fmaxf(mx, w[j]);
+    for (int d = 32; d >= 1; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
+    if (lane == 0) red[0][wave] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kRowWaves; ++i) mx = fmaxf(mx, red[0][i]);
+    float sum = 0.f;
+    for (int j = tid; j < limit; j += kRowThreads) {
+      const float e = expf(w[j] - mx);
+      w[j] = e;
+      sum += e;
+    }
+    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    if (lane == 0) red[1][wave] = sum;
+    __syncthreads();
+    sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < kRowWaves; ++i) sum += red[1][i];
+    for (int j = tid; j < Tn; j += kRowThreads) prow[j] = (j < limit) ? w[j] / sum : 0.f;
+  };
+  if (limit <= kKeptLogits) softmax_row(kept);
+  else softmax_row(prow);
 }
 
 // One thread per token adds its column in row order, sixteen rows on their way at a time; workgroups of one wave, so
@@ -713,17 +750,6 @@ __device__ __forceinline__ float fetch(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// sum over the 32 lanes of each half of a wave, in a fixed order; every lane of the half gets the total
-__device__ __forceinline__ float half_wave_sum(float x) {
-  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x128, 0xf, 0xf, false));   // row_ror:8
-  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x124, 0xf, 0xf, false));   // row_ror:4
-  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x122, 0xf, 0xf, false));   // row_ror:2
-  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x121, 0xf, 0xf, false));   // row_ror:1
-  typedef unsigned u2v __attribute__((ext_vector_type(2)));
-  const u2v r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r.x) + __uint_as_float(r.y);     // rows (0, 1) and (2, 3) of 16 lanes each
-}
-
 constexpr size_t kFusedLds = kQBytes<128> + kKBytes<128>;
 // Re-rotation of a tile (RR): the chunk table, each row's chunk, and the (cos, sin) pairs of the tile's chunks, behind the
 // staged rows.
@@ -1303,15 +1329,16 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
     if (total_probe * H > 0x7fffffff || col_blocks > 0x7fffffff)
       return fail(QCF_ERR_UNSUPPORTED, "score: too many rows");
     if (total_probe > 0) {
-      const dim3 grid((unsigned)(total_probe * H)), block(256);
-      if (L.dtype == QCF_DTYPE_BF16)
-        score_rows_generic<bf16_t><<<grid, block, 0, st>>>(
-            static_cast<const bf16_t*>(q), probe_off, total_probe, static_cast<const bf16_t*>(k), ctx_off,
-            total_ctx, B, probe_limit, H, Hkv, D, P);
-      else
-        score_rows_generic<float><<<grid, block, 0, st>>>(
-            static_cast<const float*>(q), probe_off, total_probe, static_cast<const float*>(k), ctx_off,
-            total_ctx, B, probe_limit, H, Hkv, D, P);
+      const dim3 grid((unsigned)(total_probe * H)), block(kRowThreads);
+#define QCF_ROWS(T, DIM)                                                                                             \
+  score_rows_generic<T, DIM><<<grid, block, 0, st>>>(static_cast<const T*>(q), probe_off, total_probe, static_cast<const T*>(k), \
+                                                     ctx_off, total_ctx, B, probe_limit, H, Hkv, P)
+      if (L.dtype == QCF_DTYPE_BF16) {
+        if (D == 64) QCF_ROWS(bf16_t, 64); else QCF_ROWS(bf16_t, 128);
+      } else {
+        if (D == 64) QCF_ROWS(float, 64); else QCF_ROWS(float, 128);
+      }
+#undef QCF_ROWS
       QCF_TRY_LAUNCH("score rows");
     }
     score_colmean_generic<<<dim3((unsigned)col_blocks), dim3(kColThreads), 0, st>>>(P, probe_off, total_probe, ctx_off,

@@ -596,6 +596,33 @@ def test_select_keys_per_thread(lens):
         c0, s0 = c0 + n, s0 + m
 
 
+@pytest.mark.parametrize("D,T,R", [(64, 1, 1), (64, 3, 2), (64, 255, 5), (64, 257, 3), (64, 2048, 2), (64, 2049, 2), (128, 1, 3), (128, 127, 20), (128, 2047, 3), (128, 4100, 2)])
+def test_f32_scoring_rows(D, T, R):
+    """Tokens per load and per wave, a row in LDS and in the workspace, rows that see part of the context: against float64.
+    Bound: worst case of the dot products' rounding in the exponent, of the sums over a row and over the rows."""
+    say(f"f32 scoring D={D} T={T} R={R}")
+    g = gen(61)
+    H, Hkv = 4, 2
+    q, k = torch.randn((R, H, D), generator=g, device=DEV), torch.randn((T, Hkv, D), generator=g, device=DEV)
+    limit = torch.randint(1, T + 1, (R,), generator=g, device=DEV).int()
+    desc = qb.make_desc(inputs.LayerShape(256, H, Hkv, D, 10000.0, "f32"))
+    kk = k.double().repeat_interleave(H // Hkv, 1)
+    logits = torch.einsum("rhd,thd->rht", q.double().cpu(), kk.cpu()) * D ** -0.5
+    size = float(torch.einsum("rhd,thd->rht", q.double().abs().cpu(), kk.abs().cpu()).max()) * D ** -0.5
+    bound = 2.0 ** -24 * (2 * (D + 4) * size + T + R * H + 64)
+    for lim in (None, limit):
+        out = torch.full((T,), 7.0, device=DEV)
+        if lim is None:
+            qb.qcf_score(desc, 1, q, i64([0, R]), R, k, i64([0, T]), T, None, out)
+            p = torch.softmax(logits, -1)
+        else:
+            qb.qcf_score(desc, 1, q, i64([0, R]), R, k, i64([0, T]), T, lim, out)
+            p = torch.softmax(logits.masked_fill(torch.arange(T)[None, None] >= lim.cpu()[:, None, None], -torch.inf), -1)
+        torch.cuda.synchronize()
+        ref = p.mean((0, 1))
+        assert bool(((out.double().cpu() - ref).abs() <= bound * ref).all()), float(((out.double().cpu() - ref).abs() / ref.clamp_min(1e-30)).max())
+
+
 @pytest.mark.parametrize("T", [127, 129, 1000, 1025, 3001, 9001, 40001])
 def test_select_crowded_bins_and_extreme_keys(T):
     """Keys that crowd one bin, the whole range of 32 bits, the NaN of the lowest key, more outputs than leave together:
