@@ -33,7 +33,6 @@ struct QkvArgs {
   int m_group;                   // row tiles walked together (workgroup order of the 256 x 256 kernel)
   int rows_over_xcds;            // workgroup order of the load/compute-split kernel (see there)
   int splits, split_len;         // the contraction is cut into `splits` ranges of split_len k-tiles
-  int k_spread;                  // the column blocks start at different k-tiles (see qkv_ws_kernel)
   void* part;                    // their partial sums (splits > 1), float4
   bf16_t* q;
   bf16_t* k;

@@ -608,12 +608,6 @@ __device__ __forceinline__ void wave_epilogue(const QkvArgs& a, const OutTile& o
 //   load wave:    after barrier kt it requests tile kt+S-1 into stage (kt+S-1)%S == (kt-1)%S (free: every
 //                 compute wave finished reading tile kt-1 before barrier kt), waits until its loads of
 //                 tile kt+1 have landed, barrier.
-//
-// k_spread: column block b of n starts at k-tile b nk / n and comes round to the tiles in front of it at the end.  Workgroups
-// that stream weights keep in step, and rows a power of two apart have the same columns on a few of the memory's channels:
-// with all of them at one k-tile the stream stays at 4.6 TB/s.  Gate / up weights of 235 MB (K 4096, F 14336), us, all at one
-// tile and spread, reading them at 6.2 TB/s takes 38: 16 rows 50.7 and 43.0, 61 rows 51.5 and 42.7, 128 rows 53.6 and 48.8,
-// 200 rows 65.8 and 62.5; K 8192, F 28672 of 40 rows 193 and 167; K 1024, F 2816 of 128 rows 13.7 and 10.1.
 template <int TM_, int NC_, int S_>
 struct WsTile {
   static constexpr int TM = TM_, TN = 4, NC = NC_, NL = 4, S = S_;
@@ -790,11 +784,9 @@ __global__ __launch_bounds__(C::NTHR) void qkv_ws_kernel(QkvArgs a) {
       b_off[i] = block_w_step<EPI>(a, row) * row_bytes + (uint32_t)chunk * 16u;
     }
     const char* b_base = reinterpret_cast<const char*>(a.w + block_w_row<EPI>(block) * a.d_model) + (int64_t)kt0 * kBK * 2;
-    const int first = a.k_spread ? (int)((int64_t)n_tile * nk / a.n_tiles) : 0;
-    auto issue = [&](int it) {
-      unsigned char* sA = smem + (size_t)(it % S) * C::STAGE;
+    auto issue = [&](int kt) {
+      unsigned char* sA = smem + (size_t)(kt % S) * C::STAGE;
       unsigned char* sB = sA + C::BM * kBK * 2;
-      const int kt = first + it < nk ? first + it : first + it - nk;
 #pragma unroll
       for (int i = 0; i < C::B_LD; ++i)
         load_to_lds(b_base + (int64_t)kt * kBK * 2, b_off[i], sB + (lw + C::NL * i) * 1024);
@@ -1376,11 +1368,6 @@ qcf_status run_ws(QkvArgs a, int splits, hipStream_t st) {
   if (mt > 0x7fffffff || n_wg > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "qkv: grid too large");
   const int64_t side = a.side.rows > 0 ? (a.side.total_rows + a.side.rows - 1) / a.side.rows : 0;
   a.side.first_wg = (int)n_wg;
-  // The order of a row's sums then depends on the number of rows, which the projection and the plain linear map promise not
-  // to be so without a workspace.  One or two row tiles: from three on the weights are read from the L2s (K 4096, F 14336 of
-  // 300 rows 98.9 and 99.8 us).  Other distances between the rows: no difference with one row tile, and K 5120, F 13824 of
-  // 256 rows 85.3 and 88.3 us.
-  a.k_spread = EPI == kGlu && splits == 1 && mt <= 2 && (a.d_model & (a.d_model - 1)) == 0;
   static std::atomic<uint64_t> lds_ok;
   QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&qkv_ws_kernel<C, EPI, WIDE>), C::LDS, lds_ok));
   qkv_ws_kernel<C, EPI, WIDE><<<dim3((unsigned)(n_wg + side)), dim3(C::NTHR), C::LDS, st>>>(a);

@@ -117,11 +117,11 @@ def test_gated_silu():
 
 
 @pytest.mark.parametrize("M,K,F", [
-    (16, 1024, 2816), (200, 1024, 2816),     # 44 column blocks that start at 16 k-tiles; one and two row tiles
+    (16, 1024, 2816), (200, 1024, 2816),     # 44 column blocks over 16 k-tiles; one and two row tiles
     (1, 64, 16448), (40, 128, 14336),        # one and two k-tiles, fewer than the loads on their way
     (61, 4096, 14336), (128, 2048, 8192)])
 def test_gated_weight_stream(M, K, F):
-    """Few rows, undivided: column blocks that start at different k-tiles.  Bounds as above."""
+    """Few rows, undivided.  Bounds as above."""
     print(f"gated weight stream M={M} K={K} F={F}", flush=True)
     desc = qb.make_desc(DESC)
     assert qb.load_library().qcf_linear_swiglu_workspace_bytes(C.byref(desc), M, K, F) == 0
@@ -138,3 +138,25 @@ def test_gated_weight_stream(M, K, F):
     err = (outs[0][:M].float() - ref).abs()
     assert bool((err <= 2.0 ** -8 * ref.abs() + 2.0 ** -7 * (1.1 * gate.abs() * up.abs()) + 2e-4).all()), float(err.max())
     assert torch.equal(outs[0], outs[1]) and bool((outs[0][M] == 7.0).all())
+
+
+@pytest.mark.parametrize("M,K,F", [(513, 4096, 14336), (600, 2048, 8192), (700, 1024, 2816)])
+def test_gated_product_without_workspace_has_one_order_of_sums(M, K, F):
+    """Without a workspace a row's bits depend neither on the number of rows nor on its place among them: whole rounds of 256 x 256
+    tiles and a remainder of one row (the first shape), other tiles than those of a batch cut short."""
+    print(f"order of sums of the gated product M={M} K={K} F={F}", flush=True)
+    desc, lib = qb.make_desc(DESC), qb.load_library()
+    x, w = _normal(14, M, K), _normal(15, 2 * F, K, std=K ** -0.5)
+    x[M - 1] = x[3]
+
+    def product(rows):
+        out = torch.full((rows, F), 7.0, dtype=BF, device=DEV)
+        st = torch.cuda.current_stream().cuda_stream
+        assert lib.qcf_linear_swiglu(C.byref(desc), x.data_ptr(), rows, K, w.data_ptr(), F, out.data_ptr(), None, 0, st) == 0
+        torch.cuda.synchronize()
+        return out
+
+    whole = product(M)
+    assert torch.equal(whole[M - 1], whole[3])
+    for rows in (4, 61, 128):
+        assert torch.equal(product(rows), whole[:rows]), rows
