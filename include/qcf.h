@@ -216,7 +216,10 @@ qcf_status qcf_scatter(const qcf_layer_desc* desc, const void* k_new, const void
  * are processed in blocks of consecutive rows and a block runs as far as its highest
  * position.  o_out [total_sel, H, d]; lse_out (may be NULL) [total_sel, H]
  * float32 natural-log sum-exp of the scaled logits.  A row that sees nothing gets a zero
- * output row and lse = -inf. */
+ * output row and lse = -inf.
+ * bf16, few rows of one request over a short context: the workspace that is reported lets the context be divided finer, which is
+ * faster.  With less, as long as it is what the division of a longer launch takes (nothing, for contexts of a few hundred tokens),
+ * the call divides it that way; last bits then differ.  Heads of 64 need none at all. */
 size_t qcf_recompute_attn_workspace_bytes(const qcf_layer_desc* desc, int32_t B,
                                           int64_t total_sel, int64_t total_ctx);
 qcf_status qcf_recompute_attn(const qcf_layer_desc* desc, int32_t B,

@@ -674,9 +674,6 @@ __device__ __forceinline__ float weighted(float w, float f) {
   if (SPLIT_P) return fabsf(f) < INFINITY ? w * f : f;
   return w * f;
 }
-// Element of the partial outputs: float, but for the 128-row workgroups of heads of 128 in launches that are not short, which
-// round them to bf16 (1229 rows x 32 heads over 8192 tokens write and read 20 MB of them so).
-constexpr bool part_is_f32(int D, int rows, const Split& s) { return D == 64 || rows == kWideRows || s.part_f32; }
 template <int D, int ROWS> constexpr int kMergeWgs = ROWS * (D / 8) / 256;
 template <int D, int ROWS, bool F32>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
@@ -797,18 +794,6 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
         s_out[tid / 8 * 8 + (ch ^ (r_out & 7))];
 }
 
-size_t part_o_bytes(int D, const Division& d, int Hkv) {
-  const size_t elem = part_is_f32(D, d.rows, d.split) ? sizeof(float) : sizeof(bf16_t);
-  return align_up((size_t)d.n_row_blocks * Hkv * d.split.n_seg_max * d.rows * D * elem, 256);
-}
-size_t part_lse_bytes(int D, const Division& d, int Hkv) {
-  return align_up((size_t)d.n_row_blocks * Hkv * d.split.n_seg_max * d.rows * (D == 128 ? 1 : 2) * sizeof(float), 256);
-}
-size_t units_bytes(int64_t n_row_blocks, int n_seg_max) {
-  return align_up((size_t)(n_row_blocks * n_seg_max + 1) * sizeof(int32_t), 256);
-}
-size_t blk_tiles_bytes(int64_t n_row_blocks) { return align_up((size_t)n_row_blocks * sizeof(int32_t), 256); }
-
 template <int D, int ROWS, bool F32>
 qcf_status run_mfma(const AttnArgs& a, hipStream_t st) {
   const int64_t blocks = (int64_t)a.n_row_blocks * a.Hkv;
@@ -839,15 +824,11 @@ bool use_mfma(const qcf_layer_desc& L) {
 }  // namespace
 
 size_t attn_workspace(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx) {
-  if (!use_mfma(L) || total_sel <= 0 || total_ctx <= 0) return 0;
-  const Division d = divide(L, B, total_sel, total_ctx);
-  if (d.split.n_seg_max <= 1) return 0;
-  return part_o_bytes(L.head_dim, d, L.n_kv_heads) + part_lse_bytes(L.head_dim, d, L.n_kv_heads) +
-         units_bytes(d.n_row_blocks, d.split.n_seg_max) + blk_tiles_bytes(d.n_row_blocks);
+  return use_mfma(L) && total_sel > 0 && total_ctx > 0 ? full_workspace(L, B, total_sel, total_ctx) : 0;
 }
 
 size_t attn_workspace_needed(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx) {
-  return L.head_dim == 128 ? attn_workspace(L, B, total_sel, total_ctx) : 0;
+  return use_mfma(L) && L.head_dim == 128 && total_sel > 0 && total_ctx > 0 ? least_workspace(L, B, total_sel, total_ctx) : 0;
 }
 
 qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const int32_t* sel_pos,
@@ -865,9 +846,9 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
   a.seg_tiles = 0x3fffffff; a.n_seg_max = 1; a.part_o = nullptr; a.part_lse = nullptr; a.units = nullptr; a.blk_tiles = nullptr;
   a.own_order = 0;
   if (use_mfma(L)) {
-    const Division d = divide(L, B, total_sel, total_ctx);
+    const Division d = divide(L, B, total_sel, total_ctx, ws_bytes);
     Split sp = d.split;
-    if (attn_workspace(L, B, total_sel, total_ctx) > ws_bytes) sp = Split{0x3fffffff, 1};      // (d = 64 only: optional)
+    if (workspace_of(L, d) > ws_bytes) sp = Split{0x3fffffff, 1};      // (d = 64 only: optional)
     const int64_t nb = d.n_row_blocks;
     if (nb * a.Hkv * std::max(sp.n_seg_max, d.rows * 16 / 256) > 0x7fffffff)
       return fail(QCF_ERR_UNSUPPORTED, "attn: grid too large");
@@ -878,7 +859,7 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
     if (sp.n_seg_max > 1) {
       a.part_o = ws;
       char* w = static_cast<char*>(ws);
-      a.part_lse = reinterpret_cast<float*>(w + part_o_bytes(L.head_dim, d, a.Hkv));
+      a.part_lse = reinterpret_cast<float*>(w + part_o_bytes(L, d));
       // The plan sorts the units for the compute units to take in turn.  Where all of them start at once their order does
       // not matter, and the launch is saved: 110 rows over 731 tokens 22.3 -> 19.0 us, 40 rows over 8192 30.4 -> 23.5.
       // The workgroups of one request find their places themselves (ordered_unit) up to 512 units, which covers the split
@@ -891,8 +872,8 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
       } else if (B == 1 && nb * sp.n_seg_max <= kOrderMax && nb <= kOrderBlocks) {
         a.own_order = 1;
       } else {
-        a.units = reinterpret_cast<int32_t*>(w + part_o_bytes(L.head_dim, d, a.Hkv) + part_lse_bytes(L.head_dim, d, a.Hkv));
-        a.blk_tiles = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(a.units) + units_bytes(nb, sp.n_seg_max));
+        a.units = reinterpret_cast<int32_t*>(w + part_o_bytes(L, d) + part_lse_bytes(L, d));
+        a.blk_tiles = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(a.units) + units_bytes(d));
       }
     }
     if (a.D == 64) return run_mfma<64, kNarrowRows, true>(a, st);

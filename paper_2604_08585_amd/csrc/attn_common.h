@@ -39,7 +39,7 @@ struct AttnArgs {
   int n_row_blocks;      // upper bound on row blocks over all requests (MFMA path)
   int seg_tiles;         // key tiles per work unit; a row block with more tiles is split over units
   int n_seg_max;         // units per row block the grid provides
-  void* part_o;          // [unit][rows of a workgroup][D] normalised partial outputs of split row blocks (PartOf in attn.hip)
+  void* part_o;          // [unit][32 rows][32 D] normalised partial outputs of split row blocks, in the order of the registers (attn_merge_kernel); float or bf16 (part_is_f32)
   float* part_lse;       // [unit][rows of a workgroup] log2-domain log-sum-exp of each partial (-inf: no visible key); d = 64: pairs of
                          // reference point (log2 units) and denominator against it
   int32_t* units;        // units[0] = number of work units, then (row block << 8 | segment), longest first (null: no plan)

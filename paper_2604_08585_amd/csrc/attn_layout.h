@@ -1,6 +1,7 @@
 // How the attention of the MFMA kernels is divided into workgroups.  Plain host code as well (no HIP header).
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 #include <algorithm>
@@ -99,7 +100,7 @@ inline bool takes_wide(const qcf_layer_desc& L, int32_t B, int64_t total_sel, in
   return blocks >= kWideBlocks * cus && filled * tiles >= kWideBatchTiles * cus &&
          1.12 * (filled + 0.25 * requests) * (tiles + 2.0) >= 1.01 * (filled + 0.5 * requests) * (tiles + 7.0);
 }
-inline Division divide(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx) {
+inline Division divide_plainly(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx) {
   auto of = [&](int rows) {
     const int64_t nb = row_blocks(L, rows, B, total_sel);
     return Division{rows, nb, choose_split(rows, nb * L.n_kv_heads, total_ctx)};
@@ -108,9 +109,45 @@ inline Division divide(const qcf_layer_desc& L, int32_t B, int64_t total_sel, in
     const Division wide = of(kWideRows);
     if (takes_wide(L, B, total_sel, total_ctx, wide.n_row_blocks * L.n_kv_heads)) return wide;
   }
-  Division d = of(kNarrowRows);
-  if (B == 1) d.split = short_split(L.head_dim, (double)total_sel * L.n_q_heads / kNarrowRows, total_ctx, d.split);
-  return d;
+  return of(kNarrowRows);
+}
+
+// Element of the partial outputs: float, but for the 128-row workgroups of heads of 128 in launches that are not short, which
+// round them to bf16 (1229 rows x 32 heads over 8192 tokens write and read 20 MB of them so).
+constexpr bool part_is_f32(int D, int rows, const Split& s) { return D == 64 || rows == kWideRows || s.part_f32; }
+
+// What a split launch keeps in the workspace, in this order: partial outputs, their log-sum-exps (heads of 64: pairs), the list of
+// units, the lengths of the row blocks.
+inline size_t aligned(size_t n) { return (n + 255) / 256 * 256; }
+inline size_t part_o_bytes(const qcf_layer_desc& L, const Division& d) {
+  const size_t elem = part_is_f32(L.head_dim, d.rows, d.split) ? 4 : 2;
+  return aligned((size_t)d.n_row_blocks * L.n_kv_heads * d.split.n_seg_max * d.rows * L.head_dim * elem);
+}
+inline size_t part_lse_bytes(const qcf_layer_desc& L, const Division& d) {
+  return aligned((size_t)d.n_row_blocks * L.n_kv_heads * d.split.n_seg_max * d.rows * (L.head_dim == 128 ? 1 : 2) * sizeof(float));
+}
+inline size_t units_bytes(const Division& d) { return aligned((size_t)(d.n_row_blocks * d.split.n_seg_max + 1) * sizeof(int32_t)); }
+inline size_t blk_tiles_bytes(const Division& d) { return aligned((size_t)d.n_row_blocks * sizeof(int32_t)); }
+inline size_t workspace_of(const qcf_layer_desc& L, const Division& d) {
+  if (d.split.n_seg_max <= 1) return 0;
+  return part_o_bytes(L, d) + part_lse_bytes(L, d) + units_bytes(d) + blk_tiles_bytes(d);
+}
+
+// The division of a launch with ws_bytes of workspace.  Short segments keep more than choose_split's, and the more the fewer rows
+// there are, so they are for a workspace that holds them: what a call has to be given (least_workspace) does not follow
+// from them, and one workspace serves the layers of a model whatever the number of their rows.
+inline Division divide(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx, size_t ws_bytes = SIZE_MAX) {
+  const Division plain = divide_plainly(L, B, total_sel, total_ctx);
+  if (B != 1 || plain.rows != kNarrowRows) return plain;
+  Division d = plain;
+  d.split = short_split(L.head_dim, (double)total_sel * L.n_q_heads / kNarrowRows, total_ctx, plain.split);
+  return workspace_of(L, d) <= ws_bytes ? d : plain;
+}
+inline size_t least_workspace(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx) {
+  return workspace_of(L, divide_plainly(L, B, total_sel, total_ctx));
+}
+inline size_t full_workspace(const qcf_layer_desc& L, int32_t B, int64_t total_sel, int64_t total_ctx) {
+  return std::max(least_workspace(L, B, total_sel, total_ctx), workspace_of(L, divide(L, B, total_sel, total_ctx)));
 }
 
 }  // namespace attn

@@ -18,6 +18,14 @@ extern "C" void division(const qcf_layer_desc* L, int B, long long rows, long lo
   const qcf::attn::Division d = qcf::attn::divide(*L, B, rows, tokens);
   out[0] = d.rows; out[1] = d.n_row_blocks; out[2] = d.split.n_seg_max;
 }
+// least and full workspace, and what the division takes that a workspace of `have` bytes gives
+extern "C" void attention_workspace(const qcf_layer_desc* L, int B, long long rows, long long tokens, long long have, long long* out) {
+  using namespace qcf::attn;
+  out[0] = least_workspace(*L, B, rows, tokens);
+  out[1] = full_workspace(*L, B, rows, tokens);
+  const Division d = divide(*L, B, rows, tokens, have);
+  out[2] = workspace_of(*L, d); out[3] = d.split.n_seg_max; out[4] = d.split.part_f32;
+}
 """
 
 
@@ -37,6 +45,15 @@ def attention(H, Hkv, D, T, sel):
     desc = qb.make_desc(inputs.LayerShape(2048, H, Hkv, D, 10000.0, "bf16"))
     out = (C.c_longlong * 3)()
     _library().division(C.byref(desc), len(T), C.c_longlong(sum(sel)), C.c_longlong(sum(T)), out)
+    return tuple(out)
+
+
+def attention_workspace(H, Hkv, D, T, sel, have=0):
+    """Bytes of workspace without which the attention of these requests is refused (heads of 128), bytes that are reported, and
+    of the division with `have` bytes of it: its own bytes, key segments, whether they are short ones."""
+    desc = qb.make_desc(inputs.LayerShape(2048, H, Hkv, D, 10000.0, "bf16"))
+    out = (C.c_longlong * 5)()
+    _library().attention_workspace(C.byref(desc), len(T), C.c_longlong(sum(sel)), C.c_longlong(sum(T)), C.c_longlong(have), out)
     return tuple(out)
 
 

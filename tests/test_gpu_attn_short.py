@@ -2,6 +2,8 @@
 import pytest
 
 import host_rules
+from paper_2604_08585_amd import binding as qb
+from paper_2604_08585_amd import inputs
 import test_gpu_attn_order as order
 
 pytestmark = pytest.mark.gpu
@@ -20,3 +22,21 @@ pytestmark = pytest.mark.gpu
 def test_short_segments(H, Hkv, D, T, n, segments, kind):
     assert host_rules.attention(H, Hkv, D, [T], [n])[2] == segments
     order.test_order_of_units(H, Hkv, D, T, n, kind)
+
+
+@pytest.mark.parametrize("H,Hkv,D,T,n", [
+    (32, 8, 128, 512, 77),          # none
+    (32, 8, 128, 731, 110), (32, 8, 128, 731, 300), (32, 8, 128, 2048, 100), (64, 8, 128, 731, 31),
+    (32, 8, 64, 731, 110)])         # (optional, but taken)
+def test_least_workspace(H, Hkv, D, T, n, monkeypatch):
+    """A caller whose workspace holds the division of longer launches only, or who has none where that takes none."""
+    least, full, *_ = host_rules.attention_workspace(H, Hkv, D, [T], [n])
+    assert least < full == qb.qcf_recompute_attn_workspace_bytes(qb.make_desc(inputs.LayerShape(2048, H, Hkv, D, 10000.0, "bf16")), 1, n, T)
+    assert not host_rules.attention_workspace(H, Hkv, D, [T], [n], least)[4]
+    monkeypatch.setattr(qb, "qcf_recompute_attn_workspace_bytes", lambda *a: least)
+    order.test_order_of_units(H, Hkv, D, T, n, "spread")
+    order.test_order_of_units(H, Hkv, D, T, n, "none visible")
+    if D == 128 and least:
+        monkeypatch.setattr(qb, "qcf_recompute_attn_workspace_bytes", lambda *a: least - 1)
+        with pytest.raises(qb.QcfError, match="TOO_SMALL"):
+            order.test_order_of_units(H, Hkv, D, T, n, "spread")
