@@ -650,6 +650,33 @@ def test_select_crowded_bins_and_extreme_keys(T):
             assert all(np.array_equal(x.cpu().numpy(), want) for x in (idx, row, pos)), (T, n)
 
 
+def test_select_of_many_outputs_reads_the_scores_once_more():
+    """A million keys: half of them selected takes no more passes over the keys than 8192, only more stores.  (With a pass per 8192
+    outputs 18 times as long; the line is far from that and from 1.)"""
+    say("select half of a million")
+    T = 1 << 20
+    score = torch.exp(torch.randn(T, generator=gen(63), device=DEV))
+
+    def ms(n):
+        out = [torch.empty(n, dtype=torch.int32, device=DEV) for _ in range(3)]
+        call = lambda: qb.qcf_select(1, score, i64([0, T]), T, i64([0, n]), n, None, *out)
+        call()
+        torch.cuda.synchronize()
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            call()
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        ref = torch.sort(torch.sort(score, descending=True, stable=True)[1][:n])[0].int()
+        assert all(torch.equal(x, ref) for x in out), n
+        return best
+
+    assert ms(T // 2) < 4 * ms(8192)
+
+
 def test_anchor_extraction_is_refused_under_capture():
     """Its offsets come from a pinned block that is handed back after the call; a replay would read whatever is there."""
     say("anchors under capture")
