@@ -375,7 +375,7 @@ def qcf_fuse_layer(desc: LayerDesc, critical: bool, B: int, n_chunks: int, total
     ws = (ws_rerope, ws_score, ws_select, ws_qkv, ws_attn)
     words += [0 if w is None else w.data_ptr() for w in ws]
     words += [0 if w is None else w.numel() for w in ws]
-    _check(load_library().qcf_fuse_layer(C.byref(desc), _LAYER_BUFFERS.pack(*words), critical, _stream()))
+    _check(load_library().qcf_fuse_layer(C.byref(desc), _LAYER_BUFFERS.pack(*words), 1 if critical else 0, _stream()))
 
 
 def qcf_linear_workspace_bytes(desc: LayerDesc, M: int, K: int, N: int) -> int:

@@ -39,6 +39,36 @@ def test_bad_arguments_are_those_of_the_calls():
     assert lib.qcf_fuse_layer(C.byref(desc), qb._LAYER_BUFFERS.pack(*args), 1, None) == 3      # no workspace
 
 
+class _Buffer:                                         # what the binding asks of a tensor
+    is_cuda = True
+    is_contiguous = staticmethod(lambda: True)
+    numel = staticmethod(lambda: 1 << 30)
+
+    def __init__(self, at):
+        self.data_ptr = lambda: at
+
+
+@pytest.mark.parametrize("critical", [True, False, None, "", "yes", 0.0, 0.5, 2, 1 << 32, np.bool_(True), np.zeros(1), []])
+def test_critical_is_taken_by_its_truth_value(critical, monkeypatch):
+    """As the library is called, a C int that agrees with the buffers handed over."""
+    import ctypes as C
+    seen = []
+
+    class Library:
+        @staticmethod
+        def qcf_fuse_layer(desc, buffers, flag, stream):
+            C.c_int32.from_param(flag)                 # (what the declared argument type accepts)
+            seen.append((C.c_int32(flag).value, qb._LAYER_BUFFERS.unpack(buffers)))
+            return 0
+
+    monkeypatch.setattr(qb, "load_library", lambda: Library)
+    monkeypatch.setattr(qb, "_stream", lambda: 0)
+    t = [_Buffer(16 * (i + 1)) for i in range(23)]
+    qb.qcf_fuse_layer(qb.make_desc(inputs.LayerShape(256, 4, 2, 64, 10000.0, "f32")), critical, 1, 1, 8, 1, 4, *t)
+    (flag, words), = seen
+    assert flag == int(bool(critical)) and (words[5 + 2] != 0) == (words[5 + 9] != 0) == bool(critical)      # probe_off, score
+
+
 OUTS = ("k_fused", "v_fused", "score", "sel_idx", "sel_row", "sel_pos", "q_sel", "k_sel", "v_sel", "o_sel", "lse")
 
 
