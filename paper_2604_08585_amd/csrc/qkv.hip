@@ -661,8 +661,9 @@ __device__ __forceinline__ void rerope_rows(const QkvArgs& a, int64_t r0, int n,
     const int64_t row = (int64_t)a.dst_rows[i] - r0;
     if (row >= 0 && row < n) l.chunk[row] = -1;
   }
-  const int first = l.first, pairs = (l.last - first + 1) * half;         // (disjoint chunks: at most one more than rows)
-  for (int i = tid; i < min(pairs, (kSideRows + 1) * 64); i += NTHR) {
+  // (at most one chunk more than rows where each has a token; rows of what a table of empty chunks has beyond are left as they are)
+  const int first = l.first, pairs = min(l.last - first + 1, kSideRows + 1) * half;
+  for (int i = tid; i < pairs; i += NTHR) {
     const qcf_chunk& ch = l.table[first + i / half];
     const double theta = exp2(a.neg2_over_d_log2base * (double)(i % half));
     double sn, cn;
@@ -684,6 +685,7 @@ __device__ __forceinline__ void rerope_rows(const QkvArgs& a, int64_t r0, int n,
       e0[u] = head * a.D + (s.style == 0 ? p0[u] : 2 * p0[u]);
       e1[u] = e0[u] + (s.style == 0 ? half : 8);
       c[u] = i < items ? l.chunk[at[u]] : -1;
+      if ((c[u] - first) * half >= pairs) c[u] = -1;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)

@@ -211,3 +211,28 @@ def test_rerotation_beside_the_projection(lens, gaps, kw, style):
         res.append([getattr(L, name).clone() for name in OUTS])
     for name, a, b in zip(OUTS, *res):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+
+
+@pytest.mark.gpu
+def test_a_table_of_empty_chunks_beside_the_projection():
+    """Chunks have a token each by the interface.  200 empty ones in front of a row, more than a workgroup keeps pairs for: a row is
+    re-rotated as by the calls one after the other, or left as it was."""
+    print("re-rotation beside the projection, empty chunks", flush=True)
+    L = _layer([48] + [0] * 200 + [8000], [0] * 202, R=4, style=0, dm=1024, N=1500)
+    sel = (torch.arange(1500, device="cuda:0") * 5 + 100).int()
+    for t in (L.sel_idx, L.sel_row, L.sel_pos):
+        t.copy_(sel)
+    k0, v0 = L.k_fused.clone(), L.v_fused.clone()
+    res = []
+    for run in (lambda: [fn(L) for name, fn in pipeline.FUSED_STEPS if name not in ("score", "select")],
+                lambda: pipeline.enqueue_layer(L, critical=False)):
+        L.k_fused.copy_(k0)
+        L.v_fused.copy_(v0)
+        run()
+        torch.cuda.synchronize()
+        res.append([getattr(L, name).clone() for name in OUTS])
+    for old, a, b in zip((k0, v0), *res):
+        same, left = ((b == other).flatten(1).all(1) for other in (a, old))
+        assert bool((same | left).all()) and int((~same).sum()) <= 192
+    for name, a, b in zip(OUTS[6:9], res[0][6:9], res[1][6:9]):
+        assert torch.equal(a, b), name
