@@ -116,10 +116,35 @@ template <> struct Vec16<bf16_t> {
   }
 };
 
-// a rotary pair turned by (cos, sin)
+// ---- re-rotation: what its kernels (rerope.hip, and the joined ones of score.hip and qkv.hip) have to do alike, bit for bit
+// a rotary pair turned by (cos, sin): the second product of each is rounded, the first one is fused
 __device__ __forceinline__ void turn_pair(float a, float b, float2 w, float& oa, float& ob) {
-  oa = a * w.x - b * w.y;
-  ob = b * w.x + a * w.y;
+#pragma clang fp contract(off)
+  oa = __builtin_fmaf(a, w.x, -(b * w.y));
+  ob = __builtin_fmaf(b, w.x, a * w.y);
+}
+// (cos, sin) of pair i at an angle of `positions` (a whole number) times its frequency, 2^(i * neg2_over_d_log2base)
+__device__ __forceinline__ float2 rotary_pair(double positions, double neg2_over_d_log2base, int i) {
+  const double theta = exp2(neg2_over_d_log2base * (double)i);
+  double sn, cn;
+  sincos(positions * theta, &sn, &cn);
+  return make_float2((float)cn, (float)sn);
+}
+__device__ __forceinline__ float2 shift_pair(const qcf_chunk& c, double neg2_over_d_log2base, int i) {
+  return rotary_pair((double)(c.dst_pos0 - c.src_pos0), neg2_over_d_log2base, i);
+}
+// number of the last of n chunks that starts at or before a row (0 if none); dst_row(c): first row of chunk c
+template <typename F>
+__device__ __forceinline__ int chunk_of(int n, int64_t row, F&& dst_row) {
+  int lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (dst_row(mid) <= row) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+__device__ __forceinline__ int chunk_of(const qcf_chunk* table, int n, int64_t row) {
+  return chunk_of(n, row, [&](int c) { return table[c].dst_row; });
 }
 
 // ---- gfx950 helpers shared by the MFMA kernels ---------------------------------------

@@ -97,10 +97,7 @@ struct RopeOut {
   __device__ __forceinline__ int second(int i) const { return style == 0 ? i + D / 2 : 2 * i + 1; }
   __device__ __forceinline__ bool rotated(int head) const { return head < H + Hkv; }
   __device__ __forceinline__ float2 factor(int64_t m, int i) const {
-    const double theta = exp2(neg2_over_d_log2base * (double)i);
-    double sd, cd;
-    sincos((double)pos[m] * theta, &sd, &cd);
-    return make_float2((float)cd, (float)sd);
+    return rotary_pair((double)pos[m], neg2_over_d_log2base, i);
   }
   // head `head` of output row m (null: not wanted) and of its row of the cache (null: none)
   __device__ __forceinline__ T* out(int64_t m, int head) const {
@@ -641,16 +638,8 @@ __device__ __forceinline__ void rerope_rows(const QkvArgs& a, int64_t r0, int n,
   for (int i = tid; i < s.n_chunks * (int)(sizeof(qcf_chunk) / 8); i += NTHR)
     reinterpret_cast<uint64_t*>(l.table)[i] = reinterpret_cast<const uint64_t*>(s.chunks)[i];
   __syncthreads();
-  auto chunk_of = [&](int64_t row) {              // the last that starts at or before the row (0 if none)
-    int lo = 0, hi = s.n_chunks - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (l.table[mid].dst_row <= row) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-  };
   for (int i = tid; i < n; i += NTHR) {
-    const int c = chunk_of(r0 + i);
+    const int c = chunk_of(l.table, s.n_chunks, r0 + i);
     const qcf_chunk& ch = l.table[c];
     l.chunk[i] = r0 + i >= ch.dst_row && r0 + i < ch.dst_row + ch.len ? (int16_t)c : (int16_t)-1;
     if (i == 0) l.first = c;
@@ -664,11 +653,7 @@ __device__ __forceinline__ void rerope_rows(const QkvArgs& a, int64_t r0, int n,
   // (at most one chunk more than rows where each has a token; rows of what a table of empty chunks has beyond are left as they are)
   const int first = l.first, pairs = min(l.last - first + 1, kSideRows + 1) * half;
   for (int i = tid; i < pairs; i += NTHR) {
-    const qcf_chunk& ch = l.table[first + i / half];
-    const double theta = exp2(a.neg2_over_d_log2base * (double)(i % half));
-    double sn, cn;
-    sincos((double)(ch.dst_pos0 - ch.src_pos0) * theta, &sn, &cn);
-    l.cs[i] = make_float2((float)cn, (float)sn);
+    l.cs[i] = shift_pair(l.table[first + i / half], a.neg2_over_d_log2base, i % half);
   }
   __syncthreads();
   const int row_elems = a.Hkv * a.D, per_head = half / 8, slots = a.Hkv * per_head, items = n * slots;

@@ -27,21 +27,12 @@ __global__ void rerope_plan_kernel(const qcf_chunk* __restrict__ chunks, int n_c
   const int half = D / 2;
   if (gid < n_chunks * half) {
     const int c = gid / half, i = gid - c * half;
-    const double theta = exp2(neg2_over_d_log2base * (double)i);
-    const double phi = (double)(chunks[c].dst_pos0 - chunks[c].src_pos0) * theta;
-    double sn, cn;
-    sincos(phi, &sn, &cn);
-    cs[gid] = make_float2((float)cn, (float)sn);
+    cs[gid] = shift_pair(chunks[c], neg2_over_d_log2base, i);
   }
   if (gid < n_blocks) {
     // last chunk whose first row is <= the block's first row (0 if none)
     const int64_t row = row0 + ((int64_t)gid * kThreads) / slots;
-    int lo = 0, hi = n_chunks - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (chunks[mid].dst_row <= row) lo = mid; else hi = mid - 1;
-    }
-    block_chunk[gid] = lo;
+    block_chunk[gid] = chunk_of(chunks, n_chunks, row);
   }
 }
 
@@ -66,25 +57,14 @@ __global__ __launch_bounds__(kThreads) void rerope_fused_kernel(
   const int64_t item0 = row0 * g.slots + (int64_t)blockIdx.x * kThreads;
   const int64_t r_first = item0 / g.slots;
   const int64_t r_last = min(total_rows - 1, (item0 + kThreads - 1) / g.slots);
-  if (tid == 0) {
-    int lo = 0, hi = n_chunks - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (s_row[mid] <= r_first) lo = mid; else hi = mid - 1;
-    }
-    s_first = lo;
-  }
+  if (tid == 0) s_first = chunk_of(n_chunks, r_first, [&](int c) { return s_row[c]; });
   __syncthreads();
   const int c_first = s_first;
   int c_last = c_first;                                  // last chunk that starts at or before the last row
   while (c_last + 1 < n_chunks && s_row[c_last + 1] <= r_last) ++c_last;
   const int n_mine = min(c_last - c_first + 1, kMaxWgPairs / half);   // (the launcher keeps this from truncating)
   for (int e = tid; e < n_mine * half; e += kThreads) {
-    const int c = c_first + e / half, i = e % half;
-    const double theta = exp2(neg2_over_d_log2base * (double)i);
-    double sn, cn;
-    sincos((double)(chunks[c].dst_pos0 - chunks[c].src_pos0) * theta, &sn, &cn);
-    s_cs[e] = make_float2((float)cn, (float)sn);
+    s_cs[e] = shift_pair(chunks[c_first + e / half], neg2_over_d_log2base, e % half);
   }
   __syncthreads();
 

@@ -776,24 +776,6 @@ static_assert(sizeof(qcf_chunk) % 8 == 0, "copied in words of 8 bytes");
 constexpr size_t kFusedRotLds = kFusedLds + sizeof(RotLds);
 static_assert(kFusedRotLds + 1024 <= 160 * 1024, "one workgroup's LDS");
 
-// (cos, sin) of pair i for the shift of a chunk, as qcf_rerope takes it
-__device__ __forceinline__ float2 shift_pair(const qcf_chunk& c, double neg2_over_d_log2base, int i) {
-  const double theta = exp2(neg2_over_d_log2base * (double)i);
-  double sn, cn;
-  sincos((double)(c.dst_pos0 - c.src_pos0) * theta, &sn, &cn);
-  return make_float2((float)cn, (float)sn);
-}
-
-// number of the last chunk that starts at or before a row (0 if none)
-__device__ __forceinline__ int chunk_of(const qcf_chunk* table, int n, int64_t row) {
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (table[mid].dst_row <= row) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
 __device__ __forceinline__ bf16x8 pack8(const float* o) {
   return __builtin_bit_cast(bf16x8, mk4(cvt_pk_bf16(o[0], o[1]), cvt_pk_bf16(o[2], o[3]), cvt_pk_bf16(o[4], o[5]), cvt_pk_bf16(o[6], o[7])));
 }
