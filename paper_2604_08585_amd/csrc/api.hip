@@ -391,7 +391,7 @@ qcf_status qcf_fuse_layer(const qcf_layer_desc* desc, const qcf_layer_buffers* l
   bool empty = false;
   QCF_TRY(check_rerope_args(desc, b.chunks_dev, b.n_chunks, b.total_ctx, b.k_fused, b.v_fused, b.rerope_ws, b.rerope_ws_bytes));
   const bool joined = critical && b.total_ctx > 0 && b.v_fused &&
-                      score_takes_rerope(*desc, b.B, b.n_chunks, b.total_probe, b.total_ctx) &&
+                      scoring::takes_rerope(*desc, b.B, b.n_chunks, b.total_probe, b.total_ctx) &&
                       check_score_args(desc, b.B, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.ctx_off_dev, b.total_ctx,
                                        nullptr, b.score, &empty) == QCF_OK &&
                       need_ws(b.score_ws, b.score_ws_bytes, scoring::workspace(*desc, b.B, b.total_probe, b.total_ctx)) == QCF_OK;

@@ -234,8 +234,7 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
                         int64_t total_probe, const void* k, const int64_t* ctx_off, int64_t total_ctx,
                         const int32_t* probe_limit, float* score, float alpha, float beta, void* ws, hipStream_t st);
 
-// re-rotation and scoring of one request in one launch, where score_takes_rerope (bf16 heads of 128, no probe_limit)
-bool score_takes_rerope(const qcf_layer_desc& L, int32_t B, int32_t n_chunks, int64_t total_probe, int64_t total_ctx);
+// re-rotation and scoring of one request in one launch, where scoring::takes_rerope
 qcf_status launch_rerope_score(const qcf_layer_desc& L, const qcf_chunk* chunks, int32_t n_chunks, const void* q,
                                const int64_t* probe_off, int64_t total_probe, void* k, void* v, const int64_t* ctx_off,
                                int64_t total_ctx, float* score, void* ws, hipStream_t st);

@@ -727,7 +727,6 @@ constexpr uint32_t kSpinLimit = 1u << 20;  // polls (a microsecond or two each) 
 __device__ uint32_t g_sync[kSyncSlots * kSyncWords];
 
 // Re-rotation in front of the scoring (RR): the chunks whose keys and values make up the cache that s.k points to.
-constexpr int kMaxRotChunks = 128;        // chunk table in LDS
 struct Rerotation {
   const qcf_chunk* chunks;
   int n_chunks, style;
@@ -1291,10 +1290,6 @@ qcf_status fused_args(const qcf_layer_desc& L, const ScoreArgs& a, void* ws, Fus
 }
 
 }  // namespace
-
-bool score_takes_rerope(const qcf_layer_desc& L, int32_t B, int32_t n_chunks, int64_t total_probe, int64_t total_ctx) {
-  return B == 1 && n_chunks > 0 && n_chunks <= kMaxRotChunks && use_fused(L, B, total_probe, total_ctx);
-}
 
 qcf_status launch_rerope_score(const qcf_layer_desc& L, const qcf_chunk* chunks, int32_t n_chunks, const void* q,
                                const int64_t* probe_off, int64_t total_probe, void* k, void* v, const int64_t* ctx_off,

@@ -109,6 +109,11 @@ inline bool use_fused(const qcf_layer_desc& L, int32_t B, int64_t total_probe, i
   return total_probe * G <= kRowBlock && tiles * L.n_kv_heads <= compute_unit_count() &&
          1 + (int64_t)B * L.n_kv_heads + tiles <= kSyncWords;
 }
+// Re-rotation in the same launch (no probe_limit): one request whose chunk table the kernel keeps in LDS.
+constexpr int kMaxRotChunks = 128;
+inline bool takes_rerope(const qcf_layer_desc& L, int32_t B, int32_t n_chunks, int64_t total_probe, int64_t total_ctx) {
+  return B == 1 && n_chunks > 0 && n_chunks <= kMaxRotChunks && use_fused(L, B, total_probe, total_ctx);
+}
 struct FusedWs { size_t part, colpart, total; };
 inline FusedWs fused_ws(const qcf_layer_desc& L, int32_t B, int64_t total_ctx) {
   const size_t slots = (size_t)n_tiles_upper(B, total_ctx) * L.n_kv_heads;

@@ -1,4 +1,5 @@
-"""The library's host rules, compiled from their headers for the tests (csrc/attn_layout.h; 256 compute units)."""
+"""The library's host rules, compiled from their headers for the tests (csrc/attn_layout.h, gemm_plan.h and score_layout.h; 256
+compute units)."""
 import ctypes as C
 import functools
 import os
@@ -13,6 +14,8 @@ WIDE = 256
 
 PROGRAM = r"""
 #include "attn_layout.h"
+#include "gemm_plan.h"
+#include "score_layout.h"
 namespace qcf { int compute_unit_count() { return 256; } }
 extern "C" void division(const qcf_layer_desc* L, int B, long long rows, long long tokens, long long* out) {
   const qcf::attn::Division d = qcf::attn::divide(*L, B, rows, tokens);
@@ -25,6 +28,12 @@ extern "C" void attention_workspace(const qcf_layer_desc* L, int B, long long ro
   out[1] = full_workspace(*L, B, rows, tokens);
   const Division d = divide(*L, B, rows, tokens, have);
   out[2] = workspace_of(*L, d); out[3] = d.split.n_seg_max; out[4] = d.split.part_f32;
+}
+extern "C" int takes_rerope(const qcf_layer_desc* L, int B, int n_chunks, long long probes, long long tokens) {
+  return qcf::scoring::takes_rerope(*L, B, n_chunks, probes, tokens);
+}
+extern "C" long long side_rows(const qcf_layer_desc* L, long long rows, int n_chunks, long long tokens, long long workspace) {
+  return qcf::gemm::side_rows(*L, rows, n_chunks, tokens, workspace).all;
 }
 """
 
@@ -55,6 +64,19 @@ def attention_workspace(H, Hkv, D, T, sel, have=0):
     out = (C.c_longlong * 5)()
     _library().attention_workspace(C.byref(desc), len(T), C.c_longlong(sum(sel)), C.c_longlong(sum(T)), C.c_longlong(have), out)
     return tuple(out)
+
+
+def rerotates_in_scoring(L):
+    """Whether a scored pipeline.DeviceLayer is re-rotated by its scoring kernel (csrc/score_layout.h)."""
+    return bool(_library().takes_rerope(C.byref(L.desc), L.B, L.n_chunks, C.c_longlong(L.total_probe), C.c_longlong(L.total_ctx)))
+
+
+def rows_beside_projection(L):
+    """Rows of a layer that is not scored that are re-rotated beside its projection (csrc/gemm_plan.h)."""
+    f = _library().side_rows
+    f.restype = C.c_longlong
+    have = qb.qcf_recompute_qkv_workspace_bytes(L.desc, L.total_sel)
+    return f(C.byref(L.desc), C.c_longlong(L.total_sel), L.n_chunks, C.c_longlong(L.total_ctx), C.c_longlong(have))
 
 
 def wide_workspace(Hkv, blocks, segments):

@@ -2,11 +2,13 @@
 import os
 import re
 import subprocess
+import types
 
 import numpy as np
 import pytest
 import torch
 
+import host_rules
 from oracle import qcf_oracle as orc
 from paper_2604_08585_amd import binding as qb
 from paper_2604_08585_amd import inputs, pipeline
@@ -83,6 +85,9 @@ def test_same_bits_as_the_calls_one_after_the_other(cfg, scale, ratio, critical,
     print(f"layer in one call cfg={cfg} ratio={ratio} critical={critical}", flush=True)
     L = pipeline.upload(inputs.make_config(cfg, orc.PlantOps(), scale=scale) if cfg else inputs.make_config(cfg, orc.PlantOps()),
                         torch.device("cuda:0"), ratio=ratio)
+    # (the scored layers of one bf16 request, and the one that is not scored and leaves compute units idle)
+    assert host_rules.rerotates_in_scoring(L) == (cfg in (1, 2)) and host_rules.rows_beside_projection(L) == {
+        (1, 1.0): L.total_ctx, (2, 0.15): L.total_ctx}.get((cfg, ratio), 0)
     if not workspaces:
         L.ws_rerope = L.ws_score = L.ws_select = L.ws_qkv = L.ws_attn = None
 
@@ -105,6 +110,11 @@ def test_same_bits_as_the_calls_one_after_the_other(cfg, scale, ratio, critical,
     for _ in range(2):
         for name, a, b in zip(OUTS, outputs(lambda: pipeline.enqueue_layer(L, critical)), want):
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+
+
+@pytest.mark.gpu
+def test_the_rules_are_asked_for_this_chip():
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256      # (as tests/host_rules.py has it)
 
 
 def _layer(lens, gaps, R, style, H=8, Hkv=2, dm=256, before=0, behind=0, src0=0, probes=True, seed=0, D=128,
@@ -158,6 +168,7 @@ def test_rerotation_inside_the_scoring(lens, gaps, kw, style):
     print(f"joined re-rotation {kw} style={style}", flush=True)
     kw = dict(dict(R=24), **kw)
     L = _layer(lens, gaps, style=style, **kw)
+    assert host_rules.rerotates_in_scoring(L) == (L.n_chunks <= 128)
     L.chunk_tensors[0][0].view(torch.int16)[0, 0, :4] = torch.tensor([0x7f81, -1, 0x7f80, -128], dtype=torch.int16)
     # (NaN of two kinds and both infinities in the first key row)
     k0, v0 = L.k_fused.clone(), L.v_fused.clone()
@@ -190,6 +201,7 @@ def test_rerotation_beside_the_projection(lens, gaps, kw, style):
     print(f"re-rotation beside the projection {kw} style={style}", flush=True)
     L = _layer(lens, gaps, R=4, style=style, **kw)
     N, total = L.total_sel, L.total_ctx
+    assert host_rules.rows_beside_projection(L) == (0 if L.n_chunks > 256 else 1984 if total == 8192 else total)
     g = torch.Generator(device="cuda:0").manual_seed(8)
     sel = torch.randperm(total, generator=g, device="cuda:0")[:N].sort()[0].int()
     row = sel.clone()
@@ -219,6 +231,7 @@ def test_a_table_of_empty_chunks_beside_the_projection():
     re-rotated as by the calls one after the other, or left as it was."""
     print("re-rotation beside the projection, empty chunks", flush=True)
     L = _layer([48] + [0] * 200 + [8000], [0] * 202, R=4, style=0, dm=1024, N=1500)
+    assert host_rules.rows_beside_projection(L) == L.total_ctx
     sel = (torch.arange(1500, device="cuda:0") * 5 + 100).int()
     for t in (L.sel_idx, L.sel_row, L.sel_pos):
         t.copy_(sel)
@@ -236,3 +249,20 @@ def test_a_table_of_empty_chunks_beside_the_projection():
         assert bool((same | left).all()) and int((~same).sum()) <= 192
     for name, a, b in zip(OUTS[6:9], res[0][6:9], res[1][6:9]):
         assert torch.equal(a, b), name
+
+
+def _sizes(B, n_chunks, R, T, N, H=32, Hkv=8, D=128, dm=4096, dtype="bf16"):
+    desc = qb.make_desc(inputs.LayerShape(dm, H, Hkv, D, 500000.0, dtype))
+    return types.SimpleNamespace(desc=desc, B=B, n_chunks=n_chunks, total_probe=R, total_ctx=T, total_sel=N)
+
+
+def test_which_layers_are_joined():
+    """By chunks, requests, probe rows of a group, tokens, head size and type; by the compute units that the projection leaves."""
+    scored = lambda *a, **k: host_rules.rerotates_in_scoring(_sizes(*a, **k))
+    assert scored(1, 16, 80, 8192, 1229) and scored(1, 128, 80, 731, 110)
+    assert not any([scored(1, 129, 80, 731, 110), scored(2, 16, 80, 8192, 1229), scored(1, 16, 81, 8192, 1229), scored(1, 16, 0, 8192, 1229),
+                    scored(1, 16, 80, 8193, 1229), scored(1, 16, 40, 4096, 615, D=64), scored(1, 4, 20, 512, 77, dtype="f32")])
+    beside = lambda *a, **k: host_rules.rows_beside_projection(_sizes(*a, **k))
+    assert beside(1, 3, 24, 731, 110) == 731 and beside(1, 16, 80, 8192, 410) == 8192 and beside(16, 256, 80, 8192, 410) == 8192
+    assert 0 < beside(1, 16, 80, 8192, 1229) < 8192
+    assert not any([beside(1, 257, 80, 8192, 410), beside(1, 16, 80, 8192, 1500), beside(1, 4, 20, 512, 77, dtype="f32")])
