@@ -69,8 +69,11 @@ struct SelectLds {
 // One request: T scores, N of them to select (0 < N <= T), written from sel_*[o0] on.  Wave w has the keys from w * 64 * seg
 // on, in rows of 64 (seg == 1) or 256 (seg a multiple of four: 4 to a lane), so that loads are whole lines.
 // SEG > 0: each thread keeps up to SEG keys in registers.  SEG == 0: keys are re-read in every pass (any length).
-template <int SEG>
-__device__ __forceinline__ void select_request(SelectLds& lds, const float* __restrict__ s, int64_t c0, int T, int N, int seg,
+// WHOLE: no wave lacks a row (or there is one key to a thread).  Otherwise rows that are not there are passed over: taken for keys
+// of 0 they cost time and, where the keys' range reaches down to 0 (scores of both signs), crowd one bin: 20000 keys of a normal
+// distribution 27.0 us, 14.0 so, 1300 9.0 and 6.8; all equal 13.5 and 10.0.  (The branches cost 2 to 4 % where no row is missing.)
+template <int SEG, bool WHOLE>
+__device__ __forceinline__ void select_rows(SelectLds& lds, const float* __restrict__ s, int64_t c0, int T, int N, int seg,
                                                int64_t o0, int base_pos, int32_t* __restrict__ sel_idx,
                                                int32_t* __restrict__ sel_row, int32_t* __restrict__ sel_pos) {
   constexpr int C = SEG == 1 ? 1 : 4, kRows = SEG / C;
@@ -104,8 +107,9 @@ __device__ __forceinline__ void select_request(SelectLds& lds, const float* __re
       for (int c = 0; c < C; ++c) bits[c] = 0u;
     }
   };
-  // A key that is not there is 0, what no score but one NaN maps to, and so never among the N < T largest unless that NaN is.
-  const bool full = rows_full == (SEG > 0 ? kRows : seg / C);    // (of the whole wave)
+  // A key of the last row that is not there is 0, what no score but one NaN maps to, and so never among the N < T largest unless
+  // that NaN is.
+  const bool full = rows_full == (WHOLE && SEG > 0 ? kRows : rows);      // (of the whole wave)
   uint32_t keys[SEG > 0 ? kRows : 1][C];
   uint32_t lo = 0xffffffffu, hi = 0u;                            // range of the keys
   auto order_row = [&](int q, uint32_t (&key)[C]) {
@@ -128,17 +132,20 @@ __device__ __forceinline__ void select_request(SelectLds& lds, const float* __re
     for (int q = 0; q < kRows; ++q) load_row(q, keys[q]);
     if (full) {
 #pragma unroll
-      for (int q = 0; q < kRows; ++q) { order_row(q, keys[q]); range_row(q, keys[q]); }
+      for (int q = 0; q < kRows; ++q)
+        if (WHOLE || q < rows) { order_row(q, keys[q]); range_row(q, keys[q]); }
     } else {
 #pragma unroll
-      for (int q = 0; q < kRows; ++q) { order_row(q, keys[q]); range_row(q, keys[q]); }
+      for (int q = 0; q < kRows; ++q)
+        if (WHOLE || q < rows) { order_row(q, keys[q]); range_row(q, keys[q]); }
     }
   }
   // f(q, key[C]), row by row
   auto walk = [&](auto&& f) {
     if constexpr (SEG > 0) {
 #pragma unroll
-      for (int q = 0; q < kRows; ++q) f(q, keys[q]);
+      for (int q = 0; q < kRows; ++q)
+        if (WHOLE || q < rows) f(q, keys[q]);
     } else {
       for (int q = 0; q < rows; ++q) {
         load_row(q, keys[0]);
@@ -324,8 +331,20 @@ __device__ __forceinline__ void select_request(SelectLds& lds, const float* __re
   }
 }
 
+template <int SEG>
+__device__ __forceinline__ void select_request(SelectLds& lds, const float* __restrict__ s, int64_t c0, int T, int N, int seg,
+                                               int64_t o0, int base_pos, int32_t* __restrict__ sel_idx,
+                                               int32_t* __restrict__ sel_row, int32_t* __restrict__ sel_pos) {
+  if constexpr (SEG == 1)
+    select_rows<1, true>(lds, s, c0, T, N, seg, o0, base_pos, sel_idx, sel_row, sel_pos);
+  else if (SEG > 0 && seg == SEG && T > SEG * kThreads - 256)
+    select_rows<SEG, true>(lds, s, c0, T, N, seg, o0, base_pos, sel_idx, sel_row, sel_pos);
+  else
+    select_rows<SEG, false>(lds, s, c0, T, N, seg, o0, base_pos, sel_idx, sel_row, sel_pos);
+}
+
 // Keys per thread follow the length of each request: a batch of requests whose total exceeds what registers hold does not
-// re-read every key in every pass (sixteen requests of 2K-16K tokens: 56 -> 16 us).  MAX: the most keys per thread that
+// re-read every key in every pass (sixteen requests of 2K-16K tokens, 15 % selected: 23.2 us so, 12.0 now).  MAX: the most keys per thread that
 // registers are kept for (they are allocated for the kernel as a whole); 0: and any longer request.
 template <int MAX>
 __global__ __launch_bounds__(kThreads) void select_kernel(
@@ -415,7 +434,7 @@ qcf_status launch_select(int32_t B, const float* score, const int64_t* ctx_off, 
 #define QCF_LAUNCH(MAX) \
   select_kernel<MAX><<<grid, block, 0, st>>>(score, ctx_off, total_ctx, sel_off, total_sel, ctx_pos0, sel_idx, sel_row, sel_pos)
   // A request is never longer than total_ctx.  Up to eight keys per thread the instance of the total serves every request
-  // (8192 tokens: 11.1 us, with the choice by length inside one kernel 11.5).
+  // (with the choice by length inside one kernel: 731 tokens 4.2 us both ways, 5000 6.3 so and 6.5, 8192 6.8 and 6.7).
   if (total_ctx <= kThreads) QCF_LAUNCH(1);
   else if (total_ctx <= 4 * kThreads) QCF_LAUNCH(4);
   else if (total_ctx <= 8 * kThreads) QCF_LAUNCH(8);

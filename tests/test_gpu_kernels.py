@@ -650,6 +650,20 @@ def test_select_crowded_bins_and_extreme_keys(T):
             assert all(np.array_equal(x.cpu().numpy(), want) for x in (idx, row, pos)), (T, n)
 
 
+@pytest.mark.parametrize("T", [3840, 3841, 7936, 7937, 16128, 16129, 20000, 32512, 32513])
+def test_select_rows_that_are_not_there(T):
+    """The edges between requests in which every wave has all its rows and those in which some lack one: keys of both signs, all equal,
+    and the extremes of above."""
+    say(f"select rows {T}")
+    test_select_crowded_bins_and_extreme_keys(T)
+    n = int(0.15 * T)
+    for s in (torch.randn(T, generator=gen(64), device=DEV), torch.zeros(T, device=DEV)):
+        out = [torch.full((n,), -7, dtype=torch.int32, device=DEV) for _ in range(3)]
+        qb.qcf_select(1, s, i64([0, T]), T, i64([0, n]), n, None, *out)
+        ref = torch.sort(torch.sort(s, descending=True, stable=True)[1][:n])[0].int()
+        assert all(torch.equal(x, ref) for x in out)
+
+
 def test_select_of_many_outputs_reads_the_scores_once_more():
     """A million keys: half of them selected takes no more passes over the keys than 8192, only more stores.  (With a pass per 8192
     outputs 18 times as long; the line is far from that and from 1.)"""
