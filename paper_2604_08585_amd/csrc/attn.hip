@@ -32,12 +32,20 @@ namespace {
 
 // ------------------------------------------------------------------ generic path
 
-// A tile of 256 tokens: the keys (a token to a thread) and the first 16 values of each thread (four elements of every
-// kSlices-th token) are requested together, so that a tile waits for memory once.  (Requested a tile ahead they take all registers
-// and more moves: 15.0 us for the case below.)
-template <typename T, int D>
+// A tile of 256 tokens: keys a token to a thread, values four elements of every kSlices-th token to a thread, kBatch vectors of
+// either on their way.  kBatch 16: the keys and the first 16 values are requested together, so that a tile waits for memory once.
+// (Requested a tile ahead they take all registers and more moves: 15.0 us for the case above.)  Launches of kManyWgs workgroups to a
+// compute unit hide the waits behind each other and lose by the registers (170, heads of 128): kBatch 8, values behind the
+// keys, waves without a token of the last tile pass it over.  The sums and their order are the same.  us, 16 and 8: f32, 32 / 8 heads
+// of 128, 150 rows over 1000 tokens 222 and 190, 307 over 2048 960 and 790; 16 / 8 heads of 64, 300 over 1000 122 and 98; bf16,
+// 12 / 4 heads of 128, 300 over 512 69 and 61.  The other side of the line: f32, 4 / 2 heads of 64, 80 rows over 2048 33 and 37;
+// bf16, 12 / 4 heads of 128, 77 over 512 22.1 and 23.3.  bf16 heads of 64 (130 registers): 614 rows over 4096 356 and 400, 300
+// over 512 36.3 and 38.0.
+constexpr int kManyWgs = 5;
+template <typename T, int D, int kBatch>
 __global__ __launch_bounds__(256) void attn_generic(AttnArgs a) {
-  constexpr int kQuads = D / 4, kSlices = 256 / kQuads, kVals = 256 / kSlices, kBatch = 16;
+  constexpr int kQuads = D / 4, kSlices = 256 / kQuads, kVals = 256 / kSlices;
+  constexpr bool kTogether = kBatch == 16;
   __shared__ __align__(16) float sq[D];
   __shared__ float sp[256];
   __shared__ __align__(16) float sacc[kSlices * D];
@@ -75,18 +83,20 @@ __global__ __launch_bounds__(256) void attn_generic(AttnArgs a) {
       for (int u = 0; u < kBatch; ++u) Quad<T>::load(vt + (int64_t)min(slice + (u0 + u) * kSlices, n - 1) * kv_stride, vf[u]);
     };
     float s = 0.f;
+    if (kTogether || 64 * __builtin_amdgcn_readfirstlane(wave) < n) {
 #pragma unroll
-    for (int c = 0; c < kQuads; c += kBatch) {
+      for (int c = 0; c < kQuads; c += kBatch) {
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) Quad<T>::load(kr + 4 * (c + u), kf[u]);
-      if (c + kBatch == kQuads) load_values(0);
+        for (int u = 0; u < kBatch; ++u) Quad<T>::load(kr + 4 * (c + u), kf[u]);
+        if (kTogether && c + kBatch == kQuads) load_values(0);
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const float4 w = *reinterpret_cast<const float4*>(sq + 4 * (c + u));
-        s += w.x * kf[u][0];
-        s += w.y * kf[u][1];
-        s += w.z * kf[u][2];
-        s += w.w * kf[u][3];
+        for (int u = 0; u < kBatch; ++u) {
+          const float4 w = *reinterpret_cast<const float4*>(sq + 4 * (c + u));
+          s += w.x * kf[u][0];
+          s += w.y * kf[u][1];
+          s += w.z * kf[u][2];
+          s += w.w * kf[u][3];
+        }
       }
     }
     if (tid >= n) s = -INFINITY;
@@ -110,7 +120,7 @@ __global__ __launch_bounds__(256) void attn_generic(AttnArgs a) {
 #pragma unroll
     for (int u0 = 0; u0 < kVals; u0 += kBatch) {
       if (slice + u0 * kSlices >= n) break;
-      if (u0 > 0) load_values(u0);
+      if (!kTogether || u0 > 0) load_values(u0);
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         const int jj = slice + (u0 + u) * kSlices;
@@ -882,13 +892,18 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
   }
   if (total_sel * a.H > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "attn: grid too large");
   const dim3 grid((unsigned)(total_sel * a.H)), block(256);
+  const bool many = total_sel * a.H >= (int64_t)kManyWgs * compute_unit_count();
+#define QCF_GENERIC(T, DIM, BATCH) attn_generic<T, DIM, BATCH><<<grid, block, 0, st>>>(a)
   if (L.dtype == QCF_DTYPE_BF16) {
-    if (a.D == 64) attn_generic<bf16_t, 64><<<grid, block, 0, st>>>(a);
-    else attn_generic<bf16_t, 128><<<grid, block, 0, st>>>(a);
+    if (a.D == 64) QCF_GENERIC(bf16_t, 64, 16);
+    else if (many) QCF_GENERIC(bf16_t, 128, 8);
+    else QCF_GENERIC(bf16_t, 128, 16);
+  } else if (a.D == 64) {
+    if (many) QCF_GENERIC(float, 64, 8); else QCF_GENERIC(float, 64, 16);
   } else {
-    if (a.D == 64) attn_generic<float, 64><<<grid, block, 0, st>>>(a);
-    else attn_generic<float, 128><<<grid, block, 0, st>>>(a);
+    if (many) QCF_GENERIC(float, 128, 8); else QCF_GENERIC(float, 128, 16);
   }
+#undef QCF_GENERIC
   return check_launch("attn");
 }
 

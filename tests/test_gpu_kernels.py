@@ -573,6 +573,32 @@ def test_f32_attention_general(D, T, n):
     assert float((lse.double() - rl).abs().max()) < 1e-5
 
 
+@pytest.mark.parametrize("dtype,H,Hkv,D", [("f32", 8, 2, 64), ("f32", 8, 4, 128), ("bf16", 12, 4, 128), ("bf16", 12, 4, 64)])
+@pytest.mark.parametrize("T", [1, 65, 257, 600])
+def test_generic_attention_of_many_rows(dtype, H, Hkv, D, T):
+    """Launches of many workgroups take another instance with the same sums in the same order: a row's bits are those of a launch of
+    few, which the tests above compare with float64."""
+    say(f"generic attention of many rows {dtype} D={D} T={T}")
+    g, dt, n = gen(65), inputs.torch_dtype(dtype), 200
+    q = torch.randn((n, H, D), generator=g, device=DEV).to(dt)
+    k, v = (torch.randn((T, Hkv, D), generator=g, device=DEV).to(dt) for _ in range(2))
+    pos = torch.randint(-1, T, (n,), generator=g, device=DEV).int()
+    desc = qb.make_desc(inputs.LayerShape(256, H, Hkv, D, 10000.0, dtype))
+
+    def attend(rows):
+        o, lse = torch.full((rows, H, D), 7.0, device=DEV, dtype=dt), torch.full((rows, H), 7.0, device=DEV)
+        qb.qcf_recompute_attn(desc, 1, q, pos, i64([0, rows]), rows, k, v, i64([0, T]), T, None, o, lse)
+        return o, lse
+
+    (many, many_lse), (few, few_lse) = attend(n), attend(20)
+    torch.cuda.synchronize()
+    assert torch.equal(many[:20], few) and torch.equal(many_lse[:20], few_lse)
+    ro, rl = _attention64(q, k, v, pos, D ** -0.5)
+    see = pos >= 0
+    assert float((many.double() - ro)[see].abs().max()) < (1e-5 if dtype == "f32" else 2e-2) and bool((many[~see] == 0).all())
+    assert float((many_lse.double() - rl)[see].abs().max()) < 1e-5
+
+
 @pytest.mark.parametrize("lens", [[300], [1, 1021], [4094], [5000, 3190], [1, 1024, 1025, 3], [4096, 4097, 8192, 8193, 16384], [16385, 7, 32768], [32769, 1023, 40001]])
 def test_select_keys_per_thread(lens):
     """Every number of keys per thread, requests that start at any alignment, ties: exactly the N largest, ties to the
