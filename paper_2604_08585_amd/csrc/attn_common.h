@@ -43,6 +43,7 @@ struct AttnArgs {
   float* part_lse;       // [unit][rows of a workgroup] log2-domain log-sum-exp of each partial (-inf: no visible key); d = 64: pairs of
                          // reference point (log2 units) and denominator against it
   int32_t* units;        // units[0] = number of work units, then (row block << 8 | segment), longest first (null: no plan)
+  int seg_major;         // without a plan, > 0: row blocks whose segments of one number follow each other (one request: all with rows)
   int own_order;         // without a plan, 1: every workgroup finds its unit in that order itself (ordered_unit)
   int32_t* blk_tiles;    // [row block] key tiles of the block, written by the plan kernel for the merge kernel (null: no plan)
 };
