@@ -74,15 +74,19 @@ __device__ __forceinline__ float half_wave_sum(float x) {
 // kKeptLogits tokens the row's logits and exponentials stay in LDS; through the workspace every step waits for the stores of
 // the one before.  Both kernels of a call, us, with one thread to a token and the row in the workspace, and so: 20 rows x 8 heads of
 // 64 over 512 tokens 12.8 and 10.1, over 2000 25.9 and 15.9; 80 rows x 8 heads of 128 over 1000 tokens 63.5 and 38.6.
-constexpr int kRowThreads = 512, kRowWaves = kRowThreads / 64;
+// THREADS: 512, of which a row of few tokens leaves most idle; several requests of 512 tokens or less on average take 256 (the
+// whole call, us, 512 and 256: 200 requests of 64 tokens, 20 rows x 4 heads of 64, 260 and 143, 50 of 100 32.5 and 23.4, 16
+// of 512 17.4 and 16.3; the other side of the line: 8 of 1000 16.2 and 17.2, one of 512 7.7 and 8.6).
 constexpr int kRowLoads = 8;
 constexpr int kKeptLogits = 2048;
+constexpr int kShortTokens = 512;
 
-template <typename T, int D>
-__global__ __launch_bounds__(kRowThreads) void score_rows_generic(
+template <typename T, int D, int THREADS>
+__global__ __launch_bounds__(THREADS) void score_rows_generic(
     const T* __restrict__ q, const int64_t* __restrict__ probe_off, int64_t /*total_probe*/,
     const T* __restrict__ k, const int64_t* __restrict__ ctx_off, int64_t total_ctx, int B,
     const int32_t* __restrict__ probe_limit, int H, int Hkv, float* __restrict__ P) {
+  constexpr int kRowThreads = THREADS, kRowWaves = kRowThreads / 64;
   constexpr int kLanes = D / 4, kTokens = 64 / kLanes;           // lanes of a token, tokens of a load
   static_assert(D == 64 || D == 128, "a row of 16 lanes, or two");
   __shared__ float red[2][kRowWaves];
@@ -1317,16 +1321,19 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
     if (total_probe * H > 0x7fffffff || col_blocks > 0x7fffffff)
       return fail(QCF_ERR_UNSUPPORTED, "score: too many rows");
     if (total_probe > 0) {
-      const dim3 grid((unsigned)(total_probe * H)), block(kRowThreads);
-#define QCF_ROWS(T, DIM)                                                                                             \
-  score_rows_generic<T, DIM><<<grid, block, 0, st>>>(static_cast<const T*>(q), probe_off, total_probe, static_cast<const T*>(k), \
-                                                     ctx_off, total_ctx, B, probe_limit, H, Hkv, P)
+      const dim3 grid((unsigned)(total_probe * H));
+      const bool few = B > 1 && total_ctx <= (int64_t)kShortTokens * B;
+#define QCF_ROWS_OF(T, DIM, THREADS)                                                                                  \
+  score_rows_generic<T, DIM, THREADS><<<grid, dim3(THREADS), 0, st>>>(static_cast<const T*>(q), probe_off, total_probe, \
+                                                                      static_cast<const T*>(k), ctx_off, total_ctx, B, probe_limit, H, Hkv, P)
+#define QCF_ROWS(T, DIM) { if (few) QCF_ROWS_OF(T, DIM, 256); else QCF_ROWS_OF(T, DIM, 512); }
       if (L.dtype == QCF_DTYPE_BF16) {
-        if (D == 64) QCF_ROWS(bf16_t, 64); else QCF_ROWS(bf16_t, 128);
+        if (D == 64) QCF_ROWS(bf16_t, 64) else QCF_ROWS(bf16_t, 128)
       } else {
-        if (D == 64) QCF_ROWS(float, 64); else QCF_ROWS(float, 128);
+        if (D == 64) QCF_ROWS(float, 64) else QCF_ROWS(float, 128)
       }
 #undef QCF_ROWS
+#undef QCF_ROWS_OF
       QCF_TRY_LAUNCH("score rows");
     }
     score_colmean_generic<<<dim3((unsigned)col_blocks), dim3(64 * kColWaves), 0, st>>>(P, probe_off, total_probe, ctx_off,

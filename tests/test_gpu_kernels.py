@@ -649,6 +649,32 @@ def test_f32_scoring_rows(D, T, R):
         assert bool(((out.double().cpu() - ref).abs() <= bound * ref).all()), float(((out.double().cpu() - ref).abs() / ref.clamp_min(1e-30)).max())
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("T,R", [
+    ([1, 300, 64, 0, 513, 30, 2100], [3, 1, 20, 2, 5, 0, 2]),        # 430 tokens on average: fewer threads to a row; one row in the workspace
+    ([64] * 9, [4] * 9), ([600, 425], [3, 2])])                     # 512.5: as a single request
+def test_f32_scoring_of_several_requests(D, T, R):
+    """Bounds as above, of the longest request."""
+    say(f"f32 scoring D={D} of {T} tokens")
+    g, H, Hkv, B = gen(66), 4, 2, len(T)
+    q, k = torch.randn((sum(R), H, D), generator=g, device=DEV), torch.randn((sum(T), Hkv, D), generator=g, device=DEV)
+    off = lambda n: [0] + list(np.cumsum(n))
+    po, co = off(R), off(T)
+    out = torch.full((sum(T),), 7.0, device=DEV)
+    desc = qb.make_desc(inputs.LayerShape(256, H, Hkv, D, 10000.0, "f32"))
+    qb.qcf_score(desc, B, q, i64(po), sum(R), k, i64(co), sum(T), None, out)
+    torch.cuda.synchronize()
+    for b in range(B):
+        qq, kk = q[po[b]:po[b + 1]].double().cpu(), k[co[b]:co[b + 1]].double().cpu().repeat_interleave(H // Hkv, 1)
+        got = out[co[b]:co[b + 1]].double().cpu()
+        if not R[b] or not T[b]:
+            assert bool((got == 0).all())
+            continue
+        ref = torch.softmax(torch.einsum("rhd,thd->rht", qq, kk) * D ** -0.5, -1).mean((0, 1))
+        size = float(torch.einsum("rhd,thd->rht", qq.abs(), kk.abs()).max()) * D ** -0.5
+        assert bool(((got - ref).abs() <= 2.0 ** -24 * (2 * (D + 4) * size + T[b] + R[b] * H + 64) * ref).all()), b
+
+
 @pytest.mark.parametrize("T", [127, 129, 1000, 1025, 3001, 9001, 40001])
 def test_select_crowded_bins_and_extreme_keys(T):
     """Keys that crowd one bin, the whole range of 32 bits, the NaN of the lowest key, more outputs than leave together:
