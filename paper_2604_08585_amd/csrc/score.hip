@@ -768,6 +768,7 @@ constexpr size_t kFusedLds = kQBytes<128> + kKBytes<128>;
 // Re-rotation of a tile (RR): the chunk table, each row's chunk, and the (cos, sin) pairs of the tile's chunks, behind the
 // staged rows.
 constexpr int kRotChunks = 8;                     // chunks whose pairs are kept at a time
+static_assert(kRotChunksPerTile == 2 * kRotChunks, "two fillings to a tile, on average");
 struct RotLds {
   qcf_chunk table[kMaxRotChunks];
   const char* k[kTokPerWg];                       // source of a row, for this KV head (row of no chunk: itself)

@@ -109,10 +109,14 @@ inline bool use_fused(const qcf_layer_desc& L, int32_t B, int64_t total_probe, i
   return total_probe * G <= kRowBlock && tiles * L.n_kv_heads <= compute_unit_count() &&
          1 + (int64_t)B * L.n_kv_heads + tiles <= kSyncWords;
 }
-// Re-rotation in the same launch (no probe_limit): one request whose chunk table the kernel keeps in LDS.
-constexpr int kMaxRotChunks = 128;
+// Re-rotation in the same launch (no probe_limit): one request whose chunk table the kernel keeps in LDS, and no more than two fillings
+// of its (cos, sin) pairs to a tile on average.  Critical layers of 8B shape, us, re-rotation as a launch and so: 731 tokens
+// in 16 chunks (5.6 to a tile) 57.2 and 55.0, 45 (15.8) 57.4 and 57.8, 128 (45) 57.3 and 60.9; 300 in 16 (13.7) 52.9 and 51.6, 30 (26)
+// 53.4 and 54.6; 2000 in 128 (16.4) 68.3 and 66.6.
+constexpr int kMaxRotChunks = 128, kRotChunksPerTile = 16;
 inline bool takes_rerope(const qcf_layer_desc& L, int32_t B, int32_t n_chunks, int64_t total_probe, int64_t total_ctx) {
-  return B == 1 && n_chunks > 0 && n_chunks <= kMaxRotChunks && use_fused(L, B, total_probe, total_ctx);
+  return B == 1 && n_chunks > 0 && n_chunks <= kMaxRotChunks && n_chunks * (int64_t)kTokPerWg <= kRotChunksPerTile * total_ctx + kTokPerWg &&
+         use_fused(L, B, total_probe, total_ctx);
 }
 struct FusedWs { size_t part, colpart, total; };
 inline FusedWs fused_ws(const qcf_layer_desc& L, int32_t B, int64_t total_ctx) {

@@ -156,19 +156,20 @@ def _layer(lens, gaps, R, style, H=8, Hkv=2, dm=256, before=0, behind=0, src0=0,
 @pytest.mark.parametrize("style", [0, 1])
 @pytest.mark.parametrize("lens,gaps,kw", [
     ([300, 212], [0, 0], {}),                                    # a chunk that ends inside a tile
-    ([1] * 127 + [200], [0] * 128, {}),                          # more chunks to a tile than pairs are kept for
+    ([1] * 127 + [200], [0] * 128, {}),                          # more chunks to a tile than it pays for: in two launches
+    ([1] * 127 + [2000], [0] * 128, {}),                         # more in the first tile than pairs are kept for
     ([1] * 128 + [200], [0] * 129, {}),                          # more chunks than the table holds: in two launches
     ([17, 5, 256, 90], [3, 0, 40, 300], {}),                     # rows that no chunk covers, a tile without any
     ([100, 600], [0, 0], dict(before=130, behind=77)),           # cache rows outside the request
     ([257], [0], dict(R=80, H=16, Hkv=4, src0=9)),               # every row of probes, one token in the last tile
     ([1], [0], dict(R=1)),
     ([90, 80], [0, 0], dict(probes=False))],                     # the request has no probe rows
-    ids=["two", "128 chunks", "129 chunks", "gaps", "outside", "edges", "one", "no probes"])
+    ids=["two", "128 chunks", "128 chunks, long", "129 chunks", "gaps", "outside", "edges", "one", "no probes"])
 def test_rerotation_inside_the_scoring(lens, gaps, kw, style):
     print(f"joined re-rotation {kw} style={style}", flush=True)
     kw = dict(dict(R=24), **kw)
     L = _layer(lens, gaps, style=style, **kw)
-    assert host_rules.rerotates_in_scoring(L) == (L.n_chunks <= 128)
+    assert host_rules.rerotates_in_scoring(L) == (L.n_chunks < 128 or L.total_ctx == 2127)
     L.chunk_tensors[0][0].view(torch.int16)[0, 0, :4] = torch.tensor([0x7f81, -1, 0x7f80, -128], dtype=torch.int16)
     # (NaN of two kinds and both infinities in the first key row)
     k0, v0 = L.k_fused.clone(), L.v_fused.clone()
@@ -257,10 +258,11 @@ def _sizes(B, n_chunks, R, T, N, H=32, Hkv=8, D=128, dm=4096, dtype="bf16"):
 
 
 def test_which_layers_are_joined():
-    """By chunks, requests, probe rows of a group, tokens, head size and type; by the compute units that the projection leaves."""
+    """By chunks, tokens to a chunk, requests, probe rows of a group, tokens, head size and type; by the compute units that the
+    projection leaves."""
     scored = lambda *a, **k: host_rules.rerotates_in_scoring(_sizes(*a, **k))
-    assert scored(1, 16, 80, 8192, 1229) and scored(1, 128, 80, 731, 110)
-    assert not any([scored(1, 129, 80, 731, 110), scored(2, 16, 80, 8192, 1229), scored(1, 16, 81, 8192, 1229), scored(1, 16, 0, 8192, 1229),
+    assert scored(1, 16, 80, 8192, 1229) and scored(1, 128, 80, 2032, 305) and scored(1, 45, 24, 731, 110) and scored(1, 1, 24, 1, 1)
+    assert not any([scored(1, 129, 80, 8192, 1229), scored(1, 128, 80, 2031, 305), scored(1, 47, 24, 731, 110), scored(2, 16, 80, 8192, 1229), scored(1, 16, 81, 8192, 1229), scored(1, 16, 0, 8192, 1229),
                     scored(1, 16, 80, 8193, 1229), scored(1, 16, 40, 4096, 615, D=64), scored(1, 4, 20, 512, 77, dtype="f32")])
     beside = lambda *a, **k: host_rules.rows_beside_projection(_sizes(*a, **k))
     assert beside(1, 3, 24, 731, 110) == 731 and beside(1, 16, 80, 8192, 410) == 8192 and beside(16, 256, 80, 8192, 410) == 8192
