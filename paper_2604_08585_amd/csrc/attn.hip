@@ -200,11 +200,11 @@ __global__ __launch_bounds__(256, AttnTile<D>::WGS) void attn_mfma_kernel(AttnAr
 
   // consecutive workgroup ids land on different XCDs: give each XCD its own KV heads so that a
   // head's keys and values stay in one L2; later row blocks (longer key ranges) are scheduled first
-  // Launches without a plan take the row blocks from the last (longest key range) to the first; one request first the top segments of
-  // all of them (seg_major): the segments that a block does not have, and that end at once, then come last and not among the
-  // first 256, one to a compute unit.  The block that the bound has too many stays behind them: between them its units, which
-  // end at once, fall on the same compute units again and again (16 rows over 16384 tokens: 31.1 us, 26.6 so; heads of 64 37.9, 31.8).  Of several
-  // requests the blocks that hold no rows are the last ones and go in front.  The others
+  // Launches without a plan take the row blocks from the last (longest key range) to the first; one request first the top
+  // segments of all of them (seg_major): the segments that a block does not have, and that end at once, then come last and not
+  // among the first 256, one to a compute unit.  The block that the bound has too many stays behind them: between them its
+  // units, which end at once, fall on the same compute units again and again (16 rows over 16384 tokens: 31.1 us, 26.6 so; heads
+  // of 64 37.9, 31.8).  Of several requests the blocks that hold no rows are the last ones and go in front.  The others
   // read the unit list attn_plan_kernel sorted by length, or find their place in it themselves; segments are counted from the top of
   // a block's key range, so a block's remainder segment is the one at the start of the context.
   const int g = (int)(blockIdx.x % a.Hkv);

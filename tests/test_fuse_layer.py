@@ -252,6 +252,41 @@ def test_a_table_of_empty_chunks_beside_the_projection():
         assert torch.equal(a, b), name
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("critical", [True, False])
+def test_joined_layers_replay_from_a_captured_graph(critical):
+    """Either joined form captured once: every replay, with eager work in between, gives the bits of the eager layer."""
+    print(f"joined layer under capture, critical={critical}", flush=True)
+    L = _layer([300, 212], [0, 7], R=24, style=0)
+    assert host_rules.rerotates_in_scoring(L) and host_rules.rows_beside_projection(L) == L.total_ctx
+    pipeline.enqueue_layer(L)                                    # (fixes the selection)
+    for name in OUTS[6:]:
+        getattr(L, name).fill_(1)
+    k0, v0 = L.k_fused.clone().fill_(1), L.v_fused.clone().fill_(1)
+    outs = OUTS if critical else OUTS[:2] + OUTS[6:]
+
+    def spoil():
+        L.k_fused.copy_(k0)
+        L.v_fused.copy_(v0)
+        for name in outs[2:]:
+            getattr(L, name).fill_(1)
+        torch.cuda.synchronize()
+
+    spoil()
+    pipeline.enqueue_layer(L, critical)
+    torch.cuda.synchronize()
+    want = [getattr(L, name).clone() for name in OUTS]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pipeline.enqueue_layer(L, critical)
+    for _ in range(3):
+        spoil()
+        graph.replay()
+        torch.cuda.synchronize()
+        for name, b in zip(OUTS, want):
+            assert torch.equal(getattr(L, name).view(torch.uint8), b.view(torch.uint8)), name
+
+
 def _sizes(B, n_chunks, R, T, N, H=32, Hkv=8, D=128, dm=4096, dtype="bf16"):
     desc = qb.make_desc(inputs.LayerShape(dm, H, Hkv, D, 500000.0, dtype))
     return types.SimpleNamespace(desc=desc, B=B, n_chunks=n_chunks, total_probe=R, total_ctx=T, total_sel=N)
