@@ -878,57 +878,121 @@ __global__ __launch_bounds__(C::NTHR) void qkv_ws_kernel(QkvArgs a) {
   }
 }
 
-// Sums the partial results of a split contraction, in range order, and finishes them: one workgroup per 32 rows x
-// 128 columns; wave w adds column block w, the first wave does the epilogue.
+// Sums the partial results of a split contraction, in range order, and finishes them.  One workgroup per 32 rows x 64 columns of a
+// block: the two 32-column parts that hold the halves of rotary pairs, gate and up, or else neighbours, so that a thread
+// has both partners of its eight sums and finishes them itself; the results pass through LDS to leave as 16-byte pieces.  Bound by
+// latency where rows are few: launch, one round of loads, stores.  (128 columns to a workgroup, finished by its first wave alone: calls of 61 rows, K 4096, N 4096 in
+// six ranges 15.2 us, now 13.4; 110 rows, K 4096, N 6144 in four 24.6 and 23.2; 200 rows 31.6 and 30.0.)
 template <int EPI>
 __global__ __launch_bounds__(256) void qkv_split_reduce(QkvArgs a, int n_groups) {
-  __shared__ __align__(16) float4 sSum[1024];
-  __shared__ __align__(16) unsigned char sOut[8192];
+  constexpr int LD = 68;                                         // floats of a row (an odd number of 16-byte pieces)
+  constexpr bool kApart = EPI == kRopeHalf128 || EPI == kGlu;    // the parts are 64 columns apart
+  constexpr int kChunks = EPI == kGlu ? 4 : 8;                   // 16-byte pieces of a result row
+  __shared__ __align__(16) float sOut[32 * LD];
   __shared__ float2 sRho[2 * kRho16];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int grp = blockIdx.x;                                    // 32-row group
-  const int n_tile = blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 63, q = tid >> 6, hf = lane >> 5;
+  const int grp = blockIdx.x, n_tile = blockIdx.y, half = blockIdx.z;
   const OutTile ot = out_tile_of<EPI>(a, a.n_tile0 + n_tile);
   if (!ot.out) return;
+  const int j0 = kApart ? half : 2 * half, j1 = kApart ? half + 2 : 2 * half + 1;
+  const int64_t m0 = (int64_t)grp * 32;
+  // the piece that this thread stores: row sr, eight columns from sc on (of the block's)
+  const int sr = tid / kChunks, chunk = tid % kChunks;
+  const int sc = kApart ? (chunk < 4 ? 32 * j0 + 8 * chunk : 32 * j1 + 8 * (chunk - 4)) : 64 * half + 8 * chunk;
+  const bool stores = sr < 32 && m0 + sr < a.M;
   EpiRows<1> rows;
-  load_epi_rows<1, EPI>(a, (int64_t)grp * 32, lane, rows);
-  const float4* src = static_cast<const float4*>(a.part) + ((int64_t)n_tile * n_groups + grp) * 1024 + wave * 256 + lane;
+  load_epi_rows<1, EPI>(a, m0, lane, rows);
+  u32x4 res{};
+  int32_t fused_row = -1;
+  if (stores) {
+    if (EPI == kAdd) res = *reinterpret_cast<const u32x4*>(a.residual + (m0 + sr) * ot.out_cols + ot.out_col0 + sc);
+    if (is_rope(EPI) && ot.fused) fused_row = a.dst_rows[m0 + sr];
+  }
+  const float4* src = static_cast<const float4*>(a.part) + ((int64_t)n_tile * n_groups + grp) * 1024 + lane;
+  const int at0 = (4 * j0 + q) * 64, at1 = (4 * j1 + q) * 64;
   const int64_t stride = (int64_t)a.n_tiles * n_groups * 1024;
-  float4 sum[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) sum[q] = src[q * 64];
+  float4 s0 = src[at0], s1 = src[at1];
   // ranges that are on their way together: four, then two, then one (one after the other they cost 0.3 us each)
   auto add = [&](auto n_c) {
     constexpr int N = decltype(n_c)::value;
-    float4 t[N][4];
+    float4 t[N][2];
 #pragma unroll
-    for (int u = 0; u < N; ++u)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) t[u][q] = src[(u + 1) * stride + q * 64];
+    for (int u = 0; u < N; ++u) { t[u][0] = src[(u + 1) * stride + at0]; t[u][1] = src[(u + 1) * stride + at1]; }
     src += N * stride;
 #pragma unroll
-    for (int u = 0; u < N; ++u)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) { sum[q].x += t[u][q].x; sum[q].y += t[u][q].y; sum[q].z += t[u][q].z; sum[q].w += t[u][q].w; }
+    for (int u = 0; u < N; ++u) {
+      s0.x += t[u][0].x; s0.y += t[u][0].y; s0.z += t[u][0].z; s0.w += t[u][0].w;
+      s1.x += t[u][1].x; s1.y += t[u][1].y; s1.z += t[u][1].z; s1.w += t[u][1].w;
+    }
   };
   int left = a.splits - 1;
   for (; left >= 4; left -= 4) add(std::integral_constant<int, 4>{});
   if (left & 2) add(std::integral_constant<int, 2>{});
   if (left & 1) add(std::integral_constant<int, 1>{});
+  float f0[4] = {s0.x, s0.y, s0.z, s0.w}, f1[4] = {s1.x, s1.y, s1.z, s1.w};      // columns 32 j + 8 q + 4 hf .. + 3 of row lane % 32
+  if constexpr (is_rope(EPI)) {
+    if (tid < 64) fill_rho(a, sRho, tid);
+    __syncthreads();
+    auto rotate = [&](auto far_c) {
+      constexpr bool FAR = decltype(far_c)::value;
+      if constexpr (EPI == kRopeInter) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) sSum[(4 * wave + q) * 64 + lane] = sum[q];
-  if (is_rope(EPI) && tid < 64) fill_rho(a, sRho, tid);
-  __syncthreads();
-  if (wave != 0) return;
-  floatx16 acc[1][4];
+        for (int i = 0; i < 2; ++i) {
+          float(&f)[4] = i == 0 ? f0 : f1;
+          const float2* t = sRho + ((32 * (i == 0 ? j0 : j1) & (a.D - 1)) >> 1) + 4 * q + 2 * hf;
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+          for (int c = 0; c < 2; ++c) {
+            float wx, wy;
+            rotary_factor<FAR>(rows.pos[0], Rho<FAR>(t + c), wx, wy);
+            const float x = f[2 * c], y = f[2 * c + 1];
+            f[2 * c] = turned(x, wx, -y, wy);
+            f[2 * c + 1] = turned(y, wx, x, wy);
+          }
+        }
+      } else {
+        const float2* t = sRho + (EPI == kRopeHalf128 ? 32 * half : 0) + 8 * q + 4 * hf;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float4 t = sSum[(4 * j + q) * 64 + lane];
-      acc[0][j][4 * q] = t.x; acc[0][j][4 * q + 1] = t.y; acc[0][j][4 * q + 2] = t.z; acc[0][j][4 * q + 3] = t.w;
+        for (int c = 0; c < 4; ++c) {
+          float wx, wy;
+          rotary_factor<FAR>(rows.pos[0], Rho<FAR>(t + c), wx, wy);
+          const float x = f0[c], y = f1[c];
+          f0[c] = turned(x, wx, -y, wy);
+          f1[c] = turned(y, wx, x, wy);
+        }
+      }
+    };
+    if (ot.rotate) {
+      if (__builtin_expect(__any(is_far(rows.pos[0])), 0)) rotate(std::true_type{});
+      else rotate(std::false_type{});
     }
-  wave_epilogue<1, EPI>(a, ot, acc, sRho, sOut, (int64_t)grp * 32, lane, rows);
+  }
+  if constexpr (EPI == kGlu) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {                // gate and up are rounded to bf16 first, as the separate calls store them
+      const uint32_t gu = cvt_pk_bf16(f0[c], f1[c]);
+      f0[c] = silu_mul(__uint_as_float(gu << 16), __uint_as_float(gu & 0xffff0000u));
+    }
+  }
+  if (rows.zero[0]) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) f0[c] = f1[c] = 0.f;
+  }
+  float* mine = sOut + (lane & 31) * LD + 8 * q + 4 * hf;
+  *reinterpret_cast<float4*>(mine) = make_float4(f0[0], f0[1], f0[2], f0[3]);
+  if (EPI != kGlu) *reinterpret_cast<float4*>(mine + 32) = make_float4(f1[0], f1[1], f1[2], f1[3]);
+  __syncthreads();
+  if (!stores) return;
+  const float4 o0 = *reinterpret_cast<const float4*>(sOut + sr * LD + 8 * chunk), o1 = *reinterpret_cast<const float4*>(sOut + sr * LD + 8 * chunk + 4);
+  float o[8] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
+  if (EPI == kAdd) {
+    const uint32_t r[4] = {res.x, res.y, res.z, res.w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) { o[2 * c] += __uint_as_float(r[c] << 16); o[2 * c + 1] += __uint_as_float(r[c] & 0xffff0000u); }
+  }
+  const u32x4 t = mk4(cvt_pk_bf16(o[0], o[1]), cvt_pk_bf16(o[2], o[3]), cvt_pk_bf16(o[4], o[5]), cvt_pk_bf16(o[6], o[7]));
+  *reinterpret_cast<u32x4*>(ot.out + (m0 + sr) * ot.out_cols + ot.out_col0 + sc) = t;
+  if (is_rope(EPI) && ot.fused && fused_row >= 0 && fused_row < a.fused_rows)
+    *reinterpret_cast<u32x4*>(ot.fused + (int64_t)fused_row * ot.out_cols + ot.out_col0 + sc) = t;
 }
 
 // ---- 256 x 256 tiles, four waves of 128 x 128 -----------------------------------------------------
@@ -1174,7 +1238,7 @@ static_assert(Ws256::BM == rows_of(kWs256) && Ws128::BM == rows_of(kWs128) && Ws
 // finishes a split launch whose partial sums lie in n_groups groups of 32 rows
 template <int EPI>
 qcf_status run_split_reduce(const QkvArgs& a, int64_t n_groups, hipStream_t st) {
-  const dim3 grid((unsigned)((a.M + 31) / 32), (unsigned)a.n_tiles);
+  const dim3 grid((unsigned)((a.M + 31) / 32), (unsigned)a.n_tiles, 2);
   qkv_split_reduce<EPI><<<grid, dim3(256), 0, st>>>(a, (int)n_groups);
   return check_launch("qkv split reduce");
 }

@@ -160,3 +160,38 @@ def test_gated_product_without_workspace_has_one_order_of_sums(M, K, F):
     assert torch.equal(whole[M - 1], whole[3])
     for rows in (4, 61, 128):
         assert torch.equal(product(rows), whole[:rows]), rows
+
+
+@pytest.mark.parametrize("M,D,style,far", [(33, 64, 0, False), (1, 64, 1, True), (70, 128, 1, False), (128, 128, 0, True)])
+def test_rotation_behind_the_reduction(M, D, style, far):
+    """The reduction finishes 64 columns of a block in a workgroup: every layout of rotary pairs, zero rows, rows past the last."""
+    dm, H, Hkv = 4096, 16, 4
+    print(f"reduction M={M} D={D} style={style} far={far}", flush=True)
+    sh = inputs.LayerShape(dm, H, Hkv, D, 500000.0, "bf16", style)
+    desc = qb.make_desc(sh)
+    assert qb.qcf_recompute_qkv_workspace_bytes(desc, M) > 0           # (the contraction is split)
+    x, w = _normal(15, M + 5, dm), _normal(16, sh.qkv_rows, dm, std=dm ** -0.5)
+    g = torch.Generator(device=DEV).manual_seed(17)
+    gather = torch.randperm(M + 5, generator=g, device=DEV)[:M].int()
+    gather[M // 2] = M + 5                                   # outside x: a zero row
+    pos = torch.randint(0, 2 ** 31 - 1 if far else 40000, (M,), generator=g, device=DEV).int()
+    dst = torch.randperm(M + 5, generator=g, device=DEV)[:M].int()
+    q, k, v = (torch.full((M + 1, h, D), 7.0, dtype=BF, device=DEV) for h in (H, Hkv, Hkv))
+    kf, vf = (torch.full((M + 5, Hkv, D), 7.0, dtype=BF, device=DEV) for _ in range(2))
+    qb.qcf_recompute_qkv_scatter(desc, x, M + 5, gather, M, w, pos, q, k, v, dst, kf, vf, M + 5)
+    torch.cuda.synchronize()
+    xs = x[gather.clamp(max=M + 4).long()].float()
+    xs[M // 2] = 0
+    y = (xs @ w.float().T).reshape(M, H + 2 * Hkv, D).double()
+    ang = pos.double()[:, None, None] * 500000.0 ** (-torch.arange(0, D, 2, device=DEV, dtype=torch.float64) / D)
+    even, odd = (slice(0, D // 2), slice(D // 2, D)) if style == 0 else (slice(0, D, 2), slice(1, D, 2))
+    a, b = y[:, :H + Hkv, even].clone(), y[:, :H + Hkv, odd].clone()
+    y[:, :H + Hkv, even] = a * ang.cos() - b * ang.sin()
+    y[:, :H + Hkv, odd] = b * ang.cos() + a * ang.sin()
+    for got, ref in ((q, y[:, :H]), (k, y[:, H:H + Hkv]), (v, y[:, H + Hkv:])):
+        _one_rounding(got[:M], ref.float())
+        assert bool((got[M] == 7.0).all())
+    for fused, new in ((kf, k), (vf, v)):
+        ref = torch.full_like(fused, 7.0)
+        ref[dst.long()] = new[:M]
+        assert torch.equal(fused, ref)
