@@ -21,9 +21,8 @@
 // Bound by the softmax arithmetic between the two products and by the splitting into terms.  615 rows x 32 heads over 4096
 // tokens: 1580 us with the generic kernel, 48.0 us here (41.7 with two terms); the whole layer 96.6 us (2074 before).
 //
-// Generic path (f32, or other shapes): one workgroup per (row, head), online softmax over
-// 256-token tiles.  Bound by the latency of its loads: 77 rows x 4 heads over 512 tokens in f32 16.6 us with eight values on their
-// way at a time, 11.4 with all of a tile's keys and values.
+// Generic path (f32, or other shapes): one workgroup per (row, head) or pair of heads, online softmax over
+// tiles of 256 or 512 tokens.  Bound by the latency of its loads where rows are few and by their number where they are many.
 #include "attn_common.h"
 
 namespace qcf {
@@ -32,18 +31,17 @@ namespace {
 
 // ------------------------------------------------------------------ generic path
 
-// A tile of 256 tokens: keys a token to a thread, values four elements of every kSlices-th token to a thread, kBatch vectors of
-// either on their way.  kBatch 16: the keys and the first 16 values are requested together, so that a tile waits for memory once.
-// (Requested a tile ahead they take all registers and more moves: 15.0 us for the case above.)  Launches of kManyWgs workgroups to a
-// compute unit hide the waits behind each other and lose by the registers (170, heads of 128): kBatch 8, values behind the
-// keys, waves without a token of the last tile pass it over.  The sums and their order are the same.  us, 16 and 8: f32, 32 / 8 heads
-// of 128, 150 rows over 1000 tokens 222 and 190, 307 over 2048 960 and 790; 16 / 8 heads of 64, 300 over 1000 122 and 98; bf16,
-// 12 / 4 heads of 128, 300 over 512 69 and 61.  The other side of the line: f32, 4 / 2 heads of 64, 80 rows over 2048 33 and 37;
-// bf16, 12 / 4 heads of 128, 77 over 512 22.1 and 23.3.  bf16 heads of 64 (130 registers): 614 rows over 4096 356 and 400, 300
-// over 512 36.3 and 38.0.
+// bfloat16.  A tile of 256 tokens: keys a token to a thread, values four elements of every kSlices-th token to a thread, kBatch
+// vectors of either on their way.  kBatch 16: the keys and the first 16 values are requested together, so that a tile waits for
+// memory once.  Launches of kManyWgs workgroups to a compute unit hide the waits behind each other and lose by the registers
+// (170, heads of 128): kBatch 8, values behind the keys, waves without a token of the last tile pass it over.  The sums and their
+// order are the same.  us, 16 and 8: 12 / 4 heads of 128, 300 rows over 512 69 and 61, 77 over 512 22.1 and 23.3; heads of 64
+// (130 registers) 614 rows over 4096 356 and 400, 300 over 512 36.3 and 38.0.  (Lanes that share a token, as below, lose here, where a
+// token takes 128 or 256 bytes: 300 over 512 60 and 83.)
 constexpr int kManyWgs = 5;
-template <typename T, int D, int kBatch>
+template <int D, int kBatch>
 __global__ __launch_bounds__(256) void attn_generic(AttnArgs a) {
+  typedef bf16_t T;
   constexpr int kQuads = D / 4, kSlices = 256 / kQuads, kVals = 256 / kSlices;
   constexpr bool kTogether = kBatch == 16;
   __shared__ __align__(16) float sq[D];
@@ -141,6 +139,173 @@ __global__ __launch_bounds__(256) void attn_generic(AttnArgs a) {
     Elem<T>::store(static_cast<T*>(a.o) + (row * a.H + h) * D + tid, n_vis > 0 ? o / l_run : 0.f);
   }
   if (tid == 0 && a.lse) a.lse[row * a.H + h] = n_vis > 0 ? m_run + logf(l_run) : -INFINITY;
+}
+
+// float32: D / 4 lanes take a token, so that a load brings whole key rows (a token to a thread asked for 64 lines with every load),
+// and NH heads of a KV group share a workgroup with its keys and values: two where a group has an even number.  Tiles of 512
+// tokens.  Launches of at most kFewWgs workgroups to a compute unit take 512 threads, which halves the chain of waits; more
+// of them hide each other's with 256.  The sums and their order are the same.  us, with a token
+// to a thread and a head to a workgroup, and with 512 and 256 threads so: 4 / 2 heads of 64, 77 rows over 512 tokens 10.9, 7.8, 10.0,
+// 80 over 2048 33, 22, 32, 300 over 2000 (600 workgroups) 69, 42, 37; 3 heads, 100 rows over 700 (300) 14.0, 10.2, 11.6; 8 requests
+// of 512 tokens, 80 rows each 38, 31, 21; 32 / 8 heads of 128, 150 over 1000 200, 86, 89; 16 / 8 heads of 64, 300 over 1000 100, 76,
+// 45.  (The first values requested with the keys: no difference.)  Error against 64 bits 2.5e-7, now 1.5e-7: sums in pairs.
+constexpr int kFewWgs = 2;
+constexpr int kTileF32 = 512;
+template <int D, int NH, int THREADS>
+__global__ __launch_bounds__(THREADS) void attn_generic_f32(AttnArgs a) {
+  constexpr int kQuads = D / 4, kSlices = kTileF32 / kQuads, kWaves = kTileF32 / 64;     // of a tile
+  constexpr int kVals = kTileF32 / kSlices;
+  constexpr int kTurns = kTileF32 / THREADS;                 // a thread has token and slice tid of each part of THREADS tokens
+  constexpr int kTokens = 64 / kQuads, kBatch = 8;           // keys: tokens of a load; loads on their way
+  __shared__ float sp[NH][kTileF32], slog[NH][kTileF32];
+  __shared__ __align__(16) float sacc[NH][kSlices * D];
+  __shared__ float redm[NH][kWaves], reds[NH][kWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int per_row = a.H / NH;
+  const int64_t row = blockIdx.x / per_row;
+  const int h0 = (int)(blockIdx.x - row * per_row) * NH;
+  const int quad = tid % kQuads, slice0 = tid / kQuads, token = lane / kQuads;
+  // (everything that does not depend on the request is requested in front of the search for it)
+  const float* qp = static_cast<const float*>(a.q) + (row * a.H + h0) * D + 4 * quad;
+  float q4[NH][4];
+#pragma unroll
+  for (int i = 0; i < NH; ++i) Quad<float>::load(qp + i * D, q4[i]);
+  const int pos = a.sel_pos[row];
+  int64_t ctx0 = a.ctx_off[0], ctx1 = a.ctx_off[1];
+  const int b = find_request(a.sel_off, a.B, row);
+  if (b >= a.B) return;
+  if (b > 0) { ctx0 = a.ctx_off[b]; ctx1 = a.ctx_off[b + 1]; }
+  const int64_t c0 = min(max(ctx0, (int64_t)0), a.total_ctx);
+  const int64_t c1 = min(max(ctx1, c0), a.total_ctx);
+  const int Tn = (int)(c1 - c0);
+  const int64_t p0 = a.ctx_pos0 ? a.ctx_pos0[b] : 0;
+  const int n_vis = (int)min((int64_t)Tn, max((int64_t)0, (int64_t)pos - p0 + 1));
+  const int g = h0 / a.G;
+  const int64_t kv_stride = (int64_t)a.Hkv * D;
+  const float* kb = static_cast<const float*>(a.k) + (c0 * a.Hkv + g) * D + 4 * quad;
+  const float* vb = static_cast<const float*>(a.v) + (c0 * a.Hkv + g) * D + 4 * quad;
+  const float scale = rsqrtf((float)D);
+  float m_run[NH], l_run[NH], acc[kTurns][NH][4];
+#pragma unroll
+  for (int i = 0; i < NH; ++i) {
+    m_run[i] = -INFINITY;
+    l_run[i] = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      q4[i][e] *= scale;
+#pragma unroll
+      for (int t = 0; t < kTurns; ++t) acc[t][i][e] = 0.f;
+    }
+  }
+  for (int j0 = 0; j0 < n_vis; j0 += kTileF32) {
+    const int n = min(kTileF32, n_vis - j0);
+    const float* kr = kb + (int64_t)j0 * kv_stride;
+    const float* vr = vb + (int64_t)j0 * kv_stride;
+    float s[kTurns][NH];
+#pragma unroll
+    for (int t = 0; t < kTurns; ++t) {
+      const int at = t * THREADS + 64 * wave;                // this wave's 64 tokens
+      if (at < n) {
+#pragma unroll
+        for (int c = 0; c < kQuads; c += kBatch) {
+          float kf[kBatch][4];
+#pragma unroll
+          for (int u = 0; u < kBatch; ++u)
+            Quad<float>::load(kr + (int64_t)min(at + (c + u) * kTokens + token, n - 1) * kv_stride, kf[u]);
+#pragma unroll
+          for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+            for (int i = 0; i < NH; ++i) {
+              float d = q4[i][0] * kf[u][0];
+#pragma unroll
+              for (int e = 1; e < 4; ++e) d += q4[i][e] * kf[u][e];
+              d = kQuads == 16 ? row_sum(d) : half_wave_sum(d);
+              if (quad == 0) slog[i][at + (c + u) * kTokens + token] = d;
+            }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < NH; ++i) {
+        s[t][i] = at + lane < n ? slog[i][at + lane] : -INFINITY;       // (written by this wave)
+        const float mx = wave_max(s[t][i]);
+        if (lane == 0) redm[i][at / 64] = mx;
+      }
+    }
+    __syncthreads();                               // (and the previous tile's probabilities have been read)
+    float alpha[NH];
+#pragma unroll
+    for (int i = 0; i < NH; ++i) {
+      float mx = redm[i][0];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) mx = fmaxf(mx, redm[i][w]);
+      const float m_new = fmaxf(m_run[i], mx);     // finite: the tile has at least one visible token
+#pragma unroll
+      for (int t = 0; t < kTurns; ++t) {
+        const int at = t * THREADS + 64 * wave;
+        const float p = at + lane < n ? expf(s[t][i] - m_new) : 0.f;
+        sp[i][at + lane] = p;
+        const float sum = wave_sum(p);
+        if (lane == 0) reds[i][at / 64] = sum;
+      }
+      alpha[i] = expf(m_run[i] - m_new);           // 0 on the first tile
+      m_run[i] = m_new;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NH; ++i) {
+      float sum = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) sum += reds[i][w];
+      l_run[i] = l_run[i] * alpha[i] + sum;
+#pragma unroll
+      for (int t = 0; t < kTurns; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[t][i][e] *= alpha[i];
+    }
+#pragma unroll
+    for (int t = 0; t < kTurns; ++t) {
+      const int slice = slice0 + t * (THREADS / kQuads);
+#pragma unroll
+      for (int u0 = 0; u0 < kVals; u0 += kBatch) {
+        if (slice + u0 * kSlices >= n) break;
+        float vf[kBatch][4];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) Quad<float>::load(vr + (int64_t)min(slice + (u0 + u) * kSlices, n - 1) * kv_stride, vf[u]);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          const int jj = slice + (u0 + u) * kSlices;
+          if (jj < n) {
+#pragma unroll
+            for (int i = 0; i < NH; ++i) {
+              const float w = sp[i][jj];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[t][i][e] += w * vf[u][e];
+            }
+          }
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < kTurns; ++t)
+#pragma unroll
+    for (int i = 0; i < NH; ++i)
+      *reinterpret_cast<float4*>(&sacc[i][(slice0 + t * (THREADS / kQuads)) * D + 4 * quad]) =
+          make_float4(acc[t][i][0], acc[t][i][1], acc[t][i][2], acc[t][i][3]);
+  __syncthreads();
+  if (tid < NH * D) {                              // the slices' sums in order
+    const int i = tid / D, d = tid % D;
+    float o = sacc[i][d];
+    for (int w = 1; w < kSlices; ++w) o += sacc[i][w * D + d];
+    float l = l_run[0];
+#pragma unroll
+    for (int u = 1; u < NH; ++u) l = i == u ? l_run[u] : l;
+    static_cast<float*>(a.o)[(row * a.H + h0 + i) * D + d] = n_vis > 0 ? o / l : 0.f;
+  }
+  if (tid == 0 && a.lse) {
+#pragma unroll
+    for (int i = 0; i < NH; ++i) a.lse[row * a.H + h0 + i] = n_vis > 0 ? m_run[i] + logf(l_run[i]) : -INFINITY;
+  }
 }
 
 // ------------------------------------------------------------------ MFMA path (bf16, d = 128 or 64)
@@ -899,19 +1064,22 @@ qcf_status launch_attn(const qcf_layer_desc& L, int32_t B, const void* q, const 
     return part_is_f32(a.D, d.rows, sp) ? run_mfma<128, kNarrowRows, true>(a, st) : run_mfma<128, kNarrowRows, false>(a, st);
   }
   if (total_sel * a.H > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "attn: grid too large");
-  const dim3 grid((unsigned)(total_sel * a.H)), block(256);
-  const bool many = total_sel * a.H >= (int64_t)kManyWgs * compute_unit_count();
-#define QCF_GENERIC(T, DIM, BATCH) attn_generic<T, DIM, BATCH><<<grid, block, 0, st>>>(a)
   if (L.dtype == QCF_DTYPE_BF16) {
-    if (a.D == 64) QCF_GENERIC(bf16_t, 64, 16);
-    else if (many) QCF_GENERIC(bf16_t, 128, 8);
-    else QCF_GENERIC(bf16_t, 128, 16);
-  } else if (a.D == 64) {
-    if (many) QCF_GENERIC(float, 64, 8); else QCF_GENERIC(float, 64, 16);
+    const dim3 grid((unsigned)(total_sel * a.H)), block(256);
+    if (a.D == 64) attn_generic<64, 16><<<grid, block, 0, st>>>(a);
+    else if (total_sel * a.H >= (int64_t)kManyWgs * compute_unit_count()) attn_generic<128, 8><<<grid, block, 0, st>>>(a);
+    else attn_generic<128, 16><<<grid, block, 0, st>>>(a);
   } else {
-    if (many) QCF_GENERIC(float, 128, 8); else QCF_GENERIC(float, 128, 16);
+    const bool pairs = a.G % 2 == 0;
+    const int64_t wgs = total_sel * (pairs ? a.H / 2 : a.H);
+    const bool few = wgs <= kFewWgs * (int64_t)compute_unit_count();
+#define QCF_F32(DIM, NH)                                                                                     \
+  if (few) attn_generic_f32<DIM, NH, 512><<<dim3((unsigned)wgs), dim3(512), 0, st>>>(a);                     \
+  else attn_generic_f32<DIM, NH, 256><<<dim3((unsigned)wgs), dim3(256), 0, st>>>(a)
+    if (a.D == 64) { if (pairs) { QCF_F32(64, 2); } else { QCF_F32(64, 1); } }
+    else { if (pairs) { QCF_F32(128, 2); } else { QCF_F32(128, 1); } }
+#undef QCF_F32
   }
-#undef QCF_GENERIC
   return check_launch("attn");
 }
 

@@ -217,6 +217,40 @@ __device__ __forceinline__ void load_to_lds_const(const void* base, uint32_t lan
                :: "v"(lane_off), "s"(sb), "s"(lds_base), "n"(OFF) : "scc");
 }
 
+// sums over the 16 lanes of each row and the 32 of each half of a wave, in a fixed order; every lane gets the total
+__device__ __forceinline__ float row_sum(float x) {
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x128, 0xf, 0xf, false));   // row_ror:8
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x124, 0xf, 0xf, false));   // row_ror:4
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x122, 0xf, 0xf, false));   // row_ror:2
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x121, 0xf, 0xf, false));   // row_ror:1
+  return x;
+}
+__device__ __forceinline__ float half_wave_sum(float x) {
+  x = row_sum(x);
+  typedef unsigned u2v __attribute__((ext_vector_type(2)));
+  const u2v r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r.x) + __uint_as_float(r.y);     // rows (0, 1) and (2, 3) of 16 lanes each
+}
+
+// sum and maximum over the lanes of a wave; every lane gets it
+__device__ __forceinline__ float wave_sum(float x) {
+  x = half_wave_sum(x);
+  typedef unsigned u2v __attribute__((ext_vector_type(2)));
+  const u2v r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+__device__ __forceinline__ float wave_max(float x) {
+  typedef unsigned u2v __attribute__((ext_vector_type(2)));
+  x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x128, 0xf, 0xf, false)));
+  x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x124, 0xf, 0xf, false)));
+  x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x122, 0xf, 0xf, false)));
+  x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x121, 0xf, 0xf, false)));
+  u2v r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+}
+
 // ---- launchers (one per translation unit) --------------------------------------
 // Each returns QCF_OK or an error after enqueueing on `st`; arguments were validated
 // by the entry points in api.hip.

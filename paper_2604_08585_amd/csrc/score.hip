@@ -53,21 +53,6 @@ __device__ __forceinline__ int find_request(const int64_t* __restrict__ off, int
   return b;
 }
 
-// sums over the 16 lanes of each row and the 32 of each half of a wave, in a fixed order; every lane gets the total
-__device__ __forceinline__ float row_sum(float x) {
-  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x128, 0xf, 0xf, false));   // row_ror:8
-  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x124, 0xf, 0xf, false));   // row_ror:4
-  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x122, 0xf, 0xf, false));   // row_ror:2
-  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x121, 0xf, 0xf, false));   // row_ror:1
-  return x;
-}
-__device__ __forceinline__ float half_wave_sum(float x) {
-  x = row_sum(x);
-  typedef unsigned u2v __attribute__((ext_vector_type(2)));
-  const u2v r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r.x) + __uint_as_float(r.y);     // rows (0, 1) and (2, 3) of 16 lanes each
-}
-
 // ------------------------------------------------------------------ generic path
 
 // D / 4 lanes take a token, so that a load brings whole key rows, and a wave has eight of its loads on their way.  Up to

@@ -1,6 +1,7 @@
 """GPU parity of the kernel variants that sizes, types and alignment choose between, at the sizes where each can go
 wrong (edges of tiles, remainders, smallest and largest of a range), against plain float32 PyTorch or the CPU oracle."""
 import ctypes as C
+import math
 
 import numpy as np
 import pytest
@@ -762,3 +763,32 @@ def test_anchor_extraction_is_refused_under_capture():
     got = pipeline.extract_anchors(desc, k, v, [64, 32], [4, 2])
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("many", [False, True])          # 512 and 256 threads to a workgroup
+@pytest.mark.parametrize("H,Hkv,D,T", [(4, 2, 64, 511), (4, 2, 128, 513), (3, 3, 64, 257), (6, 2, 128, 64), (8, 2, 64, 1025), (5, 1, 128, 1)])
+def test_f32_attention_by_lanes(H, Hkv, D, T, many):
+    """Tokens shared by the lanes of a wave, pairs of heads (even groups) and single ones; edges of tiles of 256 and 512 tokens, rows
+    that see one token, all of them and none, a request without rows between two others."""
+    n = 600 if many else 7
+    say(f"f32 attention by lanes H={H}/{Hkv} D={D} T={T} rows={n}")
+    g = gen(91)
+    lens, rows = [T, 5, 2 * T], [n, 0, 3]
+    off = lambda v: torch.tensor([sum(v[:i]) for i in range(len(v) + 1)], dtype=torch.int64, device=DEV)
+    q = torch.randn((sum(rows), H, D), generator=g, device=DEV)
+    k, v = (torch.randn((sum(lens), Hkv, D), generator=g, device=DEV) for _ in range(2))
+    pos = torch.cat([torch.randint(0, T, (n,), generator=g, device=DEV), torch.randint(0, 2 * T, (3,), generator=g, device=DEV)]).int()
+    pos[0], pos[1], pos[2], pos[3] = 0, T - 1, -1, T + 100            # (one token, all, none, all)
+    desc = qb.make_desc(inputs.LayerShape(256, H, Hkv, D, 10000.0, "f32"))
+    o, lse = torch.full_like(q, 7.0), torch.full((sum(rows), H), 7.0, device=DEV)
+    qb.qcf_recompute_attn(desc, 3, q, pos, off(rows), sum(rows), k, v, off(lens), sum(lens), None, o, lse)
+    torch.cuda.synchronize()
+    for lo, hi, c0, c1 in ((0, n, 0, T), (n, n + 3, T + 5, 3 * T + 5)):
+        kk, vv = (x[c0:c1].double().repeat_interleave(H // Hkv, 1) for x in (k, v))
+        s = q[lo:hi].double().transpose(0, 1) @ kk.permute(1, 2, 0).contiguous() / math.sqrt(D)
+        s.masked_fill_(torch.arange(c1 - c0, device=DEV) > pos[lo:hi].long()[None, :, None], -math.inf)
+        ref = (torch.softmax(s, -1).nan_to_num(0.0) @ vv.transpose(0, 1).contiguous()).transpose(0, 1)
+        # 32-bit logits of D terms (an error of about 1e-6 in the exponent) and sums of up to 2050 positive weights
+        assert float((o[lo:hi].double() - ref).abs().max()) < 1e-5
+        want, got = torch.logsumexp(s, -1).transpose(0, 1), lse[lo:hi].double()
+        assert bool((((got - want).abs() < 1e-5) | ((want == -math.inf) & (got == -math.inf))).all())
