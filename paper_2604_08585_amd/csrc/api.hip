@@ -239,10 +239,9 @@ size_t qcf_select_workspace_bytes(int32_t B, int64_t total_ctx) {
   return select_workspace(B, total_ctx);
 }
 
-qcf_status qcf_select(int32_t B, const float* score, const int64_t* ctx_off_dev, int64_t total_ctx,
-                      const int64_t* sel_off_dev, int64_t total_sel, const int32_t* ctx_pos0_dev,
-                      int32_t* sel_idx, int32_t* sel_row, int32_t* sel_pos, void* workspace,
-                      size_t workspace_bytes, void* stream) {
+static qcf_status check_select_args(int32_t B, const float* score, const int64_t* ctx_off_dev, int64_t total_ctx,
+                                    const int64_t* sel_off_dev, int64_t total_sel, const int32_t* ctx_pos0_dev, const int32_t* sel_idx,
+                                    const int32_t* sel_row, const int32_t* sel_pos, const void* workspace, size_t workspace_bytes) {
   if (B < 0 || total_ctx < 0 || total_sel < 0) return fail(QCF_ERR_INVALID_ARG, "negative size");
   if (total_ctx > kMaxRows) return fail(QCF_ERR_UNSUPPORTED, "too many rows");
   if (total_sel > total_ctx) return fail(QCF_ERR_INVALID_ARG, "total_sel %lld > total_ctx %lld",
@@ -256,7 +255,16 @@ qcf_status qcf_select(int32_t B, const float* score, const int64_t* ctx_off_dev,
   if (ctx_pos0_dev) QCF_TRY(need_idx_ptr(ctx_pos0_dev, "ctx_pos0_dev"));
   if (sel_row) QCF_TRY(need_idx_ptr(sel_row, "sel_row"));
   if (sel_pos) QCF_TRY(need_idx_ptr(sel_pos, "sel_pos"));
-  QCF_TRY(need_ws(workspace, workspace_bytes, select_workspace(B, total_ctx)));
+  return need_ws(workspace, workspace_bytes, select_workspace(B, total_ctx));
+}
+
+qcf_status qcf_select(int32_t B, const float* score, const int64_t* ctx_off_dev, int64_t total_ctx,
+                      const int64_t* sel_off_dev, int64_t total_sel, const int32_t* ctx_pos0_dev,
+                      int32_t* sel_idx, int32_t* sel_row, int32_t* sel_pos, void* workspace,
+                      size_t workspace_bytes, void* stream) {
+  QCF_TRY(check_select_args(B, score, ctx_off_dev, total_ctx, sel_off_dev, total_sel, ctx_pos0_dev, sel_idx, sel_row, sel_pos, workspace,
+                            workspace_bytes));
+  if (B == 0 || total_sel == 0) return QCF_OK;
   return launch_select(B, score, ctx_off_dev, total_ctx, sel_off_dev, total_sel, ctx_pos0_dev, sel_idx,
                        sel_row, sel_pos, workspace, (hipStream_t)stream);
 }
@@ -404,7 +412,20 @@ qcf_status qcf_fuse_layer(const qcf_layer_desc* desc, const qcf_layer_buffers* l
                                 b.ctx_off_dev, b.total_ctx, b.score, b.score_ws, (hipStream_t)stream));
   else if (!beside)
     QCF_TRY(qcf_rerope(desc, b.chunks_dev, b.n_chunks, b.total_ctx, b.k_fused, b.v_fused, b.rerope_ws, b.rerope_ws_bytes, stream));
-  if (critical) {
+  // Scores whose last sums the selection adds up itself (only where both calls will not fail).
+  if (critical && !joined && b.total_sel > 0 &&
+      scoring::sums_in_selection(*desc, b.B, b.total_probe, b.total_ctx) != scoring::kNoSums &&
+      check_score_args(desc, b.B, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.ctx_off_dev, b.total_ctx, nullptr, b.score,
+                       &empty) == QCF_OK &&
+      need_ws(b.score_ws, b.score_ws_bytes, scoring::workspace(*desc, b.B, b.total_probe, b.total_ctx)) == QCF_OK &&
+      check_select_args(b.B, b.score, b.ctx_off_dev, b.total_ctx, b.sel_off_dev, b.total_sel, nullptr, b.sel_idx, b.sel_row, b.sel_pos,
+                        b.select_ws, b.select_ws_bytes) == QCF_OK) {
+    ScoreSums sums{};
+    QCF_TRY(launch_score(*desc, b.B, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.ctx_off_dev, b.total_ctx, nullptr, b.score,
+                         1.f, 0.f, b.score_ws, (hipStream_t)stream, &sums));
+    QCF_TRY(launch_select_sums(sums, b.score, b.ctx_off_dev, b.total_ctx, b.sel_off_dev, b.total_sel, b.sel_idx, b.sel_row, b.sel_pos,
+                               (hipStream_t)stream));
+  } else if (critical) {
     if (!joined)
       QCF_TRY(qcf_score(desc, b.B, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.ctx_off_dev, b.total_ctx, nullptr,
                         b.score, b.score_ws, b.score_ws_bytes, stream));

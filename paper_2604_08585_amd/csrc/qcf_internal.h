@@ -264,9 +264,17 @@ qcf_status check_score_args(const qcf_layer_desc* desc, int32_t B, const void* q
                             const int64_t* probe_off_dev, int64_t total_probe, const void* k_fused,
                             const int64_t* ctx_off_dev, int64_t total_ctx, const int32_t* probe_limit_dev,
                             float* score, bool* empty);
+// The last sums of a scoring that are left to the selection of the same request (launch_score fills it in instead of adding them).
+struct ScoreSums {
+  const float* sums;             // [n][total_ctx]: of the KV heads, or of every probe row and head (rows)
+  const int64_t* probe_off;
+  int64_t total_probe;
+  int H, Hkv;
+  bool rows;
+};
 qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const int64_t* probe_off,
                         int64_t total_probe, const void* k, const int64_t* ctx_off, int64_t total_ctx,
-                        const int32_t* probe_limit, float* score, float alpha, float beta, void* ws, hipStream_t st);
+                        const int32_t* probe_limit, float* score, float alpha, float beta, void* ws, hipStream_t st, ScoreSums* left = nullptr);
 
 // re-rotation and scoring of one request in one launch, where scoring::takes_rerope
 qcf_status launch_rerope_score(const qcf_layer_desc& L, const qcf_chunk* chunks, int32_t n_chunks, const void* q,
@@ -285,6 +293,8 @@ qcf_status launch_select(int32_t B, const float* score, const int64_t* ctx_off, 
                          hipStream_t st);
 
 // Top-N of every chunk and the gather of its key and value rows; the offsets are host arrays
+qcf_status launch_select_sums(const ScoreSums& sums, float* score, const int64_t* ctx_off, int64_t total_ctx, const int64_t* sel_off,
+                              int64_t total_sel, int32_t* sel_idx, int32_t* sel_row, int32_t* sel_pos, hipStream_t st);
 qcf_status launch_select_gather(const qcf_layer_desc& L, const float* score, int32_t n_chunks, const int64_t* ctx_off,
                                 const int64_t* sel_off, const void* k, const void* v, int32_t* rows, void* k_out, void* v_out,
                                 hipStream_t st);

@@ -1179,7 +1179,7 @@ qcf_status run_fused(const FusedArgs& fa, hipStream_t st) {
 }
 
 template <int D, bool LIMIT, bool ONE>
-qcf_status run_two_pass(const Args<ONE>& a, dim3 grid, hipStream_t st) {
+qcf_status run_two_pass(const Args<ONE>& a, dim3 grid, hipStream_t st, bool reduce) {
   static std::atomic<uint64_t> lds_ok[2];
   QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass1<D, LIMIT, ONE>), kPass1Lds<D>, lds_ok[0]));
   QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass2<D, LIMIT, ONE>), kPass2Lds<D>, lds_ok[1]));
@@ -1188,21 +1188,22 @@ qcf_status run_two_pass(const Args<ONE>& a, dim3 grid, hipStream_t st) {
   QCF_TRY_LAUNCH("score pass 1");
   score_pass2<D, LIMIT, ONE><<<grid, block, kPass2Lds<D>, st>>>(a);
   QCF_TRY_LAUNCH("score pass 2");
+  if (!reduce) return QCF_OK;
   int toks = 256;
   if constexpr (!ONE) toks /= layers_at(a.n_layers);
   score_reduce<ONE><<<dim3((unsigned)((common(a).total_ctx + toks - 1) / toks)), dim3(256), 0, st>>>(a);
   return check_launch("score reduce");
 }
 template <bool ONE>
-qcf_status run_passes(int D, const Args<ONE>& a, dim3 grid, hipStream_t st) {
+qcf_status run_passes(int D, const Args<ONE>& a, dim3 grid, hipStream_t st, bool reduce) {
   const bool limit = common(a).probe_limit != nullptr;
-  if (D == 128) return limit ? run_two_pass<128, true, ONE>(a, grid, st) : run_two_pass<128, false, ONE>(a, grid, st);
-  return limit ? run_two_pass<64, true, ONE>(a, grid, st) : run_two_pass<64, false, ONE>(a, grid, st);
+  if (D == 128) return limit ? run_two_pass<128, true, ONE>(a, grid, st, reduce) : run_two_pass<128, false, ONE>(a, grid, st, reduce);
+  return limit ? run_two_pass<64, true, ONE>(a, grid, st, reduce) : run_two_pass<64, false, ONE>(a, grid, st, reduce);
 }
 
 // The two passes over n_layers layers (up to kMaxLayers); a: everything but the layers and the workspace.
 qcf_status launch_two_pass(const qcf_layer_desc& L, const ScoreArgs& a, int n_layers, const void* const* q,
-                           const void* const* k, const float* alpha, void* ws, hipStream_t st) {
+                           const void* const* k, const float* alpha, void* ws, hipStream_t st, ScoreSums* left = nullptr) {
   const PassWs w = pass_ws(L, n_layers, a.B, a.total_probe, a.total_ctx);
   if (w.n_units * n_layers * a.Hkv > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "score: grid too large");
   PassArgs pa;
@@ -1219,9 +1220,10 @@ qcf_status launch_two_pass(const qcf_layer_desc& L, const ScoreArgs& a, int n_la
   pa.unit_tiles = w.unit_tiles;
   pa.unit_magic = (uint32_t)((1ull << 32) / (unsigned)w.unit_tiles + 1);       // (a request has at most 2^22 tiles, a unit 64)
   pa.n_units = (int)w.n_units;
+  if (left) *left = ScoreSums{pa.s.colsum, a.probe_off, a.total_probe, a.H, a.Hkv, false};
   if (n_layers > 1 || w.unit_tiles > 1 || a.Hkv > 65535)
-    return run_passes<false>(L.head_dim, pa, dim3((unsigned)(w.n_units * n_layers * a.Hkv)), st);
-  return run_passes<true>(L.head_dim, pa.s, dim3((unsigned)w.n_units, (unsigned)a.Hkv), st);
+    return run_passes<false>(L.head_dim, pa, dim3((unsigned)(w.n_units * n_layers * a.Hkv)), st, !left);
+  return run_passes<true>(L.head_dim, pa.s, dim3((unsigned)w.n_units, (unsigned)a.Hkv), st, !left);
 }
 
 ScoreArgs score_args(const qcf_layer_desc& L, int32_t B, const void* q, const int64_t* probe_off, int64_t total_probe,
@@ -1293,7 +1295,7 @@ qcf_status launch_rerope_score(const qcf_layer_desc& L, const qcf_chunk* chunks,
 
 qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const int64_t* probe_off,
                         int64_t total_probe, const void* k, const int64_t* ctx_off, int64_t total_ctx,
-                        const int32_t* probe_limit, float* score, float alpha, float beta, void* ws, hipStream_t st) {
+                        const int32_t* probe_limit, float* score, float alpha, float beta, void* ws, hipStream_t st, ScoreSums* left) {
   const int H = L.n_q_heads, Hkv = L.n_kv_heads, D = L.head_dim;
   if (total_probe == 0) {      // no probe rows at all: every score is 0 (no workspace was asked for)
     const int64_t blocks = (total_ctx + 255) / 256;
@@ -1322,6 +1324,10 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
 #undef QCF_ROWS_OF
       QCF_TRY_LAUNCH("score rows");
     }
+    if (left) {
+      *left = ScoreSums{P, probe_off, total_probe, H, Hkv, true};
+      return QCF_OK;
+    }
     score_colmean_generic<<<dim3((unsigned)col_blocks), dim3(64 * kColWaves), 0, st>>>(P, probe_off, total_probe, ctx_off,
                                                                            total_ctx, B, H, score, alpha, beta);
     return check_launch("score column mean");
@@ -1333,7 +1339,7 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
     QCF_TRY(fused_args(L, a, ws, &fa));
     return probe_limit ? run_fused<true, false>(fa, st) : run_fused<false, false>(fa, st);
   }
-  return launch_two_pass(L, a, 1, &q, &k, &alpha, ws, st);
+  return launch_two_pass(L, a, 1, &q, &k, &alpha, ws, st, left);
 }
 
 // ---- several layers --------------------------------------------------------------------------------

@@ -134,6 +134,22 @@ inline size_t workspace(const qcf_layer_desc& L, int32_t B, int64_t total_probe,
   if (use_two_pass(L, B, total_probe, total_ctx)) return two_pass_bytes(L, B, total_probe, total_ctx);
   return generic_ws(L, total_probe, total_ctx);
 }
+// Where a scoring call is followed by the selection over the same tokens, the selection's workgroup adds up the last sums itself: the
+// KV heads' column sums of the two passes, or the generic path's probability rows.  One request, and no more to read than one
+// compute unit gets through in about the time of the launch that it saves (some 100 KB a microsecond): 192 KB, of the generic
+// path up to 512 tokens, where a token's rows are shared by two threads at least.  Whole layers, us, with the launch and without:
+// heads of 64 (8 KV heads), 40 probe rows over 256 tokens 45.7 and 42.8, 1024 54.3 and 51.4, 4096 (128 KB) 89.3 and 87.1; heads of
+// 128, 100 over 300 64.5 and 61.1, 4096 134.1 and 131.7; f32, 4 heads, 24 rows over 512 (192 KB) 32.0 and 30.4, 8 over 64 32.7 and
+// 30.5.  The other side of the line: f32, 20 over 600 34.6 and 37.5, 8 over 1000 43.2 and 46.5.
+enum SumsOf { kNoSums, kHeads, kRows };
+constexpr int kSumTokens = 4096, kSumRowTokens = 512;
+constexpr size_t kSumBytes = (size_t)192 << 10;
+inline SumsOf sums_in_selection(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx) {
+  if (B != 1 || total_probe <= 0 || total_ctx <= 0 || total_ctx > kSumTokens || use_fused(L, B, total_probe, total_ctx)) return kNoSums;
+  if (use_two_pass(L, B, total_probe, total_ctx)) return (size_t)L.n_kv_heads * total_ctx * sizeof(float) <= kSumBytes ? kHeads : kNoSums;
+  return total_ctx <= kSumRowTokens && generic_ws(L, total_probe, total_ctx) <= kSumBytes ? kRows : kNoSums;
+}
+
 // Layers scored by one set of launches: as many as keep the workspace within that of a single call, or 64 MiB.  One where
 // the two passes do not apply.
 inline int layers_at_once(const qcf_layer_desc& L, int32_t n_layers, int32_t B, int64_t total_probe, int64_t total_ctx) {

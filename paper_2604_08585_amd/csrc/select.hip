@@ -9,6 +9,7 @@
 // over all keys, contiguous keys per thread and outputs stored one by one, and now: 731 keys 5.9 and 3.8, 4096 8.5 and 5.1,
 // 8192 10.5 and 6.5, 32768 25.8 and 14.7, 40000 137 and 26.9; 18 requests of 2000 to 16000 21.0 and 12.0.
 #include "qcf_internal.h"
+#include "score_layout.h"
 
 namespace qcf {
 namespace {
@@ -380,6 +381,87 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
 #undef QCF_SELECT
 }
 
+// Selection of one request whose scores its workgroup adds up first, in the order of the scoring's own kernels and with their bits,
+// so that no launch of a few workgroups stands between the two.  Bound by the latency of its loads (f32, 80 rows over 512
+// tokens: 7.6 us, 3.5 and 4.0 in two launches and what lies between; with one share of the rows after the other 8.4).
+constexpr int kShares = 8;                   // of the probability rows, one after the other (as in the kernel that adds them alone)
+template <int MAX, bool ROWS>
+__global__ __launch_bounds__(kThreads) void select_sums_kernel(ScoreSums a, float* __restrict__ score, const int64_t* __restrict__ ctx_off,
+                                                               int64_t total_ctx, const int64_t* __restrict__ sel_off, int64_t total_sel,
+                                                               int32_t* __restrict__ sel_idx, int32_t* __restrict__ sel_row,
+                                                               int32_t* __restrict__ sel_pos) {
+  __shared__ SelectLds lds;
+  __shared__ __align__(16) float s[ROWS ? scoring::kSumRowTokens : scoring::kSumTokens];
+  const int tid = threadIdx.x, total = (int)total_ctx;           // (at most the size of s)
+  const int64_t p0 = min(max(a.probe_off[0], (int64_t)0), a.total_probe);
+  const int64_t p1 = min(max(a.probe_off[1], p0), a.total_probe);
+  const int64_t end = ctx_off[1];                                // tokens from here on have no score
+  const float n = (float)((p1 - p0) * a.H);
+  auto put = [&](int j, float sum) {
+    const float v = p1 > p0 ? sum / n : 0.f;
+    s[j] = v;
+    if (j < end) score[j] = v;
+  };
+  if constexpr (ROWS) {
+    float* part = reinterpret_cast<float*>(lds.list);            // [share][token]
+    static_assert(kShares * scoring::kSumRowTokens <= kStage, "within the list");
+    int width = 64;                                              // tokens side by side; the threads behind them take other shares
+    while (width < total) width *= 2;
+    const int j = tid % width, groups = kThreads / width, r0 = (int)(p0 * a.H), r1 = (int)(p1 * a.H), share = (r1 - r0 + kShares - 1) / kShares;
+    constexpr int S = 4, R = 12;                                 // shares, and rows of each, on their way together
+    for (int w0 = tid / width; w0 < kShares; w0 += S * groups) {
+      float acc[S];
+#pragma unroll
+      for (int i = 0; i < S; ++i) acc[i] = 0.f;
+      for (int r = 0; r < share; r += R) {
+        float p[S][R];
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+#pragma unroll
+          for (int u = 0; u < R; ++u)
+            p[i][u] = a.sums[(int64_t)max(min(r0 + (w0 + i * groups) * share + r + u, r1 - 1), 0) * total + min(j, total - 1)];
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+          const int first = r0 + (w0 + i * groups) * share + r, last = min(first - r + share, r1);
+#pragma unroll
+          for (int u = 0; u < R; ++u) acc[i] += first + u < last ? p[i][u] : 0.f;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < S; ++i)
+        if (j < total && w0 + i * groups < kShares) part[(w0 + i * groups) * total + j] = acc[i];
+    }
+    __syncthreads();
+    if (tid < total) {
+      float acc = 0.f;
+#pragma unroll
+      for (int w = 0; w < kShares; ++w) acc += part[w * total + tid];
+      put(tid, acc);
+    }
+  } else {
+    constexpr int U = MAX;                                       // tokens of a thread, kThreads apart
+    float acc[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc[u] = 0.f;
+#pragma unroll 8
+    for (int g = 0; g < a.Hkv; ++g)
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc[u] += a.sums[(int64_t)g * total + min(tid + u * kThreads, total - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (tid + u * kThreads < total) put(tid + u * kThreads, acc[u]);
+  }
+  __syncthreads();
+  const int64_t c0 = min(max(ctx_off[0], (int64_t)0), total_ctx), c1 = min(max(end, c0), total_ctx);
+  const int64_t o0 = min(max(sel_off[0], (int64_t)0), total_sel), o1 = min(max(sel_off[1], o0), total_sel);
+  const int T = (int)(c1 - c0), N = (int)min((int64_t)T, o1 - o0);
+  if (N <= 0) return;
+  int seg = (T + kThreads - 1) / kThreads;
+  if (seg > 1) seg = (seg + 3) & ~3;
+  if (MAX == 1 || seg > 1) select_request<MAX>(lds, s + c0, c0, T, N, seg, o0, 0, sel_idx, sel_row, sel_pos);
+  else select_request<1>(lds, s + c0, c0, T, N, seg, o0, 0, sel_idx, sel_row, sel_pos);
+}
+
 // Offline anchors: Top-N of a chunk, then its key and value rows, by the workgroup that selected them.  Bound by latency: the
 // offsets of up to kAnchorChunks chunks travel as kernel arguments (3.6 of the 4 KB a launch can have), so that no copy to
 // the device stands in front of the first kernel and no launch between the selection and the gather.  Whole extraction,
@@ -440,6 +522,17 @@ qcf_status launch_select(int32_t B, const float* score, const int64_t* ctx_off, 
   else if (total_ctx <= 8 * kThreads) QCF_LAUNCH(8);
   else if (total_ctx <= 32 * kThreads) QCF_LAUNCH(32);
   else QCF_LAUNCH(0);
+#undef QCF_LAUNCH
+  return check_launch("select");
+}
+
+qcf_status launch_select_sums(const ScoreSums& sums, float* score, const int64_t* ctx_off, int64_t total_ctx, const int64_t* sel_off,
+                              int64_t total_sel, int32_t* sel_idx, int32_t* sel_row, int32_t* sel_pos, hipStream_t st) {
+#define QCF_LAUNCH(MAX, ROWS) \
+  select_sums_kernel<MAX, ROWS><<<dim3(1), dim3(kThreads), 0, st>>>(sums, score, ctx_off, total_ctx, sel_off, total_sel, sel_idx, sel_row, sel_pos)
+  if (sums.rows) QCF_LAUNCH(1, true);
+  else if (total_ctx <= kThreads) QCF_LAUNCH(1, false);
+  else QCF_LAUNCH(4, false);
 #undef QCF_LAUNCH
   return check_launch("select");
 }

@@ -32,6 +32,9 @@ extern "C" void attention_workspace(const qcf_layer_desc* L, int B, long long ro
 extern "C" int takes_rerope(const qcf_layer_desc* L, int B, int n_chunks, long long probes, long long tokens) {
   return qcf::scoring::takes_rerope(*L, B, n_chunks, probes, tokens);
 }
+extern "C" int sums_in_selection(const qcf_layer_desc* L, int B, long long probes, long long tokens) {
+  return qcf::scoring::sums_in_selection(*L, B, probes, tokens);
+}
 extern "C" long long side_rows(const qcf_layer_desc* L, long long rows, int n_chunks, long long tokens, long long workspace) {
   return qcf::gemm::side_rows(*L, rows, n_chunks, tokens, workspace).all;
 }
@@ -69,6 +72,12 @@ def attention_workspace(H, Hkv, D, T, sel, have=0):
 def rerotates_in_scoring(L):
     """Whether a scored pipeline.DeviceLayer is re-rotated by its scoring kernel (csrc/score_layout.h)."""
     return bool(_library().takes_rerope(C.byref(L.desc), L.B, L.n_chunks, C.c_longlong(L.total_probe), C.c_longlong(L.total_ctx)))
+
+
+def sums_in_selection(L):
+    """What the selection adds up of a pipeline.DeviceLayer's scoring (csrc/score_layout.h): 0 nothing, 1 column sums of the heads, 2
+    probability rows."""
+    return _library().sums_in_selection(C.byref(L.desc), L.B, C.c_longlong(L.total_probe), C.c_longlong(L.total_ctx))
 
 
 def rows_beside_projection(L):

@@ -118,13 +118,13 @@ def test_the_rules_are_asked_for_this_chip():
 
 
 def _layer(lens, gaps, R, style, H=8, Hkv=2, dm=256, before=0, behind=0, src0=0, probes=True, seed=0, D=128,
-           N=None):
+           N=None, dtype="bf16"):
     """One request of `lens`-token chunks with gaps[i] uncovered rows in front of chunk i; `before` / `behind` rows of the cache
     lie outside the request."""
-    dev, dt = torch.device("cuda:0"), torch.bfloat16
+    dev, dt = torch.device("cuda:0"), inputs.torch_dtype(dtype)
     g = torch.Generator(device=dev).manual_seed(seed)
     rnd = lambda *s: torch.randn(s, generator=g, device=dev, dtype=dt)
-    sh = inputs.LayerShape(dm, H, Hkv, D, 500000.0, "bf16", style)
+    sh = inputs.LayerShape(dm, H, Hkv, D, 500000.0, dtype, style)
     desc = qb.make_desc(sh)
     table, keep, row = [], [], 0
     for n, gap in zip(lens, gaps):
@@ -303,3 +303,31 @@ def test_which_layers_are_joined():
     assert beside(1, 3, 24, 731, 110) == 731 and beside(1, 16, 80, 8192, 410) == 8192 and beside(16, 256, 80, 8192, 410) == 8192
     assert 0 < beside(1, 16, 80, 8192, 1229) < 8192
     assert not any([beside(1, 257, 80, 8192, 410), beside(1, 16, 80, 8192, 1500), beside(1, 4, 20, 512, 77, dtype="f32")])
+
+
+F32 = dict(dtype="f32", H=4, Hkv=2, D=64, R=20)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lens,kw,kind", [
+    ([300, 212], F32, 2), ([33], F32, 2), ([65], dict(F32, R=1), 2), ([200], dict(F32, R=3, H=3, Hkv=1), 2),
+    ([100, 300], dict(F32, before=30, behind=50), 2),            # cache rows outside the request
+    ([512], dict(F32, R=24), 2), ([512], dict(F32, R=25), 0), ([513], F32, 0),
+    ([90], dict(F32, probes=False), 2), ([40], dict(F32, D=128, N=40), 2),
+    ([4096], dict(H=16, Hkv=8, D=64, R=40), 1), ([4097], dict(H=16, Hkv=8, D=64, R=40), 0),
+    ([1024], dict(H=8, Hkv=2, D=64, R=9), 1), ([700, 325], dict(H=16, Hkv=2, R=60), 1),      # more rows than the single kernel takes
+    ([1, 2], dict(H=8, Hkv=8, D=64, R=1), 1), ([900], dict(H=8, Hkv=2, D=64, probes=False, R=4), 1)])
+def test_last_sums_in_the_selection(lens, kw, kind):
+    print(f"sums in the selection {lens} {kw}", flush=True)
+    L = _layer(lens, [0] * len(lens), style=0, **dict(dict(R=24), **kw))
+    assert host_rules.sums_in_selection(L) == kind
+    res = []
+    for run in (lambda: [fn(L) for _, fn in pipeline.FUSED_STEPS], lambda: pipeline.enqueue_layer(L)):
+        L.ws_score.fill_(0)                                      # (tokens outside the request are scored from what is there)
+        for name in OUTS:
+            getattr(L, name).fill_(1)
+        run()
+        torch.cuda.synchronize()
+        res.append([getattr(L, name).clone() for name in OUTS])
+    for name, a, b in zip(OUTS, *res):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
