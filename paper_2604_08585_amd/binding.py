@@ -123,11 +123,10 @@ def load_library() -> C.CDLL:
     lib.qcf_score_layers_workspace_bytes.argtypes = [dp, i32, i32, i64, i64]
     lib.qcf_score_layers.restype = C.c_int
     lib.qcf_score_layers.argtypes = [dp, i32, i32, pp, vp, i64, pp, vp, i64, vp, C.POINTER(C.c_float), vp, vp, sz, vp]
-    op = C.POINTER(i64)
     lib.qcf_extract_anchors_workspace_bytes.restype = sz
     lib.qcf_extract_anchors_workspace_bytes.argtypes = [dp, i32, i64]
     lib.qcf_extract_anchors.restype = C.c_int
-    lib.qcf_extract_anchors.argtypes = [dp, vp, vp, i32, op, op, vp, vp, vp, vp, sz, vp]
+    lib.qcf_extract_anchors.argtypes = [dp, vp, vp, i32, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.qcf_fuse_layer.restype = C.c_int
     lib.qcf_fuse_layer.argtypes = [dp, C.c_char_p, i32, vp]
     lib.qcf_key_norm.restype = C.c_int
@@ -418,9 +417,7 @@ def qcf_extract_anchors(desc: LayerDesc, k: torch.Tensor, v: torch.Tensor, ctx_o
     if workspace is None:
         workspace = _workspace(int(lib.qcf_extract_anchors_workspace_bytes(C.byref(desc), n, int(ctx_off[n]))), k.device)
     wp, wn = _ws_args(workspace)
-    op = C.POINTER(C.c_int64)
-    _check(lib.qcf_extract_anchors(C.byref(desc), _ptr(k), _ptr(v), n, ctx_off.ctypes.data_as(op), sel_off.ctypes.data_as(op),
-                                   _ptr(rows), _ptr(k_out), _ptr(v_out), wp, wn, _stream()))
+    _check(lib.qcf_extract_anchors(C.byref(desc), _ptr(k), _ptr(v), n, ctx_off.ctypes.data, sel_off.ctypes.data, _ptr(rows), _ptr(k_out), _ptr(v_out), wp, wn, _stream()))
 
 
 def qcf_key_norm(desc: LayerDesc, k: torch.Tensor, rows: int, norm: torch.Tensor) -> None:

@@ -8,6 +8,8 @@
 // instructions of one compute unit.  One launch of many, 15 % of T keys selected, us, with a radix select of 9 bits to a pass
 // over all keys, contiguous keys per thread and outputs stored one by one, and now: 731 keys 5.9 and 3.8, 4096 8.5 and 5.1,
 // 8192 10.5 and 6.5, 32768 25.8 and 14.7, 40000 137 and 26.9; 18 requests of 2000 to 16000 21.0 and 12.0.
+#include <type_traits>
+
 #include "qcf_internal.h"
 #include "score_layout.h"
 
@@ -466,13 +468,14 @@ __global__ __launch_bounds__(kThreads) void select_sums_kernel(ScoreSums a, floa
 // offsets of up to kAnchorChunks chunks travel as kernel arguments (3.6 of the 4 KB a launch can have), so that no copy to
 // the device stands in front of the first kernel and no launch between the selection and the gather.  Whole extraction,
 // us, with four operations on the stream and now: 64 chunks of 512, 26 rows each, 46 and 27; 4 chunks of 64 40 and 27.
-constexpr int kAnchorChunks = 448;
+constexpr int kAnchorChunks = 448, kFewChunks = 64;              // (few: half a kilobyte of arguments to hand over, not 3.6)
+template <int N>
 struct AnchorChunks {
-  int32_t ctx[kAnchorChunks + 1], sel[kAnchorChunks + 1];        // inside the totals (at most 2^30 rows)
+  int32_t ctx[N + 1], sel[N + 1];                                // inside the totals (at most 2^30 rows)
 };
 
-template <int MAX>
-__global__ __launch_bounds__(kThreads) void select_gather_kernel(const float* __restrict__ score, AnchorChunks ch,
+template <int MAX, int CHUNKS>
+__global__ __launch_bounds__(kThreads) void select_gather_kernel(const float* __restrict__ score, AnchorChunks<CHUNKS> ch,
                                                                  const u32x4* __restrict__ k, const u32x4* __restrict__ v,
                                                                  int vec_per_row, int32_t* rows, u32x4* __restrict__ k_out,
                                                                  u32x4* __restrict__ v_out) {
@@ -556,15 +559,17 @@ qcf_status launch_select_gather(const qcf_layer_desc& L, const float* score, int
     most = std::max(most, std::min(ctx(c + 1) - ctx(c), sel(c + 1) - sel(c)));
   }
   const bool gather = most * vec_per_row <= kGatherVecs;
-  for (int32_t first = 0; first < n_chunks; first += kAnchorChunks) {
-    const int n = std::min(kAnchorChunks, n_chunks - first);
-    AnchorChunks ch;
+  // one launch for the chunks from `first` on, as many as its arguments hold
+  auto launch = [&](int32_t first, auto chunks_c) {
+    constexpr int CHUNKS = decltype(chunks_c)::value;
+    const int n = std::min(CHUNKS, n_chunks - first);
+    AnchorChunks<CHUNKS> ch;
     for (int i = 0; i <= n; ++i) {
       ch.ctx[i] = (int32_t)ctx(first + i);
       ch.sel[i] = (int32_t)sel(first + i);
     }
 #define QCF_LAUNCH(MAX)                                                                              \
-  select_gather_kernel<MAX><<<dim3((unsigned)n), dim3(kThreads), 0, st>>>(                           \
+  select_gather_kernel<MAX, CHUNKS><<<dim3((unsigned)n), dim3(kThreads), 0, st>>>(                   \
       score, ch, static_cast<const u32x4*>(k), static_cast<const u32x4*>(v), vec_per_row, rows,      \
       gather ? static_cast<u32x4*>(k_out) : nullptr, static_cast<u32x4*>(v_out))
     if (longest <= kThreads) QCF_LAUNCH(1);
@@ -572,8 +577,11 @@ qcf_status launch_select_gather(const qcf_layer_desc& L, const float* score, int
     else if (longest <= 32 * kThreads) QCF_LAUNCH(32);
     else QCF_LAUNCH(0);
 #undef QCF_LAUNCH
-    QCF_TRY_LAUNCH("anchor select");
-  }
+    return check_launch("anchor select");
+  };
+  if (n_chunks <= kFewChunks) QCF_TRY(launch(0, std::integral_constant<int, kFewChunks>{}));
+  else
+    for (int32_t first = 0; first < n_chunks; first += kAnchorChunks) QCF_TRY(launch(first, std::integral_constant<int, kAnchorChunks>{}));
   return gather ? QCF_OK : launch_gather(L, k, v, rows, total_sel, total_ctx, k_out, v_out, st);
 }
 

@@ -282,14 +282,14 @@ def extract_anchors(desc, k: torch.Tensor, v: torch.Tensor, chunk_lens: List[int
     n = len(chunk_lens)
     off = np.zeros((2, n + 1), dtype=np.int64)
     lens = np.asarray(chunk_lens, dtype=np.int64)
-    np.cumsum(lens, out=off[0, 1:])
-    np.cumsum(np.minimum(_counts(n_per_chunk, n), lens), out=off[1, 1:])
+    lens.cumsum(out=off[0, 1:])
+    np.minimum(_counts(n_per_chunk, n), lens).cumsum(out=off[1, 1:])
     total = int(off[1, n])
     row = torch.empty(max(total, 1), dtype=torch.int32, device=dev)
-    ak = torch.empty((max(total, 1),) + tuple(k.shape[1:]), dtype=k.dtype, device=dev)
+    ak = k.new_empty((max(total, 1),) + k.shape[1:])
     av = torch.empty_like(ak)
     qb.qcf_extract_anchors(desc, k, v, off[0], off[1], row, ak, av)
-    return row[:total], ak[:total], av[:total]
+    return (row, ak, av) if total > 0 else (row[:0], ak[:0], av[:0])       # (a view takes a microsecond of the call's twenty)
 
 
 # ------------------------------------------------------------------ layer pipeline: chunk caches streamed from the host

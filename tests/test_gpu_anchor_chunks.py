@@ -38,3 +38,8 @@ def test_extraction_in_one_call(lens, counts, dtype):
     torch.cuda.synchronize()
     assert torch.equal(row, ref) and torch.equal(ak, rk) and torch.equal(av, rv)
     assert torch.equal(ak, k[row.long()]) and torch.equal(av, v[row.long()])
+
+
+@pytest.mark.parametrize("chunks", [63, 64, 65])              # the arguments of a launch hold 64 chunks, or 448
+def test_either_size_of_arguments(chunks):
+    test_extraction_in_one_call([0, 33, 7] * (chunks // 3) + [40] * (chunks % 3), [0, 3, 7] * (chunks // 3) + [5] * (chunks % 3), "bf16")
