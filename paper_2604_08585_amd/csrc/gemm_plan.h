@@ -28,8 +28,8 @@ inline bool use_mfma(const qcf_layer_desc& L) {
 // One workgroup per compute unit, so a launch takes (rounds of workgroups) x (time of one workgroup); the costs per
 // k-tile and per workgroup are measured ones (microseconds, all compute units busy).  A split contraction adds the
 // writing and reading of its partial sums and a launch.
-enum GemmKind { kQuad, kWs256, kWs128, kWs64 };
-constexpr int rows_of(GemmKind kind) { return kind == kWs64 ? 64 : kind == kWs128 ? 128 : 256; }
+enum GemmKind { kWs64, kWs96, kWs128, kWs160, kWs192, kWs224, kWs256, kQuad };       // 64 to 256 x 128; 256 x 256
+constexpr int rows_of(GemmKind kind) { return kind == kWs64 ? 64 : kind == kWs96 ? 96 : kind == kWs128 ? 128 : kind == kWs160 ? 160 : kind == kWs192 ? 192 : kind == kWs224 ? 224 : 256; }
 struct GemmPlan { GemmKind kind; int splits; double us; };
 
 inline double rounds_of(int64_t wgs) {
@@ -45,6 +45,18 @@ inline double ws128_us(int64_t mt, int nb, int nk) {
   const double r = rounds_of(mt * nb);
   return r * (ws128_tile_us(r) * nk + 8.0);
 }
+
+// Tiles of other heights, where they fit one round.  These kernels are bound by their loads: a compute unit has at most 256 lines of
+// 128 bytes on their way (60 GB/s from memory, 115 from the memory-side cache, whatever the depth of the ring), so a k-tile takes
+// the time that its rows and columns take to arrive, and the least height that still fits a round wins.  Calls without and with
+// them, us (weights from memory): 64 rows: K 4096, N 6144 of 300 rows 38.2 and 32.1, K 2048, N 3072 of 615 21.5 and 18.0, K 2816,
+// N 1024 of 2000 30.7 and 23.6, K 1024, N 1024 of 200 and 2000 10.2 and 9.4, 11.5 and 10.9; 96: K 4096, N 6144 of 350 31.9 and 29.6;
+// 160: K 4096, N 4096 of 1229 57.5 and 46.7, K 2048, N 3072 of 1600 34.5 and 28.5; 192: K 4096, N 6144 of 900 57.1 and
+// 50.0; 224: the same of 1100 61.2 and 57.4, K 8192, N 10240 of 615 120 and 110.  In two rounds they lose: K 4096, N 6144 of 410
+// rows in tiles of 64 56 (of 128 39), 1229 in tiles of 160 87 (of 256 62).
+struct Height { GemmKind kind; double tile_us, start_us; };
+constexpr Height kHeights[] = {{kWs64, 0.44, 6.0}, {kWs96, 0.45, 5.5}, {kWs160, 0.61, 8.6}, {kWs192, 0.65, 8.5}, {kWs224, 0.72, 11.0}};
+constexpr int kHeightTiles = 128;        // k-tiles, at most
 
 // 256 x 256 tiles with the contraction in `s` ranges of an even number of k-tiles.  The partial sums leave all at once and
 // are read again by the reduction (7 TB/s both ways: a hundred megabytes stay in the memory-side cache).  Few row tiles
@@ -65,7 +77,7 @@ inline bool quad_split_pays(int64_t mt, int nb, int nk, int s) {
 }
 inline double quad_split_us(int64_t mt, int nb, int nk, int s) {
   const double r = rounds_of(mt * ((nb + 1) / 2) * s);
-  const double t = std::max(r * 1.36 * quad_split_len(nk, s), (double)nb * nk * (kBN * kBK * 2) / 4.6e6) + r * 6.0 + 4.0 +
+  const double t = std::max(r * 1.36 * quad_split_len(nk, s), (double)nb * nk * (kBN * kBK * 2) / 4.6e6) + r * 6.0 + 2.5 +
                    (double)mt * nb * (256 * kBN * 8) * s / 7.0e6;
   return r > 1 ? 0.92 * t : t;
 }
@@ -92,11 +104,18 @@ inline double stream_us(int bm, int nb, int nk, int s, int len) {
          (s > 1 ? 0.25 * s : 0.0);
 }
 
-// the load/compute-split kernels, over nb column blocks, with at most part_bytes of partial sums
-inline GemmPlan plan_ws(int64_t M, int nb, int nk, size_t part_bytes) {
+// the load/compute-split kernels, over nb column blocks, with at most part_bytes of partial sums; `heights`: in tiles of any
+// height (not where the cache is re-rotated beside the product, on the compute units that larger tiles leave idle)
+inline GemmPlan plan_ws(int64_t M, int nb, int nk, size_t part_bytes, bool heights) {
   GemmPlan best{kWs256, 1, ws256_us((M + 255) / 256, nb, nk)};
   const double t128 = ws128_us((M + 127) / 128, nb, nk);
   if (t128 < best.us) best = GemmPlan{kWs128, 1, t128};
+  if (heights && nk <= kHeightTiles)
+    for (const Height& h : kHeights) {
+      const int64_t mt = (M + rows_of(h.kind) - 1) / rows_of(h.kind);
+      const double t = h.tile_us * nk + h.start_us;
+      if (M > 64 && mt * nb <= compute_unit_count() && t < best.us) best = GemmPlan{h.kind, 1, t};
+    }
   const int bm = M <= 64 ? 64 : 128;
   const int64_t tiles = (M + bm - 1) / bm * nb;
   const double c = bm == 64 ? 0.40 : ws128_tile_us(rounds_of(tiles));
@@ -128,8 +147,8 @@ struct ProductPlan { GemmKind kind; int64_t rows; int blocks; GemmPlan rest; dou
 // The 256 x 256 kernel takes k-tiles in pairs, and its lanes address 256 weight rows with 32-bit byte offsets.
 inline bool quad_ok(int nk) { return nk % 2 == 0 && (uint64_t)nk * kBK * 2 * kQuadCols <= (1ull << 32); }
 
-inline ProductPlan plan_product(int64_t M, int nb, int nk, bool by_rows, size_t part_bytes) {
-  const GemmPlan one = plan_ws(M, nb, nk, part_bytes);
+inline ProductPlan plan_product(int64_t M, int nb, int nk, bool by_rows, size_t part_bytes, bool heights = true) {
+  const GemmPlan one = plan_ws(M, nb, nk, part_bytes, heights);
   ProductPlan best{one.kind, 0, 0, one, one.us};                 // (rows and blocks 0: `rest` is everything)
   const int cus = compute_unit_count();
   const int64_t mt = (M + 255) / 256;
@@ -147,7 +166,7 @@ inline ProductPlan plan_product(int64_t M, int nb, int nk, bool by_rows, size_t 
     for (int64_t r = rounds; r >= 1 && r >= rounds - 1; --r) {
       const int qb = (int)(r * cus / mt * 2);
       if (qb <= 0 || qb >= nb) continue;
-      const GemmPlan rest = plan_ws(M, nb - qb, nk, 0);
+      const GemmPlan rest = plan_ws(M, nb - qb, nk, 0, false);
       const double t = quad_us(mt, qb, nk) + rest.us + 2.0;
       if (t < best.us) best = ProductPlan{kQuad, M, qb, rest, t};
     }
@@ -160,7 +179,7 @@ inline ProductPlan plan_product(int64_t M, int nb, int nk, bool by_rows, size_t 
     for (int64_t r = rounds; r >= 1 && r >= rounds - 1; --r) {
       const int64_t tiles = r * cus / units;
       if (tiles <= 0 || tiles >= mt) continue;
-      const GemmPlan rest = plan_ws(M - tiles * 256, nb, nk, part_bytes);
+      const GemmPlan rest = plan_ws(M - tiles * 256, nb, nk, part_bytes, false);
       const double t = (kind == kQuad ? quad_us(tiles, nb, nk) : ws256_us(tiles, nb, nk)) + rest.us + 2.0;
       // (256 x 256 tiles that fill half a round run faster than estimated, 256 x 128 tiles over several rounds slower:
       // 4200 rows, K 4096, N 6144 lost 28 us where 3 us were promised, 1500 rows 7 us where 14 were)
@@ -171,8 +190,8 @@ inline ProductPlan plan_product(int64_t M, int nb, int nk, bool by_rows, size_t 
 }
 
 // workspace a product of M rows x nb column blocks x nk k-tiles can use (not needed: without it the contraction stays whole)
-inline size_t gemm_part_bytes(int64_t M, int nb, int nk) {
-  const ProductPlan p = plan_product(M, nb, nk, true, SIZE_MAX);
+inline size_t gemm_part_bytes(int64_t M, int nb, int nk, bool heights = true) {
+  const ProductPlan p = plan_product(M, nb, nk, true, SIZE_MAX, heights);
   if (p.blocks == nb && p.rows == M) return split_part_bytes(M, nb, 256, p.splits);
   return split_part_bytes(p.blocks == nb ? M - p.rows : M, p.blocks > 0 && p.blocks < nb ? nb - p.blocks : nb,
                           p.rest.kind == kWs64 ? 64 : 128, p.rest.splits);
@@ -193,7 +212,7 @@ inline SideRows side_rows(const qcf_layer_desc& L, int64_t M, int32_t n_chunks, 
   const SideRows none{0, 0};
   if (!use_mfma(L) || M <= 0 || n_chunks > kSideChunks || (uint64_t)total_rows * L.d_model * 2u >= (1ull << 32)) return none;
   const int nb = (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim / kBN;
-  const ProductPlan p = plan_product(M, nb, L.d_model / kBK, true, ws_bytes);
+  const ProductPlan p = plan_product(M, nb, L.d_model / kBK, true, ws_bytes, false);
   if (p.blocks != 0) return none;
   const int bm = rows_of(p.rest.kind);
   const int64_t idle = compute_unit_count() - ws_grid((M + bm - 1) / bm, (int64_t)nb * p.rest.splits);

@@ -1231,9 +1231,14 @@ __global__ __launch_bounds__(256, 1) void qkv_quad_kernel(QkvArgs a) {
 }
 
 typedef WsTile<2, 4, 3> Ws256;         // 256 x 128
-typedef WsTile<1, 4, 4> Ws128;         // 128 x 128
-typedef WsTile<1, 2, 6> Ws64;          //  64 x 128
-static_assert(Ws256::BM == rows_of(kWs256) && Ws128::BM == rows_of(kWs128) && Ws64::BM == rows_of(kWs64) && QuadTile::BN == kQuadCols, "as planned");
+typedef WsTile<1, 7, 3> Ws224;         // and so on, as many stages as the LDS holds
+typedef WsTile<1, 6, 3> Ws192;
+typedef WsTile<1, 5, 4> Ws160;
+typedef WsTile<1, 4, 4> Ws128;
+typedef WsTile<1, 3, 5> Ws96;
+typedef WsTile<1, 2, 6> Ws64;
+static_assert(Ws256::BM == rows_of(kWs256) && Ws224::BM == rows_of(kWs224) && Ws192::BM == rows_of(kWs192) && Ws160::BM == rows_of(kWs160) &&
+              Ws128::BM == rows_of(kWs128) && Ws96::BM == rows_of(kWs96) && Ws64::BM == rows_of(kWs64) && QuadTile::BN == kQuadCols, "as planned");
 
 // finishes a split launch whose partial sums lie in n_groups groups of 32 rows
 template <int EPI>
@@ -1326,7 +1331,11 @@ qcf_status run_kind(const QkvArgs& a, GemmKind kind, int splits, hipStream_t st)
   switch (kind) {
     case kQuad: return splits > 1 ? run_quad<EPI, true>(a, splits, st) : run_quad<EPI, false>(a, 1, st);
     case kWs64: return run_ws<Ws64, EPI, false>(a, splits, st);
+    case kWs96: return run_ws<Ws96, EPI, false>(a, 1, st);
     case kWs128: return run_ws<Ws128, EPI, false>(a, splits, st);
+    case kWs160: return run_ws<Ws160, EPI, false>(a, 1, st);
+    case kWs192: return run_ws<Ws192, EPI, false>(a, 1, st);
+    case kWs224: return run_ws<Ws224, EPI, false>(a, 1, st);
     default: return run_ws<Ws256, EPI, false>(a, splits, st);
   }
 }
@@ -1342,7 +1351,7 @@ qcf_status run_gemm(const QkvArgs& a_in, int nb, void* ws, size_t ws_bytes, hipS
   // (x of 4 GiB and more needs 64-bit addresses per lane: one variant, such calls have plenty of rows)
   if (wide) return run_ws<Ws128, EPI, true>(a, 1, st);
   // (rows that x does not have read its first row: x must not be moved then)
-  const ProductPlan p = plan_product(a.M, nb, nk, a.gather || a.x_rows >= a.M, ws_bytes);
+  const ProductPlan p = plan_product(a.M, nb, nk, a.gather || a.x_rows >= a.M, ws_bytes, a.side.rows == 0);
   if (p.blocks == 0) return run_kind<EPI>(a, p.rest.kind, p.rest.splits, st);
   QkvArgs first = a;
   first.M = p.rows;
@@ -1359,7 +1368,10 @@ qcf_status run_gemm(const QkvArgs& a_in, int nb, void* ws, size_t ws_bytes, hipS
 
 size_t qkv_workspace(const qcf_layer_desc& L, int64_t M) {
   // (the MFMA path needs none; what it asks for lets small M split the contraction)
-  if (use_mfma(L)) return gemm_part_bytes(M, (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim / kBN, L.d_model / kBK);
+  if (use_mfma(L)) {
+    const int nb = (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim / kBN, nk = L.d_model / kBK;
+    return std::max(gemm_part_bytes(M, nb, nk), gemm_part_bytes(M, nb, nk, false));       // (either may be taken, see side_rows)
+  }
   return align_up((size_t)M * (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim * sizeof(float), 256);
 }
 

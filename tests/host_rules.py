@@ -35,6 +35,11 @@ extern "C" int takes_rerope(const qcf_layer_desc* L, int B, int n_chunks, long l
 extern "C" int sums_in_selection(const qcf_layer_desc* L, int B, long long probes, long long tokens) {
   return qcf::scoring::sums_in_selection(*L, B, probes, tokens);
 }
+extern "C" int tile_rows(long long rows, int columns, int contraction, long long workspace) {
+  using namespace qcf::gemm;
+  const ProductPlan p = plan_product(rows, columns / kBN, contraction / kBK, true, workspace);
+  return p.blocks != 0 || p.rest.splits > 1 ? 0 : rows_of(p.rest.kind);
+}
 extern "C" long long side_rows(const qcf_layer_desc* L, long long rows, int n_chunks, long long tokens, long long workspace) {
   return qcf::gemm::side_rows(*L, rows, n_chunks, tokens, workspace).all;
 }
@@ -78,6 +83,11 @@ def sums_in_selection(L):
     """What the selection adds up of a pipeline.DeviceLayer's scoring (csrc/score_layout.h): 0 nothing, 1 column sums of the heads, 2
     probability rows."""
     return _library().sums_in_selection(C.byref(L.desc), L.B, C.c_longlong(L.total_probe), C.c_longlong(L.total_ctx))
+
+
+def tile_rows(M, N, K, workspace=0):
+    """Rows of a tile of a bf16 product in one undivided launch (csrc/gemm_plan.h); 0: divided, or 256 x 256 tiles."""
+    return _library().tile_rows(C.c_longlong(M), N, K, C.c_longlong(workspace))
 
 
 def rows_beside_projection(L):

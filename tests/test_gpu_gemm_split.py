@@ -5,6 +5,7 @@ import ctypes as C
 import pytest
 import torch
 
+import host_rules
 from paper_2604_08585_amd import binding as qb
 from paper_2604_08585_amd import inputs
 from gpu_util import DEV
@@ -195,3 +196,45 @@ def test_rotation_behind_the_reduction(M, D, style, far):
         ref = torch.full_like(fused, 7.0)
         ref[dst.long()] = new[:M]
         assert torch.equal(fused, ref)
+
+
+@pytest.mark.parametrize("M,K,height", [
+    (65, 4096, 64), (320, 4096, 64), (321, 4096, 96), (480, 4096, 96), (481, 4096, 128), (641, 4096, 160), (800, 4096, 160),
+    (801, 4096, 192), (960, 4096, 192), (961, 4096, 224), (1120, 4096, 224), (1121, 4096, 256), (300, 64, 96), (700, 8192, 160)])
+def test_tiles_of_every_height(M, K, height):
+    """Launches that fit one round in tiles of 64 to 256 rows: a whole last tile and one of a single row, fewer k-tiles than stages; a
+    row's bits are those of a launch of few rows."""
+    dm, H, Hkv, D = K, 32, 8, 128
+    print(f"tiles of {height} rows M={M} K={K}", flush=True)
+    sh = inputs.LayerShape(dm, H, Hkv, D, 500000.0, "bf16")
+    desc, lib = qb.make_desc(sh), qb.load_library()
+    assert host_rules.tile_rows(M, sh.qkv_rows, K) == height
+    x, w = _normal(20, M, dm), _normal(21, sh.qkv_rows, dm, std=dm ** -0.5)
+    g = torch.Generator(device=DEV).manual_seed(22)
+    gather = torch.randperm(M, generator=g, device=DEV).int()
+    gather[M // 3] = -1                                      # outside x: a zero row
+    pos = torch.randint(0, 40000, (M,), generator=g, device=DEV).int()
+    dst = torch.randperm(M, generator=g, device=DEV).int()
+
+    def project(first, rows):
+        q, k, v = (torch.full((rows + 1, h, D), 7.0, dtype=BF, device=DEV) for h in (H, Hkv, Hkv))
+        kf, vf = (torch.full((M, Hkv, D), 7.0, dtype=BF, device=DEV) for _ in range(2))
+        part = [t[first:first + rows].contiguous() for t in (gather, pos, dst)]
+        st = torch.cuda.current_stream().cuda_stream
+        assert lib.qcf_recompute_qkv_scatter(C.byref(desc), x.data_ptr(), M, part[0].data_ptr(), rows, w.data_ptr(), part[1].data_ptr(),
+                                             q.data_ptr(), k.data_ptr(), v.data_ptr(), part[2].data_ptr(), kf.data_ptr(), vf.data_ptr(),
+                                             M, None, 0, st) == 0
+        torch.cuda.synchronize()
+        assert all(bool((t[rows] == 7.0).all()) for t in (q, k, v))
+        assert torch.equal(kf[part[2].long()], k[:rows]) and torch.equal(vf[part[2].long()], v[:rows])
+        return [t[:rows] for t in (q, k, v)]
+
+    whole = project(0, M)
+    for first in (0, M - min(M, 64)):
+        rows = min(M, 64)
+        assert host_rules.tile_rows(rows, sh.qkv_rows, K) in (64, 128)
+        for a, b in zip(whole, project(first, rows)):
+            assert torch.equal(a[first:first + rows], b)
+    y = x[gather.clamp(min=0).long()].float() @ w.float().T
+    y[M // 3] = 0
+    _one_rounding(whole[2].flatten(1), y[:, (H + Hkv) * D:])
