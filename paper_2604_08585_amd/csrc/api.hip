@@ -394,12 +394,13 @@ qcf_status qcf_recompute_attn(const qcf_layer_desc* desc, int32_t B, const void*
 qcf_status qcf_fuse_layer(const qcf_layer_desc* desc, const qcf_layer_buffers* layer, int32_t critical, void* stream) {
   if (!layer) return fail(QCF_ERR_INVALID_ARG, "layer buffers are NULL");
   const qcf_layer_buffers& b = *layer;
-  // One request in the single scoring kernel: it turns the keys itself.  (Only where scoring will not fail: the cache is whole
+  // One request in the single scoring kernel, or in pass 1 of two: it turns the keys itself.  (Only where scoring will not fail: the cache is whole
   // otherwise.)
   bool empty = false;
   QCF_TRY(check_rerope_args(desc, b.chunks_dev, b.n_chunks, b.total_ctx, b.k_fused, b.v_fused, b.rerope_ws, b.rerope_ws_bytes));
   const bool joined = critical && b.total_ctx > 0 && b.v_fused &&
-                      scoring::takes_rerope(*desc, b.B, b.n_chunks, b.total_probe, b.total_ctx) &&
+                      (scoring::takes_rerope(*desc, b.B, b.n_chunks, b.total_probe, b.total_ctx) ||
+                       scoring::pass1_takes_rerope(*desc, b.B, b.n_chunks, b.total_probe, b.total_ctx)) &&
                       check_score_args(desc, b.B, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.ctx_off_dev, b.total_ctx,
                                        nullptr, b.score, &empty) == QCF_OK &&
                       need_ws(b.score_ws, b.score_ws_bytes, scoring::workspace(*desc, b.B, b.total_probe, b.total_ctx)) == QCF_OK;
@@ -407,22 +408,24 @@ qcf_status qcf_fuse_layer(const qcf_layer_desc* desc, const qcf_layer_buffers* l
   const bool beside = !critical && b.n_chunks > 0 && b.total_ctx > 0 && b.total_sel > 0 &&
                       check_qkv_scatter_args(desc, b.x, b.total_ctx, b.sel_row, b.total_sel, b.w_qkv, b.sel_pos, b.q_sel, b.k_sel, b.v_sel,
                                              b.sel_row, b.k_fused, b.v_fused, b.total_ctx, b.qkv_ws, b.qkv_ws_bytes) == QCF_OK;
-  if (joined)
-    QCF_TRY(launch_rerope_score(*desc, b.chunks_dev, b.n_chunks, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.v_fused,
-                                b.ctx_off_dev, b.total_ctx, b.score, b.score_ws, (hipStream_t)stream));
-  else if (!beside)
-    QCF_TRY(qcf_rerope(desc, b.chunks_dev, b.n_chunks, b.total_ctx, b.k_fused, b.v_fused, b.rerope_ws, b.rerope_ws_bytes, stream));
   // Scores whose last sums the selection adds up itself (only where both calls will not fail).
-  if (critical && !joined && b.total_sel > 0 &&
-      scoring::sums_in_selection(*desc, b.B, b.total_probe, b.total_ctx) != scoring::kNoSums &&
+  const bool sums_left =
+      critical && b.total_sel > 0 && scoring::sums_in_selection(*desc, b.B, b.total_probe, b.total_ctx) != scoring::kNoSums &&
       check_score_args(desc, b.B, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.ctx_off_dev, b.total_ctx, nullptr, b.score,
                        &empty) == QCF_OK &&
       need_ws(b.score_ws, b.score_ws_bytes, scoring::workspace(*desc, b.B, b.total_probe, b.total_ctx)) == QCF_OK &&
       check_select_args(b.B, b.score, b.ctx_off_dev, b.total_ctx, b.sel_off_dev, b.total_sel, nullptr, b.sel_idx, b.sel_row, b.sel_pos,
-                        b.select_ws, b.select_ws_bytes) == QCF_OK) {
-    ScoreSums sums{};
-    QCF_TRY(launch_score(*desc, b.B, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.ctx_off_dev, b.total_ctx, nullptr, b.score,
-                         1.f, 0.f, b.score_ws, (hipStream_t)stream, &sums));
+                        b.select_ws, b.select_ws_bytes) == QCF_OK;
+  ScoreSums sums{};
+  if (joined)
+    QCF_TRY(launch_rerope_score(*desc, b.chunks_dev, b.n_chunks, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.v_fused,
+                                b.ctx_off_dev, b.total_ctx, b.score, b.score_ws, (hipStream_t)stream, sums_left ? &sums : nullptr));
+  else if (!beside)
+    QCF_TRY(qcf_rerope(desc, b.chunks_dev, b.n_chunks, b.total_ctx, b.k_fused, b.v_fused, b.rerope_ws, b.rerope_ws_bytes, stream));
+  if (sums_left) {
+    if (!joined)
+      QCF_TRY(launch_score(*desc, b.B, b.q_probe, b.probe_off_dev, b.total_probe, b.k_fused, b.ctx_off_dev, b.total_ctx, nullptr, b.score,
+                           1.f, 0.f, b.score_ws, (hipStream_t)stream, &sums));
     QCF_TRY(launch_select_sums(sums, b.score, b.ctx_off_dev, b.total_ctx, b.sel_off_dev, b.total_sel, b.sel_idx, b.sel_row, b.sel_pos,
                                (hipStream_t)stream));
   } else if (critical) {

@@ -279,7 +279,7 @@ qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const
 // re-rotation and scoring of one request in one launch, where scoring::takes_rerope
 qcf_status launch_rerope_score(const qcf_layer_desc& L, const qcf_chunk* chunks, int32_t n_chunks, const void* q,
                                const int64_t* probe_off, int64_t total_probe, void* k, void* v, const int64_t* ctx_off,
-                               int64_t total_ctx, float* score, void* ws, hipStream_t st);
+                               int64_t total_ctx, float* score, void* ws, hipStream_t st, ScoreSums* left);
 
 qcf_status launch_score_layers(const qcf_layer_desc& L, int32_t n_layers, int32_t B, const void* const* q,
                                const int64_t* probe_off, int64_t total_probe, const void* const* k, const int64_t* ctx_off,

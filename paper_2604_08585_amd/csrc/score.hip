@@ -409,10 +409,141 @@ __device__ __forceinline__ bool locate_unit(const PassArgs& a, Unit& u) {
 
 constexpr int kTilesPerWave = (kRowBlock / 32 + kRowGroups - 1) / kRowGroups;      // row tiles of a wave, at most
 
+struct Rerotation {
+  const qcf_chunk* chunks;
+  int n_chunks, style;
+  double neg2_over_d_log2base;
+  bf16_t* k;                 // the fused cache, keys (s.k) and values
+  bf16_t* v;
+};
+
+template <int D> constexpr size_t kPass1Lds = kQBytes<D> + kKBytes<D> + (size_t)kTokWaves * kRowBlock * sizeof(float2);
+// Re-rotation of a unit's tile inside pass 1 (RR; heads of 64): the chunk table, each row's chunk and sources, and the pairs
+// of the tile's chunks, behind pass 1's own LDS.
+struct Pass1Rot {
+  qcf_chunk table[kMaxRotChunks];
+  const char* k[kTokPerWg];                       // source of a row, for this KV head (row of no chunk: itself)
+  const char* v[kTokPerWg];
+  int chunk[kTokPerWg];                           // last chunk that starts at or before a row
+  bool covered[kTokPerWg];
+  float2 cs[kMaxRotChunks * 32];
+};
+static_assert(sizeof(qcf_chunk) % 8 == 0, "copied in words of 8 bytes");
+struct NoRerotation {};
+template <bool RR> using RerotationOf = typename std::conditional<RR, Rerotation, NoRerotation>::type;
+
+// One tile of one KV head by the whole workgroup: four threads to a row, two 16-byte vectors of keys (the partners of eight pairs) and of
+// values each.  Keys are turned and left in LDS as load_key_frags wants them; store() then writes both to the cache, at the end of the
+// kernel, where nothing waits for the stores.
+struct TileRerotation {
+  static constexpr int D = 64, kItems = (4 * kTokPerWg + kThreads - 1) / kThreads;
+  u32x4 vals[kItems][2];
+  int e0, de;                                     // first elements of a thread's two vectors
+  // beside: loads of something else, requested behind the keys' and the values' (in front of them the barriers would wait for it)
+  template <typename F>
+  __device__ __forceinline__ void load(const Rerotation& r, Pass1Rot& rot, const ScoreArgs& a, const Unit& u, unsigned char* sK, F&& beside) {
+    const int tid = threadIdx.x, n = min(kTokPerWg, u.T - u.tile0 * kTokPerWg);      // rows of the tile
+    const int64_t row0 = u.c0 + (int64_t)u.tile0 * kTokPerWg, row_elems = (int64_t)a.Hkv * D;
+    if (tid < n) {
+      const int64_t row = row0 + tid;
+      const int c = chunk_of(rot.table, r.n_chunks, row);
+      const qcf_chunk& ch = rot.table[c];
+      const bool covered = row >= ch.dst_row && row < ch.dst_row + ch.len;
+      const int64_t off = ((covered ? row - ch.dst_row : row) * row_elems + u.g * D) * 2;
+      rot.k[tid] = static_cast<const char*>(covered ? ch.k_src : r.k) + off;
+      rot.v[tid] = static_cast<const char*>(covered ? ch.v_src : r.v) + off;
+      rot.chunk[tid] = c;
+      rot.covered[tid] = covered;
+    }
+    __syncthreads();
+    const int p0 = 8 * (tid & 3);                 // (kThreads is a multiple of four: the same piece of every row)
+    e0 = r.style == 0 ? p0 : 2 * p0;
+    de = r.style == 0 ? D / 2 : 8;
+    u32x4 keys[kItems][2];
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      const int row = (tid + i * kThreads) >> 2;
+      if (row < n) {
+        keys[i][0] = *reinterpret_cast<const u32x4*>(rot.k[row] + 2 * e0);
+        keys[i][1] = *reinterpret_cast<const u32x4*>(rot.k[row] + 2 * (e0 + de));
+        vals[i][0] = *reinterpret_cast<const u32x4*>(rot.v[row] + 2 * e0);
+        vals[i][1] = *reinterpret_cast<const u32x4*>(rot.v[row] + 2 * (e0 + de));
+      }
+    }
+    beside();
+    const int first = rot.chunk[0], n_mine = rot.chunk[n - 1] - first + 1;
+    for (int i = tid; i < n_mine * (D / 2); i += kThreads)
+      rot.cs[i] = shift_pair(rot.table[first + i / (D / 2)], r.neg2_over_d_log2base, i % (D / 2));
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      const int row = (tid + i * kThreads) >> 2;
+      if (row >= kTokPerWg) continue;
+      if (row >= n) {                             // (masked tokens)
+        keys[i][0] = mk4(0, 0, 0, 0);
+        keys[i][1] = mk4(0, 0, 0, 0);
+      } else if (rot.covered[row]) {
+        const float2* cs = rot.cs + (rot.chunk[row] - first) * (D / 2) + p0;
+        float f[16], o[16];
+        Vec16<bf16_t>::unpack(keys[i][0], f);
+        Vec16<bf16_t>::unpack(keys[i][1], f + 8);
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+          float x, y;
+          turn_pair(r.style == 0 ? f[p] : f[2 * p], r.style == 0 ? f[p + 8] : f[2 * p + 1], cs[p], x, y);
+          if (r.style == 0) { o[p] = x; o[p + 8] = y; }
+          else { o[2 * p] = x; o[2 * p + 1] = y; }
+        }
+        keys[i][0] = Vec16<bf16_t>::pack(o);
+        keys[i][1] = Vec16<bf16_t>::pack(o + 8);
+      }
+      *reinterpret_cast<u32x4*>(sK + row * 2 * D + slot_of<D>(e0 / 8, row) * 16) = keys[i][0];
+      *reinterpret_cast<u32x4*>(sK + row * 2 * D + slot_of<D>((e0 + de) / 8, row) * 16) = keys[i][1];
+    }
+  }
+  __device__ __forceinline__ void store(const Rerotation& r, const Pass1Rot& rot, const ScoreArgs& a, const Unit& u, const unsigned char* sK) const {
+    const int tid = threadIdx.x, n = min(kTokPerWg, u.T - u.tile0 * kTokPerWg);
+    const int64_t row0 = u.c0 + (int64_t)u.tile0 * kTokPerWg, row_elems = (int64_t)a.Hkv * D;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      const int row = (tid + i * kThreads) >> 2;
+      if (row >= n || !rot.covered[row]) continue;
+      const int64_t dst = (row0 + row) * row_elems + u.g * D + e0;
+      *reinterpret_cast<u32x4*>(r.k + dst) = *reinterpret_cast<const u32x4*>(sK + row * 2 * D + slot_of<D>(e0 / 8, row) * 16);
+      *reinterpret_cast<u32x4*>(r.k + dst + de) = *reinterpret_cast<const u32x4*>(sK + row * 2 * D + slot_of<D>((e0 + de) / 8, row) * 16);
+      *reinterpret_cast<u32x4*>(r.v + dst) = vals[i][0];
+      *reinterpret_cast<u32x4*>(r.v + dst + de) = vals[i][1];
+    }
+  }
+};
+
+// One row and KV head that no tile covers (cache rows outside the request), by one wave.
+template <int D>
+__device__ __forceinline__ void rerotate_row(const Rerotation& r, const qcf_chunk* table, int64_t row, int Hkv, int g, int lane) {
+  const qcf_chunk ch = table[chunk_of(table, r.n_chunks, row)];
+  if (row < ch.dst_row || row >= ch.dst_row + ch.len || lane >= D / 2) return;
+  const int64_t src = (row - ch.dst_row) * Hkv * D + g * D, dst = row * Hkv * D + g * D;
+  const bf16_t* k = static_cast<const bf16_t*>(ch.k_src) + src;
+  const bf16_t* v = static_cast<const bf16_t*>(ch.v_src) + src;
+  const int ia = r.style == 0 ? lane : 2 * lane, ib = r.style == 0 ? lane + D / 2 : 2 * lane + 1;
+  float a, b;
+  turn_pair(bf16_to_f32(k[ia]), bf16_to_f32(k[ib]), shift_pair(ch, r.neg2_over_d_log2base, lane), a, b);
+  r.k[dst + ia] = f32_to_bf16(a);
+  r.k[dst + ib] = f32_to_bf16(b);
+  r.v[dst + lane] = v[lane];
+  r.v[dst + D / 2 + lane] = v[D / 2 + lane];
+}
+
 // Pass 1.  Wave (tw, rg) keeps the 64 tokens of slice tw in registers and takes every third 32-row tile of the staged
 // probe rows, starting with tile rg; a lane keeps the running (max, sum-exp) of its rows over the unit's tiles.
-template <int D, bool LIMIT, bool ONE>
-__global__ __launch_bounds__(kThreads) void score_pass1(Args<ONE> pa) {
+// RR (heads of 64, one request, one tile to a unit): the tile's keys come from the chunk caches, are turned on their way to LDS and
+// written to the cache behind everything else, with the values.  Saves the launch of qcf_rerope and the reading of the keys; a chain
+// of latencies, like score_fused's: 4096 tokens, 40 rows x 32 heads 6.6 + 6.8 us in two launches, 11.4 so (12.5 with the probe rows
+// requested first, which the barriers in front of the keys' loads then wait for).  The layer 86.6 and 84.7 us, 90 tokens 38.3 and
+// 35.9, 1230 53.8 and 52.4, 8000 178.7 and 177.1.
+template <int D, bool LIMIT, bool ONE, bool RR>
+__global__ __launch_bounds__(kThreads) void score_pass1(Args<ONE> pa, RerotationOf<RR> rr) {
+  static_assert(!RR || (D == 64 && ONE && !LIMIT), "the form that re-rotates");
   const ScoreArgs& a = common(pa);
   extern __shared__ __align__(256) unsigned char smem[];      // (fragment addresses are formed with XORs below 256)
   unsigned char* sK = smem + kQBytes<D>;
@@ -422,10 +553,33 @@ __global__ __launch_bounds__(kThreads) void score_pass1(Args<ONE> pa) {
   const int tw = wave % kTokWaves, rg = wave / kTokWaves;
   const uint32_t lds0 = lds_offset_of(smem);
   Unit u;
-  if (!locate_unit(pa, u)) return;
+  Pass1Rot& rot = *reinterpret_cast<Pass1Rot*>(smem + kPass1Lds<D>);     // (RR)
+  if constexpr (RR) {
+    for (int i = tid; i < rr.n_chunks * (int)(sizeof(qcf_chunk) / 8); i += kThreads)
+      reinterpret_cast<uint64_t*>(rot.table)[i] = reinterpret_cast<const uint64_t*>(rr.chunks)[i];
+  }
+  const bool have_unit = locate_unit(pa, u);
+  if constexpr (RR) {
+    __syncthreads();
+    const int64_t lo = min(max(a.ctx_off[0], (int64_t)0), a.total_ctx), hi = min(max(a.ctx_off[1], lo), a.total_ctx);
+    for (int64_t i = (int64_t)blockIdx.x * kWavesPerWg + wave; i < a.total_ctx - (hi - lo); i += (int64_t)gridDim.x * kWavesPerWg)
+      rerotate_row<D>(rr, rot.table, i < lo ? i : i + (hi - lo), a.Hkv, (int)blockIdx.y, lane);
+  }
+  if (!have_unit) return;
   const int64_t p0 = min(max(a.probe_off[u.b], (int64_t)0), a.total_probe);
   const int64_t p1 = min(max(a.probe_off[u.b + 1], p0), a.total_probe);
   const int rows = (int)(p1 - p0) * a.G;         // probe rows x heads of the group
+  TileRerotation turned;
+  if constexpr (RR) {
+    turned.load(rr, rot, a, u, sK, [&] {
+      const int n = min(kRowBlock, rows);
+      if (n > 0) stage_q_async<D>(a, probes_of(pa, u), p0, u.g, 0, n, (n + 31) & ~31, lds0, wave, lane);
+    });
+    if (rows == 0) {
+      __syncthreads();
+      turned.store(rr, rot, a, u, sK);
+    }
+  }
   if (rows == 0) return;
   const bf16_t* q = probes_of(pa, u);
   const KeyLoader<D> keys(keys_of(pa, u) + (u.c0 * a.Hkv + u.g) * D, a.Hkv, u.T, lds0 + (uint32_t)kQBytes<D>, wave, lane);
@@ -436,8 +590,8 @@ __global__ __launch_bounds__(kThreads) void score_pass1(Args<ONE> pa) {
     const int n_rows = min(kRowBlock, rows - r_begin);
     const int n_pad = (n_rows + 31) & ~31;
     __syncthreads();                        // the previous block's rows and partials are no longer read
-    if (ONE && r_begin == 0) keys.load(u.tile0, wave);      // (they stay in LDS)
-    stage_q_async<D>(a, q, p0, u.g, r_begin, n_rows, n_pad, lds0, wave, lane);
+    if (ONE && !RR && r_begin == 0) keys.load(u.tile0, wave);      // (they stay in LDS)
+    if (!RR || r_begin > 0) stage_q_async<D>(a, q, p0, u.g, r_begin, n_rows, n_pad, lds0, wave, lane);
     if (!ONE) keys.load(u.tile0, wave);
     // how many tokens the lane's row of row tile rt sees
     auto limit_of = [&](int rt) {
@@ -532,6 +686,7 @@ __global__ __launch_bounds__(kThreads) void score_pass1(Args<ONE> pa) {
       part[(p0 + i) * a.H + u.g * a.G + hh] = make_float2(m, z);
     }
   }
+  if constexpr (RR) turned.store(rr, rot, a, u, sK);
 }
 
 // Folds a batch of (maximum, sumexp2) partials, in order, into the running pair (m, z).  A partial that saw
@@ -716,14 +871,6 @@ constexpr uint32_t kSpinLimit = 1u << 20;  // polls (a microsecond or two each) 
 __device__ uint32_t g_sync[kSyncSlots * kSyncWords];
 
 // Re-rotation in front of the scoring (RR): the chunks whose keys and values make up the cache that s.k points to.
-struct Rerotation {
-  const qcf_chunk* chunks;
-  int n_chunks, style;
-  double neg2_over_d_log2base;
-  bf16_t* k;                 // the fused cache, keys (s.k) and values
-  bf16_t* v;
-};
-
 struct FusedArgs {
   ScoreArgs s;
   float2* part;        // [tile][Hkv][kRowBlock] (max2, sumexp2) of the tile, published with atomic stores
@@ -761,7 +908,6 @@ struct RotLds {
   int chunk[kTokPerWg];                           // of a row, -1: none
   float2 cs[kRotChunks * 64];
 };
-static_assert(sizeof(qcf_chunk) % 8 == 0, "copied in words of 8 bytes");
 constexpr size_t kFusedRotLds = kFusedLds + sizeof(RotLds);
 static_assert(kFusedRotLds + 1024 <= 160 * 1024, "one workgroup's LDS");
 
@@ -791,22 +937,6 @@ __device__ __forceinline__ void turn_frags(bf16x8 (&kf)[8], const float2* cs, in
       kf[ks] = pack8(o);
     }
   }
-}
-
-// One row and KV head that no tile covers (cache rows outside the request), by one wave.
-__device__ __forceinline__ void rerotate_row(const Rerotation& r, const qcf_chunk* table, int64_t row, int Hkv, int g, int lane) {
-  const qcf_chunk ch = table[chunk_of(table, r.n_chunks, row)];
-  if (row < ch.dst_row || row >= ch.dst_row + ch.len) return;
-  const int64_t src = (row - ch.dst_row) * Hkv * 128 + g * 128, dst = row * Hkv * 128 + g * 128;
-  const bf16_t* k = static_cast<const bf16_t*>(ch.k_src) + src;
-  const bf16_t* v = static_cast<const bf16_t*>(ch.v_src) + src;
-  const int ia = r.style == 0 ? lane : 2 * lane, ib = r.style == 0 ? lane + 64 : 2 * lane + 1;
-  float a, b;
-  turn_pair(bf16_to_f32(k[ia]), bf16_to_f32(k[ib]), shift_pair(ch, r.neg2_over_d_log2base, lane), a, b);
-  r.k[dst + ia] = f32_to_bf16(a);
-  r.k[dst + ib] = f32_to_bf16(b);
-  r.v[dst + lane] = v[lane];
-  r.v[dst + 64 + lane] = v[64 + lane];
 }
 
 // RR: the keys of the tile come from the chunk caches, are turned to their global positions in the registers that score them
@@ -936,7 +1066,7 @@ __global__ __launch_bounds__(kFusedThreads) void score_fused(FusedArgs fa) {
     if (hi - lo < a.total_ctx) {
       __syncthreads();                                  // (the table, where no tile has waited for it)
       for (int64_t i = wg_tile * kFusedWaves + wave; i < a.total_ctx - (hi - lo); i += fa.n_wg_tiles * kFusedWaves)
-        rerotate_row(fa.r, rot.table, i < lo ? i : i + (hi - lo), a.Hkv, g, lane);
+        rerotate_row<128>(fa.r, rot.table, i < lo ? i : i + (hi - lo), a.Hkv, g, lane);
     }
   }
   if (rows > 0) {
@@ -1164,7 +1294,6 @@ __global__ __launch_bounds__(256) void score_zero(float* score, int64_t n, float
   if (j < n) score[j] = (beta == 0.f) ? 0.f : beta * score[j];
 }
 
-template <int D> constexpr size_t kPass1Lds = kQBytes<D> + kKBytes<D> + (size_t)kTokWaves * kRowBlock * sizeof(float2);
 template <int D> constexpr size_t kPass2Lds = kQBytes<D> + kKBytes<D> + kRowBlock * 4 * 3 + (size_t)kRowGroups * kTokPerWg * sizeof(float);
 static_assert((size_t)kFusedWaves * kRowBlock * 8 + (size_t)kRowBlock * 4 + (size_t)kTokPerWg * 4 <= kKBytes<128>,
               "the single-kernel path's tables fit in the key tile's LDS");
@@ -1178,13 +1307,15 @@ qcf_status run_fused(const FusedArgs& fa, hipStream_t st) {
   return check_launch("score (single kernel)");
 }
 
-template <int D, bool LIMIT, bool ONE>
-qcf_status run_two_pass(const Args<ONE>& a, dim3 grid, hipStream_t st, bool reduce) {
+template <int D, bool LIMIT, bool ONE, bool RR = false>
+qcf_status run_two_pass(const Args<ONE>& a, dim3 grid, hipStream_t st, bool reduce, const RerotationOf<RR>& r = {}) {
   static std::atomic<uint64_t> lds_ok[2];
-  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass1<D, LIMIT, ONE>), kPass1Lds<D>, lds_ok[0]));
+  constexpr size_t lds = kPass1Lds<D> + (RR ? sizeof(Pass1Rot) : 0);
+  static_assert(lds + 1024 <= 160 * 1024, "one workgroup's LDS");
+  QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass1<D, LIMIT, ONE, RR>), lds, lds_ok[0]));
   QCF_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(&score_pass2<D, LIMIT, ONE>), kPass2Lds<D>, lds_ok[1]));
   const dim3 block(kThreads);
-  score_pass1<D, LIMIT, ONE><<<grid, block, kPass1Lds<D>, st>>>(a);
+  score_pass1<D, LIMIT, ONE, RR><<<grid, block, lds, st>>>(a, r);
   QCF_TRY_LAUNCH("score pass 1");
   score_pass2<D, LIMIT, ONE><<<grid, block, kPass2Lds<D>, st>>>(a);
   QCF_TRY_LAUNCH("score pass 2");
@@ -1203,7 +1334,8 @@ qcf_status run_passes(int D, const Args<ONE>& a, dim3 grid, hipStream_t st, bool
 
 // The two passes over n_layers layers (up to kMaxLayers); a: everything but the layers and the workspace.
 qcf_status launch_two_pass(const qcf_layer_desc& L, const ScoreArgs& a, int n_layers, const void* const* q,
-                           const void* const* k, const float* alpha, void* ws, hipStream_t st, ScoreSums* left = nullptr) {
+                           const void* const* k, const float* alpha, void* ws, hipStream_t st, ScoreSums* left = nullptr,
+                           const Rerotation* r = nullptr) {
   const PassWs w = pass_ws(L, n_layers, a.B, a.total_probe, a.total_ctx);
   if (w.n_units * n_layers * a.Hkv > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "score: grid too large");
   PassArgs pa;
@@ -1223,7 +1355,9 @@ qcf_status launch_two_pass(const qcf_layer_desc& L, const ScoreArgs& a, int n_la
   if (left) *left = ScoreSums{pa.s.colsum, a.probe_off, a.total_probe, a.H, a.Hkv, false};
   if (n_layers > 1 || w.unit_tiles > 1 || a.Hkv > 65535)
     return run_passes<false>(L.head_dim, pa, dim3((unsigned)(w.n_units * n_layers * a.Hkv)), st, !left);
-  return run_passes<true>(L.head_dim, pa.s, dim3((unsigned)w.n_units, (unsigned)a.Hkv), st, !left);
+  const dim3 grid((unsigned)w.n_units, (unsigned)a.Hkv);
+  if (r) return run_two_pass<64, false, true, true>(pa.s, grid, st, !left, *r);
+  return run_passes<true>(L.head_dim, pa.s, grid, st, !left);
 }
 
 ScoreArgs score_args(const qcf_layer_desc& L, int32_t B, const void* q, const int64_t* probe_off, int64_t total_probe,
@@ -1285,11 +1419,18 @@ qcf_status fused_args(const qcf_layer_desc& L, const ScoreArgs& a, void* ws, Fus
 
 qcf_status launch_rerope_score(const qcf_layer_desc& L, const qcf_chunk* chunks, int32_t n_chunks, const void* q,
                                const int64_t* probe_off, int64_t total_probe, void* k, void* v, const int64_t* ctx_off,
-                               int64_t total_ctx, float* score, void* ws, hipStream_t st) {
+                               int64_t total_ctx, float* score, void* ws, hipStream_t st, ScoreSums* left) {
+  const ScoreArgs a = score_args(L, 1, q, probe_off, total_probe, k, ctx_off, total_ctx, nullptr, score, 1.f, 0.f);
+  const Rerotation r{chunks, n_chunks, L.rope_style, -2.0 / (double)L.head_dim * std::log2(L.rope_base), static_cast<bf16_t*>(k),
+                     static_cast<bf16_t*>(v)};
+  if (!use_fused(L, 1, total_probe, total_ctx)) {
+    const void* keys = k;
+    const float alpha = 1.f;
+    return launch_two_pass(L, a, 1, &q, &keys, &alpha, ws, st, left, &r);
+  }
   FusedArgs fa;
-  QCF_TRY(fused_args(L, score_args(L, 1, q, probe_off, total_probe, k, ctx_off, total_ctx, nullptr, score, 1.f, 0.f), ws, &fa));
-  fa.r = Rerotation{chunks, n_chunks, L.rope_style, -2.0 / (double)L.head_dim * std::log2(L.rope_base), static_cast<bf16_t*>(k),
-                    static_cast<bf16_t*>(v)};
+  QCF_TRY(fused_args(L, a, ws, &fa));
+  fa.r = r;
   return run_fused<false, true>(fa, st);
 }
 

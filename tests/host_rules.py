@@ -32,6 +32,9 @@ extern "C" void attention_workspace(const qcf_layer_desc* L, int B, long long ro
 extern "C" int takes_rerope(const qcf_layer_desc* L, int B, int n_chunks, long long probes, long long tokens) {
   return qcf::scoring::takes_rerope(*L, B, n_chunks, probes, tokens);
 }
+extern "C" int pass1_takes_rerope(const qcf_layer_desc* L, int B, int n_chunks, long long probes, long long tokens) {
+  return qcf::scoring::pass1_takes_rerope(*L, B, n_chunks, probes, tokens);
+}
 extern "C" int sums_in_selection(const qcf_layer_desc* L, int B, long long probes, long long tokens) {
   return qcf::scoring::sums_in_selection(*L, B, probes, tokens);
 }
@@ -77,6 +80,11 @@ def attention_workspace(H, Hkv, D, T, sel, have=0):
 def rerotates_in_scoring(L):
     """Whether a scored pipeline.DeviceLayer is re-rotated by its scoring kernel (csrc/score_layout.h)."""
     return bool(_library().takes_rerope(C.byref(L.desc), L.B, L.n_chunks, C.c_longlong(L.total_probe), C.c_longlong(L.total_ctx)))
+
+
+def rerotates_in_pass1(L):
+    """Whether a scored pipeline.DeviceLayer with heads of 64 is re-rotated by the first pass of its scoring (csrc/score_layout.h)."""
+    return bool(_library().pass1_takes_rerope(C.byref(L.desc), L.B, L.n_chunks, C.c_longlong(L.total_probe), C.c_longlong(L.total_ctx)))
 
 
 def sums_in_selection(L):

@@ -188,6 +188,39 @@ def test_rerotation_inside_the_scoring(lens, gaps, kw, style):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("style", [0, 1])
+@pytest.mark.parametrize("lens,gaps,kw,joined", [
+    ([300, 212], [0, 0], {}, True),                                    # a chunk that ends inside a tile
+    ([1] * 127 + [200], [0] * 128, {}, False),                         # more chunks to a tile than it pays for
+    ([1] * 127 + [2000], [0] * 128, {}, True),                         # half of the pairs in one tile
+    ([1] * 128 + [3000], [0] * 129, {}, False),                        # more chunks than the table holds
+    ([17, 5, 256, 90], [3, 0, 40, 300], {}, True),                     # rows that no chunk covers, a tile without any
+    ([100, 600], [0, 0], dict(before=130, behind=77), True),           # cache rows outside the request
+    ([257], [0], dict(R=120, H=16, Hkv=4, src0=9), True),              # 480 rows of a group, one token in the last tile
+    ([1], [0], dict(R=1, N=1), True),
+    ([90, 80], [0, 0], dict(probes=False), True),                      # the request has no probe rows
+    ([4000, 4192], [0, 0], dict(Hkv=8), True), ([8193], [0], dict(Hkv=8), False)],      # a round of compute units, and a tile more
+    ids=["two", "128 chunks", "128 chunks, long", "129 chunks", "gaps", "outside", "edges", "one", "no probes", "round", "more"])
+def test_rerotation_inside_pass1(lens, gaps, kw, joined, style):
+    print(f"re-rotation in pass 1, {len(lens)} chunks {kw} style={style}", flush=True)
+    L = _layer(lens, gaps, style=style, **dict(dict(R=24, D=64, Hkv=2), **kw))
+    assert host_rules.rerotates_in_pass1(L) == joined and not host_rules.rerotates_in_scoring(L)
+    L.chunk_tensors[0][0].view(torch.int16)[0, 0, :4] = torch.tensor([0x7f81, -1, 0x7f80, -128], dtype=torch.int16)
+    k0, v0 = L.k_fused.clone(), L.v_fused.clone()
+    res = []
+    for run in (lambda: [fn(L) for _, fn in pipeline.FUSED_STEPS], lambda: pipeline.enqueue_layer(L)):
+        L.k_fused.copy_(k0)
+        L.v_fused.copy_(v0)
+        for name in OUTS[2:]:
+            getattr(L, name).fill_(1)
+        run()
+        torch.cuda.synchronize()
+        res.append([getattr(L, name).clone() for name in OUTS])
+    for name, a, b in zip(OUTS, *res):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("style", [0, 1])
 @pytest.mark.parametrize("lens,gaps,kw", [
     ([300, 212], [0, 0], {}),
     ([1] * 255 + [200], [0] * 256, {}),                          # as many chunks as the table holds
