@@ -220,6 +220,29 @@ def test_rerotation_inside_pass1(lens, gaps, kw, joined, style):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("D", [64, 128])
+def test_chunks_turned_in_place(D):
+    """Chunks whose rows are the cache's own: every row is read and written by the same workgroup in either form."""
+    print(f"re-rotation in place, heads of {D}", flush=True)
+    L = _layer([300, 212, 700], [0, 0, 0], R=24, style=0, D=D)
+    assert (host_rules.rerotates_in_pass1 if D == 64 else host_rules.rerotates_in_scoring)(L)
+    rows = [(0, 300), (300, 512), (512, 1212)]
+    L.chunks_dev = qb.chunk_table([dict(k=L.k_fused[a:b], v=L.v_fused[a:b], src_pos0=0, dst_row=a, dst_pos0=a + 5) for a, b in rows],
+                                  L.k_fused.device)
+    k0, v0 = L.k_fused.clone(), L.v_fused.clone()
+    res = []
+    for run in (lambda: [fn(L) for _, fn in pipeline.FUSED_STEPS], lambda: pipeline.enqueue_layer(L)):
+        L.k_fused.copy_(k0)
+        L.v_fused.copy_(v0)
+        run()
+        torch.cuda.synchronize()
+        res.append([getattr(L, name).clone() for name in OUTS])
+    assert not torch.equal(res[0][0], k0)
+    for name, a, b in zip(OUTS, *res):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("style", [0, 1])
 @pytest.mark.parametrize("lens,gaps,kw", [
     ([300, 212], [0, 0], {}),
