@@ -105,17 +105,14 @@ inline double stream_us(int bm, int nb, int nk, int s, int len) {
 }
 
 // the load/compute-split kernels, over nb column blocks, with at most part_bytes of partial sums; `heights`: in tiles of any
-// height (not where the cache is re-rotated beside the product, on the compute units that larger tiles leave idle)
+// height (not where the cache is re-rotated beside the product, on the compute units that larger tiles leave idle).  They stand in
+// for undivided tiles only, so that a product has one order of sums with the cache re-rotated beside it and without.  In place of
+// ranges they lose as well: K 1536, N 2048 of 100 rows 12.1 us in ranges and 14.4 in tiles of 64 (15.3 of 96), 200 rows 13.5 and 13.6;
+// K 2816, N 1024 of 1300 rows 22.6 and 22.2 (26.5); K 4096, N 12288 of 100 rows 34.5 and 34.9.
 inline GemmPlan plan_ws(int64_t M, int nb, int nk, size_t part_bytes, bool heights) {
   GemmPlan best{kWs256, 1, ws256_us((M + 255) / 256, nb, nk)};
   const double t128 = ws128_us((M + 127) / 128, nb, nk);
   if (t128 < best.us) best = GemmPlan{kWs128, 1, t128};
-  if (heights && nk <= kHeightTiles)
-    for (const Height& h : kHeights) {
-      const int64_t mt = (M + rows_of(h.kind) - 1) / rows_of(h.kind);
-      const double t = h.tile_us * nk + h.start_us;
-      if (M > 64 && mt * nb <= compute_unit_count() && t < best.us) best = GemmPlan{h.kind, 1, t};
-    }
   const int bm = M <= 64 ? 64 : 128;
   const int64_t tiles = (M + bm - 1) / bm * nb;
   const double c = bm == 64 ? 0.40 : ws128_tile_us(rounds_of(tiles));
@@ -128,6 +125,12 @@ inline GemmPlan plan_ws(int64_t M, int nb, int nk, size_t part_bytes, bool heigh
     if (s > 1) t += 4.0 + (double)tiles * bm * kBN * 8.0 * s / 4.0e6;
     if (t < best.us) best = GemmPlan{bm == 64 ? kWs64 : kWs128, s, t};
   }
+  if (heights && best.splits == 1 && M > 64 && nk <= kHeightTiles)
+    for (const Height& h : kHeights) {
+      const int64_t mt = (M + rows_of(h.kind) - 1) / rows_of(h.kind);
+      const double t = h.tile_us * nk + h.start_us;
+      if (mt * nb <= compute_unit_count() && t < best.us) best = GemmPlan{h.kind, 1, t};
+    }
   return best;
 }
 
@@ -190,8 +193,8 @@ inline ProductPlan plan_product(int64_t M, int nb, int nk, bool by_rows, size_t 
 }
 
 // workspace a product of M rows x nb column blocks x nk k-tiles can use (not needed: without it the contraction stays whole)
-inline size_t gemm_part_bytes(int64_t M, int nb, int nk, bool heights = true) {
-  const ProductPlan p = plan_product(M, nb, nk, true, SIZE_MAX, heights);
+inline size_t gemm_part_bytes(int64_t M, int nb, int nk) {
+  const ProductPlan p = plan_product(M, nb, nk, true, SIZE_MAX);
   if (p.blocks == nb && p.rows == M) return split_part_bytes(M, nb, 256, p.splits);
   return split_part_bytes(p.blocks == nb ? M - p.rows : M, p.blocks > 0 && p.blocks < nb ? nb - p.blocks : nb,
                           p.rest.kind == kWs64 ? 64 : 128, p.rest.splits);

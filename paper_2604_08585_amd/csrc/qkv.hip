@@ -1368,10 +1368,7 @@ qcf_status run_gemm(const QkvArgs& a_in, int nb, void* ws, size_t ws_bytes, hipS
 
 size_t qkv_workspace(const qcf_layer_desc& L, int64_t M) {
   // (the MFMA path needs none; what it asks for lets small M split the contraction)
-  if (use_mfma(L)) {
-    const int nb = (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim / kBN, nk = L.d_model / kBK;
-    return std::max(gemm_part_bytes(M, nb, nk), gemm_part_bytes(M, nb, nk, false));       // (either may be taken, see side_rows)
-  }
+  if (use_mfma(L)) return gemm_part_bytes(M, (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim / kBN, L.d_model / kBK);
   return align_up((size_t)M * (L.n_q_heads + 2 * L.n_kv_heads) * L.head_dim * sizeof(float), 256);
 }
 

@@ -43,6 +43,13 @@ extern "C" int tile_rows(long long rows, int columns, int contraction, long long
   const ProductPlan p = plan_product(rows, columns / kBN, contraction / kBK, true, workspace);
   return p.blocks != 0 || p.rest.splits > 1 ? 0 : rows_of(p.rest.kind);
 }
+// ranges that the contraction of a projection in one launch of tiles of 64 to 256 rows is cut into (-1: in other launches), with
+// the cache re-rotated beside it and without
+extern "C" int ranges(const qcf_layer_desc* L, long long rows, long long workspace, int beside) {
+  using namespace qcf::gemm;
+  const ProductPlan p = plan_product(rows, (L->n_q_heads + 2 * L->n_kv_heads) * L->head_dim / kBN, L->d_model / kBK, true, workspace, !beside);
+  return p.blocks == 0 ? p.rest.splits : -1;
+}
 extern "C" long long side_rows(const qcf_layer_desc* L, long long rows, int n_chunks, long long tokens, long long workspace) {
   return qcf::gemm::side_rows(*L, rows, n_chunks, tokens, workspace).all;
 }
@@ -96,6 +103,16 @@ def sums_in_selection(L):
 def tile_rows(M, N, K, workspace=0):
     """Rows of a tile of a bf16 product in one undivided launch (csrc/gemm_plan.h); 0: divided, or 256 x 256 tiles."""
     return _library().tile_rows(C.c_longlong(M), N, K, C.c_longlong(workspace))
+
+
+def ranges_of_projection(desc, rows, tokens, workspace):
+    """Ranges that the contraction of a projection of `rows` rows is cut into where the cache of `tokens` rows is re-rotated beside it,
+    and where it is not; None: it is not re-rotated beside it."""
+    lib, desc, rows, ws = _library(), C.byref(desc), C.c_longlong(rows), C.c_longlong(workspace)
+    lib.side_rows.restype = C.c_longlong
+    if lib.side_rows(desc, rows, 8, C.c_longlong(tokens), ws) <= 0:
+        return None
+    return lib.ranges(desc, rows, ws, 1), lib.ranges(desc, rows, ws, 0)
 
 
 def rows_beside_projection(L):

@@ -252,8 +252,9 @@ def test_chunks_turned_in_place(D):
     ([257], [0], dict(H=16, Hkv=4, src0=9)),
     ([3000, 9001], [0, 7], dict(dm=1024, N=1500)),               # several tiles of rows, workgroups with more than one block
     ([4000, 4192], [0, 0], dict(dm=4096, H=32, Hkv=8, N=620)),   # 16 compute units to spare: a part of the rows
-    ([20, 21], [0, 0], dict(D=64, Hkv=4)), ([2], [0], {})],
-    ids=["two", "256 chunks", "257 chunks", "gaps", "edges", "long", "part", "heads of 64", "one"])
+    ([20, 21], [0, 0], dict(D=64, Hkv=4)), ([2], [0], {}),
+    ([350], [0], dict(dm=1536, H=12, Hkv=2, N=70))],             # a contraction in ranges
+    ids=["two", "256 chunks", "257 chunks", "gaps", "edges", "long", "part", "heads of 64", "one", "ranges"])
 def test_rerotation_beside_the_projection(lens, gaps, kw, style):
     print(f"re-rotation beside the projection {kw} style={style}", flush=True)
     L = _layer(lens, gaps, R=4, style=style, **kw)
@@ -359,6 +360,22 @@ def test_which_layers_are_joined():
     assert beside(1, 3, 24, 731, 110) == 731 and beside(1, 16, 80, 8192, 410) == 8192 and beside(16, 256, 80, 8192, 410) == 8192
     assert 0 < beside(1, 16, 80, 8192, 1229) < 8192
     assert not any([beside(1, 257, 80, 8192, 410), beside(1, 16, 80, 8192, 1500), beside(1, 4, 20, 512, 77, dtype="f32")])
+
+
+@pytest.mark.parametrize("dm,H,Hkv,D", [(4096, 32, 8, 128), (1536, 12, 2, 128), (4096, 32, 32, 128), (1024, 16, 4, 64), (2048, 32, 8, 64)])
+def test_a_projection_has_one_order_of_sums(dm, H, Hkv, D):
+    """The bits of a layer in one call are those of the calls one after the other: the contraction is cut alike whether the cache is
+    re-rotated beside the projection or not."""
+    desc = qb.make_desc(inputs.LayerShape(dm, H, Hkv, D, 500000.0, "bf16"))
+    beside = 0
+    for rows in range(1, 1025):
+        reported = qb.qcf_recompute_qkv_workspace_bytes(desc, rows)
+        for tokens, workspace in ((2 * rows, reported), (20 * rows, reported), (2 * rows, 1 << 40), (2 * rows, reported // 2)):
+            ranges = host_rules.ranges_of_projection(desc, rows, tokens, workspace)
+            if ranges:
+                beside += 1
+                assert ranges[0] == ranges[1] > 0, (rows, tokens, workspace, ranges)
+    assert beside > 100
 
 
 F32 = dict(dtype="f32", H=4, Hkv=2, D=64, R=20)
