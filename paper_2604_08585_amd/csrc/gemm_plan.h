@@ -36,6 +36,13 @@ inline double rounds_of(int64_t wgs) {
   const int cus = compute_unit_count();
   return (double)((wgs + cus - 1) / cus);
 }
+// Workgroups of a launch of mt row tiles with `units` (column blocks x ranges) to each: eight times those of the XCD that has most.
+// (Column blocks are dealt to the XCDs with all their row tiles, or from kRowsOverXcds row tiles on the row tiles are; the numbers
+// that are made up to a multiple of eight return at once.)
+constexpr int64_t kRowsOverXcds = 16;
+inline int64_t ws_grid(int64_t mt, int64_t units) {
+  return mt >= kRowsOverXcds ? ((mt + 7) / 8) * 8 * units : mt * ((units + 7) / 8) * 8;
+}
 inline double quad_us(int64_t mt, int nb, int nk) { return rounds_of(mt * ((nb + 1) / 2)) * (1.40 * nk + 12.0); }
 inline double ws256_us(int64_t mt, int nb, int nk) { return rounds_of(mt * nb) * (0.75 * nk + 10.0); }
 // 128 x 128 tiles over three and more rounds wait for their operands: 2400 rows, K 8192, N 10240 take 0.7 us per k-tile.
@@ -46,7 +53,10 @@ inline double ws128_us(int64_t mt, int nb, int nk) {
   return r * (ws128_tile_us(r) * nk + 8.0);
 }
 
-// Tiles of other heights, where they fit one round.  These kernels are bound by their loads: a compute unit has at most 256 lines of
+// Tiles of other heights, where they fit one round, on each XCD: where column blocks or row tiles are no multiple of eight, some have
+// more workgroups than others (560 rows of K 4096, N 3584 in 9 x 28 tiles of 64: 36 for 32 compute units, 49.4 us; in tiles of 96
+// 34.0, of 128 36.7; 400 rows of N 4608 46.5 and 32.1; 1865 of N 3200 in tiles of 192 82.4, of 256 55.2; 2305 of N 1152 in tiles of
+// 96 48.1, of 128 38.2).  These kernels are bound by their loads: a compute unit has at most 256 lines of
 // 128 bytes on their way (60 GB/s from memory, 115 from the memory-side cache, whatever the depth of the ring), so a k-tile takes
 // the time that its rows and columns take to arrive, and the least height that still fits a round wins.  Calls without and with
 // them, us (weights from memory): 64 rows: K 4096, N 6144 of 300 rows 38.2 and 32.1, K 2048, N 3072 of 615 21.5 and 18.0, K 2816,
@@ -129,7 +139,7 @@ inline GemmPlan plan_ws(int64_t M, int nb, int nk, size_t part_bytes, bool heigh
     for (const Height& h : kHeights) {
       const int64_t mt = (M + rows_of(h.kind) - 1) / rows_of(h.kind);
       const double t = h.tile_us * nk + h.start_us;
-      if (mt * nb <= compute_unit_count() && t < best.us) best = GemmPlan{h.kind, 1, t};
+      if (ws_grid(mt, nb) <= compute_unit_count() && t < best.us) best = GemmPlan{h.kind, 1, t};
     }
   return best;
 }
@@ -199,10 +209,6 @@ inline size_t gemm_part_bytes(int64_t M, int nb, int nk) {
   return split_part_bytes(p.blocks == nb ? M - p.rows : M, p.blocks > 0 && p.blocks < nb ? nb - p.blocks : nb,
                           p.rest.kind == kWs64 ? 64 : 128, p.rest.splits);
 }
-
-// workgroups of a launch of mt row tiles with `units` (column blocks x ranges) to each
-constexpr int64_t kRowsOverXcds = 16;
-inline int64_t ws_grid(int64_t mt, int64_t units) { return mt >= kRowsOverXcds ? ((mt + 7) / 8) * 8 * units : mt * ((units + 7) / 8) * 8; }
 
 // Re-rotation beside the product: rows of the cache for each workgroup and for all of them, the first ones (0: none; those behind
 // them come from a launch in front).  It goes beside one launch of tiles of 64 to 256 rows that leaves compute units idle: all

@@ -50,6 +50,17 @@ extern "C" int ranges(const qcf_layer_desc* L, long long rows, long long workspa
   const ProductPlan p = plan_product(rows, (L->n_q_heads + 2 * L->n_kv_heads) * L->head_dim / kBN, L->d_model / kBK, true, workspace, !beside);
   return p.blocks == 0 ? p.rest.splits : -1;
 }
+// workgroups of the product on the XCD that has most of them, by the order of the launch (0: divided, or 256 x 256 tiles)
+extern "C" long long busiest_xcd(long long rows, int columns, int contraction, long long workspace) {
+  using namespace qcf::gemm;
+  const ProductPlan p = plan_product(rows, columns / kBN, contraction / kBK, true, workspace);
+  if (p.blocks != 0 || p.rest.splits > 1) return 0;
+  const int units = columns / kBN, mt = (int)((rows + rows_of(p.rest.kind) - 1) / rows_of(p.rest.kind));
+  long long n[8] = {0};
+  for (int m = 0; m < mt; ++m)
+    for (int u = 0; u < units; ++u) ++n[(mt >= kRowsOverXcds ? m : u) % 8];
+  return *std::max_element(n, n + 8);
+}
 extern "C" long long side_rows(const qcf_layer_desc* L, long long rows, int n_chunks, long long tokens, long long workspace) {
   return qcf::gemm::side_rows(*L, rows, n_chunks, tokens, workspace).all;
 }
@@ -103,6 +114,13 @@ def sums_in_selection(L):
 def tile_rows(M, N, K, workspace=0):
     """Rows of a tile of a bf16 product in one undivided launch (csrc/gemm_plan.h); 0: divided, or 256 x 256 tiles."""
     return _library().tile_rows(C.c_longlong(M), N, K, C.c_longlong(workspace))
+
+
+def busiest_xcd(M, N, K, workspace=0):
+    """Workgroups on the XCD that has most of them, of a bf16 product in one undivided launch; 0: divided, or 256 x 256 tiles."""
+    f = _library().busiest_xcd
+    f.restype = C.c_longlong
+    return f(C.c_longlong(M), N, K, C.c_longlong(workspace))
 
 
 def ranges_of_projection(desc, rows, tokens, workspace):

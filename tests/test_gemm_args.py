@@ -1,6 +1,10 @@
-"""Host arithmetic of the product's division by rows (csrc/gemm_args.h), compiled and run on the CPU."""
+"""Host arithmetic of the product's division by rows (csrc/gemm_args.h) and into tiles (csrc/gemm_plan.h), compiled and run on the CPU."""
 import os
 import subprocess
+
+import pytest
+
+import host_rules
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -59,3 +63,14 @@ def test_a_null_output_stays_null_when_rows_are_cut_off(tmp_path):
                     str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+@pytest.mark.parametrize("N,rows,height", [
+    (3584, 560, 96), (3584, 512, 64), (4608, 400, 96), (4608, 384, 64), (4608, 600, 128), (4608, 1344, 224), (4608, 1345, 256),
+    (1152, 2305, 128), (3200, 1865, 256), (3200, 1536, 192)])
+def test_tiles_fit_a_round_on_every_xcd(N, rows, height):
+    """Column blocks, or row tiles, that are no multiple of the eight XCDs: the one that has most of them has a round's workgroups."""
+    assert host_rules.tile_rows(rows, N, 4096) == height
+    for m in range(65, 3000, 7):
+        if host_rules.tile_rows(m, N, 4096) in (64, 96, 160, 192, 224):
+            assert host_rules.busiest_xcd(m, N, 4096) <= 32, m
