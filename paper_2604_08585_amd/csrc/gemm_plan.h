@@ -29,7 +29,8 @@ inline bool use_mfma(const qcf_layer_desc& L) {
 // k-tile and per workgroup are measured ones (microseconds, all compute units busy).  A split contraction adds the
 // writing and reading of its partial sums and a launch.
 enum GemmKind { kWs64, kWs96, kWs128, kWs160, kWs192, kWs224, kWs256, kQuad };       // 64 to 256 x 128; 256 x 256
-constexpr int rows_of(GemmKind kind) { return kind == kWs64 ? 64 : kind == kWs96 ? 96 : kind == kWs128 ? 128 : kind == kWs160 ? 160 : kind == kWs192 ? 192 : kind == kWs224 ? 224 : 256; }
+constexpr int kRowsOf[] = {64, 96, 128, 160, 192, 224, 256, 256};
+constexpr int rows_of(GemmKind kind) { return kRowsOf[kind]; }
 struct GemmPlan { GemmKind kind; int splits; double us; };
 
 inline double rounds_of(int64_t wgs) {
@@ -53,19 +54,23 @@ inline double ws128_us(int64_t mt, int nb, int nk) {
   return r * (ws128_tile_us(r) * nk + 8.0);
 }
 
-// Tiles of other heights, where they fit one round, on each XCD: where column blocks or row tiles are no multiple of eight, some have
-// more workgroups than others (560 rows of K 4096, N 3584 in 9 x 28 tiles of 64: 36 for 32 compute units, 49.4 us; in tiles of 96
-// 34.0, of 128 36.7; 400 rows of N 4608 46.5 and 32.1; 1865 of N 3200 in tiles of 192 82.4, of 256 55.2; 2305 of N 1152 in tiles of
-// 96 48.1, of 128 38.2).  These kernels are bound by their loads: a compute unit has at most 256 lines of
+// Tiles of other heights, where they fit one round.  These kernels are bound by their loads: a compute unit has at most 256 lines of
 // 128 bytes on their way (60 GB/s from memory, 115 from the memory-side cache, whatever the depth of the ring), so a k-tile takes
 // the time that its rows and columns take to arrive, and the least height that still fits a round wins.  Calls without and with
-// them, us (weights from memory): 64 rows: K 4096, N 6144 of 300 rows 38.2 and 32.1, K 2048, N 3072 of 615 21.5 and 18.0, K 2816,
-// N 1024 of 2000 30.7 and 23.6, K 1024, N 1024 of 200 and 2000 10.2 and 9.4, 11.5 and 10.9; 96: K 4096, N 6144 of 350 31.9 and 29.6;
-// 160: K 4096, N 4096 of 1229 57.5 and 46.7, K 2048, N 3072 of 1600 34.5 and 28.5; 192: K 4096, N 6144 of 900 57.1 and
-// 50.0; 224: the same of 1100 61.2 and 57.4, K 8192, N 10240 of 615 120 and 110.  In two rounds they lose: K 4096, N 6144 of 410
-// rows in tiles of 64 56 (of 128 39), 1229 in tiles of 160 87 (of 256 62).
+// them, us, of y = x w^T, weights from memory (buffers of 700 MB take turns): 64 rows: K 4096, N 6144 of 300 rows 35.8 and 30.6,
+// K 2048, N 3072 of 615 21.0 and 17.8, K 2816, N 1024 of 2000 29.0 and 22.4, K 1024, N 1024 of 200 and 2000 8.7 and 8.4, 12.9 and
+// 11.1; 96: K 4096, N 6144 of 350 34.9 and 32.0; 160: K 4096, N 4096 of 1229 52.5 and 45.9, K 2048, N 3072 of 1600 30.6 and 26.4;
+// 192: K 4096, N 6144 of 900 54.3 and 49.3; 224: the same of 1100 58.0 and 55.4, K 8192, N 10240 of 615 110 and 106.  (Weights in
+// the memory-side cache: 300 rows 24.5 and 23.4, 900 46.1 and 46.4, 1100 52.3 and 51.6.)  In two rounds they lose: K 4096,
+// N 6144 of 410 rows in tiles of 64 54.0, of 96 32.5, of 128 35.7; 1229 in tiles of 160 85.8, of 256 58.4.  One of 64 is before one
+// of 96 wherever both fit: K 2816, N 1024 of 2000 rows 22.6 and 26.4, K 1536, N 2048 of 900 14.5 and 16.4.
+// A round is one of each XCD: where column blocks or row tiles are no multiple of eight, some have more workgroups than others.
+// 560 rows of K 4096, N 3584 in 9 x 28 tiles of 64 (36 for 32 compute units) 49.4 us, in tiles of 96 34.4, of 128 37.3; 400 rows of
+// N 4608 46.5, 32.3 and 36.4; 1865 of N 3200 in tiles of 192 82.4, of 256 54.8; 2305 of N 1152 in tiles of 96 48.1, of 128 37.6.
+// Only up to K 8192: at K 14336 ranges of 256 x 256 tiles are faster than this says (N 4096 of 1290 rows 155 in ranges, 160 in tiles
+// of 192; 1650 169 and 182).  (In between some would gain, K 11008, N 4096 of 1290 rows 148 and 126.)
 struct Height { GemmKind kind; double tile_us, start_us; };
-constexpr Height kHeights[] = {{kWs64, 0.44, 6.0}, {kWs96, 0.45, 5.5}, {kWs160, 0.61, 8.6}, {kWs192, 0.65, 8.5}, {kWs224, 0.72, 11.0}};
+constexpr Height kHeights[] = {{kWs64, 0.44, 6.0}, {kWs96, 0.445, 6.0}, {kWs160, 0.61, 8.6}, {kWs192, 0.65, 8.5}, {kWs224, 0.72, 11.0}};
 constexpr int kHeightTiles = 128;        // k-tiles, at most
 
 // 256 x 256 tiles with the contraction in `s` ranges of an even number of k-tiles.  The partial sums leave all at once and
@@ -77,6 +82,9 @@ constexpr int kHeightTiles = 128;        // k-tiles, at most
 // and 119; K 8192, N 10240 of 129 rows 69 and 55, 512 rows 111 and 89.  The other side of the line: K 4096, N 4096 of 1229
 // rows 44 and 56, N 6144 of 700 rows 52 and 53 (a range of 22 k-tiles does not pay for its sums); K 8192, N 10240 of 900
 // rows, two rounds of ranges of 44, 159 and 162; K 14336, N 4096 of 3300 rows, two rounds of two ranges, 303 and 338.
+// (The 2.5 us behind the start are the launch of the reduction and its wait.  With 4.0, what it was when a workgroup of it finished 128
+// columns by one wave, us so and with 2.5: K 14336, N 4096 of 300 rows 77.5 and 64.8, 1650 rows 186 and 169, K 8192, N 10240 of 390
+// rows 86.1 and 84.5, all in tiles of 128 to 256 rows instead.)
 // (Weights from memory.  In the memory-side cache, which has room for those of one product at best, the undivided tiles wait less:
 // K 14336, N 4096 of 512 rows 61 and 65 there, 79 and 66 from memory, 1229 rows 145 and 125, 174 and 127; K 8192, N 10240 of
 // 256 rows 51 and 60, 82 and 61.)
@@ -179,6 +187,8 @@ inline ProductPlan plan_product(int64_t M, int nb, int nk, bool by_rows, size_t 
     for (int64_t r = rounds; r >= 1 && r >= rounds - 1; --r) {
       const int qb = (int)(r * cus / mt * 2);
       if (qb <= 0 || qb >= nb) continue;
+      // (`rest` in tiles of 128 or 256 rows, here and below: the estimates of two launches do not tell where others win.  K 4096, N
+      // 6144 of 3250 rows 157 us, with tiles of 160 148; of 3000 141, with 96 146; N 28672 of 600 143 and 144.)
       const GemmPlan rest = plan_ws(M, nb - qb, nk, 0, false);
       const double t = quad_us(mt, qb, nk) + rest.us + 2.0;
       if (t < best.us) best = ProductPlan{kQuad, M, qb, rest, t};

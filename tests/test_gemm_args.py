@@ -74,3 +74,9 @@ def test_tiles_fit_a_round_on_every_xcd(N, rows, height):
     for m in range(65, 3000, 7):
         if host_rules.tile_rows(m, N, 4096) in (64, 96, 160, 192, 224):
             assert host_rules.busiest_xcd(m, N, 4096) <= 32, m
+
+
+def test_the_least_height_that_fits_is_taken():
+    for rows, N, K in ((2000, 1024, 2816), (615, 3072, 2048), (900, 2048, 1536), (320, 6144, 4096), (200, 1024, 64)):
+        assert host_rules.tile_rows(rows, N, K) == 64, (rows, N, K)
+    assert host_rules.tile_rows(321, 6144, 4096) == host_rules.tile_rows(350, 6144, 64) == 96
