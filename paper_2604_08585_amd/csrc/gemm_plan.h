@@ -63,14 +63,16 @@ inline double ws128_us(int64_t mt, int nb, int nk) {
 // 192: K 4096, N 6144 of 900 54.3 and 49.3; 224: the same of 1100 58.0 and 55.4, K 8192, N 10240 of 615 110 and 106.  (Weights in
 // the memory-side cache: 300 rows 24.5 and 23.4, 900 46.1 and 46.4, 1100 52.3 and 51.6.)  In two rounds they lose: K 4096,
 // N 6144 of 410 rows in tiles of 64 54.0, of 96 32.5, of 128 35.7; 1229 in tiles of 160 85.8, of 256 58.4.  One of 64 is before one
-// of 96 wherever both fit: K 2816, N 1024 of 2000 rows 22.6 and 26.4, K 1536, N 2048 of 900 14.5 and 16.4.
+// of 96 where both fit, K 2816, N 1024 of 2000 rows 21.7 and 25.5, K 1536, N 2048 of 900 13.4 and 15.1, but for contractions of up to
+// 18 k-tiles, where the 96 rows' start is shorter: K 256, N 512 of 1000 5.54 and 5.30 (128 rows 5.31), N 6144 of 160 5.58 and 5.48,
+// K 512, N 2048 of 1000 7.27 and 6.82, K 1024, N 6144 of 300 11.4 and 10.8, N 1024 of 1229 9.11 and 8.92 (300: 8.53 and 8.59).
 // A round is one of each XCD: where column blocks or row tiles are no multiple of eight, some have more workgroups than others.
 // 560 rows of K 4096, N 3584 in 9 x 28 tiles of 64 (36 for 32 compute units) 49.4 us, in tiles of 96 34.4, of 128 37.3; 400 rows of
 // N 4608 46.5, 32.3 and 36.4; 1865 of N 3200 in tiles of 192 82.4, of 256 54.8; 2305 of N 1152 in tiles of 96 48.1, of 128 37.6.
 // Only up to K 8192: at K 14336 ranges of 256 x 256 tiles are faster than this says (N 4096 of 1290 rows 155 in ranges, 160 in tiles
 // of 192; 1650 169 and 182).  (In between some would gain, K 11008, N 4096 of 1290 rows 148 and 126.)
 struct Height { GemmKind kind; double tile_us, start_us; };
-constexpr Height kHeights[] = {{kWs64, 0.44, 6.0}, {kWs96, 0.445, 6.0}, {kWs160, 0.61, 8.6}, {kWs192, 0.65, 8.5}, {kWs224, 0.72, 11.0}};
+constexpr Height kHeights[] = {{kWs64, 0.44, 6.0}, {kWs96, 0.4535, 5.75}, {kWs160, 0.61, 8.6}, {kWs192, 0.65, 8.5}, {kWs224, 0.72, 11.0}};
 constexpr int kHeightTiles = 128;        // k-tiles, at most
 
 // 256 x 256 tiles with the contraction in `s` ranges of an even number of k-tiles.  The partial sums leave all at once and

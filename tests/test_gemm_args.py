@@ -77,6 +77,11 @@ def test_tiles_fit_a_round_on_every_xcd(N, rows, height):
 
 
 def test_the_least_height_that_fits_is_taken():
-    for rows, N, K in ((2000, 1024, 2816), (615, 3072, 2048), (900, 2048, 1536), (320, 6144, 4096), (200, 1024, 64)):
+    for rows, N, K in ((2000, 1024, 2816), (615, 3072, 2048), (900, 2048, 1536), (320, 6144, 4096), (200, 1024, 1216)):
         assert host_rules.tile_rows(rows, N, K) == 64, (rows, N, K)
     assert host_rules.tile_rows(321, 6144, 4096) == host_rules.tile_rows(350, 6144, 64) == 96
+
+
+def test_short_contractions_take_tiles_of_96_rows():
+    for rows, N, K in ((100, 512, 256), (1000, 512, 256), (1000, 2048, 512), (300, 6144, 1024), (1229, 1024, 1024), (300, 6144, 64)):
+        assert host_rules.tile_rows(rows, N, K) == 96, (rows, N, K)

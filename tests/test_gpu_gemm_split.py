@@ -200,7 +200,7 @@ def test_rotation_behind_the_reduction(M, D, style, far):
 
 @pytest.mark.parametrize("M,K,height", [
     (65, 4096, 64), (320, 4096, 64), (321, 4096, 96), (480, 4096, 96), (481, 4096, 128), (641, 4096, 160), (800, 4096, 160),
-    (801, 4096, 192), (960, 4096, 192), (961, 4096, 224), (1120, 4096, 224), (1121, 4096, 256), (350, 64, 96), (700, 8192, 160)])
+    (801, 4096, 192), (960, 4096, 192), (961, 4096, 224), (1120, 4096, 224), (1121, 4096, 256), (300, 64, 96), (700, 8192, 160)])
 def test_tiles_of_every_height(M, K, height):
     """Launches that fit one round in tiles of 64 to 256 rows: a whole last tile and one of a single row, fewer k-tiles than stages; a
     row's bits are those of a launch of few rows."""
