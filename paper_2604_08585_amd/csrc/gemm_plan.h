@@ -62,18 +62,30 @@ inline double ws128_us(int64_t mt, int nb, int nk) {
 // 11.1; 96: K 4096, N 6144 of 350 34.9 and 32.0; 160: K 4096, N 4096 of 1229 52.5 and 45.9, K 2048, N 3072 of 1600 30.6 and 26.4;
 // 192: K 4096, N 6144 of 900 54.3 and 49.3; 224: the same of 1100 58.0 and 55.4, K 8192, N 10240 of 615 110 and 106.  (Weights in
 // the memory-side cache: 300 rows 24.5 and 23.4, 900 46.1 and 46.4, 1100 52.3 and 51.6.)  In two rounds they lose: K 4096,
-// N 6144 of 410 rows in tiles of 64 54.0, of 96 32.5, of 128 35.7; 1229 in tiles of 160 85.8, of 256 58.4.  One of 64 is before one
-// of 96 where both fit, K 2816, N 1024 of 2000 rows 21.7 and 25.5, K 1536, N 2048 of 900 13.4 and 15.1, but for contractions of up to
-// 18 k-tiles, where the 96 rows' start is shorter: K 256, N 512 of 1000 5.54 and 5.30 (128 rows 5.31), N 6144 of 160 5.58 and 5.48,
-// K 512, N 2048 of 1000 7.27 and 6.82, K 1024, N 6144 of 300 11.4 and 10.8, N 1024 of 1229 9.11 and 8.92 (300: 8.53 and 8.59).
+// N 6144 of 410 rows in tiles of 64 54.0, of 96 32.5, of 128 35.7; 1229 in tiles of 160 85.8, of 256 58.4.
 // A round is one of each XCD: where column blocks or row tiles are no multiple of eight, some have more workgroups than others.
-// 560 rows of K 4096, N 3584 in 9 x 28 tiles of 64 (36 for 32 compute units) 49.4 us, in tiles of 96 34.4, of 128 37.3; 400 rows of
-// N 4608 46.5, 32.3 and 36.4; 1865 of N 3200 in tiles of 192 82.4, of 256 54.8; 2305 of N 1152 in tiles of 96 48.1, of 128 37.6.
+// 560 rows of K 4096, N 3584 in 9 x 28 tiles of 64 (36 for 32 compute units) 49.4 us, in tiles of 96 33.6, of 128 31.7; 400 rows of
+// N 4608 46.5, 28.9 and 30.2; 1865 of N 3200 in tiles of 192 82.4, of 256 54.8; 2305 of N 1152 in tiles of 96 48.1, of 128 37.6.
 // Only up to K 8192: at K 14336 ranges of 256 x 256 tiles are faster than this says (N 4096 of 1290 rows 155 in ranges, 160 in tiles
 // of 192; 1650 169 and 182).  (In between some would gain, K 11008, N 4096 of 1290 rows 148 and 126.)
 struct Height { GemmKind kind; double tile_us, start_us; };
-constexpr Height kHeights[] = {{kWs64, 0.44, 6.0}, {kWs96, 0.4535, 5.75}, {kWs160, 0.61, 8.6}, {kWs192, 0.65, 8.5}, {kWs224, 0.72, 11.0}};
+constexpr Height kHeights[] = {{kWs64, 0.44, 6.0}, {kWs96, 0.445, 6.0}, {kWs160, 0.61, 8.6}, {kWs192, 0.65, 8.5}, {kWs224, 0.72, 11.0}};
 constexpr int kHeightTiles = 128;        // k-tiles, at most
+
+// Tiles of 64 and 96 rows against 128 that fit a round too.  A last row tile with few rows runs ahead (the rows that it does not have
+// are one line, which hits) and has the weights fetched for the others, so a k-tile takes, us, f the share of the last tile that has
+// rows: 0.43 + 0.125 f of 128 rows, 0.40 + 0.10 f of 96, 0.375 + 0.0875 f of 64 (K 2048 and 4096, N 3072 to 6144 of 300 to 1000
+// rows, within 4 %).  us, 128 and 96 rows: K 4096, N 4096 of 560 31.9 and 34.0, of 615 36.8 and 31.2; K 2048, N 3072 of 900 17.8 and 18.2,
+// of 700 18.7 and 17.1; K 2816, N 1024 of 2200 23.2 and 25.6, of 2458 23.5 and 25.0; K 6144, N 2048 of 1400 57.9 and 49.2.
+// One of 64 is before one of 96 where both pay, K 2816, N 1024 of 2000 rows 21.7 and 25.5, K 1536, N 2048 of 900 13.4 and 15.1, but not for
+// contractions of up to kShortTiles k-tiles: K 256, N 512 of 1000 5.54 and 5.30 (128 rows 5.31), N 6144 of 160 5.58 and 5.48, K 512,
+// N 2048 of 1000 7.27 and 6.82, K 1024, N 6144 of 300 11.4 and 10.8, N 1024 of 1229 9.11 and 8.92 (300: 8.53 and 8.59).
+constexpr int kShortTiles = 18;
+inline double last_tile_share(int64_t M, int rows) { return (double)((M - 1) % rows + 1) / rows; }
+inline bool height_pays(GemmKind kind, int64_t M, int nk) {
+  const double f = last_tile_share(M, rows_of(kind)), of128 = 0.43 + 0.125 * last_tile_share(M, 128);
+  return kind == kWs96 ? 0.40 + 0.10 * f < of128 : kind == kWs64 && nk > kShortTiles && 0.375 + 0.0875 * f < of128;
+}
 
 // 256 x 256 tiles with the contraction in `s` ranges of an even number of k-tiles.  The partial sums leave all at once and
 // are read again by the reduction (7 TB/s both ways: a hundred megabytes stay in the memory-side cache).  Few row tiles
@@ -145,12 +157,15 @@ inline GemmPlan plan_ws(int64_t M, int nb, int nk, size_t part_bytes, bool heigh
     if (s > 1) t += 4.0 + (double)tiles * bm * kBN * 8.0 * s / 4.0e6;
     if (t < best.us) best = GemmPlan{bm == 64 ? kWs64 : kWs128, s, t};
   }
-  if (heights && best.splits == 1 && M > 64 && nk <= kHeightTiles)
+  if (heights && best.splits == 1 && M > 64 && nk <= kHeightTiles) {
+    auto fits = [&](GemmKind kind) { return ws_grid((M + rows_of(kind) - 1) / rows_of(kind), nb) <= compute_unit_count(); };
+    const bool over128 = best.kind == kWs128 && fits(kWs128);
     for (const Height& h : kHeights) {
-      const int64_t mt = (M + rows_of(h.kind) - 1) / rows_of(h.kind);
       const double t = h.tile_us * nk + h.start_us;
-      if (ws_grid(mt, nb) <= compute_unit_count() && t < best.us) best = GemmPlan{h.kind, 1, t};
+      if (!fits(h.kind) || !(over128 ? best.kind == kWs128 && height_pays(h.kind, M, nk) : t < best.us)) continue;
+      best = GemmPlan{h.kind, 1, t};
     }
+  }
   return best;
 }
 

@@ -66,7 +66,7 @@ def test_a_null_output_stays_null_when_rows_are_cut_off(tmp_path):
 
 
 @pytest.mark.parametrize("N,rows,height", [
-    (3584, 560, 96), (3584, 512, 64), (4608, 400, 96), (4608, 384, 64), (4608, 600, 128), (4608, 1344, 224), (4608, 1345, 256),
+    (3584, 570, 128), (3584, 615, 96), (3584, 512, 64), (4608, 400, 96), (4608, 384, 64), (4608, 600, 128), (4608, 1344, 224), (4608, 1345, 256),
     (1152, 2305, 128), (3200, 1865, 256), (3200, 1536, 192)])
 def test_tiles_fit_a_round_on_every_xcd(N, rows, height):
     """Column blocks, or row tiles, that are no multiple of the eight XCDs: the one that has most of them has a round's workgroups."""
@@ -85,3 +85,12 @@ def test_the_least_height_that_fits_is_taken():
 def test_short_contractions_take_tiles_of_96_rows():
     for rows, N, K in ((100, 512, 256), (1000, 512, 256), (1000, 2048, 512), (300, 6144, 1024), (1229, 1024, 1024), (300, 6144, 64)):
         assert host_rules.tile_rows(rows, N, K) == 96, (rows, N, K)
+
+
+@pytest.mark.parametrize("N,K,rows,height", [
+    (4096, 4096, 560, 128), (3584, 4096, 560, 128), (4608, 4096, 560, 128), (4096, 4096, 615, 96), (3072, 2048, 900, 128),
+    (3072, 2048, 700, 96), (1024, 2816, 2200, 128), (1024, 2816, 2458, 128), (1024, 2816, 1800, 64), (6144, 4096, 450, 96),
+    (8192, 8192, 350, 96), (2048, 6144, 1400, 96), (512, 256, 160, 128), (512, 256, 220, 96)])
+def test_a_thin_last_tile_of_128_rows_is_kept(N, K, rows, height):
+    """Where tiles of 128 rows fit a round as well, the choice goes by how full the last tile of either height is."""
+    assert host_rules.tile_rows(rows, N, K) == height
