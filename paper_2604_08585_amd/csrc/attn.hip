@@ -143,20 +143,33 @@ __global__ __launch_bounds__(256) void attn_generic(AttnArgs a) {
 
 // float32: D / 4 lanes take a token, so that a load brings whole key rows (a token to a thread asked for 64 lines with every load),
 // and NH heads of a KV group share a workgroup with its keys and values: two where a group has an even number.  Tiles of 512
-// tokens.  Launches of at most kFewWgs workgroups to a compute unit take 512 threads, which halves the chain of waits; more
-// of them hide each other's with 256.  The sums and their order are the same.  us, with a token
-// to a thread and a head to a workgroup, and with 512 and 256 threads so: 4 / 2 heads of 64, 77 rows over 512 tokens 10.9, 7.8, 10.0,
-// 80 over 2048 33, 22, 32, 300 over 2000 (600 workgroups) 69, 42, 37; 3 heads, 100 rows over 700 (300) 14.0, 10.2, 11.6; 8 requests
-// of 512 tokens, 80 rows each 38, 31, 21; 32 / 8 heads of 128, 150 over 1000 200, 86, 89; 16 / 8 heads of 64, 300 over 1000 100, 76,
-// 45.  (The first values requested with the keys: no difference.)  Error against 64 bits 2.5e-7, now 1.5e-7: sums in pairs.
-constexpr int kFewWgs = 2;
+// tokens, whose keys are dealt to the waves a load at a time and whose values to the slices, as many loads as the tile has tokens
+// for: by 64 tokens to a wave, a short tile was one wave's work.  Bound by latency where rows are few, by the reductions and the
+// probabilities' arithmetic where they are many.  us, with a token to a thread and a head to a workgroup, with 64 tokens to a wave, and
+// so: 4 / 2 heads of 64, 77 rows over 64 tokens 6.1, 6.4, 4.7, over 512 11.1, 8.0, 7.7, 300 over 2048 67.7, 37.0, 31; 3 heads, 1200
+// over 64 14.6, 18.3, 12.0; 32 / 8 heads of 128, one row over 64 5.5, 8.1, 4.8, 300 over 512 209, 98.6, 73.2; 8 heads, 1200 over 64
+// 59.6, 71.2, 30.4.  Error against 64 bits 4.3e-7, 2.0e-7, 2.0e-7 (the last two have the same bits).
+// Launches of at most kFewWgs workgroups to a compute unit take 512 threads, which halves the chain of waits; more of them hide each
+// other's with 256.  The sums and their order are the same.  512 and 256 threads: 4 / 2 heads of 64, 77 rows (154 workgroups) over
+// 512 tokens 7.8 and 10.8, 300 (600) over 64, 512 and 2000 7.6 and 6.7, 11.7 and 12.5, 29.7 and 37.0; 3 heads, 200 (600) over 700
+// 10.8 and 13.0; 8 requests of 512, 80 rows each (1280) 21.2 and 20.3; 16 / 8 heads, 300 (2400) over 1000 44.8 and 41.5.
+constexpr int kFewWgs = 3;
 constexpr int kTileF32 = 512;
+// n loads, eight on their way at a time; what is left in a batch of eight, four or two
+template <typename F>
+__device__ __forceinline__ void in_batches(int n, F&& f) {
+  int c = 0;
+  for (; c + 4 < n; c += 8) f(c, std::integral_constant<int, 8>{});
+  if (c + 2 < n) f(c, std::integral_constant<int, 4>{});
+  else if (c < n) f(c, std::integral_constant<int, 2>{});
+}
 template <int D, int NH, int THREADS>
 __global__ __launch_bounds__(THREADS) void attn_generic_f32(AttnArgs a) {
   constexpr int kQuads = D / 4, kSlices = kTileF32 / kQuads, kWaves = kTileF32 / 64;     // of a tile
-  constexpr int kVals = kTileF32 / kSlices;
   constexpr int kTurns = kTileF32 / THREADS;                 // a thread has token and slice tid of each part of THREADS tokens
-  constexpr int kTokens = 64 / kQuads, kBatch = 8;           // keys: tokens of a load; loads on their way
+  constexpr int kTokens = 64 / kQuads;                       // of a load of keys
+  constexpr int kDeal = THREADS / 64;                        // waves that the groups of tokens are dealt to
+  static_assert(kTileF32 / kTokens / kDeal % 8 == 0 && kTileF32 / kSlices % 8 == 0, "a whole tile is whole batches");
   __shared__ float sp[NH][kTileF32], slog[NH][kTileF32];
   __shared__ __align__(16) float sacc[NH][kSlices * D];
   __shared__ float redm[NH][kWaves], reds[NH][kWaves];
@@ -181,9 +194,10 @@ __global__ __launch_bounds__(THREADS) void attn_generic_f32(AttnArgs a) {
   const int64_t p0 = a.ctx_pos0 ? a.ctx_pos0[b] : 0;
   const int n_vis = (int)min((int64_t)Tn, max((int64_t)0, (int64_t)pos - p0 + 1));
   const int g = h0 / a.G;
-  const int64_t kv_stride = (int64_t)a.Hkv * D;
-  const float* kb = static_cast<const float*>(a.k) + (c0 * a.Hkv + g) * D + 4 * quad;
-  const float* vb = static_cast<const float*>(a.v) + (c0 * a.Hkv + g) * D + 4 * quad;
+  const uint32_t stride = (uint32_t)a.Hkv * D * sizeof(float);        // of a token; a tile's offsets are below 2^28 (1024 heads at most)
+  const char* kb = reinterpret_cast<const char*>(static_cast<const float*>(a.k) + (c0 * a.Hkv + g) * D);
+  const char* vb = reinterpret_cast<const char*>(static_cast<const float*>(a.v) + (c0 * a.Hkv + g) * D);
+  auto load4 = [&](const char* tile, int j, float* f) { Quad<float>::load(reinterpret_cast<const float*>(tile + (j * stride + 16u * quad)), f); };
   const float scale = rsqrtf((float)D);
   float m_run[NH], l_run[NH], acc[kTurns][NH][4];
 #pragma unroll
@@ -199,34 +213,36 @@ __global__ __launch_bounds__(THREADS) void attn_generic_f32(AttnArgs a) {
   }
   for (int j0 = 0; j0 < n_vis; j0 += kTileF32) {
     const int n = min(kTileF32, n_vis - j0);
-    const float* kr = kb + (int64_t)j0 * kv_stride;
-    const float* vr = vb + (int64_t)j0 * kv_stride;
+    const char* kr = kb + (int64_t)j0 * stride;
+    const char* vr = vb + (int64_t)j0 * stride;
+    // logits: groups of kTokens tokens are dealt to the waves, so that a short tile is all waves' work
+    auto logits = [&](int c, auto n_c) {
+      constexpr int N = decltype(n_c)::value;
+      float kf[N][4];
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+        load4(kr, min(((c + u) * kDeal + wave) * kTokens + token, n - 1), kf[u]);
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+#pragma unroll
+        for (int i = 0; i < NH; ++i) {
+          float d = q4[i][0] * kf[u][0];
+#pragma unroll
+          for (int e = 1; e < 4; ++e) d += q4[i][e] * kf[u][e];
+          d = kQuads == 16 ? row_sum(d) : half_wave_sum(d);
+          if (quad == 0) slog[i][((c + u) * kDeal + wave) * kTokens + token] = d;
+        }
+    };
+    const int groups = ((n + kTokens - 1) / kTokens - wave + kDeal - 1) / kDeal;      // of this wave (none: 0 or less)
+    in_batches(groups, logits);
+    __syncthreads();
     float s[kTurns][NH];
 #pragma unroll
     for (int t = 0; t < kTurns; ++t) {
       const int at = t * THREADS + 64 * wave;                // this wave's 64 tokens
-      if (at < n) {
-#pragma unroll
-        for (int c = 0; c < kQuads; c += kBatch) {
-          float kf[kBatch][4];
-#pragma unroll
-          for (int u = 0; u < kBatch; ++u)
-            Quad<float>::load(kr + (int64_t)min(at + (c + u) * kTokens + token, n - 1) * kv_stride, kf[u]);
-#pragma unroll
-          for (int u = 0; u < kBatch; ++u)
-#pragma unroll
-            for (int i = 0; i < NH; ++i) {
-              float d = q4[i][0] * kf[u][0];
-#pragma unroll
-              for (int e = 1; e < 4; ++e) d += q4[i][e] * kf[u][e];
-              d = kQuads == 16 ? row_sum(d) : half_wave_sum(d);
-              if (quad == 0) slog[i][at + (c + u) * kTokens + token] = d;
-            }
-        }
-      }
 #pragma unroll
       for (int i = 0; i < NH; ++i) {
-        s[t][i] = at + lane < n ? slog[i][at + lane] : -INFINITY;       // (written by this wave)
+        s[t][i] = at + lane < n ? slog[i][at + lane] : -INFINITY;
         const float mx = wave_max(s[t][i]);
         if (lane == 0) redm[i][at / 64] = mx;
       }
@@ -265,14 +281,13 @@ __global__ __launch_bounds__(THREADS) void attn_generic_f32(AttnArgs a) {
 #pragma unroll
     for (int t = 0; t < kTurns; ++t) {
       const int slice = slice0 + t * (THREADS / kQuads);
+      auto values = [&](int u0, auto n_c) {
+        constexpr int N = decltype(n_c)::value;
+        float vf[N][4];
 #pragma unroll
-      for (int u0 = 0; u0 < kVals; u0 += kBatch) {
-        if (slice + u0 * kSlices >= n) break;
-        float vf[kBatch][4];
+        for (int u = 0; u < N; ++u) load4(vr, min(slice + (u0 + u) * kSlices, n - 1), vf[u]);
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) Quad<float>::load(vr + (int64_t)min(slice + (u0 + u) * kSlices, n - 1) * kv_stride, vf[u]);
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
+        for (int u = 0; u < N; ++u) {
           const int jj = slice + (u0 + u) * kSlices;
           if (jj < n) {
 #pragma unroll
@@ -283,7 +298,8 @@ __global__ __launch_bounds__(THREADS) void attn_generic_f32(AttnArgs a) {
             }
           }
         }
-      }
+      };
+      in_batches((n + kSlices - 1) / kSlices, values);
     }
   }
 #pragma unroll

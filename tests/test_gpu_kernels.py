@@ -792,3 +792,28 @@ def test_f32_attention_by_lanes(H, Hkv, D, T, many):
         assert float((o[lo:hi].double() - ref).abs().max()) < 1e-5
         want, got = torch.logsumexp(s, -1).transpose(0, 1), lse[lo:hi].double()
         assert bool((((got - want).abs() < 1e-5) | ((want == -math.inf) & (got == -math.inf))).all())
+
+
+@pytest.mark.parametrize("H,Hkv,D", [(4, 2, 64), (3, 3, 64), (8, 2, 128), (5, 1, 128)])
+@pytest.mark.parametrize("T", [1, 5, 63, 64, 65, 200, 511, 513, 1100])
+def test_f32_attention_has_one_order_of_sums(H, Hkv, D, T):
+    """A row has the same bits in a call of 7 rows (512 threads to a workgroup) as among 600 (256 threads), whatever share of a tile's
+    tokens a wave gets."""
+    say(f"f32 attention, 7 rows and 600, H={H}/{Hkv} D={D} T={T}")
+    g = gen(92)
+    n = 600
+    q = torch.randn((n, H, D), generator=g, device=DEV)
+    k, v = (torch.randn((T, Hkv, D), generator=g, device=DEV) for _ in range(2))
+    pos = torch.randint(0, T, (n,), generator=g, device=DEV).int()
+    pos[0], pos[1], pos[2] = 0, T - 1, T + 7
+    desc = qb.make_desc(inputs.LayerShape(256, H, Hkv, D, 10000.0, "f32"))
+    off = lambda rows: torch.tensor([0, rows], dtype=torch.int64, device=DEV)
+
+    def attend(rows):
+        o, lse = torch.full((rows, H, D), 7.0, device=DEV), torch.full((rows, H), 7.0, device=DEV)
+        qb.qcf_recompute_attn(desc, 1, q[:rows].contiguous(), pos[:rows].contiguous(), off(rows), rows, k, v, off(T), T, None, o, lse)
+        torch.cuda.synchronize()
+        return o, lse
+
+    for few, many in zip(attend(7), attend(n)):
+        assert torch.equal(few.view(torch.int32), many[:7].view(torch.int32))
