@@ -147,17 +147,22 @@ inline size_t workspace(const qcf_layer_desc& L, int32_t B, int64_t total_probe,
 // Where a scoring call is followed by the selection over the same tokens, the selection's workgroup adds up the last sums itself: the
 // KV heads' column sums of the two passes, or the generic path's probability rows.  One request, and no more to read than one
 // compute unit gets through in about the time of the launch that it saves (some 100 KB a microsecond): 192 KB, of the generic
-// path up to 512 tokens, where a token's rows are shared by two threads at least.  Whole layers, us, with the launch and without:
-// heads of 64 (8 KV heads), 40 probe rows over 256 tokens 45.7 and 42.8, 1024 54.3 and 51.4, 4096 (128 KB) 89.3 and 87.1; heads of
-// 128, 100 over 300 64.5 and 61.1, 4096 134.1 and 131.7; f32, 4 heads, 24 rows over 512 (192 KB) 32.0 and 30.4, 8 over 64 32.7 and
-// 30.5.  The other side of the line: f32, 20 over 600 34.6 and 37.5, 8 over 1000 43.2 and 46.5.
+// path up to 512 tokens, where a token's rows are shared by two threads at least, and beyond 128 tokens up to the 96 rows that are on
+// their way at once.  Whole layers, us, with the launch and without, in a captured graph: heads of 64 (8 KV heads), 40 probe rows
+// over 256 tokens 45.7 and 42.8, 1024 55.4 and 52.7, 4096 (128 KB) 96.1 and 93.2; heads of 128, 100 over 300 64.5 and 61.1; f32, 4 heads,
+// 20 rows over 64 23.2 and 21.9, 96 over 128 (192 KB) 27.8 and 27.4, 24 over 200 26.0 and 25.5.  The other side of the line: heads of
+// 64, 6000 tokens (192 KB, and eight tokens to a thread) 139.9 and 149.4, 8192 201.3 and 212.8; f32, 8 heads, 20 rows over 300 (160 rows)
+// 32.0 and 34.9, 4 heads, 36 over 180 (144) 26.1 and 26.6; 20 over 600 34.6 and 37.5.  Just inside it, f32 of 300 to 512 tokens and 80 to 96
+// rows, a graph is slower (4 heads, 20 over 512 28.9 and 30.1), calls that the host enqueues take the same (31.5 and 31.5).
 enum SumsOf { kNoSums, kHeads, kRows };
 constexpr int kSumTokens = 4096, kSumRowTokens = 512;
+constexpr int kSumFewTokens = 128, kSumRows = 96;
 constexpr size_t kSumBytes = (size_t)192 << 10;
 inline SumsOf sums_in_selection(const qcf_layer_desc& L, int32_t B, int64_t total_probe, int64_t total_ctx) {
   if (B != 1 || total_probe <= 0 || total_ctx <= 0 || total_ctx > kSumTokens || use_fused(L, B, total_probe, total_ctx)) return kNoSums;
   if (use_two_pass(L, B, total_probe, total_ctx)) return (size_t)L.n_kv_heads * total_ctx * sizeof(float) <= kSumBytes ? kHeads : kNoSums;
-  return total_ctx <= kSumRowTokens && generic_ws(L, total_probe, total_ctx) <= kSumBytes ? kRows : kNoSums;
+  if (total_ctx > kSumRowTokens || (total_ctx > kSumFewTokens && total_probe * L.n_q_heads > kSumRows)) return kNoSums;
+  return generic_ws(L, total_probe, total_ctx) <= kSumBytes ? kRows : kNoSums;
 }
 
 // Layers scored by one set of launches: as many as keep the workspace within that of a single call, or 64 MiB.  One where

@@ -384,8 +384,10 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
 }
 
 // Selection of one request whose scores its workgroup adds up first, in the order of the scoring's own kernels and with their bits,
-// so that no launch of a few workgroups stands between the two.  Bound by the latency of its loads (f32, 80 rows over 512
-// tokens: 7.6 us, 3.5 and 4.0 in two launches and what lies between; with one share of the rows after the other 8.4).
+// so that no launch of a few workgroups stands between the two.  Probability rows: bound by the latency of their loads, up to 48 of a thread
+// on their way; shares that a thread does not have and rows that a share does not have are left out, at the sizes below (with
+// room for four shares of twelve rows each, always: whole layers of f32, 4 heads, 8 probe rows over 64 tokens 24.6 us, so 21.5, 96 over
+// 128 37.0 and 27.4, 24 over 256 27.6 and 25.1; in two launches 23.0, 27.8 and 25.5).
 constexpr int kShares = 8;                   // of the probability rows, one after the other (as in the kernel that adds them alone)
 template <int MAX, bool ROWS>
 __global__ __launch_bounds__(kThreads) void select_sums_kernel(ScoreSums a, float* __restrict__ score, const int64_t* __restrict__ ctx_off,
@@ -406,12 +408,14 @@ __global__ __launch_bounds__(kThreads) void select_sums_kernel(ScoreSums a, floa
   };
   if constexpr (ROWS) {
     float* part = reinterpret_cast<float*>(lds.list);            // [share][token]
-    static_assert(kShares * scoring::kSumRowTokens <= kStage, "within the list");
+    static_assert(kShares * scoring::kSumRowTokens <= kStage && kThreads / scoring::kSumRowTokens * 4 == kShares, "within the list; the widest have two groups");
     int width = 64;                                              // tokens side by side; the threads behind them take other shares
     while (width < total) width *= 2;
     const int j = tid % width, groups = kThreads / width, r0 = (int)(p0 * a.H), r1 = (int)(p1 * a.H), share = (r1 - r0 + kShares - 1) / kShares;
-    constexpr int S = 4, R = 12;                                 // shares, and rows of each, on their way together
-    for (int w0 = tid / width; w0 < kShares; w0 += S * groups) {
+    const int group = __builtin_amdgcn_readfirstlane(tid / width), at = min(j, total - 1);       // (a wave is in one group)
+    // S shares, and R rows of each, on their way together; row numbers are a wave's, so that a load costs no vector instruction more
+    auto add = [&](auto s_c, auto r_c) {
+      constexpr int S = decltype(s_c)::value, R = decltype(r_c)::value;
       float acc[S];
 #pragma unroll
       for (int i = 0; i < S; ++i) acc[i] = 0.f;
@@ -420,18 +424,28 @@ __global__ __launch_bounds__(kThreads) void select_sums_kernel(ScoreSums a, floa
 #pragma unroll
         for (int i = 0; i < S; ++i)
 #pragma unroll
-          for (int u = 0; u < R; ++u)
-            p[i][u] = a.sums[(int64_t)max(min(r0 + (w0 + i * groups) * share + r + u, r1 - 1), 0) * total + min(j, total - 1)];
+          for (int u = 0; u < R; ++u) p[i][u] = (a.sums + max(min(r0 + (group + i * groups) * share + r + u, r1 - 1), 0) * total)[at];
 #pragma unroll
         for (int i = 0; i < S; ++i) {
-          const int first = r0 + (w0 + i * groups) * share + r, last = min(first - r + share, r1);
+          const int first = r0 + (group + i * groups) * share + r, last = min(first - r + share, r1);
 #pragma unroll
           for (int u = 0; u < R; ++u) acc[i] += first + u < last ? p[i][u] : 0.f;
         }
       }
 #pragma unroll
       for (int i = 0; i < S; ++i)
-        if (j < total && w0 + i * groups < kShares) part[(w0 + i * groups) * total + j] = acc[i];
+        if (j < total) part[(group + i * groups) * total + j] = acc[i];
+    };
+    auto of_shares = [&](auto s_c) {
+      if (share <= 4) add(s_c, std::integral_constant<int, 4>{});
+      else if (share <= 8 || (share > 12 && share <= 16)) add(s_c, std::integral_constant<int, 8>{});
+      else if (share <= 10) add(s_c, std::integral_constant<int, 10>{});
+      else add(s_c, std::integral_constant<int, 12>{});
+    };
+    if (group < kShares) {
+      if (groups >= kShares) of_shares(std::integral_constant<int, 1>{});
+      else if (2 * groups == kShares) of_shares(std::integral_constant<int, 2>{});
+      else of_shares(std::integral_constant<int, 4>{});
     }
     __syncthreads();
     if (tid < total) {

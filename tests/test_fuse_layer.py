@@ -404,3 +404,23 @@ def test_last_sums_in_the_selection(lens, kw, kind):
         res.append([getattr(L, name).clone() for name in OUTS])
     for name, a, b in zip(OUTS, *res):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T", [63, 64, 100, 128, 129, 256, 257, 500])
+@pytest.mark.parametrize("R", [1, 8, 9, 16, 17, 20, 24, 25, 32, 40, 90])
+def test_last_sums_in_every_width(T, R):
+    """The probability rows of 4 heads, in eight shares of 1 to 45 rows, by workgroups that have 64 to 512 tokens side by side; beyond 128
+    tokens 96 rows at most."""
+    print(f"sums in the selection, {R} probe rows over {T} tokens", flush=True)
+    L = _layer([T], [0], style=0, **dict(F32, R=R))
+    assert host_rules.sums_in_selection(L) == (2 if T <= 128 or R <= 24 else 0)
+    res = []
+    for run in (lambda: [fn(L) for _, fn in pipeline.FUSED_STEPS], lambda: pipeline.enqueue_layer(L)):
+        for name in OUTS:
+            getattr(L, name).fill_(1)
+        run()
+        torch.cuda.synchronize()
+        res.append([getattr(L, name).clone() for name in OUTS])
+    for name, a, b in zip(OUTS, *res):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
