@@ -1337,6 +1337,9 @@ qcf_status launch_two_pass(const qcf_layer_desc& L, const ScoreArgs& a, int n_la
                            const void* const* k, const float* alpha, void* ws, hipStream_t st, ScoreSums* left = nullptr,
                            const Rerotation* r = nullptr) {
   const PassWs w = pass_ws(L, n_layers, a.B, a.total_probe, a.total_ctx);
+  // (nothing has been enqueued: a call that asks for a re-rotation which this would leave out must not go on without it)
+  if (r && !pass1_rerotates(L, w.unit_tiles, n_layers, a.probe_limit != nullptr))
+    return fail(QCF_ERR_UNSUPPORTED, "score: no re-rotation in units of %d tiles, %d layers, heads of %d", w.unit_tiles, n_layers, L.head_dim);
   if (w.n_units * n_layers * a.Hkv > 0x7fffffff) return fail(QCF_ERR_UNSUPPORTED, "score: grid too large");
   PassArgs pa;
   pa.s = a;

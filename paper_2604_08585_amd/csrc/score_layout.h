@@ -118,15 +118,19 @@ inline bool takes_rerope(const qcf_layer_desc& L, int32_t B, int32_t n_chunks, i
   return B == 1 && n_chunks > 0 && n_chunks <= kMaxRotChunks && n_chunks * (int64_t)kTokPerWg <= kRotChunksPerTile * total_ctx + kTokPerWg &&
          use_fused(L, B, total_probe, total_ctx);
 }
+// what the kernel of pass 1 that re-rotates is made for
+inline bool pass1_rerotates(const qcf_layer_desc& L, int unit_tiles, int n_layers, bool limit) {
+  return L.head_dim == 64 && unit_tiles == 1 && n_layers == 1 && L.n_kv_heads <= 65535 && !limit;
+}
 // Re-rotation inside pass 1: heads of 64, one request in units of one tile that all start at once, chunks as above.  Layers
 // of 32 / 8 heads, us, re-rotation as a launch and so: 8000 tokens (250 units) 178.7 and 177.1, 90 38.3 and 35.9, 4160 in 64 chunks
 // 90.7 and 88.2, 900 in 60 (17 to a tile) 53.3 and 52.4.  Beyond the line nothing is gained: 12000 tokens (376 units) 321.7 and
 // 321.0, 960 in 120 chunks (32 to a tile) 52.9 both ways.
 inline bool pass1_takes_rerope(const qcf_layer_desc& L, int32_t B, int32_t n_chunks, int64_t total_probe, int64_t total_ctx) {
-  return B == 1 && L.head_dim == 64 && n_chunks > 0 && n_chunks <= kMaxRotChunks && total_probe > 0 && total_ctx > 0 &&
+  return B == 1 && n_chunks > 0 && n_chunks <= kMaxRotChunks && total_probe > 0 && total_ctx > 0 &&
          n_chunks * (int64_t)kTokPerWg <= kRotChunksPerTile * total_ctx + kTokPerWg && use_mfma(L) &&
          use_two_pass(L, B, total_probe, total_ctx) && n_tiles_upper(B, total_ctx) * L.n_kv_heads <= compute_unit_count() &&
-         pass_ws(L, 1, B, total_probe, total_ctx).unit_tiles == 1;
+         pass1_rerotates(L, pass_ws(L, 1, B, total_probe, total_ctx).unit_tiles, 1, false);
 }
 struct FusedWs { size_t part, colpart, total; };
 inline FusedWs fused_ws(const qcf_layer_desc& L, int32_t B, int64_t total_ctx) {

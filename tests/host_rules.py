@@ -35,6 +35,12 @@ extern "C" int takes_rerope(const qcf_layer_desc* L, int B, int n_chunks, long l
 extern "C" int pass1_takes_rerope(const qcf_layer_desc* L, int B, int n_chunks, long long probes, long long tokens) {
   return qcf::scoring::pass1_takes_rerope(*L, B, n_chunks, probes, tokens);
 }
+extern "C" int pass1_rerotates(const qcf_layer_desc* L, int unit_tiles, int n_layers, int limit) {
+  return qcf::scoring::pass1_rerotates(*L, unit_tiles, n_layers, limit);
+}
+extern "C" int unit_tiles(const qcf_layer_desc* L, int B, long long probes, long long tokens) {
+  return qcf::scoring::pass_ws(*L, 1, B, probes, tokens).unit_tiles;
+}
 extern "C" int sums_in_selection(const qcf_layer_desc* L, int B, long long probes, long long tokens) {
   return qcf::scoring::sums_in_selection(*L, B, probes, tokens);
 }
@@ -103,6 +109,16 @@ def rerotates_in_scoring(L):
 def rerotates_in_pass1(L):
     """Whether a scored pipeline.DeviceLayer with heads of 64 is re-rotated by the first pass of its scoring (csrc/score_layout.h)."""
     return bool(_library().pass1_takes_rerope(C.byref(L.desc), L.B, L.n_chunks, C.c_longlong(L.total_probe), C.c_longlong(L.total_ctx)))
+
+
+def pass1_rerotates(desc, unit_tiles, layers, limit):
+    """Whether the first scoring pass has a kernel that re-rotates for launches of this form, whoever asks for it (csrc/score_layout.h)."""
+    return bool(_library().pass1_rerotates(C.byref(desc), unit_tiles, layers, int(limit)))
+
+
+def unit_tiles(desc, B, probes, tokens):
+    """Tiles to a unit of the two scoring passes over one layer."""
+    return _library().unit_tiles(C.byref(desc), B, C.c_longlong(probes), C.c_longlong(tokens))
 
 
 def sums_in_selection(L):

@@ -378,6 +378,24 @@ def test_a_projection_has_one_order_of_sums(dm, H, Hkv, D):
     assert beside > 100
 
 
+def test_re_rotation_is_refused_where_pass_1_would_leave_it_out():
+    """launch_two_pass goes by the same rule as the layer call: one tile to a unit, one layer, heads of 64, no limits."""
+    desc = lambda D, H=32, Hkv=8: qb.make_desc(inputs.LayerShape(2048, H, Hkv, D, 500000.0, "bf16"))
+    assert host_rules.pass1_rerotates(desc(64), 1, 1, False)
+    assert not any([host_rules.pass1_rerotates(desc(64), 2, 1, False), host_rules.pass1_rerotates(desc(64), 1, 2, False),
+                    host_rules.pass1_rerotates(desc(128), 1, 1, False), host_rules.pass1_rerotates(desc(64), 1, 1, True)])
+    taken = 0
+    for H, Hkv in ((32, 8), (8, 1), (16, 16), (4, 2)):
+        for tokens in list(range(1, 1200, 37)) + list(range(1200, 40000, 1111)):
+            for probes in (1, 24, 80, 400):
+                L = pipeline.DeviceLayer.__new__(pipeline.DeviceLayer)
+                L.desc, L.B, L.n_chunks, L.total_probe, L.total_ctx = desc(64, H, Hkv), 1, 1, probes, tokens
+                if host_rules.rerotates_in_pass1(L):
+                    taken += 1
+                    assert host_rules.unit_tiles(L.desc, 1, probes, tokens) == 1
+    assert taken > 200
+
+
 F32 = dict(dtype="f32", H=4, Hkv=2, D=64, R=20)
 
 
