@@ -45,9 +45,10 @@ typedef struct qcf_layer_buffers {
 /* qcf_rerope, at the critical layer qcf_score and qcf_select, qcf_recompute_qkv_scatter and qcf_recompute_attn, one after the
  * other: same results, arguments checked call by call.  A call that fails ends the layer; what is in front of it has been
  * enqueued.  Launches may be joined.  At the critical layer: where qcf_score is the one kernel whose workgroups wait for each
- * other, so is its part here, and the keys and values of one request are re-rotated by that kernel, or with heads of 64 by the first
- * pass of two (up to 128 chunks, not of a few tokens each); the last sums of the scores may be the selection's.  At the other layers: the cache rows, or a part of them, are re-rotated by workgroups behind those of the
- * projection, on the compute units that it leaves idle (bf16, up to 256 chunks); rows that the projection writes are left to it. */
+ * other, so is its part here, and the keys and values of one request are re-rotated by that kernel, or with heads of 64 by the
+ * first pass of two (up to 128 chunks, not of a few tokens each); the last sums of the scores may be the selection's.  At the other
+ * layers: the cache rows, or a part of them, are re-rotated by workgroups behind those of the projection, on the compute units that
+ * it leaves idle (bf16, up to 256 chunks); rows that the projection writes are left to it. */
 qcf_status qcf_fuse_layer(const qcf_layer_desc* desc, const qcf_layer_buffers* layer, int32_t critical, void* stream);
 
 #ifdef __cplusplus

@@ -417,7 +417,8 @@ def qcf_extract_anchors(desc: LayerDesc, k: torch.Tensor, v: torch.Tensor, ctx_o
     if workspace is None:
         workspace = _workspace(int(lib.qcf_extract_anchors_workspace_bytes(C.byref(desc), n, int(ctx_off[n]))), k.device)
     wp, wn = _ws_args(workspace)
-    _check(lib.qcf_extract_anchors(C.byref(desc), _ptr(k), _ptr(v), n, ctx_off.ctypes.data, sel_off.ctypes.data, _ptr(rows), _ptr(k_out), _ptr(v_out), wp, wn, _stream()))
+    _check(lib.qcf_extract_anchors(C.byref(desc), _ptr(k), _ptr(v), n, ctx_off.ctypes.data, sel_off.ctypes.data, _ptr(rows),
+                                   _ptr(k_out), _ptr(v_out), wp, wn, _stream()))
 
 
 def qcf_key_norm(desc: LayerDesc, k: torch.Tensor, rows: int, norm: torch.Tensor) -> None:

@@ -394,8 +394,8 @@ qcf_status qcf_recompute_attn(const qcf_layer_desc* desc, int32_t B, const void*
 qcf_status qcf_fuse_layer(const qcf_layer_desc* desc, const qcf_layer_buffers* layer, int32_t critical, void* stream) {
   if (!layer) return fail(QCF_ERR_INVALID_ARG, "layer buffers are NULL");
   const qcf_layer_buffers& b = *layer;
-  // One request in the single scoring kernel, or in pass 1 of two: it turns the keys itself.  (Only where scoring will not fail: the cache is whole
-  // otherwise.)
+  // One request in the single scoring kernel, or in pass 1 of two: it turns the keys itself.  (Only where scoring will not fail:
+  // the cache is whole otherwise.)
   bool empty = false;
   QCF_TRY(check_rerope_args(desc, b.chunks_dev, b.n_chunks, b.total_ctx, b.k_fused, b.v_fused, b.rerope_ws, b.rerope_ws_bytes));
   const bool joined = critical && b.total_ctx > 0 && b.v_fused &&

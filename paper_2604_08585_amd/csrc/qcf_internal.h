@@ -274,9 +274,11 @@ struct ScoreSums {
 };
 qcf_status launch_score(const qcf_layer_desc& L, int32_t B, const void* q, const int64_t* probe_off,
                         int64_t total_probe, const void* k, const int64_t* ctx_off, int64_t total_ctx,
-                        const int32_t* probe_limit, float* score, float alpha, float beta, void* ws, hipStream_t st, ScoreSums* left = nullptr);
+                        const int32_t* probe_limit, float* score, float alpha, float beta, void* ws, hipStream_t st,
+                        ScoreSums* left = nullptr);
 
-// re-rotation and scoring of one request in one launch, where scoring::takes_rerope
+// re-rotation and scoring of one request: in one launch where scoring::takes_rerope, the re-rotation inside the first of the two
+// passes (two launches, three where the last sums are not left to the selection) where scoring::pass1_takes_rerope
 qcf_status launch_rerope_score(const qcf_layer_desc& L, const qcf_chunk* chunks, int32_t n_chunks, const void* q,
                                const int64_t* probe_off, int64_t total_probe, void* k, void* v, const int64_t* ctx_off,
                                int64_t total_ctx, float* score, void* ws, hipStream_t st, ScoreSums* left);
@@ -292,9 +294,10 @@ qcf_status launch_select(int32_t B, const float* score, const int64_t* ctx_off, 
                          int32_t* sel_idx, int32_t* sel_row, int32_t* sel_pos, void* ws,
                          hipStream_t st);
 
-// Top-N of every chunk and the gather of its key and value rows; the offsets are host arrays
+// the last sums of a scoring (launch_score with `left`), its scores and the selection over them; the offsets are device arrays
 qcf_status launch_select_sums(const ScoreSums& sums, float* score, const int64_t* ctx_off, int64_t total_ctx, const int64_t* sel_off,
                               int64_t total_sel, int32_t* sel_idx, int32_t* sel_row, int32_t* sel_pos, hipStream_t st);
+// Top-N of every chunk and the gather of its key and value rows; the offsets are host arrays
 qcf_status launch_select_gather(const qcf_layer_desc& L, const float* score, int32_t n_chunks, const int64_t* ctx_off,
                                 const int64_t* sel_off, const void* k, const void* v, int32_t* rows, void* k_out, void* v_out,
                                 hipStream_t st);

@@ -629,7 +629,6 @@ struct SideLds {
   int first, last;                                // chunks of the first and the last row
   float2 cs[(kSideRows + 1) * 64];
 };
-static_assert(sizeof(SideLds) <= 128 * 1024, "within the ring of every tile");
 template <int NTHR>
 __device__ __forceinline__ void rerope_rows(const QkvArgs& a, int64_t r0, int n, unsigned char* smem) {
   SideLds& l = *reinterpret_cast<SideLds*>(smem);
@@ -708,6 +707,7 @@ __device__ __forceinline__ void rerope_rows(const QkvArgs& a, int64_t r0, int n,
 // WIDE: x is 4 GiB or larger (64-bit addresses per lane instead of 32-bit offsets)
 template <typename C, int EPI, bool WIDE>
 __global__ __launch_bounds__(C::NTHR) void qkv_ws_kernel(QkvArgs a) {
+  static_assert(sizeof(SideLds) <= C::LDS_MAIN, "the re-rotation works in the ring");
   constexpr int TM = C::TM, TN = C::TN, S = C::S;
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -881,8 +881,9 @@ __global__ __launch_bounds__(C::NTHR) void qkv_ws_kernel(QkvArgs a) {
 // Sums the partial results of a split contraction, in range order, and finishes them.  One workgroup per 32 rows x 64 columns of a
 // block: the two 32-column parts that hold the halves of rotary pairs, gate and up, or else neighbours, so that a thread
 // has both partners of its eight sums and finishes them itself; the results pass through LDS to leave as 16-byte pieces.  Bound by
-// latency where rows are few: launch, one round of loads, stores.  (128 columns to a workgroup, finished by its first wave alone: calls of 61 rows, K 4096, N 4096 in
-// six ranges 15.2 us, now 13.4; 110 rows, K 4096, N 6144 in four 24.6 and 23.2; 200 rows 31.6 and 30.0.)
+// latency where rows are few: launch, one round of loads, stores.  (128 columns to a workgroup, finished by its first wave alone:
+// calls of 61 rows, K 4096, N 4096 in six ranges 15.4 us, now 14.5; 100 rows, K 4096, N 6144 in four 20.3 and 19.7; 200 rows 26.6
+// and 26.0.)
 template <int EPI>
 __global__ __launch_bounds__(256) void qkv_split_reduce(QkvArgs a, int n_groups) {
   constexpr int LD = 68;                                         // floats of a row (an odd number of 16-byte pieces)

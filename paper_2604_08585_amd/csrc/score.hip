@@ -409,6 +409,7 @@ __device__ __forceinline__ bool locate_unit(const PassArgs& a, Unit& u) {
 
 constexpr int kTilesPerWave = (kRowBlock / 32 + kRowGroups - 1) / kRowGroups;      // row tiles of a wave, at most
 
+// Re-rotation inside a scoring kernel (RR): the chunks whose keys and values make up the cache that s.k points to.
 struct Rerotation {
   const qcf_chunk* chunks;
   int n_chunks, style;
@@ -870,7 +871,6 @@ constexpr uint32_t kSpinLimit = 1u << 20;  // polls (a microsecond or two each) 
 
 __device__ uint32_t g_sync[kSyncSlots * kSyncWords];
 
-// Re-rotation in front of the scoring (RR): the chunks whose keys and values make up the cache that s.k points to.
 struct FusedArgs {
   ScoreArgs s;
   float2* part;        // [tile][Hkv][kRowBlock] (max2, sumexp2) of the tile, published with atomic stores

@@ -408,10 +408,12 @@ __global__ __launch_bounds__(kThreads) void select_sums_kernel(ScoreSums a, floa
   };
   if constexpr (ROWS) {
     float* part = reinterpret_cast<float*>(lds.list);            // [share][token]
-    static_assert(kShares * scoring::kSumRowTokens <= kStage && kThreads / scoring::kSumRowTokens * 4 == kShares, "within the list; the widest have two groups");
+    static_assert(kShares * scoring::kSumRowTokens <= kStage, "within the list");
+    static_assert(kThreads / scoring::kSumRowTokens * 4 == kShares, "four shares to a thread at most");
     int width = 64;                                              // tokens side by side; the threads behind them take other shares
     while (width < total) width *= 2;
-    const int j = tid % width, groups = kThreads / width, r0 = (int)(p0 * a.H), r1 = (int)(p1 * a.H), share = (r1 - r0 + kShares - 1) / kShares;
+    const int j = tid % width, groups = kThreads / width;
+    const int r0 = (int)(p0 * a.H), r1 = (int)(p1 * a.H), share = (r1 - r0 + kShares - 1) / kShares;
     const int group = __builtin_amdgcn_readfirstlane(tid / width), at = min(j, total - 1);       // (a wave is in one group)
     // S shares, and R rows of each, on their way together; row numbers are a wave's, so that a load costs no vector instruction more
     auto add = [&](auto s_c, auto r_c) {
