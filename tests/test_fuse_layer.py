@@ -252,9 +252,8 @@ def test_chunks_turned_in_place(D):
     ([257], [0], dict(H=16, Hkv=4, src0=9)),
     ([3000, 9001], [0, 7], dict(dm=1024, N=1500)),               # several tiles of rows, workgroups with more than one block
     ([4000, 4192], [0, 0], dict(dm=4096, H=32, Hkv=8, N=620)),   # 16 compute units to spare: a part of the rows
-    ([20, 21], [0, 0], dict(D=64, Hkv=4)), ([2], [0], {}),
-    ([350], [0], dict(dm=1536, H=12, Hkv=2, N=70))],             # a contraction in ranges
-    ids=["two", "256 chunks", "257 chunks", "gaps", "edges", "long", "part", "heads of 64", "one", "ranges"])
+    ([20, 21], [0, 0], dict(D=64, Hkv=4)), ([2], [0], {})],
+    ids=["two", "256 chunks", "257 chunks", "gaps", "edges", "long", "part", "heads of 64", "one"])
 def test_rerotation_beside_the_projection(lens, gaps, kw, style):
     print(f"re-rotation beside the projection {kw} style={style}", flush=True)
     L = _layer(lens, gaps, R=4, style=style, **kw)
@@ -281,6 +280,13 @@ def test_rerotation_beside_the_projection(lens, gaps, kw, style):
         res.append([getattr(L, name).clone() for name in OUTS])
     for name, a, b in zip(OUTS, *res):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("style", [0, 1])
+def test_rerotation_beside_a_projection_in_ranges(style):
+    """A projection whose contraction is cut into ranges with the cache re-rotated beside it, and the same without."""
+    test_rerotation_beside_the_projection([350], [0], dict(dm=1536, H=12, Hkv=2, N=70), style)
 
 
 @pytest.mark.gpu
